@@ -1,0 +1,266 @@
+// Matrix-product step kernel: wide bf16 steps whose input is a plain row-major matrix, more than a row tile of it.
+// Part of the tn_linear library's single translation unit: included by tn_linear.hip inside its
+// anonymous namespace, after kernels/tiled.hpp.
+#pragma once
+
+// ---------------------------------------------------------------------------------------------
+// Out[r][c] = sum_k A[r][k] * B[c][k], A row-major with K % 64 == 0, B packed fragment-major, output through the
+// step's scatter tables in aligned pieces of 8 columns (TRANS = 0) or of 8 rows (TRANS = 1).
+//
+// What bounds it: on large shapes the power the chip may draw. With every wait hidden the clock settles at what the
+// energy of a K tile allows, so what counts is energy per product (measured at 8192 x 8192 x 5120):
+//   * v_mfma_f32_16x16x32_bf16 instead of 32x32x16: half the accumulator traffic per product. The same loop ran at
+//     1.99 GHz instead of 1.72 (1.52 instead of 1.42 PFLOP/s without its stores);
+//   * four waves, each a quarter (up to 128 x 128) of the tile, instead of eight: 64 instead of 96 KB of fragments read
+//     from LDS per 32 k. One wave per SIMD then has to keep its matrix core busy alone, so the order of the loop is
+//     written out: one LDS read or one direct-to-LDS load at a time between two MFMAs (bunched, 1.33 PFLOP/s; one by
+//     one, 1.58, without stores);
+//   * both operands go from memory to LDS without passing through registers. A row of a stage is 128 bytes (64 k),
+//     and its 16-byte chunk c sits at position c ^ ((row / 2) % 8), so that the 16 rows a read touches at a time
+//     fall on 16 different slots of the 64 banks (with c ^ (row % 8) 40 % of the LDS cycles were conflicts); B's
+//     packed blocks lie in fragment order already and are copied as they are.
+// Two stages of 64 k: the second half of a K tile (its fragments are in registers by then) frees the stage, one
+// barrier per tile lets the loads of the tile after the next into it, and they have a whole tile to arrive.
+// The sums leave straight from registers: two lane swaps turn the accumulator layout (4 consecutive values per lane)
+// into 16-byte pieces of 64-byte runs, with no second trip through LDS; the output offsets of the tile's rows and
+// columns are fetched into LDS when the tile starts.
+// 8192 x 8192 x 5120 in 467 us = 1.47 PFLOP/s (the 256 x 256 ping-pong kernel this replaces: 565 us), 8192 x 9216 x
+// 2304 in 260 us (340).
+//
+// Tile sizes: 32*TM x 32*TN, TM <= 8, TN 8 or 4; the host picks the one (and the number of K ranges) with the least
+// time by gemm_choice. XCD x takes a contiguous eighth of the tiles in bands of four row tiles (row fastest), so that
+// the 32 tiles an XCD runs at a time share 4 + 8 operand panels in its L2 and no XCD has a row tile more than another
+// (dealing whole row tiles to XCDs left 2500 rows at 10 tiles over 8 XCDs: 281 us, now 160).
+// ---------------------------------------------------------------------------------------------
+struct GemmArgs {
+    int32_t n_row, n_col;          // output tiles
+    int32_t n_split;               // ranges of K; more than one: fp32 partial sums [split][rows_pad][Cp] (TRANS = 0)
+    int32_t ktiles_per_split;      // K tiles of 64 per range, at least one in every range
+    int64_t rows_pad;
+    float* partial;
+};
+
+template <int TM, int TN>
+struct GemmShape {
+    static constexpr int BM = 32 * TM, BN = 32 * TN;
+    static constexpr int STAGE_BYTES = (BM + BN) * 128;
+    static constexpr int TAB_ROWS = (BM + 63) / 64 * 64;                 // crow of the tile's rows, ccol of its columns: 64 entries per load
+    static constexpr size_t SMEM = size_t(2) * STAGE_BYTES + size_t(TAB_ROWS + BN) * 4;
+};
+
+template <int TM, int TN, int TRANS>
+__global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs g) {
+#ifdef __HIP_DEVICE_COMPILE__
+    using S = GemmShape<TM, TN>;
+    constexpr int NW = 4, BM = S::BM, BN = S::BN, STAGE = S::STAGE_BYTES, A_BYTES = BM * 128;
+    constexpr int L = TM + TN;                           // 1 KB direct-to-LDS loads per wave and stage: TM of A, then TN of B
+    static_assert(TN % 2 == 0 && (!TRANS || TM % 2 == 0), "stores pair neighbouring tiles");
+    typedef __attribute__((address_space(3))) void lds_t;
+    typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 1, wn = wave & 1;
+
+    // workgroup -> (tile, range of K): see above
+    int row_tile, col_tile, split;
+    {
+        constexpr int BAND = 4;
+        const int n_items = g.n_row * g.n_col * g.n_split, xcd = blockIdx.x & 7;
+        const int item = int(int64_t(n_items) * xcd >> 3) + int(blockIdx.x >> 3);
+        if (item >= int(int64_t(n_items) * (xcd + 1) >> 3)) return;
+        const int tile = item / g.n_split;
+        split = item - tile * g.n_split;
+        const int band = tile / (BAND * g.n_col), in_band = tile - band * (BAND * g.n_col);
+        const int band_rows = min(BAND, g.n_row - band * BAND);
+        col_tile = in_band / band_rows;
+        row_tile = band * BAND + in_band - col_tile * band_rows;
+    }
+    const uint32_t row0 = uint32_t(row_tile) * BM;
+    const int col0 = col_tile * BN, nks = a.Kp >> 4;
+    const int kt0 = split * g.ktiles_per_split;
+    const int nk = min(a.Kp >> 6, kt0 + g.ktiles_per_split) - kt0;       // >= 1
+
+    // rows past the end read as zeros (bounds of the buffer)
+    const int row_bytes = a.K * 2;
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(static_cast<const bf16_t*>(a.A) + int64_t(row0) * a.K), 0,
+        int(min(int64_t(a.total_rows) - int64_t(row0), int64_t(BM))) * row_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<bf16_t*>(static_cast<const bf16_t*>(a.B) + int64_t(col0 >> 5) * nks * 512), 0, (BN / 32) * nks * 1024, 0x00020000);
+    // a load of A covers 8 rows x 128 bytes: lane l fills position l%8 of row l/8
+    const int va = (wave * 8 + (lane >> 3)) * row_bytes + (((lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7)) * 16);
+    const int vb = wave * 1024 + lane * 16;              // the four waves bring the four k-step blocks of a column block
+    auto load1 = [&](int j, int kt, unsigned char* s) {
+        if (j < TM)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_t*)(s + (j * NW + wave) * 1024), 16, va,
+                                                     (kt0 + kt) * 128 + j * (NW * 8) * row_bytes, 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_t*)(s + A_BYTES + ((j - TM) * NW + wave) * 1024), 16, vb,
+                                                     (kt0 + kt) * 4096 + (j - TM) * nks * 1024, 0, 0);
+    };
+    // output offsets of the tile's rows and columns; entries past the end repeat a valid one and are not used
+    unsigned char* tab = dyn_smem + 2 * STAGE;
+    {
+        const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.crow), 0, int(a.R) * 4, 0x00020000);
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.ccol), 0, a.C * 4, 0x00020000);
+        if (wave * 64 < S::TAB_ROWS) {
+            const uint32_t r = row0 + wave * 64 + lane;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rr, (lds_t*)(tab + wave * 256), 4, int((a.R == 1 ? 0u : r % a.R) * 4), 0, 0, 0);
+        }
+        if (wave * 64 < BN)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_t*)(tab + S::TAB_ROWS * 4 + wave * 256), 4,
+                                                     min(col0 + wave * 64 + lane, a.C - 1) * 4, 0, 0, 0);
+    }
+#pragma unroll
+    for (int l = 0; l < L; ++l) load1(l, 0, dyn_smem);
+#pragma unroll
+    for (int l = 0; l < L; ++l) load1(l, min(1, nk - 1), dyn_smem + STAGE);
+
+    // fragments: lane l supplies row (A) or column (B) l%16 and k = 32*ks + 8*(l/16) .. +7
+    int oa[2], ob[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+        const int r = lane & 15, c = 4 * ks + (lane >> 4);
+        oa[ks] = (wm * TM * 16 + r) * 128 + ((c ^ ((r >> 1) & 7)) * 16);
+        ob[ks] = A_BYTES + (wn * TN / 2) * 4096 + (2 * ks + (lane >> 5)) * 1024 + ((lane & 15) + 32 * ((lane >> 4) & 1)) * 16;
+    }
+    floatx4 acc[TM][TN];
+    bf16x8 fa[2][TM], fb[2][TN];
+    constexpr int NR = TM + TN;
+    auto read1 = [&](int q, int set, const unsigned char* s, int ks) {       // the columns first: every row of MFMAs needs them all
+        if (q < TN) fb[set][q] = *reinterpret_cast<const bf16x8*>(s + ob[ks] + (q >> 1) * 4096 + (q & 1) * 256);
+        else fa[set][q - TN] = *reinterpret_cast<const bf16x8*>(s + oa[ks] + (q - TN) * 2048);
+    };
+    // One k-step of 32: the MFMAs of one fragment set with the reads of the other and (NL > 0) the loads of a tile dealt
+    // out between them. The reads are done after three quarters of it.
+    auto kstep = [&](int set, const unsigned char* rs, int rks, int kt2, unsigned char* ls, auto n_loads) {
+        constexpr int NL = decltype(n_loads)::value, NM = TM * TN;
+        constexpr int RS = NM * 3 / 4 / NR > 0 ? NM * 3 / 4 / NR : 1, LS = NL && NM / NL > 0 ? NM / NL : 1;
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            const int i = m / TN, j = m % TN;
+            acc[i][j] = TRANS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[set][i], fb[set][j], acc[i][j], 0, 0, 0)
+                              : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
+            if (m % RS == 0 && m / RS < NR) read1(m / RS, set ^ 1, rs, rks);
+            if (NL && m % LS == LS / 2 && m / LS < NL) load1(m / LS, kt2, ls);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int q = (NM + RS - 1) / RS; q < NR; ++q) read1(q, set ^ 1, rs, rks);
+#pragma unroll
+        for (int l = (NM - LS / 2 + LS - 1) / LS; l < NL; ++l) load1(l, kt2, ls);
+    };
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
+            asm volatile("" : "+a"(acc[i][j]));
+        }
+    wait_vmcnt<L>();                                     // the tables and the first K tile have landed
+    __builtin_amdgcn_s_barrier();
+#pragma unroll
+    for (int q = 0; q < NR; ++q) read1(q, 0, dyn_smem, 0);
+    for (int kt = 0; kt < nk; ++kt) {
+        unsigned char* s = dyn_smem + (kt & 1) * STAGE;
+        const unsigned char* sn = dyn_smem + ((kt + 1) & 1) * STAGE;
+        __builtin_amdgcn_sched_barrier(0);
+        kstep(0, s, 1, 0, nullptr, std::integral_constant<int, 0>());
+        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): this wave has read the whole stage
+        wait_vmcnt<0>();                                 // its loads of the next stage have landed
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        // (the last two tiles load the last one again, into a stage nobody reads)
+        kstep(1, sn, 0, min(kt + 2, nk - 1), s, std::integral_constant<int, L>());
+        // keep the accumulators in the accumulation registers across the back edge
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+    }
+    wait_vmcnt<0>();                                     // no load into LDS outlives the workgroup
+
+    if (g.n_split > 1) {
+        // lane: row l%16 of tile i, columns 4*(l/16) .. +3 of tile j
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const uint32_t r = row0 + wm * TM * 16 + i * 16 + (lane & 15);
+            float* p = g.partial + (int64_t(split) * g.rows_pad + r) * a.Cp + col0 + wn * TN * 16 + 4 * (lane >> 4);
+            if (r < a.total_rows) {
+#pragma unroll
+                for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4*>(p + j * 16) = acc[i][j];
+            }
+        }
+        return;
+    }
+    // Offsets in bytes from the tile's first token (checked by the host to fit 31 bits); ~0 is out of bounds: not stored.
+    const uint32_t t_first = a.R == 1 ? row0 : row0 / a.R;
+    const __amdgpu_buffer_rsrc_t ro = __builtin_amdgcn_make_buffer_rsrc(
+        static_cast<bf16_t*>(a.Out) + int64_t(t_first) * a.c_tok_stride, 0, 0x7fffffff, 0x00020000);
+    constexpr uint32_t OUT = 0x80000000u;
+    const int32_t* tr = reinterpret_cast<const int32_t*>(tab);
+    const int32_t* tc = tr + S::TAB_ROWS;
+    const uint32_t ctok = uint32_t(a.c_tok_stride);
+    auto row_offset = [&](uint32_t lr) -> uint32_t {
+        const uint32_t r = row0 + lr, t = a.R == 1 ? r : r / a.R;
+        return r < a.total_rows ? ((t - t_first) * ctok + uint32_t(tr[lr])) * 2u : OUT;
+    };
+    auto col_offset = [&](int lc) -> uint32_t { return col0 + lc < a.C ? uint32_t(tc[lc]) * 2u : OUT; };
+    // x, y: two neighbouring 16 x 16 tiles along the direction in which a lane holds 4 consecutive values. Afterwards it
+    // holds 8: of x in lanes 0-31, of y in lanes 32-63, values 8*((l/16)%2) ..
+    auto merge = [&](const floatx4& x, const floatx4& y) -> uintx4 {
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        auto pack = [](float u, float v) {
+            bf16x2 h;
+            h[0] = bf16_t(u);
+            h[1] = bf16_t(v);
+            return __builtin_bit_cast(unsigned, h);
+        };
+        const auto s0 = __builtin_amdgcn_permlane32_swap(pack(x[0], x[1]), pack(y[0], y[1]), false, false);
+        const auto s1 = __builtin_amdgcn_permlane32_swap(pack(x[2], x[3]), pack(y[2], y[3]), false, false);
+        const auto t0 = __builtin_amdgcn_permlane16_swap(s0[0], s0[1], false, false);
+        const auto t1 = __builtin_amdgcn_permlane16_swap(s1[0], s1[1], false, false);
+        uintx4 o;
+        o[0] = t0[0];
+        o[1] = t1[0];
+        o[2] = t0[1];
+        o[3] = t1[1];
+        return o;
+    };
+    const int piece = 16 * (lane >> 5) + 8 * ((lane >> 4) & 1);
+    if (TRANS) {
+        uint32_t base[TM / 2];
+#pragma unroll
+        for (int i = 0; i < TM / 2; ++i) base[i] = row_offset(wm * TM * 16 + i * 32 + piece);
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const uint32_t co = col_offset(wn * TN * 16 + j * 16 + (lane & 15));
+            // (one column of tiles at a time: the scheduler otherwise converts all of them first, and spills)
+#pragma unroll
+            for (int i = 0; i < TM; ++i) asm volatile("" : "+a"(acc[i][j]));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < TM / 2; ++i)
+                __builtin_amdgcn_raw_buffer_store_b128(merge(acc[2 * i][j], acc[2 * i + 1][j]), ro,
+                                                       int(((base[i] | co) & OUT) ? ~0u : base[i] + co), 0, 0);
+        }
+    } else {
+        uint32_t co[TN / 2];
+#pragma unroll
+        for (int j = 0; j < TN / 2; ++j) co[j] = col_offset(wn * TN * 16 + j * 32 + piece);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const uint32_t base = row_offset(wm * TM * 16 + i * 16 + (lane & 15));
+#pragma unroll
+            for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = 0; j < TN / 2; ++j)
+                __builtin_amdgcn_raw_buffer_store_b128(merge(acc[i][2 * j], acc[i][2 * j + 1]), ro,
+                                                       int(((base | co[j]) & OUT) ? ~0u : base + co[j]), 0, 0);
+        }
+    }
+#endif
+}

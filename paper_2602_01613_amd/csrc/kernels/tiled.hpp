@@ -1,4 +1,4 @@
-// Tiled contraction-step kernels: plain FMA (any dtype), bf16 MFMA tiles with register prefetch, and the direct-to-LDS ring kernel.
+// Tiled contraction-step kernels: plain FMA (any dtype) and bf16 MFMA tiles with register prefetch.
 // Part of the tn_linear library's single translation unit: included by tn_linear.hip inside its
 // anonymous namespace, after <hip/hip_runtime.h> and tn_plan.hpp.
 #pragma once
@@ -468,256 +468,11 @@ step_mfma_pipe_kernel(StepArgs a, int cmode, int nrow_tiles, int ncol_tiles) {
     }
 }
 
-// ---------------------------------------------------------------------------------------------
-// Ping-pong bf16 MFMA step kernel (the fastest tiled kernel; needs a plain A with K % 32 == 0, 8 waves).
-//   * Two groups of four waves (one wave of each group on every SIMD) run half a period apart: while one group
-//     multiplies K tile kt out of registers (16 MFMAs per wave, raised priority), the other fetches its fragments
-//     of the next tile from LDS, stores the tile after that into LDS and issues the global loads of the one after,
-//     so a SIMD's matrix core always has a wave with work ready. Each wave alternates a memory phase M(kt) and a
-//     compute phase C(kt) with a workgroup barrier after each; group 1 passes one barrier more before its first
-//     phase and group 0 one more after its last, so all waves execute 2 * nk + 1 barriers in the loop. With the
-//     phases numbered so that group 0 runs M(kt) in phase 2kt and group 1 in phase 2kt + 1:
-//       - a K tile of 32 travels global memory -> registers (issued in M(kt-1) for tile kt+1, 16 registers per
-//         wave) -> LDS stage (kt+1) % NS (written in M(kt)) -> fragments (read in M(kt+1));
-//       - that stage is written in phase 2kt at the earliest; its last readers (tile kt+1-NS) finished in phase
-//         2(kt+1-NS)+1 < 2kt for NS >= 2, with lgkmcnt(0) before their barrier;
-//       - tile kt+1 is written by phase 2kt+1 and read from phase 2kt+2 on.
-//     (Measured against the same loop fed by global_load_lds, and against a single-phase loop with one barrier
-//     per tile: 6 % faster than either. The barriers of the loop are bare s_barrier: a fence there makes the
-//     compiler drain the global loads in flight.)
-//   * an LDS tile row is 64 bytes (4 chunks of 16 B); chunk c of row r sits at chunk position
-//     c ^ ((r >> 2) & 3), which makes the fragment reads of 16 consecutive rows conflict-free. The
-//     swizzle costs nothing: each lane simply fetches the global chunk that belongs at its LDS slot.
-// Tile numbering (XCD-aware), epilogue (CMODE 1, TRANS, scalar) and tables are those of the kernel
-// above. Rows past the end are clamped to the last row when loading and masked when storing.
-// ---------------------------------------------------------------------------------------------
+// Waits until at most N of the wave's vector-memory operations are outstanding.
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
     // s_waitcnt immediate on gfx9: vmcnt[3:0] | expcnt[6:4] | lgkmcnt[11:8] | vmcnt[5:4] at [15:14]
     constexpr int imm = (N & 0xF) | (0x7 << 4) | (0xF << 8) | ((N >> 4) << 14);
     __builtin_amdgcn_s_waitcnt(imm);
-}
-
-template <int WM, int WN, int TM, int TN, int NS, int MINB, int TRANS>
-__global__ void __launch_bounds__(WM * WN * 64, MINB)
-step_mfma_pingpong_kernel(StepArgs a, int cmode, int nrow_tiles, int ncol_tiles, int slot_base, int halves) {
-    constexpr int NT = WM * WN * 64, NWAVE = WM * WN;
-    constexpr int BM = WM * TM * 32, BN = WN * TN * 32, BK = 32;
-    constexpr int ROWB = BK * 2;                       // bytes per LDS tile row
-    constexpr int A_BYTES = BM * ROWB, STAGE_BYTES = (BM + BN) * ROWB;
-    constexpr int A_PER_WAVE = BM / 16 / NWAVE, B_PER_WAVE = BN / 16 / NWAVE;   // 1 KB loads per wave and stage
-    constexpr int L = A_PER_WAVE + B_PER_WAVE;
-    constexpr int LDC = BN + 8, LDR = BM + 8;
-    static_assert(NWAVE == 8, "two groups of four waves");
-    static_assert((BM / 16) % NWAVE == 0 && (BN / 16) % NWAVE == 0, "16-row blocks per wave");
-    static_assert(NS >= 2, "a stage is refilled while its neighbour is read");
-    extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
-
-    // A launch covers the tiles of slots slot_base .. of every XCD's walk (see tile_of_workgroup); with
-    // halves = 1 the walk is that of tiles twice as wide as this kernel's (ncol_tiles counts those) and two
-    // consecutive workgroups of an XCD take the two halves of one of them: the host runs the last, partly
-    // filled round of a launch that way, on twice as many workgroups for half as long.
-    int row_tile, col_tile;
-    {
-        const int xcd = blockIdx.x & 7;
-        int slot = blockIdx.x >> 3, half = 0;
-        if (halves) {
-            half = slot & 1;
-            slot >>= 1;
-        }
-        slot += slot_base;
-        if (slot >= ((nrow_tiles + 7) >> 3) * ncol_tiles) return;
-        tile_of_workgroup((slot << 3) | xcd, nrow_tiles, ncol_tiles, &row_tile, &col_tile);
-        if (halves) col_tile = 2 * col_tile + half;
-    }
-    if (row_tile >= nrow_tiles) return;
-    const uint32_t row0 = uint32_t(row_tile) * BM;
-    const int col0 = col_tile * BN;
-
-    const bf16_t* A = static_cast<const bf16_t*>(a.A);
-    const bf16_t* B = static_cast<const bf16_t*>(a.B);
-    bf16_t* Out = static_cast<bf16_t*>(a.Out);
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
-    const int nks = a.Kp >> 4;
-
-    // per-lane sources: lane l of a 1 KB block fills LDS row l/4, chunk position l%4 of the block
-    const int lr = lane >> 2, lpc = lane & 3;
-    const bf16_t* a_src[A_PER_WAVE];
-    const bf16_t* b_src[B_PER_WAVE];
-#pragma unroll
-    for (int j = 0; j < A_PER_WAVE; ++j) {
-        int r = (j * NWAVE + wave) * 16 + lr;
-        int c = lpc ^ ((r >> 2) & 3);
-        uint32_t g = row0 + r;
-        if (g >= a.total_rows) g = a.total_rows - 1;
-        a_src[j] = A + int64_t(g) * a.K + c * 8;
-    }
-#pragma unroll
-    for (int j = 0; j < B_PER_WAVE; ++j) {
-        int r = (j * NWAVE + wave) * 16 + lr;              // column within the tile
-        int c = lpc ^ ((r >> 2) & 3);                       // logical chunk: k = kt*32 + c*8
-        int col = col0 + r;
-        // fragment-major: block (col/32, k/16), chunk (col%32) + 32*((k/8)%2)
-        b_src[j] = B + (int64_t(col >> 5) * nks + (c >> 1)) * 512 + ((col & 31) + 32 * (c & 1)) * 8;
-    }
-    bf16x8 stg[L];                                       // the tile on its way from global memory to LDS
-    auto load_tile = [&](int kt) {
-#pragma unroll
-        for (int j = 0; j < A_PER_WAVE; ++j) stg[j] = *reinterpret_cast<const bf16x8*>(a_src[j] + kt * BK);
-#pragma unroll
-        for (int j = 0; j < B_PER_WAVE; ++j)
-            stg[A_PER_WAVE + j] = *reinterpret_cast<const bf16x8*>(b_src[j] + int64_t(kt) * 2 * 512);
-    };
-    auto store_tile = [&](int stage) {
-        unsigned char* sbase = dyn_smem + stage * STAGE_BYTES + lane * 16;
-#pragma unroll
-        for (int j = 0; j < A_PER_WAVE; ++j) *reinterpret_cast<bf16x8*>(sbase + (j * NWAVE + wave) * 1024) = stg[j];
-#pragma unroll
-        for (int j = 0; j < B_PER_WAVE; ++j)
-            *reinterpret_cast<bf16x8*>(sbase + A_BYTES + (j * NWAVE + wave) * 1024) = stg[A_PER_WAVE + j];
-    };
-
-    floatx16 acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-    // fragment read offsets: lane reads row lane%32, logical chunk ks*2 + lane/32
-    int a_off[TM][2], b_off[TN][2];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            int r = (wm * TM + i) * 32 + (lane & 31);
-            a_off[i][ks] = r * ROWB + (((ks * 2 + (lane >> 5)) ^ ((r >> 2) & 3)) * 16);
-        }
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-            int r = (wn * TN + j) * 32 + (lane & 31);
-            b_off[j][ks] = A_BYTES + r * ROWB + (((ks * 2 + (lane >> 5)) ^ ((r >> 2) & 3)) * 16);
-        }
-
-    const int nk_real = a.K / BK;                        // K % 32 == 0: only these tiles hold data; B is zero beyond
-    const int grp = wave >> 2;
-    load_tile(0);
-    store_tile(0);
-    if (nk_real > 1) load_tile(1);
-    __syncthreads();
-    bf16x8 af[2][TM], bfr[2][TN];
-    if (grp == 1) __builtin_amdgcn_s_barrier();
-    for (int kt = 0; kt < nk_real; ++kt) {
-        // ---- M(kt)
-        const unsigned char* scur = dyn_smem + (kt % NS) * STAGE_BYTES;
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks) {
-#pragma unroll
-            for (int i = 0; i < TM; ++i) af[ks][i] = *reinterpret_cast<const bf16x8*>(scur + a_off[i][ks]);
-#pragma unroll
-            for (int j = 0; j < TN; ++j) bfr[ks][j] = *reinterpret_cast<const bf16x8*>(scur + b_off[j][ks]);
-        }
-        if (kt + 1 < nk_real) store_tile((kt + 1) % NS);
-        if (kt + 2 < nk_real) load_tile(kt + 2);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): fragment reads and tile stores are done
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        // ---- C(kt)
-        __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = TRANS ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[ks][i], bfr[ks][j], acc[i][j], 0, 0, 0)
-                                      : __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfr[ks][j], af[ks][i], acc[i][j], 0, 0, 0);
-        __builtin_amdgcn_s_setprio(0);
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_barrier();
-    }
-    if (grp == 0) __builtin_amdgcn_s_barrier();
-    __syncthreads();
-
-    // ---- epilogue (see step_mfma_pipe_kernel)
-    constexpr size_t C_ELEMS = size_t(BM) * LDC > size_t(BN) * LDR ? size_t(BM) * LDC : size_t(BN) * LDR;
-    bf16_t* sC = reinterpret_cast<bf16_t*>(dyn_smem);
-    int64_t* sBase = reinterpret_cast<int64_t*>(dyn_smem + C_ELEMS * sizeof(bf16_t));
-    int32_t* sCol = reinterpret_cast<int32_t*>(sBase + BM);    // output offsets of the tile's columns (-1: no such column)
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                bf16x4 pk;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) pk[u] = bf16_t(acc[i][j][4 * q + u]);
-                if (TRANS) {
-                    int cc = (wn * TN + j) * 32 + (lane & 31);
-                    int rr = (wm * TM + i) * 32 + 8 * q + 4 * (lane >> 5);
-                    *reinterpret_cast<bf16x4*>(sC + cc * LDR + rr) = pk;
-                } else {
-                    int rr = (wm * TM + i) * 32 + (lane & 31);
-                    int cc = (wn * TN + j) * 32 + 8 * q + 4 * (lane >> 5);
-                    *reinterpret_cast<bf16x4*>(sC + rr * LDC + cc) = pk;
-                }
-            }
-    for (int rr = tid; rr < BM; rr += NT) {
-        uint32_t g = row0 + rr;
-        int64_t base = -1;
-        if (g < a.total_rows) {
-            uint32_t t = g / a.R;
-            uint32_t r = g - t * a.R;
-            base = int64_t(t) * a.c_tok_stride + a.crow[r];
-        }
-        sBase[rr] = base;
-    }
-    // (looked up once per tile: inside the store loops every lookup would sit between two stores)
-    for (int cc = tid; cc < BN; cc += NT) sCol[cc] = col0 + cc < a.C ? a.ccol[col0 + cc] : -1;
-    __syncthreads();
-    constexpr int GROUPS = BM * BN / 8;
-    if (TRANS) {
-#pragma unroll 4
-        for (int e = tid; e < GROUPS; e += NT) {
-            int rg = (e % (BM / 8)) * 8, cc = e / (BM / 8);
-            int64_t base = sBase[rg];
-            const int co = sCol[cc];
-            if (base < 0 || co < 0) continue;
-            *reinterpret_cast<bf16x8*>(Out + base + co) = *reinterpret_cast<const bf16x8*>(sC + cc * LDR + rg);
-        }
-    } else if (cmode == 1) {
-#pragma unroll 4
-        for (int e = tid; e < GROUPS; e += NT) {
-            int rr = e / (BN / 8), cg = (e % (BN / 8)) * 8;
-            int64_t base = sBase[rr];
-            const int co = sCol[cg];
-            if (base < 0 || co < 0) continue;
-            *reinterpret_cast<bf16x8*>(Out + base + co) = *reinterpret_cast<const bf16x8*>(sC + rr * LDC + cg);
-        }
-    } else {
-        for (int e = tid; e < BM * BN; e += NT) {
-            int rr = e / BN, cc = e % BN;
-            int64_t base = sBase[rr];
-            const int co = sCol[cc];
-            if (base < 0 || co < 0) continue;
-            Out[base + co] = sC[rr * LDC + cc];
-        }
-    }
-}
-
-template <int WM, int WN, int TM, int TN, int NS>
-constexpr size_t pingpong_smem_bytes() {
-    constexpr int BM = WM * TM * 32, BN = WN * TN * 32;
-    constexpr size_t stage = size_t(BM + BN) * 64 * NS;
-    constexpr size_t c_elems = size_t(BM) * (BN + 8) > size_t(BN) * (BM + 8) ? size_t(BM) * (BN + 8) : size_t(BN) * (BM + 8);
-    constexpr size_t epi = c_elems * 2 + size_t(BM) * 8 + size_t(BN) * 4;
-    return stage > epi ? stage : epi;
 }
 
 template <int WM, int WN, int TM, int TN, int STAGES>

@@ -19,6 +19,7 @@
 #include <mutex>
 #include <new>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "../../include/tn_linear.h"
@@ -36,6 +37,7 @@ namespace {
 #include "kernels/pack.hpp"
 #include "kernels/quant.hpp"
 #include "kernels/tiled.hpp"
+#include "kernels/gemm.hpp"
 #include "kernels/stream.hpp"
 #include "kernels/chained.hpp"
 #include "kernels/kronsum.hpp"
@@ -50,7 +52,7 @@ enum Variant : int {
     VAR_PIPE_128x256 = 3,     // register-prefetch tiles, 4 waves, 2 workgroups per CU, one LDS stage
     VAR_PIPE_256x128 = 8,     // same, 4 waves stacked along rows
     VAR_SHORTK = 9,           // K <= 64, store-bound: registers-only operands, barrier-free
-    VAR_PINGPONG_256x256 = 12,   // 8 waves in two alternating groups, 1 workgroup per CU
+    VAR_GEMM = 12,            // plain A with K % 64 == 0, more than 64 rows: tiles chosen per launch (gemm_choice)
     VAR_KRONSUM = 20,         // (as a forced id only, read by tn::kron_shape) the Kronecker-sum kernel wherever
                               // the plan's layout allows it
 };
@@ -226,21 +228,21 @@ void choose_variant(const tn_linear_s* h, DevStep* s, int flags) {
         // register-only kernel for short-K, wide steps
         const bool shortk_ok = p.K <= 64 && p.c_vec == 8;
         int v = round_up(int(p.C), 128) < round_up(int(p.C), 256) ? VAR_PIPE_256x128 : VAR_PIPE_128x256;
-        // direct-to-LDS tiles where A is a plain matrix whose K is a whole number of 32-wide tiles
-        const bool pingpong_ok = p.a_plain && p.K % 32 == 0 && p.K >= 64;
-        // (measured: the 8-wave 256x256 ring beats the register-prefetch tiles on every shape it
-        // fits without extra column padding; the 4-wave direct-to-LDS tiles do not)
-        if (pingpong_ok && p.C >= 256 && round_up(int(p.C), 256) == round_up(int(p.C), 128)) v = VAR_PINGPONG_256x256;
+        // the matrix-product kernel wherever A is a plain matrix of whole K tiles of 64 and the output comes in aligned
+        // pieces of 8: it has the tile sizes for any number of rows (777 rows x 5120 x 25600: 208 us, 506 us on 256x256
+        // tiles of one size; 777 x 2304 x 5120: 28 us, 119 us on the split-K kernel that too few tiles led to)
+        const bool gemm_ok = p.a_plain && p.K % 64 == 0 && p.K < (int64_t(1) << 21) && (p.c_vec == 8 || p.r_vec == 8);
+        if (gemm_ok) v = VAR_GEMM;
         if (shortk_ok && p.C >= 256) v = VAR_SHORTK;
         if (forced == VAR_PIPE_128x256 || forced == VAR_PIPE_256x128 || (forced == VAR_SHORTK && shortk_ok) ||
-            (forced == VAR_PINGPONG_256x256 && pingpong_ok))
+            (forced == VAR_GEMM && gemm_ok))
             v = forced;
         s->variant = v;
         switch (v) {
             case VAR_SHORTK: s->bm = 128; s->bn = 128; break;
             case VAR_PIPE_128x256: s->bm = 128; s->bn = 256; break;
             case VAR_PIPE_256x128: s->bm = 256; s->bn = 128; break;
-            default: s->bm = 256; s->bn = 256; break;      // VAR_PINGPONG_256x256
+            default: s->bm = 256; s->bn = p.C > 128 ? 256 : 128; break;      // VAR_GEMM
         }
     }
     // 0: plain rows of 16-byte pieces; 2: gathered rows of 16-byte pieces (the tiled pipeline kernel; every other kernel
@@ -392,46 +394,133 @@ int launch_pipe(const DevStep& s, const StepArgs& a, int64_t rows, hipStream_t s
     return TN_OK;
 }
 
-// The 256x256 ping-pong kernel and its 256x128 form. A CU holds one workgroup, so a launch runs in rounds of
-// num_cus tiles; when the last round would fill at most half of the CUs, its tiles run as a second launch of
-// half-width tiles on twice as many workgroups (same walk over the tiles, see the kernel), which takes half a round.
-using pingpong_kern_t = void (*)(StepArgs, int, int, int, int, int);
+// Tile sizes of step_gemm_kernel and what they cost, in us: `t1` per K tile of 64 with one workgroup on every CU and
+// `o1` per round of workgroups (start, first loads, stores); t2, o2 likewise with two on every CU, where they fit
+// (measured at 256 and 512 tiles, K 1024 and 5120). Larger tiles do more per us (a CU's 256 x 256 tile takes 1.44 us per K
+// tile, four 128 x 128 tiles 1.82), smaller ones leave less of the last round of workgroups empty and pad fewer rows.
+struct GemmTile {
+    int tm, tn;
+    float t1, o1, t2, o2;
+};
+constexpr int kGemmTiles = 13;
+constexpr GemmTile kGemmTile[kGemmTiles] = {
+    {8, 8, 1.44f, 8.0f, 0.f, 0.f}, {7, 8, 1.31f, 7.3f, 0.f, 0.f}, {6, 8, 1.17f, 6.6f, 0.f, 0.f}, {5, 8, 1.02f, 6.3f, 0.f, 0.f},
+    {4, 8, 0.90f, 6.2f, 0.f, 0.f}, {3, 8, 0.76f, 5.6f, 0.f, 0.f}, {2, 8, 0.71f, 3.8f, 0.f, 0.f}, {8, 4, 0.92f, 6.0f, 0.f, 0.f},
+    {6, 4, 0.81f, 2.5f, 0.f, 0.f}, {5, 4, 0.73f, 1.8f, 1.09f, 7.5f}, {4, 4, 0.64f, 2.0f, 0.91f, 5.8f},
+    {3, 4, 0.58f, 1.5f, 0.78f, 4.0f}, {2, 4, 0.54f, 1.0f, 0.63f, 3.8f}};
 
-template <int TN, int TRANS>
-pingpong_kern_t pingpong_kernel() { return step_mfma_pingpong_kernel<4, 2, 2, TN, 2, 1, TRANS>; }
+struct GemmChoice {
+    int tile = -1, n_split = 1, ktiles_per_split = 1;
+    int64_t partial_bytes = 0;
+};
 
-int configure_pingpong() {
-    const pingpong_kern_t wide[2] = {pingpong_kernel<4, 0>(), pingpong_kernel<4, 1>()};
-    const pingpong_kern_t narrow[2] = {pingpong_kernel<2, 0>(), pingpong_kernel<2, 1>()};
-    for (int i = 0; i < 2; ++i)
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(wide[i]), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                int(pingpong_smem_bytes<4, 2, 2, 4, 2>())) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void*>(narrow[i]), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                int(pingpong_smem_bytes<4, 2, 2, 2, 2>())) != hipSuccess)
-            return TN_ERR_HIP;
+constexpr int64_t kGemmMinRows = 65;        // up to 64 rows the launch is a stream of the packed tensor: the kernels of stream.hpp
+constexpr float kGemmPartialBytesPerUs = 3.5e6f;    // partial sums, written and read back, and the launch that adds them:
+constexpr float kGemmReduceUs = 4.f;
+
+// The tile size and the number of K ranges with the least time for `rows` rows; partial sums within `cap` bytes.
+GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int64_t cap) {
+    GemmChoice best;
+    float best_us = 0.f;
+    const int nk = s.Kp / 64;
+    const bool trans = s.cmode == 2;
+    const int64_t cus = h->num_cus;
+    for (int t = 0; t < kGemmTiles; ++t) {
+        const GemmTile& g = kGemmTile[t];
+        if (s.Cp % (32 * g.tn) || (trans && (g.tm & 1))) continue;
+        const int64_t tiles = ((rows + 32 * g.tm - 1) / (32 * g.tm)) * ((s.plan.C + 32 * g.tn - 1) / (32 * g.tn));
+        if (tiles > (int64_t(1) << 26)) continue;
+        for (int ns = 1; ns <= 8; ++ns) {
+            // more ranges only while they fill an idle chip, at least 4 K tiles each
+            if (ns > 1 && (trans || tiles * (ns - 1) >= 2 * cus || nk < 4 * ns)) break;
+            const int per = (nk + ns - 1) / ns, n_real = (nk + per - 1) / per;
+            if (n_real != ns) continue;
+            const int64_t pb = ns > 1 ? int64_t(ns) * rows * s.Cp * 4 : 0;
+            if (pb > cap) break;
+            const int64_t items = tiles * ns;
+            const float one = g.o1 + float(per) * g.t1, two = g.o2 + float(per) * g.t2;
+            float us;
+            if (g.t2 > 0.f) {
+                const int64_t full = items / (2 * cus), rest = items - full * 2 * cus;
+                us = float(full) * two + (rest == 0 ? 0.f : rest <= cus ? one : two);
+            } else {
+                us = float((items + cus - 1) / cus) * one;
+            }
+            if (ns > 1) us += kGemmReduceUs + 2.f * float(pb) / kGemmPartialBytesPerUs;
+            if (best.tile < 0 || us < best_us) {
+                best_us = us;
+                best.tile = t;
+                best.n_split = ns;
+                best.ktiles_per_split = per;
+                best.partial_bytes = pb;
+            }
+        }
+    }
+    return best;
+}
+
+using gemm_kern_t = void (*)(StepArgs, GemmArgs);
+
+template <int I, int TRANS>
+constexpr gemm_kern_t gemm_kernel_of() {
+    if constexpr (TRANS && (kGemmTile[I].tm & 1)) return nullptr;
+    else return step_gemm_kernel<kGemmTile[I].tm, kGemmTile[I].tn, TRANS>;
+}
+
+template <int TRANS, int... I>
+gemm_kern_t gemm_kernel_at(int tile, std::integer_sequence<int, I...>) {
+    static const gemm_kern_t k[kGemmTiles] = {gemm_kernel_of<I, TRANS>()...};
+    return k[tile];
+}
+
+template <int... I>
+size_t gemm_smem_at(int tile, std::integer_sequence<int, I...>) {
+    constexpr size_t b[kGemmTiles] = {GemmShape<kGemmTile[I].tm, kGemmTile[I].tn>::SMEM...};
+    return b[tile];
+}
+
+gemm_kern_t gemm_kernel(int tile, bool trans) {
+    using seq = std::make_integer_sequence<int, kGemmTiles>;
+    return trans ? gemm_kernel_at<1>(tile, seq()) : gemm_kernel_at<0>(tile, seq());
+}
+size_t gemm_smem(int tile) { return gemm_smem_at(tile, std::make_integer_sequence<int, kGemmTiles>()); }
+
+int configure_gemm() {
+    for (int t = 0; t < kGemmTiles; ++t)
+        for (int trans = 0; trans < 2; ++trans) {
+            const gemm_kern_t k = gemm_kernel(t, trans != 0);
+            if (k && hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         int(gemm_smem(t))) != hipSuccess)
+                return TN_ERR_HIP;
+        }
     return TN_OK;
 }
 
-int launch_pingpong(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64_t rows, hipStream_t st) {
-    const int nrow = int((rows + 255) / 256), ncol = s.Cp / 256;
-    const int trans = s.cmode == 2 ? 1 : 0;
-    const pingpong_kern_t wide = trans ? pingpong_kernel<4, 1>() : pingpong_kernel<4, 0>();
-    const pingpong_kern_t narrow = trans ? pingpong_kernel<2, 1>() : pingpong_kernel<2, 0>();
-    const int slots = ((nrow + 7) / 8) * ncol;             // per XCD (workgroup i runs on XCD i % 8)
-    const int per_xcd = h->num_cus / 8;
-    int full = slots, rest = 0;
-    if (nrow % 8 == 0 && h->num_cus % 8 == 0 && per_xcd > 0) {
-        const int r = slots % per_xcd;
-        if (r > 0 && 2 * r <= per_xcd) {
-            rest = r;
-            full = slots - r;
-        }
+// Output offsets inside one tile are 31-bit byte offsets from its first token.
+bool gemm_fits(const DevStep& s) {
+    return s.variant == VAR_GEMM && s.cmode != 0 && (256 / s.plan.R + 2) * s.plan.c_tok_stride * 2 < (int64_t(1) << 31);
+}
+
+int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64_t rows, void* partial, int64_t partial_bytes,
+                hipStream_t st) {
+    const bool trans = s.cmode == 2;
+    const GemmChoice c = gemm_choice(h, s, rows, (h->flags & TN_FLAG_NO_SPLIT_K) || !partial ? 0 : partial_bytes);
+    if (c.tile < 0) return TN_ERR_UNSUPPORTED;
+    const GemmTile& t = kGemmTile[c.tile];
+    GemmArgs g;
+    g.n_row = int32_t((rows + 32 * t.tm - 1) / (32 * t.tm));
+    g.n_col = int32_t((s.plan.C + 32 * t.tn - 1) / (32 * t.tn));
+    g.n_split = c.n_split;
+    g.ktiles_per_split = c.ktiles_per_split;
+    g.rows_pad = rows;
+    g.partial = static_cast<float*>(partial);
+    const int64_t items = int64_t(g.n_row) * g.n_col * g.n_split;
+    hipLaunchKernelGGL(gemm_kernel(c.tile, trans), dim3(uint32_t((items + 7) / 8 * 8)), dim3(256), gemm_smem(c.tile), st, a, g);
+    if (c.n_split > 1) {
+        const int64_t total = rows * s.plan.C;
+        hipLaunchKernelGGL(step_split_reduce_kernel, dim3(uint32_t(std::min<int64_t>((total + 255) / 256, 2048))), dim3(256), 0, st,
+                           a, g.partial, c.n_split, uint32_t(rows));
     }
-    constexpr size_t wide_smem = pingpong_smem_bytes<4, 2, 2, 4, 2>(), narrow_smem = pingpong_smem_bytes<4, 2, 2, 2, 2>();
-    if (full > 0)
-        hipLaunchKernelGGL(wide, dim3(uint32_t(8 * full)), dim3(512), wide_smem, st, a, s.cmode, nrow, ncol, 0, 0);
-    if (rest > 0)
-        hipLaunchKernelGGL(narrow, dim3(uint32_t(16 * rest)), dim3(512), narrow_smem, st, a, s.cmode, nrow, ncol, full, 1);
     return TN_OK;
 }
 
@@ -476,6 +565,11 @@ int launch_step(const tn_linear_s* h, const Workspace& w, const DevStep& s, cons
     a.Kp = s.Kp;
     a.C = int32_t(s.plan.C);
     a.Cp = s.Cp;
+    if (rows >= kGemmMinRows && gemm_fits(s)) {
+        const int rc = launch_gemm(h, s, a, rows, w.partial, w.partial_bytes, st);
+        if (rc != TN_OK) return rc;
+        return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
+    }
     SplitCfg sc = (h->flags & TN_FLAG_NO_SPLIT_K) ? SplitCfg() : split_config(s, rows);
     if (sc.use && (sc.partial_bytes == 0 || (w.partial && sc.partial_bytes <= w.partial_bytes))) {
         dim3 sgrid(uint32_t(sc.row_tiles), uint32_t(sc.col_blocks), uint32_t(sc.nsplit));
@@ -538,8 +632,9 @@ int launch_step(const tn_linear_s* h, const Workspace& w, const DevStep& s, cons
             if (rc != TN_OK) return rc;
             break;
         }
-        case VAR_PINGPONG_256x256: {
-            int rc = launch_pingpong(h, s, a, rows, st);
+        case VAR_GEMM: {
+            // few rows without the split-K kernels; offsets that do not fit take the register-prefetch tiles
+            int rc = gemm_fits(s) ? launch_gemm(h, s, a, rows, w.partial, w.partial_bytes, st) : launch_pipe<4, 1, 2, 4, 1, 2>(s, a, rows, st);
             if (rc != TN_OK) return rc;
             break;
         }
@@ -1604,7 +1699,7 @@ int configure_kernels(int device) {
     const tn_linear_s* no_handle = nullptr;
     int rc = launch_pipe<2, 2, 2, 4, 1, 2>(none, a, 0, nullptr);
     if (rc == TN_OK) rc = launch_pipe<4, 1, 2, 4, 1, 2>(none, a, 0, nullptr);
-    if (rc == TN_OK) rc = configure_pingpong();
+    if (rc == TN_OK) rc = configure_gemm();
     if (rc == TN_OK) rc = launch_chain2(no_handle, none, none, nullptr, nullptr, 0, nullptr);
     if (rc == TN_OK) rc = launch_chain2_split(nullptr, nullptr, nullptr);
     for (int i = 0; i < kSkinnyKernels && rc == TN_OK; ++i)
@@ -2228,10 +2323,17 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
                 need = std::max(need, kron_geometry(h, h->lazy_dims, t, kMaxPartialBytes).partial_bytes);
         for (const auto& s : h->steps)
             for (int64_t t = 1; t <= chunk; ++t) {
+                if (t * s.plan.R >= kGemmMinRows && gemm_fits(s)) break;
                 SplitCfg c = split_config(s, t * s.plan.R);
                 if (!c.use) break;          // larger passes only add tiles
                 need = std::max(need, c.partial_bytes);
             }
+        // the matrix-product kernel takes as many K ranges as the buffer has room for: sized for row counts up to where
+        // the tiles alone fill the chip
+        for (const auto& s : h->steps)
+            if (gemm_fits(s))
+                for (int64_t t = 1; t <= chunk && t * s.plan.R <= 8192; t += std::max<int64_t>(1, t / 8))
+                    if (t * s.plan.R >= kGemmMinRows) need = std::max(need, gemm_choice(h, s, t * s.plan.R, kMaxPartialBytes).partial_bytes);
         return need;
     };
     // a lazily merged plan needs room for its slices: in the caller's block they share the space of the two
@@ -2642,6 +2744,10 @@ int tn_linear_forward_scratch(tn_linear_t h, const void* x, void* y, int64_t tok
             for (const tn::LaunchIO& l : h->schedule)
                 if (l.steps == 1) {
                     const DevStep& s = h->steps[size_t(l.first)];
+                    if (tokens * s.plan.R >= kGemmMinRows && gemm_fits(s)) {
+                        part = std::max(part, gemm_choice(h, s, tokens * s.plan.R, kScratchBytes / 2).partial_bytes);
+                        continue;
+                    }
                     const SplitCfg c = split_config(s, tokens * s.plan.R);
                     if (c.use) part = std::max(part, c.partial_bytes);
                 }

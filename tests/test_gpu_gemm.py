@@ -1,0 +1,65 @@
+"""The matrix-product step kernel (wide bf16 steps with a plain input, more than 64 rows) against the fp64 product, at the
+edges of its tiles. Tolerance: inputs are exact in bf16, sums are fp32 over K terms (relative error below K * 2^-24 of the
+sum of magnitudes, 1e-3 of the largest result at K = 2304), so one bf16 rounding of the result dominates: 2^-8 of the
+largest value, doubled for the two roundings of a Tucker chain's other steps where there are any."""
+import numpy as np
+import pytest
+
+import oracle as O
+import workloads as wl
+import paper_2602_01613_amd as tn
+from gpu_util import make_layer, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_in,n_out", [(64, 40), (128, 129), (192, 264), (2304, 328), (320, 1032), (704, 2056)])
+def test_dense_tile_edges(n_in, n_out):
+    """K of one tile, two, and many; columns that end inside a tile of 128 or of 256; rows just below, at and above every
+    tile height (multiples of 32), from the smallest count the kernel takes; results that do not depend on the rows around
+    them."""
+    spec = wl.TNSpec(wl.FORMAT_DENSE, "bf16", (n_out,), (n_in,), ())
+    rng = np.random.default_rng(n_in + n_out)
+    w = wl.round_to_dtype(rng.standard_normal((n_out, n_in)) / np.sqrt(n_in), "bf16")
+    x = wl.round_to_dtype(rng.standard_normal((1030, n_in)), "bf16")
+    ref = x @ w.T
+    layer = make_layer(spec, [w], 1030)
+    if n_out % 8 == 0:
+        assert layer.query(tn.TN_QUERY_STEP_BASE + 5) == 12
+    xd = to_dev(x, "bf16")
+    for rows in (65, 95, 96, 97, 128, 159, 161, 224, 255, 257, 320, 513, 1030):
+        y = to_host(layer(xd[:rows].contiguous()))
+        assert np.max(np.abs(y - ref[:rows])) <= 2.0 ** -8 * np.max(np.abs(ref[:rows])) + 1e-3, (rows, n_in, n_out)
+    layer.close()
+
+
+@pytest.mark.parametrize("tokens", [65, 130, 999])
+def test_outputs_along_the_rows(tokens):
+    """A last step whose output runs along its rows (stores of 8 rows), rows of several tokens in one tile."""
+    spec = wl.TNSpec(wl.FORMAT_TT, "bf16", (16, 8, 8), (8, 8, 16), (1, 64, 64, 1))
+    rng = np.random.default_rng(tokens)
+    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(s[0] * s[2]), "bf16") for s in spec.tensor_shapes()]
+    flags = tn.TN_FLAG_NO_MERGE | tn.TN_FLAG_NO_SMALL_CHAIN
+    layer = make_layer(spec, ts, tokens, flags=flags)
+    x = wl.round_to_dtype(rng.standard_normal((tokens, spec.N)), "bf16")
+    err = O.rel_max_err(to_host(layer(to_dev(x, "bf16"))), O.forward(spec.format, ts, x, n_out_modes=3))
+    layer.close()
+    assert err <= 2e-2
+
+
+@pytest.mark.parametrize("rows", [65, 129, 200])
+def test_ranges_of_k(rows):
+    """Few tiles and a long K: partial sums of several ranges, the last one shorter, equal to the single range up to the
+    rounding of the result; with the split kernels switched off the same launch runs as one range."""
+    spec = wl.TNSpec(wl.FORMAT_DENSE, "bf16", (512,), (6976,), ())
+    rng = np.random.default_rng(rows)
+    w = wl.round_to_dtype(rng.standard_normal((512, 6976)) / np.sqrt(6976), "bf16")
+    x = wl.round_to_dtype(rng.standard_normal((rows, 6976)), "bf16")
+    ref = x @ w.T
+    for flags in (0, tn.TN_FLAG_NO_SPLIT_K):
+        layer = make_layer(spec, [w], rows, flags=flags)
+        a = to_host(layer(to_dev(x, "bf16")))
+        b = to_host(layer(to_dev(x, "bf16")))
+        layer.close()
+        assert np.array_equal(a, b)
+        assert np.max(np.abs(a - ref)) <= 2.0 ** -8 * np.max(np.abs(ref)) + 1e-3
