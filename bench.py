@@ -115,6 +115,7 @@ class LayerBench:
                                  tokens, workspace_mb << 20, flags=flags)
         self.y = torch.empty((tokens, self.layer.M), dtype=self.tdt, device="cuda")
         self.lazy_min = self.layer.query(tn.TN_QUERY_LAZY_MIN_TOKENS)
+        self.matrix_min = self.layer.query(tn.TN_QUERY_MATRIX_MIN_TOKENS)
 
     def close(self):
         self.layer.close()
@@ -124,6 +125,13 @@ class LayerBench:
         tokens (0: never) run on a plan whose merged tensors are rebuilt in the workspace per call: its steps, not
         the compact plan's, are the work such a call does."""
         tn, spec, layer, esize = self.tn, self.spec, self.layer, self.esize
+        if self.matrix_min and t >= self.matrix_min:
+            # the tensors are contracted with each other first (W, per call, launches of their own) and the call's
+            # profiled launch is the product with the activations
+            k, c = layer.N, layer.M
+            return {"n_steps": 1, "flops_tok": 2 * k * c + layer.query(tn.TN_QUERY_MATRIX_BUILD_FLOPS) / t,
+                    "q": lambda s, f: {0: 1, 1: k, 2: c, 3: 2 * k * c, 5: 12}.get(f, 0), "step_flops": [2 * k * c],
+                    "step_io_bytes": [esize * (k + c)], "step_param_bytes": [esize * k * c], "own_launches": True}
         if self.lazy_min and t >= self.lazy_min:
             pq = lambda what: tn.plan_query(spec.format, self.code, spec.out_modes, spec.in_modes, spec.ranks, what,
                                             flags=self.flags | tn.TN_FLAG_MERGE_HALVES)
@@ -203,7 +211,7 @@ class LayerBench:
                 "fused_with_next": fused, "steps_in_launch": last - s + 1})
         dom = max(range(n_steps), key=lambda s: per_step[s]["ms_per_forward"])
         d = per_step[dom]
-        if sum(p["launches_per_forward"] for p in per_step) == 1:
+        if sum(p["launches_per_forward"] for p in per_step) == 1 and not view.get("own_launches"):
             # one launch per forward: the K timed steps are K back-to-back launches of this kernel, and the events
             # around them give its average duration (gaps between launches included) without per-launch events
             scale = d["ms_per_forward"] / ms_events
@@ -556,8 +564,12 @@ def run_stack(args, verify=True, cpu=True):
         flops.append(layer.query(tn.TN_QUERY_FLOPS_PER_TOKEN))
         # large calls of some layers run on a cheaper plan rebuilt per call: count the work actually done
         lazy_min = layer.query(tn.TN_QUERY_LAZY_MIN_TOKENS)
-        flops_prefill.append(layer.query(tn.TN_QUERY_LAZY_FLOPS_PER_TOKEN) if lazy_min and tokens >= lazy_min
-                             else flops[-1])
+        matrix_min = layer.query(tn.TN_QUERY_MATRIX_MIN_TOKENS)
+        if matrix_min and tokens >= matrix_min:
+            flops_prefill.append(2 * spec.M * spec.N + layer.query(tn.TN_QUERY_MATRIX_BUILD_FLOPS) / tokens)
+        else:
+            flops_prefill.append(layer.query(tn.TN_QUERY_LAZY_FLOPS_PER_TOKEN) if lazy_min and tokens >= lazy_min
+                                 else flops[-1])
         flops_decode.append(layer.query(tn.TN_QUERY_LAZY_FLOPS_PER_TOKEN) if lazy_min and 1 >= lazy_min else flops[-1])
         params.append(spec.n_params)
         packed.append(layer.query(tn.TN_QUERY_PACKED_BYTES))
@@ -687,7 +699,7 @@ def run_stack(args, verify=True, cpu=True):
                 "frac": roof_fmt[dom_fmt]["frac_of_mfma_peak"], "traffic": None,
                 "kernel": f"the {counts[dom_fmt]} {dom_fmt} matrices of the prefill pass ({100 * roof_fmt[dom_fmt]['share_of_pass']:.0f} % "
                           f"of its time; executed FLOPs of their plans over the sum of their HIP-event times): the "
-                          f"Kronecker-sum kernel on half-ring slices rebuilt per call",
+                          f"matrix-product kernel, W of trains and rings built per call",
                 "whole_pass_tflops": total_flops * tokens / pre_wall / 1e12,
                 "whole_pass_frac": total_flops * tokens / pre_wall / 1e12 / PEAK_BF16_TFLOPS,
                 "by_format": roof_fmt}

@@ -52,6 +52,8 @@ TN_QUERY_BACKWARD_CHUNK_TOKENS = 14
 TN_QUERY_BACKWARD_WORKSPACE_BYTES = 15
 TN_QUERY_QUANT_BYTES = 16
 TN_QUERY_QUANT_STREAM_BYTES = 17
+TN_QUERY_MATRIX_MIN_TOKENS = 18
+TN_QUERY_MATRIX_BUILD_FLOPS = 19
 TN_QUERY_STEP_BASE = 100
 
 EXPORTED_SYMBOLS = (

@@ -42,3 +42,40 @@ __global__ void __launch_bounds__(256) pack_kernel(PackArgs p) {
     }
 }
 
+
+// An operand of the products of tn_matrix.hpp, from a caller's tensor: element (r, k) is src[sum of digit * stride], zero
+// past R and K and where a digit is past its limit; row-major [Rp][Kp], or fragment-major. Create time only.
+struct SourceArgs {
+    const bf16_t* src;
+    bf16_t* dst;
+    int64_t R, K, Rp, Kp;
+    int32_t nr, nk, packed;
+    int32_t rext[tn::kMaxGatherDims], rlim[tn::kMaxGatherDims], kext[tn::kMaxGatherDims], klim[tn::kMaxGatherDims];
+    int64_t rstr[tn::kMaxGatherDims], kstr[tn::kMaxGatherDims];
+};
+
+__global__ void __launch_bounds__(256) operand_source_kernel(SourceArgs p) {
+    const int64_t total = p.Rp * p.Kp;
+    for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < total; i += int64_t(gridDim.x) * 256) {
+        const int64_t r = i / p.Kp, k = i - r * p.Kp;
+        bool in = r < p.R && k < p.K;
+        int64_t off = 0;
+        if (in) {
+            int32_t rem = int32_t(k);
+            for (int j = p.nk - 1; j >= 0; --j) {
+                const int32_t q = rem / p.kext[j], d = rem - q * p.kext[j];
+                in = in && d < p.klim[j];
+                off += int64_t(d) * p.kstr[j];
+                rem = q;
+            }
+            rem = int32_t(r);
+            for (int j = p.nr - 1; j >= 0; --j) {
+                const int32_t q = rem / p.rext[j], d = rem - q * p.rext[j];
+                in = in && d < p.rlim[j];
+                off += int64_t(d) * p.rstr[j];
+                rem = q;
+            }
+        }
+        p.dst[p.packed ? bfrag_offset(int(r), int(k), int(p.Kp >> 4)) : i] = in ? p.src[off] : bf16_t(0.f);
+    }
+}

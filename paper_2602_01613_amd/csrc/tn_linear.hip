@@ -24,6 +24,7 @@
 
 #include "../../include/tn_linear.h"
 #include "tn_plan.hpp"
+#include "tn_matrix.hpp"
 
 // Scratch memory of tn_linear_forward_scratch: one array per GPU the library is loaded on, held until the
 // process ends. Host code never uses this name as an address; it asks the runtime for the device address once
@@ -72,6 +73,14 @@ struct DevStep {
     void* q4_codes = nullptr;     // 4-bit stream of the tensor for decode-size launches (codes, then block scales)
     void* q4_scales = nullptr;
     bool no_skinny = false;       // TN_FLAG_NO_SKINNY
+};
+
+// One product of the matrix plan (tn_matrix.hpp) as a launch of the matrix-product kernel. What it reads is either kept by
+// the layer or written by an earlier product of the same call.
+struct DevProduct {
+    DevStep s;                    // packed: the B operand
+    const void* a = nullptr;      // the A operand
+    void* out = nullptr;
 };
 
 }  // namespace
@@ -130,6 +139,18 @@ struct tn_linear_s {
     KronGenMfmaArgs lazy_gen_mfma[2];
     size_t lazy_gen_smem[2] = {0, 0};
     void* lazy_gen_tables[2] = {nullptr, nullptr};
+    // calls of at least mat_min_tokens tokens: the tensors contracted with each other into W, in the workspace and per call,
+    // and then Y = X W^T (tn_matrix.hpp)
+    bool matrix = false;
+    int64_t mat_min_tokens = 0;
+    int64_t mat_flops = 0;                    // of building W
+    int64_t mat_bytes = 0;                    // W and the halves that are built per call
+    int64_t mat_half_off[2] = {0, 0};         // byte offsets of the halves; W comes first
+    void* mat_mem = nullptr;                  // in the workspace (owned or caller's)
+    bool mat_build[2] = {false, false};       // the half is made of two tensors: built per call
+    DevProduct mat_half[2], mat_w;
+    DevStep mat_y;
+    std::vector<void*> mat_kept;              // operands made from the caller's tensors, and the tables
     // 4-bit form of the caller's tensors (TN_FLAG_QUANT_MXFP4): packed codes and block exponents per tensor
     std::vector<void*> quant_codes, quant_exps;
     std::vector<int64_t> quant_elems;
@@ -203,6 +224,9 @@ void free_handle(tn_linear_s* h) {
     for (void* v : h->lazy_gen_tables)
         if (v) (void)hipFree(v);
     if (h->lazy_slices && h->owns_workspace) (void)hipFree(h->lazy_slices);
+    for (void* v : h->mat_kept)
+        if (v) (void)hipFree(v);
+    if (h->mat_mem && h->owns_workspace) (void)hipFree(h->mat_mem);
     if (h->small_chain_image) (void)hipFree(h->small_chain_image);
     if (h->owns_workspace) {
         for (void* w : h->ws)
@@ -412,6 +436,7 @@ constexpr GemmTile kGemmTile[kGemmTiles] = {
 struct GemmChoice {
     int tile = -1, n_split = 1, ktiles_per_split = 1;
     int64_t partial_bytes = 0;
+    float us = 0.f;               // what it is expected to take
 };
 
 constexpr int64_t kGemmMinRows = 65;        // up to 64 rows the launch is a stream of the packed tensor: the kernels of stream.hpp
@@ -421,7 +446,6 @@ constexpr float kGemmReduceUs = 4.f;
 // The tile size and the number of K ranges with the least time for `rows` rows; partial sums within `cap` bytes.
 GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int64_t cap) {
     GemmChoice best;
-    float best_us = 0.f;
     const int nk = s.Kp / 64;
     const bool trans = s.cmode == 2;
     const int64_t cus = h->num_cus;
@@ -447,8 +471,8 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
                 us = float((items + cus - 1) / cus) * one;
             }
             if (ns > 1) us += kGemmReduceUs + 2.f * float(pb) / kGemmPartialBytesPerUs;
-            if (best.tile < 0 || us < best_us) {
-                best_us = us;
+            if (best.tile < 0 || us < best.us) {
+                best.us = us;
                 best.tile = t;
                 best.n_split = ns;
                 best.ktiles_per_split = per;
@@ -522,6 +546,56 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
                            a, g.partial, c.n_split, uint32_t(rows));
     }
     return TN_OK;
+}
+
+// One product of the matrix plan.
+int launch_product(const tn_linear_s* h, const DevProduct& p, void* partial, int64_t partial_bytes, hipStream_t st) {
+    StepArgs a{};
+    a.A = p.a;
+    a.B = p.s.packed;
+    a.Out = p.out;
+    a.crow = p.s.crow;
+    a.ccol = p.s.ccol;
+    a.total_rows = uint32_t(p.s.plan.R);
+    a.R = uint32_t(p.s.plan.R);
+    a.K = p.s.Kp;
+    a.Kp = p.s.Kp;
+    a.C = int32_t(p.s.plan.C);
+    a.Cp = p.s.Cp;
+    const int rc = launch_gemm(h, p.s, a, p.s.plan.R, partial, partial_bytes, st);
+    if (rc != TN_OK) return rc;
+    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
+}
+
+// W from the layer's tensors, then Y = X W^T.
+int launch_matrix_build(const tn_linear_s* h, void* partial, int64_t partial_bytes, hipStream_t st) {
+    for (int i = 0; i < 2; ++i)
+        if (h->mat_build[i]) {
+            const int rc = launch_product(h, h->mat_half[i], partial, partial_bytes, st);
+            if (rc != TN_OK) return rc;
+        }
+    return launch_product(h, h->mat_w, partial, partial_bytes, st);
+}
+
+int launch_matrix_y(const tn_linear_s* h, const void* x, void* y, int64_t tokens, void* partial, int64_t partial_bytes, hipStream_t st) {
+    const DevStep& s = h->mat_y;
+    StepArgs a{};
+    a.A = x;
+    a.B = s.packed;
+    a.Out = y;
+    a.crow = s.crow;
+    a.ccol = s.ccol;
+    a.a_tok_stride = s.plan.a_tok_stride;
+    a.c_tok_stride = s.plan.c_tok_stride;
+    a.total_rows = uint32_t(tokens);
+    a.R = 1;
+    a.K = s.Kp;
+    a.Kp = s.Kp;
+    a.C = int32_t(s.plan.C);
+    a.Cp = s.Cp;
+    const int rc = launch_gemm(h, s, a, tokens, partial, partial_bytes, st);
+    if (rc != TN_OK) return rc;
+    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
 
 // Instantiations of the split-K kernel that keeps the rows of A in LDS (one row tile of up to 32 rows): index
@@ -1440,6 +1514,188 @@ int prepare_lazy(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     return TN_OK;
 }
 
+// An operand kept for the products: allocated, written on `st`, freed with the handle.
+int keep_operand(tn_linear_s* h, const tn_linear_desc* desc, const tn::SourceOp& o, int64_t Kp, bool packed, void** out, hipStream_t st) {
+    SourceArgs a;
+    memset(&a, 0, sizeof(a));
+    a.R = o.R;
+    a.K = o.K;
+    a.Rp = packed ? (o.R + tn::kMatrixColPad - 1) / tn::kMatrixColPad * tn::kMatrixColPad : o.R;
+    a.Kp = Kp;
+    a.packed = packed ? 1 : 0;
+    a.nr = int32_t(o.rows.size());
+    a.nk = int32_t(o.ks.size());
+    for (size_t j = 0; j < o.rows.size(); ++j) {
+        a.rext[j] = int32_t(o.rows[j].extent);
+        a.rlim[j] = int32_t(o.rows[j].limit);
+        a.rstr[j] = o.rows[j].stride;
+    }
+    for (size_t j = 0; j < o.ks.size(); ++j) {
+        a.kext[j] = int32_t(o.ks[j].extent);
+        a.klim[j] = int32_t(o.ks[j].limit);
+        a.kstr[j] = o.ks[j].stride;
+    }
+    const int64_t n = a.Rp * a.Kp;
+    void* dst = nullptr;
+    if (hipMalloc(&dst, size_t(n) * sizeof(bf16_t)) != hipSuccess) return TN_ERR_ALLOC;
+    h->mat_kept.push_back(dst);
+    h->packed_bytes += n * int64_t(sizeof(bf16_t));
+    a.src = static_cast<const bf16_t*>(desc->tensors[o.slot]);
+    a.dst = static_cast<bf16_t*>(dst);
+    hipLaunchKernelGGL(operand_source_kernel, dim3(uint32_t(std::min<int64_t>((n + 255) / 256, 65536))), dim3(256), 0, st, a);
+    *out = dst;
+    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
+}
+
+void fill_product_step(DevStep* s, const tn::Product& p) {
+    s->plan.R = p.R;
+    s->plan.K = p.Kp;
+    s->plan.C = p.C;
+    s->plan.c_tok_stride = p.out_elems;
+    s->variant = VAR_GEMM;
+    s->cmode = 1;
+    s->Kp = int(p.Kp);
+    s->Cp = round_up(int(p.C), tn::kMatrixColPad);
+}
+
+// What one launch of a product takes, in us: its tiles, or the stores of its output.
+float product_us(const tn_linear_s* h, const DevStep& s) {
+    return 3.f + std::max(gemm_choice(h, s, s.plan.R, 0).us, float(s.plan.R) * float(s.plan.C) * 2.f / 3.5e6f);
+}
+
+// Decide whether calls of many tokens contract the tensors with each other first, from how many tokens on, and prepare it.
+// The other orders are priced at the rates their kernels reach at many tokens (FLOP per us: chained pair kernel 1.3e9,
+// Kronecker-sum kernel 1.25e9 with its padding counted, 1.0e9 where several chunks of o1 share a token, one launch per step 0.45e9). Measured, us per call in this order /
+// in the other: ring 25600 -> 5120 of rank 32 343 / 410 at 96 tokens, 767 / 8109 at 2048, 1955 / 30730 at 8192; ring 5120 ->
+// 8192 of rank 96 776 / 911 at 48 tokens, 885 / 35579 at 2048; train 5120 -> 8192 of rank 64 166 / 211 at 2048 tokens, 538 /
+// 783 at 8192; of rank 32, whose chain has little more than 2 M N, not taken.
+int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
+    if (h->plan.dtype != TN_DTYPE_BF16 ||
+        (desc->flags & (TN_FLAG_NO_PAIR_CHAIN | TN_FLAG_SCALAR_KERNELS | TN_FLAG_NO_MERGE | TN_FLAG_NO_LAZY_MERGE)) ||
+        ((desc->flags >> TN_FLAG_VARIANT_SHIFT) & 0xff) != 0)
+        return TN_OK;
+    // W takes at least the time to write it: where the product alone is no faster than what there is, no plan is made
+    DevStep& y = h->mat_y;
+    y.plan.R = 1;
+    y.plan.K = h->plan.N;
+    y.plan.C = h->plan.M;
+    y.plan.a_tok_stride = h->plan.N;
+    y.plan.c_tok_stride = h->plan.M;
+    y.variant = VAR_GEMM;
+    y.cmode = 1;
+    y.Kp = int(h->plan.N);
+    y.Cp = round_up(int(h->plan.M), tn::kMatrixColPad);
+    if (h->plan.N % 64 || h->plan.format == TN_FORMAT_DENSE || h->plan.format == TN_FORMAT_TUCKER || !gemm_fits(y)) return TN_OK;
+    // padded work of the Kronecker-sum kernel per token, and the tokens a round of its workgroups takes
+    auto kron_us = [&](const tn::KronDims& d, int64_t t) {
+        const int* c = tn::kKronConfig[d.cfg];
+        const double chunks = double((d.O1 + 32 * c[3] - 1) / (32 * c[3]));
+        const double flops = double(d.P) * chunks * c[3] * c[0] * (c[1] + 2 * c[2]) * 32768.0;
+        return 20.f + float(double(t) * flops / (chunks > 1 ? 1.0e9 : 1.25e9));
+    };
+    auto other_us = [&](int64_t t) {
+        if (h->pair) return std::max(12.f, float(t) * float(h->plan.flops) / 1.3e9f);
+        if (h->kron) return kron_us(h->kron_dims, t);
+        if (h->lazy) return kron_us(h->lazy_dims, t) + (desc->workspace ? float(h->lazy_slice_bytes) / 1.6e6f : 0.f);
+        return 6.f * float(h->steps.size()) + float(t) * float(h->plan.flops) / 0.45e9f;
+    };
+    auto first_tokens = [&](float build_us) {
+        for (int64_t t = 8; t <= desc->max_tokens; t += t < 64 ? 8 : t / 8)
+            if (build_us + gemm_choice(h, y, t, kMaxPartialBytes).us < other_us(t)) return t;
+        return int64_t(0);
+    };
+    if (!first_tokens(6.f + float(h->plan.M) * float(h->plan.N) * 2.f / 3.5e6f)) return TN_OK;
+    tn::Plan net;
+    tn::MatrixPlan m;
+    if (!tn::make_matrix_plan(desc, &net, &m)) return TN_OK;
+    h->mat_bytes = m.w_elems * 2;
+    float us = 0.f;
+    for (int i = 0; i < 2; ++i) {
+        h->mat_build[i] = m.half[i].tensors.size() == 2;
+        if (!h->mat_build[i]) continue;
+        h->mat_half_off[i] = h->mat_bytes;
+        h->mat_bytes += (m.half[i].build.out_elems * 2 + 255) & ~int64_t(255);
+        fill_product_step(&h->mat_half[i].s, m.half[i].build);
+        us += product_us(h, h->mat_half[i].s);
+    }
+    fill_product_step(&h->mat_w.s, m.w);
+    us += product_us(h, h->mat_w.s);
+    h->mat_flops = 2 * m.w.R * m.w.C * m.w.K;
+    for (int i = 0; i < 2; ++i)
+        if (h->mat_build[i]) h->mat_flops += 2 * m.half[i].build.R * m.half[i].build.C * m.half[i].build.K;
+    const int64_t from = first_tokens(us);
+    if (!from) return TN_OK;
+    // room in the workspace: beside what else is kept there, or sharing a caller's block with it
+    const int64_t room = desc->workspace
+                             ? desc->workspace_bytes - (desc->flags & TN_FLAG_NO_SPLIT_K ? 0 : std::min<int64_t>(kMaxPartialBytes, desc->workspace_bytes / 4)) - 512
+                             : (desc->workspace_limit_bytes > 0 ? desc->workspace_limit_bytes : kDefaultWorkspaceBytes) -
+                                   (h->lazy ? h->lazy_slice_bytes : 0) - 2 * h->plan.max_intermediate * h->elt;
+    if (h->mat_bytes > room) return TN_OK;
+    // tables: rows and columns of the three products, then of Y
+    std::vector<int32_t> tab;
+    size_t at[8];
+    auto put = [&](int i, const std::vector<int32_t>& v) {
+        at[i] = tab.size();
+        tab.insert(tab.end(), v.begin(), v.end());
+    };
+    for (int i = 0; i < 2; ++i) {
+        put(2 * i, m.half[i].build.row_off);
+        put(2 * i + 1, m.half[i].build.col_off);
+    }
+    put(4, m.w.row_off);
+    put(5, m.w.col_off);
+    put(6, {0});
+    std::vector<int32_t> cols(size_t(m.M));
+    for (int64_t c = 0; c < m.M; ++c) cols[size_t(c)] = int32_t(c);
+    put(7, cols);
+    void* tables = nullptr;
+    if (hipMalloc(&tables, tab.size() * sizeof(int32_t)) != hipSuccess) return TN_ERR_ALLOC;
+    h->mat_kept.push_back(tables);
+    if (hipMemcpyAsync(tables, tab.data(), tab.size() * sizeof(int32_t), hipMemcpyHostToDevice, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+        return TN_ERR_HIP;
+    auto set_tables = [&](DevStep* s, int i) {
+        s->crow = static_cast<const int32_t*>(tables) + at[i];
+        s->ccol = static_cast<const int32_t*>(tables) + at[i + 1];
+    };
+    for (int i = 0; i < 2; ++i) {
+        const tn::MatrixHalf& H = m.half[i];
+        int rc;
+        void* p = nullptr;
+        if (!h->mat_build[i]) {
+            rc = keep_operand(h, desc, H.keep, m.Krp, i == 1, &p, st);
+            if (i == 0) h->mat_w.a = p;
+            else h->mat_w.s.packed = p;
+        } else {
+            set_tables(&h->mat_half[i].s, 2 * i);
+            rc = keep_operand(h, desc, H.build.a, H.build.Kp, false, &p, st);
+            h->mat_half[i].a = p;
+            if (rc == TN_OK) rc = keep_operand(h, desc, H.build.b, H.build.Kp, true, &h->mat_half[i].s.packed, st);
+        }
+        if (rc != TN_OK) return rc;
+    }
+    set_tables(&h->mat_w.s, 4);
+    set_tables(&y, 6);
+    h->matrix = true;
+    h->mat_min_tokens = from;
+    return TN_OK;
+}
+
+// Where W and the halves are.
+void place_matrix(tn_linear_s* h, void* mem) {
+    char* base = static_cast<char*>(mem);
+    h->mat_mem = mem;
+    h->mat_w.out = base;
+    h->mat_y.packed = base;
+    for (int i = 0; i < 2; ++i)
+        if (h->mat_build[i]) {
+            void* half = base + h->mat_half_off[i];
+            h->mat_half[i].out = half;
+            if (i == 0) h->mat_w.a = half;
+            else h->mat_w.s.packed = half;
+        }
+}
+
 // Pairs of steps the transposing chain kernel can run (see step_chain2_kernel): both plain, the
 // first step's output stored transposed ([c1][r], which is what the second step reads as rows c1
 // with K = r), the output in aligned runs of 8 along c1 or along c2, and sizes within one of the
@@ -2290,6 +2546,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
         rc = prepare_lazy(h, desc, st);
         h->lazy_kept_bytes = h->packed_bytes - before;
     }
+    if (rc == TN_OK) rc = prepare_matrix(h, desc, st);
     if (rc == TN_OK && (desc->flags & TN_FLAG_TRAINABLE)) rc = prepare_backward(h, desc, st);
     if (rc != TN_OK) {
         (void)hipStreamSynchronize(st);
@@ -2308,6 +2565,9 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
     auto partial_need = [&](int64_t chunk) {
         int64_t need = 0;
         if (!split_ok) return need;
+        if (h->matrix)
+            for (int64_t t = h->mat_min_tokens; t <= std::min<int64_t>(h->max_tokens, 4096); t += std::max<int64_t>(1, t / 8))
+                need = std::max(need, gemm_choice(h, h->mat_y, t, kMaxPartialBytes).partial_bytes);
         if (h->kron) {
             for (int64_t t = 1; t <= std::min<int64_t>(h->max_tokens, 4 * int64_t(h->num_cus)); ++t)
                 need = std::max(need, kron_geometry(h, h->kron_dims, t, kMaxPartialBytes).partial_bytes);
@@ -2369,6 +2629,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
     // (one token's buffers stay: calls that may not use the rebuilt plan - profiled steps, the entry point that
     // allocates nothing - run the compact steps token by token)
     if (h->lazy) ws_tokens = std::min<int64_t>(ws_tokens, std::max<int64_t>(1, h->lazy_min_tokens - 1));
+    if (h->matrix) ws_tokens = std::min<int64_t>(ws_tokens, std::max<int64_t>(1, h->mat_min_tokens - 1));
     int64_t chunk = ws_tokens;
     if (desc->workspace) {
         // caller-owned block: [partial sums | buffer 0 | buffer 1], 256-byte aligned pieces
@@ -2393,9 +2654,20 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
             h->partial_bytes = part;
         }
         if (h->lazy) h->lazy_slices = base + part;
+        if (h->matrix) place_matrix(h, base + part);
         h->workspace_bytes = 0;
     } else {
         int64_t limit = desc->workspace_limit_bytes > 0 ? desc->workspace_limit_bytes : kDefaultWorkspaceBytes;
+        if (h->matrix) {
+            void* mem = nullptr;
+            if (hipMalloc(&mem, size_t(h->mat_bytes)) != hipSuccess) {
+                free_handle(h);
+                return TN_ERR_ALLOC;
+            }
+            place_matrix(h, mem);
+            h->workspace_bytes += h->mat_bytes;
+            limit -= h->mat_bytes;
+        }
         if (per_token > 0) {
             chunk = std::max<int64_t>(1, std::min<int64_t>(ws_tokens, limit / (2 * per_token)));
             chunk = std::max<int64_t>(1, std::min<int64_t>(chunk, row_cap));
@@ -2405,7 +2677,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
                     return TN_ERR_ALLOC;
                 }
             }
-            h->workspace_bytes = 2 * chunk * per_token;
+            h->workspace_bytes += 2 * chunk * per_token;
         } else {
             chunk = std::max<int64_t>(1, std::min<int64_t>(chunk, row_cap));
         }
@@ -2500,6 +2772,18 @@ int forward_in(tn_linear_s* h, const Workspace& w, bool allow_lazy, const void* 
         }
         return TN_OK;
     }
+    if (allow_lazy && h->matrix && tokens >= h->mat_min_tokens) {
+        int rc = launch_matrix_build(h, w.partial, w.partial_bytes, st);          // not part of the profiled launch
+        const int64_t pass = int64_t(1) << 20;
+        for (int64_t t0 = 0; t0 < tokens && rc == TN_OK; t0 += pass) {
+            ProfScope prof(h, 0, st);
+            if (!prof.ok) return TN_ERR_HIP;
+            rc = launch_matrix_y(h, xb + t0 * h->plan.N * h->elt, yb + t0 * h->plan.M * h->elt, std::min(pass, tokens - t0), w.partial,
+                                 w.partial_bytes, st);
+            prof.done();
+        }
+        return rc;
+    }
     const bool use_pair = h->pair && tokens >= h->pair_min_tokens;
     const bool use_kron = h->kron && tokens >= h->kron_min_tokens;
     const bool use_lazy = allow_lazy && h->lazy && tokens >= h->lazy_min_tokens;
@@ -2586,7 +2870,7 @@ int tn_linear_forward2(tn_linear_t ha, tn_linear_t hb, const void* x, void* ya, 
     auto per_step_path = [&](const tn_linear_s* h) {
         return !h->profiling && !(h->small_chain && (h->elt == 4 || tokens <= kSmallChainMaxBf16Tokens)) &&
                !(h->pair && tokens >= h->pair_min_tokens) && !(h->kron && tokens >= h->kron_min_tokens) &&
-               !(h->lazy && tokens >= h->lazy_min_tokens) && tokens <= h->chunk_tokens;
+               !(h->lazy && tokens >= h->lazy_min_tokens) && !(h->matrix && tokens >= h->mat_min_tokens) && tokens <= h->chunk_tokens;
     };
     bool together = ha != hb && per_step_path(ha) && per_step_path(hb) && ha->schedule.size() == hb->schedule.size();
     for (size_t li = 0; together && li < ha->schedule.size(); ++li) {
@@ -2806,6 +3090,8 @@ int tn_linear_query(tn_linear_t h, int32_t what, int64_t* value) {
         case TN_QUERY_CHUNK_TOKENS: *value = h->chunk_tokens; return TN_OK;
         case TN_QUERY_LAZY_MIN_TOKENS: *value = h->lazy ? h->lazy_min_tokens : 0; return TN_OK;
         case TN_QUERY_LAZY_FLOPS_PER_TOKEN: *value = h->lazy ? h->lazy_plan.flops : 0; return TN_OK;
+        case TN_QUERY_MATRIX_MIN_TOKENS: *value = h->matrix ? h->mat_min_tokens : 0; return TN_OK;
+        case TN_QUERY_MATRIX_BUILD_FLOPS: *value = h->matrix ? h->mat_flops : 0; return TN_OK;
         case TN_QUERY_QUANT_BYTES: *value = h->quant_bytes; return TN_OK;
         case TN_QUERY_QUANT_STREAM_BYTES: *value = h->q4_stream_bytes; return TN_OK;
         case TN_QUERY_BACKWARD_CHUNK_TOKENS: *value = h->trainable ? h->bwd_chunk : 0; return TN_OK;

@@ -8,7 +8,7 @@
 #include <cstdint>
 #include <vector>
 
-#include "../paper_2602_01613_amd/csrc/tn_plan.hpp"
+#include "../paper_2602_01613_amd/csrc/tn_matrix.hpp"
 
 extern "C" int plan_host_forward(const tn_linear_desc* d, const double* const* tensors, const double* x,
                                  double* y, int64_t tokens) {
@@ -112,4 +112,75 @@ extern "C" int plan_host_launch_buffers(const tn_linear_desc* d, int cap, int* i
         steps[i] = sched[i].steps;
     }
     return int(sched.size());
+}
+
+// The order that contracts the parameter tensors with each other first (tn_matrix.hpp), in double: W [M][N] as the packed
+// operand says it. Returns 1 when the layer has no such plan, negative when an output position is written twice or never
+// or lies outside.
+extern "C" int plan_host_matrix(const tn_linear_desc* d, const double* const* tensors, double* w_out) {
+    tn::Plan net;
+    tn::MatrixPlan m;
+    if (!tn::make_matrix_plan(d, &net, &m)) return 1;
+    auto operand = [&](const tn::SourceOp& o, int64_t r, int64_t k) {
+        int64_t off = 0;
+        auto walk = [&](const std::vector<tn::SourceDim>& dims, int64_t f) {
+            for (size_t j = dims.size(); j-- > 0;) {
+                const int64_t digit = f % dims[j].extent;
+                if (digit >= dims[j].limit) return false;
+                off += digit * dims[j].stride;
+                f /= dims[j].extent;
+            }
+            return true;
+        };
+        return walk(o.rows, r) && walk(o.ks, k) ? tensors[o.slot][off] : 0.0;
+    };
+    int bad = 0;
+    auto store = [&](std::vector<double>* out, std::vector<char>* hit, const tn::Product& p, int64_t r, int64_t c, double v) {
+        const int64_t o = int64_t(p.row_off[size_t(r)]) + p.col_off[size_t(c)];
+        if (o < 0 || o >= int64_t(out->size()) || (*hit)[size_t(o)]) {
+            bad = -1;
+            return;
+        }
+        (*hit)[size_t(o)] = 1;
+        (*out)[size_t(o)] = v;
+    };
+    std::vector<double> half[2];       // [modes][bond], in the half's own layout
+    for (int h = 0; h < 2; ++h) {
+        const tn::MatrixHalf& H = m.half[h];
+        if (H.tensors.size() == 1) {
+            half[h].assign(size_t((H.F + 255) / 256 * 256 * m.Krp), 0.0);
+            for (int64_t f = 0; f < H.F; ++f)
+                for (int64_t k = 0; k < H.keep.K; ++k)
+                    half[h][size_t(h == 0 ? f * m.Krp + k : tn::packed_col(f, m.Krp / 16) + tn::packed_k(k))] = operand(H.keep, f, k);
+            continue;
+        }
+        half[h].assign(size_t(H.build.out_elems), 0.0);
+        std::vector<char> hit(half[h].size(), 0);
+        for (int64_t r = 0; r < H.build.R; ++r)
+            for (int64_t c = 0; c < H.build.C; ++c) {
+                double acc = 0;
+                for (int64_t k = 0; k < H.build.K; ++k) acc += operand(H.build.a, r, k) * operand(H.build.b, c, k);
+                store(&half[h], &hit, H.build, r, c, acc);
+            }
+        int64_t n = 0;
+        for (char v : hit) n += v;
+        if (n != H.F * m.Krp) return -2;
+    }
+    std::vector<double> w(size_t(m.w_elems), 0.0);
+    std::vector<char> hit(w.size(), 0);
+    for (int64_t r = 0; r < m.w.R; ++r)
+        for (int64_t c = 0; c < m.w.C; ++c) {
+            double acc = 0;
+            for (int64_t k = 0; k < m.Krp; ++k)
+                acc += half[0][size_t(r * m.Krp + k)] * half[1][size_t(tn::packed_col(c, m.Krp / 16) + tn::packed_k(k))];
+            store(&w, &hit, m.w, r, c, acc);
+        }
+    if (bad) return bad;
+    for (int64_t i = 0; i < m.M; ++i)
+        for (int64_t j = 0; j < m.N; ++j) {
+            const size_t o = size_t(tn::packed_col(i, m.N / 16) + tn::packed_k(j));
+            if (!hit[o]) return -3;
+            w_out[i * m.N + j] = w[o];
+        }
+    return 0;
 }

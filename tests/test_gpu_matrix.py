@@ -1,0 +1,100 @@
+"""Calls of many tokens of trains and rings in the order that contracts the factors with each other first
+(TN_QUERY_MATRIX_MIN_TOKENS) against the fp64 oracle. Tolerance as for every bf16 layer: 2e-2 of the largest value, where one
+rounding of 2^-9 each for the halves, for W and for the result leave 3e-3."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import workloads as wl
+import paper_2602_01613_amd as tn
+from gpu_util import TOL, make_layer, to_dev, to_host
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (format, out modes, in modes, ranks, flags)
+    (tn.TN_FORMAT_TR, (8, 10, 8, 8), (8, 10, 8, 8), (16,) * 5, 0),                          # halves of 256 values of the bonds
+    (tn.TN_FORMAT_TR, (8, 10, 8, 8), (8, 10, 8, 8), (16, 24, 16, 8, 16), 0),                # bonds of different sizes
+    (tn.TN_FORMAT_TR, (4, 8, 4, 8), (8, 10, 8, 8), (32,) * 5, tn.TN_FLAG_TRANSPOSE),
+    (tn.TN_FORMAT_TR, (40, 8, 8), (8, 8, 40), (16, 32, 16, 16), 0),                         # three cores: a half of one, kept
+    (tn.TN_FORMAT_TT, (8, 10, 8, 8), (8, 10, 8, 8), (1, 64, 96, 64, 1), tn.TN_FLAG_TRAINABLE),   # a bond of 96, laid out as 128
+    (tn.TN_FORMAT_TT, (16, 8, 8), (8, 10, 16), (1, 128, 72, 1), tn.TN_FLAG_TRAINABLE),      # a bond of 72, a half of one core
+]
+
+
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_factors_first(case):
+    fmt, om, im, rk, flags = CASES[case]
+    spec = wl.TNSpec(fmt, "bf16", om, im, rk)
+    ts = wl.make_tensors(spec, 500 + case)
+    w = O.dense_weight(fmt, ts, len(om))
+    if flags & tn.TN_FLAG_TRANSPOSE:
+        w = w.T
+    layer = make_layer(spec, ts, 4200, flags=flags)
+    first = layer.query(tn.TN_QUERY_MATRIX_MIN_TOKENS)
+    assert 0 < first <= 4200, first
+    rng = np.random.default_rng(case)
+    again = None
+    for tokens in (first, first + 1, 1, 4200, 4201, 4200):          # the largest a layer is made for, and beyond; a small call between
+        x = wl.round_to_dtype(rng.standard_normal((tokens, w.shape[1])), "bf16") if tokens != 4200 or again is None else again[0]
+        yd = layer(to_dev(x, "bf16"))
+        assert O.rel_max_err(to_host(yd), O.apply_linear(w, x)) <= TOL["bf16"], (case, tokens)
+        if tokens == 4200:
+            if again is None:
+                again = (x, yd.clone())
+            else:
+                assert torch.equal(yd, again[1])                    # fixed-order sums, nothing left over from the calls between
+    layer.close()
+
+
+def test_shared_block_and_graph():
+    """W and the halves in a caller's block that another layer uses between the calls; the same calls as a HIP graph, replayed."""
+    specs = [wl.TNSpec(wl.FORMAT_TR, "bf16", (8, 10, 8, 8), (8, 10, 8, 8), (16,) * 5),
+             wl.TNSpec(wl.FORMAT_TT, "bf16", (8, 10, 8, 8), (8, 10, 8, 8), (1, 64, 96, 64, 1))]
+    block = torch.empty(256 << 20, dtype=torch.uint8, device="cuda")
+    layers, refs = [], []
+    for n, spec in enumerate(specs):
+        ts = wl.make_tensors(spec, 520 + n)
+        refs.append(O.dense_weight(spec.format, ts, 4))
+        layers.append(tn.TNLinear(spec.format, tn.TN_DTYPE_BF16, spec.out_modes, spec.in_modes, spec.ranks,
+                                  [to_dev(t, "bf16") for t in ts], 3000, workspace=block))
+        assert layers[-1].query(tn.TN_QUERY_WORKSPACE_BYTES) == 0
+    assert 0 < layers[0].query(tn.TN_QUERY_MATRIX_MIN_TOKENS) <= 3000
+    xd = torch.empty((3000, 5120), dtype=torch.bfloat16, device="cuda")
+    ys = [torch.empty((3000, 5120), dtype=torch.bfloat16, device="cuda") for _ in specs]
+    rng = np.random.default_rng(9)
+
+    def run():
+        for layer, y in zip(layers, ys):
+            layer.forward(xd, out=y)
+
+    run()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run()
+    for _ in range(3):
+        x = wl.round_to_dtype(rng.standard_normal((3000, 5120)), "bf16")
+        xd.copy_(to_dev(x, "bf16"))
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [y.clone() for y in ys]
+        run()
+        torch.cuda.synchronize()
+        for g, y, w in zip(got, ys, refs):
+            assert torch.equal(g, y)
+            assert O.rel_max_err(to_host(y), O.apply_linear(w, x)) <= TOL["bf16"]
+    for layer in layers:
+        layer.close()
+
+
+def test_no_room_for_w():
+    """A workspace too small for W: such calls run as before."""
+    spec = wl.TNSpec(wl.FORMAT_TR, "bf16", (8, 10, 8, 8), (8, 10, 8, 8), (16,) * 5)
+    ts = wl.make_tensors(spec, 530)
+    layer = make_layer(spec, ts, 300, workspace_limit_bytes=40 << 20)
+    assert layer.query(tn.TN_QUERY_MATRIX_MIN_TOKENS) == 0
+    x = wl.make_x(spec, 300, 530)
+    assert O.rel_max_err(to_host(layer(to_dev(x, "bf16"))), O.apply_linear(O.dense_weight(spec.format, ts, 4), x)) <= TOL["bf16"]
+    layer.close()

@@ -32,6 +32,8 @@ def host_exec():
     lib.plan_host_step_hint.restype = ctypes.c_int
     lib.plan_host_step_hint.argtypes = [ctypes.POINTER(_Desc), ctypes.c_int, ctypes.c_int,
                                         ctypes.POINTER(ctypes.c_int64)]
+    lib.plan_host_matrix.restype = ctypes.c_int
+    lib.plan_host_matrix.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p]
     return lib
 
 
@@ -397,3 +399,44 @@ def test_library_exports_every_declared_symbol():
     assert tn.tn_linear_version() == 6
     assert tn.tn_linear_strerror(0) == "success"
     assert "invalid" in tn.tn_linear_strerror(-1)
+
+
+MATRIX_CASES = [
+    # (format, out modes, in modes, ranks, has such a plan)
+    (tn.TN_FORMAT_TR, (4, 6, 2, 8), (2, 2, 4, 8), (8, 8, 8, 8, 8), True),            # two halves of two cores
+    (tn.TN_FORMAT_TR, (10, 4, 2, 8), (2, 2, 4, 8), (16, 8, 16, 8, 16), True),        # bonds of different sizes
+    (tn.TN_FORMAT_TR, (4, 2, 8), (8, 2, 8), (8, 16, 8, 8), True),                    # a half of one core
+    (tn.TN_FORMAT_TR, (4, 4, 4, 4), (4, 4, 4, 4), (6,) * 5, False),                  # 36 values of the bonds: not whole tiles
+    (tn.TN_FORMAT_TR, (8, 8), (8, 8), (8, 8, 8), True),                              # two cores
+    (tn.TN_FORMAT_TT, (4, 6, 2, 8), (2, 8, 4, 8), (1, 8, 12, 8, 1), True),           # a bond of 12, laid out as 64
+    (tn.TN_FORMAT_TT, (8, 4, 8), (4, 2, 8), (1, 5, 20, 1), True),
+    (tn.TN_FORMAT_TT, (10, 32), (10, 64), (1, 70, 1), True),                         # a bond of 70, laid out as 128
+    (tn.TN_FORMAT_TT, (5, 8), (16, 4), (1, 6, 1), False),                            # the last in-mode is no run of 8
+    (tn.TN_FORMAT_TT, (4, 9, 2), (2, 8, 16), (1, 8, 8, 1), False),                   # 9: digits that cross the blocks of 32
+    (tn.TN_FORMAT_TT, (2, 2, 3, 2, 4), (2, 2, 2, 2, 8), (1, 4, 4, 4, 4, 1), False),  # five cores: a half of three
+    (tn.TN_FORMAT_TT, (4, 6), (5, 8), (1, 4, 1), False),                             # 40 inputs: not whole tiles
+    (tn.TN_FORMAT_TR, (48,), (64,), (3, 3), False),                                  # a ring of one core
+    (tn.TN_FORMAT_TUCKER, (8, 8), (8, 8), (4, 4, 4, 4), False),
+    (tn.TN_FORMAT_DENSE, (64,), (64,), (), False),
+]
+
+
+@pytest.mark.parametrize("transpose", [0, tn.TN_FLAG_TRANSPOSE])
+@pytest.mark.parametrize("case", range(len(MATRIX_CASES)))
+def test_factors_contracted_with_each_other_first(host_exec, case, transpose):
+    """W as the plan's products build it (orders, digit offsets, packed layouts, padded bonds) against the oracle's. A plan
+    may also be refused (transposed, the other side's modes decide); it is never wrong."""
+    fmt, om, im, ranks, planned = MATRIX_CASES[case]
+    ts = [np.ascontiguousarray(t) for t in _rand_tensors(np.random.default_rng(300 + case), fmt, om, im, ranks)]
+    w_ref = O.dense_weight(fmt, ts, len(om))
+    if transpose:
+        w_ref = w_ref.T
+    d, keep = _make_desc(fmt, tn.TN_DTYPE_BF16, om, im, ranks, None, 1, 0, transpose, None)
+    ptrs = (ctypes.c_void_p * len(ts))(*[t.ctypes.data for t in ts])
+    w = np.zeros(w_ref.shape)
+    rc = host_exec.plan_host_matrix(ctypes.byref(d), ptrs, w.ctypes.data)
+    assert rc in (0, 1), rc
+    if not transpose:
+        assert (rc == 0) == planned
+    if rc == 0:
+        assert np.max(np.abs(w - w_ref)) <= 1e-12 * np.max(np.abs(w_ref))
