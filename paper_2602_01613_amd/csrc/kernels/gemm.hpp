@@ -34,10 +34,10 @@
 // ---------------------------------------------------------------------------------------------
 struct GemmArgs {
     int32_t n_row, n_col;          // output tiles
-    int32_t n_split;               // ranges of K; more than one: fp32 partial sums [split][rows_pad][Cp] (TRANS = 0)
+    int32_t n_split;               // ranges of K
     int32_t ktiles_per_split;      // K tiles of 64 per range, at least one in every range
-    int64_t rows_pad;
-    float* partial;
+    float* partial;                // not null: fp32 sums [split][rows_pad][ld] instead of the output (TRANS = 0, C % 4 == 0)
+    int64_t rows_pad, ld;
 };
 
 template <int TM, int TN>
@@ -101,7 +101,7 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
     };
     // output offsets of the tile's rows and columns; entries past the end repeat a valid one and are not used
     unsigned char* tab = dyn_smem + 2 * STAGE;
-    {
+    if (!g.partial) {
         const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.crow), 0, int(a.R) * 4, 0x00020000);
         const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.ccol), 0, a.C * 4, 0x00020000);
         if (wave * 64 < S::TAB_ROWS) {
@@ -182,15 +182,17 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
     }
     wait_vmcnt<0>();                                     // no load into LDS outlives the workgroup
 
-    if (g.n_split > 1) {
+    if (g.partial) {
         // lane: row l%16 of tile i, columns 4*(l/16) .. +3 of tile j
+        const int c = col0 + wn * TN * 16 + 4 * (lane >> 4);
 #pragma unroll
         for (int i = 0; i < TM; ++i) {
             const uint32_t r = row0 + wm * TM * 16 + i * 16 + (lane & 15);
-            float* p = g.partial + (int64_t(split) * g.rows_pad + r) * a.Cp + col0 + wn * TN * 16 + 4 * (lane >> 4);
+            float* p = g.partial + (int64_t(split) * g.rows_pad + r) * g.ld + c;
             if (r < a.total_rows) {
 #pragma unroll
-                for (int j = 0; j < TN; ++j) *reinterpret_cast<floatx4*>(p + j * 16) = acc[i][j];
+                for (int j = 0; j < TN; ++j)
+                    if (c + j * 16 < a.C) *reinterpret_cast<floatx4*>(p + j * 16) = acc[i][j];
             }
         }
         return;

@@ -260,29 +260,57 @@ __global__ void __launch_bounds__(256) grad_param_mfma_kernel(GradArgs a) {
 // step's packing recipe (PackArgs: digits of k and c times their strides); a tensor with a traced index pair (a
 // ring of one core) receives the value at every diagonal position and keeps zeros elsewhere (the caller's buffer
 // is cleared first by grad_fill_kernel).
+// Y waves share 64 neighbouring elements, each takes every Y-th split (one wave walking 512 splits of a 96 x 160 tensor took
+// 117 us, bound by the latency of its loads), and their sums are added in wave order: the order of the additions depends on
+// n_split alone.
 struct GradOutArgs {
     const float* partial;
     float* grad;
-    int32_t C, K, n_split, accumulate;
+    int64_t ld, split_stride;               // partial: elements from c to c + 1, from split to split
+    uint32_t C, K;
+    int32_t n_split, accumulate;
     int32_t nk, nc;
-    int64_t kext[tn::kMaxGatherDims], kstr[tn::kMaxGatherDims];
-    int64_t cext[tn::kMaxGatherDims], cstr[tn::kMaxGatherDims];
+    uint32_t kext[tn::kMaxGatherDims], cext[tn::kMaxGatherDims];
+    int64_t kstr[tn::kMaxGatherDims], cstr[tn::kMaxGatherDims];
     int64_t trace_extent, trace_stride;
 };
 
-__global__ void __launch_bounds__(256) grad_reduce_kernel(GradOutArgs a) {
-    const int64_t total = int64_t(a.C) * a.K;
-    for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < total; e += int64_t(gridDim.x) * 256) {
+template <int Y>
+__global__ void __launch_bounds__(Y > 4 ? 64 * Y : 256) grad_reduce_kernel(GradOutArgs a) {
+    constexpr int GROUPS = Y >= 4 ? 1 : 4 / Y;                 // sets of 64 elements a workgroup takes at a time
+    __shared__ float red[Y > 1 ? GROUPS * Y * 64 : 1];
+    const uint32_t total = a.C * a.K;                          // below 2^31 (checked by the host)
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, y = wave % Y, group = wave / Y;
+    for (uint32_t e0 = (blockIdx.x * GROUPS + group) * 64u; e0 - uint32_t(group) * 64u < total; e0 += gridDim.x * GROUPS * 64u) {
+        const uint32_t e = e0 + lane;
+        uint32_t c = e / a.K, k = e - c * a.K;
         float sum = 0.f;
-        for (int s = 0; s < a.n_split; ++s) sum += a.partial[int64_t(s) * total + e];
-        int64_t c = e / a.K, k = e - c * a.K, off = 0;
+        if (e < total) {
+            const float* p = a.partial + int64_t(c) * a.ld + k;
+#pragma unroll 8
+            for (int s = y; s < a.n_split; s += Y) sum += p[int64_t(s) * a.split_stride];
+        }
+        if (Y > 1) {
+            red[(group * Y + y) * 64 + lane] = sum;
+            __syncthreads();
+            if (y == 0) {
+                sum = 0.f;
+#pragma unroll
+                for (int j = 0; j < Y; ++j) sum += red[(group * Y + j) * 64 + lane];
+            }
+            __syncthreads();
+        }
+        if (y != 0 || e >= total) continue;
+        int64_t off = 0;
         for (int j = a.nk - 1; j >= 0; --j) {
-            off += (k % a.kext[j]) * a.kstr[j];
-            k /= a.kext[j];
+            const uint32_t q = k / a.kext[j];
+            off += int64_t(k - q * a.kext[j]) * a.kstr[j];
+            k = q;
         }
         for (int j = a.nc - 1; j >= 0; --j) {
-            off += (c % a.cext[j]) * a.cstr[j];
-            c /= a.cext[j];
+            const uint32_t q = c / a.cext[j];
+            off += int64_t(c - q * a.cext[j]) * a.cstr[j];
+            c = q;
         }
         for (int64_t d = 0; d < a.trace_extent; ++d) {
             float* p = a.grad + off + d * a.trace_stride;

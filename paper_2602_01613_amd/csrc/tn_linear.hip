@@ -36,6 +36,7 @@ namespace {
 
 #include "kernels/common.hpp"
 #include "kernels/pack.hpp"
+#include "kernels/transpose.hpp"
 #include "kernels/quant.hpp"
 #include "kernels/tiled.hpp"
 #include "kernels/gemm.hpp"
@@ -167,6 +168,21 @@ struct tn_linear_s {
     int64_t bwd_chunk = 0, bwd_ws_bytes = 0;
     float* bwd_partial = nullptr;
     int64_t bwd_partial_bytes = 0;
+    // gradients of many tokens: dW = dY^T X, and from it those of the tensors on the cut of tn_matrix.hpp (a dense layer's
+    // tensor is W)
+    bool mgrad = false;
+    int64_t mgrad_min_tokens = 0, mgrad_chunk = 0;
+    int64_t mgrad_f[2] = {0, 0};              // modes of the halves
+    int64_t mgrad_off[8] = {};                // byte offsets in bwd_ws: X, dY, dW, dW transposed, the two operands, dH, dH transposed
+    DevStep mgrad_dw;                         // rows m, columns n; K, A and B are the call's
+    struct GradHalf {
+        bool pair = false;
+        DevProduct op;                        // this half as the operand of the other one's gradient
+        DevStep dh;                           // its gradient: rows its modes, columns the bond
+        int64_t F1 = 0, F2 = 0, S = 0;
+        void *a = nullptr, *b = nullptr;      // packed [S][F1 padded], [S][F2]
+        tn::GradOut out_a, out_b;
+    } mgrad_half[2];
     struct ProfRec { int step; hipEvent_t start, stop; };
     std::vector<ProfRec> prof;
 };
@@ -525,11 +541,21 @@ bool gemm_fits(const DevStep& s) {
     return s.variant == VAR_GEMM && s.cmode != 0 && (256 / s.plan.R + 2) * s.plan.c_tok_stride * 2 < (int64_t(1) << 31);
 }
 
+// fp32 sums instead of the output: where they went.
+struct GemmSums {
+    float* sums = nullptr;         // [n_split][rows][ld]
+    int64_t ld = 0;
+    int n_split = 1;
+};
+
+// With `f32` the launch leaves its fp32 sums in `partial` (or at f32->sums, as one range with rows of f32->ld).
 int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64_t rows, void* partial, int64_t partial_bytes,
-                hipStream_t st) {
+                hipStream_t st, GemmSums* f32 = nullptr) {
     const bool trans = s.cmode == 2;
-    const GemmChoice c = gemm_choice(h, s, rows, (h->flags & TN_FLAG_NO_SPLIT_K) || !partial ? 0 : partial_bytes);
+    const bool one_range = (h->flags & TN_FLAG_NO_SPLIT_K) || !partial || (f32 && f32->sums);
+    const GemmChoice c = gemm_choice(h, s, rows, one_range ? 0 : partial_bytes);
     if (c.tile < 0) return TN_ERR_UNSUPPORTED;
+    if (f32 && !f32->sums && (!partial || int64_t(c.n_split) * rows * s.Cp * 4 > partial_bytes)) return TN_ERR_UNSUPPORTED;
     const GemmTile& t = kGemmTile[c.tile];
     GemmArgs g;
     g.n_row = int32_t((rows + 32 * t.tm - 1) / (32 * t.tm));
@@ -537,10 +563,18 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
     g.n_split = c.n_split;
     g.ktiles_per_split = c.ktiles_per_split;
     g.rows_pad = rows;
-    g.partial = static_cast<float*>(partial);
+    g.ld = s.Cp;
+    g.partial = c.n_split > 1 || f32 ? static_cast<float*>(partial) : nullptr;
+    if (f32) {
+        if (f32->sums) {
+            g.partial = f32->sums;
+            g.ld = f32->ld;
+        }
+        *f32 = GemmSums{g.partial, g.ld, c.n_split};
+    }
     const int64_t items = int64_t(g.n_row) * g.n_col * g.n_split;
     hipLaunchKernelGGL(gemm_kernel(c.tile, trans), dim3(uint32_t((items + 7) / 8 * 8)), dim3(256), gemm_smem(c.tile), st, a, g);
-    if (c.n_split > 1) {
+    if (c.n_split > 1 && !f32) {
         const int64_t total = rows * s.plan.C;
         hipLaunchKernelGGL(step_split_reduce_kernel, dim3(uint32_t(std::min<int64_t>((total + 255) / 256, 2048))), dim3(256), 0, st,
                            a, g.partial, c.n_split, uint32_t(rows));
@@ -548,23 +582,28 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
     return TN_OK;
 }
 
-// One product of the matrix plan.
-int launch_product(const tn_linear_s* h, const DevProduct& p, void* partial, int64_t partial_bytes, hipStream_t st) {
+// One product of the matrix plan: out[crow[r] + ccol[c]] = sum_k A[r][k] B[c][k], or its fp32 sums.
+int launch_product_of(const tn_linear_s* h, const DevStep& s, const void* A, const void* B, void* out, void* partial,
+                      int64_t partial_bytes, hipStream_t st, GemmSums* f32 = nullptr) {
     StepArgs a{};
-    a.A = p.a;
-    a.B = p.s.packed;
-    a.Out = p.out;
-    a.crow = p.s.crow;
-    a.ccol = p.s.ccol;
-    a.total_rows = uint32_t(p.s.plan.R);
-    a.R = uint32_t(p.s.plan.R);
-    a.K = p.s.Kp;
-    a.Kp = p.s.Kp;
-    a.C = int32_t(p.s.plan.C);
-    a.Cp = p.s.Cp;
-    const int rc = launch_gemm(h, p.s, a, p.s.plan.R, partial, partial_bytes, st);
+    a.A = A;
+    a.B = B;
+    a.Out = out;
+    a.crow = s.crow;
+    a.ccol = s.ccol;
+    a.total_rows = uint32_t(s.plan.R);
+    a.R = uint32_t(s.plan.R);
+    a.K = s.Kp;
+    a.Kp = s.Kp;
+    a.C = int32_t(s.plan.C);
+    a.Cp = s.Cp;
+    const int rc = launch_gemm(h, s, a, s.plan.R, partial, partial_bytes, st, f32);
     if (rc != TN_OK) return rc;
     return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
+}
+
+int launch_product(const tn_linear_s* h, const DevProduct& p, void* partial, int64_t partial_bytes, hipStream_t st) {
+    return launch_product_of(h, p.s, p.a, p.s.packed, p.out, partial, partial_bytes, st);
 }
 
 // W from the layer's tensors, then Y = X W^T.
@@ -2177,18 +2216,43 @@ int prepare_backward(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st)
     for (const auto& s : h->steps) max_r = std::max(max_r, s.plan.R);
     const int64_t limit = desc->workspace_limit_bytes > 0 ? desc->workspace_limit_bytes : kDefaultWorkspaceBytes;
     int64_t chunk = h->max_tokens;
+    if (h->mgrad) chunk = std::min<int64_t>(chunk, std::max<int64_t>(1, h->mgrad_min_tokens - 1));      // larger calls go through dW
     if (per_token > 0) chunk = std::min<int64_t>(chunk, std::max<int64_t>(1, limit / per_token));
     chunk = std::max<int64_t>(1, std::min<int64_t>(chunk, ((int64_t(1) << 31) - 1024) / max_r));
     h->bwd_chunk = chunk;
-    h->bwd_ws_bytes = std::max<int64_t>(256, chunk * per_token);
+    h->bwd_ws_bytes = std::max<int64_t>(std::max<int64_t>(256, h->bwd_ws_bytes), chunk * per_token);
     if (hipMalloc(&h->bwd_ws, size_t(h->bwd_ws_bytes)) != hipSuccess) return TN_ERR_ALLOC;
-    int64_t need = 0;
+    int64_t need = h->bwd_partial_bytes;
     for (const auto& s : h->steps)
         need = std::max(need, int64_t(grad_splits(h, s.plan, chunk * s.plan.R, kMaxGradPartialBytes)) * s.plan.C * s.plan.K * 4);
     h->bwd_partial_bytes = need;
     if (hipMalloc(reinterpret_cast<void**>(&h->bwd_partial), size_t(need)) != hipSuccess) return TN_ERR_ALLOC;
     h->trainable = true;
     return TN_OK;
+}
+
+void fill_grad_dims(GradOutArgs* o, const std::vector<tn::GatherDim>& rows, const std::vector<tn::GatherDim>& cols) {
+    o->nc = int32_t(rows.size());
+    o->nk = int32_t(cols.size());
+    for (size_t j = 0; j < rows.size(); ++j) {
+        o->cext[j] = uint32_t(rows[j].extent);
+        o->cstr[j] = rows[j].stride;
+    }
+    for (size_t j = 0; j < cols.size(); ++j) {
+        o->kext[j] = uint32_t(cols[j].extent);
+        o->kstr[j] = cols[j].stride;
+    }
+}
+
+// Waves that share an element's splits: measured on 512 splits of 96 x 160 (and on 8 of 9216 x 2304, where one is best).
+int launch_grad_reduce(const GradOutArgs& o, hipStream_t st) {
+    const int64_t total = int64_t(o.C) * o.K;
+    if (total >= (int64_t(1) << 31)) return TN_ERR_UNSUPPORTED;
+    auto blocks = [&](int64_t per) { return dim3(uint32_t(std::min<int64_t>((total + per - 1) / per, 16384))); };
+    if (o.n_split >= 64) hipLaunchKernelGGL(grad_reduce_kernel<16>, blocks(64), dim3(1024), 0, st, o);
+    else if (o.n_split >= 16) hipLaunchKernelGGL(grad_reduce_kernel<4>, blocks(64), dim3(256), 0, st, o);
+    else hipLaunchKernelGGL(grad_reduce_kernel<1>, blocks(256), dim3(256), 0, st, o);
+    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
 
 // dP of one step from dOut and the step's saved input, into the caller's tensor.
@@ -2240,24 +2304,267 @@ int launch_param_gradient(const tn_linear_s* h, const DevStep& s, const void* dO
     memset(&o, 0, sizeof(o));
     o.partial = h->bwd_partial;
     o.grad = grad;
-    o.C = int32_t(p.C);
-    o.K = int32_t(p.K);
+    o.C = uint32_t(p.C);
+    o.K = uint32_t(p.K);
+    o.ld = p.K;
+    o.split_stride = p.C * p.K;
     o.n_split = n_split;
     o.accumulate = accumulate ? 1 : 0;
-    o.nk = int32_t(p.kdims.size());
-    o.nc = int32_t(p.cdims.size());
-    for (int j = 0; j < o.nk; ++j) {
-        o.kext[j] = p.kdims[size_t(j)].extent;
-        o.kstr[j] = p.kdims[size_t(j)].stride;
-    }
-    for (int j = 0; j < o.nc; ++j) {
-        o.cext[j] = p.cdims[size_t(j)].extent;
-        o.cstr[j] = p.cdims[size_t(j)].stride;
-    }
+    fill_grad_dims(&o, p.cdims, p.kdims);
     o.trace_extent = p.trace_extent;
     o.trace_stride = p.trace_stride;
-    const int64_t total = p.C * p.K;
-    hipLaunchKernelGGL(grad_reduce_kernel, dim3(uint32_t(std::min<int64_t>((total + 255) / 256, 8192))), dim3(256), 0, st, o);
+    return launch_grad_reduce(o, st);
+}
+
+// ---- the same gradients through dW ----
+constexpr int64_t kGradMinTokens = 16;        // one token range is padded to 64
+constexpr int kGradSumsPad = 128;             // columns of the core gradients (a bond): padded to the narrow tiles
+
+int64_t grad_tokens_pad(int64_t tokens) { return (tokens + 63) / 64 * 64; }
+
+void launch_transpose(const void* src, void* dst, int64_t T, int64_t D, int64_t Tp, bool packed, hipStream_t st) {
+    TransposeArgs a{static_cast<const bf16_t*>(src), static_cast<bf16_t*>(dst), T, D, Tp, packed ? 1 : 0};
+    hipLaunchKernelGGL(transpose_kernel, dim3(uint32_t((D + 63) / 64), uint32_t(Tp / 64)), dim3(256), 0, st, a);
+}
+
+// Decide whether gradients of many tokens go through dW, and prepare it. The steps are priced at 0.35e9 FLOP per us and 40 us
+// a step (train 5120 -> 8192 of rank 64: 9.7 ms at 1024 tokens; ring 25600 -> 5120 of rank 32: 12.5 ms at 64).
+int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
+    const int64_t M = h->plan.M, N = h->plan.N;
+    if (h->plan.dtype != TN_DTYPE_BF16 || N % 64 || M % 8 || desc->max_tokens < kGradMinTokens ||
+        (desc->flags & (TN_FLAG_SCALAR_KERNELS | TN_FLAG_NO_MERGE | TN_FLAG_NO_LAZY_MERGE)) ||
+        ((desc->flags >> TN_FLAG_VARIANT_SHIFT) & 0xff) != 0)
+        return TN_OK;
+    const bool dense = h->plan.format == TN_FORMAT_DENSE;
+    if (dense && (desc->flags & TN_FLAG_TRANSPOSE)) return TN_OK;
+    tn::Plan net;
+    tn::MatrixPlan m;
+    tn::MatrixGrad g;
+    if (!dense && (!tn::make_matrix_plan(desc, &net, &m) || !tn::make_matrix_grad(net, m, &g))) return TN_OK;
+    auto step = [&](DevStep* s, int64_t R, int64_t K, int64_t C, int64_t out_elems, int pad) {
+        s->plan.R = R;
+        s->plan.K = K;
+        s->plan.C = C;
+        s->plan.c_tok_stride = out_elems;
+        s->variant = VAR_GEMM;
+        s->cmode = 1;
+        s->Kp = int(K);
+        s->Cp = round_up(int(C), pad);
+    };
+    if (M > (int64_t(1) << 24) || M * N > tn::kMatrixMaxElems) return TN_OK;
+    step(&h->mgrad_dw, M, 64, N, M * N, tn::kMatrixColPad);
+    // what a call moves beside its products, their times, and the memory it works in
+    int64_t fixed = 0;
+    auto room = [&](int i, int64_t elems) {
+        h->mgrad_off[i] = fixed;
+        fixed += (elems * 2 + 255) & ~int64_t(255);
+    };
+    float us = 20.f;
+    int64_t sums = 0;
+    if (!dense) {
+        room(2, M * N);
+        room(3, M * N);
+        us += float(M * N) * 6.f / 3.5e6f;
+        int64_t dh = 0, dht = 0;
+        for (int i = 0; i < 2; ++i) {
+            const tn::MatrixGradHalf& G = g.half[i];
+            auto& H = h->mgrad_half[i];
+            const int64_t F = m.half[i].F, Fo = m.half[1 - i].F;
+            h->mgrad_f[i] = F;
+            H.pair = G.pair;
+            H.F1 = G.F1;
+            H.F2 = G.F2;
+            H.S = G.pair ? G.a.R : 0;
+            H.out_a = G.out_a;
+            H.out_b = G.out_b;
+            step(&H.dh, F, Fo, m.Kr, F * m.Kr, G.pair ? tn::kMatrixColPad : kGradSumsPad);
+            us += 3.f + std::max(gemm_choice(h, H.dh, F, kMaxGradPartialBytes).us, float(F * (Fo + m.Kr)) * 2.f / 3.5e6f);
+            if (!G.pair) {
+                sums = std::max(sums, F * H.dh.Cp * 4);
+                continue;
+            }
+            if (F * m.Kr > tn::kMatrixMaxElems) return TN_OK;
+            fill_product_step(&H.op.s, G.op);
+            us += product_us(h, H.op.s);
+            room(4 + i, G.op.out_elems);
+            dh = std::max(dh, G.F1 * G.F2);
+            dht = std::max(dht, tn::detail::round64(G.F1) * G.F2);
+            sums = std::max(sums, std::max(G.F1, G.F2) * round_up(int(H.S), kGradSumsPad) * 4);
+            us += 60.f + float(G.F1 * G.F2) * 6.f / 3.5e6f;
+        }
+        room(6, dh);
+        room(7, dht);
+    }
+    // tokens per pass: X and dY transposed, tokens padded to 64
+    const int64_t limit = desc->workspace_limit_bytes > 0 ? desc->workspace_limit_bytes : kDefaultWorkspaceBytes;
+    const int64_t x_row = (N + tn::kMatrixColPad - 1) / tn::kMatrixColPad * tn::kMatrixColPad * 2, y_row = M * 2;
+    int64_t chunk = grad_tokens_pad(desc->max_tokens);
+    chunk = std::min<int64_t>(chunk, (limit - fixed - 512) / (x_row + y_row) / 64 * 64);
+    if (limit < fixed || chunk < 64) return TN_OK;
+    int64_t from = 0;
+    const float flops = 3.f * float(h->plan.flops);
+    for (int64_t t = kGradMinTokens; t <= desc->max_tokens && !from; t += t < 64 ? 8 : t / 8) {
+        DevStep dw = h->mgrad_dw;
+        dw.Kp = int(grad_tokens_pad(std::min(t, chunk)));
+        const float product = std::max(gemm_choice(h, dw, M, 0).us, float(M * N) * (dense ? 4.f : 2.f) / 3.5e6f);
+        if (us + product + float(t) * float(M + N) * 4.f / 3.5e6f < float(t) * flops / 0.35e9f + 40.f * float(h->steps.size())) from = t;
+    }
+    if (!from) return TN_OK;
+    h->mgrad_off[0] = fixed;
+    h->mgrad_off[1] = fixed + ((chunk * x_row + 255) & ~int64_t(255));
+    // tables, and the operands kept
+    std::vector<int32_t> tab;
+    auto put = [&](const std::vector<int32_t>& v) {
+        const size_t at = tab.size();
+        tab.insert(tab.end(), v.begin(), v.end());
+        return at;
+    };
+    std::vector<std::pair<DevStep*, std::pair<size_t, size_t>>> where;
+    auto tables_of = [&](DevStep* s, const std::vector<int32_t>& r, const std::vector<int32_t>& c) {
+        const size_t ra = put(r);
+        where.push_back({s, {ra, put(c)}});
+    };
+    if (!dense) {
+        tables_of(&h->mgrad_dw, g.dw_row, g.dw_col);
+        for (int i = 0; i < 2; ++i) {
+            auto& H = h->mgrad_half[i];
+            if (!H.pair) continue;          // its gradient is left as sums, which use no tables
+            tables_of(&H.dh, g.half[i].row_off, g.half[i].col_off);
+            tables_of(&H.op.s, g.half[i].op.row_off, g.half[i].op.col_off);
+        }
+    }
+    void* tables = nullptr;
+    if (hipMalloc(&tables, std::max<size_t>(1, tab.size()) * sizeof(int32_t)) != hipSuccess) return TN_ERR_ALLOC;
+    h->mat_kept.push_back(tables);
+    if (hipMemcpyAsync(tables, tab.data(), tab.size() * sizeof(int32_t), hipMemcpyHostToDevice, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+        return TN_ERR_HIP;
+    for (auto& w : where) {
+        w.first->crow = static_cast<const int32_t*>(tables) + w.second.first;
+        w.first->ccol = static_cast<const int32_t*>(tables) + w.second.second;
+    }
+    for (int i = 0; i < 2 && !dense; ++i) {
+        auto& H = h->mgrad_half[i];
+        const tn::MatrixGradHalf& G = g.half[i];
+        int rc;
+        if (!H.pair) {
+            rc = keep_operand(h, desc, G.op_keep, G.op_keep.K, true, &H.op.s.packed, st);
+        } else {
+            void* a = nullptr;
+            rc = keep_operand(h, desc, G.op.a, G.op.Kp, false, &a, st);
+            H.op.a = a;
+            if (rc == TN_OK) rc = keep_operand(h, desc, G.op.b, G.op.Kp, true, &H.op.s.packed, st);
+            if (rc == TN_OK) rc = keep_operand(h, desc, G.a, tn::detail::round64(G.F1), true, &H.a, st);
+            if (rc == TN_OK) rc = keep_operand(h, desc, G.b, G.F2, true, &H.b, st);
+        }
+        if (rc != TN_OK) return rc;
+    }
+    h->mgrad = true;
+    h->mgrad_min_tokens = from;
+    h->mgrad_chunk = chunk;
+    h->bwd_ws_bytes = h->mgrad_off[1] + chunk * y_row;
+    if (dense) sums = M * h->mgrad_dw.Cp * 4;
+    else sums = std::max(sums, std::min(kMaxGradPartialBytes, std::max(4 * sums, kMaxPartialBytes)));
+    h->bwd_partial_bytes = sums;
+    return TN_OK;
+}
+
+int reduce_sums(const GemmSums& f, const tn::GradOut& out, int64_t rows, int64_t cols, float* grad, bool accumulate, hipStream_t st) {
+    GradOutArgs o;
+    memset(&o, 0, sizeof(o));
+    o.partial = f.sums;
+    o.grad = grad;
+    o.C = uint32_t(rows);
+    o.K = uint32_t(cols);
+    o.ld = f.ld;
+    o.split_stride = rows * f.ld;
+    o.n_split = f.n_split;
+    o.accumulate = accumulate ? 1 : 0;
+    fill_grad_dims(&o, out.rows, out.cols);
+    o.trace_extent = 1;
+    return launch_grad_reduce(o, st);
+}
+
+int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const* grads, int64_t tokens, hipStream_t st) {
+    char* base = static_cast<char*>(h->bwd_ws);
+    auto at = [&](int i) -> void* { return base + h->mgrad_off[i]; };
+    const bool dense = h->plan.format == TN_FORMAT_DENSE;
+    const int64_t M = h->plan.M, N = h->plan.N;
+    void* part = h->bwd_partial;
+    const int64_t part_bytes = h->bwd_partial_bytes;
+    bool wanted[2] = {false, false};
+    for (int i = 0; i < 2 && !dense; ++i) {
+        const auto& H = h->mgrad_half[i];
+        wanted[i] = grads[H.out_a.slot] || (H.pair && grads[H.out_b.slot]);
+    }
+    if (dense ? !grads[0] : !(wanted[0] || wanted[1])) return TN_OK;
+    for (int i = 0; i < 2 && !dense; ++i)
+        if (wanted[1 - i] && h->mgrad_half[i].pair) {
+            const int rc = launch_product_of(h, h->mgrad_half[i].op.s, h->mgrad_half[i].op.a, h->mgrad_half[i].op.s.packed, at(4 + i), part,
+                                             part_bytes, st);
+            if (rc != TN_OK) return rc;
+        }
+    for (int64_t t0 = 0; t0 < tokens; t0 += h->mgrad_chunk) {
+        const int64_t nt = std::min(h->mgrad_chunk, tokens - t0), tp = grad_tokens_pad(nt);
+        const bool add = t0 > 0;
+        launch_transpose(static_cast<const char*>(x) + t0 * N * h->elt, at(0), nt, N, tp, true, st);
+        launch_transpose(static_cast<const char*>(dy) + t0 * M * h->elt, at(1), nt, M, tp, false, st);
+        DevStep dw = h->mgrad_dw;
+        dw.plan.K = tp;
+        dw.Kp = int(tp);
+        int rc;
+        if (dense) {
+            // the gradient is dW: straight into the caller's tensor, or added to it from the sums of a later pass
+            GemmSums f;
+            const bool direct = !add && (reinterpret_cast<uintptr_t>(grads[0]) & 15) == 0;       // stored in pieces of 16 bytes
+            if (direct) f = GemmSums{static_cast<float*>(grads[0]), N, 1};
+            rc = launch_product_of(h, dw, at(1), at(0), nullptr, part, part_bytes, st, &f);
+            if (rc == TN_OK && !direct) {
+                tn::GradOut out;
+                out.rows = {{M, N}};
+                out.cols = {{N, 1}};
+                rc = reduce_sums(f, out, M, N, static_cast<float*>(grads[0]), add, st);
+            }
+            if (rc != TN_OK) return rc;
+            continue;
+        }
+        rc = launch_product_of(h, dw, at(1), at(0), at(2), part, part_bytes, st);
+        if (rc != TN_OK) return rc;
+        if (wanted[1]) launch_transpose(at(2), at(3), h->mgrad_f[0], h->mgrad_f[1], h->mgrad_f[0], false, st);
+        for (int i = 0; i < 2; ++i) {
+            if (!wanted[i]) continue;
+            const auto& H = h->mgrad_half[i];
+            const auto& O = h->mgrad_half[1 - i];
+            const void* op = O.pair ? at(4 + 1 - i) : O.op.s.packed;
+            if (!H.pair) {
+                GemmSums f;
+                rc = launch_product_of(h, H.dh, at(2 + i), op, nullptr, part, part_bytes, st, &f);
+                if (rc == TN_OK) rc = reduce_sums(f, H.out_a, h->mgrad_f[i], H.dh.plan.C, static_cast<float*>(grads[H.out_a.slot]), add, st);
+                if (rc != TN_OK) return rc;
+                continue;
+            }
+            rc = launch_product_of(h, H.dh, at(2 + i), op, at(6), part, part_bytes, st);
+            if (rc != TN_OK) return rc;
+            for (int side = 0; side < 2; ++side) {
+                float* grad = static_cast<float*>(grads[side == 0 ? H.out_a.slot : H.out_b.slot]);
+                if (!grad) continue;
+                const int64_t f1p = tn::detail::round64(H.F1);
+                if (side == 1) launch_transpose(at(6), at(7), H.F1, H.F2, f1p, false, st);
+                DevStep s;
+                s.plan.R = side == 0 ? H.F1 : H.F2;
+                s.plan.C = H.S;
+                s.plan.K = side == 0 ? H.F2 : f1p;
+                s.Kp = int(s.plan.K);
+                s.Cp = round_up(int(H.S), kGradSumsPad);
+                s.cmode = 1;
+                s.variant = VAR_GEMM;
+                GemmSums f;
+                rc = launch_product_of(h, s, side == 0 ? at(6) : at(7), side == 0 ? H.b : H.a, nullptr, part, part_bytes, st, &f);
+                if (rc == TN_OK) rc = reduce_sums(f, side == 0 ? H.out_a : H.out_b, s.plan.R, H.S, grad, add, st);
+                if (rc != TN_OK) return rc;
+            }
+        }
+    }
     return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
 
@@ -2547,7 +2854,10 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
         h->lazy_kept_bytes = h->packed_bytes - before;
     }
     if (rc == TN_OK) rc = prepare_matrix(h, desc, st);
-    if (rc == TN_OK && (desc->flags & TN_FLAG_TRAINABLE)) rc = prepare_backward(h, desc, st);
+    if (rc == TN_OK && (desc->flags & TN_FLAG_TRAINABLE)) {
+        rc = prepare_matrix_grad(h, desc, st);
+        if (rc == TN_OK) rc = prepare_backward(h, desc, st);
+    }
     if (rc != TN_OK) {
         (void)hipStreamSynchronize(st);
         free_handle(h);
@@ -2952,6 +3262,7 @@ int tn_linear_param_gradients(tn_linear_t h, const void* x, const void* dy, void
     if (tokens == 0) return TN_OK;
     if (!x || !dy || !aligned16(x) || !aligned16(dy)) return TN_ERR_INVALID_ARG;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (h->mgrad && tokens >= h->mgrad_min_tokens) return matrix_gradients(h, x, dy, grads, tokens, st);
     const size_t n = h->steps.size();
     Workspace w;                                   // the forward workspace serves the split-K partial sums
     w.partial = h->partial;
@@ -3094,7 +3405,7 @@ int tn_linear_query(tn_linear_t h, int32_t what, int64_t* value) {
         case TN_QUERY_MATRIX_BUILD_FLOPS: *value = h->matrix ? h->mat_flops : 0; return TN_OK;
         case TN_QUERY_QUANT_BYTES: *value = h->quant_bytes; return TN_OK;
         case TN_QUERY_QUANT_STREAM_BYTES: *value = h->q4_stream_bytes; return TN_OK;
-        case TN_QUERY_BACKWARD_CHUNK_TOKENS: *value = h->trainable ? h->bwd_chunk : 0; return TN_OK;
+        case TN_QUERY_BACKWARD_CHUNK_TOKENS: *value = h->trainable ? (h->mgrad ? h->mgrad_chunk : h->bwd_chunk) : 0; return TN_OK;
         case TN_QUERY_BACKWARD_WORKSPACE_BYTES: *value = h->trainable ? h->bwd_ws_bytes + h->bwd_partial_bytes : 0; return TN_OK;
         default: break;
     }

@@ -283,4 +283,194 @@ inline bool make_matrix_plan(const tn_linear_desc* d, Plan* net, MatrixPlan* m) 
     return found;
 }
 
+// ---- gradients of the parameter tensors on the same cut ----
+// L = sum_{t, i} dY[t, i] Y[t, i] = sum_{m, n} dW[m, n] W[m, n] with dW = dY^T X, whatever W is made of. From there
+//     dP[f, rho] = sum_g dW[f, g] Q[g, rho],   dQ[g, rho] = sum_f dW[f, g] P[f, rho]     (f, g: modes of the halves)
+// and, where a half is two tensors contracted over s, H[f1, f2] = sum_s A[f1, s] B[f2, s],
+//     dA[f1, s] = sum_f2 dH[f1, f2] B[f2, s],  dB[f2, s] = sum_f1 dH[f1, f2] A[f1, s].
+// The modes of a half are laid out tensor by tensor here, those of each tensor as one number.
+struct GradOut {                           // [R][C] -> the caller's tensor
+    int slot = -1;
+    std::vector<GatherDim> rows, cols;
+};
+
+struct MatrixGradHalf {
+    bool pair = false;
+    // the half as an operand of the other one's gradient: packed, columns bond (in the other half's order), k = its modes
+    Product op;                            // pair
+    SourceOp op_keep;                      // one tensor
+    // its own gradient: rows its modes, columns the bond
+    std::vector<int32_t> row_off, col_off; // pair: into dH [F1][F2]
+    int64_t F1 = 1, F2 = 1;
+    SourceOp a, b;                         // pair: A and B with rows s and k = f1, f2
+    GradOut out_a, out_b;                  // pair: of dA [F1][S], dB [F2][S]; one tensor: out_a of [F][Kr]
+};
+
+struct MatrixGrad {
+    std::vector<int32_t> dw_row, dw_col;   // dW [m][n] -> [F of half 0][F of half 1]
+    MatrixGradHalf half[2];
+};
+
+namespace detail {
+
+// One number for the modes of a tensor, in the order of its axes: an id of its own, with the ids it stands for.
+struct Modes {
+    std::vector<int64_t> ext;              // of every id, those of the numbers after the network's
+    std::vector<std::vector<int>> parts;   // of the ids from first on
+    int first = 0;
+    int add(const std::vector<int>& ids) {
+        int64_t e = 1;
+        for (int i : ids) e *= ext[size_t(i)];
+        ext.push_back(e);
+        parts.push_back(ids);
+        return int(ext.size()) - 1;
+    }
+    std::vector<int> spell(const std::vector<int>& ids) const {
+        std::vector<int> r;
+        for (int i : ids) {
+            if (i < first) r.push_back(i);
+            else r.insert(r.end(), parts[size_t(i - first)].begin(), parts[size_t(i - first)].end());
+        }
+        return r;
+    }
+};
+
+inline std::vector<GatherDim> grad_dims(const Plan& p, int tensor, const std::vector<int>& ids) {
+    const NetTensor& T = p.tensors[size_t(tensor)];
+    std::vector<GatherDim> d;
+    for (int i : ids)
+        for (size_t j = 0; j < T.idx.size(); ++j)
+            if (T.idx[j] == i) d.push_back({p.extent[size_t(i)], T.stride[j]});
+    return d;
+}
+
+}  // namespace detail
+
+// False where a layout does not come out in runs of 8 or in whole tiles of k.
+inline bool make_matrix_grad(const Plan& net, const MatrixPlan& m, MatrixGrad* g) {
+    using namespace detail;
+    int last_n = -1;
+    for (int i : net.x_idx)
+        if (net.extent[size_t(i)] > 1) last_n = i;
+    if (m.half[0].F % 64 || m.half[1].F % 64 || m.Kr % 8) return false;
+    Modes md;
+    md.ext = net.extent;
+    md.first = int(net.extent.size());
+    std::vector<int> order[2], number[2];              // of each half: tensors outer -> inner, and their numbers
+    for (int h = 0; h < 2; ++h) {
+        const MatrixHalf& H = m.half[h];
+        order[h] = H.tensors;
+        auto modes = [&](int t) {
+            std::vector<int> ids;
+            for (int i : net.tensors[size_t(t)].idx)
+                if (contains(H.mn, i)) ids.push_back(i);
+            // (m, n): the in-modes innermost
+            std::stable_sort(ids.begin(), ids.end(), [&](int x, int y) { return !contains(net.x_idx, x) && contains(net.x_idx, y); });
+            return ids;
+        };
+        auto extent_of = [&](int t) { return prod_extents(modes(t), net.extent); };
+        if (order[h].size() == 2) {
+            const bool swap = h == 1 ? !contains(modes(order[h][1]), last_n) : extent_of(order[h][1]) % 16 != 0;
+            if (swap) std::swap(order[h][0], order[h][1]);
+            if (extent_of(order[h][1]) % 16) return false;
+        }
+        for (int t : order[h]) number[h].push_back(md.add(modes(t)));
+    }
+    // dW: rows m, columns n, both in the caller's order
+    DigitOffsets wt;
+    for (int h = 0; h < 2; ++h) {
+        int64_t weight = h == 0 ? m.half[1].F : 1;
+        for (size_t j = number[h].size(); j-- > 0;) {
+            const std::vector<int> ids = md.spell({number[h][j]});
+            for (size_t i = ids.size(); i-- > 0;) {
+                std::vector<int64_t>& v = wt[ids[i]];
+                for (int64_t d = 0; d < net.extent[size_t(ids[i])]; ++d) v.push_back(d * weight);
+                weight *= net.extent[size_t(ids[i])];
+            }
+        }
+    }
+    g->dw_row = digit_table(net.y_idx, net.extent, wt);
+    g->dw_col = digit_table(net.x_idx, net.extent, wt);
+    if (run_length(g->dw_col, 8) != 8 || !all_multiple_of(g->dw_row, 8)) return false;
+    auto source = [&](int t, const std::vector<int>& rows, const std::vector<int>& ks) {
+        return source_op(net, net.extent, t, md.spell(rows), md.spell(ks));
+    };
+    for (int h = 0; h < 2; ++h) {
+        const MatrixHalf& H = m.half[h];
+        MatrixGradHalf& G = g->half[h];
+        G.pair = H.tensors.size() == 2;
+        // order of the bond in its gradient's columns: for a pair, the tensor that has the innermost index is B
+        std::vector<int> bond = m.bond;
+        if (!G.pair) {
+            std::vector<int> modes = md.spell(number[h]);
+            G.out_a.slot = net.tensors[size_t(H.tensors[0])].slot;
+            G.out_a.rows = grad_dims(net, H.tensors[0], modes);
+            G.out_a.cols = grad_dims(net, H.tensors[0], bond);
+        } else {
+            const std::vector<int> s = shared_ids(net.tensors[size_t(H.tensors[0])], net.tensors[size_t(H.tensors[1])]);
+            bool ok = false;
+            for (int turn = 0; turn < 2 && !ok; ++turn) {
+                bond = m.bond;
+                if (turn && bond.size() == 2) std::swap(bond[0], bond[1]);
+                if (net.extent[size_t(bond.back())] % 8) continue;
+                const int ib = contains(net.tensors[size_t(order[h][0])].idx, bond.back()) ? 0 : 1;
+                const int ta = order[h][size_t(1 - ib)], tb = order[h][size_t(ib)];
+                std::vector<int> f1 = {number[h][size_t(1 - ib)]}, f2 = {number[h][size_t(ib)]};
+                for (int i : bond) (contains(net.tensors[size_t(tb)].idx, i) ? f2 : f1).push_back(i);
+                G.F1 = prod_extents(f1, md.ext);
+                G.F2 = prod_extents(f2, md.ext);
+                if (G.F2 % 64) continue;
+                DigitOffsets t;
+                std::vector<int> all = f1;
+                all.insert(all.end(), f2.begin(), f2.end());
+                if (!digit_offsets(all, md.ext, [](int64_t p) { return p; }, &t)) continue;
+                G.row_off = digit_table(number[h], md.ext, t);
+                G.col_off = digit_table(bond, md.ext, t);
+                if (run_length(G.col_off, 8) != 8 || !all_multiple_of(G.row_off, 8)) continue;
+                G.a = source(ta, s, f1);
+                G.b = source(tb, s, f2);
+                G.out_a.slot = net.tensors[size_t(ta)].slot;
+                G.out_a.rows = grad_dims(net, ta, md.spell(f1));
+                G.out_a.cols = grad_dims(net, ta, s);
+                G.out_b.slot = net.tensors[size_t(tb)].slot;
+                G.out_b.rows = grad_dims(net, tb, md.spell(f2));
+                G.out_b.cols = grad_dims(net, tb, s);
+                ok = true;
+            }
+            if (!ok) return false;
+        }
+        // the other half as the operand: columns in this bond order
+        const int o = 1 - h;
+        const MatrixHalf& O = m.half[o];
+        MatrixGradHalf& P = g->half[o];
+        if (O.tensors.size() == 1) {
+            P.op_keep = source(O.tensors[0], bond, number[o]);
+            continue;
+        }
+        DigitOffsets t;
+        if (!digit_offsets(bond, md.ext, [&](int64_t c) { return packed_col(c, O.F / 16); }, &t) ||
+            !digit_offsets(number[o], md.ext, packed_k, &t))
+            return false;
+        const NetTensor &A = net.tensors[size_t(order[o][0])], &B = net.tensors[size_t(order[o][1])];
+        const std::vector<int> s = shared_ids(A, B);
+        std::vector<int> rows = {number[o][0]}, cols = {number[o][1]};
+        for (int i : bond) (contains(B.idx, i) ? cols : rows).push_back(i);
+        sort_by_offset(&rows, t);
+        sort_by_offset(&cols, t);
+        Product& q = P.op;
+        q.row_off = digit_table(rows, md.ext, t);
+        q.col_off = digit_table(cols, md.ext, t);
+        if (run_length(q.col_off, 8) != 8 || !all_multiple_of(q.row_off, 8)) return false;
+        q.a = source(order[o][0], rows, s);
+        q.b = source(order[o][1], cols, s);
+        q.R = q.a.R;
+        q.C = q.b.R;
+        q.K = q.a.K;
+        q.Kp = round64(q.K);
+        q.out_elems = (m.Kr + kMatrixColPad - 1) / kMatrixColPad * kMatrixColPad * O.F;
+        if (q.out_elems > kMatrixMaxElems) return false;
+    }
+    return true;
+}
+
 }  // namespace tn

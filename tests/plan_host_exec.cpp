@@ -114,6 +114,20 @@ extern "C" int plan_host_launch_buffers(const tn_linear_desc* d, int cap, int* i
     return int(sched.size());
 }
 
+static double source_value(const double* const* tensors, const tn::SourceOp& o, int64_t r, int64_t k) {
+    int64_t off = 0;
+    auto walk = [&](const std::vector<tn::SourceDim>& dims, int64_t f) {
+        for (size_t j = dims.size(); j-- > 0;) {
+            const int64_t digit = f % dims[j].extent;
+            if (digit >= dims[j].limit) return false;
+            off += digit * dims[j].stride;
+            f /= dims[j].extent;
+        }
+        return true;
+    };
+    return walk(o.rows, r) && walk(o.ks, k) ? tensors[o.slot][off] : 0.0;
+}
+
 // The order that contracts the parameter tensors with each other first (tn_matrix.hpp), in double: W [M][N] as the packed
 // operand says it. Returns 1 when the layer has no such plan, negative when an output position is written twice or never
 // or lies outside.
@@ -121,19 +135,7 @@ extern "C" int plan_host_matrix(const tn_linear_desc* d, const double* const* te
     tn::Plan net;
     tn::MatrixPlan m;
     if (!tn::make_matrix_plan(d, &net, &m)) return 1;
-    auto operand = [&](const tn::SourceOp& o, int64_t r, int64_t k) {
-        int64_t off = 0;
-        auto walk = [&](const std::vector<tn::SourceDim>& dims, int64_t f) {
-            for (size_t j = dims.size(); j-- > 0;) {
-                const int64_t digit = f % dims[j].extent;
-                if (digit >= dims[j].limit) return false;
-                off += digit * dims[j].stride;
-                f /= dims[j].extent;
-            }
-            return true;
-        };
-        return walk(o.rows, r) && walk(o.ks, k) ? tensors[o.slot][off] : 0.0;
-    };
+    auto operand = [&](const tn::SourceOp& o, int64_t r, int64_t k) { return source_value(tensors, o, r, k); };
     int bad = 0;
     auto store = [&](std::vector<double>* out, std::vector<char>* hit, const tn::Product& p, int64_t r, int64_t c, double v) {
         const int64_t o = int64_t(p.row_off[size_t(r)]) + p.col_off[size_t(c)];
@@ -182,5 +184,88 @@ extern "C" int plan_host_matrix(const tn_linear_desc* d, const double* const* te
             if (!hit[o]) return -3;
             w_out[i * m.N + j] = w[o];
         }
+    return 0;
+}
+
+// Gradients of sum(dW * W) with respect to the parameter tensors on the same cut, in double. dw [M][N]; grads receives every
+// tensor's gradient in the caller's layout. Returns 1 when the layer has no such plan.
+extern "C" int plan_host_matrix_grad(const tn_linear_desc* d, const double* const* tensors, const double* dw, double* const* grads) {
+    tn::Plan net;
+    tn::MatrixPlan m;
+    tn::MatrixGrad g;
+    if (!tn::make_matrix_plan(d, &net, &m) || !tn::make_matrix_grad(net, m, &g)) return 1;
+    const int64_t F[2] = {m.half[0].F, m.half[1].F};
+    std::vector<double> D(size_t(m.M * m.N), 0.0);
+    std::vector<char> hit(D.size(), 0);
+    for (int64_t i = 0; i < m.M; ++i)
+        for (int64_t j = 0; j < m.N; ++j) {
+            const int64_t o = int64_t(g.dw_row[size_t(i)]) + g.dw_col[size_t(j)];
+            if (o < 0 || o >= int64_t(D.size()) || hit[size_t(o)]) return -1;
+            hit[size_t(o)] = 1;
+            D[size_t(o)] = dw[i * m.N + j];
+        }
+    auto put = [&](const tn::GradOut& o, int64_t r, int64_t c, double v) {
+        int64_t off = 0;
+        for (size_t j = o.cols.size(); j-- > 0;) {
+            off += c % o.cols[j].extent * o.cols[j].stride;
+            c /= o.cols[j].extent;
+        }
+        for (size_t j = o.rows.size(); j-- > 0;) {
+            off += r % o.rows[j].extent * o.rows[j].stride;
+            r /= o.rows[j].extent;
+        }
+        grads[o.slot][off] = v;
+    };
+    for (int h = 0; h < 2; ++h) {
+        const tn::MatrixGradHalf &G = g.half[h], &O = g.half[1 - h];
+        // the other half: packed, columns bond, k = its modes
+        std::vector<double> op(size_t((m.Kr + 255) / 256 * 256 * F[1 - h]), 0.0);
+        if (O.pair) {
+            std::vector<char> seen(op.size(), 0);
+            for (int64_t r = 0; r < O.op.R; ++r)
+                for (int64_t c = 0; c < O.op.C; ++c) {
+                    double acc = 0;
+                    for (int64_t k = 0; k < O.op.K; ++k) acc += source_value(tensors, O.op.a, r, k) * source_value(tensors, O.op.b, c, k);
+                    const int64_t o = int64_t(O.op.row_off[size_t(r)]) + O.op.col_off[size_t(c)];
+                    if (o < 0 || o >= int64_t(op.size()) || seen[size_t(o)]) return -2;
+                    seen[size_t(o)] = 1;
+                    op[size_t(o)] = acc;
+                }
+        } else {
+            for (int64_t c = 0; c < m.Kr; ++c)
+                for (int64_t k = 0; k < F[1 - h]; ++k)
+                    op[size_t(tn::packed_col(c, F[1 - h] / 16) + tn::packed_k(k))] = source_value(tensors, O.op_keep, c, k);
+        }
+        std::vector<double> dh(size_t(F[h] * m.Kr), 0.0);
+        std::vector<char> seen(dh.size(), 0);
+        for (int64_t f = 0; f < F[h]; ++f)
+            for (int64_t c = 0; c < m.Kr; ++c) {
+                double acc = 0;
+                for (int64_t k = 0; k < F[1 - h]; ++k)
+                    acc += D[size_t(h == 0 ? f * F[1] + k : k * F[1] + f)] * op[size_t(tn::packed_col(c, F[1 - h] / 16) + tn::packed_k(k))];
+                if (!G.pair) {
+                    put(G.out_a, f, c, acc);
+                    continue;
+                }
+                const int64_t o = int64_t(G.row_off[size_t(f)]) + G.col_off[size_t(c)];
+                if (o < 0 || o >= int64_t(dh.size()) || seen[size_t(o)]) return -3;
+                seen[size_t(o)] = 1;
+                dh[size_t(o)] = acc;
+            }
+        if (!G.pair) continue;
+        const int64_t S = G.a.R;
+        for (int64_t c = 0; c < S; ++c) {
+            for (int64_t f = 0; f < G.F1; ++f) {
+                double acc = 0;
+                for (int64_t k = 0; k < G.F2; ++k) acc += dh[size_t(f * G.F2 + k)] * source_value(tensors, G.b, c, k);
+                put(G.out_a, f, c, acc);
+            }
+            for (int64_t f = 0; f < G.F2; ++f) {
+                double acc = 0;
+                for (int64_t k = 0; k < G.F1; ++k) acc += dh[size_t(k * G.F2 + f)] * source_value(tensors, G.a, c, k);
+                put(G.out_b, f, c, acc);
+            }
+        }
+    }
     return 0;
 }

@@ -98,3 +98,42 @@ def test_no_room_for_w():
     x = wl.make_x(spec, 300, 530)
     assert O.rel_max_err(to_host(layer(to_dev(x, "bf16"))), O.apply_linear(O.dense_weight(spec.format, ts, 4), x)) <= TOL["bf16"]
     layer.close()
+
+
+GRAD_CASES = [
+    # (format, out modes, in modes, ranks, flags)
+    (tn.TN_FORMAT_TT, (4, 8, 4, 8), (8, 10, 8, 8), (1, 64, 64, 64, 1), 0),
+    (tn.TN_FORMAT_TT, (4, 8, 4, 8), (8, 8, 8, 8), (1, 64, 96, 64, 1), tn.TN_FLAG_TRANSPOSE),
+    (tn.TN_FORMAT_TT, (16, 8, 8), (8, 8, 16), (1, 64, 72, 1), 0),                   # a half of one core: its gradient is the first product's
+    (tn.TN_FORMAT_TR, (4, 8, 4, 8), (8, 8, 8, 8), (16, 16, 8, 16, 16), 0),
+    (tn.TN_FORMAT_TR, (8, 8, 16), (8, 16, 8), (16, 16, 8, 16), 0),
+    (tn.TN_FORMAT_DENSE, (1032,), (704,), (), 0),                                   # columns that end inside a tile
+]
+
+
+@pytest.mark.parametrize("case", range(len(GRAD_CASES)))
+def test_gradients_through_dw(case):
+    """Gradients of many tokens (a padded range, several ranges of tokens, one more than the layer is made for) against the
+    oracle; a skipped tensor; the same bits twice. Tolerance as in test_gpu_gradients."""
+    fmt, om, im, rk, flags = GRAD_CASES[case]
+    spec = wl.TNSpec(fmt, "bf16", om, im, rk)
+    rng = np.random.default_rng(540 + case)
+    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(max(1, s[-1])), "bf16") for s in spec.tensor_shapes()]
+    layer = make_layer(spec, ts, 1000, flags=tn.TN_FLAG_TRAINABLE | flags)
+    assert layer.query(tn.TN_QUERY_BACKWARD_CHUNK_TOKENS) == 1024          # through dW: whole ranges of 64
+    for tokens in (65, 1000, 1025):
+        x = wl.round_to_dtype(rng.standard_normal((tokens, layer.N)), "bf16")
+        dy = wl.round_to_dtype(rng.standard_normal((tokens, layer.M)), "bf16")
+        xd, dyd = to_dev(x, "bf16"), to_dev(dy, "bf16")
+        got = layer.param_gradients(xd, dyd)
+        ref = O.param_gradients(fmt, ts, dy if flags else x, x if flags else dy, n_out_modes=len(om))
+        for g, r in zip(got, ref):
+            assert O.rel_max_err(to_host(g), r) <= 2e-2, (case, tokens)
+        for g, a in zip(got, layer.param_gradients(xd, dyd)):
+            assert torch.equal(g, a)
+        # only the last tensor's
+        last = torch.full_like(got[-1], float("nan"))
+        tn.binding.tn_linear_param_gradients(layer._handle, xd.data_ptr(), dyd.data_ptr(), [None] * (len(ts) - 1) + [last.data_ptr()],
+                                             tokens, torch.cuda.current_stream().cuda_stream)
+        assert torch.equal(last, got[-1])
+    layer.close()

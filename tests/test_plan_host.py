@@ -34,6 +34,9 @@ def host_exec():
                                         ctypes.POINTER(ctypes.c_int64)]
     lib.plan_host_matrix.restype = ctypes.c_int
     lib.plan_host_matrix.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p]
+    lib.plan_host_matrix_grad.restype = ctypes.c_int
+    lib.plan_host_matrix_grad.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p,
+                                          ctypes.POINTER(ctypes.c_void_p)]
     return lib
 
 
@@ -440,3 +443,40 @@ def test_factors_contracted_with_each_other_first(host_exec, case, transpose):
         assert (rc == 0) == planned
     if rc == 0:
         assert np.max(np.abs(w - w_ref)) <= 1e-12 * np.max(np.abs(w_ref))
+
+
+MATRIX_GRAD_CASES = [
+    # (format, out modes, in modes, ranks, has such a plan): every mode number of an inner tensor a multiple of 16
+    (tn.TN_FORMAT_TR, (4, 4, 2, 8), (2, 4, 2, 8), (8, 8, 8, 8, 8), True),
+    (tn.TN_FORMAT_TR, (2, 4, 2, 8), (4, 4, 2, 8), (16, 8, 8, 8, 16), True),
+    (tn.TN_FORMAT_TR, (4, 2, 8), (8, 4, 8), (8, 16, 8, 8), True),
+    (tn.TN_FORMAT_TR, (8, 8), (8, 16), (8, 8, 8), True),
+    (tn.TN_FORMAT_TT, (4, 4, 2, 8), (2, 8, 4, 8), (1, 8, 8, 8, 1), True),
+    (tn.TN_FORMAT_TT, (4, 4, 2, 8), (4, 4, 4, 8), (1, 8, 24, 8, 1), True),
+    (tn.TN_FORMAT_TT, (4, 4, 2, 8), (4, 4, 4, 8), (1, 8, 12, 8, 1), False),          # a bond that is no run of 8
+    (tn.TN_FORMAT_TT, (8, 4, 8), (4, 2, 8), (1, 5, 8, 1), False),                    # 5 x 8 modes of a tensor: no whole tiles
+    (tn.TN_FORMAT_TT, (8, 8), (8, 16), (1, 8, 1), True),
+]
+
+
+@pytest.mark.parametrize("transpose", [0, tn.TN_FLAG_TRANSPOSE])
+@pytest.mark.parametrize("case", range(len(MATRIX_GRAD_CASES)))
+def test_gradients_through_the_gradient_of_w(host_exec, case, transpose):
+    """The plan's products from dW to the gradients of the cores against the oracle's gradients."""
+    fmt, om, im, ranks, planned = MATRIX_GRAD_CASES[case]
+    rng = np.random.default_rng(400 + case)
+    ts = [np.ascontiguousarray(t) for t in _rand_tensors(rng, fmt, om, im, ranks)]
+    m, n = int(np.prod(om)), int(np.prod(im))
+    x, dy = rng.standard_normal((3, n)), rng.standard_normal((3, m))
+    dw = np.ascontiguousarray((dy.T @ x).T if transpose else dy.T @ x)
+    d, keep = _make_desc(fmt, tn.TN_DTYPE_BF16, om, im, ranks, None, 1, 0, transpose, None)
+    ptrs = (ctypes.c_void_p * len(ts))(*[t.ctypes.data for t in ts])
+    grads = [np.full(t.shape, np.nan) for t in ts]
+    gptrs = (ctypes.c_void_p * len(ts))(*[g.ctypes.data for g in grads])
+    rc = host_exec.plan_host_matrix_grad(ctypes.byref(d), ptrs, dw.ctypes.data, gptrs)
+    assert rc in (0, 1), rc
+    if not transpose:
+        assert (rc == 0) == planned
+    if rc == 0:
+        for g, ref in zip(grads, O.param_gradients(fmt, ts, x, dy, n_out_modes=len(om))):
+            assert np.max(np.abs(g - ref)) <= 1e-11 * np.max(np.abs(ref))
