@@ -2169,7 +2169,12 @@ int prepare_backward(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st)
         b.plan.R = f.R;
         b.plan.K = f.C;
         b.plan.C = f.K;
-        b.plan.a_plain = false;                         // dOut is read through the forward step's scatter tables
+        // dOut is read through the forward step's scatter tables, or as it stands where those leave a plain matrix (the core
+        // of a Tucker layer, one row per token: 500 tokens x 9216 x 2304 in 48 us on the matrix-product kernel, 1116 us
+        // gathered on the split-K kernel)
+        b.plan.a_plain = f.c_tok_stride == f.R * f.C;
+        for (int64_t r = 0; r < f.R && b.plan.a_plain; ++r) b.plan.a_plain = f.crow[size_t(r)] == r * f.C;
+        for (int64_t c = 0; c < f.C && b.plan.a_plain; ++c) b.plan.a_plain = f.ccol[size_t(c)] == c;
         b.plan.a_tok_stride = f.c_tok_stride;
         b.plan.c_tok_stride = f.a_tok_stride;
         b.plan.c_vec = (f.K % 8 == 0) ? 8 : 1;
