@@ -435,19 +435,25 @@ int launch_pipe(const DevStep& s, const StepArgs& a, int64_t rows, hipStream_t s
 }
 
 // Tile sizes of step_gemm_kernel and what they cost, in us: `t1` per K tile of 64 with one workgroup on every CU and
-// `o1` per round of workgroups (start, first loads, stores); t2, o2 likewise with two on every CU, where they fit
-// (measured at 256 and 512 tiles, K 1024 and 5120). Larger tiles do more per us (a CU's 256 x 256 tile takes 1.44 us per K
-// tile, four 128 x 128 tiles 1.82), smaller ones leave less of the last round of workgroups empty and pad fewer rows.
+// `o1` per round of workgroups (start, first loads, stores); t2, o2 likewise with two on every CU, where they fit: there the
+// start and the stores of one run under the products of the other, and short K or many rounds favour them (6144 x 15360 x
+// 128: 256 x 256 tiles 54 us, 192 x 128 67, 160 x 128 55; 5120 x 10240 x 64: 34, 37, 28). Fitted to 8192 x 8192 x 5120 and to
+// the products of short K. Larger tiles do more per us, smaller ones leave less of the last round of workgroups empty and pad
+// fewer rows.
 struct GemmTile {
     int tm, tn;
     float t1, o1, t2, o2;
 };
 constexpr int kGemmTiles = 13;
 constexpr GemmTile kGemmTile[kGemmTiles] = {
-    {8, 8, 1.44f, 8.0f, 0.f, 0.f}, {7, 8, 1.31f, 7.3f, 0.f, 0.f}, {6, 8, 1.17f, 6.6f, 0.f, 0.f}, {5, 8, 1.02f, 6.3f, 0.f, 0.f},
-    {4, 8, 0.90f, 6.2f, 0.f, 0.f}, {3, 8, 0.76f, 5.6f, 0.f, 0.f}, {2, 8, 0.71f, 3.8f, 0.f, 0.f}, {8, 4, 0.92f, 6.0f, 0.f, 0.f},
-    {6, 4, 0.81f, 2.5f, 0.f, 0.f}, {5, 4, 0.73f, 1.8f, 1.09f, 7.5f}, {4, 4, 0.64f, 2.0f, 0.91f, 5.8f},
-    {3, 4, 0.58f, 1.5f, 0.78f, 4.0f}, {2, 4, 0.54f, 1.0f, 0.63f, 3.8f}};
+    {8, 8, 1.38f, 6.3f, 0.f, 0.f}, {7, 8, 1.18f, 6.3f, 0.f, 0.f}, {6, 8, 1.01f, 5.8f, 0.f, 0.f}, {5, 8, 0.90f, 4.8f, 0.f, 0.f},
+    {4, 8, 0.86f, 4.1f, 0.f, 0.f}, {3, 8, 0.75f, 3.4f, 0.f, 0.f}, {2, 8, 0.67f, 2.6f, 0.f, 0.f}, {8, 4, 0.95f, 3.6f, 0.f, 0.f},
+    {6, 4, 0.75f, 3.0f, 0.f, 0.f}, {5, 4, 0.73f, 1.8f, 0.93f, 4.3f}, {4, 4, 0.64f, 2.0f, 0.84f, 3.5f},
+    {3, 4, 0.58f, 1.5f, 0.69f, 2.8f}, {2, 4, 0.54f, 1.0f, 0.55f, 1.9f}};
+
+// The clock rises when part of the chip idles: products take this share of their time with a share u of the slots for
+// workgroups taken (1024 x 5120 x 8192, us per K tile against the table: 0.76 at u = 0.31, 0.83 at 0.47, 0.95 at 0.86).
+inline float gemm_clock(float u) { return std::min(1.f, 0.6f + 0.4f * u); }
 
 struct GemmChoice {
     int tile = -1, n_split = 1, ktiles_per_split = 1;
@@ -478,14 +484,14 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
             const int64_t pb = ns > 1 ? int64_t(ns) * rows * s.Cp * 4 : 0;
             if (pb > cap) break;
             const int64_t items = tiles * ns;
-            const float one = g.o1 + float(per) * g.t1, two = g.o2 + float(per) * g.t2;
-            float us;
-            if (g.t2 > 0.f) {
-                const int64_t full = items / (2 * cus), rest = items - full * 2 * cus;
-                us = float(full) * two + (rest == 0 ? 0.f : rest <= cus ? one : two);
-            } else {
-                us = float((items + cus - 1) / cus) * one;
-            }
+            const int64_t slots = g.t2 > 0.f ? 2 * cus : cus;
+            const int64_t full = items / slots, rest = items - full * slots;
+            const bool half = g.t2 > 0.f && rest > 0 && rest <= cus;            // a last round with one workgroup per CU
+            const float per_tile = g.t2 > 0.f ? g.t2 : g.t1, per_round = g.t2 > 0.f ? g.o2 : g.o1;
+            const float rounds = float(full + (rest > 0 && !half ? 1 : 0));
+            const float used = float(items) / float((full + (rest > 0 ? 1 : 0)) * (half && full == 0 ? cus : slots));
+            float us = rounds * per_round + (half ? g.o1 : 0.f) +
+                       float(per) * (rounds * per_tile + (half ? g.t1 : 0.f)) * gemm_clock(used);
             if (ns > 1) us += kGemmReduceUs + 2.f * float(pb) / kGemmPartialBytesPerUs;
             if (best.tile < 0 || us < best.us) {
                 best.us = us;
