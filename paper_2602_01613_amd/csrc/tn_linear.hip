@@ -135,6 +135,9 @@ struct tn_linear_s {
     int32_t* lazy_tables = nullptr;           // xrow | xcol | yrow | ycol of the merged plan
     const int32_t *lazy_xrow = nullptr, *lazy_xcol = nullptr, *lazy_yrow = nullptr, *lazy_ycol = nullptr;
     KronGenArgs lazy_gen[2];
+    // the slices as two products of the matrix-product kernel, where the modes' digits allow it (tn::SlicePlan)
+    bool lazy_products = false;
+    DevProduct lazy_half[2];
     // the same slices by MFMA (one workgroup per value of the bond), where the half's shape allows it
     bool lazy_mfma[2] = {false, false};
     KronGenMfmaArgs lazy_gen_mfma[2];
@@ -1217,6 +1220,10 @@ int gen_mfma_both_dispatch(const KronGenMfmaArgs* a0, const KronGenMfmaArgs* a1,
 }
 
 int launch_lazy_generate(const tn_linear_s* h, hipStream_t st) {
+    if (h->lazy_products) {
+        int rc = launch_product(h, h->lazy_half[0], nullptr, 0, st);
+        return rc != TN_OK ? rc : launch_product(h, h->lazy_half[1], nullptr, 0, st);
+    }
     if (h->lazy_mfma[0] && h->lazy_mfma[1]) {
         int rc = gen_mfma_both_dispatch(&h->lazy_gen_mfma[0], &h->lazy_gen_mfma[1],
                                         std::max(h->lazy_gen_smem[0], h->lazy_gen_smem[1]), st);
@@ -1417,6 +1424,51 @@ void fill_gen_dims(GenDims* g, const std::vector<tn::GatherDim>& d) {
     }
 }
 
+// An operand kept for the products: allocated, written on `st`, freed with the handle.
+int keep_operand(tn_linear_s* h, const tn_linear_desc* desc, const tn::SourceOp& o, int64_t Kp, bool packed, void** out, hipStream_t st,
+                 std::vector<void*>* owner = nullptr) {
+    SourceArgs a;
+    memset(&a, 0, sizeof(a));
+    a.R = o.R;
+    a.K = o.K;
+    a.Rp = packed ? (o.R + tn::kMatrixColPad - 1) / tn::kMatrixColPad * tn::kMatrixColPad : o.R;
+    a.Kp = Kp;
+    a.packed = packed ? 1 : 0;
+    a.nr = int32_t(o.rows.size());
+    a.nk = int32_t(o.ks.size());
+    for (size_t j = 0; j < o.rows.size(); ++j) {
+        a.rext[j] = int32_t(o.rows[j].extent);
+        a.rlim[j] = int32_t(o.rows[j].limit);
+        a.rstr[j] = o.rows[j].stride;
+    }
+    for (size_t j = 0; j < o.ks.size(); ++j) {
+        a.kext[j] = int32_t(o.ks[j].extent);
+        a.klim[j] = int32_t(o.ks[j].limit);
+        a.kstr[j] = o.ks[j].stride;
+    }
+    const int64_t n = a.Rp * a.Kp;
+    void* dst = nullptr;
+    if (hipMalloc(&dst, size_t(n) * sizeof(bf16_t)) != hipSuccess) return TN_ERR_ALLOC;
+    (owner ? owner : &h->mat_kept)->push_back(dst);
+    h->packed_bytes += n * int64_t(sizeof(bf16_t));
+    a.src = static_cast<const bf16_t*>(desc->tensors[o.slot]);
+    a.dst = static_cast<bf16_t*>(dst);
+    hipLaunchKernelGGL(operand_source_kernel, dim3(uint32_t(std::min<int64_t>((n + 255) / 256, 65536))), dim3(256), 0, st, a);
+    *out = dst;
+    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
+}
+
+void fill_product_step(DevStep* s, const tn::Product& p) {
+    s->plan.R = p.R;
+    s->plan.K = p.Kp;
+    s->plan.C = p.C;
+    s->plan.c_tok_stride = p.out_elems;
+    s->variant = VAR_GEMM;
+    s->cmode = 1;
+    s->Kp = int(p.Kp);
+    s->Cp = round_up(int(p.C), tn::kMatrixColPad);
+}
+
 // Decide whether the layer gets a lazily merged plan, and prepare it: the plan TN_FLAG_MERGE_GROW would give
 // must be two steps the Kronecker-sum kernel takes (large intermediate, little padding), each absorbing a
 // tensor merged from two of the caller's, and cheaper than the compact plan. Nothing of that plan is stored
@@ -1446,6 +1498,45 @@ int prepare_lazy(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     KronTiles kt;
     if (kron_dispatch(d.cfg, nullptr, 0, nullptr, &kt) != TN_OK) return TN_OK;
     const int at = kt.at, ks0 = kt.ks0, o2t = kt.o2t, o1t = kt.o1t;
+    tn::Plan net;
+    tn::SlicePlan sp;
+    if (!(desc->flags & TN_FLAG_SCALAR_GENERATE) && tn::build_network(desc, &net) == TN_OK && tn::make_slice_plan(net, q, d, &sp)) {
+        std::vector<int32_t> tab;
+        size_t at[8];
+        const std::vector<int32_t>* all[8] = {&sp.xrow, &sp.xcol, &sp.yrow, &sp.ycol, &sp.half[0].row_off, &sp.half[0].col_off,
+                                              &sp.half[1].row_off, &sp.half[1].col_off};
+        for (int i = 0; i < 8; ++i) {
+            at[i] = tab.size();
+            tab.insert(tab.end(), all[i]->begin(), all[i]->end());
+        }
+        if (hipMalloc(reinterpret_cast<void**>(&h->lazy_tables), tab.size() * sizeof(int32_t)) != hipSuccess) return TN_ERR_ALLOC;
+        if (hipMemcpyAsync(h->lazy_tables, tab.data(), tab.size() * sizeof(int32_t), hipMemcpyHostToDevice, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess)
+            return TN_ERR_HIP;
+        h->lazy_xrow = h->lazy_tables + at[0];
+        h->lazy_xcol = h->lazy_tables + at[1];
+        h->lazy_yrow = h->lazy_tables + at[2];
+        h->lazy_ycol = h->lazy_tables + at[3];
+        for (int w = 0; w < 2; ++w) {
+            DevProduct& p = h->lazy_half[w];
+            fill_product_step(&p.s, sp.half[w]);
+            p.s.crow = h->lazy_tables + at[4 + 2 * w];
+            p.s.ccol = h->lazy_tables + at[5 + 2 * w];
+            void* a = nullptr;
+            int rc = keep_operand(h, desc, sp.half[w].a, sp.half[w].Kp, false, &a, st, &h->lazy_sources);
+            p.a = a;
+            if (rc == TN_OK) rc = keep_operand(h, desc, sp.half[w].b, sp.half[w].Kp, true, &p.s.packed, st, &h->lazy_sources);
+            if (rc != TN_OK) return rc;
+        }
+        d.x_vec8 = sp.x_vec8;
+        h->lazy_h1_offset = sp.h1_offset;
+        h->lazy_slice_bytes = sp.bytes;
+        h->lazy_products = true;
+        h->lazy = true;
+        h->lazy_dims = d;
+        h->lazy_min_tokens = kLazyMinTokens;
+        return TN_OK;
+    }
     // the four source matrices (shared indices innermost), written from the caller's tensors
     const int32_t sp_len[2] = {round_up(int(mo[0]->K), 16), round_up(int(mo[1]->K), 16)};
     for (int w = 0; w < 2; ++w)
@@ -1557,50 +1648,6 @@ int prepare_lazy(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     h->lazy_dims = d;
     h->lazy_min_tokens = kLazyMinTokens;
     return TN_OK;
-}
-
-// An operand kept for the products: allocated, written on `st`, freed with the handle.
-int keep_operand(tn_linear_s* h, const tn_linear_desc* desc, const tn::SourceOp& o, int64_t Kp, bool packed, void** out, hipStream_t st) {
-    SourceArgs a;
-    memset(&a, 0, sizeof(a));
-    a.R = o.R;
-    a.K = o.K;
-    a.Rp = packed ? (o.R + tn::kMatrixColPad - 1) / tn::kMatrixColPad * tn::kMatrixColPad : o.R;
-    a.Kp = Kp;
-    a.packed = packed ? 1 : 0;
-    a.nr = int32_t(o.rows.size());
-    a.nk = int32_t(o.ks.size());
-    for (size_t j = 0; j < o.rows.size(); ++j) {
-        a.rext[j] = int32_t(o.rows[j].extent);
-        a.rlim[j] = int32_t(o.rows[j].limit);
-        a.rstr[j] = o.rows[j].stride;
-    }
-    for (size_t j = 0; j < o.ks.size(); ++j) {
-        a.kext[j] = int32_t(o.ks[j].extent);
-        a.klim[j] = int32_t(o.ks[j].limit);
-        a.kstr[j] = o.ks[j].stride;
-    }
-    const int64_t n = a.Rp * a.Kp;
-    void* dst = nullptr;
-    if (hipMalloc(&dst, size_t(n) * sizeof(bf16_t)) != hipSuccess) return TN_ERR_ALLOC;
-    h->mat_kept.push_back(dst);
-    h->packed_bytes += n * int64_t(sizeof(bf16_t));
-    a.src = static_cast<const bf16_t*>(desc->tensors[o.slot]);
-    a.dst = static_cast<bf16_t*>(dst);
-    hipLaunchKernelGGL(operand_source_kernel, dim3(uint32_t(std::min<int64_t>((n + 255) / 256, 65536))), dim3(256), 0, st, a);
-    *out = dst;
-    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
-}
-
-void fill_product_step(DevStep* s, const tn::Product& p) {
-    s->plan.R = p.R;
-    s->plan.K = p.Kp;
-    s->plan.C = p.C;
-    s->plan.c_tok_stride = p.out_elems;
-    s->variant = VAR_GEMM;
-    s->cmode = 1;
-    s->Kp = int(p.Kp);
-    s->Cp = round_up(int(p.C), tn::kMatrixColPad);
 }
 
 // What one launch of a product takes, in us: its tiles, or the stores of its output.
@@ -3022,6 +3069,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
     for (int w = 0; w < 2 && h->lazy; ++w) {
         h->lazy_gen[w].dst = static_cast<char*>(h->lazy_slices) + (w == 0 ? 0 : h->lazy_h1_offset);
         h->lazy_gen_mfma[w].dst = h->lazy_gen[w].dst;
+        h->lazy_half[w].out = h->lazy_gen[w].dst;
     }
     h->chunk_tokens = chunk;
     if (h->lazy && h->owns_workspace) {

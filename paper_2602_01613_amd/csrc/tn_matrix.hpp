@@ -473,4 +473,106 @@ inline bool make_matrix_grad(const Plan& net, const MatrixPlan& m, MatrixGrad* g
     return true;
 }
 
+// ---- slices of the Kronecker-sum kernel as products ----
+// The kernel (kernels/kronsum.hpp) reads, per value rho of the bond, two small matrices in fragment order: H0 with columns o1
+// and k, H1 with columns o2 and a, where (o1, k) and (o2, a) are the modes of the halves. How it numbers o1, k, o2, a and rho
+// is free, as long as the tables through which it reads x and writes y use the same numbers. The numbers are chosen such that
+// both slice arrays are sums of one offset per digit: then each is one product of the two tensors of its half. k and a are
+// padded with zeros to what the kernel's instantiation holds.
+struct SlicePlan {
+    Product half[2];
+    std::vector<int32_t> xrow, xcol, yrow, ycol;       // where a and k sit in a token of x, o1 and o2 in one of y
+    bool x_vec8 = true;                                 // 8 consecutive k of one a are one aligned piece of x
+    int64_t h1_offset = 0, bytes = 0;                   // of the second array, and of both
+};
+
+// `q`: the plan of two steps whose tensors are merged from two of the caller's each; `net`: the network before the merges.
+inline bool make_slice_plan(const Plan& net, const Plan& q, const KronDims& d, SlicePlan* out) {
+    using namespace detail;
+    const int nc = net.n_caller_tensors;
+    const int *cfg = kKronConfig[d.cfg], at = cfg[0], ks0 = cfg[1], o2t = cfg[2], o1t = cfg[3];
+    int tensors[2][2];
+    for (int h = 0; h < 2; ++h) {
+        const int mi = q.steps[size_t(h)].slot - nc;
+        if (mi < 0 || mi >= int(q.merges.size()) || q.merges[size_t(mi)].p_slot >= nc || q.merges[size_t(mi)].q_slot >= nc) return false;
+        tensors[h][0] = q.merges[size_t(mi)].p_slot;
+        tensors[h][1] = q.merges[size_t(mi)].q_slot;
+    }
+    if (d.A % 16 || d.K0 % 8) return false;
+    std::vector<int64_t> ext = net.extent;
+    const std::vector<int> bond = [&] {
+        std::vector<int> b;
+        for (int t : tensors[0])
+            for (int i : net.tensors[size_t(t)].idx)
+                for (int u : tensors[1])
+                    if (contains(net.tensors[size_t(u)].idx, i) && !contains(b, i)) b.push_back(i);
+        return b;
+    }();
+    if (prod_extents(bond, ext) != d.P) return false;
+    // offsets of a mode's digits in a token of x or y
+    auto strides = [&](const std::vector<int>& layout, const std::vector<int>& ids, const std::vector<int64_t>& e) {
+        std::vector<int32_t> tab(1, 0);
+        for (int i : ids) {
+            int64_t st = 1;
+            for (size_t j = layout.size(); j-- > 0 && layout[j] != i;) st *= net.extent[size_t(layout[j])];
+            std::vector<int32_t> next;
+            for (int32_t o : tab)
+                for (int64_t v = 0; v < e[size_t(i)]; ++v) next.push_back(o + int32_t(v * st));
+            tab.swap(next);
+        }
+        return tab;
+    };
+    const int64_t slice[2] = {int64_t(o1t) * ks0 * 512, int64_t(o2t) * 2 * at * 512};
+    const int64_t chunks = (d.O1 + 32 * o1t - 1) / (32 * o1t);
+    const int64_t elems[2] = {chunks * d.P * slice[0], d.P * slice[1]};
+    for (int h = 0; h < 2; ++h) {
+        std::vector<int> o, k;                          // out-modes and in-modes of the half
+        for (int t : tensors[h])
+            for (int i : net.tensors[size_t(t)].idx) {
+                if (contains(net.y_idx, i)) o.push_back(i);
+                if (contains(net.x_idx, i)) k.push_back(i);
+            }
+        if (prod_extents(o, ext) != (h == 0 ? d.O1 : d.C1) || prod_extents(k, ext) != (h == 0 ? d.K0 : d.A)) return false;
+        const int64_t k_real = h == 0 ? d.K0 : d.A, k_pad = h == 0 ? 16 * int64_t(ks0) : 32 * int64_t(at), nks = h == 0 ? ks0 : 2 * at;
+        // x's innermost mode first as the inner digit of k, then the others; both orders of the out-modes
+        std::stable_sort(k.begin(), k.end(), [&](int a, int b) { return a < b; });
+        bool ok = false;
+        for (int turn = 0; turn < 4 && !ok; ++turn) {
+            std::vector<int> oo = o, kk = k;
+            if (turn & 1) std::reverse(oo.begin(), oo.end());
+            if (turn & 2) std::reverse(kk.begin(), kk.end());
+            std::vector<int64_t> e = ext;
+            const int outer = kk[0];
+            const int64_t inner = k_real / e[size_t(outer)];
+            if (k_pad % inner || e[size_t(kk.back())] % 8) continue;
+            e[size_t(outer)] = k_pad / inner;
+            DigitOffsets t;
+            const int64_t P = d.P;
+            auto col = [&](int64_t c) {
+                return h == 0 ? c / (32 * o1t) * P * slice[0] + c % (32 * o1t) / 32 * nks * 512 + c % 32 * 8 : c / 32 * nks * 512 + c % 32 * 8;
+            };
+            if (!digit_offsets(oo, e, col, &t) || !digit_offsets(kk, e, packed_k, &t) ||
+                !digit_offsets(bond, e, [&](int64_t r) { return r * slice[h]; }, &t) ||
+                !pair_product(net, e, tensors[h][0], tensors[h][1], t, elems[h], &out->half[h]))
+                continue;
+            const std::vector<int32_t> x_of = strides(net.x_idx, kk, net.extent);
+            (h == 0 ? out->yrow : out->ycol) = strides(net.y_idx, oo, net.extent);
+            if (h == 0) {
+                out->xcol = x_of;
+            } else {
+                // the kernel's a in a block of 16 sits at 8 * ((a / 4) % 2) + 4 * ((a / 8) % 2) + a % 4
+                out->xrow.resize(size_t(d.A));
+                for (int64_t a = 0; a < d.A; ++a)
+                    out->xrow[size_t(a)] = x_of[size_t((a & ~int64_t(15)) + 8 * ((a >> 2) & 1) + 4 * ((a >> 3) & 1) + (a & 3))];
+            }
+            ok = true;
+        }
+        if (!ok) return false;
+    }
+    out->x_vec8 = run_length(out->xcol, 8) == 8 && all_multiple_of(out->xrow, 8);
+    out->h1_offset = (elems[0] * 2 + 255) & ~int64_t(255);
+    out->bytes = out->h1_offset + ((elems[1] * 2 + 255) & ~int64_t(255));
+    return true;
+}
+
 }  // namespace tn

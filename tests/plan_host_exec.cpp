@@ -269,3 +269,58 @@ extern "C" int plan_host_matrix_grad(const tn_linear_desc* d, const double* cons
     }
     return 0;
 }
+
+// The slices of the Kronecker-sum kernel as products of the cores, in double, put together to W [M][N] the way the kernel reads
+// them. Returns 1 when the layer has no such plan.
+extern "C" int plan_host_slices(const tn_linear_desc* d, const double* const* tensors, double* w_out) {
+    tn_linear_desc halves = *d;
+    halves.flags |= TN_FLAG_MERGE_HALVES | (20 << TN_FLAG_VARIANT_SHIFT);
+    tn::Plan q, net;
+    tn::KronDims k;
+    tn::SlicePlan s;
+    if (tn::make_plan(&halves, &q) != TN_OK || q.steps.size() != 2 || q.merges.size() != 2 || !tn::kron_shape(q, &k) ||
+        tn::build_network(d, &net) != TN_OK || !tn::make_slice_plan(net, q, k, &s))
+        return 1;
+    const int *cfg = tn::kKronConfig[k.cfg], at = cfg[0], ks0 = cfg[1], o2t = cfg[2], o1t = cfg[3];
+    std::vector<double> H[2];
+    for (int h = 0; h < 2; ++h) {
+        const tn::Product& p = s.half[h];
+        H[h].assign(size_t(p.out_elems), 1e300);               // what is not written must not be used
+        std::vector<char> hit(H[h].size(), 0);
+        for (int64_t r = 0; r < p.R; ++r)
+            for (int64_t c = 0; c < p.C; ++c) {
+                double acc = 0;
+                for (int64_t e = 0; e < p.K; ++e) acc += source_value(tensors, p.a, r, e) * source_value(tensors, p.b, c, e);
+                const int64_t o = int64_t(p.row_off[size_t(r)]) + p.col_off[size_t(c)];
+                if (o < 0 || o >= int64_t(H[h].size()) || hit[size_t(o)]) return -1;
+                hit[size_t(o)] = 1;
+                H[h][size_t(o)] = acc;
+            }
+    }
+    auto h0 = [&](int64_t o1, int64_t rho, int64_t kk) {
+        const int64_t chunk = o1 / (32 * o1t), t = o1 % (32 * o1t) / 32, l = o1 % 32 + 32 * (kk % 16 / 8);
+        return H[0][size_t((((chunk * k.P + rho) * o1t + t) * ks0 + kk / 16) * 512 + l * 8 + kk % 8)];
+    };
+    auto h1 = [&](int64_t o2, int64_t rho, int64_t a) {
+        const int64_t m = a % 16, e = m / 8 * 4 + m % 4, l = o2 % 32 + 32 * (m % 8 / 4);
+        return H[1][size_t(((rho * o2t + o2 / 32) * 2 * at + a / 16) * 512 + l * 8 + e)];
+    };
+    // the kernel multiplies padded k and a by zeros of x: they have to hold numbers
+    for (int64_t rho = 0; rho < k.P; ++rho) {
+        for (int64_t o = 0; o < k.O1; ++o)
+            for (int64_t kk = k.K0; kk < 16 * ks0; ++kk)
+                if (h0(o, rho, kk) != 0.0) return -2;
+        for (int64_t o = 0; o < k.C1; ++o)
+            for (int64_t a = k.A; a < 32 * at; ++a)
+                if (h1(o, rho, a) != 0.0) return -3;
+    }
+    for (int64_t o1 = 0; o1 < k.O1; ++o1)
+        for (int64_t o2 = 0; o2 < k.C1; ++o2)
+            for (int64_t a = 0; a < k.A; ++a)
+                for (int64_t kk = 0; kk < k.K0; ++kk) {
+                    double acc = 0;
+                    for (int64_t rho = 0; rho < k.P; ++rho) acc += h0(o1, rho, kk) * h1(o2, rho, a);
+                    w_out[(int64_t(s.yrow[size_t(o1)]) + s.ycol[size_t(o2)]) * q.N + s.xrow[size_t(a)] + s.xcol[size_t(kk)]] = acc;
+                }
+    return 0;
+}

@@ -34,6 +34,8 @@ def host_exec():
                                         ctypes.POINTER(ctypes.c_int64)]
     lib.plan_host_matrix.restype = ctypes.c_int
     lib.plan_host_matrix.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p]
+    lib.plan_host_slices.restype = ctypes.c_int
+    lib.plan_host_slices.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p]
     lib.plan_host_matrix_grad.restype = ctypes.c_int
     lib.plan_host_matrix_grad.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p,
                                           ctypes.POINTER(ctypes.c_void_p)]
@@ -480,3 +482,29 @@ def test_gradients_through_the_gradient_of_w(host_exec, case, transpose):
     if rc == 0:
         for g, ref in zip(grads, O.param_gradients(fmt, ts, x, dy, n_out_modes=len(om))):
             assert np.max(np.abs(g - ref)) <= 1e-11 * np.max(np.abs(ref))
+
+
+SLICE_CASES = [
+    # (format, out modes, in modes, ranks, has such a plan)
+    (tn.TN_FORMAT_TR, (4, 8, 4, 8), (8, 10, 8, 8), (8, 4, 8, 4, 8), True),        # k of 80, bonds of different sizes
+    (tn.TN_FORMAT_TR, (8, 4, 8, 4), (8, 4, 8, 8), (8, 8, 8, 8, 8), True),
+    (tn.TN_FORMAT_TT, (4, 8, 4, 8), (6, 8, 10, 8), (1, 16, 8, 16, 1), True),      # k or a of 80 and 48, held as 64 and 96
+    (tn.TN_FORMAT_TT, (4, 8, 4, 8), (8, 10, 8, 8), (1, 16, 8, 16, 1), True),
+    (tn.TN_FORMAT_TR, (4, 8, 4, 8), (4, 10, 6, 4), (2, 4, 2, 4, 2), False),       # no in-mode of a half a multiple of 8
+]
+
+
+@pytest.mark.parametrize("case", range(len(SLICE_CASES)))
+def test_slices_as_products(host_exec, case):
+    """The slice arrays of the Kronecker-sum kernel as products of the cores: the numbers of k, a, o1, o2 and the bond, the
+    zeros of the padding, and W as the kernel would apply it."""
+    fmt, om, im, ranks, planned = SLICE_CASES[case]
+    ts = [np.ascontiguousarray(t) for t in _rand_tensors(np.random.default_rng(450 + case), fmt, om, im, ranks)]
+    w_ref = O.dense_weight(fmt, ts, len(om))
+    d, keep = _make_desc(fmt, tn.TN_DTYPE_BF16, om, im, ranks, None, 1, 0, 0, None)
+    ptrs = (ctypes.c_void_p * len(ts))(*[t.ctypes.data for t in ts])
+    w = np.full(w_ref.shape, np.nan)
+    rc = host_exec.plan_host_slices(ctypes.byref(d), ptrs, w.ctypes.data)
+    assert rc == (0 if planned else 1), rc
+    if planned:
+        assert np.max(np.abs(w - w_ref)) <= 1e-12 * np.max(np.abs(w_ref))
