@@ -5,7 +5,7 @@
 
 // ---------------------------------------------------------------------------------------------
 // src [T][D] row-major, D % 8 == 0 -> dst with rows d and k = t, zeros for t in [T, Tp): row-major [D][Tp], or packed
-// fragment-major (columns d). Tp % 64 == 0. Bound by memory: a workgroup takes 64 x 64 elements through LDS, reads rows of
+// fragment-major (columns d). With a table, d goes to row or column to[d] instead. Tp % 64 == 0. Bound by memory: a workgroup takes 64 x 64 elements through LDS, reads rows of
 // 128 bytes and writes rows of 128 bytes (packed: 16-byte chunks of 8 t, 32 neighbouring d = 512 bytes together). The LDS
 // rows are 65 words of 4 bytes (two neighbouring t) long, so that the 8 d of a loaded piece and the t of a stored chunk both
 // go over different banks.
@@ -15,6 +15,7 @@ struct TransposeArgs {
     bf16_t* dst;
     int64_t T, D, Tp;
     int32_t packed;
+    const int32_t* to;
 };
 
 __global__ void __launch_bounds__(256) transpose_kernel(TransposeArgs p) {
@@ -45,7 +46,9 @@ __global__ void __launch_bounds__(256) transpose_kernel(TransposeArgs p) {
         o.z = tile[4 * tq + 2][dl];
         o.w = tile[4 * tq + 3][dl];
         const int64_t d = d0 + dl, t = t0 + 8 * tq;
-        if (d < p.D)
-            *reinterpret_cast<uint4*>(p.dst + (p.packed ? bfrag_offset(int(d), int(t), int(p.Tp >> 4)) : d * p.Tp + t)) = o;
+        if (d < p.D) {
+            const int64_t to = p.to ? p.to[d] : d;
+            *reinterpret_cast<uint4*>(p.dst + (p.packed ? bfrag_offset(int(to), int(t), int(p.Tp >> 4)) : to * p.Tp + t)) = o;
+        }
     }
 }

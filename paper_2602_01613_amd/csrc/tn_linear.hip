@@ -74,6 +74,8 @@ struct DevStep {
     void* q4_codes = nullptr;     // 4-bit stream of the tensor for decode-size launches (codes, then block scales)
     void* q4_scales = nullptr;
     bool no_skinny = false;       // TN_FLAG_NO_SKINNY
+    // gradient of the step's tensor as one product over the tokens: the row of c and the column of k in the caller's tensor
+    const int32_t *grad_row = nullptr, *grad_col = nullptr;
 };
 
 // One product of the matrix plan (tn_matrix.hpp) as a launch of the matrix-product kernel. What it reads is either kept by
@@ -171,6 +173,7 @@ struct tn_linear_s {
     int64_t bwd_chunk = 0, bwd_ws_bytes = 0;
     float* bwd_partial = nullptr;
     int64_t bwd_partial_bytes = 0;
+    void* grad_product_mem = nullptr;         // in bwd_ws: transposed operands of launch_grad_product
     // gradients of many tokens: dW = dY^T X, and from it those of the tensors on the cut of tn_matrix.hpp (a dense layer's
     // tensor is W)
     bool mgrad = false;
@@ -2195,6 +2198,66 @@ int grad_splits(const tn_linear_s* h, const tn::Step& p, int64_t rows, int64_t c
     return int(n);
 }
 
+int64_t grad_tokens_pad(int64_t tokens) { return (tokens + 63) / 64 * 64; }
+
+void launch_transpose(const void* src, void* dst, int64_t T, int64_t D, int64_t Tp, bool packed, hipStream_t st,
+                      const int32_t* to = nullptr) {
+    TransposeArgs a{static_cast<const bf16_t*>(src), static_cast<bf16_t*>(dst), T, D, Tp, packed ? 1 : 0, to};
+    hipLaunchKernelGGL(transpose_kernel, dim3(uint32_t((D + 63) / 64), uint32_t(Tp / 64)), dim3(256), 0, st, a);
+}
+
+// A step's gradient as one product over the tokens, straight into the caller's tensor: one row per token, both operands plain
+// matrices, k and c the tensor's inner and outer axes in any order. From kGradProductElems elements on, where a pass of fp32
+// sums through memory is what the tile kernel takes its time for (core of 9216 x 2304 at 500 tokens: 71 us and 109 to put the
+// sums in place; 34 us here and 10 for the transposed copies).
+constexpr int64_t kGradProductElems = int64_t(1) << 20;
+
+bool grad_product_perms(const tn_linear_s* h, const tn::Step& p, std::vector<int32_t>* rows, std::vector<int32_t>* cols) {
+    if (h->elt != 2 || (h->flags & TN_FLAG_SCALAR_KERNELS) || ((h->flags >> TN_FLAG_VARIANT_SHIFT) & 0xff) != 0) return false;
+    if (p.R != 1 || !p.a_plain || p.trace_extent != 1 || p.K % 8 || p.C % 8 || p.K * p.C < kGradProductElems ||
+        p.K * p.C >= (int64_t(1) << 31) || p.c_tok_stride != p.C || p.a_tok_stride != p.K || p.crow[0] != 0)
+        return false;
+    for (int64_t c = 0; c < p.C; ++c)
+        if (p.ccol[size_t(c)] != c) return false;
+    *rows = gather_table(p.cdims, p.C);
+    *cols = gather_table(p.kdims, p.K);
+    std::vector<char> row_hit(size_t(p.C), 0), col_hit(size_t(p.K), 0);
+    for (int32_t& r : *rows) {
+        if (r % p.K || r / p.K >= p.C || row_hit[size_t(r / p.K)]) return false;
+        r = int32_t(r / p.K);
+        row_hit[size_t(r)] = 1;
+    }
+    for (int32_t c : *cols) {
+        if (c >= p.K || col_hit[size_t(c)]) return false;
+        col_hit[size_t(c)] = 1;
+    }
+    return true;
+}
+
+// Bytes of the two transposed operands.
+int64_t grad_product_bytes(const tn::Step& p, int64_t tokens) {
+    return (p.C + (p.K + tn::kMatrixColPad - 1) / tn::kMatrixColPad * tn::kMatrixColPad) * grad_tokens_pad(tokens) * 2;
+}
+
+int launch_grad_product(const tn_linear_s* h, const DevStep& s, const void* dOut, const void* In, float* grad, int64_t tokens, hipStream_t st) {
+    const tn::Step& p = s.plan;
+    const int64_t tp = grad_tokens_pad(tokens);
+    char* a = static_cast<char*>(h->grad_product_mem);
+    char* b = a + p.C * tp * 2;
+    launch_transpose(dOut, a, tokens, p.C, tp, false, st, s.grad_row);
+    launch_transpose(In, b, tokens, p.K, tp, true, st, s.grad_col);
+    DevStep g;
+    g.plan.R = p.C;
+    g.plan.K = tp;
+    g.plan.C = p.K;
+    g.Kp = int(tp);
+    g.Cp = round_up(int(p.K), tn::kMatrixColPad);
+    g.cmode = 1;
+    g.variant = VAR_GEMM;
+    GemmSums f{grad, p.K, 1};
+    return launch_product_of(h, g, a, b, nullptr, nullptr, 0, st, &f);
+}
+
 int prepare_backward(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     const size_t n = h->steps.size();
     if (!h->plan.merges.empty()) return TN_ERR_UNSUPPORTED;
@@ -2207,6 +2270,16 @@ int prepare_backward(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st)
         off[s] = tab.size();
         for (int64_t r = 0; r < f.R; ++r) tab.push_back(int32_t(r * f.K));
         for (int64_t k = 0; k < f.K; ++k) tab.push_back(int32_t(k));
+    }
+    std::vector<size_t> grad_at(n, 0);
+    std::vector<char> as_product(n, 0);
+    for (size_t s = 0; s < n; ++s) {
+        std::vector<int32_t> rows, cols;
+        if (!grad_product_perms(h, h->steps[s].plan, &rows, &cols)) continue;
+        as_product[s] = 1;
+        grad_at[s] = tab.size();
+        tab.insert(tab.end(), rows.begin(), rows.end());
+        tab.insert(tab.end(), cols.begin(), cols.end());
     }
     if (hipMalloc(reinterpret_cast<void**>(&h->bwd_tables), std::max<size_t>(1, tab.size()) * sizeof(int32_t)) != hipSuccess)
         return TN_ERR_ALLOC;
@@ -2278,8 +2351,17 @@ int prepare_backward(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st)
     if (per_token > 0) chunk = std::min<int64_t>(chunk, std::max<int64_t>(1, limit / per_token));
     chunk = std::max<int64_t>(1, std::min<int64_t>(chunk, ((int64_t(1) << 31) - 1024) / max_r));
     h->bwd_chunk = chunk;
-    h->bwd_ws_bytes = std::max<int64_t>(std::max<int64_t>(256, h->bwd_ws_bytes), chunk * per_token);
+    const int64_t chain_bytes = (chunk * per_token + 255) & ~int64_t(255);
+    int64_t product_bytes = 0;
+    for (size_t s = 0; s < n; ++s)
+        if (as_product[s] && chain_bytes + grad_product_bytes(h->steps[s].plan, chunk) <= limit) {
+            product_bytes = std::max(product_bytes, grad_product_bytes(h->steps[s].plan, chunk));
+            h->steps[s].grad_row = h->bwd_tables + grad_at[s];
+            h->steps[s].grad_col = h->steps[s].grad_row + h->steps[s].plan.C;
+        }
+    h->bwd_ws_bytes = std::max<int64_t>(std::max<int64_t>(256, h->bwd_ws_bytes), chain_bytes + product_bytes);
     if (hipMalloc(&h->bwd_ws, size_t(h->bwd_ws_bytes)) != hipSuccess) return TN_ERR_ALLOC;
+    h->grad_product_mem = static_cast<char*>(h->bwd_ws) + chain_bytes;
     int64_t need = h->bwd_partial_bytes;
     for (const auto& s : h->steps)
         need = std::max(need, int64_t(grad_splits(h, s.plan, chunk * s.plan.R, kMaxGradPartialBytes)) * s.plan.C * s.plan.K * 4);
@@ -2317,6 +2399,8 @@ int launch_grad_reduce(const GradOutArgs& o, hipStream_t st) {
 int launch_param_gradient(const tn_linear_s* h, const DevStep& s, const void* dOut, const void* In, float* grad,
                           int64_t grad_elems, int64_t tokens, bool accumulate, hipStream_t st) {
     const tn::Step& p = s.plan;
+    if (s.grad_row && !accumulate && (reinterpret_cast<uintptr_t>(grad) & 15) == 0)
+        return launch_grad_product(h, s, dOut, In, grad, tokens, st);
     const int64_t rows = tokens * p.R;
     const int n_split = grad_splits(h, p, rows, h->bwd_partial_bytes);
     if (int64_t(n_split) * p.C * p.K * 4 > h->bwd_partial_bytes) return TN_ERR_UNSUPPORTED;
@@ -2377,13 +2461,6 @@ int launch_param_gradient(const tn_linear_s* h, const DevStep& s, const void* dO
 // ---- the same gradients through dW ----
 constexpr int64_t kGradMinTokens = 16;        // one token range is padded to 64
 constexpr int kGradSumsPad = 128;             // columns of the core gradients (a bond): padded to the narrow tiles
-
-int64_t grad_tokens_pad(int64_t tokens) { return (tokens + 63) / 64 * 64; }
-
-void launch_transpose(const void* src, void* dst, int64_t T, int64_t D, int64_t Tp, bool packed, hipStream_t st) {
-    TransposeArgs a{static_cast<const bf16_t*>(src), static_cast<bf16_t*>(dst), T, D, Tp, packed ? 1 : 0};
-    hipLaunchKernelGGL(transpose_kernel, dim3(uint32_t((D + 63) / 64), uint32_t(Tp / 64)), dim3(256), 0, st, a);
-}
 
 // Decide whether gradients of many tokens go through dW, and prepare it. The steps are priced at 0.35e9 FLOP per us and 40 us
 // a step (train 5120 -> 8192 of rank 64: 9.7 ms at 1024 tokens; ring 25600 -> 5120 of rank 32: 12.5 ms at 64).
