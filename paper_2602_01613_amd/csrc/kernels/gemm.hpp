@@ -27,7 +27,7 @@
 // 8192 x 8192 x 5120 in 467 us = 1.47 PFLOP/s (the 256 x 256 ping-pong kernel this replaces: 565 us), 8192 x 9216 x
 // 2304 in 260 us (340).
 //
-// Tile sizes: 32*TM x 32*TN, TM <= 8, TN 8 or 4; the host picks the one (and the number of K ranges) with the least
+// Tile sizes: 32*TM x 32*TN, TM <= 8, TN 8, 4 or 2; the host picks the one (and the number of K ranges) with the least
 // time by gemm_choice. XCD x takes a contiguous eighth of the tiles in bands of four row tiles (row fastest), so that
 // the 32 tiles an XCD runs at a time share 4 + 8 operand panels in its L2 and no XCD has a row tile more than another
 // (dealing whole row tiles to XCDs left 2500 rows at 10 tiles over 8 XCDs: 281 us, now 160).

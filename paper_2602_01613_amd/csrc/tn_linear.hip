@@ -444,18 +444,20 @@ int launch_pipe(const DevStep& s, const StepArgs& a, int64_t rows, hipStream_t s
 // `o1` per round of workgroups (start, first loads, stores); t2, o2 likewise with two on every CU, where they fit: there the
 // start and the stores of one run under the products of the other, and short K or many rounds favour them (6144 x 15360 x
 // 128: 256 x 256 tiles 54 us, 192 x 128 67, 160 x 128 55; 5120 x 10240 x 64: 34, 37, 28). Fitted to 8192 x 8192 x 5120 and to
-// the products of short K. Larger tiles do more per us, smaller ones leave less of the last round of workgroups empty and pad
-// fewer rows.
+// the products of short K. 64 x 64 is for outputs of up to 64 columns, the gradients towards a bond, which read A once and are
+// bound by the loads in flight (10240 x 64 x 4096: 31 us, 64 x 128 36; 5120 x 32 x 2560: 12 and 20). Larger tiles do more
+// per us, smaller ones leave less of the last round of workgroups empty and pad fewer rows.
 struct GemmTile {
     int tm, tn;
     float t1, o1, t2, o2;
 };
-constexpr int kGemmTiles = 13;
+constexpr int kGemmTiles = 14;
 constexpr GemmTile kGemmTile[kGemmTiles] = {
     {8, 8, 1.38f, 6.3f, 0.f, 0.f}, {7, 8, 1.18f, 6.3f, 0.f, 0.f}, {6, 8, 1.01f, 5.8f, 0.f, 0.f}, {5, 8, 0.90f, 4.8f, 0.f, 0.f},
     {4, 8, 0.86f, 4.1f, 0.f, 0.f}, {3, 8, 0.75f, 3.4f, 0.f, 0.f}, {2, 8, 0.67f, 2.6f, 0.f, 0.f}, {8, 4, 0.95f, 3.6f, 0.f, 0.f},
     {6, 4, 0.75f, 3.0f, 0.f, 0.f}, {5, 4, 0.73f, 1.8f, 0.93f, 4.3f}, {4, 4, 0.64f, 2.0f, 0.84f, 3.5f},
-    {3, 4, 0.58f, 1.5f, 0.69f, 2.8f}, {2, 4, 0.54f, 1.0f, 0.55f, 1.9f}};
+    {3, 4, 0.58f, 1.5f, 0.69f, 2.8f}, {2, 4, 0.54f, 1.0f, 0.55f, 1.9f},
+    {2, 2, 0.45f, 1.0f, 0.50f, 1.6f}};
 
 // The clock rises when part of the chip idles: products take this share of their time with a share u of the slots for
 // workgroups taken (1024 x 5120 x 8192, us per K tile against the table: 0.76 at u = 0.31, 0.83 at 0.47, 0.95 at 0.86).
@@ -498,7 +500,7 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
             const float used = float(items) / float((full + (rest > 0 ? 1 : 0)) * (half && full == 0 ? cus : slots));
             float us = rounds * per_round + (half ? g.o1 : 0.f) +
                        float(per) * (rounds * per_tile + (half ? g.t1 : 0.f)) * gemm_clock(used);
-            if (ns > 1) us += kGemmReduceUs + 2.f * float(pb) / kGemmPartialBytesPerUs;
+            if (ns > 1) us += kGemmReduceUs + 2.f * float(ns) * float(rows) * float(s.plan.C) * 4.f / kGemmPartialBytesPerUs;
             if (best.tile < 0 || us < best.us) {
                 best.us = us;
                 best.tile = t;
