@@ -1080,8 +1080,10 @@ KronGeom kron_geometry(const tn_linear_s* h, const tn::KronDims& d, int64_t toke
     // workgroups a CU holds at a time: one when the three LDS stages take more than half of its 160 KB
     const int* cfg = tn::kKronConfig[d.cfg];
     const int64_t stage_bytes = 4096 * int64_t((cfg[3] * cfg[1] + cfg[2] * 2 * cfg[0] + 3) / 4);
-    // (measured: with several chunks of o1 the two-round split is the faster one at rank 96, so it is kept there)
-    const int64_t per_cu = (3 * stage_bytes > 80 * 1024 && g.n_chunks == 1) ? 1 : 2;
+    // (two rounds of such workgroups pay the start, the input's fragments and the partial sums twice: 5120 -> 25600 with its
+    // five chunks of o1, us per call in two rounds / one: rank 32 84 / 65 at one token, 133 / 100 at 8; rank 64 150 / 143 and
+    // 284 / 248; rank 96 361 / 347 and 600 / 555)
+    const int64_t per_cu = 3 * stage_bytes > 80 * 1024 ? 1 : 2;
     // as many splits as keep the grid within one round of workgroups (rounding up instead left a second round with a
     // handful of workgroups: 300 tokens took as long as 512)
     int64_t want = std::max<int64_t>(1, per_cu * int64_t(h->num_cus) / base);
