@@ -1088,8 +1088,11 @@ KronGeom kron_geometry(const tn_linear_s* h, const tn::KronDims& d, int64_t toke
     // handful of workgroups: 300 tokens took as long as 512)
     int64_t want = std::max<int64_t>(1, per_cu * int64_t(h->num_cus) / base);
     if (base >= h->num_cus) want = 1;
-    // at least 4 values of the bond per workgroup, partial sums within their buffer
-    want = std::min<int64_t>(want, std::max<int64_t>(1, d.P / 4));
+    // at least 4 values of the bond per workgroup, or 2 where that leaves most of the chip without one (a train's bond of 96, us
+    // per call at 4 / at 2: 25600 -> 5120 37.5 / 34.9 at one token, 48.5 / 45.4 at 16 (96 workgroups at 4); 5120 -> 25600 at 4
+    // tokens (120) 41.6 / 44.6; 5120 -> 1024 at 32 tokens (192) 19.5 / 22.5); partial sums within their buffer
+    const int64_t least = base * std::max<int64_t>(1, d.P / 4) * 5 < 2 * h->num_cus ? 2 : 4;
+    want = std::min<int64_t>(want, std::max<int64_t>(1, d.P / least));
     want = std::min<int64_t>(want, std::max<int64_t>(1, partial_cap / (tokens * h->plan.M * 4)));
     g.rho_per_split = int((d.P + want - 1) / want);
     g.n_splits = int((d.P + g.rho_per_split - 1) / g.rho_per_split);      // no empty split
