@@ -101,8 +101,9 @@ extern "C" {
 #define TN_FLAG_NO_CHAIN2       64   /* never run two small transposing steps (Tucker factor products) as one
                                        chained launch: always one launch per step */
 #define TN_FLAG_NO_SMALL_CHAIN (1 << 20) /* never run a small layer as one launch with all its tensors in LDS */
-#define TN_FLAG_NO_LAZY_MERGE (1 << 21)  /* never run large calls on a merged plan rebuilt in the workspace (see
-                                       TN_QUERY_LAZY_MIN_TOKENS): every call runs the compact steps */
+#define TN_FLAG_NO_LAZY_MERGE (1 << 21)  /* never run large calls on tensors rebuilt in the workspace (see
+                                       TN_QUERY_LAZY_MIN_TOKENS, TN_QUERY_MATRIX_MIN_TOKENS), nor gradients
+                                       through that of W: every call runs the compact steps */
 #define TN_FLAG_SCALAR_GENERATE (1 << 23) /* rebuild the slices of a lazily merged plan with the plain FMA kernel
                                        instead of the MFMA one */
 #define TN_FLAG_NO_DECODE_FUSION (1 << 24) /* none of the forms kept for calls of a few tokens: a chained factor pair and the
