@@ -1666,10 +1666,10 @@ float product_us(const tn_linear_s* h, const DevStep& s) {
 }
 
 // Decide whether calls of many tokens contract the tensors with each other first, from how many tokens on, and prepare it.
-// The other orders are priced at the rates their kernels reach at many tokens (FLOP per us: chained pair kernel 1.3e9,
-// Kronecker-sum kernel 1.25e9 with its padding counted, 1.0e9 where several chunks of o1 share a token, one launch per step 0.45e9). Measured, us per call in this order /
-// in the other: ring 25600 -> 5120 of rank 32 343 / 410 at 96 tokens, 767 / 8109 at 2048, 1955 / 30730 at 8192; ring 5120 ->
-// 8192 of rank 96 776 / 911 at 48 tokens, 885 / 35579 at 2048; train 5120 -> 8192 of rank 64 166 / 211 at 2048 tokens, 538 /
+// The other orders are priced at the rates their kernels reach at many tokens (FLOP per us: chained pair kernel 1.3e9, one
+// launch per step 0.45e9; the Kronecker-sum kernel as below). Measured, us per call in this order / in the other: ring
+// 25600 -> 5120 of rank 32 343 / 410 at 96 tokens, 767 / 8109 at 2048, 1955 / 30730 at 8192; ring 5120 -> 8192 of rank 96 776 /
+// 911 at 48 tokens, 885 / 35579 at 2048; train 5120 -> 25600 of rank 96 226 / 207 at 387 tokens, 226 / 391 at 420; train 5120 -> 8192 of rank 64 166 / 211 at 2048 tokens, 538 /
 // 783 at 8192; of rank 32, whose chain has little more than 2 M N, not taken.
 int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     if (h->plan.dtype != TN_DTYPE_BF16 ||
@@ -1688,12 +1688,16 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     y.Kp = int(h->plan.N);
     y.Cp = round_up(int(h->plan.M), tn::kMatrixColPad);
     if (h->plan.N % 64 || h->plan.format == TN_FORMAT_DENSE || h->plan.format == TN_FORMAT_TUCKER || !gemm_fits(y)) return TN_OK;
-    // padded work of the Kronecker-sum kernel per token, and the tokens a round of its workgroups takes
+    // the Kronecker-sum kernel: 22 ns per MFMA of a wave, values of the bond one after another, in rounds of one or two workgroups
+    // per CU (train 5120 -> 25600 of rank 96: 387 tokens are 245 workgroups and 200 us, 512 are 320 and 395)
     auto kron_us = [&](const tn::KronDims& d, int64_t t) {
         const int* c = tn::kKronConfig[d.cfg];
-        const double chunks = double((d.O1 + 32 * c[3] - 1) / (32 * c[3]));
-        const double flops = double(d.P) * chunks * c[3] * c[0] * (c[1] + 2 * c[2]) * 32768.0;
-        return 20.f + float(double(t) * flops / (chunks > 1 ? 1.0e9 : 1.25e9));
+        const KronGeom g = kron_geometry(h, d, t, kMaxPartialBytes);
+        const int64_t stage = 4096 * int64_t((c[3] * c[1] + c[2] * 2 * c[0] + 3) / 4);
+        const int64_t slots = int64_t(h->num_cus) * (3 * stage > 80 * 1024 ? 1 : 2);
+        const int64_t rounds = (g.quads * g.n_chunks * g.n_splits + slots - 1) / slots;
+        const float per_rho = float(c[3] * c[0] * (c[1] + 2 * c[2]) * g.tpw) * 0.022f;
+        return 10.f + float(rounds) * (10.f + float(g.rho_per_split) * per_rho) + float(g.partial_bytes) / kGemmPartialBytesPerUs;
     };
     auto other_us = [&](int64_t t) {
         if (h->pair) return std::max(12.f, float(t) * float(h->plan.flops) / 1.3e9f);
@@ -1703,7 +1707,7 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     };
     auto first_tokens = [&](float build_us) {
         for (int64_t t = 8; t <= desc->max_tokens; t += t < 64 ? 8 : t / 8)
-            if (build_us + gemm_choice(h, y, t, kMaxPartialBytes).us < other_us(t)) return t;
+            if (1.15f * (build_us + gemm_choice(h, y, t, kMaxPartialBytes).us) < other_us(t)) return t;      // only where it is clear
         return int64_t(0);
     };
     if (!first_tokens(6.f + float(h->plan.M) * float(h->plan.N) * 2.f / 3.5e6f)) return TN_OK;
