@@ -1695,9 +1695,11 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
         const KronGeom g = kron_geometry(h, d, t, kMaxPartialBytes);
         const int64_t stage = 4096 * int64_t((c[3] * c[1] + c[2] * 2 * c[0] + 3) / 4);
         const int64_t slots = int64_t(h->num_cus) * (3 * stage > 80 * 1024 ? 1 : 2);
-        const int64_t rounds = (g.quads * g.n_chunks * g.n_splits + slots - 1) / slots;
+        const int64_t wgs = g.quads * g.n_chunks * g.n_splits;
+        const int64_t rounds = (wgs + slots - 1) / slots, turns = (wgs + h->num_cus - 1) / h->num_cus;     // two on a CU share its matrix cores
         const float per_rho = float(c[3] * c[0] * (c[1] + 2 * c[2]) * g.tpw) * 0.022f;
-        return 10.f + float(rounds) * (10.f + float(g.rho_per_split) * per_rho) + float(g.partial_bytes) / kGemmPartialBytesPerUs;
+        return 10.f + float(rounds) * 10.f + float(turns) * float(g.rho_per_split) * per_rho +
+               float(g.partial_bytes) / kGemmPartialBytesPerUs;
     };
     auto other_us = [&](int64_t t) {
         if (h->pair) return std::max(12.f, float(t) * float(h->plan.flops) / 1.3e9f);
