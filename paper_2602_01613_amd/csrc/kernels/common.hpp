@@ -53,3 +53,9 @@ template <typename T> __device__ __forceinline__ T from_float(float v);
 template <> __device__ __forceinline__ float from_float<float>(float v) { return v; }
 template <> __device__ __forceinline__ bf16_t from_float<bf16_t>(float v) { return bf16_t(v); }
 
+// What rounding to bf16 takes off; 0 for an infinity or a NaN, which the high part carries.
+__device__ __forceinline__ float low_part(float v) {
+    const float d = v - float(bf16_t(v));
+    return fabsf(d) < __builtin_huge_valf() ? d : 0.f;
+}
+

@@ -38,6 +38,9 @@ struct GemmArgs {
     int32_t ktiles_per_split;      // K tiles of 64 per range, at least one in every range
     float* partial;                // not null: fp32 sums [split][rows_pad][ld] instead of the output (TRANS = 0, C % 4 == 0)
     int64_t rows_pad, ld;
+    // PARTS = 2, in elements, 0: there is none
+    int64_t a_lo, b_lo;            // from an operand to its low part
+    int64_t out_lo;                // from the output to where its low part goes
 };
 
 template <int TM, int TN>
@@ -48,7 +51,11 @@ struct GemmShape {
     static constexpr size_t SMEM = size_t(2) * STAGE_BYTES + size_t(TAB_ROWS + BN) * 4;
 };
 
-template <int TM, int TN, int TRANS>
+// PARTS = 2: a matrix of fp32 significance as a sum of two of bf16, high = bf16(v) and low = bf16(v - high), which leaves 2^-17
+// of v. With low parts the K tiles are walked two or three times, (A, B), (A low, B), (A, B low), into the same sums, which is
+// the fp32 product but for terms of 2^-16: sums over tokens have to pass through here without losing what averaging over
+// the tokens gained. Instantiations of their own, so that the loop above stays as it was measured.
+template <int TM, int TN, int TRANS, int PARTS = 1>
 __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs g) {
 #ifdef __HIP_DEVICE_COMPILE__
     using S = GemmShape<TM, TN>;
@@ -79,20 +86,32 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
     const uint32_t row0 = uint32_t(row_tile) * BM;
     const int col0 = col_tile * BN, nks = a.Kp >> 4;
     const int kt0 = split * g.ktiles_per_split;
-    const int nk = min(a.Kp >> 6, kt0 + g.ktiles_per_split) - kt0;       // >= 1
+    const int nk_seg = a.Kp >> 6, n_seg = PARTS == 1 ? 1 : 1 + (g.a_lo != 0) + (g.b_lo != 0);
+    const int nk = min(nk_seg * n_seg, kt0 + g.ktiles_per_split) - kt0;  // >= 1
 
     // rows past the end read as zeros (bounds of the buffer)
     const int row_bytes = a.K * 2;
-    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(static_cast<const bf16_t*>(a.A) + int64_t(row0) * a.K), 0,
-        int(min(int64_t(a.total_rows) - int64_t(row0), int64_t(BM))) * row_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<bf16_t*>(static_cast<const bf16_t*>(a.B) + int64_t(col0 >> 5) * nks * 512), 0, (BN / 32) * nks * 1024, 0x00020000);
+    const bf16_t* pa = static_cast<const bf16_t*>(a.A) + int64_t(row0) * a.K;
+    const bf16_t* pb = static_cast<const bf16_t*>(a.B) + int64_t(col0 >> 5) * nks * 512;
+    const int a_size = int(min(int64_t(a.total_rows) - int64_t(row0), int64_t(BM))) * row_bytes, b_size = (BN / 32) * nks * 1024;
+    const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(pa), 0, a_size, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(pb), 0, b_size, 0x00020000);
     // a load of A covers 8 rows x 128 bytes: lane l fills position l%8 of row l/8
     const int va = (wave * 8 + (lane >> 3)) * row_bytes + (((lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7)) * 16);
     const int vb = wave * 1024 + lane * 16;              // the four waves bring the four k-step blocks of a column block
     auto load1 = [&](int j, int kt, unsigned char* s) {
-        if (j < TM)
+        if (PARTS == 2) {
+            const int t = kt0 + kt, seg = (t >= nk_seg) + (t >= 2 * nk_seg), tk = t - seg * nk_seg;
+            const bool a_low = seg == 1 && g.a_lo, b_low = seg && !a_low;
+            if (j < TM)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(pa + (a_low ? g.a_lo : 0)), 0, a_size, 0x00020000),
+                    (lds_t*)(s + (j * NW + wave) * 1024), 16, va, tk * 128 + j * (NW * 8) * row_bytes, 0, 0);
+            else
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(pb + (b_low ? g.b_lo : 0)), 0, b_size, 0x00020000),
+                    (lds_t*)(s + A_BYTES + ((j - TM) * NW + wave) * 1024), 16, vb, tk * 4096 + (j - TM) * nks * 1024, 0, 0);
+        } else if (j < TM)
             __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_t*)(s + (j * NW + wave) * 1024), 16, va,
                                                      (kt0 + kt) * 128 + j * (NW * 8) * row_bytes, 0, 0);
         else
@@ -232,6 +251,14 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
         return o;
     };
     const int piece = 16 * (lane >> 5) + 8 * ((lane >> 4) & 1);
+    const __amdgpu_buffer_rsrc_t rlo = __builtin_amdgcn_make_buffer_rsrc(
+        static_cast<bf16_t*>(a.Out) + int64_t(t_first) * a.c_tok_stride + (PARTS == 2 ? g.out_lo : 0), 0, 0x7fffffff, 0x00020000);
+    auto low = [](const floatx4& v) -> floatx4 {
+        floatx4 r;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) r[e] = low_part(v[e]);
+        return r;
+    };
     if (TRANS) {
         uint32_t base[TM / 2];
 #pragma unroll
@@ -262,6 +289,12 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
             for (int j = 0; j < TN / 2; ++j)
                 __builtin_amdgcn_raw_buffer_store_b128(merge(acc[i][2 * j], acc[i][2 * j + 1]), ro,
                                                        int(((base | co[j]) & OUT) ? ~0u : base + co[j]), 0, 0);
+            if (PARTS == 2 && g.out_lo) {
+#pragma unroll
+                for (int j = 0; j < TN / 2; ++j)
+                    __builtin_amdgcn_raw_buffer_store_b128(merge(low(acc[i][2 * j]), low(acc[i][2 * j + 1])), rlo,
+                                                           int(((base | co[j]) & OUT) ? ~0u : base + co[j]), 0, 0);
+            }
         }
     }
 #endif

@@ -76,6 +76,9 @@ struct DevStep {
     bool no_skinny = false;       // TN_FLAG_NO_SKINNY
     // gradient of the step's tensor as one product over the tokens: the row of c and the column of k in the caller's tensor
     const int32_t *grad_row = nullptr, *grad_col = nullptr;
+    // operands and output in two parts (see step_gemm_kernel): how far the low ones are, in elements, 0: one part
+    int64_t a_lo = 0, b_lo = 0, out_lo = 0;
+    int segments() const { return 1 + (a_lo != 0) + (b_lo != 0); }
 };
 
 // One product of the matrix plan (tn_matrix.hpp) as a launch of the matrix-product kernel. What it reads is either kept by
@@ -179,7 +182,8 @@ struct tn_linear_s {
     bool mgrad = false;
     int64_t mgrad_min_tokens = 0, mgrad_chunk = 0;
     int64_t mgrad_f[2] = {0, 0};              // modes of the halves
-    int64_t mgrad_off[8] = {};                // byte offsets in bwd_ws: X, dY, dW, dW transposed, the two operands, dH, dH transposed
+    int64_t mgrad_off[8] = {};                // byte offsets in bwd_ws: X, dY; in two parts each: dW, dW transposed, the two
+                                              // operands, dH, dH transposed
     DevStep mgrad_dw;                         // rows m, columns n; K, A and B are the call's
     struct GradHalf {
         bool pair = false;
@@ -476,7 +480,7 @@ constexpr float kGemmReduceUs = 4.f;
 // The tile size and the number of K ranges with the least time for `rows` rows; partial sums within `cap` bytes.
 GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int64_t cap) {
     GemmChoice best;
-    const int nk = s.Kp / 64;
+    const int nk = s.Kp / 64 * s.segments();
     const bool trans = s.cmode == 2;
     const int64_t cus = h->num_cus;
     for (int t = 0; t < kGemmTiles; ++t) {
@@ -515,15 +519,15 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
 
 using gemm_kern_t = void (*)(StepArgs, GemmArgs);
 
-template <int I, int TRANS>
+template <int I, int TRANS, int PARTS>
 constexpr gemm_kern_t gemm_kernel_of() {
     if constexpr (TRANS && (kGemmTile[I].tm & 1)) return nullptr;
-    else return step_gemm_kernel<kGemmTile[I].tm, kGemmTile[I].tn, TRANS>;
+    else return step_gemm_kernel<kGemmTile[I].tm, kGemmTile[I].tn, TRANS, PARTS>;
 }
 
-template <int TRANS, int... I>
+template <int TRANS, int PARTS, int... I>
 gemm_kern_t gemm_kernel_at(int tile, std::integer_sequence<int, I...>) {
-    static const gemm_kern_t k[kGemmTiles] = {gemm_kernel_of<I, TRANS>()...};
+    static const gemm_kern_t k[kGemmTiles] = {gemm_kernel_of<I, TRANS, PARTS>()...};
     return k[tile];
 }
 
@@ -533,16 +537,17 @@ size_t gemm_smem_at(int tile, std::integer_sequence<int, I...>) {
     return b[tile];
 }
 
-gemm_kern_t gemm_kernel(int tile, bool trans) {
+gemm_kern_t gemm_kernel(int tile, bool trans, bool parts) {
     using seq = std::make_integer_sequence<int, kGemmTiles>;
-    return trans ? gemm_kernel_at<1>(tile, seq()) : gemm_kernel_at<0>(tile, seq());
+    if (parts) return trans ? nullptr : gemm_kernel_at<0, 2>(tile, seq());
+    return trans ? gemm_kernel_at<1, 1>(tile, seq()) : gemm_kernel_at<0, 1>(tile, seq());
 }
 size_t gemm_smem(int tile) { return gemm_smem_at(tile, std::make_integer_sequence<int, kGemmTiles>()); }
 
 int configure_gemm() {
     for (int t = 0; t < kGemmTiles; ++t)
-        for (int trans = 0; trans < 2; ++trans) {
-            const gemm_kern_t k = gemm_kernel(t, trans != 0);
+        for (int form = 0; form < 3; ++form) {
+            const gemm_kern_t k = gemm_kernel(t, form == 1, form == 2);
             if (k && hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
                                          int(gemm_smem(t))) != hipSuccess)
                 return TN_ERR_HIP;
@@ -568,7 +573,7 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
     const bool trans = s.cmode == 2;
     const bool one_range = (h->flags & TN_FLAG_NO_SPLIT_K) || !partial || (f32 && f32->sums);
     const GemmChoice c = gemm_choice(h, s, rows, one_range ? 0 : partial_bytes);
-    if (c.tile < 0) return TN_ERR_UNSUPPORTED;
+    if (c.tile < 0 || (trans && (s.a_lo || s.b_lo || s.out_lo))) return TN_ERR_UNSUPPORTED;
     if (f32 && !f32->sums && (!partial || int64_t(c.n_split) * rows * s.Cp * 4 > partial_bytes)) return TN_ERR_UNSUPPORTED;
     const GemmTile& t = kGemmTile[c.tile];
     GemmArgs g;
@@ -578,6 +583,10 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
     g.ktiles_per_split = c.ktiles_per_split;
     g.rows_pad = rows;
     g.ld = s.Cp;
+    g.a_lo = s.a_lo;
+    g.b_lo = s.b_lo;
+    g.out_lo = s.out_lo;
+    const bool parts = s.a_lo || s.b_lo || s.out_lo;
     g.partial = c.n_split > 1 || f32 ? static_cast<float*>(partial) : nullptr;
     if (f32) {
         if (f32->sums) {
@@ -587,11 +596,11 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
         *f32 = GemmSums{g.partial, g.ld, c.n_split};
     }
     const int64_t items = int64_t(g.n_row) * g.n_col * g.n_split;
-    hipLaunchKernelGGL(gemm_kernel(c.tile, trans), dim3(uint32_t((items + 7) / 8 * 8)), dim3(256), gemm_smem(c.tile), st, a, g);
+    hipLaunchKernelGGL(gemm_kernel(c.tile, trans, parts), dim3(uint32_t((items + 7) / 8 * 8)), dim3(256), gemm_smem(c.tile), st, a, g);
     if (c.n_split > 1 && !f32) {
         const int64_t total = rows * s.plan.C;
         hipLaunchKernelGGL(step_split_reduce_kernel, dim3(uint32_t(std::min<int64_t>((total + 255) / 256, 2048))), dim3(256), 0, st,
-                           a, g.partial, c.n_split, uint32_t(rows));
+                           a, g.partial, c.n_split, uint32_t(rows), s.out_lo);
     }
     return TN_OK;
 }
@@ -739,7 +748,7 @@ int launch_step(const tn_linear_s* h, const Workspace& w, const DevStep& s, cons
             int64_t total = rows * s.plan.C;
             uint32_t blocks = uint32_t(std::min<int64_t>((total + 255) / 256, 2048));
             hipLaunchKernelGGL(step_split_reduce_kernel, dim3(blocks), dim3(256), 0, st, a, part, sc.nsplit,
-                               uint32_t(sc.row_tiles * 32 * sc.tm));
+                               uint32_t(sc.row_tiles * 32 * sc.tm), int64_t(0));
         }
         return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
     }
@@ -1662,7 +1671,7 @@ int prepare_lazy(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
 
 // What one launch of a product takes, in us: its tiles, or the stores of its output.
 float product_us(const tn_linear_s* h, const DevStep& s) {
-    return 3.f + std::max(gemm_choice(h, s, s.plan.R, 0).us, float(s.plan.R) * float(s.plan.C) * 2.f / 3.5e6f);
+    return 3.f + std::max(gemm_choice(h, s, s.plan.R, 0).us, float(s.plan.R) * float(s.plan.C) * (s.out_lo ? 4.f : 2.f) / 3.5e6f);
 }
 
 // Decide whether calls of many tokens contract the tensors with each other first, from how many tokens on, and prepare it.
@@ -2475,7 +2484,11 @@ int launch_param_gradient(const tn_linear_s* h, const DevStep& s, const void* dO
 constexpr int64_t kGradMinTokens = 16;        // one token range is padded to 64
 constexpr int kGradSumsPad = 128;             // columns of the core gradients (a bond): padded to the narrow tiles
 
-// Decide whether gradients of many tokens go through dW, and prepare it. The steps are priced at 0.35e9 FLOP per us and 40 us
+// Decide whether gradients of many tokens go through dW, and prepare it. dW and dH are sums over the tokens and the products of
+// two cores meet such a sum: they are kept in two parts each, as the caller gets fp32 (in one
+// part, core gradients of the rank-64 train 5120 -> 8192 at 1024 tokens with a common component are 2.9e-3 off in the 2-norm, in
+// two 5e-6; the steps, whose roundings average out over the tokens, leave 0.9 to 1.8e-4. The train's fine-tuning step takes 642 us,
+// with one part 525). The steps are priced at 0.35e9 FLOP per us and 40 us
 // a step (train 5120 -> 8192 of rank 64: 9.7 ms at 1024 tokens; ring 25600 -> 5120 of rank 32: 12.5 ms at 64).
 int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     const int64_t M = h->plan.M, N = h->plan.N;
@@ -2505,14 +2518,15 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
     int64_t fixed = 0;
     auto room = [&](int i, int64_t elems) {
         h->mgrad_off[i] = fixed;
-        fixed += (elems * 2 + 255) & ~int64_t(255);
+        fixed += (elems * 4 + 255) & ~int64_t(255);      // two parts
     };
     float us = 20.f;
     int64_t sums = 0;
     if (!dense) {
         room(2, M * N);
         room(3, M * N);
-        us += float(M * N) * 6.f / 3.5e6f;
+        h->mgrad_dw.out_lo = M * N;
+        us += 6.f + float(M * N) * 8.f / 3.5e6f;
         int64_t dh = 0, dht = 0;
         for (int i = 0; i < 2; ++i) {
             const tn::MatrixGradHalf& G = g.half[i];
@@ -2526,19 +2540,23 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
             H.out_a = G.out_a;
             H.out_b = G.out_b;
             step(&H.dh, F, Fo, m.Kr, F * m.Kr, G.pair ? tn::kMatrixColPad : kGradSumsPad);
-            us += 3.f + std::max(gemm_choice(h, H.dh, F, kMaxGradPartialBytes).us, float(F * (Fo + m.Kr)) * 2.f / 3.5e6f);
+            H.dh.a_lo = M * N;
+            H.dh.b_lo = g.half[1 - i].pair ? g.half[1 - i].op.out_elems : 0;
+            H.dh.out_lo = G.pair ? F * m.Kr : 0;
+            us += 3.f + std::max(gemm_choice(h, H.dh, F, kMaxGradPartialBytes).us, float(F * (Fo + m.Kr)) * 4.f / 3.5e6f);
             if (!G.pair) {
                 sums = std::max(sums, F * H.dh.Cp * 4);
                 continue;
             }
             if (F * m.Kr > tn::kMatrixMaxElems) return TN_OK;
             fill_product_step(&H.op.s, G.op);
+            H.op.s.out_lo = G.op.out_elems;
             us += product_us(h, H.op.s);
             room(4 + i, G.op.out_elems);
             dh = std::max(dh, G.F1 * G.F2);
             dht = std::max(dht, tn::detail::round64(G.F1) * G.F2);
             sums = std::max(sums, std::max(G.F1, G.F2) * round_up(int(H.S), kGradSumsPad) * 4);
-            us += 60.f + float(G.F1 * G.F2) * 6.f / 3.5e6f;
+            us += 80.f + float(G.F1 * G.F2) * 12.f / 3.5e6f;
         }
         room(6, dh);
         room(7, dht);
@@ -2554,7 +2572,7 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
     for (int64_t t = kGradMinTokens; t <= desc->max_tokens && !from; t += t < 64 ? 8 : t / 8) {
         DevStep dw = h->mgrad_dw;
         dw.Kp = int(grad_tokens_pad(std::min(t, chunk)));
-        const float product = std::max(gemm_choice(h, dw, M, 0).us, float(M * N) * (dense ? 4.f : 2.f) / 3.5e6f);
+        const float product = std::max(gemm_choice(h, dw, M, 0).us, float(M * N) * 4.f / 3.5e6f);
         if (us + product + float(t) * float(M + N) * 4.f / 3.5e6f < float(t) * flops / 0.35e9f + 40.f * float(h->steps.size())) from = t;
     }
     if (!from) return TN_OK;
@@ -2678,7 +2696,12 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
         }
         rc = launch_product_of(h, dw, at(1), at(0), at(2), part, part_bytes, st);
         if (rc != TN_OK) return rc;
-        if (wanted[1]) launch_transpose(at(2), at(3), h->mgrad_f[0], h->mgrad_f[1], h->mgrad_f[0], false, st);
+        // both parts of a matrix [r][c], the low one right after the high one
+        auto transpose_parts = [&](int from, int to, int64_t r, int64_t c, int64_t rp) {
+            for (int part = 0; part < 2; ++part)
+                launch_transpose(static_cast<char*>(at(from)) + part * r * c * 2, static_cast<char*>(at(to)) + part * c * rp * 2, r, c, rp, false, st);
+        };
+        if (wanted[1]) transpose_parts(2, 3, h->mgrad_f[0], h->mgrad_f[1], h->mgrad_f[0]);
         for (int i = 0; i < 2; ++i) {
             if (!wanted[i]) continue;
             const auto& H = h->mgrad_half[i];
@@ -2697,11 +2720,12 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
                 float* grad = static_cast<float*>(grads[side == 0 ? H.out_a.slot : H.out_b.slot]);
                 if (!grad) continue;
                 const int64_t f1p = tn::detail::round64(H.F1);
-                if (side == 1) launch_transpose(at(6), at(7), H.F1, H.F2, f1p, false, st);
+                if (side == 1) transpose_parts(6, 7, H.F1, H.F2, f1p);
                 DevStep s;
                 s.plan.R = side == 0 ? H.F1 : H.F2;
                 s.plan.C = H.S;
                 s.plan.K = side == 0 ? H.F2 : f1p;
+                s.a_lo = side == 0 ? H.F1 * H.F2 : H.F2 * f1p;
                 s.Kp = int(s.plan.K);
                 s.Cp = round_up(int(H.S), kGradSumsPad);
                 s.cmode = 1;

@@ -137,3 +137,27 @@ def test_gradients_through_dw(case):
                                              tokens, torch.cuda.current_stream().cuda_stream)
         assert torch.equal(last, got[-1])
     layer.close()
+
+
+@pytest.mark.parametrize("mean", [0.0, 1.0, 5.0])
+@pytest.mark.parametrize("case", range(len(GRAD_CASES)))
+def test_gradients_keep_what_averages_out_over_tokens(case, mean):
+    """Activations and output gradients with a component common to all tokens, as in fine-tuning: the sum over tokens has to be
+    held to more than bf16. Relative 2-norm error; every product of a sum leaves at most 2 * 2^-16 (the low part's rounding, and the
+    product of two low parts) = 3e-5 of its terms, three products in a row 1e-4. (Rounded to bf16 the sum left 2.8e-3, and the
+    steps that round per token leave 1e-4 to 3e-4 where there is such a component.)"""
+    fmt, om, im, rk, flags = GRAD_CASES[case]
+    spec = wl.TNSpec(fmt, "bf16", om, im, rk)
+    rng = np.random.default_rng(560 + case)
+    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(max(1, s[-1])), "bf16") for s in spec.tensor_shapes()]
+    layer = make_layer(spec, ts, 1000, flags=tn.TN_FLAG_TRAINABLE | flags)
+    assert layer.query(tn.TN_QUERY_BACKWARD_CHUNK_TOKENS) == 1024
+    x = wl.round_to_dtype(rng.standard_normal((1025, layer.N)) + mean * rng.choice([-1.0, 1.0], layer.N), "bf16")
+    dy = wl.round_to_dtype(rng.standard_normal((1025, layer.M)) + mean * rng.choice([-1.0, 1.0], layer.M), "bf16")
+    for tokens in (1000, 1025):
+        got = layer.param_gradients(to_dev(x[:tokens], "bf16"), to_dev(dy[:tokens], "bf16"))
+        ref = O.param_gradients(fmt, ts, dy[:tokens] if flags else x[:tokens], x[:tokens] if flags else dy[:tokens], n_out_modes=len(om))
+        for n, (g, r) in enumerate(zip(got, ref)):
+            err = np.linalg.norm(to_host(g) - r) / np.linalg.norm(r)
+            assert err <= 1e-4, (case, tokens, n, err)
+    layer.close()
