@@ -66,6 +66,7 @@ struct MatrixPlan {
 
 constexpr int64_t kMatrixMaxElems = int64_t(1) << 30;      // outputs are addressed with 31-bit byte offsets
 constexpr int kMatrixColPad = 256;
+constexpr int64_t kMatrixMaxDigits = int64_t(1) << 22;     // positions that a check value by value walks (64 MB of host memory)
 
 namespace detail {
 
@@ -79,7 +80,7 @@ bool digit_offsets(const std::vector<int>& ids, const std::vector<int64_t>& ext,
     for (size_t j = ids.size(); j-- > 0;) {
         weight[j] = total;
         total *= ext[size_t(ids[j])];
-        if (total > kMatrixMaxElems) return false;
+        if (total > kMatrixMaxDigits) return false;
     }
     std::vector<int64_t> sums(1, 0);       // of every position over the ids so far
     for (size_t j = 0; j < ids.size(); ++j) {
@@ -95,6 +96,17 @@ bool digit_offsets(const std::vector<int>& ids, const std::vector<int64_t>& ext,
     for (int64_t p = 0; p < total; ++p)
         if (sums[size_t(p)] != f(p)) return false;
     return true;
+}
+
+// The same where f is the position itself: a sum by construction, whatever its length.
+inline void flat_offsets(const std::vector<int>& ids, const std::vector<int64_t>& ext, DigitOffsets* out) {
+    int64_t weight = 1;
+    for (size_t j = ids.size(); j-- > 0;) {
+        std::vector<int64_t>& v = (*out)[ids[j]];
+        v.clear();
+        for (int64_t d = 0; d < ext[size_t(ids[j])]; ++d) v.push_back(d * weight);
+        weight *= ext[size_t(ids[j])];
+    }
 }
 
 // ids with the one whose neighbouring digits lie closest in the output innermost
@@ -419,11 +431,11 @@ inline bool make_matrix_grad(const Plan& net, const MatrixPlan& m, MatrixGrad* g
                 for (int i : bond) (contains(net.tensors[size_t(tb)].idx, i) ? f2 : f1).push_back(i);
                 G.F1 = prod_extents(f1, md.ext);
                 G.F2 = prod_extents(f2, md.ext);
-                if (G.F2 % 64) continue;
+                if (G.F2 % 64 || G.F1 > kMatrixMaxElems / G.F2) continue;
                 DigitOffsets t;
                 std::vector<int> all = f1;
                 all.insert(all.end(), f2.begin(), f2.end());
-                if (!digit_offsets(all, md.ext, [](int64_t p) { return p; }, &t)) continue;
+                flat_offsets(all, md.ext, &t);
                 G.row_off = digit_table(number[h], md.ext, t);
                 G.col_off = digit_table(bond, md.ext, t);
                 if (run_length(G.col_off, 8) != 8 || !all_multiple_of(G.row_off, 8)) continue;

@@ -324,3 +324,11 @@ extern "C" int plan_host_slices(const tn_linear_desc* d, const double* const* te
                 }
     return 0;
 }
+
+// The plan of the gradients alone: 0, or 1 when the layer has none.
+extern "C" int plan_host_matrix_grad_plan(const tn_linear_desc* d) {
+    tn::Plan net;
+    tn::MatrixPlan m;
+    tn::MatrixGrad g;
+    return tn::make_matrix_plan(d, &net, &m) && tn::make_matrix_grad(net, m, &g) ? 0 : 1;
+}

@@ -4,6 +4,7 @@ test-only C++ walker of the plan and compared with the oracle."""
 import ctypes
 import os
 import subprocess
+import sys
 import tempfile
 
 import numpy as np
@@ -508,3 +509,20 @@ def test_slices_as_products(host_exec, case):
     assert rc == (0 if planned else 1), rc
     if planned:
         assert np.max(np.abs(w - w_ref)) <= 1e-12 * np.max(np.abs(w_ref))
+
+
+def test_gradient_plan_of_a_large_ring_in_little_memory(host_exec):
+    """The rank-96 ring 25600 -> 5120: tables of its modes and bonds, nothing as long as a half with its bond (0.9 GB of int64)."""
+    spec = wl.stack_spec(wl.FORMAT_TR, 25600, 5120, 96)
+    code = f"""
+import ctypes, resource
+import paper_2602_01613_amd as tn
+from paper_2602_01613_amd.binding import _Desc, _make_desc
+lib = ctypes.CDLL({host_exec._name!r})
+d, keep = _make_desc({spec.format}, tn.TN_DTYPE_BF16, {spec.out_modes}, {spec.in_modes}, {spec.ranks}, None, 1, 0, 0, None)
+used = int(open("/proc/self/statm").read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (128 << 20), resource.getrlimit(resource.RLIMIT_AS)[1]))
+raise SystemExit(lib.plan_host_matrix_grad_plan(ctypes.byref(d)))
+"""
+    res = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(HERE), capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-500:]
