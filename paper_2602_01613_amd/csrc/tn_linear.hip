@@ -160,6 +160,13 @@ struct tn_linear_s {
     DevProduct mat_half[2], mat_w;
     DevStep mat_y;
     std::vector<void*> mat_kept;              // operands made from the caller's tensors, and the tables
+    std::vector<std::vector<int32_t>> create_tables;     // host copies of tables on their way to the GPU, until create's last wait
+    // the plan of that order, made once and used by the two prepare functions; cleared when create ends
+    struct MatrixPlans {
+        bool tried = false, ok = false;
+        tn::Plan net;
+        tn::MatrixPlan m;
+    } matrix_plans;
     // 4-bit form of the caller's tensors (TN_FLAG_QUANT_MXFP4): packed codes and block exponents per tensor
     std::vector<void*> quant_codes, quant_exps;
     std::vector<int64_t> quant_elems;
@@ -482,22 +489,24 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
     GemmChoice best;
     const int nk = s.Kp / 64 * s.segments();
     const bool trans = s.cmode == 2;
-    const int64_t cus = h->num_cus;
+    const uint32_t cus = uint32_t(h->num_cus);
     for (int t = 0; t < kGemmTiles; ++t) {
         const GemmTile& g = kGemmTile[t];
-        if (s.Cp % (32 * g.tn) || (trans && (g.tm & 1))) continue;
-        const int64_t tiles = ((rows + 32 * g.tm - 1) / (32 * g.tm)) * ((s.plan.C + 32 * g.tn - 1) / (32 * g.tn));
-        if (tiles > (int64_t(1) << 26)) continue;
+        if (uint32_t(s.Cp) % uint32_t(32 * g.tn) || (trans && (g.tm & 1))) continue;
+        const int64_t all_tiles = int64_t((uint32_t(rows) + 32 * g.tm - 1) / uint32_t(32 * g.tm)) *
+                                  ((uint32_t(s.plan.C) + 32 * g.tn - 1) / uint32_t(32 * g.tn));      // rows and columns below 2^31
+        if (all_tiles > (int64_t(1) << 26)) continue;
+        const uint32_t tiles = uint32_t(all_tiles);
         for (int ns = 1; ns <= 8; ++ns) {
             // more ranges only while they fill an idle chip, at least 4 K tiles each
-            if (ns > 1 && (trans || tiles * (ns - 1) >= 2 * cus || nk < 4 * ns)) break;
+            if (ns > 1 && (trans || tiles * uint32_t(ns - 1) >= 2 * cus || nk < 4 * ns)) break;
             const int per = (nk + ns - 1) / ns, n_real = (nk + per - 1) / per;
             if (n_real != ns) continue;
             const int64_t pb = ns > 1 ? int64_t(ns) * rows * s.Cp * 4 : 0;
             if (pb > cap) break;
-            const int64_t items = tiles * ns;
-            const int64_t slots = g.t2 > 0.f ? 2 * cus : cus;
-            const int64_t full = items / slots, rest = items - full * slots;
+            const uint32_t items = tiles * uint32_t(ns);
+            const uint32_t slots = g.t2 > 0.f ? 2 * cus : cus;
+            const uint32_t full = items / slots, rest = items - full * slots;
             const bool half = g.t2 > 0.f && rest > 0 && rest <= cus;            // a last round with one workgroup per CU
             const float per_tile = g.t2 > 0.f ? g.t2 : g.t1, per_round = g.t2 > 0.f ? g.o2 : g.o1;
             const float rounds = float(full + (rest > 0 && !half ? 1 : 0));
@@ -1443,6 +1452,20 @@ void fill_gen_dims(GenDims* g, const std::vector<tn::GatherDim>& d) {
     }
 }
 
+// Tables to the GPU without waiting for them: the host copy stays with the handle until create's last wait.
+int upload_tables(tn_linear_s* h, std::vector<int32_t>&& tab, void* dst, hipStream_t st) {
+    h->create_tables.push_back(std::move(tab));
+    const std::vector<int32_t>& t = h->create_tables.back();
+    return hipMemcpyAsync(dst, t.data(), t.size() * sizeof(int32_t), hipMemcpyHostToDevice, st) == hipSuccess ? TN_OK : TN_ERR_HIP;
+}
+
+bool matrix_plan_of(tn_linear_s* h, const tn_linear_desc* desc) {
+    tn_linear_s::MatrixPlans& p = h->matrix_plans;
+    if (!p.tried) p.ok = tn::make_matrix_plan(desc, &p.net, &p.m);
+    p.tried = true;
+    return p.ok;
+}
+
 // An operand kept for the products: allocated, written on `st`, freed with the handle.
 int keep_operand(tn_linear_s* h, const tn_linear_desc* desc, const tn::SourceOp& o, int64_t Kp, bool packed, void** out, hipStream_t st,
                  std::vector<void*>* owner = nullptr) {
@@ -1722,9 +1745,8 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
         return int64_t(0);
     };
     if (!first_tokens(6.f + float(h->plan.M) * float(h->plan.N) * 2.f / 3.5e6f)) return TN_OK;
-    tn::Plan net;
-    tn::MatrixPlan m;
-    if (!tn::make_matrix_plan(desc, &net, &m)) return TN_OK;
+    if (!matrix_plan_of(h, desc)) return TN_OK;
+    const tn::MatrixPlan& m = h->matrix_plans.m;
     h->mat_bytes = m.w_elems * 2;
     float us = 0.f;
     for (int i = 0; i < 2; ++i) {
@@ -1768,9 +1790,7 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     void* tables = nullptr;
     if (hipMalloc(&tables, tab.size() * sizeof(int32_t)) != hipSuccess) return TN_ERR_ALLOC;
     h->mat_kept.push_back(tables);
-    if (hipMemcpyAsync(tables, tab.data(), tab.size() * sizeof(int32_t), hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return TN_ERR_HIP;
+    if (upload_tables(h, std::move(tab), tables, st) != TN_OK) return TN_ERR_HIP;
     auto set_tables = [&](DevStep* s, int i) {
         s->crow = static_cast<const int32_t*>(tables) + at[i];
         s->ccol = static_cast<const int32_t*>(tables) + at[i + 1];
@@ -2498,10 +2518,9 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
         return TN_OK;
     const bool dense = h->plan.format == TN_FORMAT_DENSE;
     if (dense && (desc->flags & TN_FLAG_TRANSPOSE)) return TN_OK;
-    tn::Plan net;
-    tn::MatrixPlan m;
+    const tn::MatrixPlan& m = h->matrix_plans.m;
     tn::MatrixGrad g;
-    if (!dense && (!tn::make_matrix_plan(desc, &net, &m) || !tn::make_matrix_grad(net, m, &g))) return TN_OK;
+    if (!dense && (!matrix_plan_of(h, desc) || !tn::make_matrix_grad(h->matrix_plans.net, m, &g))) return TN_OK;
     auto step = [&](DevStep* s, int64_t R, int64_t K, int64_t C, int64_t out_elems, int pad) {
         s->plan.R = R;
         s->plan.K = K;
@@ -2602,9 +2621,7 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
     void* tables = nullptr;
     if (hipMalloc(&tables, std::max<size_t>(1, tab.size()) * sizeof(int32_t)) != hipSuccess) return TN_ERR_ALLOC;
     h->mat_kept.push_back(tables);
-    if (hipMemcpyAsync(tables, tab.data(), tab.size() * sizeof(int32_t), hipMemcpyHostToDevice, st) != hipSuccess ||
-        hipStreamSynchronize(st) != hipSuccess)
-        return TN_ERR_HIP;
+    if (!tab.empty() && upload_tables(h, std::move(tab), tables, st) != TN_OK) return TN_ERR_HIP;
     for (auto& w : where) {
         w.first->crow = static_cast<const int32_t*>(tables) + w.second.first;
         w.first->ccol = static_cast<const int32_t*>(tables) + w.second.second;
@@ -3210,6 +3227,8 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
     }
     for (void* v : h->create_temps) (void)hipFree(v);
     h->create_temps.clear();
+    h->create_tables = {};
+    h->matrix_plans = {};
     *out = h;
     return TN_OK;
 }

@@ -82,16 +82,15 @@ bool digit_offsets(const std::vector<int>& ids, const std::vector<int64_t>& ext,
         total *= ext[size_t(ids[j])];
         if (total > kMatrixMaxDigits) return false;
     }
-    std::vector<int64_t> sums(1, 0);       // of every position over the ids so far
-    for (size_t j = 0; j < ids.size(); ++j) {
+    // sums of every position, grown from the innermost id outwards
+    std::vector<int64_t> sums(size_t(total), 0);
+    for (size_t j = ids.size(); j-- > 0;) {
         std::vector<int64_t>& v = (*out)[ids[j]];
-        v.clear();
-        for (int64_t d = 0; d < ext[size_t(ids[j])]; ++d) v.push_back(f(d * weight[j]));
-        std::vector<int64_t> next;
-        next.reserve(sums.size() * v.size());
-        for (int64_t s : sums)
-            for (int64_t o : v) next.push_back(s + o);
-        sums.swap(next);
+        v.resize(size_t(ext[size_t(ids[j])]));
+        for (size_t d = v.size(); d-- > 0;) {
+            v[d] = f(int64_t(d) * weight[j]);
+            for (int64_t p = 0; p < weight[j]; ++p) sums[d * size_t(weight[j]) + size_t(p)] = sums[size_t(p)] + v[d];
+        }
     }
     for (int64_t p = 0; p < total; ++p)
         if (sums[size_t(p)] != f(p)) return false;
@@ -122,10 +121,10 @@ inline std::vector<int32_t> digit_table(const std::vector<int>& ids, const std::
     std::vector<int32_t> tab(1, 0);
     for (int i : ids) {
         const std::vector<int64_t>& v = t.at(i);
-        std::vector<int32_t> next;
-        next.reserve(tab.size() * v.size());
+        std::vector<int32_t> next(tab.size() * v.size());
+        size_t at = 0;
         for (int32_t o : tab)
-            for (int64_t d : v) next.push_back(o + int32_t(d));
+            for (int64_t d : v) next[at++] = o + int32_t(d);
         tab.swap(next);
     }
     return tab;
@@ -198,8 +197,9 @@ inline bool pair_product(const Plan& p, const std::vector<int64_t>& ext, int ta,
 
 }  // namespace detail
 
-// The plan for one cut of the network: the tensors of group[0] and of group[1], one or two each.
-inline bool matrix_plan_of_cut(const Plan& net, const std::vector<int> (&group)[2], MatrixPlan* m) {
+// The plan for one cut of the network: the tensors of group[0] and of group[1], one or two each. `wt`: offsets of the modes' digits
+// in the packed W.
+inline bool matrix_plan_of_cut(const Plan& net, const std::vector<int> (&group)[2], const detail::DigitOffsets& wt, MatrixPlan* m) {
     using namespace detail;
     std::vector<int> open[2];              // ids of a group that its own tensors do not contract
     for (int g = 0; g < 2; ++g) {
@@ -216,7 +216,6 @@ inline bool matrix_plan_of_cut(const Plan& net, const std::vector<int> (&group)[
     *m = MatrixPlan();
     m->M = net.M;
     m->N = net.N;
-    if (m->N % 64 || m->M % 8 || m->N >= (int64_t(1) << 21)) return false;
     for (int i : open[1 - q])
         if (contains(open[q], i)) m->bond.push_back(i);
     if (m->bond.empty() || m->bond.size() > 2) return false;
@@ -226,10 +225,6 @@ inline bool matrix_plan_of_cut(const Plan& net, const std::vector<int> (&group)[
     std::vector<int64_t> ext = net.extent;
     if (m->bond.size() == 1) ext[size_t(m->bond[0])] = m->Krp;
     else if (m->Kr != m->Krp) return false;
-    DigitOffsets wt;
-    const int64_t nks = m->N / 16;
-    if (!digit_offsets(net.y_idx, ext, [&](int64_t c) { return packed_col(c, nks); }, &wt) || !digit_offsets(net.x_idx, ext, packed_k, &wt))
-        return false;
     m->w_elems = (m->M + kMatrixColPad - 1) / kMatrixColPad * kMatrixColPad * m->N;
     if (m->w_elems > kMatrixMaxElems) return false;
     for (int h = 0; h < 2; ++h) {
@@ -280,19 +275,34 @@ inline bool make_matrix_plan(const tn_linear_desc* d, Plan* net, MatrixPlan* m) 
     if (n < 2 || n > 4) return false;
     for (const NetTensor& T : net->tensors)
         if (T.trace_extent != 1) return false;
-    bool found = false;
+    if (net->N % 64 || net->M % 8 || net->N >= (int64_t(1) << 21)) return false;
+    detail::DigitOffsets wt;
+    const int64_t nks = net->N / 16;
+    if (!detail::digit_offsets(net->y_idx, net->extent, [&](int64_t c) { return packed_col(c, nks); }, &wt) ||
+        !detail::digit_offsets(net->x_idx, net->extent, packed_k, &wt))
+        return false;
+    // the cuts, smallest bond first: the first that has a plan is the one
+    struct Cut {
+        int64_t bond;
+        std::vector<int> group[2];
+    };
+    std::vector<Cut> cuts;
     for (int first = 0; first < (d->format == TN_FORMAT_TR ? n : 1); ++first)
         for (int len = 1; len < n; ++len) {
             if (len > 2 || n - len > 2) continue;
-            std::vector<int> group[2];
-            for (int j = 0; j < n; ++j) group[j < len ? 0 : 1].push_back((first + j) % n);
-            MatrixPlan c;
-            if (matrix_plan_of_cut(*net, group, &c) && (!found || c.Kr < m->Kr)) {
-                *m = c;
-                found = true;
-            }
+            Cut c{1, {}};
+            for (int j = 0; j < n; ++j) c.group[j < len ? 0 : 1].push_back((first + j) % n);
+            std::vector<int> shared;
+            for (int t : c.group[0])
+                for (int u : c.group[1])
+                    for (int i : detail::shared_ids(net->tensors[size_t(t)], net->tensors[size_t(u)])) shared.push_back(i);
+            c.bond = detail::prod_extents(shared, net->extent);
+            cuts.push_back(c);
         }
-    return found;
+    std::stable_sort(cuts.begin(), cuts.end(), [](const Cut& x, const Cut& y) { return x.bond < y.bond; });
+    for (const Cut& c : cuts)
+        if (matrix_plan_of_cut(*net, c.group, wt, m)) return true;
+    return false;
 }
 
 // ---- gradients of the parameter tensors on the same cut ----
