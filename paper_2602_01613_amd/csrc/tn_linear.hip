@@ -618,6 +618,19 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
     return TN_OK;
 }
 
+// A launch for the matrix-product kernel: more than a row tile of rows, and not a short K whose output blocks fill at most one round
+// of the split-K kernel in one range, which then has the shorter chain: 0.95 us and 0.115 per 16 k (core of the rank-64 Tucker
+// layer 5120 -> 1024 at 460 tokens, K = 1024: 8.3 us, 9.5 on 64 x 64 tiles; K = 2304 17.7, 12.5 in four ranges). A tile's first
+// loads come 1.2 us later than gemm_choice has it, which compares tiles with each other.
+bool gemm_rows(const tn_linear_s* h, const DevStep& s, int64_t rows) {
+    if (rows < kGemmMinRows || !gemm_fits(s)) return false;
+    const float split_us = 0.95f + 0.115f * float(s.Kp / 16);
+    if (split_us > 10.f || s.q4_codes || (h->flags & TN_FLAG_NO_SPLIT_K)) return true;
+    const SplitCfg c = split_config(s, rows);
+    if (!c.use || c.nsplit != 1 || c.lds_rows || c.skinny || int64_t(c.row_tiles) * c.col_blocks > h->num_cus) return true;
+    return split_us > gemm_choice(h, s, rows, 0).us + 1.2f;
+}
+
 // One product of the matrix plan: out[crow[r] + ccol[c]] = sum_k A[r][k] B[c][k], or its fp32 sums.
 int launch_product_of(const tn_linear_s* h, const DevStep& s, const void* A, const void* B, void* out, void* partial,
                       int64_t partial_bytes, hipStream_t st, GemmSums* f32 = nullptr) {
@@ -714,7 +727,7 @@ int launch_step(const tn_linear_s* h, const Workspace& w, const DevStep& s, cons
     a.Kp = s.Kp;
     a.C = int32_t(s.plan.C);
     a.Cp = s.Cp;
-    if (rows >= kGemmMinRows && gemm_fits(s)) {
+    if (gemm_rows(h, s, rows)) {
         const int rc = launch_gemm(h, s, a, rows, w.partial, w.partial_bytes, st);
         if (rc != TN_OK) return rc;
         return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;

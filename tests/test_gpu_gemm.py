@@ -33,6 +33,22 @@ def test_dense_tile_edges(n_in, n_out):
     layer.close()
 
 
+@pytest.mark.parametrize("n_out", [1024, 4104])
+def test_short_k_between_the_two_kernels(n_out):
+    """K = 1024: row counts on both sides of where the split-K kernel in one range gives way to the tiles, and back."""
+    spec = wl.TNSpec(wl.FORMAT_DENSE, "bf16", (n_out,), (1024,), ())
+    rng = np.random.default_rng(n_out)
+    w = wl.round_to_dtype(rng.standard_normal((n_out, 1024)) / 32, "bf16")
+    x = wl.round_to_dtype(rng.standard_normal((520, 1024)), "bf16")
+    ref = x @ w.T
+    layer = make_layer(spec, [w], 520)
+    xd = to_dev(x, "bf16")
+    for rows in (64, 65, 100, 128, 129, 320, 321, 385, 460, 512, 513, 520):
+        y = to_host(layer(xd[:rows].contiguous()))
+        assert np.max(np.abs(y - ref[:rows])) <= 2.0 ** -8 * np.max(np.abs(ref[:rows])) + 1e-3, (rows, n_out)
+    layer.close()
+
+
 @pytest.mark.parametrize("tokens", [65, 130, 999])
 def test_outputs_along_the_rows(tokens):
     """A last step whose output runs along its rows (stores of 8 rows), rows of several tokens in one tile."""
