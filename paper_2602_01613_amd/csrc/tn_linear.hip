@@ -1100,6 +1100,25 @@ constexpr int64_t kKronShareMaxTokens = 1;
 // 64 tokens 0.63 / 0.67, 128 1.15 / 1.23, 300 2.46 / 2.74, 8192 58.4 / 65.6)
 constexpr int64_t kKronTwoTokensMin = 64;
 
+// workgroups a CU holds at a time: one when the three LDS stages take more than half of its 160 KB
+int kron_per_cu(const tn::KronDims& d) {
+    const int* c = tn::kKronConfig[d.cfg];
+    return 3 * 4096 * ((c[3] * c[1] + c[2] * 2 * c[0] + 3) / 4) > 80 * 1024 ? 1 : 2;
+}
+
+// What a launch of the Kronecker-sum kernel is expected to take: 22 ns per MFMA of a wave, values of the bond one after another,
+// in rounds of one or two workgroups per CU, two on a CU sharing its matrix cores (train 5120 -> 25600 of rank 96: 387 tokens are
+// 245 workgroups and 200 us, 512 are 320 and 395), and the partial sums.
+float kron_us(const tn_linear_s* h, const tn::KronDims& d, const KronGeom& g) {
+    const int* c = tn::kKronConfig[d.cfg];
+    const int64_t slots = int64_t(h->num_cus) * kron_per_cu(d);
+    const int64_t wgs = g.quads * g.n_chunks * g.n_splits;
+    const int64_t rounds = (wgs + slots - 1) / slots, turns = (wgs + h->num_cus - 1) / h->num_cus;
+    const float per_rho = float(c[3] * c[0] * (c[1] + 2 * c[2]) * g.tpw) * 0.022f;
+    return 10.f + float(rounds) * 10.f + float(turns) * float(g.rho_per_split) * per_rho +
+           float(g.partial_bytes) / kGemmPartialBytesPerUs;
+}
+
 KronGeom kron_geometry(const tn_linear_s* h, const tn::KronDims& d, int64_t tokens, int64_t partial_cap) {
     KronGeom g;
     const int o1_chunk = 32 * tn::kKronConfig[d.cfg][3];
@@ -1112,27 +1131,41 @@ KronGeom kron_geometry(const tn_linear_s* h, const tn::KronDims& d, int64_t toke
     }
     g.quads = g.share ? tokens : (tokens + 4 * g.tpw - 1) / (4 * g.tpw);
     int64_t base = g.quads * g.n_chunks;
-    // workgroups a CU holds at a time: one when the three LDS stages take more than half of its 160 KB
-    const int* cfg = tn::kKronConfig[d.cfg];
-    const int64_t stage_bytes = 4096 * int64_t((cfg[3] * cfg[1] + cfg[2] * 2 * cfg[0] + 3) / 4);
-    // (two rounds of such workgroups pay the start, the input's fragments and the partial sums twice: 5120 -> 25600 with its
-    // five chunks of o1, us per call in two rounds / one: rank 32 84 / 65 at one token, 133 / 100 at 8; rank 64 150 / 143 and
-    // 284 / 248; rank 96 361 / 347 and 600 / 555)
-    const int64_t per_cu = 3 * stage_bytes > 80 * 1024 ? 1 : 2;
-    // as many splits as keep the grid within one round of workgroups (rounding up instead left a second round with a
-    // handful of workgroups: 300 tokens took as long as 512)
-    int64_t want = std::max<int64_t>(1, per_cu * int64_t(h->num_cus) / base);
-    if (base >= h->num_cus) want = 1;
-    // at least 4 values of the bond per workgroup, or 2 where that leaves most of the chip without one (a train's bond of 96, us
-    // per call at 4 / at 2: 25600 -> 5120 37.5 / 34.9 at one token, 48.5 / 45.4 at 16 (96 workgroups at 4); 5120 -> 25600 at 4
-    // tokens (120) 41.6 / 44.6; 5120 -> 1024 at 32 tokens (192) 19.5 / 22.5); partial sums within their buffer
-    const int64_t least = base * std::max<int64_t>(1, d.P / 4) * 5 < 2 * h->num_cus ? 2 : 4;
-    want = std::min<int64_t>(want, std::max<int64_t>(1, d.P / least));
-    want = std::min<int64_t>(want, std::max<int64_t>(1, partial_cap / (tokens * h->plan.M * 4)));
-    g.rho_per_split = int((d.P + want - 1) / want);
-    g.n_splits = int((d.P + g.rho_per_split - 1) / g.rho_per_split);      // no empty split
-    g.partial_bytes = g.n_splits > 1 ? int64_t(g.n_splits) * tokens * h->plan.M * 4 : 0;
-    return g;
+    // As many splits as keep the grid within one round of workgroups (rounding up instead left a second round with a handful of
+    // workgroups: 300 tokens took as long as 512), at least 4 values of the bond each, partial sums within their buffer. Where
+    // the chunks of o1 are several and a CU holds one workgroup, also two rounds; and 2 values each where 4 leave CUs without a
+    // workgroup: whichever is priced lowest, the partial sums counted twice (at 24 tokens the rank-64 train 8192 ->
+    // 5120 gains less from 2 values each than they cost: 33.8 / 34.5 us). Two rounds pay the start and the partial sums twice, but
+    // divide the bond more evenly. us per call of rings 5120 -> 25600 in two rounds / one: rank 32 84 / 65 at one token, 133 / 100 at 8, 334 / 343 at 56;
+    // rank 64 284 / 248 at 8, 536 / 500 at 24, 1138 / 1247 at 56. Trains of rank 96 and 64 at 4 values / at 2: 25600 -> 5120 37.5 / 34.9 at one
+    // token, 48.5 / 45.4 at 16; 5120 -> 25600 at 4 tokens 35.0 / 36.9 (rank 64), 41.6 / 44.6.
+    const int64_t cap = std::max<int64_t>(1, partial_cap / (tokens * h->plan.M * 4));
+    auto with = [&](int64_t want) {
+        KronGeom c = g;
+        want = std::min(want, cap);
+        c.rho_per_split = int((d.P + want - 1) / want);
+        c.n_splits = int((d.P + c.rho_per_split - 1) / c.rho_per_split);      // no empty split
+        c.partial_bytes = c.n_splits > 1 ? int64_t(c.n_splits) * tokens * h->plan.M * 4 : 0;
+        return c;
+    };
+    if (base >= h->num_cus) return with(1);
+    const bool one_per_cu = kron_per_cu(d) == 1;
+    KronGeom best;
+    float best_us = 0.f;
+    bool any = false;
+    for (int rounds = one_per_cu ? 1 : 2; rounds <= (one_per_cu && g.n_chunks == 1 ? 1 : 2); ++rounds)
+        for (int least = 4; least >= 2; least -= 2) {
+            const int64_t fit = std::max<int64_t>(1, rounds * int64_t(h->num_cus) / base), most = std::max<int64_t>(1, d.P / least);
+            if (least == 2 && (fit <= std::max<int64_t>(1, d.P / 4) || base * std::max<int64_t>(1, d.P / 4) >= h->num_cus)) continue;
+            const KronGeom c = with(std::min(fit, most));
+            const float us = kron_us(h, d, c) + float(c.partial_bytes) / kGemmPartialBytesPerUs;
+            if (!any || us < best_us) {
+                best = c;
+                best_us = us;
+                any = true;
+            }
+        }
+    return best;
 }
 
 int prepare_kron(tn_linear_s* h, hipStream_t st) {
@@ -1737,23 +1770,10 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     y.Kp = int(h->plan.N);
     y.Cp = round_up(int(h->plan.M), tn::kMatrixColPad);
     if (h->plan.N % 64 || h->plan.format == TN_FORMAT_DENSE || h->plan.format == TN_FORMAT_TUCKER || !gemm_fits(y)) return TN_OK;
-    // the Kronecker-sum kernel: 22 ns per MFMA of a wave, values of the bond one after another, in rounds of one or two workgroups
-    // per CU (train 5120 -> 25600 of rank 96: 387 tokens are 245 workgroups and 200 us, 512 are 320 and 395)
-    auto kron_us = [&](const tn::KronDims& d, int64_t t) {
-        const int* c = tn::kKronConfig[d.cfg];
-        const KronGeom g = kron_geometry(h, d, t, kMaxPartialBytes);
-        const int64_t stage = 4096 * int64_t((c[3] * c[1] + c[2] * 2 * c[0] + 3) / 4);
-        const int64_t slots = int64_t(h->num_cus) * (3 * stage > 80 * 1024 ? 1 : 2);
-        const int64_t wgs = g.quads * g.n_chunks * g.n_splits;
-        const int64_t rounds = (wgs + slots - 1) / slots, turns = (wgs + h->num_cus - 1) / h->num_cus;     // two on a CU share its matrix cores
-        const float per_rho = float(c[3] * c[0] * (c[1] + 2 * c[2]) * g.tpw) * 0.022f;
-        return 10.f + float(rounds) * 10.f + float(turns) * float(g.rho_per_split) * per_rho +
-               float(g.partial_bytes) / kGemmPartialBytesPerUs;
-    };
     auto other_us = [&](int64_t t) {
         if (h->pair) return std::max(12.f, float(t) * float(h->plan.flops) / 1.3e9f);
-        if (h->kron) return kron_us(h->kron_dims, t);
-        if (h->lazy) return kron_us(h->lazy_dims, t) + (desc->workspace ? float(h->lazy_slice_bytes) / 1.6e6f : 0.f);
+        if (h->kron) return kron_us(h, h->kron_dims, kron_geometry(h, h->kron_dims, t, kMaxPartialBytes));
+        if (h->lazy) return kron_us(h, h->lazy_dims, kron_geometry(h, h->lazy_dims, t, kMaxPartialBytes)) + (desc->workspace ? float(h->lazy_slice_bytes) / 1.6e6f : 0.f);
         return 6.f * float(h->steps.size()) + float(t) * float(h->plan.flops) / 0.45e9f;
     };
     auto first_tokens = [&](float build_us) {
