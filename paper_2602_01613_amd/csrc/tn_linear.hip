@@ -471,10 +471,11 @@ constexpr GemmTile kGemmTile[kGemmTiles] = {
     {2, 2, 0.45f, 1.0f, 0.50f, 1.6f}};
 
 // The clock rises when part of the chip idles: products take this share of their time with a share u of the slots for
-// workgroups taken (1024 x 5120 x 8192, us per K tile against the table: 0.76 at u = 0.31, 0.83 at 0.47, 0.95 at 0.86). Tiles of
+// workgroups taken (1024 x 5120 x 8192, us per K tile against the table: 0.76 at u = 0.31, 0.83 at 0.47, 0.95 at 0.86; but 160 x
+// 256 tiles of 800 x 8192 x 5120 1.06 at 0.63, and 0.8 picks better than 0.6 over all). Tiles of
 // up to 128 x 128 are not bound by their products but wait for their loads, 0.5 us per K tile whatever the clock (460 x 1024 x
 // 2304 on operands that the caches of the workgroups' XCDs do not hold: 64 x 64 in one range 18.5 us, in four 12.5).
-inline float gemm_clock(const GemmTile& g, float u) { return g.tm * g.tn <= 16 ? 1.f : std::min(1.f, 0.6f + 0.4f * u); }
+inline float gemm_clock(const GemmTile& g, float u) { return g.tm * g.tn <= 16 ? 1.f : std::min(1.f, 0.8f + 0.2f * u); }
 
 struct GemmChoice {
     int tile = -1, n_split = 1, ktiles_per_split = 1;
@@ -485,8 +486,8 @@ struct GemmChoice {
 constexpr int64_t kGemmMinRows = 65;        // up to 64 rows the launch is a stream of the packed tensor: the kernels of stream.hpp
 constexpr float kGemmPartialBytesPerUs = 3.5e6f;    // partial sums, written and read back, and the launch that adds them:
 constexpr float kGemmReduceUs = 3.f;
-// (with these two the choice is 1.7 % above the best tile and number of ranges on average and 12 % at most over 117 products of
-// 66 to 2048 rows, operands as above; with the clock's share for all tiles and 4 us, 6.6 % and 48 %)
+// (with these the choice is 2.0 % above the best tile and number of ranges on average and 16 % at most over 165 products of 66 to
+// 4000 rows, operands as above; with 0.6 + 0.4 u for all tiles and 4 us, 6 % and 48 %)
 
 // The tile size and the number of K ranges with the least time for `rows` rows; partial sums within `cap` bytes.
 GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int64_t cap) {
