@@ -153,12 +153,16 @@ extern "C" {
 #define TN_QUERY_QUANT_BYTES       16   /* handle only: bytes of the 4-bit codes and block exponents of all tensors (0: not quantised) */
 #define TN_QUERY_QUANT_STREAM_BYTES 17  /* handle only: bytes of the 4-bit streams that decode-size calls read instead of the
                                            bf16 tensors (0: no step of the layer qualifies, or not quantised) */
-#define TN_QUERY_MATRIX_MIN_TOKENS 18   /* handle only: 0, or the token count from which tn_linear_forward contracts the tensors
+#define TN_QUERY_MATRIX_MIN_TOKENS 18   /* handle only: 0, or the least token count for which tn_linear_forward contracts the tensors
                                            of a train or ring with each other first (W, in the workspace, by every such call)
                                            and the activations last: 2 M N (tokens + bond) operations in all, however many the
-                                           chain through the activations takes. Not taken where the workspace has no room for
-                                           W, nor with TN_FLAG_NO_MERGE or TN_FLAG_NO_LAZY_MERGE. */
+                                           chain through the activations takes. Larger calls do so where it is the cheaper
+                                           order (TN_QUERY_MATRIX_TOKENS_BASE). Not taken where the workspace has no room for
+                                           W, nor with TN_FLAG_NO_MERGE, TN_FLAG_NO_LAZY_MERGE, TN_FLAG_NO_PAIR_CHAIN,
+                                           TN_FLAG_SCALAR_KERNELS or a forced variant. */
 #define TN_QUERY_MATRIX_BUILD_FLOPS 19  /* handle only: FLOPs such a call spends on W (0 if none) */
+#define TN_QUERY_MATRIX_TOKENS_BASE (1 << 30) /* handle only: TN_QUERY_MATRIX_TOKENS_BASE + t: 1 if a call of t tokens takes the
+                                           order of TN_QUERY_MATRIX_MIN_TOKENS, else 0 */
 #define TN_QUERY_STEP_BASE        100   /* 100 + 10*s + f: field f of step s:
                                            f=0 rows per token, 1 K, 2 columns, 3 FLOPs per token,
                                            4 id of the absorbed tensor (index into desc.tensors; ids >=

@@ -148,10 +148,10 @@ struct tn_linear_s {
     KronGenMfmaArgs lazy_gen_mfma[2];
     size_t lazy_gen_smem[2] = {0, 0};
     void* lazy_gen_tables[2] = {nullptr, nullptr};
-    // calls of at least mat_min_tokens tokens: the tensors contracted with each other into W, in the workspace and per call,
-    // and then Y = X W^T (tn_matrix.hpp)
+    // calls whose token count lies in one of mat_ranges: the tensors contracted with each other into W, in the workspace and per
+    // call, and then Y = X W^T (tn_matrix.hpp)
     bool matrix = false;
-    int64_t mat_min_tokens = 0;
+    std::vector<std::pair<int64_t, int64_t>> mat_ranges;      // [first, end), ascending
     int64_t mat_flops = 0;                    // of building W
     int64_t mat_bytes = 0;                    // W and the halves that are built per call
     int64_t mat_half_off[2] = {0, 0};         // byte offsets of the halves; W comes first
@@ -489,12 +489,18 @@ constexpr float kGemmReduceUs = 3.f;
 // (with these the choice is 2.0 % above the best tile and number of ranges on average and 16 % at most over 165 products of 66 to
 // 4000 rows, operands as above; with 0.6 + 0.4 u for all tiles and 4 us, 6 % and 48 %)
 
+// A column operand above this passes through the caches once per band of four row tiles: 33 us for 262 MB (4000 x 25600 x 5120: tiles
+// of 256 rows 808 us, of 192 887, of 160 934; their K tiles alone 817, 766, 764). One band and its remainder overlap (600 x 25600 x
+// 5120: five tiles of 128 rows 157 us, four of 160 181).
+constexpr float kGemmCachedBytes = 128e6f;
+
 // The tile size and the number of K ranges with the least time for `rows` rows; partial sums within `cap` bytes.
 GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int64_t cap) {
     GemmChoice best;
     const int nk = s.Kp / 64 * s.segments();
     const bool trans = s.cmode == 2;
     const uint32_t cus = uint32_t(h->num_cus);
+    const float b_bytes = 2.f * float(s.plan.C) * float(s.Kp);
     for (int t = 0; t < kGemmTiles; ++t) {
         const GemmTile& g = kGemmTile[t];
         if (uint32_t(s.Cp) % uint32_t(32 * g.tn) || (trans && (g.tm & 1))) continue;
@@ -518,6 +524,7 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
             const float used = float(items) / float((full + (rest > 0 ? 1 : 0)) * (half && full == 0 ? cus : slots));
             float us = rounds * per_round + (half ? g.o1 : 0.f) +
                        float(per) * (rounds * per_tile + (half ? g.t1 : 0.f)) * gemm_clock(g, used);
+            if (b_bytes > kGemmCachedBytes) us += std::max(1.25f, 0.25f * float((uint32_t(rows) + 32 * g.tm - 1) / uint32_t(32 * g.tm))) * b_bytes / 8e6f;
             if (ns > 1) us += kGemmReduceUs + 2.f * float(ns) * float(rows) * float(s.plan.C) * 4.f / kGemmPartialBytesPerUs;
             if (best.tile < 0 || us < best.us) {
                 best.us = us;
@@ -1107,16 +1114,19 @@ int kron_per_cu(const tn::KronDims& d) {
     return 3 * 4096 * ((c[3] * c[1] + c[2] * 2 * c[0] + 3) / 4) > 80 * 1024 ? 1 : 2;
 }
 
-// What a launch of the Kronecker-sum kernel is expected to take: 22 ns per MFMA of a wave, values of the bond one after another,
-// in rounds of one or two workgroups per CU, two on a CU sharing its matrix cores (train 5120 -> 25600 of rank 96: 387 tokens are
-// 245 workgroups and 200 us, 512 are 320 and 395), and the partial sums.
+// What a launch of the Kronecker-sum kernel is expected to take: per value of the bond 21 ns per MFMA of a wave and 0.25 us (half of
+// that where two workgroups on a CU share its matrix cores), values one after another, in rounds of workgroups; per round the start, longer
+// with the fragments and stores of two tokens per wave; and the partial sums. Expected / measured, us: trains 5120 -> 25600 of rank
+// 96 at 600 tokens 384 / 395, of rank 64 at 4000 1396 / 1499; 8192 -> 5120 of rank 32 at 600 99 / 108, of rank 96 at 4000 722 /
+// 764; 25600 -> 5120 of rank 96 at 4000 1434 / 1492; 5120 -> 8192 of rank 96 at 600 189 / 191.
 float kron_us(const tn_linear_s* h, const tn::KronDims& d, const KronGeom& g) {
     const int* c = tn::kKronConfig[d.cfg];
-    const int64_t slots = int64_t(h->num_cus) * kron_per_cu(d);
+    const int per_cu = kron_per_cu(d);
+    const int64_t slots = int64_t(h->num_cus) * per_cu;
     const int64_t wgs = g.quads * g.n_chunks * g.n_splits;
     const int64_t rounds = (wgs + slots - 1) / slots, turns = (wgs + h->num_cus - 1) / h->num_cus;
-    const float per_rho = float(c[3] * c[0] * (c[1] + 2 * c[2]) * g.tpw) * 0.022f;
-    return 10.f + float(rounds) * 10.f + float(turns) * float(g.rho_per_split) * per_rho +
+    const float per_rho = float(c[3] * c[0] * (c[1] + 2 * c[2]) * g.tpw) * 0.021f + 0.25f / float(per_cu);
+    return 10.f + float(rounds) * (g.tpw == 2 && per_cu == 1 ? 42.f : 10.f) + float(turns) * float(g.rho_per_split) * per_rho +
            float(g.partial_bytes) / kGemmPartialBytesPerUs;
 }
 
@@ -1745,7 +1755,17 @@ int prepare_lazy(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
 
 // What one launch of a product takes, in us: its tiles, or the stores of its output.
 float product_us(const tn_linear_s* h, const DevStep& s) {
-    return 3.f + std::max(gemm_choice(h, s, s.plan.R, 0).us, float(s.plan.R) * float(s.plan.C) * (s.out_lo ? 4.f : 2.f) / 3.5e6f);
+    return 5.f + std::max(gemm_choice(h, s, s.plan.R, 0).us, float(s.plan.R) * float(s.plan.C) * (s.out_lo ? 4.f : 2.f) / 3.5e6f);
+}
+
+constexpr int64_t kMatrixNoEnd = std::numeric_limits<int64_t>::max();
+
+// Does a call of so many tokens contract the tensors with each other first?
+bool takes_matrix(const tn_linear_s* h, int64_t tokens) {
+    if (!h->matrix) return false;
+    for (const auto& r : h->mat_ranges)
+        if (tokens >= r.first && tokens < r.second) return true;
+    return false;
 }
 
 // Decide whether calls of many tokens contract the tensors with each other first, from how many tokens on, and prepare it.
@@ -1777,12 +1797,22 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
         if (h->lazy) return kron_us(h, h->lazy_dims, kron_geometry(h, h->lazy_dims, t, kMaxPartialBytes)) + (desc->workspace ? float(h->lazy_slice_bytes) / 1.6e6f : 0.f);
         return 6.f * float(h->steps.size()) + float(t) * float(h->plan.flops) / 0.45e9f;
     };
-    auto first_tokens = [&](float build_us) {
-        for (int64_t t = 8; t <= desc->max_tokens; t += t < 64 ? 8 : t / 8)
-            if (1.15f * (build_us + gemm_choice(h, y, t, kMaxPartialBytes).us) < other_us(t)) return t;      // only where it is clear
-        return int64_t(0);
+    // Token counts [first, end) for which this order is taken: from where it is clearly the cheaper one to where it no longer is.
+    // There may be several such ranges: the price of the Kronecker-sum kernel is a staircase, in steps of a round of workgroups.
+    auto ranges = [&](float build_us) {
+        std::vector<std::pair<int64_t, int64_t>> r;
+        bool in = false;
+        int64_t last = 0;
+        for (int64_t t = 8; t <= desc->max_tokens; last = t, t += t < 64 ? 8 : t / 16) {
+            const float us = build_us + gemm_choice(h, y, t, kMaxPartialBytes).us, other = other_us(t);
+            if (!in && 1.04f * us < other) r.push_back({t, kMatrixNoEnd});
+            else if (in && us >= other) r.back().second = last + 1;
+            else continue;
+            in = !in;
+        }
+        return r;
     };
-    if (!first_tokens(6.f + float(h->plan.M) * float(h->plan.N) * 2.f / 3.5e6f)) return TN_OK;
+    if (ranges(6.f + float(h->plan.M) * float(h->plan.N) * 2.f / 3.5e6f).empty()) return TN_OK;
     if (!matrix_plan_of(h, desc)) return TN_OK;
     const tn::MatrixPlan& m = h->matrix_plans.m;
     h->mat_bytes = m.w_elems * 2;
@@ -1800,8 +1830,8 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     h->mat_flops = 2 * m.w.R * m.w.C * m.w.K;
     for (int i = 0; i < 2; ++i)
         if (h->mat_build[i]) h->mat_flops += 2 * m.half[i].build.R * m.half[i].build.C * m.half[i].build.K;
-    const int64_t from = first_tokens(us);
-    if (!from) return TN_OK;
+    const std::vector<std::pair<int64_t, int64_t>> taken = ranges(us);
+    if (taken.empty()) return TN_OK;
     // room in the workspace: beside what else is kept there, or sharing a caller's block with it
     const int64_t room = desc->workspace
                              ? desc->workspace_bytes - (desc->flags & TN_FLAG_NO_SPLIT_K ? 0 : std::min<int64_t>(kMaxPartialBytes, desc->workspace_bytes / 4)) - 512
@@ -1852,7 +1882,7 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     set_tables(&h->mat_w.s, 4);
     set_tables(&y, 6);
     h->matrix = true;
-    h->mat_min_tokens = from;
+    h->mat_ranges = taken;
     return TN_OK;
 }
 
@@ -3103,7 +3133,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
         int64_t need = 0;
         if (!split_ok) return need;
         if (h->matrix)
-            for (int64_t t = h->mat_min_tokens; t <= std::min<int64_t>(h->max_tokens, 4096); t += std::max<int64_t>(1, t / 8))
+            for (int64_t t = h->mat_ranges.front().first; t <= std::min<int64_t>(h->max_tokens, 4096); t += std::max<int64_t>(1, t / 8))
                 need = std::max(need, gemm_choice(h, h->mat_y, t, kMaxPartialBytes).partial_bytes);
         if (h->kron) {
             for (int64_t t = 1; t <= std::min<int64_t>(h->max_tokens, 4 * int64_t(h->num_cus)); ++t)
@@ -3166,7 +3196,11 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
     // (one token's buffers stay: calls that may not use the rebuilt plan - profiled steps, the entry point that
     // allocates nothing - run the compact steps token by token)
     if (h->lazy) ws_tokens = std::min<int64_t>(ws_tokens, std::max<int64_t>(1, h->lazy_min_tokens - 1));
-    if (h->matrix) ws_tokens = std::min<int64_t>(ws_tokens, std::max<int64_t>(1, h->mat_min_tokens - 1));
+    if (h->matrix) {
+        // between the ranges a call runs in one launch (the pair or the Kronecker-sum kernel); a layer without one has no such gaps
+        if (!h->pair && !h->kron && !h->lazy) h->mat_ranges = {{h->mat_ranges.back().first, kMatrixNoEnd}};
+        ws_tokens = std::min<int64_t>(ws_tokens, std::max<int64_t>(1, h->mat_ranges.front().first - 1));
+    }
     int64_t chunk = ws_tokens;
     if (desc->workspace) {
         // caller-owned block: [partial sums | buffer 0 | buffer 1], 256-byte aligned pieces
@@ -3312,7 +3346,7 @@ int forward_in(tn_linear_s* h, const Workspace& w, bool allow_lazy, const void* 
         }
         return TN_OK;
     }
-    if (allow_lazy && h->matrix && tokens >= h->mat_min_tokens) {
+    if (allow_lazy && takes_matrix(h, tokens)) {
         int rc = launch_matrix_build(h, w.partial, w.partial_bytes, st);          // not part of the profiled launch
         const int64_t pass = int64_t(1) << 20;
         for (int64_t t0 = 0; t0 < tokens && rc == TN_OK; t0 += pass) {
@@ -3410,7 +3444,7 @@ int tn_linear_forward2(tn_linear_t ha, tn_linear_t hb, const void* x, void* ya, 
     auto per_step_path = [&](const tn_linear_s* h) {
         return !h->profiling && !(h->small_chain && (h->elt == 4 || tokens <= kSmallChainMaxBf16Tokens)) &&
                !(h->pair && tokens >= h->pair_min_tokens) && !(h->kron && tokens >= h->kron_min_tokens) &&
-               !(h->lazy && tokens >= h->lazy_min_tokens) && !(h->matrix && tokens >= h->mat_min_tokens) && tokens <= h->chunk_tokens;
+               !(h->lazy && tokens >= h->lazy_min_tokens) && !takes_matrix(h, tokens) && tokens <= h->chunk_tokens;
     };
     bool together = ha != hb && per_step_path(ha) && per_step_path(hb) && ha->schedule.size() == hb->schedule.size();
     for (size_t li = 0; together && li < ha->schedule.size(); ++li) {
@@ -3631,13 +3665,17 @@ int tn_linear_query(tn_linear_t h, int32_t what, int64_t* value) {
         case TN_QUERY_CHUNK_TOKENS: *value = h->chunk_tokens; return TN_OK;
         case TN_QUERY_LAZY_MIN_TOKENS: *value = h->lazy ? h->lazy_min_tokens : 0; return TN_OK;
         case TN_QUERY_LAZY_FLOPS_PER_TOKEN: *value = h->lazy ? h->lazy_plan.flops : 0; return TN_OK;
-        case TN_QUERY_MATRIX_MIN_TOKENS: *value = h->matrix ? h->mat_min_tokens : 0; return TN_OK;
+        case TN_QUERY_MATRIX_MIN_TOKENS: *value = h->matrix ? h->mat_ranges.front().first : 0; return TN_OK;
         case TN_QUERY_MATRIX_BUILD_FLOPS: *value = h->matrix ? h->mat_flops : 0; return TN_OK;
         case TN_QUERY_QUANT_BYTES: *value = h->quant_bytes; return TN_OK;
         case TN_QUERY_QUANT_STREAM_BYTES: *value = h->q4_stream_bytes; return TN_OK;
         case TN_QUERY_BACKWARD_CHUNK_TOKENS: *value = h->trainable ? (h->mgrad ? h->mgrad_chunk : h->bwd_chunk) : 0; return TN_OK;
         case TN_QUERY_BACKWARD_WORKSPACE_BYTES: *value = h->trainable ? h->bwd_ws_bytes + h->bwd_partial_bytes : 0; return TN_OK;
         default: break;
+    }
+    if (what >= TN_QUERY_MATRIX_TOKENS_BASE) {
+        *value = takes_matrix(h, int64_t(what) - TN_QUERY_MATRIX_TOKENS_BASE) ? 1 : 0;
+        return TN_OK;
     }
     if (what >= TN_QUERY_STEP_BASE && (what - TN_QUERY_STEP_BASE) % 10 == 5) {
         int s = (what - TN_QUERY_STEP_BASE) / 10;

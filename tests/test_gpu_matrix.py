@@ -48,6 +48,28 @@ def test_factors_first(case):
     layer.close()
 
 
+def test_ranges_of_token_counts():
+    """Where the other order's price is a staircase (train 25600 -> 5120, rank 64), the order of a call follows its token count:
+    both sides of every change agree with the layer that never takes this order (two bf16 results, each within the
+    tolerance of test_factors_first of the same numbers)."""
+    spec = wl.stack_spec(wl.FORMAT_TT, 25600, 5120, 64)
+    ts = wl.make_tensors(spec, 510)
+    layer = make_layer(spec, ts, 4000)
+    plain = make_layer(spec, ts, 4000, flags=tn.TN_FLAG_NO_LAZY_MERGE)
+    taken = [layer.query(tn.TN_QUERY_MATRIX_TOKENS_BASE + t) for t in range(4001)]
+    first = layer.query(tn.TN_QUERY_MATRIX_MIN_TOKENS)
+    assert not any(taken[:first or 4001]) and (not first or taken[first])
+    assert not any(plain.query(tn.TN_QUERY_MATRIX_TOKENS_BASE + t) for t in (1, 64, 4000))
+    changes = [t for t in range(1, 4001) if taken[t] != taken[t - 1]]
+    x = wl.make_x(spec, max(changes + [64]), 510)
+    xd = to_dev(x, "bf16")
+    for t in sorted({1, 64} | set(changes) | {c - 1 for c in changes}):
+        a, b = to_host(layer(xd[:t].contiguous())), to_host(plain(xd[:t].contiguous()))
+        assert O.rel_max_err(a, b) <= TOL["bf16"], t
+    layer.close()
+    plain.close()
+
+
 def test_shared_block_and_graph():
     """W and the halves in a caller's block that another layer uses between the calls; the same calls as a HIP graph, replayed."""
     specs = [wl.TNSpec(wl.FORMAT_TR, "bf16", (8, 10, 8, 8), (8, 10, 8, 8), (16,) * 5),
