@@ -116,7 +116,7 @@ extern "C" {
                                        gives a workgroup 256 columns: such launches use the split-K kernel of one column block */
 #define TN_FLAG_VARIANT_SHIFT   8   /* bits 8..15: kernel variant id for the wide bf16 steps (0 = library's choice):
                                        3 = 128x256 and 8 = 256x128 register-prefetch tiles, 9 = short-K store kernel,
-                                       12 = matrix-product kernel (K a multiple of 64); 20 = the Kronecker-sum kernel for every two-step
+                                       12 = matrix-product kernel (K a multiple of 32); 20 = the Kronecker-sum kernel for every two-step
                                        plan whose layout allows it, whatever its size (see TN_QUERY_KRON_CHAINABLE);
                                        ignored where the variant cannot run the step */
 #define TN_FLAG_SHORTK_SHIFT   16   /* bits 16..19: form of the short-K kernel (0 = library's choice) */

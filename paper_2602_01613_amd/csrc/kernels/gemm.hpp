@@ -4,8 +4,9 @@
 #pragma once
 
 // ---------------------------------------------------------------------------------------------
-// Out[r][c] = sum_k A[r][k] * B[c][k], A row-major with K % 64 == 0, B packed fragment-major, output through the
-// step's scatter tables in aligned pieces of 8 columns (TRANS = 0) or of 8 rows (TRANS = 1).
+// Out[r][c] = sum_k A[r][k] * B[c][k], A row-major with K % 8 == 0, B packed fragment-major with zeros from K to whole tiles of
+// 64, output through the step's scatter tables in aligned pieces of 8 columns (TRANS = 0) or of 8 rows (TRANS = 1), or
+// (TRANS = 1, scalar_out) one value at a time where it comes in neither: 16 neighbouring columns per store.
 //
 // What bounds it: on large shapes the power the chip may draw. With every wait hidden the clock settles at what the
 // energy of a K tile allows, so what counts is energy per product (measured at 8192 x 8192 x 5120):
@@ -36,6 +37,7 @@ struct GemmArgs {
     int32_t n_row, n_col;          // output tiles
     int32_t n_split;               // ranges of K
     int32_t ktiles_per_split;      // K tiles of 64 per range, at least one in every range
+    int32_t scalar_out;            // TRANS = 1: outputs in no aligned pieces
     float* partial;                // not null: fp32 sums [split][rows_pad][ld] instead of the output (TRANS = 0, C % 4 == 0)
     int64_t rows_pad, ld;
     // PARTS = 2, in elements, 0: there is none
@@ -97,7 +99,10 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
     const __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(pa), 0, a_size, 0x00020000);
     const __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(pb), 0, b_size, 0x00020000);
     // a load of A covers 8 rows x 128 bytes: lane l fills position l%8 of row l/8
-    const int va = (wave * 8 + (lane >> 3)) * row_bytes + (((lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7)) * 16);
+    const int chunk = (lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7);
+    int va = (wave * 8 + (lane >> 3)) * row_bytes + chunk * 16;
+    // in a last tile that K does not fill, chunks past it read as zeros too: what follows them is the next row
+    const int va_last = ((a.K & 63) && kt0 + nk == nk_seg * n_seg && chunk * 8 >= (a.K & 63)) ? int(0x80000000u) : va;
     const int vb = wave * 1024 + lane * 16;              // the four waves bring the four k-step blocks of a column block
     auto load1 = [&](int j, int kt, unsigned char* s) {
         if (PARTS == 2) {
@@ -131,8 +136,10 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_t*)(tab + S::TAB_ROWS * 4 + wave * 256), 4,
                                                      min(col0 + wave * 64 + lane, a.C - 1) * 4, 0, 0, 0);
     }
+    if (nk == 1) va = va_last;
 #pragma unroll
     for (int l = 0; l < L; ++l) load1(l, 0, dyn_smem);
+    if (nk == 2) va = va_last;
 #pragma unroll
     for (int l = 0; l < L; ++l) load1(l, min(1, nk - 1), dyn_smem + STAGE);
 
@@ -192,6 +199,7 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         // (the last two tiles load the last one again, into a stage nobody reads)
+        if (kt + 3 == nk) va = va_last;
         kstep(1, sn, 0, min(kt + 2, nk - 1), s, std::integral_constant<int, L>());
         // keep the accumulators in the accumulation registers across the back edge
 #pragma unroll
@@ -259,7 +267,27 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
         for (int e = 0; e < 4; ++e) r[e] = low_part(v[e]);
         return r;
     };
-    if (TRANS) {
+    if (TRANS && g.scalar_out) {
+        // lane: column l%16 of tile j, rows 4*(l/16) .. +3 of tile i
+        uint32_t co[TN];
+#pragma unroll
+        for (int j = 0; j < TN; ++j) co[j] = col_offset(wn * TN * 16 + j * 16 + (lane & 15));
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            uint32_t base[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) base[v] = row_offset(wm * TM * 16 + i * 16 + 4 * (lane >> 4) + v);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                asm volatile("" : "+a"(acc[i][j]));
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, bf16_t(acc[i][j][v])), ro,
+                                                          int(((base[v] | co[j]) & OUT) ? ~0u : base[v] + co[j]), 0, 0);
+            }
+        }
+    } else if (TRANS) {
         uint32_t base[TM / 2];
 #pragma unroll
         for (int i = 0; i < TM / 2; ++i) base[i] = row_offset(wm * TM * 16 + i * 32 + piece);

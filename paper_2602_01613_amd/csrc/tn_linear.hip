@@ -54,7 +54,7 @@ enum Variant : int {
     VAR_PIPE_128x256 = 3,     // register-prefetch tiles, 4 waves, 2 workgroups per CU, one LDS stage
     VAR_PIPE_256x128 = 8,     // same, 4 waves stacked along rows
     VAR_SHORTK = 9,           // K <= 64, store-bound: registers-only operands, barrier-free
-    VAR_GEMM = 12,            // plain A with K % 64 == 0, more than 64 rows: tiles chosen per launch (gemm_choice)
+    VAR_GEMM = 12,            // plain A with K % 32 == 0, more than 64 rows: tiles chosen per launch (gemm_choice)
     VAR_KRONSUM = 20,         // (as a forced id only, read by tn::kron_shape) the Kronecker-sum kernel wherever
                               // the plan's layout allows it
 };
@@ -285,10 +285,13 @@ void choose_variant(const tn_linear_s* h, DevStep* s, int flags) {
         // register-only kernel for short-K, wide steps
         const bool shortk_ok = p.K <= 64 && p.c_vec == 8;
         int v = round_up(int(p.C), 128) < round_up(int(p.C), 256) ? VAR_PIPE_256x128 : VAR_PIPE_128x256;
-        // the matrix-product kernel wherever A is a plain matrix of whole K tiles of 64 and the output comes in aligned
+        // the matrix-product kernel wherever A is a plain matrix, K a multiple of 32 and the output comes in aligned
         // pieces of 8: it has the tile sizes for any number of rows (777 rows x 5120 x 25600: 208 us, 506 us on 256x256
         // tiles of one size; 777 x 2304 x 5120: 28 us, 119 us on the split-K kernel that too few tiles led to)
-        const bool gemm_ok = p.a_plain && p.K % 64 == 0 && p.K < (int64_t(1) << 21) && (p.c_vec == 8 || p.r_vec == 8);
+        // Outputs in no such pieces (an odd number of columns) are stored one by one: from 256 columns on, where that does not pad
+        // them further, it is still the faster kernel.
+        const bool gemm_ok = p.a_plain && p.K % 32 == 0 && p.K >= 64 && p.K < (int64_t(1) << 21) &&
+                             (p.c_vec == 8 || p.r_vec == 8 || (p.C >= 256 && round_up(int(p.C), 128) == round_up(int(p.C), 256)));
         if (gemm_ok) v = VAR_GEMM;
         if (shortk_ok && p.C >= 256) v = VAR_SHORTK;
         if (forced == VAR_PIPE_128x256 || forced == VAR_PIPE_256x128 || (forced == VAR_SHORTK && shortk_ok) ||
@@ -498,7 +501,7 @@ constexpr float kGemmCachedBytes = 128e6f;
 GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int64_t cap) {
     GemmChoice best;
     const int nk = s.Kp / 64 * s.segments();
-    const bool trans = s.cmode == 2;
+    const bool trans = s.cmode != 1;
     const uint32_t cus = uint32_t(h->num_cus);
     const float b_bytes = 2.f * float(s.plan.C) * float(s.Kp);
     for (int t = 0; t < kGemmTiles; ++t) {
@@ -578,7 +581,7 @@ int configure_gemm() {
 
 // Output offsets inside one tile are 31-bit byte offsets from its first token.
 bool gemm_fits(const DevStep& s) {
-    return s.variant == VAR_GEMM && s.cmode != 0 && (256 / s.plan.R + 2) * s.plan.c_tok_stride * 2 < (int64_t(1) << 31);
+    return s.variant == VAR_GEMM && (256 / s.plan.R + 2) * s.plan.c_tok_stride * 2 < (int64_t(1) << 31);
 }
 
 // fp32 sums instead of the output: where they went.
@@ -591,7 +594,7 @@ struct GemmSums {
 // With `f32` the launch leaves its fp32 sums in `partial` (or at f32->sums, as one range with rows of f32->ld).
 int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64_t rows, void* partial, int64_t partial_bytes,
                 hipStream_t st, GemmSums* f32 = nullptr) {
-    const bool trans = s.cmode == 2;
+    const bool trans = s.cmode != 1;
     const bool one_range = (h->flags & TN_FLAG_NO_SPLIT_K) || !partial || (f32 && f32->sums);
     const GemmChoice c = gemm_choice(h, s, rows, one_range ? 0 : partial_bytes);
     if (c.tile < 0 || (trans && (s.a_lo || s.b_lo || s.out_lo))) return TN_ERR_UNSUPPORTED;
@@ -604,6 +607,7 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
     g.ktiles_per_split = c.ktiles_per_split;
     g.rows_pad = rows;
     g.ld = s.Cp;
+    g.scalar_out = s.cmode == 0;
     g.a_lo = s.a_lo;
     g.b_lo = s.b_lo;
     g.out_lo = s.out_lo;
@@ -626,12 +630,13 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
     return TN_OK;
 }
 
-// A launch for the matrix-product kernel: more than a row tile of rows, and not a short K whose output blocks fill at most one round
+// A launch for the matrix-product kernel (a step stored one by one only where the split-K kernel has no use for its ranges): more than a row tile of rows, and not a short K whose output blocks fill at most one round
 // of the split-K kernel in one range, which then has the shorter chain: 0.95 us and 0.115 per 16 k (core of the rank-64 Tucker
 // layer 5120 -> 1024 at 460 tokens, K = 1024: 8.3 us, 9.5 on 64 x 64 tiles; K = 2304 17.7, 12.5 in four ranges). A tile's first
 // loads come 1.2 us later than gemm_choice has it, which compares tiles with each other.
 bool gemm_rows(const tn_linear_s* h, const DevStep& s, int64_t rows) {
     if (rows < kGemmMinRows || !gemm_fits(s)) return false;
+    if (s.cmode == 0) return !split_config(s, rows).use;      // one range only: where there are tiles enough without K ranges
     const float split_us = 0.95f + 0.115f * float(s.Kp / 16);
     if (split_us > 10.f || s.q4_codes || (h->flags & TN_FLAG_NO_SPLIT_K)) return true;
     const SplitCfg c = split_config(s, rows);
@@ -3150,7 +3155,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
                 need = std::max(need, kron_geometry(h, h->lazy_dims, t, kMaxPartialBytes).partial_bytes);
         for (const auto& s : h->steps)
             for (int64_t t = 1; t <= chunk; ++t) {
-                if (t * s.plan.R >= kGemmMinRows && gemm_fits(s)) break;
+                if (t * s.plan.R >= kGemmMinRows && gemm_fits(s) && s.cmode != 0) break;
                 SplitCfg c = split_config(s, t * s.plan.R);
                 if (!c.use) break;          // larger passes only add tiles
                 need = std::max(need, c.partial_bytes);
@@ -3603,7 +3608,7 @@ int tn_linear_forward_scratch(tn_linear_t h, const void* x, void* y, int64_t tok
             for (const tn::LaunchIO& l : h->schedule)
                 if (l.steps == 1) {
                     const DevStep& s = h->steps[size_t(l.first)];
-                    if (tokens * s.plan.R >= kGemmMinRows && gemm_fits(s)) {
+                    if (tokens * s.plan.R >= kGemmMinRows && gemm_fits(s) && s.cmode != 0) {
                         part = std::max(part, gemm_choice(h, s, tokens * s.plan.R, kScratchBytes / 2).partial_bytes);
                         continue;
                     }

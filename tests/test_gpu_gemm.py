@@ -33,6 +33,28 @@ def test_dense_tile_edges(n_in, n_out):
     layer.close()
 
 
+@pytest.mark.parametrize("n_in,n_out", [(96, 264), (160, 510), (288, 1023), (1056, 1000), (5152, 520), (8192, 511), (2336, 4095)])
+def test_k_of_half_a_tile_and_outputs_one_by_one(n_in, n_out):
+    """K that ends in the middle of a tile of 64 (one tile, two, many, several ranges), with infinities in the rows that follow: what
+    lies behind a row must not reach it. Columns that allow no aligned pieces, from 256 on."""
+    spec = wl.TNSpec(wl.FORMAT_DENSE, "bf16", (n_out,), (n_in,), ())
+    rng = np.random.default_rng(n_in + n_out)
+    w = wl.round_to_dtype(rng.standard_normal((n_out, n_in)) / np.sqrt(n_in), "bf16")
+    x = wl.round_to_dtype(rng.standard_normal((1030, n_in)), "bf16")
+    ref = x @ w.T
+    layer = make_layer(spec, [w], 1030)
+    assert layer.query(tn.TN_QUERY_STEP_BASE + 5) == 12
+    xd = to_dev(x, "bf16")
+    for rows in (64, 65, 97, 128, 161, 257, 513, 1030):
+        y = to_host(layer(xd[:rows].contiguous()))
+        assert np.max(np.abs(y - ref[:rows])) <= 2.0 ** -8 * np.max(np.abs(ref[:rows])) + 1e-3, (rows, n_in, n_out)
+    odd = xd.clone()
+    odd[1::2] = float("inf")
+    y = to_host(layer(odd))[0::2]
+    assert np.max(np.abs(y - ref[0::2])) <= 2.0 ** -8 * np.max(np.abs(ref)) + 1e-3
+    layer.close()
+
+
 @pytest.mark.parametrize("n_out", [1024, 4104])
 def test_short_k_between_the_two_kernels(n_out):
     """K = 1024: row counts on both sides of where the split-K kernel in one range gives way to the tiles, and back."""
