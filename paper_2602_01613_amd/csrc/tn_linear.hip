@@ -159,6 +159,8 @@ struct tn_linear_s {
     bool mat_build[2] = {false, false};       // the half is made of two tensors: built per call
     DevProduct mat_half[2], mat_w;
     DevStep mat_y;
+    size_t mat_kept_count = 0;                // of mat_kept: those of the forward order, which come first
+    int64_t mat_kept_bytes = 0;
     std::vector<void*> mat_kept;              // operands made from the caller's tensors, and the tables
     std::vector<std::vector<int32_t>> create_tables;     // host copies of tables on their way to the GPU, until create's last wait
     // the plan of that order, made once and used by the two prepare functions; cleared when create ends
@@ -1891,6 +1893,19 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     return TN_OK;
 }
 
+// The plan and what it kept go away: every call runs the other orders.
+int drop_matrix(tn_linear_s* h, hipStream_t st) {
+    (void)hipGetLastError();                                        // of the allocation that was refused
+    if (hipStreamSynchronize(st) != hipSuccess) return TN_ERR_HIP;  // the kernels that write the operands may still be running
+    for (size_t i = 0; i < h->mat_kept_count; ++i) (void)hipFree(h->mat_kept[i]);
+    h->mat_kept.erase(h->mat_kept.begin(), h->mat_kept.begin() + std::ptrdiff_t(h->mat_kept_count));
+    h->packed_bytes -= h->mat_kept_bytes;
+    h->mat_kept_count = 0;
+    h->mat_kept_bytes = 0;
+    h->matrix = false;
+    return TN_OK;
+}
+
 // Where W and the halves are.
 void place_matrix(tn_linear_s* h, void* mem) {
     char* base = static_cast<char*>(mem);
@@ -3115,7 +3130,17 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
         rc = prepare_lazy(h, desc, st);
         h->lazy_kept_bytes = h->packed_bytes - before;
     }
-    if (rc == TN_OK) rc = prepare_matrix(h, desc, st);
+    if (rc == TN_OK) {
+        const int64_t before = h->packed_bytes;
+        rc = prepare_matrix(h, desc, st);
+        h->mat_kept_count = h->mat_kept.size();
+        h->mat_kept_bytes = h->packed_bytes - before;
+        if (rc == TN_OK && h->matrix && !desc->workspace && hipMalloc(&h->mat_mem, size_t(h->mat_bytes)) != hipSuccess) {
+            h->mat_mem = nullptr;
+            rc = TN_ERR_ALLOC;
+        }
+        if (rc == TN_ERR_ALLOC) rc = drop_matrix(h, st);      // an order less, not a layer less
+    }
     if (rc == TN_OK && (desc->flags & TN_FLAG_TRAINABLE)) {
         rc = prepare_matrix_grad(h, desc, st);
         if (rc == TN_OK) rc = prepare_backward(h, desc, st);
@@ -3235,12 +3260,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
     } else {
         int64_t limit = desc->workspace_limit_bytes > 0 ? desc->workspace_limit_bytes : kDefaultWorkspaceBytes;
         if (h->matrix) {
-            void* mem = nullptr;
-            if (hipMalloc(&mem, size_t(h->mat_bytes)) != hipSuccess) {
-                free_handle(h);
-                return TN_ERR_ALLOC;
-            }
-            place_matrix(h, mem);
+            place_matrix(h, h->mat_mem);
             h->workspace_bytes += h->mat_bytes;
             limit -= h->mat_bytes;
         }

@@ -1,0 +1,68 @@
+"""tn_linear_create on a HIP runtime of the host (fake_hip.cpp): what a layer falls back to when memory is short, and what it holds."""
+import json
+import os
+import subprocess
+import sys
+import tempfile
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+CHILD = """
+import ctypes, json, sys
+import paper_2602_01613_amd as tn
+import workloads as wl
+from paper_2602_01613_amd.binding import _make_desc
+fmt, out_modes, in_modes, ranks, max_tokens, limit, flags, whats = json.loads(sys.argv[1])
+spec = wl.TNSpec(fmt, "bf16", tuple(out_modes), tuple(in_modes), tuple(ranks))
+mem = ctypes.create_string_buffer(64)
+lib = tn.load_library()
+ptrs = [ctypes.addressof(mem)] * len(spec.tensor_shapes())
+d, keep = _make_desc(fmt, tn.TN_DTYPE_BF16, out_modes, in_modes, ranks, ptrs, max_tokens, limit, flags, None)
+h = ctypes.c_void_p()
+rc = lib.tn_linear_create(ctypes.byref(h), ctypes.byref(d))
+res = {"rc": rc}
+for w in whats:
+    v = ctypes.c_int64(-1)
+    if rc == 0:
+        assert lib.tn_linear_query(h, w, ctypes.byref(v)) == 0
+    res[str(w)] = v.value
+if rc == 0:
+    lib.tn_linear_destroy(h)
+print("RESULT " + json.dumps(res))
+"""
+
+
+@pytest.fixture(scope="module")
+def fake_hip():
+    out = os.path.join(tempfile.mkdtemp(prefix="tn_fake_hip_"), "libfake_hip.so")
+    subprocess.check_call(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I/opt/rocm/include", os.path.join(HERE, "fake_hip.cpp"), "-o", out])
+    return out
+
+
+def create(fake_hip, spec, max_tokens, whats, limit=0, flags=0, refuse=None):
+    env = dict(os.environ, LD_PRELOAD=fake_hip)
+    if refuse:
+        env["FAKE_HIP_REFUSE_FROM"], env["FAKE_HIP_REFUSE_TO"] = str(refuse[0]), str(refuse[1])
+    arg = json.dumps([spec.format, list(spec.out_modes), list(spec.in_modes), list(spec.ranks), max_tokens, limit, flags, whats])
+    r = subprocess.run([sys.executable, "-c", CHILD, arg], cwd=os.path.dirname(HERE), env=env, capture_output=True, text=True, timeout=300)
+    lines = [l for l in r.stdout.splitlines() if l.startswith("RESULT ")]
+    assert lines, r.stderr[-800:]
+    return json.loads(lines[0][7:])
+
+
+def test_no_memory_for_w_leaves_the_other_orders(fake_hip):
+    """W of a train 5120 -> 8192 is 84 MB: where that allocation, or that of its 148 KB of tables, is refused, the layer is
+    made as one that never takes this order."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    spec = wl.baseline_spec(1)[0]
+    what = [tn.TN_QUERY_MATRIX_MIN_TOKENS, tn.TN_QUERY_WORKSPACE_BYTES, tn.TN_QUERY_PACKED_BYTES]
+    full = create(fake_hip, spec, 8192, what)
+    assert full["rc"] == 0 and full[str(what[0])] > 0 and full[str(what[1])] >= 84 << 20 >> 1
+    never = create(fake_hip, spec, 8192, what, flags=tn.TN_FLAG_NO_LAZY_MERGE)
+    for refuse in ((80 << 20, 90 << 20), (140000, 150000)):
+        short = create(fake_hip, spec, 8192, what, refuse=refuse)
+        assert short["rc"] == 0 and short[str(what[0])] == 0, refuse
+        assert short[str(what[1])] == never[str(what[1])] and short[str(what[2])] == never[str(what[2])], refuse
