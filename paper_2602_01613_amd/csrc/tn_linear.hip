@@ -3623,25 +3623,27 @@ int tn_linear_forward_scratch(tn_linear_t h, const void* x, void* y, int64_t tok
         w.partial_bytes = kScratchBytes;
     } else {
         // the compact steps in one pass: [partial sums | buffer 0 | buffer 1], 256-byte aligned pieces
-        int64_t part = 0;
-        if (!(h->flags & TN_FLAG_NO_SPLIT_K) && h->elt == 2)
-            for (const tn::LaunchIO& l : h->schedule)
-                if (l.steps == 1) {
-                    const DevStep& s = h->steps[size_t(l.first)];
-                    if (tokens * s.plan.R >= kGemmMinRows && gemm_fits(s) && s.cmode != 0) {
-                        part = std::max(part, gemm_choice(h, s, tokens * s.plan.R, kScratchBytes / 2).partial_bytes);
-                        continue;
-                    }
-                    const SplitCfg c = split_config(s, tokens * s.plan.R);
-                    if (c.use) part = std::max(part, c.partial_bytes);
-                }
-        part = (part + 255) & ~int64_t(255);
         int64_t max_r = 1;
         for (const auto& s : h->steps) max_r = std::max(max_r, s.plan.R);
         if (tokens > ((int64_t(1) << 31) - 1024) / max_r) return TN_ERR_SCRATCH;      // rows of a pass are indexed with 32 bits
         const int64_t per_token = h->plan.max_intermediate * h->elt;
         if (per_token > 0 && tokens > kScratchBytes / per_token) return TN_ERR_SCRATCH;
         const int64_t buf = (tokens * per_token + 255) & ~int64_t(255);
+        // the split-K kernels' sums have to fit; the matrix-product kernel takes as many ranges of K as there is room for
+        const int64_t room = kScratchBytes - 2 * buf - 256;
+        int64_t part = 0;
+        if (!(h->flags & TN_FLAG_NO_SPLIT_K) && h->elt == 2)
+            for (const tn::LaunchIO& l : h->schedule)
+                if (l.steps == 1) {
+                    const DevStep& s = h->steps[size_t(l.first)];
+                    if (tokens * s.plan.R >= kGemmMinRows && gemm_fits(s) && s.cmode != 0) {
+                        part = std::max(part, gemm_choice(h, s, tokens * s.plan.R, std::max<int64_t>(0, std::min(kScratchBytes / 2, room))).partial_bytes);
+                        continue;
+                    }
+                    const SplitCfg c = split_config(s, tokens * s.plan.R);
+                    if (c.use) part = std::max(part, c.partial_bytes);
+                }
+        part = (part + 255) & ~int64_t(255);
         if (part + 2 * buf > kScratchBytes) return TN_ERR_SCRATCH;
         char* b = static_cast<char*>(base);
         w.partial = part > 0 ? b : nullptr;

@@ -14,7 +14,7 @@ import ctypes, json, sys
 import paper_2602_01613_amd as tn
 import workloads as wl
 from paper_2602_01613_amd.binding import _make_desc
-fmt, out_modes, in_modes, ranks, max_tokens, limit, flags, whats = json.loads(sys.argv[1])
+fmt, out_modes, in_modes, ranks, max_tokens, limit, flags, whats, scratch_tokens = json.loads(sys.argv[1])
 spec = wl.TNSpec(fmt, "bf16", tuple(out_modes), tuple(in_modes), tuple(ranks))
 mem = ctypes.create_string_buffer(64)
 lib = tn.load_library()
@@ -28,6 +28,10 @@ for w in whats:
     if rc == 0:
         assert lib.tn_linear_query(h, w, ctypes.byref(v)) == 0
     res[str(w)] = v.value
+lib.tn_linear_forward_scratch.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
+buf = ctypes.create_string_buffer(1024)
+at = (ctypes.addressof(buf) + 255) // 256 * 256
+res["scratch"] = [lib.tn_linear_forward_scratch(h, at, at + 256, t, None) for t in scratch_tokens] if rc == 0 else []
 if rc == 0:
     lib.tn_linear_destroy(h)
 print("RESULT " + json.dumps(res))
@@ -41,11 +45,11 @@ def fake_hip():
     return out
 
 
-def create(fake_hip, spec, max_tokens, whats, limit=0, flags=0, refuse=None):
+def create(fake_hip, spec, max_tokens, whats, limit=0, flags=0, refuse=None, scratch_tokens=()):
     env = dict(os.environ, LD_PRELOAD=fake_hip)
     if refuse:
         env["FAKE_HIP_REFUSE_FROM"], env["FAKE_HIP_REFUSE_TO"] = str(refuse[0]), str(refuse[1])
-    arg = json.dumps([spec.format, list(spec.out_modes), list(spec.in_modes), list(spec.ranks), max_tokens, limit, flags, whats])
+    arg = json.dumps([spec.format, list(spec.out_modes), list(spec.in_modes), list(spec.ranks), max_tokens, limit, flags, whats, list(scratch_tokens)])
     r = subprocess.run([sys.executable, "-c", CHILD, arg], cwd=os.path.dirname(HERE), env=env, capture_output=True, text=True, timeout=300)
     lines = [l for l in r.stdout.splitlines() if l.startswith("RESULT ")]
     assert lines, r.stderr[-800:]
@@ -66,3 +70,17 @@ def test_no_memory_for_w_leaves_the_other_orders(fake_hip):
         short = create(fake_hip, spec, 8192, what, refuse=refuse)
         assert short["rc"] == 0 and short[str(what[0])] == 0, refuse
         assert short[str(what[1])] == never[str(what[1])] and short[str(what[2])] == never[str(what[2])], refuse
+
+
+@pytest.mark.parametrize("fmt,om,im,rk,tokens", [(3, (48, 64), (48, 128), (8, 64, 48, 64), (1719, 2079, 2514)),
+                                                 (1, (32, 4, 8), (4, 32, 32), (1, 128, 128, 1), (42, 50, 60))])
+def test_scratch_takes_the_ranges_of_k_that_fit(fake_hip, fmt, om, im, rk, tokens):
+    """Calls whose intermediates leave less than half of the scratch array: sums of K ranges take what room there is and never
+    refuse the call."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    spec = wl.TNSpec(fmt, "bf16", om, im, rk)
+    inter = tn.plan_query(fmt, tn.TN_DTYPE_BF16, om, im, rk, tn.TN_QUERY_MAX_INTERMEDIATE, flags=tn.TN_FLAG_NO_MERGE)
+    most = (32 << 20) // (4 * inter)
+    got = create(fake_hip, spec, 2000, [], flags=tn.TN_FLAG_NO_MERGE, scratch_tokens=list(tokens) + [most + 1])
+    assert got["rc"] == 0 and got["scratch"] == [0] * len(tokens) + [-5]
