@@ -267,7 +267,7 @@ struct GradOutArgs {
     const float* partial;
     float* grad;
     int64_t ld, split_stride;               // partial: elements from c to c + 1, from split to split
-    uint32_t C, K;
+    uint32_t c0, C, K;                      // rows c0 .. c0 + C - 1
     int32_t n_split, accumulate;
     int32_t nk, nc;
     uint32_t kext[tn::kMaxGatherDims], cext[tn::kMaxGatherDims];
@@ -284,6 +284,7 @@ __global__ void __launch_bounds__(Y > 4 ? 64 * Y : 256) grad_reduce_kernel(GradO
     for (uint32_t e0 = (blockIdx.x * GROUPS + group) * 64u; e0 - uint32_t(group) * 64u < total; e0 += gridDim.x * GROUPS * 64u) {
         const uint32_t e = e0 + lane;
         uint32_t c = e / a.K, k = e - c * a.K;
+        c += a.c0;
         float sum = 0.f;
         if (e < total) {
             const float* p = a.partial + int64_t(c) * a.ld + k;

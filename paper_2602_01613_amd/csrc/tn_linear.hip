@@ -2515,13 +2515,16 @@ void fill_grad_dims(GradOutArgs* o, const std::vector<tn::GatherDim>& rows, cons
 }
 
 // Waves that share an element's splits: measured on 512 splits of 96 x 160 (and on 8 of 9216 x 2304, where one is best).
-int launch_grad_reduce(const GradOutArgs& o, hipStream_t st) {
-    const int64_t total = int64_t(o.C) * o.K;
-    if (total >= (int64_t(1) << 31)) return TN_ERR_UNSUPPORTED;
-    auto blocks = [&](int64_t per) { return dim3(uint32_t(std::min<int64_t>((total + per - 1) / per, 16384))); };
-    if (o.n_split >= 64) hipLaunchKernelGGL(grad_reduce_kernel<16>, blocks(64), dim3(1024), 0, st, o);
-    else if (o.n_split >= 16) hipLaunchKernelGGL(grad_reduce_kernel<4>, blocks(64), dim3(256), 0, st, o);
-    else hipLaunchKernelGGL(grad_reduce_kernel<1>, blocks(256), dim3(256), 0, st, o);
+int launch_grad_reduce(GradOutArgs o, hipStream_t st) {
+    const uint32_t rows = uint32_t((int64_t(1) << 31) / o.K - 1);      // a launch counts its elements in 31 bits
+    for (const uint32_t C = o.C; o.c0 < C; o.c0 += rows) {
+        o.C = std::min(rows, C - o.c0);
+        const int64_t total = int64_t(o.C) * o.K;
+        auto blocks = [&](int64_t per) { return dim3(uint32_t(std::min<int64_t>((total + per - 1) / per, 16384))); };
+        if (o.n_split >= 64) hipLaunchKernelGGL(grad_reduce_kernel<16>, blocks(64), dim3(1024), 0, st, o);
+        else if (o.n_split >= 16) hipLaunchKernelGGL(grad_reduce_kernel<4>, blocks(64), dim3(256), 0, st, o);
+        else hipLaunchKernelGGL(grad_reduce_kernel<1>, blocks(256), dim3(256), 0, st, o);
+    }
     return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
 

@@ -14,7 +14,7 @@ import ctypes, json, sys
 import paper_2602_01613_amd as tn
 import workloads as wl
 from paper_2602_01613_amd.binding import _make_desc
-fmt, out_modes, in_modes, ranks, max_tokens, limit, flags, whats, scratch_tokens = json.loads(sys.argv[1])
+fmt, out_modes, in_modes, ranks, max_tokens, limit, flags, whats, scratch_tokens, grad_tokens = json.loads(sys.argv[1])
 spec = wl.TNSpec(fmt, "bf16", tuple(out_modes), tuple(in_modes), tuple(ranks))
 mem = ctypes.create_string_buffer(64)
 lib = tn.load_library()
@@ -32,6 +32,9 @@ lib.tn_linear_forward_scratch.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctyp
 buf = ctypes.create_string_buffer(1024)
 at = (ctypes.addressof(buf) + 255) // 256 * 256
 res["scratch"] = [lib.tn_linear_forward_scratch(h, at, at + 256, t, None) for t in scratch_tokens] if rc == 0 else []
+lib.tn_linear_param_gradients.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
+grads = (ctypes.c_void_p * len(ptrs))(*[at + 512] * len(ptrs))
+res["gradients"] = [lib.tn_linear_param_gradients(h, at, at + 256, grads, t, None) for t in grad_tokens] if rc == 0 else []
 if rc == 0:
     lib.tn_linear_destroy(h)
 print("RESULT " + json.dumps(res))
@@ -45,11 +48,11 @@ def fake_hip():
     return out
 
 
-def create(fake_hip, spec, max_tokens, whats, limit=0, flags=0, refuse=None, scratch_tokens=()):
+def create(fake_hip, spec, max_tokens, whats, limit=0, flags=0, refuse=None, scratch_tokens=(), grad_tokens=()):
     env = dict(os.environ, LD_PRELOAD=fake_hip)
     if refuse:
         env["FAKE_HIP_REFUSE_FROM"], env["FAKE_HIP_REFUSE_TO"] = str(refuse[0]), str(refuse[1])
-    arg = json.dumps([spec.format, list(spec.out_modes), list(spec.in_modes), list(spec.ranks), max_tokens, limit, flags, whats, list(scratch_tokens)])
+    arg = json.dumps([spec.format, list(spec.out_modes), list(spec.in_modes), list(spec.ranks), max_tokens, limit, flags, whats, list(scratch_tokens), list(grad_tokens)])
     r = subprocess.run([sys.executable, "-c", CHILD, arg], cwd=os.path.dirname(HERE), env=env, capture_output=True, text=True, timeout=300)
     lines = [l for l in r.stdout.splitlines() if l.startswith("RESULT ")]
     assert lines, r.stderr[-800:]
@@ -84,3 +87,11 @@ def test_scratch_takes_the_ranges_of_k_that_fit(fake_hip, fmt, om, im, rk, token
     most = (32 << 20) // (4 * inter)
     got = create(fake_hip, spec, 2000, [], flags=tn.TN_FLAG_NO_MERGE, scratch_tokens=list(tokens) + [most + 1])
     assert got["rc"] == 0 and got["scratch"] == [0] * len(tokens) + [-5]
+
+
+def test_gradient_of_a_tensor_of_more_than_31_bits(fake_hip):
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    spec = wl.TNSpec(wl.FORMAT_DENSE, "bf16", (46344,), (46400,), ())
+    got = create(fake_hip, spec, 8, [], flags=tn.TN_FLAG_TRAINABLE, grad_tokens=[1, 8])
+    assert got["rc"] == 0 and got["gradients"] == [0, 0]
