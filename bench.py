@@ -71,20 +71,19 @@ def cpu_baseline(spec, tensors, sample_tokens, transpose=False, x_used=None, y_g
     return out
 
 
-def measured_traffic(workload, flags, tokens, fused):
+def measured_traffic(workload, flags, tokens, kernel):
     """HBM-side bytes per launch of the dominant kernel of workloads 1 to 3 and of the dense matrix (4) at their default settings, as
     measured in separate rocprofv3 counter runs (FETCH_SIZE, WRITE_SIZE, calibrated on a copy kernel) and
-    recorded in profiles/: counters cannot be read from inside this process. Returns (bytes, file) or (None, None)."""
-    if flags or tokens != 8192 or fused != (workload in (1, 3)):
+    recorded in profiles/ under the kernel's name: counters cannot be read from inside this process. Returns (bytes, file), or
+    (None, None) where that kernel was not measured."""
+    if flags or tokens != 8192:
         return None, None
-    name, key = {1: ("tt_q_proj_prefill8192_hbm_traffic.txt", "pair"),
-                 2: ("tucker_up_proj_prefill8192_hbm_traffic.txt", "core"),
-                 3: ("tr_down_proj_prefill8192_hbm_traffic.txt", "kronsum"),
-                 4: ("dense_q_proj_prefill8192_hbm_traffic.txt", "gemm")}.get(workload, (None, None))
+    name = {1: "tt_q_proj_prefill8192_hbm_traffic.txt", 2: "tucker_up_proj_prefill8192_hbm_traffic.txt",
+            3: "tr_down_proj_prefill8192_hbm_traffic.txt", 4: "dense_q_proj_prefill8192_hbm_traffic.txt"}.get(workload)
     if name is None:
         return None, None
     try:
-        m = re.search(rf"TRAFFIC_BYTES_PER_LAUNCH {key} = (\d+)", open(os.path.join(ROOT, "profiles", name)).read())
+        m = re.search(rf"TRAFFIC_BYTES_PER_LAUNCH {kernel} = (\d+)", open(os.path.join(ROOT, "profiles", name)).read())
         return (int(m.group(1)), "profiles/" + name) if m else (None, None)
     except OSError:
         return None, None
@@ -115,7 +114,7 @@ class LayerBench:
                                  tokens, workspace_mb << 20, flags=flags)
         self.y = torch.empty((tokens, self.layer.M), dtype=self.tdt, device="cuda")
         self.lazy_min = self.layer.query(tn.TN_QUERY_LAZY_MIN_TOKENS)
-        self.matrix_min = self.layer.query(tn.TN_QUERY_MATRIX_MIN_TOKENS)
+        self.takes_matrix = lambda t: self.layer.query(tn.TN_QUERY_MATRIX_TOKENS_BASE + t) == 1
 
     def close(self):
         self.layer.close()
@@ -125,7 +124,7 @@ class LayerBench:
         tokens (0: never) run on a plan whose merged tensors are rebuilt in the workspace per call: its steps, not
         the compact plan's, are the work such a call does."""
         tn, spec, layer, esize = self.tn, self.spec, self.layer, self.esize
-        if self.matrix_min and t >= self.matrix_min:
+        if self.takes_matrix(t):
             # the tensors are contracted with each other first (W, per call, launches of their own) and the call's
             # profiled launch is the product with the activations
             k, c = layer.N, layer.M
@@ -225,7 +224,9 @@ class LayerBench:
         else:
             roof = {"bound": "hbm", "achieved": d["algorithmic_GBps"], "peak": PEAK_HBM_GBS, "unit": "GB/s"}
         roof["frac"] = roof["achieved"] / roof["peak"]
-        roof["traffic"], src = measured_traffic(workload_id, self.flags, tokens, d["fused_with_next"])
+        kernel = ({2: "step_pair_kernel", 4: "step_kronsum_kernel"}.get(q(dom, 6)) if d["fused_with_next"]
+                  else {12: "step_gemm_kernel"}.get(q(dom, 5)))
+        roof["traffic"], src = measured_traffic(workload_id, self.flags, tokens, kernel)
         if src:
             roof["traffic_source"] = src + " (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this workload, per launch)"
         if d["fused_with_next"]:
@@ -474,9 +475,9 @@ def quant_record(spec, config_id, args):
 
 def gradient_record(spec, config_id, tokens, reps=3):
     """tn_linear_param_gradients (gradients of a loss with respect to every parameter tensor, Section 3.4) on a
-    trainable copy of the layer: tokens/s of one call (forward with saved intermediates + backward) and the FLOP/s of
-    its executed contractions (per step: the forward product, the parameter gradient and, except for the first step,
-    the input gradient)."""
+    trainable copy of the layer: tokens/s of one call and the FLOP/s of the contractions it executes. Either dW = dY^T X over
+    the tokens padded to 64 and the products that make the tensors' gradients of it, or (few tokens, Tucker layers) per
+    step the forward product, the parameter gradient and, except for the first step, the input gradient."""
     import torch
     import workloads as wl
     import paper_2602_01613_amd as tn
@@ -496,19 +497,26 @@ def gradient_record(spec, config_id, tokens, reps=3):
     torch.cuda.synchronize()
     sec = (time.perf_counter() - t0) / reps
     n = layer.query(tn.TN_QUERY_NUM_STEPS)
-    step_flops = [layer.query(tn.TN_QUERY_STEP_BASE + 10 * s + 3) for s in range(n)]
-    flops = sum(step_flops[:-1]) + sum(step_flops) + sum(step_flops[1:])
-    out = {"workload": f"{spec.name}: parameter gradients, {tokens} tokens, {n} steps (no create-time merges)",
+    through_dw = 0 < layer.query(tn.TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS) <= tokens
+    if through_dw:
+        passes = -(-tokens // layer.query(tn.TN_QUERY_BACKWARD_CHUNK_TOKENS))
+        flops = (2 * spec.M * spec.N * (-(-tokens // 64) * 64) + passes * layer.query(tn.TN_QUERY_GRADIENT_MATRIX_FLOPS)) / tokens
+        kernel = ("whole call: dW = dY^T X and the products from it to the tensors' gradients on step_gemm_kernel (high and low parts), "
+                  "transposed copies between them")
+    else:
+        step_flops = [layer.query(tn.TN_QUERY_STEP_BASE + 10 * s + 3) for s in range(n)]
+        flops = sum(step_flops[:-1]) + sum(step_flops) + sum(step_flops[1:])
+        kernel = ("whole call: forward and input-gradient steps on the step kernels, parameter gradients on grad_param_mfma_kernel, on "
+                  "step_gemm_kernel (a core as one product over the tokens) or on plain fp32 FMA (tensors under 8 wide)")
+    assert flops * tokens / sec / 1e12 <= PEAK_BF16_TFLOPS, "more FLOP/s than the card has: the count is wrong"
+    out = {"workload": f"{spec.name}: parameter gradients, {tokens} tokens, " + ("through dW" if through_dw else f"{n} steps"),
            "tokens": tokens, "ms_per_call": 1e3 * sec, "tokens_per_s": tokens / sec,
            "flops_per_token": flops, "tflops": flops * tokens / sec / 1e12,
            "backward_chunk_tokens": layer.query(tn.TN_QUERY_BACKWARD_CHUNK_TOKENS),
            "backward_workspace_MB": layer.query(tn.TN_QUERY_BACKWARD_WORKSPACE_BYTES) / 1e6,
            "roofline": {"bound": "mfma", "achieved": flops * tokens / sec / 1e12, "peak": 2500.0, "unit": "TFLOP/s",
                         "frac": flops * tokens / sec / 1e12 / 2500.0,
-                        "kernel": "whole call: forward and input-gradient steps on the MFMA step kernels, parameter-gradient "
-                                  "contractions on grad_param_mfma_kernel (128 x 128 tiles; both operands transposed through LDS, "
-                                  "loaded in 16-byte pieces where their layout allows) or, for tensors under 8 wide or not bf16, on "
-                                  "plain fp32 FMA"}}
+                        "kernel": kernel}}
     layer.close()
     return out
 
@@ -564,8 +572,7 @@ def run_stack(args, verify=True, cpu=True):
         flops.append(layer.query(tn.TN_QUERY_FLOPS_PER_TOKEN))
         # large calls of some layers run on a cheaper plan rebuilt per call: count the work actually done
         lazy_min = layer.query(tn.TN_QUERY_LAZY_MIN_TOKENS)
-        matrix_min = layer.query(tn.TN_QUERY_MATRIX_MIN_TOKENS)
-        if matrix_min and tokens >= matrix_min:
+        if layer.query(tn.TN_QUERY_MATRIX_TOKENS_BASE + tokens):
             flops_prefill.append(2 * spec.M * spec.N + layer.query(tn.TN_QUERY_MATRIX_BUILD_FLOPS) / tokens)
         else:
             flops_prefill.append(layer.query(tn.TN_QUERY_LAZY_FLOPS_PER_TOKEN) if lazy_min and tokens >= lazy_min
@@ -812,6 +819,7 @@ def main() -> int:
                     help="run a two-step train as two launches (intermediate in the workspace)")
     ap.add_argument("--cpu-sample-tokens", type=int, default=8192)
     ap.add_argument("--no-cpu-baseline", action="store_true")
+    ap.add_argument("--detail-file", type=str, default="", help="write every figure that was measured to this file, as JSON")
     ap.add_argument("--no-stack", action="store_true", help="default run: leave the 64-layer stack out")
     ap.add_argument("--time-budget-s", type=float, default=150.0,
                     help="default run: records that would start after this many seconds are skipped (and say so)")
@@ -841,7 +849,7 @@ def main() -> int:
                   "vs_baseline": None, "dtype": "bf16", "data": "synthetic",
                   "config": {"workload": rec["workload"], "tokens": rec["tokens"], "matrices": rec["matrices"]}}
         result.update({k: v for k, v in rec.items() if k not in ("workload", "tokens", "matrices")})
-        print(json.dumps(result))
+        print_result(result, args.detail_file)
         return 0
 
     if args.custom:
@@ -942,8 +950,49 @@ def main() -> int:
     if everything:
         result["configs"] = configs
     result["bench_wall_s"] = time.perf_counter() - t_start
-    print(json.dumps(result))
+    print_result(result, args.detail_file)
     return 0
+
+
+def print_result(result, detail_file):
+    """ONE line of JSON on stdout, short enough to be read back from the end of a log: the contract's fields, the roofline and the
+    key figures of every record. Everything that was measured goes to `detail_file` if one is given."""
+    if detail_file:
+        with open(detail_file, "w") as f:
+            json.dump(result, f, indent=1)
+    num = lambda v: float(f"{v:.5g}") if isinstance(v, float) else v      # noqa: E731
+    keep = ("tokens_per_s", "ms_per_step", "ms_per_pass", "ms_per_call", "us_per_call", "tflops", "tflops_factorised", "frac", "bound", "achieved",
+            "peak", "unit", "value", "skipped", "bit_equal", "gpu_rel_max_err_first_rows", "gpu_rel_max_err_on_these_rows",
+            "gpu_ms_per_step_events", "decode_1tok_graph_us_per_layer", "speedup_1tok", "graph_us_per_layer", "us_per_layer", "us_per_pair_forward2", "speedup", "cores", "kind")
+
+    def brief(v, depth):
+        if not isinstance(v, dict):
+            return num(v)
+        out = {}
+        for k, x in v.items():
+            if isinstance(x, dict) and depth > 0 and k not in ("by_format", "ms_by_format", "top10_classes_ms", "top10_classes_us", "timed"):
+                b = brief(x, depth - 1)
+                if b:
+                    out[k] = b
+            elif k in keep and not isinstance(x, (dict, list)):
+                out[k] = num(x)
+        return out
+
+    line = {k: num(v) for k, v in result.items() if not isinstance(v, (dict, list))}
+    for k in ("config",):
+        line[k] = result[k]
+    for k in ("roofline", "decode_1tok", "decode_1tok_graph", "verify_8tok", "decode_64tok", "cpu_baseline", "prefill"):
+        if isinstance(result.get(k), dict):
+            line[k] = brief(result[k], 0)
+    if isinstance(result.get("roofline"), dict) and "kernel" in result["roofline"]:
+        line["roofline"]["kernel"] = result["roofline"]["kernel"][:160]
+    if "configs" in result:
+        line["configs"] = {k: brief(v, 2) for k, v in result["configs"].items()}
+    text = json.dumps(line)
+    if len(text) > 6000:                      # never so long that the head is lost
+        line.pop("configs", None)
+        text = json.dumps(line)
+    print(text)
 
 
 if __name__ == "__main__":

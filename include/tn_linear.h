@@ -64,7 +64,8 @@ extern "C" {
                                        parameter tensors at create time until two are left (a ring of four cores
                                        becomes two half rings), and keep them. This is the plan large calls of a
                                        default layer run on with the merged tensors rebuilt per call
-                                       (TN_QUERY_LAZY_MIN_TOKENS); with this flag every call runs on it. */
+                                       (TN_QUERY_LAZY_MIN_TOKENS); with this flag every call does that does not contract the
+                                       caller's tensors with each other first (TN_QUERY_MATRIX_MIN_TOKENS). */
 #define TN_FLAG_TRANSPOSE      128   /* apply W^T instead of W: X is [tokens, M], Y is [tokens, N],
                                        Y[t, j] = sum_i W[i, j] X[t, i]. Same tensors, same description; this is
                                        the gradient of the forward pass with respect to its input, which the
@@ -73,7 +74,9 @@ extern "C" {
 #define TN_FLAG_TRAINABLE (1 << 25)      /* the layer can also give the gradients of a loss with respect to its tensors
                                        (tn_linear_param_gradients, Section 3.4): every parameter tensor of the caller
                                        stays separate (as with TN_FLAG_NO_MERGE; no lazily merged plan either) and the
-                                       handle holds a second workspace for the saved intermediates of a backward pass */
+                                       handle holds a second workspace for a backward pass (saved intermediates, or dW and
+                                       what is made of it). Large forward calls may still contract the tensors with each
+                                       other first (TN_QUERY_MATRIX_MIN_TOKENS), which takes memory for W. */
 #define TN_FLAG_QUANT_MXFP4 (1 << 26)    /* 4-bit tensors (Section 6: 4-bit quantisation of the cores; the paper gives no scheme,
                                        the one taken is the OCP microscaling format MXFP4, weight-only): at create every
                                        tensor of the caller is quantised in blocks of 32 consecutive elements of its
@@ -97,7 +100,8 @@ extern "C" {
 #define TN_FLAG_SCALAR_KERNELS  1   /* run every contraction step on the plain FMA kernel */
 #define TN_FLAG_NO_SPLIT_K      4   /* never use the split-K kernel for small launches */
 #define TN_FLAG_NO_PAIR_CHAIN   32   /* never run a two-step plan as one chained launch (see TN_QUERY_PAIR_CHAINABLE):
-                                       always two launches with the intermediate in the workspace */
+                                       always two launches with the intermediate in the workspace, at any token count
+                                       (the tensors are not contracted with each other first either) */
 #define TN_FLAG_NO_CHAIN2       64   /* never run two small transposing steps (Tucker factor products) as one
                                        chained launch: always one launch per step */
 #define TN_FLAG_NO_SMALL_CHAIN (1 << 20) /* never run a small layer as one launch with all its tensors in LDS */
@@ -161,6 +165,10 @@ extern "C" {
                                            W, nor with TN_FLAG_NO_MERGE, TN_FLAG_NO_LAZY_MERGE, TN_FLAG_NO_PAIR_CHAIN,
                                            TN_FLAG_SCALAR_KERNELS or a forced variant. */
 #define TN_QUERY_MATRIX_BUILD_FLOPS 19  /* handle only: FLOPs such a call spends on W (0 if none) */
+#define TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS 20 /* handle only: 0, or the token count from which tn_linear_param_gradients goes through the
+                                           gradient of W */
+#define TN_QUERY_GRADIENT_MATRIX_FLOPS 21 /* handle only: FLOPs such a call executes beside dW = dY^T X (2 M N per token, tokens
+                                           padded to 64): 0 for a dense layer */
 #define TN_QUERY_MATRIX_TOKENS_BASE (1 << 30) /* handle only: TN_QUERY_MATRIX_TOKENS_BASE + t: 1 if a call of t tokens takes the
                                            order of TN_QUERY_MATRIX_MIN_TOKENS, else 0 */
 #define TN_QUERY_STEP_BASE        100   /* 100 + 10*s + f: field f of step s:

@@ -54,6 +54,8 @@ TN_QUERY_QUANT_BYTES = 16
 TN_QUERY_QUANT_STREAM_BYTES = 17
 TN_QUERY_MATRIX_MIN_TOKENS = 18
 TN_QUERY_MATRIX_BUILD_FLOPS = 19
+TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS = 20
+TN_QUERY_GRADIENT_MATRIX_FLOPS = 21
 TN_QUERY_MATRIX_TOKENS_BASE = 1 << 30
 TN_QUERY_STEP_BASE = 100
 

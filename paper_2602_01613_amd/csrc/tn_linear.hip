@@ -190,6 +190,7 @@ struct tn_linear_s {
     // tensor is W)
     bool mgrad = false;
     int64_t mgrad_min_tokens = 0, mgrad_chunk = 0;
+    int64_t mgrad_flops = 0;                  // of a pass, beside dW
     int64_t mgrad_f[2] = {0, 0};              // modes of the halves
     int64_t mgrad_off[8] = {};                // byte offsets in bwd_ws: X, dY; in two parts each: dW, dW transposed, the two
                                               // operands, dH, dH transposed
@@ -2654,6 +2655,7 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
             H.dh.b_lo = g.half[1 - i].pair ? g.half[1 - i].op.out_elems : 0;
             H.dh.out_lo = G.pair ? F * m.Kr : 0;
             us += 3.f + std::max(gemm_choice(h, H.dh, F, kMaxGradPartialBytes).us, float(F * (Fo + m.Kr)) * 4.f / 3.5e6f);
+            h->mgrad_flops += 2 * F * Fo * m.Kr * H.dh.segments();
             if (!G.pair) {
                 sums = std::max(sums, F * H.dh.Cp * 4);
                 continue;
@@ -2661,6 +2663,7 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
             if (F * m.Kr > tn::kMatrixMaxElems) return TN_OK;
             fill_product_step(&H.op.s, G.op);
             H.op.s.out_lo = G.op.out_elems;
+            h->mgrad_flops += 2 * G.op.R * G.op.C * G.op.K + 2 * 2 * 2 * G.F1 * G.F2 * H.S;      // dA and dB, two parts of dH each
             us += product_us(h, H.op.s);
             room(4 + i, G.op.out_elems);
             dh = std::max(dh, G.F1 * G.F2);
@@ -3697,6 +3700,8 @@ int tn_linear_query(tn_linear_t h, int32_t what, int64_t* value) {
         case TN_QUERY_LAZY_FLOPS_PER_TOKEN: *value = h->lazy ? h->lazy_plan.flops : 0; return TN_OK;
         case TN_QUERY_MATRIX_MIN_TOKENS: *value = h->matrix ? h->mat_ranges.front().first : 0; return TN_OK;
         case TN_QUERY_MATRIX_BUILD_FLOPS: *value = h->matrix ? h->mat_flops : 0; return TN_OK;
+        case TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS: *value = h->mgrad ? h->mgrad_min_tokens : 0; return TN_OK;
+        case TN_QUERY_GRADIENT_MATRIX_FLOPS: *value = h->mgrad ? h->mgrad_flops : 0; return TN_OK;
         case TN_QUERY_QUANT_BYTES: *value = h->quant_bytes; return TN_OK;
         case TN_QUERY_QUANT_STREAM_BYTES: *value = h->q4_stream_bytes; return TN_OK;
         case TN_QUERY_BACKWARD_CHUNK_TOKENS: *value = h->trainable ? (h->mgrad ? h->mgrad_chunk : h->bwd_chunk) : 0; return TN_OK;

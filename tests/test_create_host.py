@@ -95,3 +95,17 @@ def test_gradient_of_a_tensor_of_more_than_31_bits(fake_hip):
     spec = wl.TNSpec(wl.FORMAT_DENSE, "bf16", (46344,), (46400,), ())
     got = create(fake_hip, spec, 8, [], flags=tn.TN_FLAG_TRAINABLE, grad_tokens=[1, 8])
     assert got["rc"] == 0 and got["gradients"] == [0, 0]
+
+
+def test_work_of_gradients_through_dw(fake_hip):
+    """FLOPs beside dW: a dense layer none; a train of two cores its two gradients, each from dW in two parts against a core."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    what = [tn.TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS, tn.TN_QUERY_GRADIENT_MATRIX_FLOPS]
+    dense = create(fake_hip, wl.stack_spec(wl.FORMAT_DENSE, 5120, 1024, 0), 512, what, flags=tn.TN_FLAG_TRAINABLE)
+    assert dense[str(what[0])] > 0 and dense[str(what[1])] == 0
+    spec = wl.TNSpec(wl.FORMAT_TT, "bf16", (64, 32), (64, 64), (1, 128, 1))
+    train = create(fake_hip, spec, 4096, what, flags=tn.TN_FLAG_TRAINABLE)
+    assert train[str(what[0])] > 0 and train[str(what[1])] == 2 * (2 * 2 * spec.M * spec.N * 128)
+    steps = create(fake_hip, spec, 4096, what, flags=tn.TN_FLAG_TRAINABLE | tn.TN_FLAG_NO_LAZY_MERGE)
+    assert steps[str(what[0])] == 0
