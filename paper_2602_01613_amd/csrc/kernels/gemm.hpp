@@ -4,9 +4,8 @@
 #pragma once
 
 // ---------------------------------------------------------------------------------------------
-// Out[r][c] = sum_k A[r][k] * B[c][k], A row-major with K % 8 == 0, B packed fragment-major with zeros from K to whole tiles of
-// 64, output through the step's scatter tables in aligned pieces of 8 columns (TRANS = 0) or of 8 rows (TRANS = 1), or
-// (TRANS = 1, scalar_out) one value at a time where it comes in neither: 16 neighbouring columns per store.
+// Out[r][c] = sum_k A[r][k] * B[c][k], A row-major with K % 64 == 0, B packed fragment-major, output through the
+// step's scatter tables in aligned pieces of 8 columns (TRANS = 0) or of 8 rows (TRANS = 1).
 //
 // What bounds it: on large shapes the power the chip may draw. With every wait hidden the clock settles at what the
 // energy of a K tile allows, so what counts is energy per product (measured at 8192 x 8192 x 5120):
@@ -37,10 +36,10 @@ struct GemmArgs {
     int32_t n_row, n_col;          // output tiles
     int32_t n_split;               // ranges of K
     int32_t ktiles_per_split;      // K tiles of 64 per range, at least one in every range
-    int32_t scalar_out;            // TRANS = 1: outputs in no aligned pieces
+    int32_t scalar_out;            // GEMM_ANY, TRANS = 1: outputs in no aligned pieces
     float* partial;                // not null: fp32 sums [split][rows_pad][ld] instead of the output (TRANS = 0, C % 4 == 0)
     int64_t rows_pad, ld;
-    // PARTS = 2, in elements, 0: there is none
+    // GEMM_PARTS, in elements, 0: there is none
     int64_t a_lo, b_lo;            // from an operand to its low part
     int64_t out_lo;                // from the output to where its low part goes
 };
@@ -53,11 +52,17 @@ struct GemmShape {
     static constexpr size_t SMEM = size_t(2) * STAGE_BYTES + size_t(TAB_ROWS + BN) * 4;
 };
 
-// PARTS = 2: a matrix of fp32 significance as a sum of two of bf16, high = bf16(v) and low = bf16(v - high), which leaves 2^-17
-// of v. With low parts the K tiles are walked two or three times, (A, B), (A low, B), (A, B low), into the same sums, which is
-// the fp32 product but for terms of 2^-16: sums over tokens have to pass through here without losing what averaging over
-// the tokens gained. Instantiations of their own, so that the loop above stays as it was measured.
-template <int TM, int TN, int TRANS, int PARTS = 1>
+// Forms of the kernel, instantiations of their own so that the loop above stays as it was measured (with the second and third as
+// branches in it, launches of 10 us took 0.2 to 0.5 longer: the arguments are fetched later).
+//   GEMM_PARTS  a matrix of fp32 significance as a sum of two of bf16, high = bf16(v) and low = bf16(v - high), which leaves 2^-17
+//               of v. With low parts the K tiles are walked two or three times, (A, B), (A low, B), (A, B low), into the same
+//               sums, which is the fp32 product but for terms of 2^-16: sums over tokens have to pass through here without
+//               losing what averaging over the tokens gained.
+//   GEMM_ANY    K % 8 == 0: B holds zeros from K to whole tiles, and chunks of A past it read as zeros; and outputs in neither
+//               kind of piece (TRANS = 1, scalar_out): one value at a time, 16 neighbouring columns per store.
+enum GemmForm : int { GEMM_PLAIN = 1, GEMM_PARTS = 2, GEMM_ANY = 3 };
+
+template <int TM, int TN, int TRANS, int FORM = GEMM_PLAIN>
 __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs g) {
 #ifdef __HIP_DEVICE_COMPILE__
     using S = GemmShape<TM, TN>;
@@ -88,7 +93,7 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
     const uint32_t row0 = uint32_t(row_tile) * BM;
     const int col0 = col_tile * BN, nks = a.Kp >> 4;
     const int kt0 = split * g.ktiles_per_split;
-    const int nk_seg = a.Kp >> 6, n_seg = PARTS == 1 ? 1 : 1 + (g.a_lo != 0) + (g.b_lo != 0);
+    const int nk_seg = a.Kp >> 6, n_seg = FORM != GEMM_PARTS ? 1 : 1 + (g.a_lo != 0) + (g.b_lo != 0);
     const int nk = min(nk_seg * n_seg, kt0 + g.ktiles_per_split) - kt0;  // >= 1
 
     // rows past the end read as zeros (bounds of the buffer)
@@ -102,10 +107,10 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
     const int chunk = (lane & 7) ^ ((wave * 4 + (lane >> 4)) & 7);
     int va = (wave * 8 + (lane >> 3)) * row_bytes + chunk * 16;
     // in a last tile that K does not fill, chunks past it read as zeros too: what follows them is the next row
-    const int va_last = ((a.K & 63) && kt0 + nk == nk_seg * n_seg && chunk * 8 >= (a.K & 63)) ? int(0x80000000u) : va;
+    const int va_last = (FORM == GEMM_ANY && (a.K & 63) && kt0 + nk == nk_seg * n_seg && chunk * 8 >= (a.K & 63)) ? int(0x80000000u) : va;
     const int vb = wave * 1024 + lane * 16;              // the four waves bring the four k-step blocks of a column block
     auto load1 = [&](int j, int kt, unsigned char* s) {
-        if (PARTS == 2) {
+        if (FORM == GEMM_PARTS) {
             const int t = kt0 + kt, seg = (t >= nk_seg) + (t >= 2 * nk_seg), tk = t - seg * nk_seg;
             const bool a_low = seg == 1 && g.a_lo, b_low = seg && !a_low;
             if (j < TM)
@@ -136,10 +141,10 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_t*)(tab + S::TAB_ROWS * 4 + wave * 256), 4,
                                                      min(col0 + wave * 64 + lane, a.C - 1) * 4, 0, 0, 0);
     }
-    if (nk == 1) va = va_last;
+    if (FORM == GEMM_ANY && nk == 1) va = va_last;
 #pragma unroll
     for (int l = 0; l < L; ++l) load1(l, 0, dyn_smem);
-    if (nk == 2) va = va_last;
+    if (FORM == GEMM_ANY && nk == 2) va = va_last;
 #pragma unroll
     for (int l = 0; l < L; ++l) load1(l, min(1, nk - 1), dyn_smem + STAGE);
 
@@ -199,7 +204,7 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_sched_barrier(0);
         // (the last two tiles load the last one again, into a stage nobody reads)
-        if (kt + 3 == nk) va = va_last;
+        if (FORM == GEMM_ANY && kt + 3 == nk) va = va_last;
         kstep(1, sn, 0, min(kt + 2, nk - 1), s, std::integral_constant<int, L>());
         // keep the accumulators in the accumulation registers across the back edge
 #pragma unroll
@@ -260,14 +265,14 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
     };
     const int piece = 16 * (lane >> 5) + 8 * ((lane >> 4) & 1);
     const __amdgpu_buffer_rsrc_t rlo = __builtin_amdgcn_make_buffer_rsrc(
-        static_cast<bf16_t*>(a.Out) + int64_t(t_first) * a.c_tok_stride + (PARTS == 2 ? g.out_lo : 0), 0, 0x7fffffff, 0x00020000);
+        static_cast<bf16_t*>(a.Out) + int64_t(t_first) * a.c_tok_stride + (FORM == GEMM_PARTS ? g.out_lo : 0), 0, 0x7fffffff, 0x00020000);
     auto low = [](const floatx4& v) -> floatx4 {
         floatx4 r;
 #pragma unroll
         for (int e = 0; e < 4; ++e) r[e] = low_part(v[e]);
         return r;
     };
-    if (TRANS && g.scalar_out) {
+    if (FORM == GEMM_ANY && TRANS && g.scalar_out) {
         // lane: column l%16 of tile j, rows 4*(l/16) .. +3 of tile i
         uint32_t co[TN];
 #pragma unroll
@@ -317,7 +322,7 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
             for (int j = 0; j < TN / 2; ++j)
                 __builtin_amdgcn_raw_buffer_store_b128(merge(acc[i][2 * j], acc[i][2 * j + 1]), ro,
                                                        int(((base | co[j]) & OUT) ? ~0u : base + co[j]), 0, 0);
-            if (PARTS == 2 && g.out_lo) {
+            if (FORM == GEMM_PARTS && g.out_lo) {
 #pragma unroll
                 for (int j = 0; j < TN / 2; ++j)
                     __builtin_amdgcn_raw_buffer_store_b128(merge(low(acc[i][2 * j]), low(acc[i][2 * j + 1])), rlo,

@@ -626,10 +626,10 @@ __global__ void __launch_bounds__(NW * 64) step_split_q4_kernel(StepArgs a, floa
                                 gridDim.x * (TM * 32));
 }
 
-// Sums the partial results of the split-K kernel in split order and stores through the tables; with out_lo, what rounding
-// takes off goes there.
-__global__ void __launch_bounds__(256) step_split_reduce_kernel(StepArgs a, const float* partial, int nsplit,
-                                                                uint32_t rows_pad, int64_t out_lo) {
+// Sums the partial results of the split-K kernel in split order and stores through the tables; PARTS = 2: what rounding takes off
+// goes out_lo elements further.
+template <int PARTS>
+__device__ __forceinline__ void split_reduce(const StepArgs& a, const float* partial, int nsplit, uint32_t rows_pad, int64_t out_lo) {
     bf16_t* Out = static_cast<bf16_t*>(a.Out);
     int64_t total = int64_t(a.total_rows) * a.C;
     for (int64_t e = int64_t(blockIdx.x) * 256 + threadIdx.x; e < total; e += int64_t(gridDim.x) * 256) {
@@ -648,10 +648,20 @@ __global__ void __launch_bounds__(256) step_split_reduce_kernel(StepArgs a, cons
         }
         uint32_t t = g / a.R;
         uint32_t r = g - t * a.R;
-        bf16_t* out = Out + (int64_t(t) * a.c_tok_stride + a.crow[r] + a.ccol[c]);
-        *out = bf16_t(sum);
-        if (out_lo) out[out_lo] = bf16_t(low_part(sum));
+        const int64_t at = int64_t(t) * a.c_tok_stride + a.crow[r] + a.ccol[c];
+        Out[at] = bf16_t(sum);
+        if (PARTS == 2) Out[at + out_lo] = bf16_t(low_part(sum));
     }
+}
+
+__global__ void __launch_bounds__(256) step_split_reduce_kernel(StepArgs a, const float* partial, int nsplit,
+                                                                uint32_t rows_pad) {
+    split_reduce<1>(a, partial, nsplit, rows_pad, 0);
+}
+
+__global__ void __launch_bounds__(256) step_split_reduce_parts_kernel(StepArgs a, const float* partial, int nsplit,
+                                                                      uint32_t rows_pad, int64_t out_lo) {
+    split_reduce<2>(a, partial, nsplit, rows_pad, out_lo);
 }
 
 // ---------------------------------------------------------------------------------------------

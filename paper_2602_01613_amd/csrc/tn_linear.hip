@@ -546,15 +546,15 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
 
 using gemm_kern_t = void (*)(StepArgs, GemmArgs);
 
-template <int I, int TRANS, int PARTS>
+template <int I, int TRANS, int FORM>
 constexpr gemm_kern_t gemm_kernel_of() {
     if constexpr (TRANS && (kGemmTile[I].tm & 1)) return nullptr;
-    else return step_gemm_kernel<kGemmTile[I].tm, kGemmTile[I].tn, TRANS, PARTS>;
+    else return step_gemm_kernel<kGemmTile[I].tm, kGemmTile[I].tn, TRANS, FORM>;
 }
 
-template <int TRANS, int PARTS, int... I>
+template <int TRANS, int FORM, int... I>
 gemm_kern_t gemm_kernel_at(int tile, std::integer_sequence<int, I...>) {
-    static const gemm_kern_t k[kGemmTiles] = {gemm_kernel_of<I, TRANS, PARTS>()...};
+    static const gemm_kern_t k[kGemmTiles] = {gemm_kernel_of<I, TRANS, FORM>()...};
     return k[tile];
 }
 
@@ -564,17 +564,18 @@ size_t gemm_smem_at(int tile, std::integer_sequence<int, I...>) {
     return b[tile];
 }
 
-gemm_kern_t gemm_kernel(int tile, bool trans, bool parts) {
+gemm_kern_t gemm_kernel(int tile, bool trans, int form) {
     using seq = std::make_integer_sequence<int, kGemmTiles>;
-    if (parts) return trans ? nullptr : gemm_kernel_at<0, 2>(tile, seq());
-    return trans ? gemm_kernel_at<1, 1>(tile, seq()) : gemm_kernel_at<0, 1>(tile, seq());
+    if (form == GEMM_PARTS) return trans ? nullptr : gemm_kernel_at<0, GEMM_PARTS>(tile, seq());
+    if (form == GEMM_ANY) return trans ? gemm_kernel_at<1, GEMM_ANY>(tile, seq()) : gemm_kernel_at<0, GEMM_ANY>(tile, seq());
+    return trans ? gemm_kernel_at<1, GEMM_PLAIN>(tile, seq()) : gemm_kernel_at<0, GEMM_PLAIN>(tile, seq());
 }
 size_t gemm_smem(int tile) { return gemm_smem_at(tile, std::make_integer_sequence<int, kGemmTiles>()); }
 
 int configure_gemm() {
     for (int t = 0; t < kGemmTiles; ++t)
-        for (int form = 0; form < 3; ++form) {
-            const gemm_kern_t k = gemm_kernel(t, form == 1, form == 2);
+        for (int form = 0; form < 6; ++form) {
+            const gemm_kern_t k = gemm_kernel(t, (form & 1) != 0, GEMM_PLAIN + form / 2);
             if (k && hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
                                          int(gemm_smem(t))) != hipSuccess)
                 return TN_ERR_HIP;
@@ -614,7 +615,7 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
     g.a_lo = s.a_lo;
     g.b_lo = s.b_lo;
     g.out_lo = s.out_lo;
-    const bool parts = s.a_lo || s.b_lo || s.out_lo;
+    const int form = s.a_lo || s.b_lo || s.out_lo ? GEMM_PARTS : (a.K % 64 || s.cmode == 0 ? GEMM_ANY : GEMM_PLAIN);
     g.partial = c.n_split > 1 || f32 ? static_cast<float*>(partial) : nullptr;
     if (f32) {
         if (f32->sums) {
@@ -624,11 +625,14 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
         *f32 = GemmSums{g.partial, g.ld, c.n_split};
     }
     const int64_t items = int64_t(g.n_row) * g.n_col * g.n_split;
-    hipLaunchKernelGGL(gemm_kernel(c.tile, trans, parts), dim3(uint32_t((items + 7) / 8 * 8)), dim3(256), gemm_smem(c.tile), st, a, g);
+    hipLaunchKernelGGL(gemm_kernel(c.tile, trans, form), dim3(uint32_t((items + 7) / 8 * 8)), dim3(256), gemm_smem(c.tile), st, a, g);
     if (c.n_split > 1 && !f32) {
         const int64_t total = rows * s.plan.C;
-        hipLaunchKernelGGL(step_split_reduce_kernel, dim3(uint32_t(std::min<int64_t>((total + 255) / 256, 2048))), dim3(256), 0, st,
-                           a, g.partial, c.n_split, uint32_t(rows), s.out_lo);
+        const dim3 blocks(uint32_t(std::min<int64_t>((total + 255) / 256, 2048)));
+        if (s.out_lo)
+            hipLaunchKernelGGL(step_split_reduce_parts_kernel, blocks, dim3(256), 0, st, a, g.partial, c.n_split, uint32_t(rows), s.out_lo);
+        else
+            hipLaunchKernelGGL(step_split_reduce_kernel, blocks, dim3(256), 0, st, a, g.partial, c.n_split, uint32_t(rows));
     }
     return TN_OK;
 }
@@ -790,7 +794,7 @@ int launch_step(const tn_linear_s* h, const Workspace& w, const DevStep& s, cons
             int64_t total = rows * s.plan.C;
             uint32_t blocks = uint32_t(std::min<int64_t>((total + 255) / 256, 2048));
             hipLaunchKernelGGL(step_split_reduce_kernel, dim3(blocks), dim3(256), 0, st, a, part, sc.nsplit,
-                               uint32_t(sc.row_tiles * 32 * sc.tm), int64_t(0));
+                               uint32_t(sc.row_tiles * 32 * sc.tm));
         }
         return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
     }
