@@ -71,16 +71,23 @@ def test_short_k_between_the_two_kernels(n_out):
     layer.close()
 
 
-@pytest.mark.parametrize("tokens", [65, 130, 999])
-def test_outputs_along_the_rows(tokens):
-    """A last step whose output runs along its rows (stores of 8 rows), rows of several tokens in one tile."""
-    spec = wl.TNSpec(wl.FORMAT_TT, "bf16", (16, 8, 8), (8, 8, 16), (1, 64, 64, 1))
+@pytest.mark.parametrize("om,im,rk,last", [((72, 8), (16, 64), (1, 64, 1), (8, 1024, 72)),           # 8 rows a token
+                                           ((160, 160), (8, 16), (1, 64, 1), (160, 512, 160)),
+                                           ((104, 8, 8), (8, 8, 8), (1, 64, 64, 1), (64, 512, 104))])
+@pytest.mark.parametrize("tokens", [9, 65, 130, 331])
+def test_outputs_along_the_rows(om, im, rk, last, tokens):
+    """A last step whose output runs along its rows (stores of 8 rows), rows of several tokens in one tile, tokens that end inside
+    one, columns that end inside a tile."""
+    spec = wl.TNSpec(wl.FORMAT_TT, "bf16", om, im, rk)
     rng = np.random.default_rng(tokens)
     ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(s[0] * s[2]), "bf16") for s in spec.tensor_shapes()]
-    flags = tn.TN_FLAG_NO_MERGE | tn.TN_FLAG_NO_SMALL_CHAIN
+    flags = tn.TN_FLAG_NO_MERGE | tn.TN_FLAG_NO_SMALL_CHAIN | tn.TN_FLAG_NO_PAIR_CHAIN
     layer = make_layer(spec, ts, tokens, flags=flags)
+    step = tn.TN_QUERY_STEP_BASE + 10 * (len(om) - 1)
+    assert layer.query(tn.TN_QUERY_NUM_STEPS) == len(om) and layer.query(step + 5) == 12
+    assert tuple(layer.query(step + f) for f in range(3)) == last
     x = wl.round_to_dtype(rng.standard_normal((tokens, spec.N)), "bf16")
-    err = O.rel_max_err(to_host(layer(to_dev(x, "bf16"))), O.forward(spec.format, ts, x, n_out_modes=3))
+    err = O.rel_max_err(to_host(layer(to_dev(x, "bf16"))), O.forward(spec.format, ts, x, n_out_modes=len(om)))
     layer.close()
     assert err <= 2e-2
 

@@ -268,9 +268,9 @@ def test_every_stack_class(n):
 
 @pytest.mark.parametrize("n_in,n_out,r", [(25600, 5120, 96), (5120, 25600, 64), (8192, 5120, 96), (5120, 8192, 64)])
 def test_stack_rings_prefill_8192(n_in, n_out, r):
-    """The rings that carry the stack's prefill time (ranks 64 and 96 on the wide projections: bonds of 4096 and
-    9216 values through the Kronecker-sum kernel on slices rebuilt per call) at 8192 tokens as the stack
-    benchmark launches them: a seeded sample of output features over all 8192 tokens."""
+    """The rings of ranks 64 and 96 on the wide projections (bonds of 4096 and 9216 values) at 8192 tokens as the stack
+    benchmark launches them, the cores contracted with each other first: a seeded sample of output features over all
+    8192 tokens. (The Kronecker-sum kernel at many tokens: test_kronecker_sum_kernel.)"""
     tokens = 8192
     spec = wl.stack_spec(wl.FORMAT_TR, n_in, n_out, r)
     ts = wl.make_tensors(spec, 4, instance=9)
@@ -280,6 +280,7 @@ def test_stack_rings_prefill_8192(n_in, n_out, r):
     x = wl.make_x(spec, tokens, 4, instance=9)
     layer = make_layer(spec, ts, tokens)
     assert layer.query(tn.TN_QUERY_LAZY_MIN_TOKENS) == 1
+    assert layer.query(tn.TN_QUERY_MATRIX_TOKENS_BASE + tokens) == 1
     yd = layer(to_dev(x, spec.dtype))
     torch.cuda.synchronize()
     y = to_host(yd[:, torch.from_numpy(rows).cuda()])
@@ -317,9 +318,8 @@ def test_stack_shapes_prefill_8192(fmt, n_in, n_out, r):
 
 @pytest.mark.parametrize("n_out,n_in", [(9216, 64), (8448, 96), (1024, 160), (4352, 64)])
 def test_partly_filled_last_round(n_out, n_in):
-    """The 256x256 kernel at 2048 rows (8 row tiles, one per XCD): 36 and 33 column tiles leave a last
-    round of 4 and 1 tiles per XCD, which runs as half-width tiles in a second launch; 4 column tiles run
-    as half-width tiles altogether; 17 stay as they are. Whole output against the oracle."""
+    """The matrix-product kernel at 2048 rows and numbers of columns that leave part of the last round of workgroups
+    empty in every tile size, K of one tile to two and a half. Whole output against the oracle."""
     spec = _spec(tn.TN_FORMAT_DENSE, "bf16", (n_out,), (n_in,), ())
     ts = _rand_layer(spec, 900 + n_out)
     x = wl.round_to_dtype(np.random.default_rng(n_out).standard_normal((2048, spec.N)), "bf16")
@@ -481,8 +481,8 @@ def test_chained_pair_kernel_small(case):
 def test_chained_pair_kernel_q_proj(tokens, dense_w):
     spec, ts, w = dense_w(1)
     x = wl.make_x(spec, tokens, 1)
-    layer = make_layer(spec, ts, tokens)
-    assert layer.query(tn.TN_QUERY_PAIR_CHAINABLE) == 1
+    layer = make_layer(spec, ts, tokens, flags=tn.TN_FLAG_NO_LAZY_MERGE)      # (the cores are not contracted with each other first)
+    assert layer.query(tn.TN_QUERY_PAIR_CHAINABLE) == 1 and layer.query(tn.TN_QUERY_MATRIX_MIN_TOKENS) == 0
     y = to_host(layer(to_dev(x, "bf16")))
     layer.close()
     assert O.rel_max_err(y, O.apply_linear(w, x)) <= TOL["bf16"]
@@ -521,8 +521,10 @@ def test_kronecker_sum_kernel(case):
         print(f"kron case {case} tokens {tokens}", flush=True)
         x = wl.round_to_dtype(np.random.default_rng(case + tokens).standard_normal((tokens, spec.N)), "bf16")
         ref = O.apply_linear(w, x)
-        layer = make_layer(spec, ts, tokens, flags=flags)
+        # (many tokens would contract the factors with each other first)
+        layer = make_layer(spec, ts, tokens, flags=flags | tn.TN_FLAG_NO_LAZY_MERGE)
         assert layer.query(tn.TN_QUERY_NUM_STEPS) == 2 and layer.query(tn.TN_QUERY_STEP_BASE + 6) == 4
+        assert layer.query(tn.TN_QUERY_MATRIX_MIN_TOKENS) == 0
         yd = layer(to_dev(x, "bf16"))
         torch.cuda.synchronize()
         assert torch.equal(yd, layer(to_dev(x, "bf16")))          # same bits on a second call
@@ -557,6 +559,10 @@ LAZY_CASES = [
     ((10, 16, 10, 16), (8, 10, 8, 8), (32,) * 5),       # five chunks of o1, x gathered element-wise
     ((8, 16, 8, 8), (8, 10, 8, 8), (48,) * 5),          # 2304 values of the shared bond: over a quarter of dense
     ((4, 8, 4, 8), (8, 10, 8, 8), (32,) * 5),           # 32 x 32 outputs per term: the smallest instantiation
+    # modes whose digits do not add up in the slice layout (tn::make_slice_plan refuses them, test_plan_host.py): the slices
+    # are written by the kernel of one workgroup per value of the bond
+    ((16, 7, 6, 4), (5, 8, 8, 9), (16,) * 5),
+    ((4, 7, 16, 8), (12, 6, 7, 4), (20,) * 5),
 ]
 
 

@@ -526,3 +526,27 @@ raise SystemExit(lib.plan_host_matrix_grad_plan(ctypes.byref(d)))
 """
     res = subprocess.run([sys.executable, "-c", code], cwd=os.path.dirname(HERE), capture_output=True, text=True, timeout=300)
     assert res.returncode == 0, res.stderr[-500:]
+
+
+@pytest.mark.parametrize("om,im,rk", [((16, 7, 6, 4), (5, 8, 8, 9), (16,) * 5), ((4, 7, 16, 8), (12, 6, 7, 4), (20,) * 5)])
+def test_rings_without_slices_as_products(host_exec, om, im, rk):
+    """The rings of test_lazily_merged_ring whose slices have no plan as products."""
+    d, keep = _make_desc(tn.TN_FORMAT_TR, tn.TN_DTYPE_BF16, om, im, rk, None, 64, 0, 0, None)
+    assert tn.plan_query(tn.TN_FORMAT_TR, tn.TN_DTYPE_BF16, om, im, rk, tn.TN_QUERY_KRON_CHAINABLE, flags=tn.TN_FLAG_MERGE_HALVES) > 0
+    ts = [np.zeros((rk[0], m, n, rk[0])) for m, n in zip(om, im)]
+    ptrs = (ctypes.c_void_p * 4)(*[t.ctypes.data for t in ts])
+    w = np.zeros((int(np.prod(om)), int(np.prod(im))))
+    assert host_exec.plan_host_slices(ctypes.byref(d), ptrs, w.ctypes.data) == 1
+
+
+@pytest.mark.parametrize("om,im,rk", [((72, 8), (16, 64), (1, 64, 1)), ((160, 160), (8, 16), (1, 64, 1)),
+                                      ((104, 8, 8), (8, 8, 8), (1, 64, 64, 1))])
+def test_last_steps_along_the_rows(host_exec, om, im, rk):
+    """The layers of test_outputs_along_the_rows: aligned runs of 8 along the rows of the last step, none along its columns."""
+    d, keep = _make_desc(tn.TN_FORMAT_TT, tn.TN_DTYPE_BF16, om, im, rk, None, 1, 0, tn.TN_FLAG_NO_MERGE, None)
+    v = ctypes.c_int64()
+    hints = []
+    for field in range(3):
+        assert host_exec.plan_host_step_hint(ctypes.byref(d), len(om) - 1, field, ctypes.byref(v)) == 0
+        hints.append(v.value)
+    assert hints[0] < 8 and hints[1] == 8 and hints[2] == 1
