@@ -495,9 +495,9 @@ constexpr float kGemmReduceUs = 3.f;
 // (with these the choice is 2.0 % above the best tile and number of ranges on average and 16 % at most over 165 products of 66 to
 // 4000 rows, operands as above; with 0.6 + 0.4 u for all tiles and 4 us, 6 % and 48 %)
 
-// A column operand above this passes through the caches once per band of four row tiles: 33 us for 262 MB (4000 x 25600 x 5120: tiles
-// of 256 rows 808 us, of 192 887, of 160 934; their K tiles alone 817, 766, 764). One band and its remainder overlap (600 x 25600 x
-// 5120: five tiles of 128 rows 157 us, four of 160 181).
+// A column operand above this passes through the caches once per band of four row tiles: 33 us for 262 MB, which tiles of 256 x 256
+// hide and smaller ones less (4000 x 25600 x 5120: tiles of 256 rows 808 us, of 224 865, of 192 887, of 160 934; their K tiles alone
+// 817, 805, 779, 764). One band and its remainder overlap (600 x 25600 x 5120: five tiles of 128 rows 157 us, four of 160 181).
 constexpr float kGemmCachedBytes = 128e6f;
 
 // The tile size and the number of K ranges with the least time for `rows` rows; partial sums within `cap` bytes.
@@ -530,7 +530,11 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
             const float used = float(items) / float((full + (rest > 0 ? 1 : 0)) * (half && full == 0 ? cus : slots));
             float us = rounds * per_round + (half ? g.o1 : 0.f) +
                        float(per) * (rounds * per_tile + (half ? g.t1 : 0.f)) * gemm_clock(g, used);
-            if (b_bytes > kGemmCachedBytes) us += std::max(1.25f, 0.25f * float((uint32_t(rows) + 32 * g.tm - 1) / uint32_t(32 * g.tm))) * b_bytes / 8e6f;
+            if (b_bytes > kGemmCachedBytes) {
+                const float bands = 0.25f * float((uint32_t(rows) + 32 * g.tm - 1) / uint32_t(32 * g.tm));
+                const float shown = std::min(1.f, float(64 - g.tm * g.tn) / 24.f);       // the largest tiles hide the passes
+                us += (1.25f + std::max(0.f, bands - 1.25f) * shown) * b_bytes / 8e6f;
+            }
             if (ns > 1) us += kGemmReduceUs + 2.f * float(ns) * float(rows) * float(s.plan.C) * 4.f / kGemmPartialBytesPerUs;
             if (best.tile < 0 || us < best.us) {
                 best.us = us;
