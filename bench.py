@@ -78,12 +78,12 @@ def measured_traffic(workload, flags, tokens, kernel):
     (None, None) where that kernel was not measured."""
     if flags or tokens != 8192:
         return None, None
-    name = {1: "tt_q_proj_prefill8192_hbm_traffic.txt", 2: "tucker_up_proj_prefill8192_hbm_traffic.txt",
-            3: "tr_down_proj_prefill8192_hbm_traffic.txt", 4: "dense_q_proj_prefill8192_hbm_traffic.txt"}.get(workload)
+    name = {"step_gemm_kernel": "matrix_product_kernel_counters.txt", "step_pair_kernel": "tt_q_proj_prefill8192_hbm_traffic.txt",
+            "step_kronsum_kernel": "tr_down_proj_prefill8192_hbm_traffic.txt"}.get(kernel)
     if name is None:
         return None, None
     try:
-        m = re.search(rf"TRAFFIC_BYTES_PER_LAUNCH {kernel} = (\d+)", open(os.path.join(ROOT, "profiles", name)).read())
+        m = re.search(rf"TRAFFIC_BYTES_PER_LAUNCH {kernel} workload {workload} = (\d+)", open(os.path.join(ROOT, "profiles", name)).read())
         return (int(m.group(1)), "profiles/" + name) if m else (None, None)
     except OSError:
         return None, None
@@ -962,7 +962,7 @@ def print_result(result, detail_file):
             json.dump(result, f, indent=1)
     num = lambda v: float(f"{v:.5g}") if isinstance(v, float) else v      # noqa: E731
     keep = ("tokens_per_s", "ms_per_step", "ms_per_pass", "ms_per_call", "us_per_call", "tflops", "tflops_factorised", "frac", "bound", "achieved",
-            "peak", "unit", "value", "skipped", "bit_equal", "gpu_rel_max_err_first_rows", "gpu_rel_max_err_on_these_rows",
+            "peak", "unit", "traffic", "value", "skipped", "bit_equal", "gpu_rel_max_err_first_rows", "gpu_rel_max_err_on_these_rows",
             "gpu_ms_per_step_events", "decode_1tok_graph_us_per_layer", "speedup_1tok", "graph_us_per_layer", "us_per_layer", "us_per_pair_forward2", "speedup", "cores", "kind")
 
     def brief(v, depth):
