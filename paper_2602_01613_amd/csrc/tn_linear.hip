@@ -1786,7 +1786,7 @@ bool takes_matrix(const tn_linear_s* h, int64_t tokens) {
 
 // Decide whether calls of many tokens contract the tensors with each other first, from how many tokens on, and prepare it.
 // The other orders are priced at the rates their kernels reach at many tokens (FLOP per us: chained pair kernel 1.3e9, one
-// launch per step 0.45e9; the Kronecker-sum kernel as below). Measured, us per call in this order / in the other: ring
+// launch per step 0.45e9; the Kronecker-sum kernel by kron_us). Measured, us per call in this order / in the other: ring
 // 25600 -> 5120 of rank 32 343 / 410 at 96 tokens, 767 / 8109 at 2048, 1955 / 30730 at 8192; ring 5120 -> 8192 of rank 96 776 /
 // 911 at 48 tokens, 885 / 35579 at 2048; train 5120 -> 25600 of rank 96 226 / 207 at 387 tokens, 226 / 391 at 420; train 5120 -> 8192 of rank 64 166 / 211 at 2048 tokens, 538 /
 // 783 at 8192; of rank 32, whose chain has little more than 2 M N, not taken.
@@ -2677,7 +2677,7 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
             dh = std::max(dh, G.F1 * G.F2);
             dht = std::max(dht, tn::detail::round64(G.F1) * G.F2);
             sums = std::max(sums, std::max(G.F1, G.F2) * round_up(int(H.S), kGradSumsPad) * 4);
-            us += 80.f + float(G.F1 * G.F2) * 12.f / 3.5e6f;
+            us += 46.f + float(G.F1 * G.F2) * 12.f / 3.5e6f;
         }
         room(6, dh);
         room(7, dht);
