@@ -19,8 +19,13 @@
 //     and its 16-byte chunk c sits at position c ^ ((row / 2) % 8), so that the 16 rows a read touches at a time
 //     fall on 16 different slots of the 64 banks (with c ^ (row % 8) 40 % of the LDS cycles were conflicts); B's
 //     packed blocks lie in fragment order already and are copied as they are.
-// Two stages of 64 k: the second half of a K tile (its fragments are in registers by then) frees the stage, one
-// barrier per tile lets the loads of the tile after the next into it, and they have a whole tile to arrive.
+// NS stages of 64 k. Once the fragments of a tile's second half are in registers its stage is free: one barrier per tile
+// lets the loads of the tile NS further on into it. The largest tiles leave LDS for two stages; a third, and the loads dealt out
+// evenly over the whole of a tile instead of over its second half, is worth 10 to 18 % to the smaller ones, which move more bytes
+// per product and do not cover the memory's latency with one tile (us with two stages and bunched loads / as it is: 1024 x
+// 8192 x 5120 on 128 x 256 tiles 98 / 77, 777 x 25600 x 5120 on 160 x 256 206 / 170, 2500 x 8192 x 5120 195 / 159; 8192 x
+// 8192 x 5120 on 256 x 256, two stages as before, 531 / 507). Tiles of which a CU holds two workgroups keep to half of its LDS.
+// Loads past the last tile are out of bounds and read no memory.
 // The sums leave straight from registers: two lane swaps turn the accumulator layout (4 consecutive values per lane)
 // into 16-byte pieces of 64-byte runs, with no second trip through LDS; the output offsets of the tile's rows and
 // columns are fetched into LDS when the tile starts.
@@ -44,12 +49,12 @@ struct GemmArgs {
     int64_t out_lo;                // from the output to where its low part goes
 };
 
-template <int TM, int TN>
+template <int TM, int TN, int NS>
 struct GemmShape {
     static constexpr int BM = 32 * TM, BN = 32 * TN;
     static constexpr int STAGE_BYTES = (BM + BN) * 128;
     static constexpr int TAB_ROWS = (BM + 63) / 64 * 64;                 // crow of the tile's rows, ccol of its columns: 64 entries per load
-    static constexpr size_t SMEM = size_t(2) * STAGE_BYTES + size_t(TAB_ROWS + BN) * 4;
+    static constexpr size_t SMEM = size_t(NS) * STAGE_BYTES + size_t(TAB_ROWS + BN) * 4;
 };
 
 // Forms of the kernel, instantiations of their own so that the loop above stays as it was measured (with the second and third as
@@ -62,10 +67,15 @@ struct GemmShape {
 //               kind of piece (TRANS = 1, scalar_out): one value at a time, 16 neighbouring columns per store.
 enum GemmForm : int { GEMM_PLAIN = 1, GEMM_PARTS = 2, GEMM_ANY = 3 };
 
-template <int TM, int TN, int TRANS, int FORM = GEMM_PLAIN>
+template <typename F, int... Q>
+__device__ __forceinline__ void for_constants(F&& f, std::integer_sequence<int, Q...>) {
+    (f(std::integral_constant<int, Q>()), ...);
+}
+
+template <int TM, int TN, int NS, int TRANS, int FORM = GEMM_PLAIN>
 __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs g) {
 #ifdef __HIP_DEVICE_COMPILE__
-    using S = GemmShape<TM, TN>;
+    using S = GemmShape<TM, TN, NS>;
     constexpr int NW = 4, BM = S::BM, BN = S::BN, STAGE = S::STAGE_BYTES, A_BYTES = BM * 128;
     constexpr int L = TM + TN;                           // 1 KB direct-to-LDS loads per wave and stage: TM of A, then TN of B
     static_assert(TN % 2 == 0 && (!TRANS || TM % 2 == 0), "stores pair neighbouring tiles");
@@ -109,27 +119,29 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
     // in a last tile that K does not fill, chunks past it read as zeros too: what follows them is the next row
     const int va_last = (FORM == GEMM_ANY && (a.K & 63) && kt0 + nk == nk_seg * n_seg && chunk * 8 >= (a.K & 63)) ? int(0x80000000u) : va;
     const int vb = wave * 1024 + lane * 16;              // the four waves bring the four k-step blocks of a column block
-    auto load1 = [&](int j, int kt, unsigned char* s) {
+    // tiles past the range: out of bounds, no memory is read
+    auto past = [&](int kt) -> int { return kt < nk ? 0 : int(0x80000000u); };
+    auto load1 = [&](int j, int kt, int off, unsigned char* s) {
         if (FORM == GEMM_PARTS) {
             const int t = kt0 + kt, seg = (t >= nk_seg) + (t >= 2 * nk_seg), tk = t - seg * nk_seg;
             const bool a_low = seg == 1 && g.a_lo, b_low = seg && !a_low;
             if (j < TM)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(pa + (a_low ? g.a_lo : 0)), 0, a_size, 0x00020000),
-                    (lds_t*)(s + (j * NW + wave) * 1024), 16, va, tk * 128 + j * (NW * 8) * row_bytes, 0, 0);
+                    (lds_t*)(s + (j * NW + wave) * 1024), 16, va | off, tk * 128 + j * (NW * 8) * row_bytes, 0, 0);
             else
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(pb + (b_low ? g.b_lo : 0)), 0, b_size, 0x00020000),
-                    (lds_t*)(s + A_BYTES + ((j - TM) * NW + wave) * 1024), 16, vb, tk * 4096 + (j - TM) * nks * 1024, 0, 0);
+                    (lds_t*)(s + A_BYTES + ((j - TM) * NW + wave) * 1024), 16, vb | off, tk * 4096 + (j - TM) * nks * 1024, 0, 0);
         } else if (j < TM)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_t*)(s + (j * NW + wave) * 1024), 16, va,
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_t*)(s + (j * NW + wave) * 1024), 16, va | off,
                                                      (kt0 + kt) * 128 + j * (NW * 8) * row_bytes, 0, 0);
         else
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_t*)(s + A_BYTES + ((j - TM) * NW + wave) * 1024), 16, vb,
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rb, (lds_t*)(s + A_BYTES + ((j - TM) * NW + wave) * 1024), 16, vb | off,
                                                      (kt0 + kt) * 4096 + (j - TM) * nks * 1024, 0, 0);
     };
     // output offsets of the tile's rows and columns; entries past the end repeat a valid one and are not used
-    unsigned char* tab = dyn_smem + 2 * STAGE;
+    unsigned char* tab = dyn_smem + NS * STAGE;
     if (!g.partial) {
         const __amdgpu_buffer_rsrc_t rr = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.crow), 0, int(a.R) * 4, 0x00020000);
         const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.ccol), 0, a.C * 4, 0x00020000);
@@ -141,12 +153,22 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rc, (lds_t*)(tab + S::TAB_ROWS * 4 + wave * 256), 4,
                                                      min(col0 + wave * 64 + lane, a.C - 1) * 4, 0, 0, 0);
     }
-    if (FORM == GEMM_ANY && nk == 1) va = va_last;
+    // One K tile is 2 * TM * TN MFMAs. The reads of the second half's fragments are dealt out over the first RS * NR of them and
+    // are followed by the barrier (BAR); the loads of the tile NS further on into the stage that is free from there on are
+    // dealt out over what is left of the tile, or, with a stage to spare, over a whole tile's length: the last of them
+    // go with the first MFMAs of the next tile. A load keeps the vector-memory path of the CU for 16 cycles, an MFMA its
+    // SIMD's matrix core: all of them in the second half of a tile (4 x 8: 48 loads, 768 cycles, beside 512 of MFMAs) stall it.
+    constexpr int NM = TM * TN, NR = TM + TN;
+    constexpr int RS = NM * 3 / 4 / NR > 1 ? NM * 3 / 4 / NR : 1, BAR = RS * NR + 4 < NM ? RS * NR + 4 : NM;
+    constexpr int SPAN = NS > 2 ? 2 * NM : 2 * NM - BAR;
+    constexpr int L_NOW = NS > 2 ? ((2 * NM - BAR) * L + SPAN - 1) / SPAN : L;      // loads l with BAR + l * SPAN / L < 2 * NM
+    static_assert(L_NOW <= L && BAR + (L_NOW - 1) * SPAN / L < 2 * NM && (L_NOW == L || BAR + L_NOW * SPAN / L >= 2 * NM), "load slots");
 #pragma unroll
-    for (int l = 0; l < L; ++l) load1(l, 0, dyn_smem);
-    if (FORM == GEMM_ANY && nk == 2) va = va_last;
+    for (int q = 0; q < NS; ++q) {
+        if (FORM == GEMM_ANY && nk == q + 1) va = va_last;
 #pragma unroll
-    for (int l = 0; l < L; ++l) load1(l, min(1, nk - 1), dyn_smem + STAGE);
+        for (int l = 0; l < (q == NS - 1 ? L_NOW : L); ++l) load1(l, q, past(q), dyn_smem + q * STAGE);
+    }
 
     // fragments: lane l supplies row (A) or column (B) l%16 and k = 32*ks + 8*(l/16) .. +7
     int oa[2], ob[2];
@@ -158,29 +180,9 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
     }
     floatx4 acc[TM][TN];
     bf16x8 fa[2][TM], fb[2][TN];
-    constexpr int NR = TM + TN;
     auto read1 = [&](int q, int set, const unsigned char* s, int ks) {       // the columns first: every row of MFMAs needs them all
         if (q < TN) fb[set][q] = *reinterpret_cast<const bf16x8*>(s + ob[ks] + (q >> 1) * 4096 + (q & 1) * 256);
         else fa[set][q - TN] = *reinterpret_cast<const bf16x8*>(s + oa[ks] + (q - TN) * 2048);
-    };
-    // One k-step of 32: the MFMAs of one fragment set with the reads of the other and (NL > 0) the loads of a tile dealt
-    // out between them. The reads are done after three quarters of it.
-    auto kstep = [&](int set, const unsigned char* rs, int rks, int kt2, unsigned char* ls, auto n_loads) {
-        constexpr int NL = decltype(n_loads)::value, NM = TM * TN;
-        constexpr int RS = NM * 3 / 4 / NR > 0 ? NM * 3 / 4 / NR : 1, LS = NL && NM / NL > 0 ? NM / NL : 1;
-#pragma unroll
-        for (int m = 0; m < NM; ++m) {
-            const int i = m / TN, j = m % TN;
-            acc[i][j] = TRANS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[set][i], fb[set][j], acc[i][j], 0, 0, 0)
-                              : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[set][j], fa[set][i], acc[i][j], 0, 0, 0);
-            if (m % RS == 0 && m / RS < NR) read1(m / RS, set ^ 1, rs, rks);
-            if (NL && m % LS == LS / 2 && m / LS < NL) load1(m / LS, kt2, ls);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-#pragma unroll
-        for (int q = (NM + RS - 1) / RS; q < NR; ++q) read1(q, set ^ 1, rs, rks);
-#pragma unroll
-        for (int l = (NM - LS / 2 + LS - 1) / LS; l < NL; ++l) load1(l, kt2, ls);
     };
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -190,22 +192,45 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
             for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
             asm volatile("" : "+a"(acc[i][j]));
         }
-    wait_vmcnt<L>();                                     // the tables and the first K tile have landed
+    wait_vmcnt<(NS - 2) * L + L_NOW>();                  // the tables and the first K tile have landed
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int q = 0; q < NR; ++q) read1(q, 0, dyn_smem, 0);
+    int at = 0, at_prev = (NS - 1) * STAGE;              // byte offsets of this tile's stage and of the one before
     for (int kt = 0; kt < nk; ++kt) {
-        unsigned char* s = dyn_smem + (kt & 1) * STAGE;
-        const unsigned char* sn = dyn_smem + ((kt + 1) & 1) * STAGE;
+        unsigned char *s = dyn_smem + at, *sp = dyn_smem + at_prev;
+        at_prev = at;
+        at = at == (NS - 1) * STAGE ? 0 : at + STAGE;
+        const unsigned char* sn = dyn_smem + at;
+        const int off_prev = past(kt + NS - 1), off = past(kt + NS);
         __builtin_amdgcn_sched_barrier(0);
-        kstep(0, s, 1, 0, nullptr, std::integral_constant<int, 0>());
-        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): this wave has read the whole stage
-        wait_vmcnt<0>();                                 // its loads of the next stage have landed
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        // (the last two tiles load the last one again, into a stage nobody reads)
-        if (FORM == GEMM_ANY && kt + 3 == nk) va = va_last;
-        kstep(1, sn, 0, min(kt + 2, nk - 1), s, std::integral_constant<int, L>());
+        // (slots as compile-time constants: as a loop, 128 of them are not unrolled in time to keep the fragments in registers)
+        auto slot = [&](auto slot_index) {
+            constexpr int q = decltype(slot_index)::value, half = q / NM, m = q % NM, i = m / TN, j = m % TN;
+            if constexpr (q == BAR) {
+                __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): this wave has read the whole stage
+                wait_vmcnt<(NS - 2) * L>();              // its loads of the next stage have landed
+                __builtin_amdgcn_s_barrier();
+                if (FORM == GEMM_ANY && kt + NS + 1 == nk) va = va_last;
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            acc[i][j] = TRANS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[half][i], fb[half][j], acc[i][j], 0, 0, 0)
+                              : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[half][j], fa[half][i], acc[i][j], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (m % RS == 0 && m / RS < NR) read1(m / RS, half ^ 1, half ? sn : s, half ^ 1);
+            if constexpr (NR > NM && m == NM - 1) {
+#pragma unroll
+                for (int r = NM; r < NR; ++r) read1(r, half ^ 1, half ? sn : s, half ^ 1);
+            }
+#pragma unroll
+            for (int l = 0; l < L_NOW; ++l)
+                if (BAR + l * SPAN / L == q) load1(l, kt + NS, off, s);
+#pragma unroll
+            for (int l = L_NOW; l < L; ++l)
+                if (BAR + l * SPAN / L == q + 2 * NM) load1(l, kt + NS - 1, off_prev, sp);
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        for_constants(slot, std::make_integer_sequence<int, 2 * NM>());
         // keep the accumulators in the accumulation registers across the back edge
 #pragma unroll
         for (int i = 0; i < TM; ++i)

@@ -457,31 +457,29 @@ int launch_pipe(const DevStep& s, const StepArgs& a, int64_t rows, hipStream_t s
     return TN_OK;
 }
 
-// Tile sizes of step_gemm_kernel and what they cost, in us: `t1` per K tile of 64 with one workgroup on every CU and
+// Tile sizes of step_gemm_kernel, their LDS stages, and what they cost, in us: `t1` per K tile of 64 with one workgroup on every CU and
 // `o1` per round of workgroups (start, first loads, stores); t2, o2 likewise with two on every CU, where they fit: there the
-// start and the stores of one run under the products of the other, and short K or many rounds favour them (6144 x 15360 x
-// 128: 256 x 256 tiles 54 us, 192 x 128 67, 160 x 128 55; 5120 x 10240 x 64: 34, 37, 28). Fitted to 8192 x 8192 x 5120 and to
-// the products of short K. 64 x 64 is for outputs of up to 64 columns, the gradients towards a bond, which read A once and are
-// bound by the loads in flight (10240 x 64 x 4096: 31 us, 64 x 128 36; 5120 x 32 x 2560: 12 and 20). Larger tiles do more
-// per us, smaller ones leave less of the last round of workgroups empty and pad fewer rows.
+// start and the stores of one run under the products of the other, and short K or many rounds favour them (10240 x 4096 x 64: 160 x 128
+// tiles 22.4 us, 224 x 256 24.1, 192 x 128 29). Fitted to 212 products of 70 to 15360 rows, 32 to 25600 columns and K of 64 to
+// 40960, every tile and number of K ranges of each: the choice is 1.4 % above the best on average, 5 % at the 90th percentile, 20 %
+// at most. 64 x 64 is for outputs of up to 64 columns, the gradients towards a bond, which read A once and are
+// bound by the loads in flight. Larger tiles do more per us, smaller ones leave less of the last round of workgroups empty and
+// pad fewer rows.
 struct GemmTile {
-    int tm, tn;
+    int tm, tn, stages;
     float t1, o1, t2, o2;
 };
 constexpr int kGemmTiles = 14;
 constexpr GemmTile kGemmTile[kGemmTiles] = {
-    {8, 8, 1.38f, 6.3f, 0.f, 0.f}, {7, 8, 1.18f, 6.3f, 0.f, 0.f}, {6, 8, 1.01f, 5.8f, 0.f, 0.f}, {5, 8, 0.90f, 4.8f, 0.f, 0.f},
-    {4, 8, 0.86f, 4.1f, 0.f, 0.f}, {3, 8, 0.75f, 3.4f, 0.f, 0.f}, {2, 8, 0.67f, 2.6f, 0.f, 0.f}, {8, 4, 0.95f, 3.6f, 0.f, 0.f},
-    {6, 4, 0.75f, 3.0f, 0.f, 0.f}, {5, 4, 0.73f, 1.8f, 0.93f, 4.3f}, {4, 4, 0.64f, 2.0f, 0.84f, 3.5f},
-    {3, 4, 0.58f, 1.5f, 0.69f, 2.8f}, {2, 4, 0.54f, 1.0f, 0.55f, 1.9f},
-    {2, 2, 0.45f, 1.0f, 0.50f, 1.6f}};
+    {8, 8, 2, 1.25f, 7.1f, 0.f, 0.f}, {7, 8, 2, 1.14f, 6.4f, 0.f, 0.f}, {6, 8, 2, 0.95f, 6.7f, 0.f, 0.f}, {5, 8, 3, 0.79f, 6.3f, 0.f, 0.f},
+    {4, 8, 3, 0.69f, 5.3f, 0.f, 0.f}, {3, 8, 3, 0.59f, 4.4f, 0.f, 0.f}, {2, 8, 3, 0.43f, 4.6f, 0.f, 0.f}, {8, 4, 3, 0.71f, 4.8f, 0.f, 0.f},
+    {6, 4, 3, 0.59f, 4.0f, 0.f, 0.f}, {5, 4, 2, 0.67f, 3.4f, 0.96f, 4.6f}, {4, 4, 2, 0.61f, 3.2f, 0.84f, 3.7f},
+    {3, 4, 2, 0.54f, 3.2f, 0.71f, 2.9f}, {2, 4, 3, 0.27f, 3.4f, 0.60f, 2.4f},
+    {2, 2, 4, 0.18f, 3.0f, 0.34f, 3.2f}};
 
-// The clock rises when part of the chip idles: products take this share of their time with a share u of the slots for
-// workgroups taken (1024 x 5120 x 8192, us per K tile against the table: 0.76 at u = 0.31, 0.83 at 0.47, 0.95 at 0.86; but 160 x
-// 256 tiles of 800 x 8192 x 5120 1.06 at 0.63, and 0.8 picks better than 0.6 over all). Tiles of
-// up to 128 x 128 are not bound by their products but wait for their loads, 0.5 us per K tile whatever the clock (460 x 1024 x
-// 2304 on operands that the caches of the workgroups' XCDs do not hold: 64 x 64 in one range 18.5 us, in four 12.5).
-inline float gemm_clock(const GemmTile& g, float u) { return g.tm * g.tn <= 16 ? 1.f : std::min(1.f, 0.8f + 0.2f * u); }
+// A K tile takes at least a load's time divided by the tiles in flight; a column operand above kGemmColdBytes comes from
+// memory. Without this, 600 x 5120 x 8192 takes 64-row tiles (92 us instead of 65).
+constexpr float kGemmColdUs = 1.0f, kGemmColdBytes = 60e6f;
 
 struct GemmChoice {
     int tile = -1, n_split = 1, ktiles_per_split = 1;
@@ -490,10 +488,8 @@ struct GemmChoice {
 };
 
 constexpr int64_t kGemmMinRows = 65;        // up to 64 rows the launch is a stream of the packed tensor: the kernels of stream.hpp
-constexpr float kGemmPartialBytesPerUs = 3.5e6f;    // partial sums, written and read back, and the launch that adds them:
+constexpr float kGemmPartialBytesPerUs = 5e6f;    // partial sums, written and read back, and the launch that adds them:
 constexpr float kGemmReduceUs = 3.f;
-// (with these the choice is 2.0 % above the best tile and number of ranges on average and 16 % at most over 165 products of 66 to
-// 4000 rows, operands as above; with 0.6 + 0.4 u for all tiles and 4 us, 6 % and 48 %)
 
 // A column operand above this passes through the caches once per band of four row tiles: 33 us for 262 MB, which tiles of 256 x 256
 // hide and smaller ones less (4000 x 25600 x 5120: tiles of 256 rows 808 us, of 224 865, of 192 887, of 160 934; their K tiles alone
@@ -525,11 +521,10 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
             const uint32_t slots = g.t2 > 0.f ? 2 * cus : cus;
             const uint32_t full = items / slots, rest = items - full * slots;
             const bool half = g.t2 > 0.f && rest > 0 && rest <= cus;            // a last round with one workgroup per CU
-            const float per_tile = g.t2 > 0.f ? g.t2 : g.t1, per_round = g.t2 > 0.f ? g.o2 : g.o1;
+            const float least = b_bytes > kGemmColdBytes ? kGemmColdUs / float(g.stages - 1) : 0.f;
+            const float per_tile = std::max(g.t2 > 0.f ? g.t2 : g.t1, least), per_round = g.t2 > 0.f ? g.o2 : g.o1;
             const float rounds = float(full + (rest > 0 && !half ? 1 : 0));
-            const float used = float(items) / float((full + (rest > 0 ? 1 : 0)) * (half && full == 0 ? cus : slots));
-            float us = rounds * per_round + (half ? g.o1 : 0.f) +
-                       float(per) * (rounds * per_tile + (half ? g.t1 : 0.f)) * gemm_clock(g, used);
+            float us = rounds * per_round + (half ? g.o1 : 0.f) + float(per) * (rounds * per_tile + (half ? std::max(g.t1, least) : 0.f));
             if (b_bytes > kGemmCachedBytes) {
                 const float bands = 0.25f * float((uint32_t(rows) + 32 * g.tm - 1) / uint32_t(32 * g.tm));
                 const float shown = std::min(1.f, float(64 - g.tm * g.tn) / 24.f);       // the largest tiles hide the passes
@@ -553,7 +548,7 @@ using gemm_kern_t = void (*)(StepArgs, GemmArgs);
 template <int I, int TRANS, int FORM>
 constexpr gemm_kern_t gemm_kernel_of() {
     if constexpr (TRANS && (kGemmTile[I].tm & 1)) return nullptr;
-    else return step_gemm_kernel<kGemmTile[I].tm, kGemmTile[I].tn, TRANS, FORM>;
+    else return step_gemm_kernel<kGemmTile[I].tm, kGemmTile[I].tn, kGemmTile[I].stages, TRANS, FORM>;
 }
 
 template <int TRANS, int FORM, int... I>
@@ -564,7 +559,7 @@ gemm_kern_t gemm_kernel_at(int tile, std::integer_sequence<int, I...>) {
 
 template <int... I>
 size_t gemm_smem_at(int tile, std::integer_sequence<int, I...>) {
-    constexpr size_t b[kGemmTiles] = {GemmShape<kGemmTile[I].tm, kGemmTile[I].tn>::SMEM...};
+    constexpr size_t b[kGemmTiles] = {GemmShape<kGemmTile[I].tm, kGemmTile[I].tn, kGemmTile[I].stages>::SMEM...};
     return b[tile];
 }
 
@@ -1130,6 +1125,8 @@ int kron_per_cu(const tn::KronDims& d) {
     return 3 * 4096 * ((c[3] * c[1] + c[2] * 2 * c[0] + 3) / 4) > 80 * 1024 ? 1 : 2;
 }
 
+constexpr float kKronPartialBytesPerUs = 3.5e6f;      // partial sums, written and read back
+
 // What a launch of the Kronecker-sum kernel is expected to take: per value of the bond 21 ns per MFMA of a wave and 0.25 us (half of
 // that where two workgroups on a CU share its matrix cores), values one after another, in rounds of workgroups; per round the start, longer
 // with the fragments and stores of two tokens per wave; and the partial sums. Expected / measured, us: trains 5120 -> 25600 of rank
@@ -1143,7 +1140,7 @@ float kron_us(const tn_linear_s* h, const tn::KronDims& d, const KronGeom& g) {
     const int64_t rounds = (wgs + slots - 1) / slots, turns = (wgs + h->num_cus - 1) / h->num_cus;
     const float per_rho = float(c[3] * c[0] * (c[1] + 2 * c[2]) * g.tpw) * 0.021f + 0.25f / float(per_cu);
     return 10.f + float(rounds) * (g.tpw == 2 && per_cu == 1 ? 42.f : 10.f) + float(turns) * float(g.rho_per_split) * per_rho +
-           float(g.partial_bytes) / kGemmPartialBytesPerUs;
+           float(g.partial_bytes) / kKronPartialBytesPerUs;
 }
 
 KronGeom kron_geometry(const tn_linear_s* h, const tn::KronDims& d, int64_t tokens, int64_t partial_cap) {
@@ -1185,7 +1182,7 @@ KronGeom kron_geometry(const tn_linear_s* h, const tn::KronDims& d, int64_t toke
             const int64_t fit = std::max<int64_t>(1, rounds * int64_t(h->num_cus) / base), most = std::max<int64_t>(1, d.P / least);
             if (least == 2 && (fit <= std::max<int64_t>(1, d.P / 4) || base * std::max<int64_t>(1, d.P / 4) >= h->num_cus)) continue;
             const KronGeom c = with(std::min(fit, most));
-            const float us = kron_us(h, d, c) + float(c.partial_bytes) / kGemmPartialBytesPerUs;
+            const float us = kron_us(h, d, c) + float(c.partial_bytes) / kKronPartialBytesPerUs;
             if (!any || us < best_us) {
                 best = c;
                 best_us = us;

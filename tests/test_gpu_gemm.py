@@ -33,6 +33,24 @@ def test_dense_tile_edges(n_in, n_out):
     layer.close()
 
 
+@pytest.mark.parametrize("k_tiles", [1, 2, 3, 4, 5, 7])
+def test_k_tiles_and_stages(k_tiles):
+    """As many K tiles as the LDS has stages (two to four), fewer and more, for the tiles that rows and columns of these numbers lead to."""
+    n_in = 64 * k_tiles
+    rng = np.random.default_rng(k_tiles)
+    x = wl.round_to_dtype(rng.standard_normal((2600, n_in)), "bf16")
+    xd = to_dev(x, "bf16")
+    for n_out in (64, 1032, 5128):
+        spec = wl.TNSpec(wl.FORMAT_DENSE, "bf16", (n_out,), (n_in,), ())
+        w = wl.round_to_dtype(rng.standard_normal((n_out, n_in)) / np.sqrt(n_in), "bf16")
+        ref = x @ w.T
+        layer = make_layer(spec, [w], 2600, flags=tn.TN_FLAG_NO_SMALL_CHAIN | (12 << tn.TN_FLAG_VARIANT_SHIFT))
+        for rows in (70, 200, 300, 500, 777, 1030, 1500, 2600):
+            y = to_host(layer(xd[:rows].contiguous()))
+            assert np.max(np.abs(y - ref[:rows])) <= 2.0 ** -8 * np.max(np.abs(ref[:rows])) + 1e-3, (rows, n_in, n_out)
+        layer.close()
+
+
 @pytest.mark.parametrize("n_in,n_out", [(96, 264), (160, 510), (288, 1023), (1056, 1000), (5152, 520), (8192, 511), (2336, 4095)])
 def test_k_of_half_a_tile_and_outputs_one_by_one(n_in, n_out):
     """K that ends in the middle of a tile of 64 (one tile, two, many, several ranges), with infinities in the rows that follow: what
