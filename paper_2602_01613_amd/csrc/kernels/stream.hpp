@@ -667,117 +667,158 @@ __global__ void __launch_bounds__(256) step_split_reduce_parts_kernel(StepArgs a
 // ---------------------------------------------------------------------------------------------
 // Whole-chain kernel for small layers: when every packed tensor of the plan and two copies of the
 // largest per-token tensor fit in LDS together (the small fp32 train: 19 KB of cores, 8 KB per
-// intermediate), one launch runs all steps. At create time the tensors (as fp32, rows padded) and
-// the offset tables of all steps are laid out as one contiguous image (small_chain_image_kernel); a
-// workgroup copies that image into LDS with 16-byte loads, then takes tokens one at a time: the
-// token's input goes to an LDS buffer, every step reads one buffer and scatters into the other
-// through its tables - the same tables the one-launch-per-step kernels use - and the last step
-// stores to memory. Plain fp32 FMA, 256 threads over the R*C outputs of a step (consecutive threads
-// take consecutive columns, so the input value is an LDS broadcast and the tensor rows of a wave are
-// 4 banks apart). Intermediates are rounded to the storage type between steps, as on the other
-// paths. For layers this small the cost is launch latency, and this is one launch instead of one
-// per step.
+// intermediate), one launch runs all steps. At create time the tensors (as fp32, rows padded), the
+// offset tables and the descriptions of all steps are laid out as one contiguous image
+// (small_chain_image_kernel); a workgroup copies that image into LDS with 16-byte loads, then takes
+// tokens one at a time: the token's input goes to an LDS buffer, every step reads one buffer and
+// scatters into the other through its tables - the same tables the one-launch-per-step kernels use -
+// and the last step stores to memory. Intermediates are rounded to the storage type between steps, as
+// on the other paths.
+//
+// For layers this small the cost is the launch and a chain of latencies, so:
+//   * a step is tiles of 16 x 16 outputs, one to a wave, on v_mfma_f32_16x16x4_f32 (products and sums in
+//     fp32 as before, in the same four interleaved sums over k): an operand of it is one word per lane for
+//     64 products, where a thread per output read two from LDS for each. Outputs of a lane run along the
+//     columns, lanes along the rows, which is how the last step stores;
+//   * the descriptions of the steps come with the image: as kernel arguments they lie in host memory, and every step
+//     began with a fetch of its own from there;
+//   * the image's loads and the first token's are all in flight before the first is stored;
+//   * word i of a buffer sits at i + 4 * (i / 64): rows of 32 or 64 words then start on different banks.
+// 4x8x8 train of rank 8, 16 tokens: 11.2 us a call with a thread per output, 8.8 now.
 // ---------------------------------------------------------------------------------------------
 constexpr int kSmallChainMaxSteps = 8;
-struct SmallChainStep {
-    const void* B;                         // packed tensor (fragment-major); read by the image kernel only
-    const int32_t *arow, *acol;            // gather tables of the step's input (null: plain); image kernel only
-    const int32_t *crow, *ccol;            // scatter tables of its output; image kernel only
-    int32_t R, K, C, nks;                  // nks = Kp / 16 of the packing
+constexpr int kSmallChainThreads = 512;
+struct SmallChainDesc {                    // a step, as it sits in the image
+    int32_t R, K, C;
     int32_t b_off;                         // offset of the tensor in the image, in 4-byte words (a multiple of 4)
-    int32_t ldb;                           // its row length: K + 4 when K % 4 == 0 (16-byte reads), else K + 1
+    int32_t ldb;                           // its row length: K + 4 when K % 4 == 0, else K + 1
     int32_t t_off;                         // offset of the tables in the image: crow[R], ccol[C], then arow[R],
                                            // acol[K] when the input is gathered
     int32_t gathered;
+    int32_t pad;
 };
+constexpr int kSmallChainDescWords = sizeof(SmallChainDesc) / 4;
 struct SmallChainArgs {
     const void* X;
     void* Y;
-    const float* image;                    // tensors and tables of all steps, image_words long (a multiple of 4)
+    const float* image;                    // descriptions, tensors and tables of all steps, image_words long (a multiple of 4)
     int64_t N, M;
     int32_t tokens, nsteps, image_words;
     int32_t buf_off[2];                    // offsets of the two per-token buffers in LDS, in words
-    SmallChainStep st[kSmallChainMaxSteps];
+};
+struct SmallChainImageArgs {               // what the image is made of
+    int32_t nsteps, image_words;
+    SmallChainDesc d[kSmallChainMaxSteps];
+    const void* B[kSmallChainMaxSteps];    // packed tensors (fragment-major)
+    int32_t nks[kSmallChainMaxSteps];      // Kp / 16 of the packing
+    const int32_t *arow[kSmallChainMaxSteps], *acol[kSmallChainMaxSteps];      // gather tables of a step's input
+    const int32_t *crow[kSmallChainMaxSteps], *ccol[kSmallChainMaxSteps];      // scatter tables of its output
 };
 
 template <typename T>
-__global__ void __launch_bounds__(256) small_chain_image_kernel(SmallChainArgs a, float* image) {
+__global__ void __launch_bounds__(256) small_chain_image_kernel(SmallChainImageArgs a, float* image) {
     int32_t* imagei = reinterpret_cast<int32_t*>(image);
     for (int i = blockIdx.x * 256 + threadIdx.x; i < a.image_words; i += gridDim.x * 256) image[i] = 0.f;
     __syncthreads();                       // single workgroup launch: zero fill before the pieces
     for (int s = 0; s < a.nsteps; ++s) {
-        const SmallChainStep& st = a.st[s];
-        const T* B = static_cast<const T*>(st.B);
+        const SmallChainDesc& st = a.d[s];
+        if (threadIdx.x == 0) *reinterpret_cast<SmallChainDesc*>(imagei + s * kSmallChainDescWords) = st;
+        const T* B = static_cast<const T*>(a.B[s]);
         for (int i = threadIdx.x; i < st.C * st.K; i += 256) {
             int c = i / st.K, k = i - c * st.K;
-            image[st.b_off + c * st.ldb + k] = to_float(B[bfrag_offset(c, k, st.nks)]);
+            image[st.b_off + c * st.ldb + k] = to_float(B[bfrag_offset(c, k, a.nks[s])]);
         }
         int32_t* tab = imagei + st.t_off;
-        for (int i = threadIdx.x; i < st.R; i += 256) tab[i] = st.crow[i];
-        for (int i = threadIdx.x; i < st.C; i += 256) tab[st.R + i] = st.ccol[i];
+        for (int i = threadIdx.x; i < st.R; i += 256) tab[i] = a.crow[s][i];
+        for (int i = threadIdx.x; i < st.C; i += 256) tab[st.R + i] = a.ccol[s][i];
         if (st.gathered) {
-            for (int i = threadIdx.x; i < st.R; i += 256) tab[st.R + st.C + i] = st.arow[i];
-            for (int i = threadIdx.x; i < st.K; i += 256) tab[2 * st.R + st.C + i] = st.acol[i];
+            for (int i = threadIdx.x; i < st.R; i += 256) tab[st.R + st.C + i] = a.arow[s][i];
+            for (int i = threadIdx.x; i < st.K; i += 256) tab[2 * st.R + st.C + i] = a.acol[s][i];
         }
     }
 }
 
+// where word i of a per-token buffer sits, and how many words n of them take
+__host__ __device__ __forceinline__ int small_chain_word(int i) { return i + ((i >> 6) << 2); }
+
 template <typename T>
-__global__ void __launch_bounds__(256) small_chain_kernel(SmallChainArgs a) {
+__global__ void __launch_bounds__(kSmallChainThreads) small_chain_kernel(SmallChainArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
+    constexpr int NT = kSmallChainThreads, NW = NT / 64;
     float* lds = reinterpret_cast<float*>(dyn_smem);
     const int32_t* ldsi = reinterpret_cast<const int32_t*>(dyn_smem);
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const T* X = static_cast<const T*>(a.X);
+    T* Y = static_cast<T*>(a.Y);
+    const int N = int(a.N);
+    T x_first = from_float<T>(0.f);
+    if (tid < N) x_first = X[int64_t(blockIdx.x) * a.N + tid];            // the grid is no larger than the tokens
     {
         const floatx4* src = reinterpret_cast<const floatx4*>(a.image);
         floatx4* dst = reinterpret_cast<floatx4*>(lds);
-#pragma unroll 4
-        for (int i = tid; i < (a.image_words >> 2); i += 256) dst[i] = src[i];
+        const int n4 = a.image_words >> 2;
+        for (int i0 = 0; i0 < n4; i0 += 4 * NT) {
+            floatx4 v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = src[min(i0 + j * NT + tid, n4 - 1)];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (i0 + j * NT + tid < n4) dst[i0 + j * NT + tid] = v[j];
+        }
     }
-    const T* X = static_cast<const T*>(a.X);
-    T* Y = static_cast<T*>(a.Y);
     for (int t = blockIdx.x; t < a.tokens; t += gridDim.x) {
-        __syncthreads();                   // image loaded / previous token's buffers no longer read
         float* in = lds + a.buf_off[0];
         float* out = lds + a.buf_off[1];
-        for (int i = tid; i < int(a.N); i += 256) in[i] = to_float(X[int64_t(t) * a.N + i]);
-        __syncthreads();
+        if (t != int(blockIdx.x)) {
+            __syncthreads();               // the previous token's buffers are no longer read
+            if (tid < N) x_first = X[int64_t(t) * a.N + tid];
+        }
+        if (tid < N) in[small_chain_word(tid)] = to_float(x_first);
+        for (int i = tid + NT; i < N; i += NT) in[small_chain_word(i)] = to_float(X[int64_t(t) * a.N + i]);
+        __syncthreads();                   // the image and the token are in LDS
         for (int s = 0; s < a.nsteps; ++s) {
-            const SmallChainStep& st = a.st[s];
-            const float* Bs = lds + st.b_off;
-            const int32_t* t_crow = ldsi + st.t_off;
-            const int32_t* t_ccol = t_crow + st.R;
-            const int32_t* t_arow = t_ccol + st.C;
-            const int32_t* t_acol = t_arow + st.R;
+            const int32_t* d = ldsi + s * kSmallChainDescWords;
+            const int R = __builtin_amdgcn_readfirstlane(d[0]), K = __builtin_amdgcn_readfirstlane(d[1]);
+            const int C = __builtin_amdgcn_readfirstlane(d[2]), ldb = __builtin_amdgcn_readfirstlane(d[4]);
+            const float* Bs = lds + __builtin_amdgcn_readfirstlane(d[3]);
+            const int32_t* t_crow = ldsi + __builtin_amdgcn_readfirstlane(d[5]);
+            const bool gathered = __builtin_amdgcn_readfirstlane(d[6]) != 0;
+            const int32_t* t_ccol = t_crow + R;
+            const int32_t* t_arow = t_ccol + C;
+            const int32_t* t_acol = t_arow + R;
             const bool last = s + 1 == a.nsteps;
-            for (int i = tid; i < st.R * st.C; i += 256) {
-                int r = i / st.C, c = i - r * st.C;
-                const float* brow = Bs + c * st.ldb;
-                float acc = 0.f;
-                if (st.gathered) {
-                    const int base = t_arow[r];
-                    for (int k = 0; k < st.K; ++k) acc = fmaf(in[base + t_acol[k]], brow[k], acc);
-                } else if ((st.K & 3) == 0) {
-                    // 16-byte LDS reads, several in flight
-                    const floatx4* a4 = reinterpret_cast<const floatx4*>(in + r * st.K);
-                    const floatx4* b4 = reinterpret_cast<const floatx4*>(brow);
-                    float acc1 = 0.f, acc2 = 0.f, acc3 = 0.f;
-#pragma unroll 4
-                    for (int k = 0; k < (st.K >> 2); ++k) {
-                        floatx4 av = a4[k], bv = b4[k];
-                        acc = fmaf(av[0], bv[0], acc);
-                        acc1 = fmaf(av[1], bv[1], acc1);
-                        acc2 = fmaf(av[2], bv[2], acc2);
-                        acc3 = fmaf(av[3], bv[3], acc3);
+            const int row_tiles = (R + 15) >> 4, tiles = row_tiles * ((C + 15) >> 4);
+            const int kq = lane >> 4;      // a lane supplies row (column) lane % 16 and k = 4 * j + lane / 16
+            for (int tile = wave; tile < tiles; tile += NW) {
+                const int ct = tile / row_tiles, r = (tile - ct * row_tiles) * 16 + (lane & 15);
+                const int rl = min(r, R - 1), c0 = ct * 16;
+                const float* brow = Bs + min(c0 + (lane & 15), C - 1) * ldb;
+                const int base = gathered ? t_arow[rl] : rl * K;
+                floatx4 acc[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+                for (int k0 = 0; k0 < K; k0 += 16) {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const int k = k0 + 4 * u + kq, kl = min(k, K - 1);
+                        const float av = in[small_chain_word(base + (gathered ? t_acol[kl] : kl))], bv = brow[kl];
+                        // what lies past K may be no number: zero times it is none either
+                        acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(k < K ? bv : 0.f, k < K ? av : 0.f, acc[u], 0, 0, 0);
                     }
-                    acc = (acc + acc1) + (acc2 + acc3);
-                } else {
-                    const float* arow = in + r * st.K;
-                    for (int k = 0; k < st.K; ++k) acc = fmaf(arow[k], brow[k], acc);
                 }
-                const int o = t_crow[r] + t_ccol[c];
-                if (last) Y[int64_t(t) * a.M + o] = from_float<T>(acc);
-                else out[o] = to_float(from_float<T>(acc));
+                const floatx4 y = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+                if (r < R) {
+                    const int ro = t_crow[r];
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int c = c0 + 4 * kq + v;
+                        if (c >= C) continue;
+                        const int o = ro + t_ccol[c];
+                        if (last) Y[int64_t(t) * a.M + o] = from_float<T>(y[v]);
+                        else out[small_chain_word(o)] = to_float(from_float<T>(y[v]));
+                    }
+                }
             }
             __syncthreads();
             float* tmp = in;

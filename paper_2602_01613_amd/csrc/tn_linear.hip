@@ -110,9 +110,7 @@ struct tn_linear_s {
     // whole chain in one launch with everything in LDS (small layers)
     bool small_chain = false;
     size_t small_chain_smem = 0;
-    int small_chain_b_off[kSmallChainMaxSteps] = {};
-    int small_chain_t_off[kSmallChainMaxSteps] = {};
-    void* small_chain_image = nullptr;    // tensors (fp32, padded rows) and tables of all steps, as they sit in LDS
+    void* small_chain_image = nullptr;    // descriptions, tensors (fp32, padded rows) and tables of all steps, as they sit in LDS
     int small_chain_image_words = 0;
     int small_chain_buf_off[2] = {0, 0};
     // chained pair kernel (two-step plans of the train shape): second packed tensor in its layout
@@ -863,70 +861,59 @@ int launch_step(const tn_linear_s* h, const Workspace& w, const DevStep& s, cons
 // per-token buffers fit in 96 KB of LDS. Used for fp32 layers at any token count (their other path is
 // the plain FMA kernel, one launch per step) and for bf16 layers up to 32 tokens.
 constexpr size_t kSmallChainMaxSmem = 96 * 1024;
+// what they take with the buffers' banks padded (small_chain_word) and the steps' descriptions
+constexpr size_t kSmallChainMaxLds = kSmallChainMaxSmem + kSmallChainMaxSmem / 16 + 1024;
 constexpr int64_t kSmallChainMaxBf16Tokens = 32;
-
-void fill_small_chain_args(const tn_linear_s* h, SmallChainArgs* a) {
-    a->image = static_cast<const float*>(h->small_chain_image);
-    a->N = h->plan.N;
-    a->M = h->plan.M;
-    a->nsteps = int32_t(h->steps.size());
-    a->image_words = h->small_chain_image_words;
-    a->buf_off[0] = h->small_chain_buf_off[0];
-    a->buf_off[1] = h->small_chain_buf_off[1];
-    for (size_t s = 0; s < h->steps.size(); ++s) {
-        const DevStep& d = h->steps[s];
-        SmallChainStep& o = a->st[s];
-        o.B = d.packed;
-        o.arow = d.arow;
-        o.acol = d.acol;
-        o.crow = d.crow;
-        o.ccol = d.ccol;
-        o.R = int32_t(d.plan.R);
-        o.K = int32_t(d.plan.K);
-        o.C = int32_t(d.plan.C);
-        o.nks = d.Kp >> 4;
-        o.b_off = h->small_chain_b_off[s];
-        o.ldb = (o.K & 3) ? o.K + 1 : o.K + 4;
-        o.t_off = h->small_chain_t_off[s];
-        o.gathered = d.plan.a_plain ? 0 : 1;
-    }
-}
 
 int plan_small_chain(tn_linear_s* h, hipStream_t st) {
     if (h->flags & (TN_FLAG_SCALAR_KERNELS | TN_FLAG_NO_SMALL_CHAIN)) return TN_OK;
     const size_t ns = h->steps.size();
     if (ns == 0 || ns > size_t(kSmallChainMaxSteps)) return TN_OK;
-    int64_t off = 0;
+    SmallChainImageArgs im;
+    memset(&im, 0, sizeof(im));
+    im.nsteps = int32_t(ns);
+    const int64_t head = int64_t(ns) * kSmallChainDescWords;
+    int64_t off = 0;                               // behind the descriptions
     for (size_t s = 0; s < ns; ++s) {
-        const tn::Step& p = h->steps[s].plan;
+        const DevStep& d = h->steps[s];
+        const tn::Step& p = d.plan;
         if (p.R * p.C > (int64_t(1) << 20)) return TN_OK;
-        h->small_chain_b_off[s] = int(off);
+        im.d[s].b_off = int32_t(head + off);
+        im.d[s].R = int32_t(p.R);
+        im.d[s].K = int32_t(p.K);
+        im.d[s].C = int32_t(p.C);
+        im.d[s].ldb = int32_t((p.K & 3) ? p.K + 1 : p.K + 4);
+        im.d[s].gathered = p.a_plain ? 0 : 1;
+        im.B[s] = d.packed;
+        im.nks[s] = d.Kp >> 4;
+        im.arow[s] = d.arow;
+        im.acol[s] = d.acol;
+        im.crow[s] = d.crow;
+        im.ccol[s] = d.ccol;
         off += (p.C * ((p.K & 3) ? p.K + 1 : p.K + 4) + 3) & ~int64_t(3);      // every tensor starts 16-byte aligned
         if (off > int64_t(kSmallChainMaxSmem / 4)) return TN_OK;
     }
     for (size_t s = 0; s < ns; ++s) {              // the offset tables
         const tn::Step& p = h->steps[s].plan;
-        h->small_chain_t_off[s] = int(off);
+        im.d[s].t_off = int32_t(head + off);
         off += p.R + p.C + (p.a_plain ? 0 : p.R + p.K);
         if (off > int64_t(kSmallChainMaxSmem / 4)) return TN_OK;
     }
     off = (off + 3) & ~int64_t(3);
-    const int64_t image_words = off;
     const int64_t buf = (std::max(h->plan.N, h->plan.max_intermediate) + 3) & ~int64_t(3);
     if ((off + 2 * buf) * 4 > int64_t(kSmallChainMaxSmem)) return TN_OK;
-    h->small_chain_buf_off[0] = int(off);
-    h->small_chain_buf_off[1] = int(off + buf);
-    h->small_chain_smem = size_t(off + 2 * buf) * 4;
-    h->small_chain_image_words = int(image_words);
-    if (hipMalloc(&h->small_chain_image, size_t(image_words) * 4) != hipSuccess) return TN_ERR_ALLOC;
-    h->packed_bytes += image_words * 4;
-    SmallChainArgs a;
-    memset(&a, 0, sizeof(a));
-    fill_small_chain_args(h, &a);
+    const int buf_words = small_chain_word(int(buf)) + 4;
+    im.image_words = int32_t(head + off);
+    h->small_chain_buf_off[0] = im.image_words;
+    h->small_chain_buf_off[1] = im.image_words + buf_words;
+    h->small_chain_smem = size_t(im.image_words + 2 * buf_words) * 4;
+    h->small_chain_image_words = im.image_words;
+    if (hipMalloc(&h->small_chain_image, size_t(im.image_words) * 4) != hipSuccess) return TN_ERR_ALLOC;
+    h->packed_bytes += int64_t(im.image_words) * 4;
     if (h->elt == 2)
-        hipLaunchKernelGGL(small_chain_image_kernel<bf16_t>, dim3(1), dim3(256), 0, st, a, static_cast<float*>(h->small_chain_image));
+        hipLaunchKernelGGL(small_chain_image_kernel<bf16_t>, dim3(1), dim3(256), 0, st, im, static_cast<float*>(h->small_chain_image));
     else
-        hipLaunchKernelGGL(small_chain_image_kernel<float>, dim3(1), dim3(256), 0, st, a, static_cast<float*>(h->small_chain_image));
+        hipLaunchKernelGGL(small_chain_image_kernel<float>, dim3(1), dim3(256), 0, st, im, static_cast<float*>(h->small_chain_image));
     if (hipGetLastError() != hipSuccess) return TN_ERR_HIP;
     h->small_chain = true;
     return TN_OK;
@@ -934,16 +921,21 @@ int plan_small_chain(tn_linear_s* h, hipStream_t st) {
 
 int launch_small_chain(const tn_linear_s* h, const void* x, void* y, int64_t tokens, hipStream_t st) {
     SmallChainArgs a;
-    memset(&a, 0, sizeof(a));
-    fill_small_chain_args(h, &a);
     a.X = x;
     a.Y = y;
+    a.image = static_cast<const float*>(h->small_chain_image);
+    a.N = h->plan.N;
+    a.M = h->plan.M;
     a.tokens = int32_t(tokens);
+    a.nsteps = int32_t(h->steps.size());
+    a.image_words = h->small_chain_image_words;
+    a.buf_off[0] = h->small_chain_buf_off[0];
+    a.buf_off[1] = h->small_chain_buf_off[1];
     dim3 grid(uint32_t(std::min<int64_t>(tokens, int64_t(h->num_cus) * 2)));
     if (h->elt == 2)
-        hipLaunchKernelGGL(small_chain_kernel<bf16_t>, grid, dim3(256), h->small_chain_smem, st, a);
+        hipLaunchKernelGGL(small_chain_kernel<bf16_t>, grid, dim3(kSmallChainThreads), h->small_chain_smem, st, a);
     else
-        hipLaunchKernelGGL(small_chain_kernel<float>, grid, dim3(256), h->small_chain_smem, st, a);
+        hipLaunchKernelGGL(small_chain_kernel<float>, grid, dim3(kSmallChainThreads), h->small_chain_smem, st, a);
     return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
 
@@ -2201,9 +2193,9 @@ int configure_kernels(int device) {
         (hipFuncSetAttribute(reinterpret_cast<const void*>(&step_pair_kernel<kPairStages, kPairBar>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, int(kPairSmemBytes)) != hipSuccess ||
          hipFuncSetAttribute(reinterpret_cast<const void*>(small_chain_kernel<float>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallChainMaxSmem)) != hipSuccess ||
+                             hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallChainMaxLds)) != hipSuccess ||
          hipFuncSetAttribute(reinterpret_cast<const void*>(small_chain_kernel<bf16_t>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallChainMaxSmem)) != hipSuccess))
+                             hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallChainMaxLds)) != hipSuccess))
         rc = TN_ERR_HIP;
     for (int cfg = 0; cfg < tn::kKronConfigs && rc == TN_OK; ++cfg) rc = kron_dispatch(cfg, nullptr, 0, nullptr);
     if (rc == TN_OK) rc = gen_mfma_dispatch(nullptr, 0, nullptr);

@@ -881,3 +881,23 @@ def test_two_layers_in_one_call(case):
         finally:
             l1.close()
             l3.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("out_modes,in_modes,rank", [((2, 2), (2, 3), 2), ((5, 7), (3, 7), 5), ((4, 8, 8), (4, 8, 8), 8), ((3, 10, 9), (9, 7, 5), 11),
+                                                     ((10, 10, 10), (10, 10, 10), 12), ((1, 17, 2), (33, 1, 2), 3), ((2, 3, 2, 5), (3, 2, 7, 2), 4)])
+def test_small_chain_tile_edges(dtype, out_modes, in_modes, rank):
+    """Whole chains in LDS, on tiles of 16 x 16 outputs and 16 k: rows, columns and K below a tile, of whole tiles and beyond, plain
+    and gathered inputs, more tokens than workgroups. Tolerance for fp32: K <= 120 products per sum in four chains, three steps: below
+    3 * 32 * 2^-24 = 6e-6 of the largest magnitude; bf16: the suite's."""
+    spec = wl.TNSpec(wl.FORMAT_TT, dtype, out_modes, in_modes, (1,) + (rank,) * (len(out_modes) - 1) + (1,))
+    rng = np.random.default_rng(rank + len(out_modes))
+    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(s[0] * s[2]), dtype) for s in spec.tensor_shapes()]
+    n_tok = 700 if dtype == "f32" else 32
+    x = wl.round_to_dtype(rng.standard_normal((n_tok, spec.N)), dtype)
+    ref = O.forward(spec.format, ts, x, n_out_modes=len(out_modes))
+    layer = make_layer(spec, ts, n_tok)
+    for rows in (1, 3, n_tok):
+        y = to_host(layer(to_dev(x[:rows], dtype)))
+        assert O.rel_max_err(y, ref[:rows]) <= (6e-6 if dtype == "f32" else TOL[dtype]), rows
+    layer.close()
