@@ -256,6 +256,230 @@ __global__ void __launch_bounds__(256) grad_param_mfma_kernel(GradArgs a) {
         }
 }
 
+// ---------------------------------------------------------------------------------------------
+// Both halves' gradients towards a narrow bond in one pass over dW. With D [F0][F1] the gradient of the matrix with its modes
+// ordered by halves (stored [F1 / 32][F0][32]), in two bf16 parts (high, low: see step_gemm_kernel), and the halves P0 [F0][S], P1 [F1][S]:
+//     dH0[f0][s] = sum_f1 D[f0][f1] P1[f1][s]        dH1[f1][s] = sum_f0 D[f0][f1] P0[f0][s]
+// each as the fp32 product but for terms of 2^-16: D high and low with P high, D high with P low.
+// Bound by memory: D (168 MB for 5120 x 8192) is larger than what the products, 2 S MACs an element of it, take on the matrix
+// cores. As two products of step_gemm_kernel it was read twice, and for the second one transposed through memory first: 180 us at
+// S = 64 for 4096 x 10240, 68 here with the launches that add the sums (51 for this one: 168 MB read and 59 MB of
+// sums written, 4.4 TB/s).
+//   * a workgroup owns 256 rows of D and walks over tiles of 32 columns of its range: 3 or 4 stages of (16 KB of each part of D and
+//     the 32 columns' P1), direct to LDS. dW's product leaves D tile by tile, [F1 / 32][F0][32], so that a
+//     workgroup's 16 KB lie together (as pieces of 64 bytes of row-major D, 3 stages: 69 us instead of 51). A wave holds the sums of dH0 for 64 rows in registers throughout;
+//   * the 32 rows of dH1 that a tile gives are shared out to the waves, (16 columns) x (half of the bond), so that no sums cross
+//     waves. D is contracted along its rows there: the operand is read with the transposing LDS read (ds_read_b64_tr_b16), and the
+//     wave's 256 rows x half a bond of P0 stay in registers for the whole walk;
+//   * 256 rows: the sums of dH1 leave per 256 rows of D, S/256 of D's fp32 size written and read again; with 512 there is no room for
+//     P0 next to the sums;
+//   * a 16-byte chunk c of a row of 64 bytes sits at c ^ (row / 4 % 4): the 16 rows of a read (or the 8 of a transposing one)
+//     then fall on different banks.
+// Columns of a range past its end load nothing (out of bounds).
+// ---------------------------------------------------------------------------------------------
+constexpr int kBondRows = 256, kBondCols = 32;
+struct BondGradArgs {
+    const void *D, *P0, *P1;               // D [F1 / 32][F0][32]; P0, P1 packed fragment-major, columns s, k = f0 (f1)
+    int64_t d_lo, p0_lo, p1_lo;            // from a matrix to its low part, in elements
+    float *sums0, *sums1;                  // [ranges][F0][S], [row panels][F1][S]
+    int64_t F0, F1;                        // multiples of 64
+    int32_t S;                             // 32 * S32
+    int32_t tiles, tiles_per_range, ranges;      // of 32 columns; no range is empty
+};
+
+template <int S32>
+struct BondGradShape {
+    static constexpr int ST = 2 * S32;                              // 16-wide tiles of the bond
+    static constexpr int D_BYTES = kBondRows * kBondCols * 2, P_BYTES = ST * 1024;
+    static constexpr int STAGE = 2 * (D_BYTES + P_BYTES), NS = S32 < 3 ? 4 : 3;
+    static constexpr size_t SMEM = size_t(NS) * STAGE;
+};
+
+template <int S32>
+__global__ void __launch_bounds__(256, 1) bond_grad_kernel(BondGradArgs a) {
+#ifdef __HIP_DEVICE_COMPILE__
+    using Sh = BondGradShape<S32>;
+    constexpr int ST = Sh::ST, SH = S32, STAGE = Sh::STAGE, NS = Sh::NS, D_BYTES = Sh::D_BYTES;
+    constexpr int L = 8 + SH;                            // 1 KB loads per wave and stage: 4 of each part of D, SH of P1
+    constexpr int KS = kBondRows / 32;
+    typedef __attribute__((address_space(3))) void lds_t;
+    typedef short shortx4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int panel = blockIdx.x / a.ranges, range = blockIdx.x - panel * a.ranges;
+    const int64_t row0 = int64_t(panel) * kBondRows;
+    const int tile0 = range * a.tiles_per_range, n = min(a.tiles, tile0 + a.tiles_per_range) - tile0;
+    const int nks0 = int(a.F0 >> 4), nks1 = int(a.F1 >> 4);
+
+    // P0: rows s of the wave's half of the bond, k-steps of 32 rows of D
+    const int s_tile0 = (wave >> 1) * SH;
+    bf16x8 p0[2][KS][SH];
+    {
+        const bf16_t* P0 = static_cast<const bf16_t*>(a.P0);
+        bf16x8 zero;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) zero[e] = bf16_t(0.f);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int j = 0; j < SH; ++j) {
+                p0[0][ks][j] = p0[1][ks][j] = zero;
+                if (row0 + ks * 32 < a.F0) {             // a multiple of 64 rows: k-steps are whole
+                    const bf16_t* src = P0 + bfrag_offset((s_tile0 + j) * 16 + (lane & 15), int(row0) + ks * 32 + 8 * (lane >> 4), nks0);
+                    p0[0][ks][j] = *reinterpret_cast<const bf16x8*>(src);
+                    p0[1][ks][j] = *reinterpret_cast<const bf16x8*>(src + a.p0_lo);
+                }
+            }
+        // they have landed before the loop, whose waits count its own loads only
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int j = 0; j < SH; ++j) asm volatile("" : "+v"(p0[0][ks][j]), "+v"(p0[1][ks][j]));
+    }
+
+    // rows past the end load nothing, which leaves zeros: 64 rows of a wave are all there or none is
+    const bf16_t* D = static_cast<const bf16_t*>(a.D) + row0 * kBondCols;
+    const int d_tile = int(a.F0) * kBondCols * 2;
+    const __amdgpu_buffer_rsrc_t rd = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(D), 0, 0x7fffffff, 0x00020000);
+    const __amdgpu_buffer_rsrc_t rl = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(D + a.d_lo), 0, 0x7fffffff, 0x00020000);
+    const int vd = row0 + wave * 64 < a.F0 ? wave * 4096 + (lane >> 2) * 64 + ((lane & 3) ^ ((lane >> 4) & 3)) * 16 : int(0x80000000u);
+    const bf16_t* P1 = static_cast<const bf16_t*>(a.P1);
+    const int p_size = a.S * int(a.F1) * 2;
+    auto issue = [&](int t, int stage) {
+        unsigned char* s = dyn_smem + stage * STAGE;
+        const int off = t < n ? 0 : int(0x80000000u), tile = tile0 + t;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int so = tile * d_tile + q * 1024;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rd, (lds_t*)(s + (wave * 4 + q) * 1024), 16, vd | off, so, 0, 0);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(rl, (lds_t*)(s + D_BYTES + (wave * 4 + q) * 1024), 16, vd | off, so, 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < SH; ++q) {
+            // block j % ST: (32 columns of the bond) x (16 k), of the high part, then of the low one
+            const int j = wave + 4 * q, b = j < ST ? j : j - ST;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(P1 + (j < ST ? 0 : a.p1_lo)), 0, p_size, 0x00020000),
+                (lds_t*)(s + 2 * D_BYTES + j * 1024), 16, (lane * 16) | off, ((b >> 1) * nks1 + tile * 2 + (b & 1)) * 1024, 0, 0);
+        }
+    };
+
+    // fragments: lane l supplies row (column) l%16 and k = 8*(l/16) .. +7
+    const int od = (wave * 64 + (lane & 15)) * 64 + (((lane >> 4) ^ ((lane >> 2) & 3)) * 16);
+    const int op = 2 * D_BYTES + (lane >> 5) * 1024 + ((lane & 15) + 32 * ((lane >> 4) & 1)) * 16;
+    int ot[2];                                           // transposing read: four rows of 16 columns per 16 lanes
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int row = 8 * (lane >> 4) + 4 * h + ((lane & 15) >> 2), chunk = 2 * (wave & 1) + ((lane & 3) >> 1);
+        ot[h] = row * 64 + ((chunk ^ ((row >> 2) & 3)) * 16) + (lane & 1) * 8;
+    }
+    auto read8 = [&](const unsigned char* p) { return *reinterpret_cast<const bf16x8*>(p); };
+    // four k-steps of both parts, [k-step][part]. (One block with its own wait: before the builtin of this read the compiler waits
+    // for every load to LDS that is in flight, the next tiles' among them.)
+    const uint32_t lds0 = uint32_t(uintptr_t((lds_t*)dyn_smem));
+    auto read_t4 = [&](int at, bf16x8 (&f)[4][2]) {
+        shortx4 u[16];
+        const uint32_t a0 = lds0 + uint32_t(at + ot[0]), a1 = lds0 + uint32_t(at + ot[1]);
+        static_assert(D_BYTES == 16384 && kBondCols * 64 == 2048, "offsets below");
+        asm volatile(
+            "ds_read_b64_tr_b16 %0, %16\n\tds_read_b64_tr_b16 %1, %17\n\t"
+            "ds_read_b64_tr_b16 %2, %16 offset:16384\n\tds_read_b64_tr_b16 %3, %17 offset:16384\n\t"
+            "ds_read_b64_tr_b16 %4, %16 offset:2048\n\tds_read_b64_tr_b16 %5, %17 offset:2048\n\t"
+            "ds_read_b64_tr_b16 %6, %16 offset:18432\n\tds_read_b64_tr_b16 %7, %17 offset:18432\n\t"
+            "ds_read_b64_tr_b16 %8, %16 offset:4096\n\tds_read_b64_tr_b16 %9, %17 offset:4096\n\t"
+            "ds_read_b64_tr_b16 %10, %16 offset:20480\n\tds_read_b64_tr_b16 %11, %17 offset:20480\n\t"
+            "ds_read_b64_tr_b16 %12, %16 offset:6144\n\tds_read_b64_tr_b16 %13, %17 offset:6144\n\t"
+            "ds_read_b64_tr_b16 %14, %16 offset:22528\n\tds_read_b64_tr_b16 %15, %17 offset:22528\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(u[0]), "=&v"(u[1]), "=&v"(u[2]), "=&v"(u[3]), "=&v"(u[4]), "=&v"(u[5]), "=&v"(u[6]), "=&v"(u[7]), "=&v"(u[8]),
+              "=&v"(u[9]), "=&v"(u[10]), "=&v"(u[11]), "=&v"(u[12]), "=&v"(u[13]), "=&v"(u[14]), "=&v"(u[15])
+            : "v"(a0), "v"(a1)
+            : "memory");
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            f[q >> 1][q & 1] = __builtin_bit_cast(bf16x8, __builtin_shufflevector(u[2 * q], u[2 * q + 1], 0, 1, 2, 3, 4, 5, 6, 7));
+    };
+
+    floatx4 acc[4][ST];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < ST; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float* out1 = a.sums1 + (int64_t(panel) * a.F1 + (wave & 1) * 16 + (lane & 15)) * a.S + s_tile0 * 16 + 4 * (lane >> 4);
+
+#pragma unroll
+    for (int q = 0; q < NS - 1; ++q) issue(q, q);
+    int st = 0;
+    for (int t = 0; t < n; ++t) {
+        __builtin_amdgcn_s_waitcnt(0xC07F);              // lgkmcnt(0): this wave has read the tile before
+        wait_vmcnt<(NS - 2) * L>();                      // its loads of this tile have landed (those of the next NS - 2 may not have)
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        issue(t + NS - 1, st == 0 ? NS - 1 : st - 1);
+        const int at = st * STAGE;
+        const unsigned char* s = dyn_smem + at;
+        st = st == NS - 1 ? 0 : st + 1;
+        // dH0: sums of 64 rows
+        {
+            bf16x8 h[4], l[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                h[i] = read8(s + od + i * 1024);
+                l[i] = read8(s + D_BYTES + od + i * 1024);
+            }
+#pragma unroll
+            for (int j = 0; j < ST; ++j) {
+                const bf16x8 ph = read8(s + op + (j >> 1) * 2048 + (j & 1) * 256);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, h[i], acc[i][j], 0, 0, 0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ph, l[i], acc[i][j], 0, 0, 0);
+                const bf16x8 pl = read8(s + op + Sh::P_BYTES + (j >> 1) * 2048 + (j & 1) * 256);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pl, h[i], acc[i][j], 0, 0, 0);
+            }
+        }
+        // dH1: 16 rows of it from 256 rows of D, in two chains of sums
+        floatx4 acc1[2][SH];
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+#pragma unroll
+            for (int j = 0; j < SH; ++j) acc1[c][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k4 = 0; k4 < KS / 4; ++k4) {
+            bf16x8 f[4][2];
+            read_t4(at + k4 * 8192, f);
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int j = 0; j < SH; ++j) {
+                    acc1[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0[0][4 * k4 + k][j], f[k][0], acc1[0][j], 0, 0, 0);
+                    acc1[1][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0[0][4 * k4 + k][j], f[k][1], acc1[1][j], 0, 0, 0);
+                    acc1[1][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p0[1][4 * k4 + k][j], f[k][0], acc1[1][j], 0, 0, 0);
+                }
+        }
+        float* o = out1 + int64_t(tile0 + t) * kBondCols * a.S;
+#pragma unroll
+        for (int j = 0; j < SH; ++j) *reinterpret_cast<floatx4*>(o + j * 16) = acc1[0][j] + acc1[1][j];
+        // keep the accumulators in the accumulation registers across the back edge
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < ST; ++j) asm volatile("" : "+a"(acc[i][j]));
+    }
+    wait_vmcnt<0>();                                     // no load into LDS outlives the workgroup
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int64_t r = row0 + wave * 64 + i * 16 + (lane & 15);
+        if (r >= a.F0) continue;
+        float* o = a.sums0 + (int64_t(range) * a.F0 + r) * a.S + 4 * (lane >> 4);
+#pragma unroll
+        for (int j = 0; j < ST; ++j) *reinterpret_cast<floatx4*>(o + j * 16) = acc[i][j];
+    }
+#endif
+}
+
 // grad[position of (c, k) in the caller's tensor] (+)= sum over splits of partial[split][c][k]. The position follows the
 // step's packing recipe (PackArgs: digits of k and c times their strides); a tensor with a traced index pair (a
 // ring of one core) receives the value at every diagonal position and keeps zeros elsewhere (the caller's buffer

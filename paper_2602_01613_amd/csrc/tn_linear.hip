@@ -201,6 +201,10 @@ struct tn_linear_s {
         void *a = nullptr, *b = nullptr;      // packed [S][F1 padded], [S][F2]
         tn::GradOut out_a, out_b;
     } mgrad_half[2];
+    // both halves' gradients in one pass over dW (bond_grad_kernel), where the bond is narrow
+    bool mgrad_bond = false;
+    int32_t bond_ranges = 0, bond_tiles_per_range = 0;
+    int64_t bond_sums_bytes[2] = {0, 0};      // at the start of bwd_partial
     struct ProfRec { int step; hipEvent_t start, stop; };
     std::vector<ProfRec> prof;
 };
@@ -2195,7 +2199,13 @@ int configure_kernels(int device) {
          hipFuncSetAttribute(reinterpret_cast<const void*>(small_chain_kernel<float>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallChainMaxLds)) != hipSuccess ||
          hipFuncSetAttribute(reinterpret_cast<const void*>(small_chain_kernel<bf16_t>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallChainMaxLds)) != hipSuccess))
+                             hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallChainMaxLds)) != hipSuccess ||
+         hipFuncSetAttribute(reinterpret_cast<const void*>(bond_grad_kernel<1>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, int(BondGradShape<1>::SMEM)) != hipSuccess ||
+         hipFuncSetAttribute(reinterpret_cast<const void*>(bond_grad_kernel<2>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, int(BondGradShape<2>::SMEM)) != hipSuccess ||
+         hipFuncSetAttribute(reinterpret_cast<const void*>(bond_grad_kernel<3>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, int(BondGradShape<3>::SMEM)) != hipSuccess))
         rc = TN_ERR_HIP;
     for (int cfg = 0; cfg < tn::kKronConfigs && rc == TN_OK; ++cfg) rc = kron_dispatch(cfg, nullptr, 0, nullptr);
     if (rc == TN_OK) rc = gen_mfma_dispatch(nullptr, 0, nullptr);
@@ -2593,11 +2603,61 @@ int launch_param_gradient(const tn_linear_s* h, const DevStep& s, const void* dO
 constexpr int64_t kGradMinTokens = 16;        // one token range is padded to 64
 constexpr int kGradSumsPad = 128;             // columns of the core gradients (a bond): padded to the narrow tiles
 
+// bond_grad_kernel takes halves of two cores each over a bond of 32, 64 or 96 (its sums and its operand stay in registers); the columns are cut into as many ranges as
+// leave the least to the busiest compute unit, at least 4 tiles each, the sums within kMaxGradPartialBytes.
+bool plan_bond_grad(tn_linear_s* h, const tn::MatrixPlan& m, const tn::MatrixGrad& g) {
+    const int64_t F0 = m.half[0].F, F1 = m.half[1].F, S = m.Kr;
+    if (!g.half[0].pair || !g.half[1].pair || S % 32 || S > 96 || F0 % 64 || F1 % 64 || F1 > (int64_t(1) << 21) || F0 > (int64_t(1) << 24) ||
+        F0 * F1 > (int64_t(1) << 29))      // 31-bit offsets in bytes
+        return false;
+    const int64_t panels = (F0 + kBondRows - 1) / kBondRows, tiles = F1 / kBondCols;
+    int64_t best = 0;
+    for (int64_t n = 1; n <= 64 && (n == 1 || 4 * n <= tiles); ++n) {
+        const int64_t per = (tiles + n - 1) / n;
+        if ((tiles + per - 1) / per != n) continue;                               // an empty range
+        const int64_t bytes0 = (n * F0 * S * 4 + 255) & ~int64_t(255), bytes1 = (panels * F1 * S * 4 + 255) & ~int64_t(255);
+        if (panels * n >= (int64_t(1) << 31) || bytes0 + bytes1 > kMaxGradPartialBytes) break;
+        // a workgroup's start and end take about 8 tiles' time (4096 columns of 40 panels: 6 ranges 69 us, 32 ranges 95, before dW came in tiles)
+        const int64_t cost = (panels * n + h->num_cus - 1) / h->num_cus * (per + 8);
+        if (best && cost >= best) continue;
+        best = cost;
+        h->bond_ranges = int32_t(n);
+        h->bond_tiles_per_range = int32_t(per);
+        h->bond_sums_bytes[0] = bytes0;
+        h->bond_sums_bytes[1] = bytes1;
+    }
+    return best > 0;
+}
+
+int launch_bond_grad(const tn_linear_s* h, const void* D, const void* P0, const void* P1, int64_t p0_lo, int64_t p1_lo, hipStream_t st) {
+    BondGradArgs a;
+    a.D = D;
+    a.P0 = P0;
+    a.P1 = P1;
+    a.d_lo = h->plan.M * h->plan.N;
+    a.p0_lo = p0_lo;
+    a.p1_lo = p1_lo;
+    a.sums0 = h->bwd_partial;
+    a.sums1 = reinterpret_cast<float*>(reinterpret_cast<char*>(h->bwd_partial) + h->bond_sums_bytes[0]);
+    a.F0 = h->mgrad_f[0];
+    a.F1 = h->mgrad_f[1];
+    a.S = int32_t(h->mgrad_half[0].dh.plan.C);
+    a.tiles = int32_t(a.F1 / kBondCols);
+    a.tiles_per_range = h->bond_tiles_per_range;
+    a.ranges = h->bond_ranges;
+    const dim3 grid(uint32_t((a.F0 + kBondRows - 1) / kBondRows * a.ranges));
+    switch (a.S) {
+        case 32: hipLaunchKernelGGL(bond_grad_kernel<1>, grid, dim3(256), BondGradShape<1>::SMEM, st, a); break;
+        case 64: hipLaunchKernelGGL(bond_grad_kernel<2>, grid, dim3(256), BondGradShape<2>::SMEM, st, a); break;
+        default: hipLaunchKernelGGL(bond_grad_kernel<3>, grid, dim3(256), BondGradShape<3>::SMEM, st, a); break;
+    }
+    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
+}
+
 // Decide whether gradients of many tokens go through dW, and prepare it. dW and dH are sums over the tokens and the products of
 // two cores meet such a sum: they are kept in two parts each, as the caller gets fp32 (in one
 // part, core gradients of the rank-64 train 5120 -> 8192 at 1024 tokens with a common component are 2.9e-3 off in the 2-norm, in
-// two 5e-6; the steps, whose roundings average out over the tokens, leave 0.9 to 1.8e-4. The train's fine-tuning step takes 642 us,
-// with one part 525). The steps are priced at 0.35e9 FLOP per us and 40 us
+// two 5e-6; the steps, whose roundings average out over the tokens, leave 0.9 to 1.8e-4). The steps are priced at 0.35e9 FLOP per us and 40 us
 // a step (train 5120 -> 8192 of rank 64: 9.7 ms at 1024 tokens; ring 25600 -> 5120 of rank 32: 12.5 ms at 64).
 int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     const int64_t M = h->plan.M, N = h->plan.N;
@@ -2609,7 +2669,15 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
     if (dense && (desc->flags & TN_FLAG_TRANSPOSE)) return TN_OK;
     const tn::MatrixPlan& m = h->matrix_plans.m;
     tn::MatrixGrad g;
-    if (!dense && (!matrix_plan_of(h, desc) || !tn::make_matrix_grad(h->matrix_plans.net, m, &g))) return TN_OK;
+    if (!dense) {
+        if (!matrix_plan_of(h, desc)) return TN_OK;
+        // dW in tiles where one pass over it gives both halves' gradients, as a matrix for the products
+        h->mgrad_bond = tn::make_matrix_grad(h->matrix_plans.net, m, &g, true) && g.tiled && plan_bond_grad(h, m, g);
+        if (!h->mgrad_bond) {
+            g = tn::MatrixGrad();
+            if (!tn::make_matrix_grad(h->matrix_plans.net, m, &g)) return TN_OK;
+        }
+    }
     auto step = [&](DevStep* s, int64_t R, int64_t K, int64_t C, int64_t out_elems, int pad) {
         s->plan.R = R;
         s->plan.K = K;
@@ -2632,9 +2700,11 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
     int64_t sums = 0;
     if (!dense) {
         room(2, M * N);
-        room(3, M * N);
+        if (!h->mgrad_bond) room(3, M * N);
         h->mgrad_dw.out_lo = M * N;
-        us += 6.f + float(M * N) * 8.f / 3.5e6f;
+        if (h->mgrad_bond)      // 51 us and 17 for the two launches that add the sums, of 168 MB in two parts and 59 MB of sums
+            us += 12.f + float(M * N) * 4.f / 3.6e6f + float(h->bond_sums_bytes[0] + h->bond_sums_bytes[1]) / 5e6f;
+        else us += 6.f + float(M * N) * 8.f / 3.5e6f;
         int64_t dh = 0, dht = 0;
         for (int i = 0; i < 2; ++i) {
             const tn::MatrixGradHalf& G = g.half[i];
@@ -2651,7 +2721,7 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
             H.dh.a_lo = M * N;
             H.dh.b_lo = g.half[1 - i].pair ? g.half[1 - i].op.out_elems : 0;
             H.dh.out_lo = G.pair ? F * m.Kr : 0;
-            us += 3.f + std::max(gemm_choice(h, H.dh, F, kMaxGradPartialBytes).us, float(F * (Fo + m.Kr)) * 4.f / 3.5e6f);
+            if (!h->mgrad_bond) us += 3.f + std::max(gemm_choice(h, H.dh, F, kMaxGradPartialBytes).us, float(F * (Fo + m.Kr)) * 4.f / 3.5e6f);
             h->mgrad_flops += 2 * F * Fo * m.Kr * H.dh.segments();
             if (!G.pair) {
                 sums = std::max(sums, F * H.dh.Cp * 4);
@@ -2739,7 +2809,7 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
     h->bwd_ws_bytes = h->mgrad_off[1] + chunk * y_row;
     if (dense) sums = M * h->mgrad_dw.Cp * 4;
     else sums = std::max(sums, std::min(kMaxGradPartialBytes, std::max(4 * sums, kMaxPartialBytes)));
-    h->bwd_partial_bytes = sums;
+    h->bwd_partial_bytes = sums + (h->mgrad_bond ? h->bond_sums_bytes[0] + h->bond_sums_bytes[1] : 0);
     return TN_OK;
 }
 
@@ -2764,8 +2834,10 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
     auto at = [&](int i) -> void* { return base + h->mgrad_off[i]; };
     const bool dense = h->plan.format == TN_FORMAT_DENSE;
     const int64_t M = h->plan.M, N = h->plan.N;
-    void* part = h->bwd_partial;
-    const int64_t part_bytes = h->bwd_partial_bytes;
+    // the sums of bond_grad_kernel come first, those of the products behind them
+    const int64_t bond_bytes = h->mgrad_bond ? h->bond_sums_bytes[0] + h->bond_sums_bytes[1] : 0;
+    void* part = reinterpret_cast<char*>(h->bwd_partial) + bond_bytes;
+    const int64_t part_bytes = h->bwd_partial_bytes - bond_bytes;
     bool wanted[2] = {false, false};
     for (int i = 0; i < 2 && !dense; ++i) {
         const auto& H = h->mgrad_half[i];
@@ -2773,7 +2845,7 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
     }
     if (dense ? !grads[0] : !(wanted[0] || wanted[1])) return TN_OK;
     for (int i = 0; i < 2 && !dense; ++i)
-        if (wanted[1 - i] && h->mgrad_half[i].pair) {
+        if ((wanted[1 - i] || h->mgrad_bond) && h->mgrad_half[i].pair) {
             const int rc = launch_product_of(h, h->mgrad_half[i].op.s, h->mgrad_half[i].op.a, h->mgrad_half[i].op.s.packed, at(4 + i), part,
                                              part_bytes, st);
             if (rc != TN_OK) return rc;
@@ -2809,12 +2881,18 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
             for (int part = 0; part < 2; ++part)
                 launch_transpose(static_cast<char*>(at(from)) + part * r * c * 2, static_cast<char*>(at(to)) + part * c * rp * 2, r, c, rp, false, st);
         };
-        if (wanted[1]) transpose_parts(2, 3, h->mgrad_f[0], h->mgrad_f[1], h->mgrad_f[0]);
+        auto operand = [&](int i) -> const void* { return h->mgrad_half[i].pair ? at(4 + i) : h->mgrad_half[i].op.s.packed; };
+        if (h->mgrad_bond) {
+            // how far the low part of the operand made of a half is: known to the step that it is the column operand of
+            rc = launch_bond_grad(h, at(2), operand(0), operand(1), h->mgrad_half[1].dh.b_lo, h->mgrad_half[0].dh.b_lo, st);
+            if (rc != TN_OK) return rc;
+        } else if (wanted[1]) {
+            transpose_parts(2, 3, h->mgrad_f[0], h->mgrad_f[1], h->mgrad_f[0]);
+        }
         for (int i = 0; i < 2; ++i) {
             if (!wanted[i]) continue;
             const auto& H = h->mgrad_half[i];
-            const auto& O = h->mgrad_half[1 - i];
-            const void* op = O.pair ? at(4 + 1 - i) : O.op.s.packed;
+            const void* op = operand(1 - i);
             if (!H.pair) {
                 GemmSums f;
                 rc = launch_product_of(h, H.dh, at(2 + i), op, nullptr, part, part_bytes, st, &f);
@@ -2822,7 +2900,22 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
                 if (rc != TN_OK) return rc;
                 continue;
             }
-            rc = launch_product_of(h, H.dh, at(2 + i), op, at(6), part, part_bytes, st);
+            if (h->mgrad_bond) {
+                // the sums of its ranges or row panels, in place and in two parts
+                StepArgs r{};
+                r.Out = at(6);
+                r.crow = H.dh.crow;
+                r.ccol = H.dh.ccol;
+                r.total_rows = r.R = uint32_t(h->mgrad_f[i]);
+                r.C = r.Cp = int32_t(H.dh.plan.C);
+                const int64_t total = h->mgrad_f[i] * H.dh.plan.C;
+                const char* sums = reinterpret_cast<const char*>(h->bwd_partial) + (i ? h->bond_sums_bytes[0] : 0);
+                hipLaunchKernelGGL(step_split_reduce_parts_kernel, dim3(uint32_t(std::min<int64_t>((total + 255) / 256, 8192))), dim3(256), 0, st, r,
+                                   reinterpret_cast<const float*>(sums), i ? int((h->mgrad_f[0] + kBondRows - 1) / kBondRows) : h->bond_ranges, r.R,
+                                   H.dh.out_lo);
+            } else {
+                rc = launch_product_of(h, H.dh, at(2 + i), op, at(6), part, part_bytes, st);
+            }
             if (rc != TN_OK) return rc;
             for (int side = 0; side < 2; ++side) {
                 float* grad = static_cast<float*>(grads[side == 0 ? H.out_a.slot : H.out_b.slot]);

@@ -329,7 +329,8 @@ struct MatrixGradHalf {
 };
 
 struct MatrixGrad {
-    std::vector<int32_t> dw_row, dw_col;   // dW [m][n] -> [F of half 0][F of half 1]
+    std::vector<int32_t> dw_row, dw_col;   // dW [m][n] -> [F of half 0][F of half 1], or with
+    bool tiled = false;                    // -> [F of half 1 / 32][F of half 0][32]
     MatrixGradHalf half[2];
 };
 
@@ -369,7 +370,7 @@ inline std::vector<GatherDim> grad_dims(const Plan& p, int tensor, const std::ve
 }  // namespace detail
 
 // False where a layout does not come out in runs of 8 or in whole tiles of k.
-inline bool make_matrix_grad(const Plan& net, const MatrixPlan& m, MatrixGrad* g) {
+inline bool make_matrix_grad(const Plan& net, const MatrixPlan& m, MatrixGrad* g, bool want_tiled = false) {
     using namespace detail;
     int last_n = -1;
     for (int i : net.x_idx)
@@ -410,6 +411,24 @@ inline bool make_matrix_grad(const Plan& net, const MatrixPlan& m, MatrixGrad* g
                 weight *= net.extent[size_t(ids[i])];
             }
         }
+    }
+    if (want_tiled) {
+        // a sum of one offset per digit where the digits' parts below 32 never carry
+        int64_t below = 0;
+        std::vector<int> inner;
+        for (int n : number[1])
+            for (int i : md.spell({n})) inner.push_back(i);
+        for (int i : inner) {
+            int64_t most = 0;
+            for (int64_t v : wt[i]) most = std::max(most, v % 32);
+            below += most;
+        }
+        g->tiled = m.half[1].F % 32 == 0 && below < 32;
+        if (g->tiled)
+            for (auto& d : wt) {
+                const bool in = contains(inner, d.first);
+                for (int64_t& v : d.second) v = in ? v / 32 * m.half[0].F * 32 + v % 32 : v / m.half[1].F * 32;
+            }
     }
     g->dw_row = digit_table(net.y_idx, net.extent, wt);
     g->dw_col = digit_table(net.x_idx, net.extent, wt);

@@ -117,3 +117,27 @@ def test_param_gradients_random_layers(seed):
     for tokens in (3, 70):
         errs = _check(spec, ts, tokens, 99500 + seed * 3 + tokens)
         assert max(errs) <= GRAD_TOL["bf16"], (seed, tokens, errs)
+
+
+@pytest.mark.parametrize("rank", [32, 64, 96])
+@pytest.mark.parametrize("om,im", [((8, 10, 8, 8), (8, 16, 8, 8)),        # halves of several row panels and of whole tiles
+                                   ((4, 4, 8, 8), (4, 4, 4, 8)),          # 256 rows (or less) against more columns
+                                   ((4, 5, 8, 8), (4, 4, 4, 8)),          # a last panel of 64 rows
+                                   ((8, 10, 8, 8), (4, 4, 3, 16)),        # 1280 rows, 96 tiles of columns, modes of no power of two
+                                   ((10, 16, 8, 8), (8, 8))])             # halves of one core: as two products
+def test_param_gradients_through_a_narrow_bond(om, im, rank):
+    """Trains whose two halves' gradients come from one pass over dW (bonds of 32, 64 and 96), at the edges of its row panels and column
+    ranges. dW and the halves are kept to 2^-16, the sums in fp32: 2^-13 of the largest value allows for three such steps."""
+    if len(im) == 2:
+        om, im = (om[0] * om[1], om[2] * om[3]), im
+    spec = wl.TNSpec(tn.TN_FORMAT_TT, "bf16", om, im, (1,) + tuple(rank if k == len(om) // 2 else min(rank, 32) for k in range(1, len(om))) + (1,))
+    rng = np.random.default_rng(rank + spec.M)
+    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(s[0] * s[2]), "bf16") for s in spec.tensor_shapes()]
+    tokens = 1000
+    layer = make_layer(spec, ts, tokens, flags=tn.TN_FLAG_TRAINABLE)
+    through_dw = 0 < layer.query(tn.TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS) <= tokens
+    layer.close()
+    assert through_dw or len(im) == 2
+    errs = _check(spec, ts, tokens, 41 + tokens)
+    # (step by step, which the library may price lower for the smallest: the suite's tolerance)
+    assert max(errs) <= (2.0 ** -13 if through_dw else GRAD_TOL["bf16"]), errs
