@@ -82,6 +82,9 @@ __global__ void __launch_bounds__(256) step_scalar_kernel(StepArgs a) {
 //   AMODE 0: A rows are plain and K % 8 == 0 -> 16-byte global loads
 //   AMODE 1: element-wise gather (tables, or K not a multiple of 8)
 //   AMODE 2 (step_mfma_pipe_kernel only): rows through the tables, the k of a row in aligned contiguous runs of 8
+//   AMODE 3 (step_mfma_pipe_kernel only): the rows of a k in aligned contiguous runs of 8 (R % 8 == 0), through the tables: a
+//           thread loads 8 rows x 8 k as 8 such pieces, whole lines per k, and turns them round in registers. Element by element
+//           the input gradient of a Tucker out-factor (500 x 96 rows, K = 160, 96 columns) took 69 us, 21 here
 //            (tn::Step::a_vec): 16-byte loads at arow[r] + acol[k]
 //   CMODE 0: scalar stores; 1: 8 contiguous columns per store; 2: 8 contiguous rows per store
 // ---------------------------------------------------------------------------------------------
@@ -303,8 +306,16 @@ step_mfma_pipe_kernel(StepArgs a, int cmode, int nrow_tiles, int ncol_tiles) {
 
     // A addressing: AMODE 0 -> one pointer, rows 32*j apart; AMODE 1 -> per-row element offsets
     const bf16_t* a_ptr = A + int64_t(row0 + lrow) * a.K + lkc;
-    int64_t a_base[AMODE != 0 ? A_CHUNKS : 1];
-    if (AMODE != 0) {
+    int64_t a_base[AMODE == 1 || AMODE == 2 ? A_CHUNKS : 1];
+    // AMODE 3: this thread's block of 8 rows and 8 k
+    constexpr int RGS = BM / 8;
+    const int tr8 = (tid % RGS) * 8, tk8 = (tid / RGS) * 8;
+    static_assert(AMODE != 3 || (A_CHUNKS == 8 && NT / RGS == 8), "a block of 8 x 8 per thread");
+    if (AMODE == 3) {
+        const uint32_t g = row0 + tr8, t = g / a.R;
+        a_base[0] = g < a.total_rows ? int64_t(t) * a.a_tok_stride + a.arow[g - t * a.R] : -1;
+    }
+    if (AMODE == 1 || AMODE == 2) {
 #pragma unroll
         for (int j = 0; j < A_CHUNKS; ++j) {
             uint32_t g = row0 + lrow + RPP * j;
@@ -332,6 +343,8 @@ step_mfma_pipe_kernel(StepArgs a, int cmode, int nrow_tiles, int ncol_tiles) {
             if (AMODE == 0) {
                 if (row0 + lrow + RPP * j < a.total_rows && k < a.K)
                     v = *reinterpret_cast<const bf16x8*>(a_ptr + int64_t(RPP * j) * a.K + k0);
+            } else if (AMODE == 3) {
+                if (a_base[0] >= 0 && k0 + tk8 + j < a.K) v = *reinterpret_cast<const bf16x8*>(A + a_base[0] + a.acol[k0 + tk8 + j]);
             } else if (AMODE == 2) {
                 if (a_base[j] >= 0 && k < a.K) v = *reinterpret_cast<const bf16x8*>(A + a_base[j] + a.acol[k]);
             } else if (a_base[j] >= 0) {
@@ -352,8 +365,16 @@ step_mfma_pipe_kernel(StepArgs a, int cmode, int nrow_tiles, int ncol_tiles) {
         bf16_t* sA = smem + stage * STAGE_ELEMS;
         bf16_t* sB = sA + A_ELEMS;
 #pragma unroll
-        for (int j = 0; j < A_CHUNKS; ++j)
-            *reinterpret_cast<bf16x8*>(sA + (lrow + RPP * j) * LDK + lkc) = ra[j];
+        for (int j = 0; j < A_CHUNKS; ++j) {
+            if (AMODE == 3) {
+                bf16x8 v;
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v[q] = ra[q][j];
+                *reinterpret_cast<bf16x8*>(sA + (tr8 + j) * LDK + tk8) = v;
+            } else {
+                *reinterpret_cast<bf16x8*>(sA + (lrow + RPP * j) * LDK + lkc) = ra[j];
+            }
+        }
 #pragma unroll
         for (int j = 0; j < B_CHUNKS; ++j) {
             int blk = (tid >> 6) + (NT / 64) * j;

@@ -311,7 +311,7 @@ void choose_variant(const tn_linear_s* h, DevStep* s, int flags) {
         }
     }
     // 0: plain rows of 16-byte pieces; 2: gathered rows of 16-byte pieces (the tiled pipeline kernel; every other kernel
-    // reads such a step element by element, like 1); 1: element-wise gather
+    // reads such a step element by element, like 1); 1: element-wise gather; 3: 16-byte pieces along the rows (prepare_backward)
     s->amode = (p.a_plain && p.K % 8 == 0) ? 0 : (p.a_vec == 8 ? 2 : 1);
     s->cmode = p.c_vec == 8 ? 1 : (p.r_vec == 8 ? 2 : 0);
     s->Kp = round_up(int(p.K), 64);
@@ -443,10 +443,12 @@ int launch_pipe(const DevStep& s, const StepArgs& a, int64_t rows, hipStream_t s
     int nrow_pad = (nrow + 7) / 8 * 8;
     dim3 grid(uint32_t(nrow_pad) * uint32_t(ncol));
     using kern_t = void (*)(StepArgs, int, int, int);
-    static const kern_t kerns[6] = {
+    constexpr int ROWS = BM == 256 ? 3 : 1;            // the mode of row runs where a thread has a block of 8 x 8 of the tile
+    static const kern_t kerns[8] = {
         step_mfma_pipe_kernel<WM, WN, TM, TN, 0, STAGES, MINB, 0>, step_mfma_pipe_kernel<WM, WN, TM, TN, 1, STAGES, MINB, 0>,
-        step_mfma_pipe_kernel<WM, WN, TM, TN, 2, STAGES, MINB, 0>, step_mfma_pipe_kernel<WM, WN, TM, TN, 0, STAGES, MINB, 1>,
-        step_mfma_pipe_kernel<WM, WN, TM, TN, 1, STAGES, MINB, 1>, step_mfma_pipe_kernel<WM, WN, TM, TN, 2, STAGES, MINB, 1>};
+        step_mfma_pipe_kernel<WM, WN, TM, TN, 2, STAGES, MINB, 0>, step_mfma_pipe_kernel<WM, WN, TM, TN, ROWS, STAGES, MINB, 0>,
+        step_mfma_pipe_kernel<WM, WN, TM, TN, 0, STAGES, MINB, 1>, step_mfma_pipe_kernel<WM, WN, TM, TN, 1, STAGES, MINB, 1>,
+        step_mfma_pipe_kernel<WM, WN, TM, TN, 2, STAGES, MINB, 1>, step_mfma_pipe_kernel<WM, WN, TM, TN, ROWS, STAGES, MINB, 1>};
     if (!s.packed) {                       // configuration call (create time): raise the kernels' LDS limit
         for (kern_t k : kerns)
             if (hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -454,7 +456,7 @@ int launch_pipe(const DevStep& s, const StepArgs& a, int64_t rows, hipStream_t s
                 return TN_ERR_HIP;
         return TN_OK;
     }
-    kern_t k = kerns[(s.cmode == 2 ? 3 : 0) + s.amode];
+    kern_t k = kerns[(s.cmode == 2 ? 4 : 0) + s.amode];
     hipLaunchKernelGGL(k, grid, dim3(WM * WN * 64), smem, st, a, s.cmode, nrow, ncol);
     return TN_OK;
 }
@@ -2454,6 +2456,16 @@ int prepare_backward(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st)
         b.crow = h->bwd_tables + off[s];
         b.ccol = b.crow + f.R;
         choose_variant(h, &b, desc->flags);
+        // dOut's rows in 16-byte runs (the forward step's output runs along them): the tile of 256 rows turns them round as it loads
+        // them, and no other kernel can; 128 columns at a time cost a second read of dOut, from L2, where there are more
+        if (b.amode == 1 && f.r_vec == 8 && f.R % 8 == 0 && f.c_tok_stride % 8 == 0 &&
+            (b.variant == VAR_PIPE_128x256 || b.variant == VAR_PIPE_256x128) && ((desc->flags >> TN_FLAG_VARIANT_SHIFT) & 0xff) == 0) {
+            b.variant = VAR_PIPE_256x128;
+            b.amode = 3;
+            b.bm = 256;
+            b.bn = 128;
+            b.Cp = round_up(int(b.plan.C), 128);
+        }
         const int64_t bytes = int64_t(b.Cp) * b.Kp * h->elt;
         if (hipMalloc(&b.packed, size_t(bytes)) != hipSuccess) return TN_ERR_ALLOC;
         h->packed_bytes += bytes;

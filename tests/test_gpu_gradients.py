@@ -141,3 +141,16 @@ def test_param_gradients_through_a_narrow_bond(om, im, rank):
     errs = _check(spec, ts, tokens, 41 + tokens)
     # (step by step, which the library may price lower for the smallest: the suite's tolerance)
     assert max(errs) <= (2.0 ** -13 if through_dw else GRAD_TOL["bf16"]), errs
+
+
+@pytest.mark.parametrize("om,im,rk", [((40, 72), (24, 16), (40, 64, 16, 16)), ((72, 160), (24, 16), (72, 136, 8, 16)), ((264, 48), (16, 16), (40, 48, 16, 8)),
+                                      ((33, 40), (16, 24), (33, 40, 16, 16)), ((40, 33), (16, 24), (40, 33, 16, 16))])
+def test_input_gradients_along_row_runs(om, im, rk):
+    """Tucker layers whose out-factor steps read the output's gradient in runs along its rows: K below, at and above a tile of 64, one
+    and two tiles of 128 columns, rows that end inside a tile of 256, and extents that allow no such runs."""
+    spec = wl.TNSpec(tn.TN_FORMAT_TUCKER, "bf16", om, im, rk)
+    rng = np.random.default_rng(sum(om) + rk[1])
+    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(max(1, s[-1])), "bf16") for s in spec.tensor_shapes()]
+    for tokens in (40, 333):
+        errs = _check(spec, ts, tokens, 51 + tokens)
+        assert max(errs) <= GRAD_TOL["bf16"], (tokens, errs)
