@@ -63,9 +63,12 @@ struct GemmShape {
 //               of v. With low parts the K tiles are walked two or three times, (A, B), (A low, B), (A, B low), into the same
 //               sums, which is the fp32 product but for terms of 2^-16: sums over tokens have to pass through here without
 //               losing what averaging over the tokens gained.
+//   GEMM_SHORT  K of one or two tiles, NS of them: bound by the stores and by how many workgroups have theirs under way, so as
+//               little as possible is held by one. Every K tile has its stage and all are loaded at once, one set of
+//               fragments: 36 KB of LDS (one tile) and 118 registers at 160 x 128, three or four workgroups on a CU instead of two.
 //   GEMM_ANY    K % 8 == 0: B holds zeros from K to whole tiles, and chunks of A past it read as zeros; and outputs in neither
 //               kind of piece (TRANS = 1, scalar_out): one value at a time, 16 neighbouring columns per store.
-enum GemmForm : int { GEMM_PLAIN = 1, GEMM_PARTS = 2, GEMM_ANY = 3 };
+enum GemmForm : int { GEMM_PLAIN = 1, GEMM_PARTS = 2, GEMM_ANY = 3, GEMM_SHORT = 4 };
 
 template <typename F, int... Q>
 __device__ __forceinline__ void for_constants(F&& f, std::integer_sequence<int, Q...>) {
@@ -73,7 +76,7 @@ __device__ __forceinline__ void for_constants(F&& f, std::integer_sequence<int, 
 }
 
 template <int TM, int TN, int NS, int TRANS, int FORM = GEMM_PLAIN>
-__global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs g) {
+__global__ void __launch_bounds__(256, FORM == GEMM_SHORT ? 3 : 1) step_gemm_kernel(StepArgs a, GemmArgs g) {
 #ifdef __HIP_DEVICE_COMPILE__
     using S = GemmShape<TM, TN, NS>;
     constexpr int NW = 4, BM = S::BM, BN = S::BN, STAGE = S::STAGE_BYTES, A_BYTES = BM * 128;
@@ -162,12 +165,19 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
     constexpr int RS = NM * 3 / 4 / NR > 1 ? NM * 3 / 4 / NR : 1, BAR = RS * NR + 4 < NM ? RS * NR + 4 : NM;
     constexpr int SPAN = NS > 2 ? 2 * NM : 2 * NM - BAR;
     constexpr int L_NOW = NS > 2 ? ((2 * NM - BAR) * L + SPAN - 1) / SPAN : L;      // loads l with BAR + l * SPAN / L < 2 * NM
-    static_assert(L_NOW <= L && BAR + (L_NOW - 1) * SPAN / L < 2 * NM && (L_NOW == L || BAR + L_NOW * SPAN / L >= 2 * NM), "load slots");
+    static_assert(FORM == GEMM_SHORT || (L_NOW <= L && BAR + (L_NOW - 1) * SPAN / L < 2 * NM && (L_NOW == L || BAR + L_NOW * SPAN / L >= 2 * NM)), "load slots");
+    if constexpr (FORM == GEMM_SHORT) {
 #pragma unroll
-    for (int q = 0; q < NS; ++q) {
-        if (FORM == GEMM_ANY && nk == q + 1) va = va_last;
+        for (int q = 0; q < NS; ++q)
 #pragma unroll
-        for (int l = 0; l < (q == NS - 1 ? L_NOW : L); ++l) load1(l, q, past(q), dyn_smem + q * STAGE);
+            for (int l = 0; l < L; ++l) load1(l, q, 0, dyn_smem + q * STAGE);
+    } else {
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            if (FORM == GEMM_ANY && nk == q + 1) va = va_last;
+#pragma unroll
+            for (int l = 0; l < (q == NS - 1 ? L_NOW : L); ++l) load1(l, q, past(q), dyn_smem + q * STAGE);
+        }
     }
 
     // fragments: lane l supplies row (A) or column (B) l%16 and k = 32*ks + 8*(l/16) .. +7
@@ -192,50 +202,70 @@ __global__ void __launch_bounds__(256, 1) step_gemm_kernel(StepArgs a, GemmArgs 
             for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
             asm volatile("" : "+a"(acc[i][j]));
         }
-    wait_vmcnt<(NS - 2) * L + L_NOW>();                  // the tables and the first K tile have landed
-    __builtin_amdgcn_s_barrier();
+    if constexpr (FORM == GEMM_SHORT) {
 #pragma unroll
-    for (int q = 0; q < NR; ++q) read1(q, 0, dyn_smem, 0);
-    int at = 0, at_prev = (NS - 1) * STAGE;              // byte offsets of this tile's stage and of the one before
-    for (int kt = 0; kt < nk; ++kt) {
-        unsigned char *s = dyn_smem + at, *sp = dyn_smem + at_prev;
-        at_prev = at;
-        at = at == (NS - 1) * STAGE ? 0 : at + STAGE;
-        const unsigned char* sn = dyn_smem + at;
-        const int off_prev = past(kt + NS - 1), off = past(kt + NS);
-        __builtin_amdgcn_sched_barrier(0);
-        // (slots as compile-time constants: as a loop, 128 of them are not unrolled in time to keep the fragments in registers)
-        auto slot = [&](auto slot_index) {
-            constexpr int q = decltype(slot_index)::value, half = q / NM, m = q % NM, i = m / TN, j = m % TN;
-            if constexpr (q == BAR) {
-                __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): this wave has read the whole stage
-                wait_vmcnt<(NS - 2) * L>();              // its loads of the next stage have landed
-                __builtin_amdgcn_s_barrier();
-                if (FORM == GEMM_ANY && kt + NS + 1 == nk) va = va_last;
+        for (int kt = 0; kt < NS; ++kt) {
+            if (kt + 1 < NS) wait_vmcnt<(NS - 1) * L>();
+            else wait_vmcnt<0>();
+            __builtin_amdgcn_s_barrier();
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+                for (int q = 0; q < NR; ++q) read1(q, 0, dyn_smem + kt * STAGE, ks);
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+                        acc[i][j] = TRANS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[0][i], fb[0][j], acc[i][j], 0, 0, 0)
+                                          : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[0][j], fa[0][i], acc[i][j], 0, 0, 0);
+            }
+        }
+    } else {
+        wait_vmcnt<(NS - 2) * L + L_NOW>();                  // the tables and the first K tile have landed
+        __builtin_amdgcn_s_barrier();
+#pragma unroll
+        for (int q = 0; q < NR; ++q) read1(q, 0, dyn_smem, 0);
+        int at = 0, at_prev = (NS - 1) * STAGE;              // byte offsets of this tile's stage and of the one before
+        for (int kt = 0; kt < nk; ++kt) {
+            unsigned char *s = dyn_smem + at, *sp = dyn_smem + at_prev;
+            at_prev = at;
+            at = at == (NS - 1) * STAGE ? 0 : at + STAGE;
+            const unsigned char* sn = dyn_smem + at;
+            const int off_prev = past(kt + NS - 1), off = past(kt + NS);
+            __builtin_amdgcn_sched_barrier(0);
+            // (slots as compile-time constants: as a loop, 128 of them are not unrolled in time to keep the fragments in registers)
+            auto slot = [&](auto slot_index) {
+                constexpr int q = decltype(slot_index)::value, half = q / NM, m = q % NM, i = m / TN, j = m % TN;
+                if constexpr (q == BAR) {
+                    __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): this wave has read the whole stage
+                    wait_vmcnt<(NS - 2) * L>();              // its loads of the next stage have landed
+                    __builtin_amdgcn_s_barrier();
+                    if (FORM == GEMM_ANY && kt + NS + 1 == nk) va = va_last;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                acc[i][j] = TRANS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[half][i], fb[half][j], acc[i][j], 0, 0, 0)
+                                  : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[half][j], fa[half][i], acc[i][j], 0, 0, 0);
                 __builtin_amdgcn_sched_barrier(0);
-            }
-            acc[i][j] = TRANS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[half][i], fb[half][j], acc[i][j], 0, 0, 0)
-                              : __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[half][j], fa[half][i], acc[i][j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            if constexpr (m % RS == 0 && m / RS < NR) read1(m / RS, half ^ 1, half ? sn : s, half ^ 1);
-            if constexpr (NR > NM && m == NM - 1) {
+                if constexpr (m % RS == 0 && m / RS < NR) read1(m / RS, half ^ 1, half ? sn : s, half ^ 1);
+                if constexpr (NR > NM && m == NM - 1) {
 #pragma unroll
-                for (int r = NM; r < NR; ++r) read1(r, half ^ 1, half ? sn : s, half ^ 1);
-            }
+                    for (int r = NM; r < NR; ++r) read1(r, half ^ 1, half ? sn : s, half ^ 1);
+                }
 #pragma unroll
-            for (int l = 0; l < L_NOW; ++l)
-                if (BAR + l * SPAN / L == q) load1(l, kt + NS, off, s);
+                for (int l = 0; l < L_NOW; ++l)
+                    if (BAR + l * SPAN / L == q) load1(l, kt + NS, off, s);
 #pragma unroll
-            for (int l = L_NOW; l < L; ++l)
-                if (BAR + l * SPAN / L == q + 2 * NM) load1(l, kt + NS - 1, off_prev, sp);
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        for_constants(slot, std::make_integer_sequence<int, 2 * NM>());
-        // keep the accumulators in the accumulation registers across the back edge
+                for (int l = L_NOW; l < L; ++l)
+                    if (BAR + l * SPAN / L == q + 2 * NM) load1(l, kt + NS - 1, off_prev, sp);
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            for_constants(slot, std::make_integer_sequence<int, 2 * NM>());
+            // keep the accumulators in the accumulation registers across the back edge
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+                for (int j = 0; j < TN; ++j) asm volatile("" : "+a"(acc[i][j]));
+        }
     }
     wait_vmcnt<0>();                                     // no load into LDS outlives the workgroup
 

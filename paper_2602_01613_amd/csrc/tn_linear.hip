@@ -495,13 +495,20 @@ constexpr int64_t kGemmMinRows = 65;        // up to 64 rows the launch is a str
 constexpr float kGemmPartialBytesPerUs = 5e6f;    // partial sums, written and read back, and the launch that adds them:
 constexpr float kGemmReduceUs = 3.f;
 
+// Tile of the form for K of one or two tiles (GEMM_SHORT), us per tile and the least it takes: 10240 x 4096 x 64 22.2 us (27.3 on the tiles
+// above), 4096 x 23040 x 128 70 (74), 5120 x 25600 x 128 76 (84), 7168 x 5120 x 128 24.5 (31.6). 128 x 128 tiles take 21.6, 68, 77 and 25.5, 64 x 128 24.6, 74,
+// 84 and 28.
+constexpr int kGemmShortTm = 5, kGemmShortTn = 4;
+constexpr float kGemmShortUs[2] = {0.009f, 0.0115f}, kGemmShortLeastUs[2] = {4.4f, 5.2f};
+
 // A column operand above this passes through the caches once per band of four row tiles: 33 us for 262 MB, which tiles of 256 x 256
 // hide and smaller ones less (4000 x 25600 x 5120: tiles of 256 rows 808 us, of 224 865, of 192 887, of 160 934; their K tiles alone
 // 817, 805, 779, 764). One band and its remainder overlap (600 x 25600 x 5120: five tiles of 128 rows 157 us, four of 160 181).
 constexpr float kGemmCachedBytes = 128e6f;
 
 // The tile size and the number of K ranges with the least time for `rows` rows; partial sums within `cap` bytes.
-GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int64_t cap) {
+// `brief`: the form for K of one or two tiles may be taken (tile = kGemmTiles).
+GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int64_t cap, bool brief = false) {
     GemmChoice best;
     const int nk = s.Kp / 64 * s.segments();
     const bool trans = s.cmode != 1;
@@ -544,6 +551,16 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
             }
         }
     }
+    if (brief && !trans && nk <= 2 && uint32_t(s.Cp) % uint32_t(32 * kGemmShortTn) == 0) {
+        const int64_t tiles = ((rows + 32 * kGemmShortTm - 1) / (32 * kGemmShortTm)) * ((s.plan.C + 32 * kGemmShortTn - 1) / (32 * kGemmShortTn));
+        const float us = std::max(float(tiles) * kGemmShortUs[nk - 1] * 256.f / float(h->num_cus), kGemmShortLeastUs[nk - 1]);
+        if (tiles <= (int64_t(1) << 26) && (best.tile < 0 || us < best.us)) {
+            best = GemmChoice();
+            best.us = us;
+            best.tile = kGemmTiles;
+            best.ktiles_per_split = nk;
+        }
+    }
     return best;
 }
 
@@ -573,6 +590,11 @@ gemm_kern_t gemm_kernel(int tile, bool trans, int form) {
     if (form == GEMM_ANY) return trans ? gemm_kernel_at<1, GEMM_ANY>(tile, seq()) : gemm_kernel_at<0, GEMM_ANY>(tile, seq());
     return trans ? gemm_kernel_at<1, GEMM_PLAIN>(tile, seq()) : gemm_kernel_at<0, GEMM_PLAIN>(tile, seq());
 }
+gemm_kern_t gemm_short_kernel(int nk) {
+    return nk == 1 ? step_gemm_kernel<kGemmShortTm, kGemmShortTn, 1, 0, GEMM_SHORT> : step_gemm_kernel<kGemmShortTm, kGemmShortTn, 2, 0, GEMM_SHORT>;
+}
+size_t gemm_short_smem(int nk) { return nk == 1 ? GemmShape<kGemmShortTm, kGemmShortTn, 1>::SMEM : GemmShape<kGemmShortTm, kGemmShortTn, 2>::SMEM; }
+
 size_t gemm_smem(int tile) { return gemm_smem_at(tile, std::make_integer_sequence<int, kGemmTiles>()); }
 
 int configure_gemm() {
@@ -583,6 +605,10 @@ int configure_gemm() {
                                          int(gemm_smem(t))) != hipSuccess)
                 return TN_ERR_HIP;
         }
+    for (int nk = 1; nk <= 2; ++nk)
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_short_kernel(nk)), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                int(gemm_short_smem(nk))) != hipSuccess)
+            return TN_ERR_HIP;
     return TN_OK;
 }
 
@@ -603,10 +629,11 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
                 hipStream_t st, GemmSums* f32 = nullptr) {
     const bool trans = s.cmode != 1;
     const bool one_range = (h->flags & TN_FLAG_NO_SPLIT_K) || !partial || (f32 && f32->sums);
-    const GemmChoice c = gemm_choice(h, s, rows, one_range ? 0 : partial_bytes);
+    const int form = s.a_lo || s.b_lo || s.out_lo ? GEMM_PARTS : (a.K % 64 || s.cmode == 0 ? GEMM_ANY : GEMM_PLAIN);
+    const GemmChoice c = gemm_choice(h, s, rows, one_range ? 0 : partial_bytes, form == GEMM_PLAIN && !f32);
     if (c.tile < 0 || (trans && (s.a_lo || s.b_lo || s.out_lo))) return TN_ERR_UNSUPPORTED;
     if (f32 && !f32->sums && (!partial || int64_t(c.n_split) * rows * s.Cp * 4 > partial_bytes)) return TN_ERR_UNSUPPORTED;
-    const GemmTile& t = kGemmTile[c.tile];
+    const GemmTile t = c.tile == kGemmTiles ? GemmTile{kGemmShortTm, kGemmShortTn, 0, 0.f, 0.f, 0.f, 0.f} : kGemmTile[c.tile];
     GemmArgs g;
     g.n_row = int32_t((rows + 32 * t.tm - 1) / (32 * t.tm));
     g.n_col = int32_t((s.plan.C + 32 * t.tn - 1) / (32 * t.tn));
@@ -618,7 +645,6 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
     g.a_lo = s.a_lo;
     g.b_lo = s.b_lo;
     g.out_lo = s.out_lo;
-    const int form = s.a_lo || s.b_lo || s.out_lo ? GEMM_PARTS : (a.K % 64 || s.cmode == 0 ? GEMM_ANY : GEMM_PLAIN);
     g.partial = c.n_split > 1 || f32 ? static_cast<float*>(partial) : nullptr;
     if (f32) {
         if (f32->sums) {
@@ -628,7 +654,9 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
         *f32 = GemmSums{g.partial, g.ld, c.n_split};
     }
     const int64_t items = int64_t(g.n_row) * g.n_col * g.n_split;
-    hipLaunchKernelGGL(gemm_kernel(c.tile, trans, form), dim3(uint32_t((items + 7) / 8 * 8)), dim3(256), gemm_smem(c.tile), st, a, g);
+    const bool brief = c.tile == kGemmTiles;
+    hipLaunchKernelGGL(brief ? gemm_short_kernel(s.Kp / 64) : gemm_kernel(c.tile, trans, form), dim3(uint32_t((items + 7) / 8 * 8)), dim3(256),
+                       brief ? gemm_short_smem(s.Kp / 64) : gemm_smem(c.tile), st, a, g);
     if (c.n_split > 1 && !f32) {
         const int64_t total = rows * s.plan.C;
         const dim3 blocks(uint32_t(std::min<int64_t>((total + 255) / 256, 2048)));

@@ -126,3 +126,21 @@ def test_ranges_of_k(rows):
         layer.close()
         assert np.array_equal(a, b)
         assert np.max(np.abs(a - ref)) <= 2.0 ** -8 * np.max(np.abs(ref)) + 1e-3
+
+
+@pytest.mark.parametrize("n_in", [64, 128])
+@pytest.mark.parametrize("n_out", [520, 10248])
+def test_short_k_tile_edges(n_in, n_out):
+    """K of one and two tiles against many columns: the form that loads all of K at once, with rows and columns that end inside its tiles
+    of 160 x 128."""
+    rng = np.random.default_rng(n_in + n_out)
+    x = wl.round_to_dtype(rng.standard_normal((8000, n_in)), "bf16")
+    spec = wl.TNSpec(wl.FORMAT_DENSE, "bf16", (n_out,), (n_in,), ())
+    w = wl.round_to_dtype(rng.standard_normal((n_out, n_in)) / np.sqrt(n_in), "bf16")
+    layer = make_layer(spec, [w], 8000, flags=tn.TN_FLAG_NO_SMALL_CHAIN | (12 << tn.TN_FLAG_VARIANT_SHIFT))
+    xd = to_dev(x, "bf16")
+    for rows in (159, 161, 1119, 1441, 8000 if n_out < 1000 else 2560):
+        ref = x[:rows] @ w.T
+        y = to_host(layer(xd[:rows].contiguous()))
+        assert np.max(np.abs(y - ref)) <= 2.0 ** -8 * np.max(np.abs(ref)) + 1e-3, rows
+    layer.close()
