@@ -521,7 +521,10 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
                                   ((uint32_t(s.plan.C) + 32 * g.tn - 1) / uint32_t(32 * g.tn));      // rows and columns below 2^31
         if (all_tiles > (int64_t(1) << 26)) continue;
         const uint32_t tiles = uint32_t(all_tiles);
-        for (int ns = 1; ns <= 8; ++ns) {
+        // (an output of a few tiles: a core's gradient from that of its half, 128 x 64 with K of 2 x 5120, is a chain of K tiles that
+        // wait for memory: 8 ranges 16 us, 32 ranges 7)
+        const int most = tiles <= 16 ? 32 : 8;
+        for (int ns = 1; ns <= most; ++ns) {
             // more ranges only while they fill an idle chip, at least 4 K tiles each
             if (ns > 1 && (trans || tiles * uint32_t(ns - 1) >= 2 * cus || nk < 4 * ns)) break;
             const int per = (nk + ns - 1) / ns, n_real = (nk + per - 1) / per;
@@ -2848,7 +2851,8 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
     h->mgrad_chunk = chunk;
     h->bwd_ws_bytes = h->mgrad_off[1] + chunk * y_row;
     if (dense) sums = M * h->mgrad_dw.Cp * 4;
-    else sums = std::max(sums, std::min(kMaxGradPartialBytes, std::max(4 * sums, kMaxPartialBytes)));
+    // (the large products' sums of K ranges, where there are such products)
+    else sums = std::max(sums, std::min(kMaxGradPartialBytes, std::max(4 * sums, h->mgrad_bond ? kMaxPartialBytes / 4 : kMaxPartialBytes)));
     h->bwd_partial_bytes = sums + (h->mgrad_bond ? h->bond_sums_bytes[0] + h->bond_sums_bytes[1] : 0);
     return TN_OK;
 }
