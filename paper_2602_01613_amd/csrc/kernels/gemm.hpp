@@ -165,6 +165,12 @@ __global__ void __launch_bounds__(256, FORM == GEMM_SHORT ? 3 : 1) step_gemm_ker
     constexpr int RS = NM * 3 / 4 / NR > 1 ? NM * 3 / 4 / NR : 1, BAR = RS * NR + 4 < NM ? RS * NR + 4 : NM;
     constexpr int SPAN = NS > 2 ? 2 * NM : 2 * NM - BAR;
     constexpr int L_NOW = NS > 2 ? ((2 * NM - BAR) * L + SPAN - 1) / SPAN : L;      // loads l with BAR + l * SPAN / L < 2 * NM
+    // With two stages the next tile's loads get until its first fragment is read (a barrier of its own, after the EARLY first loads of
+    // the tile after it), or the last of them would have 37 MFMAs' time on 6 x 8 tiles. (Two products of 1321 x 25600 x 5120, 6 x 8 tiles:
+    // 631 us with one wait, 576 so; rank-32 ring 25600 -> 5120 at 8192 tokens, 7 x 8: 1901 / 1797; 8192 x 9216 x 2304, 8 x 8: 1.5 % of it.)
+    constexpr bool LATE = NS == 2 && BAR < NM;
+    constexpr int EARLY = ((NM - BAR) * L + SPAN - 1) / SPAN;      // loads l with BAR + l * SPAN / L < NM
+    static_assert(FORM == GEMM_SHORT || !LATE || (BAR + (EARLY - 1) * SPAN / L < NM && BAR + EARLY * SPAN / L >= NM), "early loads");
     static_assert(FORM == GEMM_SHORT || (L_NOW <= L && BAR + (L_NOW - 1) * SPAN / L < 2 * NM && (L_NOW == L || BAR + L_NOW * SPAN / L >= 2 * NM)), "load slots");
     if constexpr (FORM == GEMM_SHORT) {
 #pragma unroll
@@ -238,9 +244,14 @@ __global__ void __launch_bounds__(256, FORM == GEMM_SHORT ? 3 : 1) step_gemm_ker
                 constexpr int q = decltype(slot_index)::value, half = q / NM, m = q % NM, i = m / TN, j = m % TN;
                 if constexpr (q == BAR) {
                     __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): this wave has read the whole stage
-                    wait_vmcnt<(NS - 2) * L>();              // its loads of the next stage have landed
+                    if constexpr (!LATE) wait_vmcnt<(NS - 2) * L>();      // its loads of the next stage have landed
                     __builtin_amdgcn_s_barrier();
                     if (FORM == GEMM_ANY && kt + NS + 1 == nk) va = va_last;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if constexpr (LATE && q == NM) {
+                    wait_vmcnt<EARLY>();                     // the next stage is read from here on
+                    __builtin_amdgcn_s_barrier();
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 acc[i][j] = TRANS ? __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[half][i], fb[half][j], acc[i][j], 0, 0, 0)
