@@ -19,8 +19,8 @@
 //     and its 16-byte chunk c sits at position c ^ ((row / 2) % 8), so that the 16 rows a read touches at a time
 //     fall on 16 different slots of the 64 banks (with c ^ (row % 8) 40 % of the LDS cycles were conflicts); B's
 //     packed blocks lie in fragment order already and are copied as they are.
-// NS stages of 64 k. Once the fragments of a tile's second half are in registers its stage is free: one barrier per tile
-// lets the loads of the tile NS further on into it. The largest tiles leave LDS for two stages; a third, and the loads dealt out
+// NS stages of 64 k. Once the fragments of a tile's second half are in registers its stage is free: one barrier per tile (two
+// stages: and one where the next is read) lets the loads of the tile NS further on into it. The largest tiles leave LDS for two stages; a third, and the loads dealt out
 // evenly over the whole of a tile instead of over its second half, is worth 10 to 18 % to the smaller ones, which move more bytes
 // per product and do not cover the memory's latency with one tile (us with two stages and bunched loads / as it is: 1024 x
 // 8192 x 5120 on 128 x 256 tiles 98 / 77, 777 x 25600 x 5120 on 160 x 256 206 / 170, 2500 x 8192 x 5120 195 / 159; 8192 x
