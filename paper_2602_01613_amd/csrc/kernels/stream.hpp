@@ -672,22 +672,23 @@ __global__ void __launch_bounds__(256) step_split_reduce_parts_kernel(StepArgs a
 // (small_chain_image_kernel); a workgroup copies that image into LDS with 16-byte loads, then takes
 // tokens one at a time: the token's input goes to an LDS buffer, every step reads one buffer and
 // scatters into the other through its tables - the same tables the one-launch-per-step kernels use -
-// and the last step stores to memory. Intermediates are rounded to the storage type between steps, as
-// on the other paths.
+// and the last step stores to memory. Products and sums are fp32, four sums of every fourth k (tiles: of every
+// fourth group of four) each; intermediates are rounded to the storage type between steps, as on the other paths.
 //
-// For layers this small the cost is the launch and a chain of latencies, so:
-//   * a step is tiles of 16 x 16 outputs, one to a wave, on v_mfma_f32_16x16x4_f32 (products and sums in
-//     fp32 as before, in the same four interleaved sums over k): an operand of it is one word per lane for
-//     64 products, where a thread per output read two from LDS for each. Outputs of a lane run along the
-//     columns, lanes along the rows, which is how the last step stores;
-//   * the descriptions of the steps come with the image: as kernel arguments they lie in host memory, and every step
-//     began with a fetch of its own from there;
-//   * the image's loads and the first token's are all in flight before the first is stored;
-//   * word i of a buffer sits at i + 4 * (i / 64): rows of 32 or 64 words then start on different banks.
-// 4x8x8 train of rank 8, 16 tokens: 11.2 us a call with a thread per output, 8.8 now.
+// For layers this small the cost is the launch and a chain of latencies. Two forms, chosen by what a token's chain
+// takes in each (small_chain_on_tiles):
+//   * TILES: a step is tiles of 16 x 16 outputs, one to a wave, on v_mfma_f32_16x16x4_f32: an operand of it is one word
+//     per lane for 64 products. Outputs of a lane run along the columns, lanes along the rows, which is how the last step
+//     stores. The descriptions of the steps are read from the image: kernel arguments lie in host memory, and every step
+//     began with a fetch of its own from there. The image's loads and the first token's are all in flight before the
+//     first is stored; word i of a buffer sits at i + 4 * (i / 64), so that rows of 32 or 64 words start on different
+//     banks. 4x8x8 train of rank 8, 16 tokens: 11.3 us a call with an output per thread, 7.1 so.
+//   * else an output per thread and 256 threads, consecutive threads on consecutive columns: where a step has one row or a few,
+//     as in a dense layer, tiles are mostly padding and their stores 4 lanes each (dense 256 x 64: 3.6 us of the GPU's time at 16 tokens
+//     and 40 at 16384, on tiles 7.2 and 214).
 // ---------------------------------------------------------------------------------------------
 constexpr int kSmallChainMaxSteps = 8;
-constexpr int kSmallChainThreads = 512;
+constexpr int small_chain_threads(bool tiles) { return tiles ? 512 : 256; }
 struct SmallChainDesc {                    // a step, as it sits in the image
     int32_t R, K, C;
     int32_t b_off;                         // offset of the tensor in the image, in 4-byte words (a multiple of 4)
@@ -695,7 +696,7 @@ struct SmallChainDesc {                    // a step, as it sits in the image
     int32_t t_off;                         // offset of the tables in the image: crow[R], ccol[C], then arow[R],
                                            // acol[K] when the input is gathered
     int32_t gathered;
-    int32_t pad;
+    int32_t pad;                           // descriptions are 16-byte pieces of the image
 };
 constexpr int kSmallChainDescWords = sizeof(SmallChainDesc) / 4;
 struct SmallChainArgs {
@@ -705,6 +706,7 @@ struct SmallChainArgs {
     int64_t N, M;
     int32_t tokens, nsteps, image_words;
     int32_t buf_off[2];                    // offsets of the two per-token buffers in LDS, in words
+    SmallChainDesc d[kSmallChainMaxSteps]; // the descriptions again
 };
 struct SmallChainImageArgs {               // what the image is made of
     int32_t nsteps, image_words;
@@ -738,13 +740,13 @@ __global__ void __launch_bounds__(256) small_chain_image_kernel(SmallChainImageA
     }
 }
 
-// where word i of a per-token buffer sits, and how many words n of them take
+// where word i of a per-token buffer of the kernel on tiles sits, and how many words n of them take
 __host__ __device__ __forceinline__ int small_chain_word(int i) { return i + ((i >> 6) << 2); }
 
-template <typename T>
-__global__ void __launch_bounds__(kSmallChainThreads) small_chain_kernel(SmallChainArgs a) {
+template <typename T, bool TILES>
+__global__ void __launch_bounds__(small_chain_threads(TILES)) small_chain_kernel(SmallChainArgs a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char dyn_smem[];
-    constexpr int NT = kSmallChainThreads, NW = NT / 64;
+    constexpr int NT = small_chain_threads(TILES), NW = NT / 64;
     float* lds = reinterpret_cast<float*>(dyn_smem);
     const int32_t* ldsi = reinterpret_cast<const int32_t*>(dyn_smem);
     const int tid = threadIdx.x, lane = tid & 63;
@@ -752,12 +754,13 @@ __global__ void __launch_bounds__(kSmallChainThreads) small_chain_kernel(SmallCh
     const T* X = static_cast<const T*>(a.X);
     T* Y = static_cast<T*>(a.Y);
     const int N = int(a.N);
+    auto word = [](int i) { return TILES ? small_chain_word(i) : i; };
+    const floatx4* src = reinterpret_cast<const floatx4*>(a.image);
+    floatx4* dst = reinterpret_cast<floatx4*>(lds);
+    const int n4 = a.image_words >> 2;
     T x_first = from_float<T>(0.f);
-    if (tid < N) x_first = X[int64_t(blockIdx.x) * a.N + tid];            // the grid is no larger than the tokens
-    {
-        const floatx4* src = reinterpret_cast<const floatx4*>(a.image);
-        floatx4* dst = reinterpret_cast<floatx4*>(lds);
-        const int n4 = a.image_words >> 2;
+    if constexpr (TILES) {
+        if (tid < N) x_first = X[int64_t(blockIdx.x) * a.N + tid];        // the grid is no larger than the tokens
         for (int i0 = 0; i0 < n4; i0 += 4 * NT) {
             floatx4 v[4];
 #pragma unroll
@@ -766,58 +769,104 @@ __global__ void __launch_bounds__(kSmallChainThreads) small_chain_kernel(SmallCh
             for (int j = 0; j < 4; ++j)
                 if (i0 + j * NT + tid < n4) dst[i0 + j * NT + tid] = v[j];
         }
+    } else {
+#pragma unroll 4
+        for (int i = tid; i < n4; i += NT) dst[i] = src[i];
     }
     for (int t = blockIdx.x; t < a.tokens; t += gridDim.x) {
         float* in = lds + a.buf_off[0];
         float* out = lds + a.buf_off[1];
-        if (t != int(blockIdx.x)) {
-            __syncthreads();               // the previous token's buffers are no longer read
-            if (tid < N) x_first = X[int64_t(t) * a.N + tid];
+        if (t != int(blockIdx.x)) __syncthreads();               // the previous token's buffers are no longer read
+        if constexpr (TILES) {
+            if (t != int(blockIdx.x) && tid < N) x_first = X[int64_t(t) * a.N + tid];
+            if (tid < N) in[word(tid)] = to_float(x_first);
+            for (int i = tid + NT; i < N; i += NT) in[word(i)] = to_float(X[int64_t(t) * a.N + i]);
+        } else {
+            for (int i = tid; i < N; i += NT) in[i] = to_float(X[int64_t(t) * a.N + i]);
         }
-        if (tid < N) in[small_chain_word(tid)] = to_float(x_first);
-        for (int i = tid + NT; i < N; i += NT) in[small_chain_word(i)] = to_float(X[int64_t(t) * a.N + i]);
         __syncthreads();                   // the image and the token are in LDS
         for (int s = 0; s < a.nsteps; ++s) {
-            const int32_t* d = ldsi + s * kSmallChainDescWords;
-            const int R = __builtin_amdgcn_readfirstlane(d[0]), K = __builtin_amdgcn_readfirstlane(d[1]);
-            const int C = __builtin_amdgcn_readfirstlane(d[2]), ldb = __builtin_amdgcn_readfirstlane(d[4]);
-            const float* Bs = lds + __builtin_amdgcn_readfirstlane(d[3]);
-            const int32_t* t_crow = ldsi + __builtin_amdgcn_readfirstlane(d[5]);
-            const bool gathered = __builtin_amdgcn_readfirstlane(d[6]) != 0;
+            SmallChainDesc d;
+            if constexpr (TILES) {
+                const int32_t* w = ldsi + s * kSmallChainDescWords;
+                auto at = [&](int i) { return __builtin_amdgcn_readfirstlane(w[i]); };
+                d = {at(0), at(1), at(2), at(3), at(4), at(5), at(6), 0};
+            } else {
+                d = a.d[s];
+            }
+            const int R = d.R, K = d.K, C = d.C, ldb = d.ldb;
+            const float* Bs = lds + d.b_off;
+            const int32_t* t_crow = ldsi + d.t_off;
+            const bool gathered = d.gathered != 0;
             const int32_t* t_ccol = t_crow + R;
             const int32_t* t_arow = t_ccol + C;
             const int32_t* t_acol = t_arow + R;
             const bool last = s + 1 == a.nsteps;
-            const int row_tiles = (R + 15) >> 4, tiles = row_tiles * ((C + 15) >> 4);
-            const int kq = lane >> 4;      // a lane supplies row (column) lane % 16 and k = 4 * j + lane / 16
-            for (int tile = wave; tile < tiles; tile += NW) {
-                const int ct = tile / row_tiles, r = (tile - ct * row_tiles) * 16 + (lane & 15);
-                const int rl = min(r, R - 1), c0 = ct * 16;
-                const float* brow = Bs + min(c0 + (lane & 15), C - 1) * ldb;
-                const int base = gathered ? t_arow[rl] : rl * K;
-                floatx4 acc[4];
+            auto leave = [&](int o, float y) {
+                if (last) Y[int64_t(t) * a.M + o] = from_float<T>(y);
+                else out[word(o)] = to_float(from_float<T>(y));
+            };
+            if constexpr (TILES) {
+                const int row_tiles = (R + 15) >> 4, tiles = row_tiles * ((C + 15) >> 4);
+                const int kq = lane >> 4;      // a lane supplies row (column) lane % 16 and k = 4 * j + lane / 16
+                for (int tile = wave; tile < tiles; tile += NW) {
+                    const int ct = tile / row_tiles, r = (tile - ct * row_tiles) * 16 + (lane & 15);
+                    const int rl = min(r, R - 1), c0 = ct * 16;
+                    const float* brow = Bs + min(c0 + (lane & 15), C - 1) * ldb;
+                    const int base = gathered ? t_arow[rl] : rl * K;
+                    floatx4 acc[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
-                for (int k0 = 0; k0 < K; k0 += 16) {
+                    for (int u = 0; u < 4; ++u) acc[u] = floatx4{0.f, 0.f, 0.f, 0.f};
+                    for (int k0 = 0; k0 < K; k0 += 16) {
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int k = k0 + 4 * u + kq, kl = min(k, K - 1);
-                        const float av = in[small_chain_word(base + (gathered ? t_acol[kl] : kl))], bv = brow[kl];
-                        // what lies past K may be no number: zero times it is none either
-                        acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(k < K ? bv : 0.f, k < K ? av : 0.f, acc[u], 0, 0, 0);
+                        for (int u = 0; u < 4; ++u) {
+                            const int k = k0 + 4 * u + kq, kl = min(k, K - 1);
+                            const float av = in[word(base + (gathered ? t_acol[kl] : kl))], bv = brow[kl];
+                            // what lies past K may be no number: zero times it is none either
+                            acc[u] = __builtin_amdgcn_mfma_f32_16x16x4f32(k < K ? bv : 0.f, k < K ? av : 0.f, acc[u], 0, 0, 0);
+                        }
+                    }
+                    const floatx4 y = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+                    if (r < R) {
+                        const int ro = t_crow[r];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v)
+                            if (c0 + 4 * kq + v < C) leave(ro + t_ccol[c0 + 4 * kq + v], y[v]);
                     }
                 }
-                const floatx4 y = (acc[0] + acc[1]) + (acc[2] + acc[3]);
-                if (r < R) {
-                    const int ro = t_crow[r];
+            } else {
+                for (int i = tid; i < R * C; i += NT) {
+                    const int r = i / C, c = i - r * C;
+                    const float* brow = Bs + c * ldb;
+                    float acc[4] = {0.f, 0.f, 0.f, 0.f};
+                    if (!gathered && (K & 3) == 0) {
+                        // 16-byte LDS reads, several in flight
+                        const floatx4* a4 = reinterpret_cast<const floatx4*>(in + r * K);
+                        const floatx4* b4 = reinterpret_cast<const floatx4*>(brow);
+#pragma unroll 4
+                        for (int k = 0; k < (K >> 2); ++k) {
+                            const floatx4 av = a4[k], bv = b4[k];
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int c = c0 + 4 * kq + v;
-                        if (c >= C) continue;
-                        const int o = ro + t_ccol[c];
-                        if (last) Y[int64_t(t) * a.M + o] = from_float<T>(y[v]);
-                        else out[small_chain_word(o)] = to_float(from_float<T>(y[v]));
+                            for (int u = 0; u < 4; ++u) acc[u] = fmaf(av[u], bv[u], acc[u]);
+                        }
+                    } else {
+                        const float* arow = in + (gathered ? t_arow[r] : r * K);
+                        auto sum = [&](auto at) {
+                            int k = 0;
+#pragma unroll 2
+                            for (; k + 4 <= K; k += 4) {
+                                float av[4], bv[4];
+#pragma unroll
+                                for (int u = 0; u < 4; ++u) av[u] = arow[at(k + u)], bv[u] = brow[k + u];
+#pragma unroll
+                                for (int u = 0; u < 4; ++u) acc[u] = fmaf(av[u], bv[u], acc[u]);
+                            }
+                            for (; k < K; ++k) acc[0] = fmaf(arow[at(k)], brow[k], acc[0]);
+                        };
+                        if (gathered) sum([&](int k) { return t_acol[k]; });
+                        else sum([](int k) { return k; });
                     }
+                    leave(t_crow[r] + t_ccol[c], (acc[0] + acc[1]) + (acc[2] + acc[3]));
                 }
             }
             __syncthreads();

@@ -109,10 +109,11 @@ struct tn_linear_s {
     bool profiling = false;
     // whole chain in one launch with everything in LDS (small layers)
     bool small_chain = false;
-    size_t small_chain_smem = 0;
     void* small_chain_image = nullptr;    // descriptions, tensors (fp32, padded rows) and tables of all steps, as they sit in LDS
     int small_chain_image_words = 0;
-    int small_chain_buf_off[2] = {0, 0};
+    SmallChainDesc small_chain_desc[kSmallChainMaxSteps] = {};
+    int small_chain_buf_words[2] = {0, 0};      // of a per-token buffer: an output per thread, tiles
+    bool small_chain_tiles[2] = {false, false}; // the form on tiles: calls of up to a token per compute unit, larger ones
     // chained pair kernel (two-step plans of the train shape): second packed tensor in its layout
     bool pair = false;
     void* pair_b1f = nullptr;
@@ -902,6 +903,39 @@ constexpr size_t kSmallChainMaxSmem = 96 * 1024;
 constexpr size_t kSmallChainMaxLds = kSmallChainMaxSmem + kSmallChainMaxSmem / 16 + 1024;
 constexpr int64_t kSmallChainMaxBf16Tokens = 32;
 
+using small_chain_t = void (*)(SmallChainArgs);
+small_chain_t small_chain_kernel_of(bool bf16, bool tiles) {
+    if (bf16) return tiles ? small_chain_kernel<bf16_t, true> : small_chain_kernel<bf16_t, false>;
+    return tiles ? small_chain_kernel<float, true> : small_chain_kernel<float, false>;
+}
+
+// Which form of the whole-chain kernel: what a token takes in each, in us, beside what both take. Fitted to 195 random layers
+// (dense, trains, rings, Tucker; 1 to 5 steps) at 16 and 256 tokens, where a compute unit has one workgroup, and at 512 and 16384
+// (`many`), where it has two. Of the layers one in three is faster on tiles, by up to 2.4 times, the others by up to 5 times with an output
+// per thread (dense 256 x 64 at 16384 tokens 41 us, on tiles 215; the four steps 54 x 90 x 70 and smaller ones of a train 44 us at 16 tokens, on tiles
+// 23). The choice is 0.2 % above the better one on average, 10 % at most (29 % at 16384 tokens), and no more than 3 % slower
+// than an output per thread at any.
+bool small_chain_on_tiles(const SmallChainImageArgs& im, bool many) {
+    float threads = many ? -0.04f : -0.12f, tiles = 0.f;
+    for (int s = 0; s < im.nsteps; ++s) {
+        const SmallChainDesc& d = im.d[s];
+        const float turns = float((int64_t(d.R) * d.C + small_chain_threads(false) - 1) / small_chain_threads(false));
+        // an output per thread: per k one word of the tensor, whose rows fall on the same banks where their length has powers of two
+        // in it, or with 16-byte reads a quarter of that; gathered, a table's word too
+        float per_k = many ? 0.006f : 0.005f;
+        if (d.gathered || (d.K & 3)) {
+            const float rows = float(std::min(d.C, 64)) * float(std::min(d.ldb & -d.ldb, 64)) / 64.f;
+            per_k = (d.gathered ? (many ? 0.0235f : 0.0177f) : (many ? 0.012f : 0.0102f)) + (many ? 0.0053f : 0.0029f) * (std::max(1.f, rows) - 1.f);
+        }
+        threads += (many ? 0.12f : 0.2f) + turns * ((many ? 0.42f : 0.327f) + per_k * float(d.K));
+        // tiles: a wave's, one after another, and what all of them read from LDS
+        const int n = (d.R + 15) / 16 * ((d.C + 15) / 16), waves = small_chain_threads(true) / 64, k16 = (d.K + 15) / 16;
+        tiles += (many ? 0.084f : 0.226f) + float((n + waves - 1) / waves) * ((many ? 0.715f : 0.478f) + (many ? 0.286f : 0.305f) * float(k16)) +
+                 (many ? 0.049f : 0.018f) * float(n) * float(k16);
+    }
+    return (many ? 1.1f : 1.05f) * tiles < threads;
+}
+
 int plan_small_chain(tn_linear_s* h, hipStream_t st) {
     if (h->flags & (TN_FLAG_SCALAR_KERNELS | TN_FLAG_NO_SMALL_CHAIN)) return TN_OK;
     const size_t ns = h->steps.size();
@@ -939,11 +973,11 @@ int plan_small_chain(tn_linear_s* h, hipStream_t st) {
     off = (off + 3) & ~int64_t(3);
     const int64_t buf = (std::max(h->plan.N, h->plan.max_intermediate) + 3) & ~int64_t(3);
     if ((off + 2 * buf) * 4 > int64_t(kSmallChainMaxSmem)) return TN_OK;
-    const int buf_words = small_chain_word(int(buf)) + 4;
     im.image_words = int32_t(head + off);
-    h->small_chain_buf_off[0] = im.image_words;
-    h->small_chain_buf_off[1] = im.image_words + buf_words;
-    h->small_chain_smem = size_t(im.image_words + 2 * buf_words) * 4;
+    memcpy(h->small_chain_desc, im.d, sizeof(im.d));
+    for (int many = 0; many < 2; ++many) h->small_chain_tiles[many] = small_chain_on_tiles(im, many != 0);
+    h->small_chain_buf_words[0] = int(buf);
+    h->small_chain_buf_words[1] = small_chain_word(int(buf)) + 4;
     h->small_chain_image_words = im.image_words;
     if (hipMalloc(&h->small_chain_image, size_t(im.image_words) * 4) != hipSuccess) return TN_ERR_ALLOC;
     h->packed_bytes += int64_t(im.image_words) * 4;
@@ -966,13 +1000,15 @@ int launch_small_chain(const tn_linear_s* h, const void* x, void* y, int64_t tok
     a.tokens = int32_t(tokens);
     a.nsteps = int32_t(h->steps.size());
     a.image_words = h->small_chain_image_words;
-    a.buf_off[0] = h->small_chain_buf_off[0];
-    a.buf_off[1] = h->small_chain_buf_off[1];
+    const bool tiles = h->small_chain_tiles[tokens > h->num_cus ? 1 : 0];
+    const int buf_words = h->small_chain_buf_words[tiles ? 1 : 0];
+    a.buf_off[0] = a.image_words;
+    a.buf_off[1] = a.image_words + buf_words;
+    memcpy(a.d, h->small_chain_desc, sizeof(a.d));
+    const size_t smem = size_t(a.image_words + 2 * buf_words) * 4;
+    const dim3 block{uint32_t(small_chain_threads(tiles))};
     dim3 grid(uint32_t(std::min<int64_t>(tokens, int64_t(h->num_cus) * 2)));
-    if (h->elt == 2)
-        hipLaunchKernelGGL(small_chain_kernel<bf16_t>, grid, dim3(kSmallChainThreads), h->small_chain_smem, st, a);
-    else
-        hipLaunchKernelGGL(small_chain_kernel<float>, grid, dim3(kSmallChainThreads), h->small_chain_smem, st, a);
+    hipLaunchKernelGGL(small_chain_kernel_of(h->elt == 2, tiles), grid, block, smem, st, a);
     return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
 
@@ -2229,10 +2265,6 @@ int configure_kernels(int device) {
     if (rc == TN_OK &&
         (hipFuncSetAttribute(reinterpret_cast<const void*>(&step_pair_kernel<kPairStages, kPairBar>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, int(kPairSmemBytes)) != hipSuccess ||
-         hipFuncSetAttribute(reinterpret_cast<const void*>(small_chain_kernel<float>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallChainMaxLds)) != hipSuccess ||
-         hipFuncSetAttribute(reinterpret_cast<const void*>(small_chain_kernel<bf16_t>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallChainMaxLds)) != hipSuccess ||
          hipFuncSetAttribute(reinterpret_cast<const void*>(bond_grad_kernel<1>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, int(BondGradShape<1>::SMEM)) != hipSuccess ||
          hipFuncSetAttribute(reinterpret_cast<const void*>(bond_grad_kernel<2>),
@@ -2240,6 +2272,10 @@ int configure_kernels(int device) {
          hipFuncSetAttribute(reinterpret_cast<const void*>(bond_grad_kernel<3>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, int(BondGradShape<3>::SMEM)) != hipSuccess))
         rc = TN_ERR_HIP;
+    for (int i = 0; i < 4 && rc == TN_OK; ++i)
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(small_chain_kernel_of((i & 1) != 0, (i & 2) != 0)),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallChainMaxLds)) != hipSuccess)
+            rc = TN_ERR_HIP;
     for (int cfg = 0; cfg < tn::kKronConfigs && rc == TN_OK; ++cfg) rc = kron_dispatch(cfg, nullptr, 0, nullptr);
     if (rc == TN_OK) rc = gen_mfma_dispatch(nullptr, 0, nullptr);
     if (rc == TN_OK) rc = gen_mfma_both_dispatch(nullptr, nullptr, 0, nullptr);

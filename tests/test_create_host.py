@@ -1,6 +1,7 @@
 """tn_linear_create on a HIP runtime of the host (fake_hip.cpp): what a layer falls back to when memory is short, and what it holds."""
 import json
 import os
+import re
 import subprocess
 import sys
 import tempfile
@@ -10,16 +11,17 @@ import pytest
 HERE = os.path.dirname(os.path.abspath(__file__))
 
 CHILD = """
-import ctypes, json, sys
+import ctypes, json, os, sys
+fake = os.environ['LD_PRELOAD']
 import paper_2602_01613_amd as tn
 import workloads as wl
 from paper_2602_01613_amd.binding import _make_desc
-fmt, out_modes, in_modes, ranks, max_tokens, limit, flags, whats, scratch_tokens, grad_tokens = json.loads(sys.argv[1])
-spec = wl.TNSpec(fmt, "bf16", tuple(out_modes), tuple(in_modes), tuple(ranks))
+fmt, dtype, out_modes, in_modes, ranks, max_tokens, limit, flags, whats, scratch_tokens, grad_tokens, tokens, wanted = json.loads(sys.argv[1])
+spec = wl.TNSpec(fmt, dtype, tuple(out_modes), tuple(in_modes), tuple(ranks))
 mem = ctypes.create_string_buffer(64)
 lib = tn.load_library()
 ptrs = [ctypes.addressof(mem)] * len(spec.tensor_shapes())
-d, keep = _make_desc(fmt, tn.TN_DTYPE_BF16, out_modes, in_modes, ranks, ptrs, max_tokens, limit, flags, None)
+d, keep = _make_desc(fmt, tn.TN_DTYPE_BF16 if dtype == 'bf16' else tn.TN_DTYPE_F32, out_modes, in_modes, ranks, ptrs, max_tokens, limit, flags, None)
 h = ctypes.c_void_p()
 rc = lib.tn_linear_create(ctypes.byref(h), ctypes.byref(d))
 res = {"rc": rc}
@@ -33,8 +35,21 @@ buf = ctypes.create_string_buffer(1024)
 at = (ctypes.addressof(buf) + 255) // 256 * 256
 res["scratch"] = [lib.tn_linear_forward_scratch(h, at, at + 256, t, None) for t in scratch_tokens] if rc == 0 else []
 lib.tn_linear_param_gradients.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
-grads = (ctypes.c_void_p * len(ptrs))(*[at + 512] * len(ptrs))
-res["gradients"] = [lib.tn_linear_param_gradients(h, at, at + 256, grads, t, None) for t in grad_tokens] if rc == 0 else []
+grads = (ctypes.c_void_p * len(ptrs))(*[at + 512 if wanted is None or i in wanted else None for i in range(len(ptrs))])
+hip = ctypes.CDLL(fake)
+hip.fake_hip_take_launches.restype = ctypes.c_char_p
+def launches():
+    return [[l.split()[0]] + [int(v) for v in l.split()[1:]] for l in hip.fake_hip_take_launches().decode().splitlines()]
+res["launches"], res["gradient_launches"] = [], []
+if rc == 0:
+    launches()
+    for t in tokens:
+        assert lib.tn_linear_forward(h, at, at + 256, t, None) == 0
+        res["launches"].append(launches())
+res["gradients"] = []
+for t in grad_tokens if rc == 0 else []:
+    res["gradients"].append(lib.tn_linear_param_gradients(h, at, at + 256, grads, t, None))
+    res["gradient_launches"].append(launches())
 if rc == 0:
     lib.tn_linear_destroy(h)
 print("RESULT " + json.dumps(res))
@@ -48,15 +63,32 @@ def fake_hip():
     return out
 
 
-def create(fake_hip, spec, max_tokens, whats, limit=0, flags=0, refuse=None, scratch_tokens=(), grad_tokens=()):
+def create(fake_hip, spec, max_tokens, whats, limit=0, flags=0, refuse=None, scratch_tokens=(), grad_tokens=(), tokens=(), wanted=None):
     env = dict(os.environ, LD_PRELOAD=fake_hip)
     if refuse:
         env["FAKE_HIP_REFUSE_FROM"], env["FAKE_HIP_REFUSE_TO"] = str(refuse[0]), str(refuse[1])
-    arg = json.dumps([spec.format, list(spec.out_modes), list(spec.in_modes), list(spec.ranks), max_tokens, limit, flags, whats, list(scratch_tokens), list(grad_tokens)])
+    arg = json.dumps([spec.format, spec.dtype, list(spec.out_modes), list(spec.in_modes), list(spec.ranks), max_tokens, limit, flags, whats,
+                      list(scratch_tokens), list(grad_tokens), list(tokens), wanted])
     r = subprocess.run([sys.executable, "-c", CHILD, arg], cwd=os.path.dirname(HERE), env=env, capture_output=True, text=True, timeout=300)
     lines = [l for l in r.stdout.splitlines() if l.startswith("RESULT ")]
     assert lines, r.stderr[-800:]
-    return json.loads(lines[0][7:])
+    res = json.loads(lines[0][7:])
+    for k in ("launches", "gradient_launches"):
+        res[k] = [[Launch(*l) for l in call] for call in res[k]]
+    return res
+
+
+class Launch:
+    """One kernel launch: its name, the numbers among its template arguments in order, grid and dynamic LDS."""
+
+    def __init__(self, mangled, grid_x, grid_y, lds):
+        found = re.search(r"\d+([a-z]\w*?kernel)(I.*?EE?v|E?v|E)", mangled)
+        self.kernel = found.group(1) if found else mangled
+        self.args = tuple(int(v) for v in re.findall(r"L[ib](\d+)E", found.group(2))) if found else ()
+        self.grid, self.lds = (grid_x, grid_y), lds
+
+    def __repr__(self):
+        return f"{self.kernel}{self.args} {self.grid} {self.lds}"
 
 
 def test_no_memory_for_w_leaves_the_other_orders(fake_hip):
@@ -109,3 +141,18 @@ def test_work_of_gradients_through_dw(fake_hip):
     assert train[str(what[0])] > 0 and train[str(what[1])] == 2 * (2 * 2 * spec.M * spec.N * 128)
     steps = create(fake_hip, spec, 4096, what, flags=tn.TN_FLAG_TRAINABLE | tn.TN_FLAG_NO_LAZY_MERGE)
     assert steps[str(what[0])] == 0
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_form_of_small_layers(fake_hip, dtype):
+    """Each layer of the parity test of small layers is one launch of the whole-chain kernel, in the form that it names: tiles where steps have
+    rows enough to fill them, an output per thread where they have one or a few."""
+    import workloads as wl
+    from test_gpu_parity import SMALL_CHAINS
+    most = 0
+    for fmt, om, im, rk, few, many in SMALL_CHAINS:
+        got = create(fake_hip, wl.TNSpec(fmt, dtype, om, im, rk), 4096, [], tokens=(1, 256, 257, 4096) if dtype == "f32" else (1, 32))
+        assert all(len(call) == 1 and call[0].kernel == "small_chain_kernel" for call in got["launches"]), (om, im)
+        assert [call[0].args for call in got["launches"]] == ([(int(few),)] * 2 + [(int(many),)] * (2 if dtype == "f32" else 0)), (om, im)
+        most = max(most, got["launches"][0][0].lds)
+    assert most > 96 << 10

@@ -883,16 +883,39 @@ def test_two_layers_in_one_call(case):
             l3.close()
 
 
+# Layers that run as one launch in LDS (test_create_host.py checks which form of that kernel each takes): format, modes, ranks, and
+# whether on tiles up to a token per compute unit and with more
+SMALL_CHAINS = [
+    (wl.FORMAT_TT, (2, 2), (2, 3), (1, 2, 1), False, False),
+    (wl.FORMAT_TT, (5, 7), (3, 7), (1, 5, 1), False, False),
+    (wl.FORMAT_TT, (4, 8, 8), (4, 8, 8), (1, 8, 8, 1), True, True),
+    (wl.FORMAT_TT, (3, 10, 9), (9, 7, 5), (1, 11, 11, 1), True, True),
+    (wl.FORMAT_TT, (8, 8, 8), (9, 8, 8), (1, 12, 12, 1), True, True),              # 95 KB of the 96 there may be
+    (wl.FORMAT_TT, (1, 17, 2), (33, 1, 2), (1, 3, 3, 1), False, False),
+    (wl.FORMAT_TT, (2, 3, 2, 5), (3, 2, 7, 2), (1, 4, 4, 4, 1), False, False),
+    (wl.FORMAT_TT, (6, 9, 6), (7, 4, 7), (1, 4, 4, 1), True, True),
+    (wl.FORMAT_TR, (9, 22), (6, 18), (5, 5, 5), False, False),
+    (wl.FORMAT_TR, (5, 21), (12, 12), (5, 5, 5), False, True),
+    (wl.FORMAT_TR, (20, 21), (6, 14), (5, 5, 5), True, False),
+    (wl.FORMAT_TUCKER, (12, 6), (10, 19), (9, 6, 9, 9), False, False),
+    (wl.FORMAT_DENSE, (256,), (64,), (), False, False),
+    (wl.FORMAT_DENSE, (17,), (33,), (), False, False),
+    (wl.FORMAT_DENSE, (60,), (300,), (), False, False),
+]
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("out_modes,in_modes,rank", [((2, 2), (2, 3), 2), ((5, 7), (3, 7), 5), ((4, 8, 8), (4, 8, 8), 8), ((3, 10, 9), (9, 7, 5), 11),
-                                                     ((10, 10, 10), (10, 10, 10), 12), ((1, 17, 2), (33, 1, 2), 3), ((2, 3, 2, 5), (3, 2, 7, 2), 4)])
-def test_small_chain_tile_edges(dtype, out_modes, in_modes, rank):
-    """Whole chains in LDS, on tiles of 16 x 16 outputs and 16 k: rows, columns and K below a tile, of whole tiles and beyond, plain
-    and gathered inputs, more tokens than workgroups. Tolerance for fp32: K <= 120 products per sum in four chains, three steps: below
-    3 * 32 * 2^-24 = 6e-6 of the largest magnitude; bf16: the suite's."""
-    spec = wl.TNSpec(wl.FORMAT_TT, dtype, out_modes, in_modes, (1,) + (rank,) * (len(out_modes) - 1) + (1,))
-    rng = np.random.default_rng(rank + len(out_modes))
-    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(s[0] * s[2]), dtype) for s in spec.tensor_shapes()]
+@pytest.mark.parametrize("case", range(len(SMALL_CHAINS)))
+def test_small_chain_tile_edges(dtype, case):
+    """Whole chains in LDS, in both forms (tiles of 16 x 16 outputs and 16 k, an output per thread): rows, columns and K below a tile, of
+    whole tiles and beyond, plain and gathered inputs, more tokens than workgroups. Tolerance for fp32: K <= 120 products per sum in four
+    chains, three steps: below 3 * 32 * 2^-24 = 6e-6 of the largest magnitude (one or two steps of up to 300: their 2 * 75 roundings per chain
+    are of either sign); bf16: the suite's."""
+    fmt, out_modes, in_modes, ranks, _, _ = SMALL_CHAINS[case]
+    spec = wl.TNSpec(fmt, dtype, out_modes, in_modes, ranks)
+    rng = np.random.default_rng(case + len(out_modes))
+    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(s[0] * s[2] if fmt in (wl.FORMAT_TT, wl.FORMAT_TR) else s[-1]), dtype)
+          for s in spec.tensor_shapes()]
     n_tok = 700 if dtype == "f32" else 32
     x = wl.round_to_dtype(rng.standard_normal((n_tok, spec.N)), dtype)
     ref = O.forward(spec.format, ts, x, n_out_modes=len(out_modes))
