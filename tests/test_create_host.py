@@ -12,47 +12,47 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 CHILD = """
 import ctypes, json, os, sys
-fake = os.environ['LD_PRELOAD']
 import paper_2602_01613_amd as tn
 import workloads as wl
 from paper_2602_01613_amd.binding import _make_desc
-fmt, dtype, out_modes, in_modes, ranks, max_tokens, limit, flags, whats, scratch_tokens, grad_tokens, tokens, wanted = json.loads(sys.argv[1])
-spec = wl.TNSpec(fmt, dtype, tuple(out_modes), tuple(in_modes), tuple(ranks))
-mem = ctypes.create_string_buffer(64)
 lib = tn.load_library()
-ptrs = [ctypes.addressof(mem)] * len(spec.tensor_shapes())
-d, keep = _make_desc(fmt, tn.TN_DTYPE_BF16 if dtype == 'bf16' else tn.TN_DTYPE_F32, out_modes, in_modes, ranks, ptrs, max_tokens, limit, flags, None)
-h = ctypes.c_void_p()
-rc = lib.tn_linear_create(ctypes.byref(h), ctypes.byref(d))
-res = {"rc": rc}
-for w in whats:
-    v = ctypes.c_int64(-1)
-    if rc == 0:
-        assert lib.tn_linear_query(h, w, ctypes.byref(v)) == 0
-    res[str(w)] = v.value
 lib.tn_linear_forward_scratch.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
-buf = ctypes.create_string_buffer(1024)
-at = (ctypes.addressof(buf) + 255) // 256 * 256
-res["scratch"] = [lib.tn_linear_forward_scratch(h, at, at + 256, t, None) for t in scratch_tokens] if rc == 0 else []
 lib.tn_linear_param_gradients.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64, ctypes.c_void_p]
-grads = (ctypes.c_void_p * len(ptrs))(*[at + 512 if wanted is None or i in wanted else None for i in range(len(ptrs))])
-hip = ctypes.CDLL(fake)
+hip = ctypes.CDLL(os.environ['LD_PRELOAD'])
 hip.fake_hip_take_launches.restype = ctypes.c_char_p
 def launches():
     return [[l.split()[0]] + [int(v) for v in l.split()[1:]] for l in hip.fake_hip_take_launches().decode().splitlines()]
-res["launches"], res["gradient_launches"] = [], []
-if rc == 0:
-    launches()
-    for t in tokens:
-        assert lib.tn_linear_forward(h, at, at + 256, t, None) == 0
-        res["launches"].append(launches())
-res["gradients"] = []
-for t in grad_tokens if rc == 0 else []:
-    res["gradients"].append(lib.tn_linear_param_gradients(h, at, at + 256, grads, t, None))
-    res["gradient_launches"].append(launches())
-if rc == 0:
-    lib.tn_linear_destroy(h)
-print("RESULT " + json.dumps(res))
+def layer(fmt, dtype, out_modes, in_modes, ranks, max_tokens, limit, flags, whats, scratch_tokens, grad_tokens, tokens, wanted):
+    spec = wl.TNSpec(fmt, dtype, tuple(out_modes), tuple(in_modes), tuple(ranks))
+    mem = ctypes.create_string_buffer(64)
+    ptrs = [ctypes.addressof(mem)] * len(spec.tensor_shapes())
+    d, keep = _make_desc(fmt, tn.TN_DTYPE_BF16 if dtype == 'bf16' else tn.TN_DTYPE_F32, out_modes, in_modes, ranks, ptrs, max_tokens, limit, flags, None)
+    h = ctypes.c_void_p()
+    rc = lib.tn_linear_create(ctypes.byref(h), ctypes.byref(d))
+    res = {"rc": rc}
+    for w in whats:
+        v = ctypes.c_int64(-1)
+        if rc == 0:
+            assert lib.tn_linear_query(h, w, ctypes.byref(v)) == 0
+        res[str(w)] = v.value
+    buf = ctypes.create_string_buffer(1024)
+    at = (ctypes.addressof(buf) + 255) // 256 * 256
+    res["scratch"] = [lib.tn_linear_forward_scratch(h, at, at + 256, t, None) for t in scratch_tokens] if rc == 0 else []
+    grads = (ctypes.c_void_p * len(ptrs))(*[at + 512 if wanted is None or i in wanted else None for i in range(len(ptrs))])
+    res["launches"], res["gradient_launches"] = [], []
+    if rc == 0:
+        launches()
+        for t in tokens:
+            assert lib.tn_linear_forward(h, at, at + 256, t, None) == 0
+            res["launches"].append(launches())
+    res["gradients"] = []
+    for t in grad_tokens if rc == 0 else []:
+        res["gradients"].append(lib.tn_linear_param_gradients(h, at, at + 256, grads, t, None))
+        res["gradient_launches"].append(launches())
+    if rc == 0:
+        lib.tn_linear_destroy(h)
+    return res
+print("RESULT " + json.dumps([layer(*job) for job in json.loads(sys.stdin.read())]))
 """
 
 
@@ -63,19 +63,28 @@ def fake_hip():
     return out
 
 
-def create(fake_hip, spec, max_tokens, whats, limit=0, flags=0, refuse=None, scratch_tokens=(), grad_tokens=(), tokens=(), wanted=None):
+def job(spec, max_tokens, whats=(), limit=0, flags=0, scratch_tokens=(), grad_tokens=(), tokens=(), wanted=None):
+    """A layer to make, and what to do with it."""
+    return [spec.format, spec.dtype, list(spec.out_modes), list(spec.in_modes), list(spec.ranks), max_tokens, limit, flags, list(whats),
+            list(scratch_tokens), list(grad_tokens), list(tokens), wanted]
+
+
+def create_all(fake_hip, jobs, refuse=None):
     env = dict(os.environ, LD_PRELOAD=fake_hip)
     if refuse:
         env["FAKE_HIP_REFUSE_FROM"], env["FAKE_HIP_REFUSE_TO"] = str(refuse[0]), str(refuse[1])
-    arg = json.dumps([spec.format, spec.dtype, list(spec.out_modes), list(spec.in_modes), list(spec.ranks), max_tokens, limit, flags, whats,
-                      list(scratch_tokens), list(grad_tokens), list(tokens), wanted])
-    r = subprocess.run([sys.executable, "-c", CHILD, arg], cwd=os.path.dirname(HERE), env=env, capture_output=True, text=True, timeout=300)
+    r = subprocess.run([sys.executable, "-c", CHILD], input=json.dumps(jobs), cwd=os.path.dirname(HERE), env=env, capture_output=True, text=True, timeout=300)
     lines = [l for l in r.stdout.splitlines() if l.startswith("RESULT ")]
     assert lines, r.stderr[-800:]
-    res = json.loads(lines[0][7:])
-    for k in ("launches", "gradient_launches"):
-        res[k] = [[Launch(*l) for l in call] for call in res[k]]
-    return res
+    results = json.loads(lines[0][7:])
+    for res in results:
+        for k in ("launches", "gradient_launches"):
+            res[k] = [[Launch(*l) for l in call] for call in res[k]]
+    return results
+
+
+def create(fake_hip, spec, max_tokens, whats, refuse=None, **kw):
+    return create_all(fake_hip, [job(spec, max_tokens, whats, **kw)], refuse)[0]
 
 
 class Launch:
@@ -150,9 +159,47 @@ def test_form_of_small_layers(fake_hip, dtype):
     import workloads as wl
     from test_gpu_parity import SMALL_CHAINS
     most = 0
-    for fmt, om, im, rk, few, many in SMALL_CHAINS:
-        got = create(fake_hip, wl.TNSpec(fmt, dtype, om, im, rk), 4096, [], tokens=(1, 256, 257, 4096) if dtype == "f32" else (1, 32))
+    made = create_all(fake_hip, [job(wl.TNSpec(fmt, dtype, om, im, rk), 4096, tokens=(1, 256, 257, 4096) if dtype == "f32" else (1, 32))
+                                 for fmt, om, im, rk, _, _ in SMALL_CHAINS])
+    for (_, om, im, _, few, many), got in zip(SMALL_CHAINS, made):
         assert all(len(call) == 1 and call[0].kernel == "small_chain_kernel" for call in got["launches"]), (om, im)
         assert [call[0].args for call in got["launches"]] == ([(int(few),)] * 2 + [(int(many),)] * (2 if dtype == "f32" else 0)), (om, im)
         most = max(most, got["launches"][0][0].lds)
     assert most > 96 << 10
+
+
+def test_tiles_of_the_matrix_product_tests(fake_hip):
+    """The calls of the GPU tests that name a tile of the matrix-product kernel, or its form for short K, take it."""
+    import workloads as wl
+    from test_gpu_gemm import PINNED, SHORT_K_ROWS, TILE_CALLS
+    calls = [(tile, k, n_out, (rows,)) for tile, n_out, rows, ks in TILE_CALLS for k in ks]
+    calls += [((5, 4, k // 64), k, n_out, rows) for k in (64, 128) for n_out, rows in SHORT_K_ROWS.items()]
+    made = create_all(fake_hip, [job(wl.TNSpec(wl.FORMAT_DENSE, "bf16", (n_out,), (k,), ()), max(rows), flags=PINNED, tokens=rows)
+                                 for _, k, n_out, rows in calls])
+    for (tile, k, n_out, rows), got in zip(calls, made):
+        for call in got["launches"]:
+            used = [l.args for l in call if l.kernel == "step_gemm_kernel"]
+            form = 3 if k % 64 else 1 if len(rows) == 1 else 4
+            assert used == [(*tile, 0, form)], (tile, k, n_out, rows, used)
+    assert {t for t, *_ in TILE_CALLS} >= {(8, 8, 2), (7, 8, 2), (6, 8, 2), (5, 8, 3), (4, 8, 3), (3, 8, 3), (2, 8, 3), (8, 4, 3), (6, 4, 3),
+                                           (5, 4, 2), (4, 4, 2), (3, 4, 2), (2, 4, 3), (2, 2, 4)}
+
+
+def test_kernels_of_the_gradient_tests(fake_hip):
+    """The layers of the GPU tests of gradients take the kernels that these tests name: one pass over dW, and row runs read in 16-byte pieces."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    from test_gpu_gradients import NARROW_BONDS, ROW_RUNS, narrow_bond
+    bonds = [narrow_bond(case, rank) for case in range(len(NARROW_BONDS)) for rank in (32, 64, 96, 128)]
+    through_dw = tn.TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS
+    made = create_all(fake_hip, [job(spec, 1000, [through_dw], flags=tn.TN_FLAG_TRAINABLE, grad_tokens=[1000]) for spec, _ in bonds])
+    for (spec, one_pass), got in zip(bonds, made):
+        assert got[str(through_dw)] > 0
+        assert [l.args for l in got["gradient_launches"][0] if l.kernel == "bond_grad_kernel"] == ([(spec.ranks[len(spec.out_modes) // 2] // 32,)] if one_pass else [])
+    made = create_all(fake_hip, [job(wl.TNSpec(wl.FORMAT_TUCKER, "bf16", om, im, rk), 400, flags=tn.TN_FLAG_TRAINABLE, grad_tokens=(40, 333))
+                                 for om, im, rk, _, _ in ROW_RUNS])
+    for (om, _, rk, *named), got in zip(ROW_RUNS, made):
+        for tokens, steps, call in zip((40, 333), named, got["gradient_launches"]):
+            # one workgroup per 256 rows, padded to 8 of them, and 128 columns
+            grids = sorted(((tokens * rows + 255) // 256 + 7) // 8 * 8 * ((cols + 127) // 128) for _, cols, rows in steps)
+            assert sorted(l.grid[0] for l in call if l.kernel == "step_mfma_pipe_kernel" and l.args[4] == 3) == grids, (om, rk, tokens)

@@ -11,6 +11,7 @@ import paper_2602_01613_amd as tn
 from gpu_util import make_layer, to_dev, to_host
 
 pytestmark = pytest.mark.gpu
+PINNED = tn.TN_FLAG_NO_SMALL_CHAIN | (12 << tn.TN_FLAG_VARIANT_SHIFT)      # the matrix-product kernel, at any number of rows
 
 
 @pytest.mark.parametrize("n_in,n_out", [(64, 40), (128, 129), (192, 264), (2304, 328), (320, 1032), (704, 2056)])
@@ -128,19 +129,48 @@ def test_ranges_of_k(rows):
         assert np.max(np.abs(a - ref)) <= 2.0 ** -8 * np.max(np.abs(ref)) + 1e-3
 
 
+# rows that end inside the tiles of 160 x 128 of the form for K of one and two tiles, one short of their end and one past it
+SHORT_K_ROWS = {1032: (8000, 9601), 5128: (1281, 1599, 1600, 1601), 10248: (799, 801, 959, 960, 961, 2560), 20488: (319, 320, 639)}
+
+
 @pytest.mark.parametrize("n_in", [64, 128])
-@pytest.mark.parametrize("n_out", [520, 10248])
+@pytest.mark.parametrize("n_out", sorted(SHORT_K_ROWS))
 def test_short_k_tile_edges(n_in, n_out):
     """K of one and two tiles against many columns: the form that loads all of K at once, with rows and columns that end inside its tiles
     of 160 x 128."""
     rng = np.random.default_rng(n_in + n_out)
-    x = wl.round_to_dtype(rng.standard_normal((8000, n_in)), "bf16")
+    rows_of = SHORT_K_ROWS[n_out]
+    x = wl.round_to_dtype(rng.standard_normal((max(rows_of), n_in)), "bf16")
     spec = wl.TNSpec(wl.FORMAT_DENSE, "bf16", (n_out,), (n_in,), ())
     w = wl.round_to_dtype(rng.standard_normal((n_out, n_in)) / np.sqrt(n_in), "bf16")
-    layer = make_layer(spec, [w], 8000, flags=tn.TN_FLAG_NO_SMALL_CHAIN | (12 << tn.TN_FLAG_VARIANT_SHIFT))
+    layer = make_layer(spec, [w], max(rows_of), flags=PINNED)
     xd = to_dev(x, "bf16")
-    for rows in (159, 161, 1119, 1441, 8000 if n_out < 1000 else 2560):
+    for rows in rows_of:
         ref = x[:rows] @ w.T
         y = to_host(layer(xd[:rows].contiguous()))
         assert np.max(np.abs(y - ref)) <= 2.0 ** -8 * np.max(np.abs(ref)) + 1e-3, rows
     layer.close()
+
+
+# (rows and columns of the tile in units of 32, its LDS stages), columns, rows of a call, K: the fewest K tiles with which the tile is
+# chosen (the wide ones with three stages pay from 9 on) and the two numbers after it, so that the last tile falls on each of its
+# stages; the last K ends in the middle of a tile
+TILE_CALLS = [((2, 2, 4), 4104, 66, (192, 256, 320, 224)), ((2, 4, 3), 136, 8215, (64, 128, 96)), ((2, 4, 3), 8200, 66, (192, 256, 320, 160)),
+              ((3, 4, 2), 520, 6752, (64, 128, 192, 160)), ((4, 4, 2), 520, 9995, (192, 256, 160)), ((5, 4, 2), 776, 9611, (192, 256, 160)),
+              ((2, 8, 3), 8200, 199, (832, 896, 960, 800)), ((3, 8, 3), 8200, 66, (3904, 3968, 4032, 3872)), ((4, 8, 3), 8200, 808, (704, 768, 832, 672)),
+              ((5, 8, 3), 8200, 908, (704, 768, 832, 672)), ((6, 4, 3), 8200, 451, (640, 704, 768, 608)), ((8, 4, 3), 8200, 678, (576, 640, 704, 544)),
+              ((6, 8, 2), 14344, 641, (192, 256, 160)), ((7, 8, 2), 1032, 9995, (192, 256, 160)), ((8, 8, 2), 1544, 8215, (192, 256, 160))]
+
+
+@pytest.mark.parametrize("case", range(len(TILE_CALLS)))
+def test_every_tile_at_its_fewest_k_tiles(case):
+    """Each tile size where its first loads and its last ones meet, K of whole tiles and not. Tolerance as above."""
+    _, n_out, rows, ks = TILE_CALLS[case]
+    rng = np.random.default_rng(case)
+    for n_in in ks:
+        x = wl.round_to_dtype(rng.standard_normal((rows, n_in)), "bf16")
+        w = wl.round_to_dtype(rng.standard_normal((n_out, n_in)) / np.sqrt(n_in), "bf16")
+        layer = make_layer(wl.TNSpec(wl.FORMAT_DENSE, "bf16", (n_out,), (n_in,), ()), [w], rows, flags=PINNED)
+        y, ref = to_host(layer(to_dev(x, "bf16"))), x @ w.T
+        layer.close()
+        assert np.max(np.abs(y - ref)) <= 2.0 ** -8 * np.max(np.abs(ref)) + 1e-3, n_in

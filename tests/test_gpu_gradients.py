@@ -119,36 +119,54 @@ def test_param_gradients_random_layers(seed):
         assert max(errs) <= GRAD_TOL["bf16"], (seed, tokens, errs)
 
 
-@pytest.mark.parametrize("rank", [32, 64, 96])
-@pytest.mark.parametrize("om,im", [((8, 10, 8, 8), (8, 16, 8, 8)),        # halves of several row panels and of whole tiles
-                                   ((4, 4, 8, 8), (4, 4, 4, 8)),          # 256 rows (or less) against more columns
-                                   ((4, 5, 8, 8), (4, 4, 4, 8)),          # a last panel of 64 rows
-                                   ((8, 10, 8, 8), (4, 4, 3, 16)),        # 1280 rows, 96 tiles of columns, modes of no power of two
-                                   ((10, 16, 8, 8), (8, 8))])             # halves of one core: as two products
-def test_param_gradients_through_a_narrow_bond(om, im, rank):
-    """Trains whose two halves' gradients come from one pass over dW (bonds of 32, 64 and 96), at the edges of its row panels and column
-    ranges. dW and the halves are kept to 2^-16, the sums in fp32: 2^-13 of the largest value allows for three such steps."""
-    if len(im) == 2:
-        om, im = (om[0] * om[1], om[2] * om[3]), im
+# modes of trains: in the first four one pass over dW gives the gradients of both halves
+NARROW_BONDS = [((8, 10, 8, 8), (8, 16, 8, 8)),        # halves of several row panels and of whole tiles
+                ((4, 4, 8, 8), (4, 4, 4, 8)),          # 256 rows (or less) against more columns
+                ((4, 5, 8, 8), (4, 4, 4, 8)),          # a last panel of 64 rows
+                ((8, 10, 8, 8), (4, 4, 3, 16)),        # 1280 rows, 96 tiles of columns, modes of no power of two
+                ((160, 64), (8, 8))]                   # halves of one core: as two products, like a bond of 128
+
+
+def narrow_bond(case, rank):
+    """The train, and whether its gradients come from one pass over dW."""
+    om, im = NARROW_BONDS[case]
     spec = wl.TNSpec(tn.TN_FORMAT_TT, "bf16", om, im, (1,) + tuple(rank if k == len(om) // 2 else min(rank, 32) for k in range(1, len(om))) + (1,))
+    return spec, rank < 128 and len(om) == 4
+
+
+@pytest.mark.parametrize("rank", [32, 64, 96, 128])
+@pytest.mark.parametrize("case", range(len(NARROW_BONDS)))
+def test_param_gradients_through_a_narrow_bond(case, rank):
+    """Trains whose two halves' gradients come from one pass over dW (bonds of 32, 64 and 96), at the edges of its row panels and column
+    ranges, and those that two products give. dW and the halves are kept to 2^-16, the sums in fp32: 2^-13 of the largest value allows for
+    three such steps."""
+    spec, _ = narrow_bond(case, rank)
     rng = np.random.default_rng(rank + spec.M)
     ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(s[0] * s[2]), "bf16") for s in spec.tensor_shapes()]
     tokens = 1000
     layer = make_layer(spec, ts, tokens, flags=tn.TN_FLAG_TRAINABLE)
-    through_dw = 0 < layer.query(tn.TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS) <= tokens
+    assert 0 < layer.query(tn.TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS) <= tokens
     layer.close()
-    assert through_dw or len(im) == 2
     errs = _check(spec, ts, tokens, 41 + tokens)
-    # (step by step, which the library may price lower for the smallest: the suite's tolerance)
-    assert max(errs) <= (2.0 ** -13 if through_dw else GRAD_TOL["bf16"]), errs
+    assert max(errs) <= 2.0 ** -13, errs
 
 
-@pytest.mark.parametrize("om,im,rk", [((40, 72), (24, 16), (40, 64, 16, 16)), ((72, 160), (24, 16), (72, 136, 8, 16)), ((264, 48), (16, 16), (40, 48, 16, 8)),
-                                      ((33, 40), (16, 24), (33, 40, 16, 16)), ((40, 33), (16, 24), (40, 33, 16, 16))])
-def test_input_gradients_along_row_runs(om, im, rk):
-    """Tucker layers whose out-factor steps read the output's gradient in runs along its rows: K below, at and above a tile of 64, one
-    and two tiles of 128 columns, rows that end inside a tile of 256, and extents that allow no such runs."""
-    spec = wl.TNSpec(tn.TN_FORMAT_TUCKER, "bf16", om, im, rk)
+# Tucker layers and, at 40 and at 333 tokens, the products towards an out-factor's rank that read the output's gradient in runs along its
+# rows: (K, columns, rows per token) of each
+ROW_RUNS = [((40, 72), (24, 16), (40, 64, 16, 16), [(40, 40, 64)], [(40, 40, 64)]),                     # K below a tile of 64
+            ((64, 72), (24, 16), (40, 64, 16, 16), [(64, 40, 72)], [(64, 40, 72)]),                     # at one
+            ((136, 160), (24, 16), (72, 136, 8, 16), [], [(136, 72, 160), (160, 136, 72)]),             # two and three, one and two tiles of 128 columns
+            ((264, 160), (24, 16), (72, 136, 8, 16), [(264, 72, 160)], [(264, 72, 160), (160, 136, 72)]),
+            ((264, 48), (16, 16), (40, 48, 16, 8), [(48, 48, 40), (264, 40, 48)], [(48, 48, 40)]),
+            ((33, 40), (16, 24), (33, 40, 16, 16), [(33, 33, 40)], [(33, 33, 40)]),                     # a K of no whole pieces
+            ((40, 33), (16, 24), (40, 33, 16, 16), [], [])]                                             # an extent that allows no such runs
+
+
+@pytest.mark.parametrize("case", range(len(ROW_RUNS)))
+def test_input_gradients_along_row_runs(case):
+    """Tucker layers whose out-factor steps read the output's gradient in runs along its rows, with rows that end inside a tile of 256."""
+    om, im, rk, _, _ = ROW_RUNS[case]
+    spec = wl.TNSpec(wl.FORMAT_TUCKER, "bf16", om, im, rk)
     rng = np.random.default_rng(sum(om) + rk[1])
     ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(max(1, s[-1])), "bf16") for s in spec.tensor_shapes()]
     for tokens in (40, 333):
