@@ -470,6 +470,9 @@ int launch_pipe(const DevStep& s, const StepArgs& a, int64_t rows, hipStream_t s
 // at most. 64 x 64 is for outputs of up to 64 columns, the gradients towards a bond, which read A once and are
 // bound by the loads in flight. Larger tiles do more per us, smaller ones leave less of the last round of workgroups empty and
 // pad fewer rows.
+// As times, which is how the orders of contraction are compared, they are 6 % low on average with the column operand in the caches, as W is
+// (0.92 to 1.19 of the price; 70 to 8192 rows of six products of up to 84 MB), and 13 % with it in memory (0.91 to 1.53, most at few rows); of
+// the two products with 262 MB of it 10 % high (0.71 to 1.04).
 struct GemmTile {
     int tm, tn, stages;
     float t1, o1, t2, o2;
@@ -1831,9 +1834,12 @@ int prepare_lazy(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     return TN_OK;
 }
 
-// What one launch of a product takes, in us: its tiles, or the stores of its output.
+// What one launch of a product takes, in us: its tiles, or the stores of its output (W of 10240 x 4096 in 22 us, 84 MB; in two parts 3.5 TB/s).
+// Without the form for short K, which W's product of a narrow bond runs on, W was priced 7 us too high.
+constexpr float kGemmStoreBytesPerUs = 4e6f;
 float product_us(const tn_linear_s* h, const DevStep& s) {
-    return 5.f + std::max(gemm_choice(h, s, s.plan.R, 0).us, float(s.plan.R) * float(s.plan.C) * (s.out_lo ? 4.f : 2.f) / 3.5e6f);
+    const bool plain = !s.a_lo && !s.b_lo && !s.out_lo;
+    return 5.f + std::max(gemm_choice(h, s, s.plan.R, 0, plain).us, float(s.plan.R) * float(s.plan.C) * (plain ? 2.f / kGemmStoreBytesPerUs : 4.f / 3.5e6f));
 }
 
 constexpr int64_t kMatrixNoEnd = std::numeric_limits<int64_t>::max();
@@ -1850,8 +1856,11 @@ bool takes_matrix(const tn_linear_s* h, int64_t tokens) {
 // The other orders are priced at the rates their kernels reach at many tokens (FLOP per us: chained pair kernel 1.3e9, one
 // launch per step 0.45e9; the Kronecker-sum kernel by kron_us). Measured, us per call in this order / in the other: ring
 // 25600 -> 5120 of rank 32 343 / 410 at 96 tokens, 767 / 8109 at 2048, 1955 / 30730 at 8192; ring 5120 -> 8192 of rank 96 776 /
-// 911 at 48 tokens, 885 / 35579 at 2048; train 5120 -> 25600 of rank 96 226 / 207 at 387 tokens, 226 / 391 at 420; train 5120 -> 8192 of rank 64 166 / 211 at 2048 tokens, 538 /
-// 783 at 8192; of rank 32, whose chain has little more than 2 M N, not taken.
+// 911 at 48 tokens, 885 / 35579 at 2048; train 5120 -> 25600 of rank 96 226 / 207 at 387 tokens, 226 / 391 at 420; train 5120 -> 8192 of rank 64 107 / 188 at 1202 tokens, 143 / 199 at
+// 2048, 488 / 792 at 8192; of rank 32, whose chain has little more than 2 M N, 100 / 81 at 1000, 99 / 145 at 1025, 145 / 154 at 2048.
+// Of 500 such pairs (trains and rings of ranks 32 to 96, five projections, 16 to 8192 tokens) this order is never taken where it is more than 6 %
+// slower; it is left where it is up to 1.8 times as fast (train 5120 -> 8192 of rank 64, 103 / 185 at 1100 tokens): the chained pair kernel is priced
+// by the token, while it takes rounds of workgroups.
 int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     if (h->plan.dtype != TN_DTYPE_BF16 ||
         (desc->flags & (TN_FLAG_NO_PAIR_CHAIN | TN_FLAG_SCALAR_KERNELS | TN_FLAG_NO_MERGE | TN_FLAG_NO_LAZY_MERGE)) ||
@@ -1876,21 +1885,31 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
         return 6.f * float(h->steps.size()) + float(t) * float(h->plan.flops) / 0.45e9f;
     };
     // Token counts [first, end) for which this order is taken: from where it is clearly the cheaper one to where it no longer is.
-    // There may be several such ranges: the price of the Kronecker-sum kernel is a staircase, in steps of a round of workgroups.
+    // There may be several such ranges: the prices are staircases, in row tiles here and in rounds of workgroups of the Kronecker-sum kernel.
+    // They are looked for on a grid of counts and their ends between its points: with the ends on the grid, a train 5120 -> 8192 of rank 64
+    // took this order at 1260 tokens and not at 1259 or 1261.
     auto ranges = [&](float build_us) {
         std::vector<std::pair<int64_t, int64_t>> r;
-        bool in = false;
-        int64_t last = 0;
-        for (int64_t t = 8; t <= desc->max_tokens; last = t, t += t < 64 ? 8 : t / 16) {
+        auto changes = [&](int64_t t, bool in) {
             const float us = build_us + gemm_choice(h, y, t, kMaxPartialBytes).us, other = other_us(t);
-            if (!in && 1.04f * us < other) r.push_back({t, kMatrixNoEnd});
-            else if (in && us >= other) r.back().second = last + 1;
-            else continue;
+            return in ? us >= other : 1.04f * us < other;
+        };
+        bool in = false;
+        int64_t last = 7;
+        for (int64_t t = 8; t <= desc->max_tokens; last = t, t += t < 64 ? 8 : t / 16) {
+            if (!changes(t, in)) continue;
+            int64_t at = t;                        // the first count of this interval that does, not the grid's
+            for (int64_t lo = last; at - lo > 1;) {
+                const int64_t mid = lo + (at - lo) / 2;
+                (changes(mid, in) ? at : lo) = mid;
+            }
+            if (in) r.back().second = at;
+            else r.push_back({at, kMatrixNoEnd});
             in = !in;
         }
         return r;
     };
-    if (ranges(6.f + float(h->plan.M) * float(h->plan.N) * 2.f / 3.5e6f).empty()) return TN_OK;
+    if (ranges(5.f + float(h->plan.M) * float(h->plan.N) * 2.f / kGemmStoreBytesPerUs).empty()) return TN_OK;
     if (!matrix_plan_of(h, desc)) return TN_OK;
     const tn::MatrixPlan& m = h->matrix_plans.m;
     h->mat_bytes = m.w_elems * 2;

@@ -168,6 +168,21 @@ def test_form_of_small_layers(fake_hip, dtype):
     assert most > 96 << 10
 
 
+@pytest.mark.parametrize("n_in,n_out,rank", [(5120, 8192, 64), (5120, 25600, 32), (5120, 1024, 96), (25600, 5120, 64)])
+def test_order_by_token_count_follows_the_prices(fake_hip, n_in, n_out, rank):
+    """Token counts that contract the tensors first come in ranges between the prices' crossings: none is a point of the grid that
+    they are looked for on. A row tile of the matrix-product kernel is 32 rows at least, and so are they."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    spec = wl.stack_spec(wl.FORMAT_TT, n_in, n_out, rank)
+    most = 2600
+    got = create(fake_hip, spec, most, [tn.TN_QUERY_MATRIX_TOKENS_BASE + t for t in range(1, most + 1)])
+    taken = [got[str(tn.TN_QUERY_MATRIX_TOKENS_BASE + t)] for t in range(1, most + 1)]
+    assert any(taken)
+    changes = [t for t in range(1, most) if taken[t] != taken[t - 1]]
+    assert all(b - a >= 32 for a, b in zip(changes, changes[1:])), changes
+
+
 def test_tiles_of_the_matrix_product_tests(fake_hip):
     """The calls of the GPU tests that name a tile of the matrix-product kernel, or its form for short K, take it."""
     import workloads as wl
