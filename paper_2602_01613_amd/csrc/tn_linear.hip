@@ -675,18 +675,13 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
     return TN_OK;
 }
 
-// A launch for the matrix-product kernel (a step stored one by one only where the split-K kernel has no use for its ranges): more than a row tile of rows, and not a short K whose output blocks fill at most one round
-// of the split-K kernel in one range, which then has the shorter chain: 0.95 us and 0.115 per 16 k (core of the rank-64 Tucker
-// layer 5120 -> 1024 at 460 tokens, K = 1024: 8.3 us, 9.5 on 64 x 64 tiles; K = 2304 17.7, 12.5 in four ranges). A tile's first
-// loads come 1.2 us later than gemm_choice has it, which compares tiles with each other.
-bool gemm_rows(const tn_linear_s* h, const DevStep& s, int64_t rows) {
+// A launch for the matrix-product kernel: more than a row tile of rows; a step stored one by one only where the split-K kernel has no
+// use for its ranges. (Short K whose output blocks are at most one round of the split-K kernel in one range is faster here too: K = 128,
+// 66 to 1000 rows of 64 to 2048 columns 3.1 to 3.4 us, 5.7 to 6.2 there; K = 1024, 460 x 1024 5.6 and 8.4; of 350 calls of random
+// layers with such steps none took longer, 11 took 0.76 to 0.95 of the time.)
+bool gemm_rows(const DevStep& s, int64_t rows) {
     if (rows < kGemmMinRows || !gemm_fits(s)) return false;
-    if (s.cmode == 0) return !split_config(s, rows).use;      // one range only: where there are tiles enough without K ranges
-    const float split_us = 0.95f + 0.115f * float(s.Kp / 16);
-    if (split_us > 10.f || s.q4_codes || (h->flags & TN_FLAG_NO_SPLIT_K)) return true;
-    const SplitCfg c = split_config(s, rows);
-    if (!c.use || c.nsplit != 1 || c.lds_rows || c.skinny || int64_t(c.row_tiles) * c.col_blocks > h->num_cus) return true;
-    return split_us > gemm_choice(h, s, rows, 0).us + 1.2f;
+    return s.cmode != 0 || !split_config(s, rows).use;
 }
 
 // One product of the matrix plan: out[crow[r] + ccol[c]] = sum_k A[r][k] B[c][k], or its fp32 sums.
@@ -785,7 +780,7 @@ int launch_step(const tn_linear_s* h, const Workspace& w, const DevStep& s, cons
     a.Kp = s.Kp;
     a.C = int32_t(s.plan.C);
     a.Cp = s.Cp;
-    if (gemm_rows(h, s, rows)) {
+    if (gemm_rows(s, rows)) {
         const int rc = launch_gemm(h, s, a, rows, w.partial, w.partial_bytes, st);
         if (rc != TN_OK) return rc;
         return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;

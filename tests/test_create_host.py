@@ -183,6 +183,15 @@ def test_order_by_token_count_follows_the_prices(fake_hip, n_in, n_out, rank):
     assert all(b - a >= 32 for a, b in zip(changes, changes[1:])), changes
 
 
+def test_short_k_of_more_than_a_row_tile(fake_hip):
+    """From 65 rows on a step of short K is the matrix-product kernel's, also where its outputs are few."""
+    import workloads as wl
+    shapes = [(k, c) for k in (128, 1024, 1216) for c in (64, 512, 2048)]
+    made = create_all(fake_hip, [job(wl.TNSpec(wl.FORMAT_DENSE, "bf16", (c,), (k,), ()), 1000, tokens=(66, 260, 1000)) for k, c in shapes])
+    for shape, got in zip(shapes, made):
+        assert all("step_gemm_kernel" in [l.kernel for l in call] for call in got["launches"]), (shape, got["launches"])
+
+
 def test_tiles_of_the_matrix_product_tests(fake_hip):
     """The calls of the GPU tests that name a tile of the matrix-product kernel, or its form for short K, take it."""
     import workloads as wl
