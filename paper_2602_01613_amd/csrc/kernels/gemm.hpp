@@ -20,17 +20,17 @@
 //     fall on 16 different slots of the 64 banks (with c ^ (row % 8) 40 % of the LDS cycles were conflicts); B's
 //     packed blocks lie in fragment order already and are copied as they are.
 // NS stages of 64 k. Once the fragments of a tile's second half are in registers its stage is free: one barrier per tile (two
-// stages: and one where the next is read) lets the loads of the tile NS further on into it. The largest tiles leave LDS for two stages; a third, and the loads dealt out
-// evenly over the whole of a tile instead of over its second half, is worth 10 to 18 % to the smaller ones, which move more bytes
-// per product and do not cover the memory's latency with one tile (us with two stages and bunched loads / as it is: 1024 x
-// 8192 x 5120 on 128 x 256 tiles 98 / 77, 777 x 25600 x 5120 on 160 x 256 206 / 170, 2500 x 8192 x 5120 195 / 159; 8192 x
-// 8192 x 5120 on 256 x 256, two stages as before, 531 / 507). Tiles of which a CU holds two workgroups keep to half of its LDS.
-// Loads past the last tile are out of bounds and read no memory.
+// stages: and one where the next is read) lets the loads of the tile NS further on into it. The largest tiles leave LDS for two
+// stages; a third, and the loads dealt out evenly over the whole of a tile instead of over its second half, is worth 17 to 21 %
+// to the smaller ones, which move more bytes per product and do not cover the memory's latency with one tile (us with two
+// stages and bunched loads / as it is: 1024 x 8192 x 5120 on 128 x 256 tiles 98 / 77, 777 x 25600 x 5120 on 160 x 256 206 / 170,
+// 2500 x 8192 x 5120 195 / 159). Tiles of which a CU holds two workgroups keep to half of its LDS. Loads past the last tile are
+// out of bounds and read no memory.
 // The sums leave straight from registers: two lane swaps turn the accumulator layout (4 consecutive values per lane)
 // into 16-byte pieces of 64-byte runs, with no second trip through LDS; the output offsets of the tile's rows and
 // columns are fetched into LDS when the tile starts.
-// 8192 x 8192 x 5120 in 467 us = 1.47 PFLOP/s (the 256 x 256 ping-pong kernel this replaces: 565 us), 8192 x 9216 x
-// 2304 in 260 us (340).
+// 8192 x 8192 x 5120 in 466 us = 1.47 PFLOP/s (the 256 x 256 ping-pong kernel this replaces: 565 us), 8192 x 9216 x
+// 2304 in 270 us (340).
 //
 // Tile sizes: 32*TM x 32*TN, TM <= 8, TN 8, 4 or 2; the host picks the one (and the number of K ranges) with the least
 // time by gemm_choice. XCD x takes a contiguous eighth of the tiles in bands of four row tiles (row fastest), so that

@@ -82,10 +82,10 @@ __global__ void __launch_bounds__(256) step_scalar_kernel(StepArgs a) {
 //   AMODE 0: A rows are plain and K % 8 == 0 -> 16-byte global loads
 //   AMODE 1: element-wise gather (tables, or K not a multiple of 8)
 //   AMODE 2 (step_mfma_pipe_kernel only): rows through the tables, the k of a row in aligned contiguous runs of 8
+//           (tn::Step::a_vec): 16-byte loads at arow[r] + acol[k]
 //   AMODE 3 (step_mfma_pipe_kernel only): the rows of a k in aligned contiguous runs of 8 (R % 8 == 0), through the tables: a
 //           thread loads 8 rows x 8 k as 8 such pieces, whole lines per k, and turns them round in registers. Element by element
 //           the input gradient of a Tucker out-factor (500 x 96 rows, K = 160, 96 columns) took 69 us, 21 here
-//            (tn::Step::a_vec): 16-byte loads at arow[r] + acol[k]
 //   CMODE 0: scalar stores; 1: 8 contiguous columns per store; 2: 8 contiguous rows per store
 // ---------------------------------------------------------------------------------------------
 template <int WM, int WN, int TM, int TN, int AMODE>

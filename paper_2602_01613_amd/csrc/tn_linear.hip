@@ -2696,8 +2696,9 @@ int launch_param_gradient(const tn_linear_s* h, const DevStep& s, const void* dO
 constexpr int64_t kGradMinTokens = 16;        // one token range is padded to 64
 constexpr int kGradSumsPad = 128;             // columns of the core gradients (a bond): padded to the narrow tiles
 
-// bond_grad_kernel takes halves of two cores each over a bond of 32, 64 or 96 (its sums and its operand stay in registers); the columns are cut into as many ranges as
-// leave the least to the busiest compute unit, at least 4 tiles each, the sums within kMaxGradPartialBytes.
+// bond_grad_kernel takes halves of two cores each (a half of one core has no low part, and the kernel reads both parts of both) over
+// a bond of 32, 64 or 96 (its sums and its operand stay in registers); the columns are cut into as many ranges as leave the least to the
+// busiest compute unit, at least 4 tiles each, the sums within kMaxGradPartialBytes.
 bool plan_bond_grad(tn_linear_s* h, const tn::MatrixPlan& m, const tn::MatrixGrad& g) {
     const int64_t F0 = m.half[0].F, F1 = m.half[1].F, S = m.Kr;
     if (!g.half[0].pair || !g.half[1].pair || S % 32 || S > 96 || F0 % 64 || F1 % 64 || F1 > (int64_t(1) << 21) || F0 > (int64_t(1) << 24) ||
@@ -2751,7 +2752,10 @@ int launch_bond_grad(const tn_linear_s* h, const void* D, const void* P0, const 
 // two cores meet such a sum: they are kept in two parts each, as the caller gets fp32 (in one
 // part, core gradients of the rank-64 train 5120 -> 8192 at 1024 tokens with a common component are 2.9e-3 off in the 2-norm, in
 // two 5e-6; the steps, whose roundings average out over the tokens, leave 0.9 to 1.8e-4). The steps are priced at 0.35e9 FLOP per us and 40 us
-// a step (train 5120 -> 8192 of rank 64: 9.7 ms at 1024 tokens; ring 25600 -> 5120 of rank 32: 12.5 ms at 64).
+// a step (train 5120 -> 8192 of rank 64: 9.7 ms at 1024 tokens; ring 25600 -> 5120 of rank 32: 12.5 ms at 64). Through dW / step by
+// step in us at the first count that takes dW, and at 204 tokens, trains of rank 32, 64 and 96: 5120 -> 8192 129 / 206 at 40 tokens, 153 / 247 at
+// 16, 191 / 362 at 16 (204: 140 / 668, 168 / 1893, 205 / 3725); 5120 -> 25600 344 / 639 at 102 (the first is 81), 367 / 429 at 24, 414 / 533 at 16;
+// 25600 -> 5120 of rank 64 386 / 388 at 24; 5120 -> 1024 at 16: 84 / 150, 89 / 275, 99 / 261; rings at 16, by 1.6 times and more. At no count of 270 this order is the slower one where it is taken.
 int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     const int64_t M = h->plan.M, N = h->plan.N;
     if (h->plan.dtype != TN_DTYPE_BF16 || N % 64 || M % 8 || desc->max_tokens < kGradMinTokens ||
@@ -2978,7 +2982,7 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
         auto operand = [&](int i) -> const void* { return h->mgrad_half[i].pair ? at(4 + i) : h->mgrad_half[i].op.s.packed; };
         if (h->mgrad_bond) {
             // how far the low part of the operand made of a half is: known to the step that it is the column operand of
-            rc = launch_bond_grad(h, at(2), operand(0), operand(1), h->mgrad_half[1].dh.b_lo, h->mgrad_half[0].dh.b_lo, st);
+            rc = launch_bond_grad(h, at(2), at(4), at(5), h->mgrad_half[1].dh.b_lo, h->mgrad_half[0].dh.b_lo, st);
             if (rc != TN_OK) return rc;
         } else if (wanted[1]) {
             transpose_parts(2, 3, h->mgrad_f[0], h->mgrad_f[1], h->mgrad_f[0]);
