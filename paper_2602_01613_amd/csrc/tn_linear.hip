@@ -3353,9 +3353,27 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
     for (const auto& s : h->steps) max_r = std::max(max_r, s.plan.R);
     const int64_t row_cap = ((int64_t(1) << 31) - 1024) / max_r;      // rows of a pass are indexed with 32 bits
     const bool split_ok = !(desc->flags & TN_FLAG_NO_SPLIT_K) && h->elt == 2;
+    auto step_need = [&](const DevStep& s, int64_t chunk) {
+        int64_t need = 0;
+        for (int64_t t = 1; t <= chunk; ++t) {
+            if (t * s.plan.R >= kGemmMinRows && gemm_fits(s) && s.cmode != 0) break;
+            SplitCfg c = split_config(s, t * s.plan.R);
+            if (!c.use) break;          // larger passes only add tiles
+            need = std::max(need, c.partial_bytes);
+        }
+        // the matrix-product kernel takes as many K ranges as the buffer has room for: sized for row counts up to where
+        // the tiles alone fill the chip
+        if (gemm_fits(s))
+            for (int64_t t = 1; t <= chunk && t * s.plan.R <= 8192; t += std::max<int64_t>(1, t / 8))
+                if (t * s.plan.R >= kGemmMinRows) need = std::max(need, gemm_choice(h, s, t * s.plan.R, kMaxPartialBytes).partial_bytes);
+        return need;
+    };
     auto partial_need = [&](int64_t chunk) {
         int64_t need = 0;
         if (!split_ok) return need;
+        // a backward pass runs its steps, both ways, with the same buffer
+        for (size_t i = 0; h->trainable && i < h->steps.size(); ++i)
+            need = std::max({need, step_need(h->steps[i], h->bwd_chunk), i > 0 ? step_need(h->bwd[i], h->bwd_chunk) : 0});
         if (h->matrix)
             for (int64_t t = h->mat_ranges.front().first; t <= std::min<int64_t>(h->max_tokens, 4096); t += std::max<int64_t>(1, t / 8))
                 need = std::max(need, gemm_choice(h, h->mat_y, t, kMaxPartialBytes).partial_bytes);
@@ -3372,19 +3390,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
         if (h->lazy)
             for (int64_t t = h->lazy_min_tokens; t <= std::min<int64_t>(h->max_tokens, 4 * int64_t(h->num_cus)); ++t)
                 need = std::max(need, kron_geometry(h, h->lazy_dims, t, kMaxPartialBytes).partial_bytes);
-        for (const auto& s : h->steps)
-            for (int64_t t = 1; t <= chunk; ++t) {
-                if (t * s.plan.R >= kGemmMinRows && gemm_fits(s) && s.cmode != 0) break;
-                SplitCfg c = split_config(s, t * s.plan.R);
-                if (!c.use) break;          // larger passes only add tiles
-                need = std::max(need, c.partial_bytes);
-            }
-        // the matrix-product kernel takes as many K ranges as the buffer has room for: sized for row counts up to where
-        // the tiles alone fill the chip
-        for (const auto& s : h->steps)
-            if (gemm_fits(s))
-                for (int64_t t = 1; t <= chunk && t * s.plan.R <= 8192; t += std::max<int64_t>(1, t / 8))
-                    if (t * s.plan.R >= kGemmMinRows) need = std::max(need, gemm_choice(h, s, t * s.plan.R, kMaxPartialBytes).partial_bytes);
+        for (const auto& s : h->steps) need = std::max(need, step_need(s, chunk));
         return need;
     };
     // a lazily merged plan needs room for its slices: in the caller's block they share the space of the two

@@ -192,6 +192,16 @@ def test_short_k_of_more_than_a_row_tile(fake_hip):
         assert all("step_gemm_kernel" in [l.kernel for l in call] for call in got["launches"]), (shape, got["launches"])
 
 
+def test_backward_steps_have_room_for_their_sums(fake_hip):
+    """Few tokens: steps of a backward pass are cut into ranges of K like those of a forward, also where no forward step needs sums."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    spec = wl.TNSpec(wl.FORMAT_TT, "bf16", (5, 33, 64), (3, 2, 8), (1, 96, 96, 1))
+    got = create(fake_hip, spec, 1500, [], flags=tn.TN_FLAG_TRAINABLE, grad_tokens=[2])
+    kernels = [l.kernel for l in got["gradient_launches"][0]]
+    assert "step_mfma_pipe_kernel" not in kernels and kernels[kernels.index("step_split_reduce_kernel") - 1] == "step_split_kernel", kernels
+
+
 def test_tiles_of_the_matrix_product_tests(fake_hip):
     """The calls of the GPU tests that name a tile of the matrix-product kernel, or its form for short K, take it."""
     import workloads as wl
