@@ -1830,11 +1830,13 @@ int prepare_lazy(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
 }
 
 // What one launch of a product takes, in us: its tiles, or the stores of its output (W of 10240 x 4096 in 22 us, 84 MB; in two parts 3.5 TB/s).
-// Without the form for short K, which W's product of a narrow bond runs on, W was priced 7 us too high.
-constexpr float kGemmStoreBytesPerUs = 4e6f;
+// Without the form for short K, which W's product of a narrow bond runs on, W was priced 7 us too high. The price of a tile has 3 us of a
+// launch in it, 3 more are what a launch costs a program that does not replay a graph. With 5, two products of 3.2 and 4.4 us of a train of two
+// cores (40 x 8, 32 x 16, rank 24) were left for steps that take 12.6 to 15.2 at 33 to 500 tokens, 8.7 to 8.9 so.
+constexpr float kGemmStoreBytesPerUs = 4e6f, kGemmLaunchUs = 3.f;
 float product_us(const tn_linear_s* h, const DevStep& s) {
     const bool plain = !s.a_lo && !s.b_lo && !s.out_lo;
-    return 5.f + std::max(gemm_choice(h, s, s.plan.R, 0, plain).us, float(s.plan.R) * float(s.plan.C) * (plain ? 2.f / kGemmStoreBytesPerUs : 4.f / 3.5e6f));
+    return kGemmLaunchUs + std::max(gemm_choice(h, s, s.plan.R, 0, plain).us, float(s.plan.R) * float(s.plan.C) * (plain ? 2.f / kGemmStoreBytesPerUs : 4.f / 3.5e6f));
 }
 
 constexpr int64_t kMatrixNoEnd = std::numeric_limits<int64_t>::max();
@@ -1851,10 +1853,10 @@ bool takes_matrix(const tn_linear_s* h, int64_t tokens) {
 // The other orders are priced at the rates their kernels reach at many tokens (FLOP per us: chained pair kernel 1.3e9, one
 // launch per step 0.45e9; the Kronecker-sum kernel by kron_us). Measured, us per call in this order / in the other: ring
 // 25600 -> 5120 of rank 32 343 / 410 at 96 tokens, 767 / 8109 at 2048, 1955 / 30730 at 8192; ring 5120 -> 8192 of rank 96 776 /
-// 911 at 48 tokens, 885 / 35579 at 2048; train 5120 -> 25600 of rank 96 226 / 207 at 387 tokens, 226 / 391 at 420; train 5120 -> 8192 of rank 64 107 / 188 at 1202 tokens, 143 / 199 at
+// 911 at 48 tokens, 885 / 35579 at 2048; train 5120 -> 25600 of rank 96 226 / 207 at 387 tokens, 226 / 391 at 420; train 5120 -> 8192 of rank 64 106 / 184 at 1138 tokens, 143 / 199 at
 // 2048, 488 / 792 at 8192; of rank 32, whose chain has little more than 2 M N, 100 / 81 at 1000, 99 / 145 at 1025, 145 / 154 at 2048.
 // Of 500 such pairs (trains and rings of ranks 32 to 96, five projections, 16 to 8192 tokens) this order is never taken where it is more than 6 %
-// slower; it is left where it is up to 1.8 times as fast (train 5120 -> 8192 of rank 64, 103 / 185 at 1100 tokens): the chained pair kernel is priced
+// slower; it is left where it is up to 1.8 times as fast (train 5120 -> 8192 of rank 64, 103 / 181 at 1060 tokens): the chained pair kernel is priced
 // by the token, while it takes rounds of workgroups.
 int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     if (h->plan.dtype != TN_DTYPE_BF16 ||
@@ -1904,7 +1906,7 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
         }
         return r;
     };
-    if (ranges(5.f + float(h->plan.M) * float(h->plan.N) * 2.f / kGemmStoreBytesPerUs).empty()) return TN_OK;
+    if (ranges(kGemmLaunchUs + float(h->plan.M) * float(h->plan.N) * 2.f / kGemmStoreBytesPerUs).empty()) return TN_OK;
     if (!matrix_plan_of(h, desc)) return TN_OK;
     const tn::MatrixPlan& m = h->matrix_plans.m;
     h->mat_bytes = m.w_elems * 2;

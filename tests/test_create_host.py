@@ -192,6 +192,14 @@ def test_short_k_of_more_than_a_row_tile(fake_hip):
         assert all("step_gemm_kernel" in [l.kernel for l in call] for call in got["launches"]), (shape, got["launches"])
 
 
+def test_two_small_products_before_longer_steps(fake_hip):
+    """A train of two cores of small modes: W and Y are two short products, the steps two longer ones."""
+    import workloads as wl
+    spec = wl.TNSpec(wl.FORMAT_TT, "bf16", (40, 8), (32, 16), (1, 24, 1))
+    got = create(fake_hip, spec, 1500, [], tokens=(33, 100, 500, 1500))
+    assert [[l.kernel for l in call] for call in got["launches"]] == [["step_gemm_kernel"] * 2] * 4
+
+
 def test_backward_steps_have_room_for_their_sums(fake_hip):
     """Few tokens: steps of a backward pass are cut into ranges of K like those of a forward, also where no forward step needs sums."""
     import paper_2602_01613_amd as tn
