@@ -1885,7 +1885,7 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     // There may be several such ranges: the prices are staircases, in row tiles here and in rounds of workgroups of the Kronecker-sum kernel.
     // They are looked for on a grid of counts and their ends between its points: with the ends on the grid, a train 5120 -> 8192 of rank 64
     // took this order at 1260 tokens and not at 1259 or 1261.
-    auto ranges = [&](float build_us) {
+    auto ranges = [&](float build_us, bool any = false) {      // any: whether there are, the first point is enough
         std::vector<std::pair<int64_t, int64_t>> r;
         auto changes = [&](int64_t t, bool in) {
             const float us = build_us + gemm_choice(h, y, t, kMaxPartialBytes).us, other = other_us(t);
@@ -1895,6 +1895,7 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
         int64_t last = 7;
         for (int64_t t = 8; t <= desc->max_tokens; last = t, t += t < 64 ? 8 : t / 16) {
             if (!changes(t, in)) continue;
+            if (any) return std::vector<std::pair<int64_t, int64_t>>{{t, kMatrixNoEnd}};
             int64_t at = t;                        // the first count of this interval that does, not the grid's
             for (int64_t lo = last; at - lo > 1;) {
                 const int64_t mid = lo + (at - lo) / 2;
@@ -1906,7 +1907,7 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
         }
         return r;
     };
-    if (ranges(kGemmLaunchUs + float(h->plan.M) * float(h->plan.N) * 2.f / kGemmStoreBytesPerUs).empty()) return TN_OK;
+    if (ranges(kGemmLaunchUs + float(h->plan.M) * float(h->plan.N) * 2.f / kGemmStoreBytesPerUs, true).empty()) return TN_OK;
     if (!matrix_plan_of(h, desc)) return TN_OK;
     const tn::MatrixPlan& m = h->matrix_plans.m;
     h->mat_bytes = m.w_elems * 2;
@@ -3392,7 +3393,8 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
         if (h->lazy)
             for (int64_t t = h->lazy_min_tokens; t <= std::min<int64_t>(h->max_tokens, 4 * int64_t(h->num_cus)); ++t)
                 need = std::max(need, kron_geometry(h, h->lazy_dims, t, kMaxPartialBytes).partial_bytes);
-        for (const auto& s : h->steps) need = std::max(need, step_need(s, chunk));
+        if (!h->trainable || chunk > h->bwd_chunk)
+            for (const auto& s : h->steps) need = std::max(need, step_need(s, chunk));
         return need;
     };
     // a lazily merged plan needs room for its slices: in the caller's block they share the space of the two
