@@ -43,6 +43,7 @@ namespace {
 #include "kernels/stream.hpp"
 #include "kernels/chained.hpp"
 #include "kernels/kronsum.hpp"
+#include "kernels/krondirect.hpp"
 #include "kernels/grad.hpp"
 
 // ---------------------------------------------------------------------------------------------
@@ -90,6 +91,15 @@ struct DevProduct {
 };
 
 }  // namespace
+
+// A call on the kernel that makes the slices on chip: blocks of res_per x str_per values of the bond, a workgroup each.
+struct DirectGeom {
+    int res_per = 1, str_per = 1, str_blocks = 1, n_splits = 1;
+    int64_t partial_bytes = 0;
+    float us = 0.f;
+    bool taken = false;       // the price is below that of the slices in memory
+};
+constexpr int64_t kDirectMaxTokens = 16;      // the price grows with the token: rings of rank 32 pay up to here, of rank 96 up to 3 tokens
 
 struct tn_linear_s {
     tn::Plan plan;
@@ -147,6 +157,11 @@ struct tn_linear_s {
     KronGenMfmaArgs lazy_gen_mfma[2];
     size_t lazy_gen_smem[2] = {0, 0};
     void* lazy_gen_tables[2] = {nullptr, nullptr};
+    // calls of a few tokens of such a layer: the slices made on chip (tn::DirectPlan); what it keeps is in lazy_sources
+    bool direct = false;
+    int direct_cfg = 0, direct_steps = 1;
+    KronDirectArgs direct_args;               // what does not depend on the call
+    DirectGeom direct_geom[kDirectMaxTokens + 1];
     // calls whose token count lies in one of mat_ranges: the tensors contracted with each other into W, in the workspace and per
     // call, and then Y = X W^T (tn_matrix.hpp)
     bool matrix = false;
@@ -1574,6 +1589,111 @@ int launch_kron_lazy(const tn_linear_s* h, const Workspace& w, const void* x, vo
     return launch_kron(h, w, k, x, y, tokens, st);
 }
 
+template <int CFG, int SS>
+int direct_entry(const KronDirectArgs* p, uint32_t grid, hipStream_t st) {
+    constexpr size_t smem = KronDirectShape<CFG, SS>::SMEM;
+    if (!p)         // configuration call (create time)
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(step_krondirect_kernel<CFG, SS>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   int(smem)) == hipSuccess
+                   ? TN_OK
+                   : TN_ERR_HIP;
+    hipLaunchKernelGGL((step_krondirect_kernel<CFG, SS>), dim3(grid), dim3(256), smem, st, *p);
+    return TN_OK;
+}
+
+template <int CFG>
+int direct_of(int steps, const KronDirectArgs* p, uint32_t grid, hipStream_t st) {
+    static_assert(tn::kDirectMaxSteps == 3, "one case per number of steps");
+    switch (steps) {
+        case 1: return direct_entry<CFG, 1>(p, grid, st);
+        case 2: return direct_entry<CFG, 2>(p, grid, st);
+        case 3: return direct_entry<CFG, 3>(p, grid, st);
+        default: return TN_ERR_INVALID_ARG;
+    }
+}
+
+int direct_dispatch(int cfg, int steps, const KronDirectArgs* p, uint32_t grid, hipStream_t st) {
+    static_assert(tn::kDirectConfigs == 5, "one case per instantiation");
+    switch (cfg) {
+        case 0: return direct_of<0>(steps, p, grid, st);
+        case 1: return direct_of<1>(steps, p, grid, st);
+        case 2: return direct_of<2>(steps, p, grid, st);
+        case 3: return direct_of<3>(steps, p, grid, st);
+        case 4: return direct_of<4>(steps, p, grid, st);
+        default: return TN_ERR_INVALID_ARG;
+    }
+}
+
+// Sums a split of a token leaves: whole tiles of the output.
+int64_t direct_sums(const tn_linear_s* h) {
+    return int64_t((h->direct_args.O1 + 15) / 16) * ((h->direct_args.C1 + 15) / 16) * 256;
+}
+
+// Blocks of the bond for the workgroups of a call, one to a compute unit, of the least time: the launches, a value of the bond
+// (0.2 us, 0.5 with the resident cores in LDS, and 12 ns per MFMA of a wave), a turn of the resident cores, and the partial sums written and read. Expected /
+// measured, us: rings of one token 5120 -> 8192 rank 96 57 / 50 to 56, rank 32 17 / 16; 5120 -> 25600 rank 96 108 / 104 to 111, rank 32 30 / 31;
+// 25600 -> 5120 rank 96 99 / 102 to 109; 5120 -> 1024 rank 96 32 / 26 to 29; of two tokens 5120 -> 8192 rank 96 101 / 86.
+DirectGeom direct_geometry(const tn_linear_s* h, int64_t tokens, int64_t partial_cap) {
+    const KronDirectArgs& a = h->direct_args;
+    const int* g = tn::kDirectConfig[h->direct_cfg];
+    const int mfmas = h->direct_steps * (g[6] * g[7] + g[9] * g[10]) + g[2] * (g[0] * g[1] + g[3] * ((g[0] + 1) / 2));
+    const float per_value = (g[12] ? 0.5f : 0.2f) + float(mfmas) * 0.0123f;
+    const int64_t slots = std::max<int64_t>(1, h->num_cus / tokens);
+    DirectGeom best;
+    best.us = std::numeric_limits<float>::max();
+    for (int str_per = 1; str_per <= a.n_str; ++str_per) {
+        const int str_blocks = (a.n_str + str_per - 1) / str_per;
+        if ((a.n_str + str_blocks - 1) / str_blocks != str_per) continue;        // as many blocks with fewer values each
+        for (int64_t want = std::max<int64_t>(1, slots / str_blocks); want >= 1; want /= 2) {
+            const int64_t blocks = std::min<int64_t>(want, a.n_res);
+            DirectGeom c;
+            c.str_per = str_per;
+            c.str_blocks = str_blocks;
+            c.res_per = int((a.n_res + blocks - 1) / blocks);
+            c.n_splits = (a.n_res + c.res_per - 1) / c.res_per * str_blocks;
+            c.partial_bytes = c.n_splits > 1 ? int64_t(c.n_splits) * tokens * direct_sums(h) * 4 : 0;
+            const int64_t rounds = (tokens * c.n_splits + h->num_cus - 1) / h->num_cus;
+            c.us = 9.f + float(rounds) * float(c.res_per) * (1.f + float(str_per) * per_value) + float(c.partial_bytes) / 2e6f;
+            if (c.partial_bytes <= partial_cap && c.us < best.us) best = c;
+        }
+    }
+    return best;
+}
+
+// The calls that take it, against the slices in memory (of a layer that shares its workspace: written by every call: two launches, 3.4 TB/s). us per
+// call, made on chip / in memory, shared workspace, then a workspace of its own: rings 5120 -> 8192 of rank 96 at one token 56 / 179, 50 / 95, at 2
+// 86 / 180, 86 / 97, at 4 157 / 185, 157 / 100; of rank 32 16 / 50, 16 / 30, at 4 25 / 50, 25 / 36; 5120 -> 25600 of rank 64 at one 56 / 144,
+// 52 / 102; 25600 -> 5120 of rank 96 109 / 294, 102 / 177; 5120 -> 1024 of rank 96 29 / 61, 26 / 32, at 2 43 / 61, 43 / 32; trains 25600 ->
+// 5120 of rank 96 at one 18 / 33, 17 / 24, at 4 23 / 35, 22 / 26.
+void price_direct(tn_linear_s* h) {
+    for (int64_t t = 1; h->direct && t <= std::min(h->max_tokens, kDirectMaxTokens); ++t) {
+        DirectGeom g = direct_geometry(h, t, h->partial ? h->partial_bytes : 0);
+        const float slices = h->lazy_slices_kept ? 0.f : 8.f + float(h->lazy_slice_bytes) / 3.4e6f;
+        g.taken = g.us < kron_us(h, h->lazy_dims, kron_geometry(h, h->lazy_dims, t, h->partial ? h->partial_bytes : 0)) + slices;
+        h->direct_geom[t] = g;
+    }
+}
+
+int launch_direct(const tn_linear_s* h, const Workspace& w, const DirectGeom& g, const void* x, void* y, int64_t tokens, hipStream_t st) {
+    KronDirectArgs p = h->direct_args;
+    p.X = x;
+    p.Y = g.n_splits > 1 ? w.partial : y;
+    p.tokens = int32_t(tokens);
+    p.res_per = g.res_per;
+    p.str_per = g.str_per;
+    p.str_blocks = g.str_blocks;
+    p.n_splits = g.n_splits;
+    if (g.partial_bytes > (w.partial ? w.partial_bytes : 0)) return TN_ERR_UNSUPPORTED;      // never write past the buffer
+    const int rc = direct_dispatch(h->direct_cfg, h->direct_steps, &p, uint32_t(tokens * g.n_splits), st);
+    if (rc != TN_OK) return rc;
+    if (g.n_splits > 1) {
+        p.Y = y;
+        hipLaunchKernelGGL(krondirect_reduce_kernel, dim3(uint32_t(tokens * direct_sums(h) / 64)), dim3(256), 0, st, p,
+                           static_cast<const float*>(w.partial));
+    }
+    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
+}
+
 // Token count from which a lazily merged plan replaces the compact steps: every call. With the one-token form of
 // the Kronecker-sum kernel (four waves share the token) rebuilding the slices and streaming them once is as fast as
 // the compact steps or faster on every ring class of the 64-layer stack (us per one-token call, rebuilt / compact:
@@ -1827,6 +1947,61 @@ int prepare_lazy(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     h->lazy_dims = d;
     h->lazy_min_tokens = kLazyMinTokens;
     return TN_OK;
+}
+
+// A lazily merged layer: the plan with the slices made on chip, where an instantiation holds its shape.
+int prepare_direct(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
+    if (!h->lazy || (desc->flags & (TN_FLAG_NO_DECODE_FUSION | TN_FLAG_SCALAR_GENERATE))) return TN_OK;
+    tn::Plan net;
+    tn::DirectPlan d;
+    int tensors[2][2];
+    if (tn::build_network(desc, &net) != TN_OK || !tn::merged_tensors(net, h->lazy_plan, tensors) || !tn::make_direct_plan(net, tensors, &d)) return TN_OK;
+    KronDirectArgs& a = h->direct_args;
+    memset(&a, 0, sizeof(a));
+    for (int w = 0; w < 2; ++w)
+        for (int side = 0; side < 2; ++side) {
+            void* p = nullptr;
+            const int rc = keep_operand(h, desc, d.src[w][side], 32 * d.steps, true, &p, st, &h->lazy_sources);
+            if (rc != TN_OK) return rc;
+            a.src[w][side] = p;
+            a.tiles[w][side] = int32_t(d.tiles[w][side]);
+        }
+    std::vector<int32_t> tab;
+    size_t at[6];
+    const std::vector<int32_t>* all[4] = {&d.xrow, &d.xcol, &d.yrow, &d.ycol};
+    for (int i = 0; i < 4; ++i) {
+        at[i] = tab.size();
+        tab.insert(tab.end(), all[i]->begin(), all[i]->end());
+    }
+    for (int w = 0; w < 2; ++w) {
+        at[4 + w] = tab.size();
+        tab.resize(tab.size() + (d.unit[w].size() + 1) / 2);
+        memcpy(&tab[at[4 + w]], d.unit[w].data(), d.unit[w].size() * sizeof(uint16_t));
+    }
+    void* mem = nullptr;
+    if (hipMalloc(&mem, tab.size() * sizeof(int32_t)) != hipSuccess) return TN_ERR_ALLOC;
+    h->lazy_sources.push_back(mem);
+    h->packed_bytes += int64_t(tab.size() * sizeof(int32_t));
+    const int32_t* dev = static_cast<const int32_t*>(mem);
+    a.xrow = dev + at[0];
+    a.xcol = dev + at[1];
+    a.yrow = dev + at[2];
+    a.ycol = dev + at[3];
+    a.unit[0] = reinterpret_cast<const uint16_t*>(dev + at[4]);
+    a.unit[1] = reinterpret_cast<const uint16_t*>(dev + at[5]);
+    a.N = h->plan.N;
+    a.M = h->plan.M;
+    a.A = int32_t(d.A);
+    a.K0 = int32_t(d.K0);
+    a.O1 = int32_t(d.O1);
+    a.C1 = int32_t(d.C1);
+    a.n_res = int32_t(d.n_res);
+    a.n_str = int32_t(d.n_str);
+    a.x_vec8 = d.x_vec8 ? 1 : 0;
+    h->direct_cfg = d.cfg;
+    h->direct_steps = d.steps;
+    h->direct = true;
+    return upload_tables(h, std::move(tab), mem, st);
 }
 
 // What one launch of a product takes, in us: its tiles, or the stores of its output (W of 10240 x 4096 in 22 us, 84 MB; in two parts 3.5 TB/s).
@@ -2294,6 +2469,8 @@ int configure_kernels(int device) {
                                 hipFuncAttributeMaxDynamicSharedMemorySize, int(kSmallChainMaxLds)) != hipSuccess)
             rc = TN_ERR_HIP;
     for (int cfg = 0; cfg < tn::kKronConfigs && rc == TN_OK; ++cfg) rc = kron_dispatch(cfg, nullptr, 0, nullptr);
+    for (int cfg = 0; cfg < tn::kDirectConfigs; ++cfg)
+        for (int steps = 1; steps <= tn::kDirectMaxSteps && rc == TN_OK; ++steps) rc = direct_dispatch(cfg, steps, nullptr, 0, nullptr);
     if (rc == TN_OK) rc = gen_mfma_dispatch(nullptr, 0, nullptr);
     if (rc == TN_OK) rc = gen_mfma_both_dispatch(nullptr, nullptr, 0, nullptr);
     if (rc == TN_OK && device >= 0 && device < 64) {
@@ -3325,6 +3502,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
     if (rc == TN_OK) {
         const int64_t before = h->packed_bytes;
         rc = prepare_lazy(h, desc, st);
+        if (rc == TN_OK) rc = prepare_direct(h, desc, st);
         h->lazy_kept_bytes = h->packed_bytes - before;
     }
     if (rc == TN_OK) {
@@ -3393,6 +3571,8 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
         if (h->lazy)
             for (int64_t t = h->lazy_min_tokens; t <= std::min<int64_t>(h->max_tokens, 4 * int64_t(h->num_cus)); ++t)
                 need = std::max(need, kron_geometry(h, h->lazy_dims, t, kMaxPartialBytes).partial_bytes);
+        for (int64_t t = 1; h->direct && t <= std::min(h->max_tokens, kDirectMaxTokens); ++t)
+            need = std::max(need, direct_geometry(h, t, kMaxPartialBytes).partial_bytes);
         if (!h->trainable || chunk > h->bwd_chunk)
             for (const auto& s : h->steps) need = std::max(need, step_need(s, chunk));
         return need;
@@ -3410,7 +3590,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
                 free_handle(h);
                 return TN_ERR_HIP;
             }
-            h->lazy = false;
+            h->lazy = h->direct = false;
             h->packed_bytes -= h->lazy_kept_bytes;
             h->lazy_kept_bytes = 0;
             for (void* v : h->lazy_sources) (void)hipFree(v);
@@ -3515,6 +3695,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
         }
         h->lazy_slices_kept = true;
     }
+    price_direct(h);
     {
         std::vector<int> fuse(h->steps.size(), 0);
         for (size_t i = 0; i < h->steps.size(); ++i) fuse[i] = h->steps[i].fuse_next ? 1 : 0;
@@ -3590,6 +3771,13 @@ int forward_in(tn_linear_s* h, const Workspace& w, bool allow_lazy, const void* 
     const bool use_pair = h->pair && tokens >= h->pair_min_tokens;
     const bool use_kron = h->kron && tokens >= h->kron_min_tokens;
     const bool use_lazy = allow_lazy && h->lazy && tokens >= h->lazy_min_tokens;
+    if (use_lazy && !use_pair && !use_kron && tokens <= kDirectMaxTokens && h->direct_geom[tokens].taken) {
+        ProfScope prof(h, 0, st);
+        if (!prof.ok) return TN_ERR_HIP;
+        const int rc = launch_direct(h, w, h->direct_geom[tokens], x, y, tokens, st);
+        prof.done();
+        return rc;
+    }
     if (use_pair || use_kron || use_lazy) {
         // both steps in one launch, no intermediate in memory; passes only bound the 32-bit token index
         // (and, for the Kronecker-sum kernel, keep a call's partial sums within their buffer)

@@ -527,18 +527,23 @@ struct SlicePlan {
     int64_t h1_offset = 0, bytes = 0;                   // of the second array, and of both
 };
 
-// `q`: the plan of two steps whose tensors are merged from two of the caller's each; `net`: the network before the merges.
-inline bool make_slice_plan(const Plan& net, const Plan& q, const KronDims& d, SlicePlan* out) {
-    using namespace detail;
+// `q`: a plan of two steps whose tensors are merged from two of the caller's each; `net`: the network before the merges.
+inline bool merged_tensors(const Plan& net, const Plan& q, int (&tensors)[2][2]) {
     const int nc = net.n_caller_tensors;
-    const int *cfg = kKronConfig[d.cfg], at = cfg[0], ks0 = cfg[1], o2t = cfg[2], o1t = cfg[3];
-    int tensors[2][2];
     for (int h = 0; h < 2; ++h) {
         const int mi = q.steps[size_t(h)].slot - nc;
         if (mi < 0 || mi >= int(q.merges.size()) || q.merges[size_t(mi)].p_slot >= nc || q.merges[size_t(mi)].q_slot >= nc) return false;
         tensors[h][0] = q.merges[size_t(mi)].p_slot;
         tensors[h][1] = q.merges[size_t(mi)].q_slot;
     }
+    return true;
+}
+
+inline bool make_slice_plan(const Plan& net, const Plan& q, const KronDims& d, SlicePlan* out) {
+    using namespace detail;
+    const int *cfg = kKronConfig[d.cfg], at = cfg[0], ks0 = cfg[1], o2t = cfg[2], o1t = cfg[3];
+    int tensors[2][2];
+    if (!merged_tensors(net, q, tensors)) return false;
     if (d.A % 16 || d.K0 % 8) return false;
     std::vector<int64_t> ext = net.extent;
     const std::vector<int> bond = [&] {
@@ -613,6 +618,189 @@ inline bool make_slice_plan(const Plan& net, const Plan& q, const KronDims& d, S
     out->x_vec8 = run_length(out->xcol, 8) == 8 && all_multiple_of(out->xrow, 8);
     out->h1_offset = (elems[0] * 2 + 255) & ~int64_t(255);
     out->bytes = out->h1_offset + ((elems[1] * 2 + 255) & ~int64_t(255));
+    return true;
+}
+
+// ---- slices of the Kronecker-sum kernel made on chip ----
+// kernels/krondirect.hpp: per value of the bond a workgroup makes both slices from slabs of the cores, for calls of a few
+// tokens. A row of kDirectConfig is an instantiation:
+//   AT tiles of 16 of a, KS steps of 32 of k; a wave has O1W tiles of 16 of o1 and O2W of o2, the four waves in W1 columns of o1;
+//   per half, WS of the waves along the streamed core's tiles, F of its tiles and C of the resident one's to a wave;
+//   whether the rows of the second half's product are the streamed core's (the first half's always are); resident cores in LDS.
+constexpr int kDirectConfigs = 5;
+constexpr int kDirectConfig[kDirectConfigs][13] = {
+    {5, 2, 1, 8, 4, 4, 1, 4, 4, 1, 10, 1, 0},
+    {5, 2, 1, 1, 2, 4, 1, 2, 2, 1, 3, 1, 0},
+    {8, 2, 1, 5, 4, 4, 1, 4, 4, 1, 10, 1, 0},
+    {4, 3, 3, 10, 4, 2, 3, 5, 4, 2, 5, 1, 0},
+    {10, 5, 1, 5, 4, 4, 2, 5, 2, 3, 5, 0, 1}};
+constexpr int kDirectMaxSteps = 3;                      // of 32, of the bond inside a half
+
+struct DirectPlan {
+    int cfg = -1, steps = 1;
+    SourceOp src[2][2];                                 // per half: resident, streamed core; rows: its value of the bond, then its modes
+    int64_t tiles[2][2] = {{0, 0}, {0, 0}};             // of 16 rows of a slab
+    int64_t n_res = 1, n_str = 1;
+    int64_t A = 0, K0 = 0, O1 = 0, C1 = 0;
+    std::vector<int32_t> xrow, xcol, yrow, ycol;
+    std::vector<uint16_t> unit[2];                      // [row tile][column tile][lane]: LDS position / 8 in the slice
+    bool x_vec8 = false;
+};
+
+// Position in its slice, in bytes, of column o and contracted index k (w = 0), or a (w = 1: numbered within 32 as the
+// accumulators of the first product come out).
+inline int64_t direct_position(int w, int64_t o, int64_t k, int64_t steps) {
+    const int64_t block = ((o / 16) * steps + k / 32) * 1024;
+    return w == 0 ? block + ((k % 32) / 8 * 16 + o % 16) * 16 + (k % 8) * 2
+                  : block + ((k % 16) / 4 * 16 + o % 16) * 16 + (k % 32) / 16 * 8 + (k % 4) * 2;
+}
+
+// `tensors`: the two of each half. False where no instantiation holds the shape.
+inline bool make_direct_plan(const Plan& net, const int (&tensors)[2][2], DirectPlan* out) {
+    using namespace detail;
+    const std::vector<int64_t>& ext = net.extent;
+    struct Core {
+        int t = -1, m = -1, n = -1;
+        int64_t M = 1, N = 1;
+    };
+    auto core_of = [&](int t, Core* c) {
+        c->t = t;
+        for (int i : net.tensors[size_t(t)].idx) {
+            if (ext[size_t(i)] == 1) continue;
+            if (contains(net.y_idx, i)) {
+                if (c->m >= 0) return false;
+                c->m = i;
+            }
+            if (contains(net.x_idx, i)) {
+                if (c->n >= 0) return false;
+                c->n = i;
+            }
+        }
+        if (c->m < 0 || c->n < 0 || net.tensors[size_t(t)].trace_extent != 1) return false;
+        c->M = ext[size_t(c->m)];
+        c->N = ext[size_t(c->n)];
+        return c->M * c->N % 16 == 0;
+    };
+    Core cores[2][2];
+    int inner[2];                                       // the id contracted inside a half
+    std::vector<int> bond;
+    for (int h = 0; h < 2; ++h) {
+        for (int i = 0; i < 2; ++i)
+            if (!core_of(tensors[h][i], &cores[h][i])) return false;
+        inner[h] = -1;
+        for (int i : shared_ids(net.tensors[size_t(tensors[h][0])], net.tensors[size_t(tensors[h][1])])) {
+            if (ext[size_t(i)] == 1) continue;
+            if (inner[h] >= 0) return false;
+            inner[h] = i;
+        }
+        if (inner[h] < 0) return false;
+    }
+    for (int t : tensors[0])
+        for (int i : net.tensors[size_t(t)].idx)
+            for (int u : tensors[1])
+                if (ext[size_t(i)] > 1 && contains(net.tensors[size_t(u)].idx, i) && !contains(bond, i)) bond.push_back(i);
+    if (bond.empty() || bond.size() > 2) return false;
+    const int64_t longest = std::max(ext[size_t(inner[0])], ext[size_t(inner[1])]);
+    const int steps = int((longest + 31) / 32);
+    if (steps > kDirectMaxSteps) return false;
+    // every id of a core is accounted for: its modes, the half's own bond, a value of the bond between the halves
+    for (int h = 0; h < 2; ++h)
+        for (const Core& c : cores[h])
+            for (int i : net.tensors[size_t(c.t)].idx)
+                if (ext[size_t(i)] > 1 && i != c.m && i != c.n && i != inner[h] && !contains(bond, i)) return false;
+    auto x_stride = [&](const std::vector<int>& layout, int id) {
+        int64_t st = 1;
+        for (size_t j = layout.size(); j-- > 0 && layout[j] != id;) st *= ext[size_t(layout[j])];
+        return st;
+    };
+    int64_t best = 0;
+    struct Pick {
+        int cfg, first, res;
+    } pick{-1, 0, 0};
+    auto of_half = [&](int first, int w) { return w == 0 ? first : 1 - first; };
+    // the resident core of half h is the one that carries bond[res], the streamed one must not
+    auto resident = [&](int h, int res) {
+        const bool c0 = contains(net.tensors[size_t(cores[h][0].t)].idx, bond[size_t(res)]);
+        const bool c1 = contains(net.tensors[size_t(cores[h][1].t)].idx, bond[size_t(res)]);
+        return c0 == c1 ? -1 : c0 ? 0 : 1;
+    };
+    for (int first = 0; first < 2; ++first)
+        for (int res = 0; res < int(bond.size()); ++res) {
+            const int i0 = resident(of_half(first, 0), res), i1 = resident(of_half(first, 1), res);
+            if (i0 < 0 || i1 < 0) continue;
+            if (bond.size() == 2) {
+                const int j0 = resident(of_half(first, 0), 1 - res), j1 = resident(of_half(first, 1), 1 - res);
+                if (j0 != 1 - i0 || j1 != 1 - i1) continue;
+            }
+            const Core &R0 = cores[of_half(first, 0)][i0], &S0 = cores[of_half(first, 0)][1 - i0];
+            const Core &R1 = cores[of_half(first, 1)][i1], &S1 = cores[of_half(first, 1)][1 - i1];
+            const int64_t K0 = R0.N * S0.N, A = R1.N * S1.N, O1 = R0.M * S0.M, C1 = R1.M * S1.M;
+            if (S0.N % 4 || K0 % 8 || A % 4) continue;
+            const int64_t t[2][2] = {{R0.M * R0.N / 16, S0.M * S0.N / 16}, {R1.M * R1.N / 16, S1.M * S1.N / 16}};
+            for (int c = 0; c < kDirectConfigs; ++c) {
+                const int* g = kDirectConfig[c];
+                const int at = g[0], ks = g[1], o1w = g[2], o2w = g[3], w1 = g[4], as = (at + 1) / 2;
+                if ((g[11] ? S1.N : R1.N) % 4) continue;
+                if (A > 16 * at || K0 > 32 * ks || O1 > 16 * o1w * w1 || C1 > 16 * o2w * (4 / w1)) continue;
+                if (t[0][1] > g[5] * g[6] || t[0][0] > (4 / g[5]) * g[7] || t[1][1] > g[8] * g[9] || t[1][0] > (4 / g[8]) * g[10]) continue;
+                const int64_t mfmas = 4 * (int64_t(steps) * (g[6] * g[7] + g[9] * g[10]) + o1w * (at * ks + o2w * as));
+                // at least 35 % of it real, as in kron_shape
+                const double real = double(longest) * double(O1 * K0 + C1 * A) + double(O1) * double(A) * double(K0 + C1);
+                if (real < 0.35 * double(mfmas) * 8192.0) continue;
+                if (pick.cfg < 0 || mfmas < best) {
+                    pick = {c, first, res};
+                    best = mfmas;
+                }
+            }
+        }
+    if (pick.cfg < 0) return false;
+    const int* g = kDirectConfig[pick.cfg];
+    *out = DirectPlan();
+    out->cfg = pick.cfg;
+    out->steps = steps;
+    std::vector<int64_t> padded = ext;
+    for (int w = 0; w < 2; ++w) padded[size_t(inner[w])] = 32 * steps;
+    const int res_id = bond[size_t(pick.res)], str_id = bond.size() == 2 ? bond[size_t(1 - pick.res)] : -1;
+    out->n_res = ext[size_t(res_id)];
+    out->n_str = str_id >= 0 ? ext[size_t(str_id)] : 1;
+    for (int w = 0; w < 2; ++w) {
+        const int h = of_half(pick.first, w), i = resident(h, pick.res);
+        const Core &R = cores[h][i], &Q = cores[h][1 - i];
+        const bool rows_streamed = w == 0 || g[11];
+        const Core &row = rows_streamed ? Q : R, &col = rows_streamed ? R : Q;
+        for (int side = 0; side < 2; ++side) {
+            const Core& c = side == 0 ? R : Q;
+            std::vector<int> ids;
+            const int id = side == 0 ? res_id : str_id;
+            if (id >= 0) ids.push_back(id);
+            if (c.t == row.t) {
+                ids.push_back(c.m);
+                ids.push_back(c.n);
+            } else {
+                ids.push_back(c.n);
+                ids.push_back(c.m);
+            }
+            out->src[w][side] = source_op(net, padded, c.t, ids, {inner[h]});
+            out->tiles[w][side] = c.M * c.N / 16;
+            if (out->src[w][side].R > (int64_t(1) << 24)) return false;
+        }
+        // o = (rows' m, columns' m), k or a = (columns' n, rows' n)
+        const int64_t O = row.M * col.M, K = row.N * col.N, k_steps = w == 0 ? g[1] : (g[0] + 1) / 2;
+        std::vector<int32_t>&y = w == 0 ? out->yrow : out->ycol, &x = w == 0 ? out->xcol : out->xrow;
+        for (int64_t o = 0; o < O; ++o) y.push_back(int32_t(o / col.M * x_stride(net.y_idx, row.m) + o % col.M * x_stride(net.y_idx, col.m)));
+        for (int64_t k = 0; k < K; ++k) x.push_back(int32_t(k / row.N * x_stride(net.x_idx, col.n) + k % row.N * x_stride(net.x_idx, row.n)));
+        const int64_t tr = row.M * row.N / 16, tc = col.M * col.N / 16;
+        for (int64_t r = 0; r < tr; ++r)
+            for (int64_t c = 0; c < tc; ++c)
+                for (int64_t l = 0; l < 64; ++l) {
+                    const int64_t fr = 16 * r + 4 * (l / 16), fc = 16 * c + l % 16;
+                    const int64_t o = fr / row.N * col.M + fc % col.M, k = fc / col.M * row.N + fr % row.N;
+                    out->unit[w].push_back(uint16_t(direct_position(w, o, k, k_steps) / 8));
+                }
+        (w == 0 ? out->O1 : out->C1) = O;
+        (w == 0 ? out->K0 : out->A) = K;
+    }
+    out->x_vec8 = run_length(out->xcol, 8) == 8 && all_multiple_of(out->xrow, 8);
     return true;
 }
 

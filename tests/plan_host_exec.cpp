@@ -325,6 +325,62 @@ extern "C" int plan_host_slices(const tn_linear_desc* d, const double* const* te
     return 0;
 }
 
+// One token through the plan with the slices made on chip, tile by tile as kernels/krondirect.hpp walks it. 0 or, with no such plan, 1;
+// *cfg: the instantiation.
+extern "C" int plan_host_direct(const tn_linear_desc* d, const double* const* tensors, const double* x, double* y, int* cfg) {
+    tn_linear_desc halves = *d;
+    halves.flags |= TN_FLAG_MERGE_HALVES;
+    tn::Plan q, net;
+    tn::DirectPlan s;
+    int pairs[2][2];
+    if (tn::make_plan(&halves, &q) != TN_OK || q.steps.size() != 2 || q.merges.size() != 2 || tn::build_network(d, &net) != TN_OK ||
+        !tn::merged_tensors(net, q, pairs) || !tn::make_direct_plan(net, pairs, &s))
+        return 1;
+    const int* g = tn::kDirectConfig[s.cfg];
+    *cfg = s.cfg;
+    const int64_t steps[2] = {g[1], (g[0] + 1) / 2}, columns[2] = {s.O1, s.C1}, contracted[2] = {s.K0, s.A};
+    for (int64_t m = 0; m < net.M; ++m) y[m] = 0;
+    std::vector<double> D(size_t(s.A));
+    for (int64_t rr = 0; rr < s.n_res; ++rr)
+        for (int64_t rs = 0; rs < s.n_str; ++rs) {
+            std::vector<double> L[2];
+            for (int w = 0; w < 2; ++w) {
+                const int rows = w == 0 || g[11] ? 1 : 0;          // the side (resident, streamed) of the rows
+                const tn::SourceOp &R = s.src[w][rows], &C = s.src[w][1 - rows];
+                const int64_t slab[2] = {rr, rs}, tr = s.tiles[w][rows], tc = s.tiles[w][1 - rows];
+                if (int64_t(s.unit[w].size()) != tr * tc * 64) return -1;
+                L[w].assign(size_t((columns[w] + 15) / 16 * steps[w] * 512), 0.0);
+                std::vector<char> hit(L[w].size(), 0);
+                for (int64_t r = 0; r < tr; ++r)
+                    for (int64_t c = 0; c < tc; ++c)
+                        for (int64_t l = 0; l < 64; ++l)
+                            for (int64_t v = 0; v < 4; ++v) {
+                                const int64_t fr = (slab[rows] * tr + r) * 16 + 4 * (l / 16) + v, fc = (slab[1 - rows] * tc + c) * 16 + l % 16;
+                                double acc = 0;
+                                for (int64_t e = 0; e < R.K; ++e) acc += source_value(tensors, R, fr, e) * source_value(tensors, C, fc, e);
+                                const size_t at = size_t(s.unit[w][size_t((r * tc + c) * 64 + l)]) * 4 + size_t(v);
+                                if (at >= L[w].size() || hit[at]) return -2;
+                                hit[at] = 1;
+                                L[w][at] = acc;
+                            }
+                int64_t n = 0;
+                for (char h : hit) n += h;
+                if (n != columns[w] * contracted[w]) return -3;
+            }
+            for (int64_t o1 = 0; o1 < s.O1; ++o1) {
+                for (int64_t a = 0; a < s.A; ++a) {
+                    D[size_t(a)] = 0;
+                    for (int64_t k = 0; k < s.K0; ++k)
+                        D[size_t(a)] += x[s.xrow[size_t(a)] + s.xcol[size_t(k)]] * L[0][size_t(tn::direct_position(0, o1, k, steps[0]) / 2)];
+                }
+                for (int64_t o2 = 0; o2 < s.C1; ++o2)
+                    for (int64_t a = 0; a < s.A; ++a)
+                        y[s.yrow[size_t(o1)] + s.ycol[size_t(o2)]] += D[size_t(a)] * L[1][size_t(tn::direct_position(1, o2, a, steps[1]) / 2)];
+            }
+        }
+    return 0;
+}
+
 // The plan of the gradients alone: 0, or 1 when the layer has none.
 extern "C" int plan_host_matrix_grad_plan(const tn_linear_desc* d) {
     tn::Plan net;

@@ -210,6 +210,21 @@ def test_backward_steps_have_room_for_their_sums(fake_hip):
     assert "step_mfma_pipe_kernel" not in kernels and kernels[kernels.index("step_split_reduce_kernel") - 1] == "step_split_kernel", kernels
 
 
+def test_layers_of_the_direct_kernel_tests(fake_hip):
+    """The layers of the GPU tests of slices made on chip: one token takes the instantiation that they name, 64 tokens the slices in memory; and the
+    switch of decode fusion keeps them there."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    from test_gpu_direct import DIRECT_LAYERS
+    for flags, n in ((0, len(DIRECT_LAYERS)), (tn.TN_FLAG_NO_DECODE_FUSION, 1)):
+        made = create_all(fake_hip, [job(wl.TNSpec(fmt, "bf16", om, im, rk), 64, flags=flags, tokens=(1, 64)) for fmt, om, im, rk, _, _ in DIRECT_LAYERS[:n]])
+        for (_, om, _, _, cfg, steps), got in zip(DIRECT_LAYERS, made):
+            one, many = got["launches"]
+            assert (one[0].kernel == "step_krondirect_kernel") == (flags == 0), (om, one)
+            assert flags or (one[0].args == (cfg, steps) and len(one) <= 2), (om, one)
+            assert all(l.kernel != "step_krondirect_kernel" for l in many), (om, many)
+
+
 def test_tiles_of_the_matrix_product_tests(fake_hip):
     """The calls of the GPU tests that name a tile of the matrix-product kernel, or its form for short K, take it."""
     import workloads as wl

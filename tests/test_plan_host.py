@@ -37,6 +37,9 @@ def host_exec():
     lib.plan_host_matrix.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p]
     lib.plan_host_slices.restype = ctypes.c_int
     lib.plan_host_slices.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p]
+    lib.plan_host_direct.restype = ctypes.c_int
+    lib.plan_host_direct.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p, ctypes.c_void_p,
+                                     ctypes.POINTER(ctypes.c_int)]
     lib.plan_host_matrix_grad.restype = ctypes.c_int
     lib.plan_host_matrix_grad.argtypes = [ctypes.POINTER(_Desc), ctypes.POINTER(ctypes.c_void_p), ctypes.c_void_p,
                                           ctypes.POINTER(ctypes.c_void_p)]
@@ -509,6 +512,45 @@ def test_slices_as_products(host_exec, case):
     assert rc == (0 if planned else 1), rc
     if planned:
         assert np.max(np.abs(w - w_ref)) <= 1e-12 * np.max(np.abs(w_ref))
+
+
+# every instantiation that makes the slices on chip, rings and trains, both ways; shapes that fill it and that do not
+DIRECT_CASES = [
+    (tn.TN_FORMAT_TR, (8, 16, 8, 8), (8, 10, 8, 8), (20, 3, 20, 2, 20), 0, 0),
+    (tn.TN_FORMAT_TR, (8, 16, 8, 8), (8, 10, 8, 8), (20, 3, 20, 2, 20), tn.TN_FLAG_TRANSPOSE, 2),
+    (tn.TN_FORMAT_TR, (4, 8, 4, 8), (8, 10, 8, 8), (20, 3, 17, 4, 20), 0, 1),
+    (tn.TN_FORMAT_TR, (8, 10, 8, 8), (8, 16, 8, 8), (24, 2, 24, 3, 24), 0, 2),
+    (tn.TN_FORMAT_TR, (10, 16, 10, 16), (8, 10, 8, 8), (18, 2, 18, 3, 18), 0, 3),
+    (tn.TN_FORMAT_TR, (8, 10, 8, 8), (10, 16, 10, 16), (18, 3, 18, 2, 18), 0, 4),
+    (tn.TN_FORMAT_TR, (8, 10, 8, 8), (10, 16, 10, 16), (40, 3, 40, 3, 40), 0, 4),
+    (tn.TN_FORMAT_TR, (8, 8, 8, 8), (8, 8, 8, 8), (20, 2, 20, 2, 20), 0, 0),
+    (tn.TN_FORMAT_TT, (8, 10, 8, 8), (10, 16, 10, 16), (1, 32, 12, 28, 1), 0, 4),
+    (tn.TN_FORMAT_TT, (10, 16, 10, 16), (8, 10, 8, 8), (1, 32, 12, 32, 1), 0, 3),
+    (tn.TN_FORMAT_TT, (4, 8, 4, 8), (8, 10, 8, 8), (1, 32, 40, 32, 1), 0, 1),
+    (tn.TN_FORMAT_TR, (8, 16, 8, 8), (8, 10, 8, 8), (100,) * 5, 0, None),          # a bond of more than three steps of 32
+    (tn.TN_FORMAT_TR, (6, 16, 8, 8), (6, 10, 10, 8), (20,) * 5, 0, None),          # no four in-modes in a row
+    (tn.TN_FORMAT_TR, (8, 16, 8, 8), (8, 10, 8, 8), (4,) * 5, 0, None),            # mostly padding
+]
+
+
+@pytest.mark.parametrize("case", range(len(DIRECT_CASES)))
+def test_slices_made_on_chip_are_the_rings(host_exec, case):
+    """One token through tn::DirectPlan, tile by tile, against the oracle."""
+    fmt, om, im, rk, flags, want = DIRECT_CASES[case]
+    rng = np.random.default_rng(900 + case)
+    ts = [np.ascontiguousarray(t) for t in _rand_tensors(rng, fmt, om, im, rk)]
+    transposed = bool(flags & tn.TN_FLAG_TRANSPOSE)
+    n, m = (np.prod(om), np.prod(im)) if transposed else (np.prod(im), np.prod(om))
+    x, y = rng.standard_normal((1, int(n))), np.zeros((1, int(m)))
+    d, keep = _make_desc(fmt, tn.TN_DTYPE_BF16, om, im, rk, None, 1, 0, flags, None)
+    ptrs = (ctypes.c_void_p * len(ts))(*[t.ctypes.data for t in ts])
+    cfg = ctypes.c_int(-1)
+    rc = host_exec.plan_host_direct(ctypes.byref(d), ptrs, x.ctypes.data, y.ctypes.data, ctypes.byref(cfg))
+    assert rc == (1 if want is None else 0)
+    if want is not None:
+        assert cfg.value == want
+        w = O.dense_weight(fmt, ts, len(om))
+        assert O.rel_max_err(y, x @ (w if transposed else w.T)) < 1e-12
 
 
 def test_gradient_plan_of_a_large_ring_in_little_memory(host_exec):
