@@ -687,6 +687,10 @@ __global__ void __launch_bounds__(64) step_chain2_fine_kernel(Chain2Args c0, Cha
     it.compute(c, static_cast<bf16_t*>(c.Out));
 }
 
+// A workgroup walks column blocks blockIdx.x, + gridDim.x, ... with the next block's pieces requested as the present one's are
+// multiplied: its registers leave room for one workgroup on a CU, and with a block each, the two layers' 2 x 288 blocks of the Tucker
+// pair 5120 -> 25600 of rank 96 were 2.25 rounds of workgroups that each started with the pair's result and an empty pipeline. us per
+// call over cold copies, a block each / so: that pair at one token 27.9 / 24.6, one layer 20.0 / 18.2, the pair in 4 bits 18.0 / 15.7.
 // KPW: pieces of 64 k per wave. Q4: the wide step's tensor is read in its 4-bit form (see q4_stream_pack_kernel), one
 // 16-byte load of codes and one scale byte per lane and piece instead of four fragment loads.
 template <int K1S, int RUN_C1, int KPW, int Q4>
@@ -704,8 +708,9 @@ __global__ void __launch_bounds__(512) step_chain2_split_kernel(Chain2Args c0, S
     bf16_t* Out = static_cast<bf16_t*>(a.Out);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int cb = blockIdx.x;
-    if (cb * 32 >= a.C) return;                                            // the two layers' grids may differ
+    int cb = blockIdx.x;
+    const int n_cb = (a.C + 31) >> 5;
+    if (cb >= n_cb) return;                                                // the two layers' grids may differ
     const int nks = a.Kp >> 4;
     const int lrow = lane & 31, lhalf = lane >> 5;
     bf16x8 zero;
@@ -724,80 +729,69 @@ __global__ void __launch_bounds__(512) step_chain2_split_kernel(Chain2Args c0, S
     uint4 qc[Q4 ? KPW : 1];
     unsigned qs[Q4 ? KPW : 1];
     const int n_chunks = nks >> 2;
-    if (Q4) {
-        const uint4* qp = static_cast<const uint4*>(a.B) + int64_t(cb) * n_chunks * 64 + lane;
-        const unsigned char* sp = static_cast<const unsigned char*>(a.Bs) + int64_t(cb) * n_chunks * 64 + lane;
+    auto request = [&](int u, int block) {
+        const int64_t ch = int64_t(block) * n_chunks + min(wave + NW * u, n_chunks - 1);
+        if (Q4) {
+            qc[Q4 ? u : 0] = (static_cast<const uint4*>(a.B) + lane)[ch * 64];
+            qs[Q4 ? u : 0] = (static_cast<const unsigned char*>(a.Bs) + lane)[ch * 64];
+        } else {
 #pragma unroll
-        for (int u = 0; u < KPW; ++u) {
-            const int ch = min(wave + NW * u, n_chunks - 1);
-            qc[u] = qp[int64_t(ch) * 64];
-            qs[u] = sp[int64_t(ch) * 64];
+            for (int ks = 0; ks < 4; ++ks) bf[Q4 ? 0 : u][ks] = *reinterpret_cast<const bf16x8*>(B + lane * 8 + (ch * 4 + ks) * 512);
         }
-    } else {
-        const bf16_t* bp = B + (int64_t(cb) * nks) * 512 + lane * 8;
+    };
 #pragma unroll
-        for (int u = 0; u < KPW; ++u) {
-            const int ch = min(wave + NW * u, n_chunks - 1);
-#pragma unroll
-            for (int ks = 0; ks < 4; ++ks) bf[u][ks] = *reinterpret_cast<const bf16x8*>(bp + (int64_t(ch) * 4 + ks) * 512);
-        }
-    }
+    for (int u = 0; u < KPW; ++u) request(u, cb);
     __builtin_amdgcn_sched_barrier(0);
     // ---- 3. the chained pair for the item, into LDS
     if (has_item) item.compute(c, z);
     __syncthreads();
-    // ---- 4. the wide step: lane l supplies token l%32, k = 16*ks + 8*(l/32) .. +7 from the LDS buffer
-    floatx16 acc;
+    // ---- 4. the wide step, a block of 32 columns after the other; a piece's registers take the same piece of the next block as soon as
+    //         they are multiplied. Lane l supplies token l%32, k = 16*ks + 8*(l/32) .. +7 from the LDS buffer
+    const bool tv = lrow < int(a.total_rows);
+    const bf16_t* zrow = z + int64_t(tv ? lrow : 0) * a.a_tok_stride + (Q4 ? 32 : 8) * lhalf;
+    for (;;) {
+        const int next = cb + int(gridDim.x);
+        floatx16 acc;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    {
-        const bool tv = lrow < int(a.total_rows);
-        const bf16_t* zrow = z + int64_t(tv ? lrow : 0) * a.a_tok_stride + 8 * lhalf;
-        if (Q4) {
-            // lanes 0-31 hold block 2*ch, lanes 32-63 block 2*ch + 1: k-step u of a piece takes k = 64*ch + 32*(l/32) + 8u ..
-            const bf16_t* zq = z + int64_t(tv ? lrow : 0) * a.a_tok_stride + 32 * lhalf;
+        for (int v = 0; v < 16; ++v) acc[v] = 0.f;
 #pragma unroll
-            for (int u = 0; u < KPW; ++u) {
-                const int ch = wave + NW * u;
-                if (ch < n_chunks) {                                           // wave-uniform
-                    bf16x8 w[4];
-                    q4_dequant_block(qc[u], qs[u], w);
+        for (int u = 0; u < KPW; ++u) {
+            const int ch = wave + NW * u;
+            if (ch < n_chunks) {                                           // wave-uniform
+                bf16x8 w[4];
+                if (Q4) {
+                    // lanes 0-31 hold block 2*ch, lanes 32-63 block 2*ch + 1: k-step u of a piece takes k = 64*ch + 32*(l/32) + 8u ..
+                    q4_dequant_block(qc[Q4 ? u : 0], qs[Q4 ? u : 0], w);
+                } else {
 #pragma unroll
-                    for (int ks = 0; ks < 4; ++ks) {
-                        const int k = 64 * ch + 8 * ks;
-                        const bf16x8 x = (tv && k + 32 * lhalf < a.K) ? *reinterpret_cast<const bf16x8*>(zq + k) : zero;
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[ks], x, acc, 0, 0, 0);
-                    }
+                    for (int ks = 0; ks < 4; ++ks) w[ks] = bf[Q4 ? 0 : u][ks];
+                }
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) {
+                    const int k = 64 * ch + (Q4 ? 8 : 16) * ks;
+                    const bf16x8 x = (tv && k + (Q4 ? 32 : 8) * lhalf < a.K) ? *reinterpret_cast<const bf16x8*>(zrow + k) : zero;
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[ks], x, acc, 0, 0, 0);
                 }
             }
-        } else {
-#pragma unroll
-            for (int u = 0; u < KPW; ++u) {
-                const int ch = wave + NW * u;
-                if (ch < n_chunks) {                                           // wave-uniform
-#pragma unroll
-                    for (int ks = 0; ks < 4; ++ks) {
-                        const int k = 64 * ch + 16 * ks;
-                        const bf16x8 x = (tv && k + 8 * lhalf < a.K) ? *reinterpret_cast<const bf16x8*>(zrow + k) : zero;
-                        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[u][ks], x, acc, 0, 0, 0);
-                    }
-                }
-            }
+            if (next < n_cb) request(u, next);
         }
-    }
 #pragma unroll
-    for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[v];
-    __syncthreads();
-    // lane l, register v holds row (token) l%32, column 8*(v/4) + 4*(l/32) + v%4
-    for (int e = tid; e < 1024; e += NW * 64) {
-        const int v = (e >> 6) & 15, l = e & 63;
-        float sum = 0.f;
+        for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[v];
+        __syncthreads();
+        // lane l, register v holds row (token) l%32, column 8*(v/4) + 4*(l/32) + v%4
+        for (int e = tid; e < 1024; e += NW * 64) {
+            const int v = (e >> 6) & 15, l = e & 63;
+            float sum = 0.f;
 #pragma unroll
-        for (int w = 0; w < NW; ++w) sum += red[w * 1024 + e];
-        const uint32_t g = uint32_t(l & 31);
-        const int col = cb * 32 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
-        if (g >= a.total_rows || col >= a.C) continue;
-        Out[int64_t(g) * a.c_tok_stride + a.crow[0] + a.ccol[col]] = bf16_t(sum);
+            for (int w = 0; w < NW; ++w) sum += red[w * 1024 + e];
+            const uint32_t g = uint32_t(l & 31);
+            const int col = cb * 32 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
+            if (g >= a.total_rows || col >= a.C) continue;
+            Out[int64_t(g) * a.c_tok_stride + a.crow[0] + a.ccol[col]] = bf16_t(sum);
+        }
+        if (next >= n_cb) break;
+        cb = next;
+        __syncthreads();                                                   // the sums have been read
     }
 }
 

@@ -2300,6 +2300,7 @@ int launch_chain2(const tn_linear_s* h, const DevStep& s1, const DevStep& s2, co
 // split-K kernel with one split and 8 waves, its rows are the tokens themselves (R = 1), its K fits the kernel's
 // register budget and every (token, column tile) item of the pair gets a wave of its own.
 constexpr int64_t kFusedDecodeMaxZBytes = 32 * 1024;
+constexpr uint32_t kFusedDecodeWorkgroups = 256;
 constexpr size_t kFusedDecodeRedBytes = 8 * 1024 * sizeof(float);
 constexpr int kFusedDecodeKPW = 5;           // pieces of 64 k of the wide step per wave: K <= 8 * 5 * 64 = 2560
 
@@ -2365,7 +2366,9 @@ int launch_chain2_split(const Chain2SplitArgs* p0, const Chain2SplitArgs* p1, hi
         return TN_OK;
     }
     const Chain2SplitArgs& q = p1 ? *p1 : *p0;
-    const uint32_t blocks = std::max(p0->col_blocks, q.col_blocks);
+    // one workgroup to a compute unit (registers), each with the same number of blocks where the layers are alike
+    const uint32_t most = std::max(p0->col_blocks, q.col_blocks), all = p0->col_blocks + (p1 ? p1->col_blocks : 0);
+    const uint32_t per = (all + kFusedDecodeWorkgroups - 1) / kFusedDecodeWorkgroups, blocks = (most + per - 1) / per;
     const size_t smem = kFusedDecodeRedBytes + size_t(std::max(p0->z_bytes, q.z_bytes));
     hipLaunchKernelGGL(kerns[p0->kern], dim3(blocks, p1 ? 2 : 1), dim3(512), smem, st, p0->c, p0->a, p0->z_bytes, q.c, q.a,
                        q.z_bytes);
