@@ -75,9 +75,9 @@ __device__ __forceinline__ void for_constants(F&& f, std::integer_sequence<int, 
     (f(std::integral_constant<int, Q>()), ...);
 }
 
-template <int TM, int TN, int NS, int TRANS, int FORM = GEMM_PLAIN>
-__global__ void __launch_bounds__(256, FORM == GEMM_SHORT ? 3 : 1) step_gemm_kernel(StepArgs a, GemmArgs g) {
 #ifdef __HIP_DEVICE_COMPILE__
+template <int TM, int TN, int NS, int TRANS, int FORM>
+__device__ __forceinline__ void gemm_tile(const StepArgs& a, const GemmArgs& g) {
     using S = GemmShape<TM, TN, NS>;
     constexpr int NW = 4, BM = S::BM, BN = S::BN, STAGE = S::STAGE_BYTES, A_BYTES = BM * 128;
     constexpr int L = TM + TN;                           // 1 KB direct-to-LDS loads per wave and stage: TM of A, then TN of B
@@ -396,5 +396,27 @@ __global__ void __launch_bounds__(256, FORM == GEMM_SHORT ? 3 : 1) step_gemm_ker
             }
         }
     }
+}
+#endif
+
+template <int TM, int TN, int NS, int TRANS, int FORM = GEMM_PLAIN>
+__global__ void __launch_bounds__(256, FORM == GEMM_SHORT ? 3 : 1) step_gemm_kernel(StepArgs a, GemmArgs g) {
+#ifdef __HIP_DEVICE_COMPILE__
+    gemm_tile<TM, TN, NS, TRANS, FORM>(a, g);
+#endif
+}
+
+// Products that do not wait for each other, in one launch: blockIdx.y says which. The two halves of a train are a few tiles each, and
+// so are the four products that give its cores' gradients: a launch of one of them takes 4.6 us on an idle chip, whatever it does.
+constexpr int kGemmMany = 4;
+struct GemmMany {
+    StepArgs a[kGemmMany];
+    GemmArgs g[kGemmMany];
+};
+
+template <int TM, int TN, int NS, int FORM>
+__global__ void __launch_bounds__(256, 1) step_gemm_many_kernel(GemmMany m) {
+#ifdef __HIP_DEVICE_COMPILE__
+    gemm_tile<TM, TN, NS, 0, FORM>(m.a[blockIdx.y], m.g[blockIdx.y]);
 #endif
 }

@@ -559,13 +559,15 @@ __global__ void __launch_bounds__(Y > 4 ? 64 * Y : 256) grad_reduce_kernel(GradO
 
 // Several tensors in one launch, blockIdx.y says which (two elements a lane: the four factors of a Tucker layer with ranks of 96
 // and 48, 250 splits of 38 thousand elements, are 290 workgroups).
+constexpr int kGradOutMany = 4;
 struct GradOutMany {
-    GradOutArgs o[4];
+    GradOutArgs o[kGradOutMany];
 };
 
-template <int Y>
+template <int Y, int V>
 __global__ void __launch_bounds__(Y > 4 ? 64 * Y : 256) grad_reduce_many_kernel(GradOutMany m) {
-    grad_reduce<Y, 2>(m.o[blockIdx.y]);
+    if (Y == 4 && m.o[blockIdx.y].n_split < 4) grad_reduce<1, V>(m.o[blockIdx.y]);      // no splits to share out
+    else grad_reduce<Y, V>(m.o[blockIdx.y]);
 }
 
 __global__ void __launch_bounds__(256) grad_fill_kernel(float* p, int64_t n) {

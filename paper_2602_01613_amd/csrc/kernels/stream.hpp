@@ -664,6 +664,22 @@ __global__ void __launch_bounds__(256) step_split_reduce_parts_kernel(StepArgs a
     split_reduce<2>(a, partial, nsplit, rows_pad, out_lo);
 }
 
+// Two of them in one launch, blockIdx.y says which.
+struct SplitReduceParts {
+    StepArgs a;
+    const float* partial;
+    int32_t nsplit;
+    uint32_t rows_pad;
+    int64_t out_lo;
+};
+struct SplitReducePartsTwo {
+    SplitReduceParts p[2];
+};
+__global__ void __launch_bounds__(256) step_split_reduce_parts_two_kernel(SplitReducePartsTwo m) {
+    const SplitReduceParts& p = m.p[blockIdx.y];
+    split_reduce<2>(p.a, p.partial, p.nsplit, p.rows_pad, p.out_lo);
+}
+
 // ---------------------------------------------------------------------------------------------
 // Whole-chain kernel for small layers: when every packed tensor of the plan and two copies of the
 // largest per-token tensor fit in LDS together (the small fp32 train: 19 KB of cores, 8 KB per

@@ -18,9 +18,18 @@ struct TransposeArgs {
     const int32_t* to;
 };
 
-__global__ void __launch_bounds__(256) transpose_kernel(TransposeArgs p) {
+// Up to kTransposeMany matrices in one launch, blockIdx.y says which.
+constexpr int kTransposeMany = 4;
+struct TransposeMany {
+    TransposeArgs m[kTransposeMany];
+};
+
+__global__ void __launch_bounds__(256) transpose_kernel(TransposeMany many) {
     __shared__ uint32_t tile[32][65];                    // [t / 2][d]: t even in the low half
-    const int64_t t0 = int64_t(blockIdx.y) * 64, d0 = int64_t(blockIdx.x) * 64;
+    const TransposeArgs& p = many.m[blockIdx.y];
+    const uint32_t across = uint32_t((p.D + 63) >> 6), down = blockIdx.x / across;
+    const int64_t t0 = int64_t(down) * 64, d0 = int64_t(blockIdx.x - down * across) * 64;
+    if (t0 >= p.Tp) return;
     const int tid = threadIdx.x;
     {
         // a thread: rows t0 + 2 * (tid / 8), + 1, eight d

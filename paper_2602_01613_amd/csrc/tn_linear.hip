@@ -217,8 +217,9 @@ struct tn_linear_s {
     int64_t mgrad_min_tokens = 0, mgrad_chunk = 0;
     int64_t mgrad_flops = 0;                  // of a pass, beside dW
     int64_t mgrad_f[2] = {0, 0};              // modes of the halves
-    int64_t mgrad_off[8] = {};                // byte offsets in bwd_ws: X, dY; in two parts each: dW, dW transposed, the two
-                                              // operands, dH, dH transposed
+    int64_t mgrad_off[10] = {};               // byte offsets in bwd_ws: X, dY; in two parts each: dW, dW transposed, the two
+                                              // operands, and of either half dH, dH transposed
+    bool mgrad_together = false;              // the halves' cores in shared launches (else they share the room for dH)
     DevStep mgrad_dw;                         // rows m, columns n; K, A and B are the call's
     struct GradHalf {
         bool pair = false;
@@ -529,6 +530,7 @@ struct GemmChoice {
     float us = 0.f;               // what it is expected to take
 };
 
+constexpr float kGemmLaunchUs = 3.f;
 constexpr int64_t kGemmMinRows = 65;        // up to 64 rows the launch is a stream of the packed tensor: the kernels of stream.hpp
 constexpr float kGemmPartialBytesPerUs = 5e6f;    // partial sums, written and read back, and the launch that adds them:
 constexpr float kGemmReduceUs = 3.f;
@@ -546,14 +548,15 @@ constexpr float kGemmCachedBytes = 128e6f;
 
 // The tile size and the number of K ranges with the least time for `rows` rows; partial sums within `cap` bytes.
 // `brief`: the form for K of one or two tiles may be taken (tile = kGemmTiles).
-GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int64_t cap, bool brief = false) {
+// `only`: of this tile.
+GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int64_t cap, bool brief = false, int only = -1) {
     GemmChoice best;
     const int nk = s.Kp / 64 * s.segments();
     const bool trans = s.cmode != 1;
     const uint32_t cus = uint32_t(h->num_cus);
     const float b_bytes = 2.f * float(s.plan.C) * float(s.Kp);
     const bool cold = s.kept && rows <= kGemmColdRows && b_bytes >= kGemmKeptColdBytes && b_bytes <= kGemmColdBytes;
-    for (int t = 0; t < kGemmTiles; ++t) {
+    for (int t = only < 0 ? 0 : only; t < (only < 0 ? kGemmTiles : only + 1); ++t) {
         const GemmTile& g = kGemmTile[t];
         if (uint32_t(s.Cp) % uint32_t(32 * g.tn) || (trans && (g.tm & 1))) continue;
         const int64_t all_tiles = int64_t((uint32_t(rows) + 32 * g.tm - 1) / uint32_t(32 * g.tm)) *
@@ -640,7 +643,20 @@ size_t gemm_short_smem(int nk) { return nk == 1 ? GemmShape<kGemmShortTm, kGemmS
 
 size_t gemm_smem(int tile) { return gemm_smem_at(tile, std::make_integer_sequence<int, kGemmTiles>()); }
 
+// The tile of the launches of several products.
+constexpr int kGemmManyTile = kGemmTiles - 1;
+static_assert(kGemmTile[kGemmManyTile].tm == 2 && kGemmTile[kGemmManyTile].tn == 2, "64 x 64");
+using gemm_many_t = void (*)(GemmMany);
+gemm_many_t gemm_many_kernel(int form) {
+    constexpr GemmTile t = kGemmTile[kGemmManyTile];
+    return form == GEMM_PARTS ? step_gemm_many_kernel<t.tm, t.tn, t.stages, GEMM_PARTS> : step_gemm_many_kernel<t.tm, t.tn, t.stages, GEMM_PLAIN>;
+}
+
 int configure_gemm() {
+    for (int form : {GEMM_PLAIN, GEMM_PARTS})
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(gemm_many_kernel(form)), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                int(gemm_smem(kGemmManyTile))) != hipSuccess)
+            return TN_ERR_HIP;
     for (int t = 0; t < kGemmTiles; ++t)
         for (int form = 0; form < 6; ++form) {
             const gemm_kern_t k = gemm_kernel(t, (form & 1) != 0, GEMM_PLAIN + form / 2);
@@ -667,16 +683,11 @@ struct GemmSums {
     int n_split = 1;
 };
 
-// With `f32` the launch leaves its fp32 sums in `partial` (or at f32->sums, as one range with rows of f32->ld).
-int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64_t rows, void* partial, int64_t partial_bytes,
-                hipStream_t st, GemmSums* f32 = nullptr) {
-    const bool trans = s.cmode != 1;
-    const bool one_range = (h->flags & TN_FLAG_NO_SPLIT_K) || !partial || (f32 && f32->sums);
-    const int form = s.a_lo || s.b_lo || s.out_lo ? GEMM_PARTS : (a.K % 64 || s.cmode == 0 ? GEMM_ANY : GEMM_PLAIN);
-    const GemmChoice c = gemm_choice(h, s, rows, one_range ? 0 : partial_bytes, form == GEMM_PLAIN && !f32);
-    if (c.tile < 0 || (trans && (s.a_lo || s.b_lo || s.out_lo))) return TN_ERR_UNSUPPORTED;
-    if (f32 && !f32->sums && (!partial || int64_t(c.n_split) * rows * s.Cp * 4 > partial_bytes)) return TN_ERR_UNSUPPORTED;
-    const GemmTile t = c.tile == kGemmTiles ? GemmTile{kGemmShortTm, kGemmShortTn, 0} : kGemmTile[c.tile];
+int gemm_form(const DevStep& s, const StepArgs& a) {
+    return s.a_lo || s.b_lo || s.out_lo ? GEMM_PARTS : (a.K % 64 || s.cmode == 0 ? GEMM_ANY : GEMM_PLAIN);
+}
+
+GemmArgs gemm_args(const DevStep& s, const GemmTile& t, const GemmChoice& c, int64_t rows) {
     GemmArgs g;
     g.n_row = int32_t((rows + 32 * t.tm - 1) / (32 * t.tm));
     g.n_col = int32_t((s.plan.C + 32 * t.tn - 1) / (32 * t.tn));
@@ -688,6 +699,21 @@ int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64
     g.a_lo = s.a_lo;
     g.b_lo = s.b_lo;
     g.out_lo = s.out_lo;
+    g.partial = nullptr;
+    return g;
+}
+
+// With `f32` the launch leaves its fp32 sums in `partial` (or at f32->sums, as one range with rows of f32->ld).
+int launch_gemm(const tn_linear_s* h, const DevStep& s, const StepArgs& a, int64_t rows, void* partial, int64_t partial_bytes,
+                hipStream_t st, GemmSums* f32 = nullptr) {
+    const bool trans = s.cmode != 1;
+    const bool one_range = (h->flags & TN_FLAG_NO_SPLIT_K) || !partial || (f32 && f32->sums);
+    const int form = gemm_form(s, a);
+    const GemmChoice c = gemm_choice(h, s, rows, one_range ? 0 : partial_bytes, form == GEMM_PLAIN && !f32);
+    if (c.tile < 0 || (trans && (s.a_lo || s.b_lo || s.out_lo))) return TN_ERR_UNSUPPORTED;
+    if (f32 && !f32->sums && (!partial || int64_t(c.n_split) * rows * s.Cp * 4 > partial_bytes)) return TN_ERR_UNSUPPORTED;
+    const GemmTile t = c.tile == kGemmTiles ? GemmTile{kGemmShortTm, kGemmShortTn, 0} : kGemmTile[c.tile];
+    GemmArgs g = gemm_args(s, t, c, rows);
     g.partial = c.n_split > 1 || f32 ? static_cast<float*>(partial) : nullptr;
     if (f32) {
         if (f32->sums) {
@@ -720,9 +746,7 @@ bool gemm_rows(const DevStep& s, int64_t rows) {
     return s.cmode != 0 || !split_config(s, rows).use;
 }
 
-// One product of the matrix plan: out[crow[r] + ccol[c]] = sum_k A[r][k] B[c][k], or its fp32 sums.
-int launch_product_of(const tn_linear_s* h, const DevStep& s, const void* A, const void* B, void* out, void* partial,
-                      int64_t partial_bytes, hipStream_t st, GemmSums* f32 = nullptr) {
+StepArgs product_args(const DevStep& s, const void* A, const void* B, void* out) {
     StepArgs a{};
     a.A = A;
     a.B = B;
@@ -735,9 +759,73 @@ int launch_product_of(const tn_linear_s* h, const DevStep& s, const void* A, con
     a.Kp = s.Kp;
     a.C = int32_t(s.plan.C);
     a.Cp = s.Cp;
-    const int rc = launch_gemm(h, s, a, s.plan.R, partial, partial_bytes, st, f32);
+    return a;
+}
+
+// One product of the matrix plan: out[crow[r] + ccol[c]] = sum_k A[r][k] B[c][k], or its fp32 sums.
+int launch_product_of(const tn_linear_s* h, const DevStep& s, const void* A, const void* B, void* out, void* partial,
+                      int64_t partial_bytes, hipStream_t st, GemmSums* f32 = nullptr) {
+    const int rc = launch_gemm(h, s, product_args(s, A, B, out), s.plan.R, partial, partial_bytes, st, f32);
     if (rc != TN_OK) return rc;
     return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
+}
+
+// Products that do not wait for each other: in one launch where none would take longer by more than that launch saves (halves of a
+// rank-64 train 5120 -> 8192: 5.0 us, one after the other 9.4) and all of them fit the chip at once, else one by one. With `f32`
+// they leave their sums, each in its own part of `partial`; otherwise they are outputs, in one range of K.
+struct ProductJob {
+    const DevStep* s;
+    const void *A, *B;
+    void* out;
+    GemmSums f32;
+};
+
+int64_t one_range_bytes(const DevStep& s) { return (s.plan.R * s.Cp * 4 + 255) & ~int64_t(255); }
+
+int launch_products(const tn_linear_s* h, ProductJob* jobs, int n, bool f32, void* partial, int64_t partial_bytes, hipStream_t st) {
+    // the sums: a range's for each, and an equal share of what is left
+    int64_t spare = partial_bytes, at[kGemmMany + 1] = {};
+    for (int i = 0; i < n && f32; ++i) spare -= one_range_bytes(*jobs[i].s);
+    if (n > kGemmMany || (f32 && spare < 0)) return TN_ERR_UNSUPPORTED;
+    for (int i = 0; i < n && f32; ++i) at[i + 1] = at[i] + one_range_bytes(*jobs[i].s) + (spare / n & ~int64_t(255));
+    GemmMany m;
+    memset(&m, 0, sizeof(m));
+    int64_t all = 0, most = 0;
+    bool one = n > 1;
+    int form = 0;
+    for (int i = 0; i < n && one; ++i) {
+        const DevStep& s = *jobs[i].s;
+        m.a[i] = product_args(s, jobs[i].A, jobs[i].B, jobs[i].out);
+        const int f = gemm_form(s, m.a[i]);
+        one = s.cmode == 1 && f != GEMM_ANY && (i == 0 || f == form);
+        form = f;
+        if (!one) break;
+        const bool ranges = !(h->flags & TN_FLAG_NO_SPLIT_K);
+        const int64_t room = f32 ? at[i + 1] - at[i] : partial_bytes;
+        const GemmChoice best = gemm_choice(h, s, s.plan.R, ranges ? room : 0, form == GEMM_PLAIN && !f32);
+        const GemmChoice c = gemm_choice(h, s, s.plan.R, ranges && f32 ? room : 0, false, kGemmManyTile);
+        one = c.tile >= 0 && c.us <= best.us + kGemmLaunchUs;
+        if (!one) break;
+        m.g[i] = gemm_args(s, kGemmTile[kGemmManyTile], c, s.plan.R);
+        if (f32) {
+            m.g[i].partial = reinterpret_cast<float*>(static_cast<char*>(partial) + at[i]);
+            jobs[i].f32 = GemmSums{m.g[i].partial, m.g[i].ld, c.n_split};
+        }
+        const int64_t items = int64_t(m.g[i].n_row) * m.g[i].n_col * m.g[i].n_split;
+        all += items;
+        most = std::max(most, items);
+    }
+    if (one && all <= 2 * int64_t(h->num_cus)) {
+        hipLaunchKernelGGL(gemm_many_kernel(form), dim3(uint32_t((most + 7) / 8 * 8), uint32_t(n)), dim3(256), gemm_smem(kGemmManyTile), st, m);
+        return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
+    }
+    for (int i = 0; i < n; ++i) {
+        jobs[i].f32 = GemmSums{};
+        const int rc = launch_product_of(h, *jobs[i].s, jobs[i].A, jobs[i].B, jobs[i].out, f32 ? static_cast<char*>(partial) + at[i] : partial,
+                                         f32 ? at[i + 1] - at[i] : partial_bytes, st, f32 ? &jobs[i].f32 : nullptr);
+        if (rc != TN_OK) return rc;
+    }
+    return TN_OK;
 }
 
 int launch_product(const tn_linear_s* h, const DevProduct& p, void* partial, int64_t partial_bytes, hipStream_t st) {
@@ -746,11 +834,12 @@ int launch_product(const tn_linear_s* h, const DevProduct& p, void* partial, int
 
 // W from the layer's tensors, then Y = X W^T.
 int launch_matrix_build(const tn_linear_s* h, void* partial, int64_t partial_bytes, hipStream_t st) {
+    ProductJob jobs[2];
+    int n = 0;
     for (int i = 0; i < 2; ++i)
-        if (h->mat_build[i]) {
-            const int rc = launch_product(h, h->mat_half[i], partial, partial_bytes, st);
-            if (rc != TN_OK) return rc;
-        }
+        if (h->mat_build[i]) jobs[n++] = ProductJob{&h->mat_half[i].s, h->mat_half[i].a, h->mat_half[i].s.packed, h->mat_half[i].out, {}};
+    const int rc = launch_products(h, jobs, n, false, partial, partial_bytes, st);
+    if (rc != TN_OK) return rc;
     return launch_product(h, h->mat_w, partial, partial_bytes, st);
 }
 
@@ -2029,7 +2118,7 @@ int prepare_direct(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
 // Without the form for short K, which W's product of a narrow bond runs on, W was priced 7 us too high. The price of a tile has 3 us of a
 // launch in it, 3 more are what a launch costs a program that does not replay a graph. With 5, two products of 3.2 and 4.4 us of a train of two
 // cores (40 x 8, 32 x 16, rank 24) were left for steps that take 12.6 to 15.2 at 33 to 500 tokens, 8.7 to 8.9 so.
-constexpr float kGemmStoreBytesPerUs = 4e6f, kGemmLaunchUs = 3.f;
+constexpr float kGemmStoreBytesPerUs = 4e6f;
 float product_us(const tn_linear_s* h, const DevStep& s) {
     const bool plain = !s.a_lo && !s.b_lo && !s.out_lo;
     return kGemmLaunchUs + std::max(gemm_choice(h, s, s.plan.R, 0, plain).us, float(s.plan.R) * float(s.plan.C) * (plain ? 2.f / kGemmStoreBytesPerUs : 4.f / 3.5e6f));
@@ -2650,10 +2739,20 @@ int grad_splits(const tn_linear_s* h, const tn::Step& p, int64_t rows, int64_t c
 
 int64_t grad_tokens_pad(int64_t tokens) { return (tokens + 63) / 64 * 64; }
 
-void launch_transpose(const void* src, void* dst, int64_t T, int64_t D, int64_t Tp, bool packed, hipStream_t st,
-                      const int32_t* to = nullptr) {
-    TransposeArgs a{static_cast<const bf16_t*>(src), static_cast<bf16_t*>(dst), T, D, Tp, packed ? 1 : 0, to};
-    hipLaunchKernelGGL(transpose_kernel, dim3(uint32_t((D + 63) / 64), uint32_t(Tp / 64)), dim3(256), 0, st, a);
+TransposeArgs transpose_args(const void* src, void* dst, int64_t T, int64_t D, int64_t Tp, bool packed, const int32_t* to = nullptr) {
+    return TransposeArgs{static_cast<const bf16_t*>(src), static_cast<bf16_t*>(dst), T, D, Tp, packed ? 1 : 0, to};
+}
+
+// Up to kTransposeMany matrices at a time.
+void launch_transposes(const TransposeArgs* m, int n, hipStream_t st) {
+    TransposeMany many;
+    memset(&many, 0, sizeof(many));
+    int64_t most = 0;
+    for (int i = 0; i < n; ++i) {
+        many.m[i] = m[i];
+        most = std::max(most, (m[i].D + 63) / 64 * (m[i].Tp / 64));
+    }
+    hipLaunchKernelGGL(transpose_kernel, dim3(uint32_t(most), uint32_t(n)), dim3(256), 0, st, many);
 }
 
 // A step's gradient as one product over the tokens, straight into the caller's tensor: one row per token, both operands plain
@@ -2694,8 +2793,8 @@ int launch_grad_product(const tn_linear_s* h, const DevStep& s, const void* dOut
     const int64_t tp = grad_tokens_pad(tokens);
     char* a = static_cast<char*>(h->grad_product_mem);
     char* b = a + p.C * tp * 2;
-    launch_transpose(dOut, a, tokens, p.C, tp, false, st, s.grad_row);
-    launch_transpose(In, b, tokens, p.K, tp, true, st, s.grad_col);
+    const TransposeArgs both[2] = {transpose_args(dOut, a, tokens, p.C, tp, false, s.grad_row), transpose_args(In, b, tokens, p.K, tp, true, s.grad_col)};
+    launch_transposes(both, 2, st);
     DevStep g;
     g.plan.R = p.C;
     g.plan.K = tp;
@@ -2943,12 +3042,31 @@ int launch_grad_reduce(GradOutArgs o, hipStream_t st) {
     return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
 
+// Tensors of under 2^31 elements, up to kGradOutMany of them in one launch.
+void launch_grad_reduce_many(const GradOutMany& m, int count, hipStream_t st) {
+    int64_t most = 0;
+    int n_split = 0;
+    bool pairs = true;
+    for (int i = 0; i < count; ++i) {
+        const GradOutArgs& o = m.o[i];
+        most = std::max(most, int64_t(o.C) * o.K);
+        n_split = std::max(n_split, o.n_split);
+        pairs = pairs && o.K % 2 == 0 && o.ld % 2 == 0 && o.split_stride % 2 == 0;
+    }
+    using reduce_t = void (*)(GradOutMany);
+    static const reduce_t kerns[6] = {grad_reduce_many_kernel<1, 1>, grad_reduce_many_kernel<1, 2>, grad_reduce_many_kernel<4, 1>,
+                                      grad_reduce_many_kernel<4, 2>, grad_reduce_many_kernel<16, 1>, grad_reduce_many_kernel<16, 2>};
+    const int y = n_split >= 64 ? 2 : (n_split >= 16 ? 1 : 0);
+    const int64_t per = (y ? 64 : 256) * (pairs ? 2 : 1);
+    hipLaunchKernelGGL(kerns[2 * y + (pairs ? 1 : 0)], dim3(uint32_t(std::min<int64_t>((most + per - 1) / per, 4096)), uint32_t(count)),
+                       dim3(y == 2 ? 1024 : 256), 0, st, m);
+}
+
 // The sums that factor_grad_kernel left, of both sides in one launch.
 int launch_factor_grad_reduce(const tn_linear_s* h, void* const* grads, int64_t tokens, bool accumulate, hipStream_t st) {
     GradOutMany m;
     memset(&m, 0, sizeof(m));
     int count = 0;
-    int64_t most = 0;
     const size_t n = h->steps.size();
     const int64_t groups = factor_grad_groups(h, tokens);
     for (int side = 0; side < 2; ++side) {
@@ -2971,14 +3089,10 @@ int launch_factor_grad_reduce(const tn_linear_s* h, void* const* grads, int64_t 
             o.accumulate = accumulate ? 1 : 0;
             fill_grad_dims(&o, side ? p.cdims : p.kdims, side ? p.kdims : p.cdims);
             o.trace_extent = 1;
-            most = std::max(most, rows * cols);
         }
     }
     if (count == 0) return TN_OK;
-    const dim3 grid(uint32_t((most + 127) / 128), uint32_t(count));
-    if (groups >= 64) hipLaunchKernelGGL(grad_reduce_many_kernel<16>, grid, dim3(1024), 0, st, m);
-    else if (groups >= 16) hipLaunchKernelGGL(grad_reduce_many_kernel<4>, grid, dim3(256), 0, st, m);
-    else hipLaunchKernelGGL(grad_reduce_many_kernel<1>, grid, dim3(256), 0, st, m);
+    launch_grad_reduce_many(m, count, st);
     return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
 
@@ -3047,6 +3161,7 @@ int launch_param_gradient(const tn_linear_s* h, const DevStep& s, const void* dO
 
 // ---- the same gradients through dW ----
 constexpr int64_t kGradMinTokens = 16;        // one token range is padded to 64
+constexpr int64_t kMatrixTogetherBytes = int64_t(32) << 20;      // of a half's dH, twice, in two parts
 constexpr int kGradSumsPad = 128;             // columns of the core gradients (a bond): padded to the narrow tiles
 
 // bond_grad_kernel takes halves of two cores each (a half of one core has no low part, and the kernel reads both parts of both) over
@@ -3188,8 +3303,14 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
             sums = std::max(sums, std::max(G.F1, G.F2) * round_up(int(H.S), kGradSumsPad) * 4);
             us += 46.f + float(G.F1 * G.F2) * 12.f / 3.5e6f;
         }
+        // (a ring's dH may be as large as dW: one after the other then)
+        h->mgrad_together = h->mgrad_half[0].pair && h->mgrad_half[1].pair && (h->mgrad_bond || (dh + dht) * 4 <= kMatrixTogetherBytes);
         room(6, dh);
         room(7, dht);
+        for (int i = 6; i < 8; ++i) {
+            if (h->mgrad_together) room(i + 2, i == 6 ? dh : dht);
+            else h->mgrad_off[i + 2] = h->mgrad_off[i];
+        }
     }
     // tokens per pass: X and dY transposed, tokens padded to 64
     const int64_t limit = desc->workspace_limit_bytes > 0 ? desc->workspace_limit_bytes : kDefaultWorkspaceBytes;
@@ -3264,7 +3385,7 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
     return TN_OK;
 }
 
-int reduce_sums(const GemmSums& f, const tn::GradOut& out, int64_t rows, int64_t cols, float* grad, bool accumulate, hipStream_t st) {
+GradOutArgs sums_out(const GemmSums& f, const tn::GradOut& out, int64_t rows, int64_t cols, float* grad, bool accumulate) {
     GradOutArgs o;
     memset(&o, 0, sizeof(o));
     o.partial = f.sums;
@@ -3277,7 +3398,67 @@ int reduce_sums(const GemmSums& f, const tn::GradOut& out, int64_t rows, int64_t
     o.accumulate = accumulate ? 1 : 0;
     fill_grad_dims(&o, out.rows, out.cols);
     o.trace_extent = 1;
-    return launch_grad_reduce(o, st);
+    return o;
+}
+
+// The gradients of the cores of halves `first` to `last`, from the halves' own in two parts: transposed copies for the second core of a
+// pair, the products, and their sums put in place, a launch each (one after the other they were 12 launches of 4.6 us and up, on an
+// idle chip: 66 us of a rank-64 train's 244, 22 so).
+int core_gradients(const tn_linear_s* h, int first, int last, void* const* grads, void* part, int64_t part_bytes, bool add, hipStream_t st) {
+    char* base = static_cast<char*>(h->bwd_ws);
+    TransposeArgs turn[kTransposeMany];
+    DevStep steps[kGemmMany];
+    ProductJob jobs[kGemmMany];
+    const tn::GradOut* outs[kGemmMany];
+    float* to[kGemmMany];
+    int turns = 0, n = 0;
+    for (int i = first; i <= last; ++i) {
+        const auto& H = h->mgrad_half[i];
+        char *dh = base + h->mgrad_off[6 + 2 * i], *dht = base + h->mgrad_off[7 + 2 * i];
+        const int64_t f1p = tn::detail::round64(H.F1);
+        for (int side = 0; side < 2; ++side) {
+            outs[n] = side == 0 ? &H.out_a : &H.out_b;
+            to[n] = static_cast<float*>(grads[outs[n]->slot]);
+            if (!to[n]) continue;
+            if (side == 1)
+                for (int p = 0; p < 2; ++p)      // the low part right after the high one
+                    turn[turns++] = transpose_args(dh + p * H.F1 * H.F2 * 2, dht + p * H.F2 * f1p * 2, H.F1, H.F2, f1p, false);
+            DevStep& s = steps[n];
+            s.plan.R = side == 0 ? H.F1 : H.F2;
+            s.plan.C = H.S;
+            s.plan.K = side == 0 ? H.F2 : f1p;
+            s.a_lo = side == 0 ? H.F1 * H.F2 : H.F2 * f1p;
+            s.Kp = int(s.plan.K);
+            s.Cp = round_up(int(H.S), kGradSumsPad);
+            s.cmode = 1;
+            s.variant = VAR_GEMM;
+            jobs[n] = ProductJob{&s, side == 0 ? dh : dht, side == 0 ? H.b : H.a, nullptr, {}};
+            ++n;
+        }
+    }
+    if (turns) launch_transposes(turn, turns, st);
+    // all at once where their sums have room beside each other and a launch can count their elements
+    int64_t need = 0;
+    bool together = true;
+    for (int j = 0; j < n; ++j) {
+        need += one_range_bytes(steps[j]);
+        together = together && steps[j].plan.R * steps[j].plan.C < (int64_t(1) << 31);
+    }
+    together = together && need <= part_bytes;
+    for (int j = 0; j < n; j += together ? n : 1) {
+        const int rc = launch_products(h, jobs + j, together ? n : 1, true, part, part_bytes, st);
+        if (rc != TN_OK) return rc;
+        if (!together) {
+            const int rr = launch_grad_reduce(sums_out(jobs[j].f32, *outs[j], steps[j].plan.R, steps[j].plan.C, to[j], add), st);
+            if (rr != TN_OK) return rr;
+        }
+    }
+    if (!together || n == 0) return TN_OK;
+    GradOutMany m;
+    memset(&m, 0, sizeof(m));
+    for (int j = 0; j < n; ++j) m.o[j] = sums_out(jobs[j].f32, *outs[j], steps[j].plan.R, steps[j].plan.C, to[j], add);
+    launch_grad_reduce_many(m, n, st);
+    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
 
 int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const* grads, int64_t tokens, hipStream_t st) {
@@ -3295,17 +3476,23 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
         wanted[i] = grads[H.out_a.slot] || (H.pair && grads[H.out_b.slot]);
     }
     if (dense ? !grads[0] : !(wanted[0] || wanted[1])) return TN_OK;
+    ProductJob ops[2];
+    int n_ops = 0;
     for (int i = 0; i < 2 && !dense; ++i)
         if ((wanted[1 - i] || h->mgrad_bond) && h->mgrad_half[i].pair) {
-            const int rc = launch_product_of(h, h->mgrad_half[i].op.s, h->mgrad_half[i].op.a, h->mgrad_half[i].op.s.packed, at(4 + i), part,
-                                             part_bytes, st);
-            if (rc != TN_OK) return rc;
+            const DevProduct& op = h->mgrad_half[i].op;
+            ops[n_ops++] = ProductJob{&op.s, op.a, op.s.packed, at(4 + i), {}};
         }
+    {
+        const int rc = launch_products(h, ops, n_ops, false, part, part_bytes, st);
+        if (rc != TN_OK) return rc;
+    }
     for (int64_t t0 = 0; t0 < tokens; t0 += h->mgrad_chunk) {
         const int64_t nt = std::min(h->mgrad_chunk, tokens - t0), tp = grad_tokens_pad(nt);
         const bool add = t0 > 0;
-        launch_transpose(static_cast<const char*>(x) + t0 * N * h->elt, at(0), nt, N, tp, true, st);
-        launch_transpose(static_cast<const char*>(dy) + t0 * M * h->elt, at(1), nt, M, tp, false, st);
+        const TransposeArgs acts[2] = {transpose_args(static_cast<const char*>(x) + t0 * N * h->elt, at(0), nt, N, tp, true),
+                                       transpose_args(static_cast<const char*>(dy) + t0 * M * h->elt, at(1), nt, M, tp, false)};
+        launch_transposes(acts, 2, st);
         DevStep dw = h->mgrad_dw;
         dw.plan.K = tp;
         dw.Kp = int(tp);
@@ -3320,25 +3507,48 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
                 tn::GradOut out;
                 out.rows = {{M, N}};
                 out.cols = {{N, 1}};
-                rc = reduce_sums(f, out, M, N, static_cast<float*>(grads[0]), add, st);
+                rc = launch_grad_reduce(sums_out(f, out, M, N, static_cast<float*>(grads[0]), add), st);
             }
             if (rc != TN_OK) return rc;
             continue;
         }
         rc = launch_product_of(h, dw, at(1), at(0), at(2), part, part_bytes, st);
         if (rc != TN_OK) return rc;
-        // both parts of a matrix [r][c], the low one right after the high one
-        auto transpose_parts = [&](int from, int to, int64_t r, int64_t c, int64_t rp) {
-            for (int part = 0; part < 2; ++part)
-                launch_transpose(static_cast<char*>(at(from)) + part * r * c * 2, static_cast<char*>(at(to)) + part * c * rp * 2, r, c, rp, false, st);
-        };
         auto operand = [&](int i) -> const void* { return h->mgrad_half[i].pair ? at(4 + i) : h->mgrad_half[i].op.s.packed; };
         if (h->mgrad_bond) {
             // how far the low part of the operand made of a half is: known to the step that it is the column operand of
             rc = launch_bond_grad(h, at(2), at(4), at(5), h->mgrad_half[1].dh.b_lo, h->mgrad_half[0].dh.b_lo, st);
             if (rc != TN_OK) return rc;
         } else if (wanted[1]) {
-            transpose_parts(2, 3, h->mgrad_f[0], h->mgrad_f[1], h->mgrad_f[0]);
+            TransposeArgs parts[2];
+            for (int p = 0; p < 2; ++p)
+                parts[p] = transpose_args(static_cast<char*>(at(2)) + p * M * N * 2, static_cast<char*>(at(3)) + p * M * N * 2, h->mgrad_f[0],
+                                          h->mgrad_f[1], h->mgrad_f[0], false);
+            launch_transposes(parts, 2, st);
+        }
+        if (h->mgrad_bond) {
+            // the sums of its ranges or row panels, in place and in two parts
+            SplitReducePartsTwo two;
+            memset(&two, 0, sizeof(two));
+            int n = 0;
+            int64_t most = 0;
+            for (int i = 0; i < 2; ++i) {
+                if (!wanted[i]) continue;
+                const auto& H = h->mgrad_half[i];
+                SplitReduceParts& r = two.p[n++];
+                r.a.Out = at(6 + 2 * i);
+                r.a.crow = H.dh.crow;
+                r.a.ccol = H.dh.ccol;
+                r.a.total_rows = r.a.R = uint32_t(h->mgrad_f[i]);
+                r.a.C = r.a.Cp = int32_t(H.dh.plan.C);
+                r.partial = reinterpret_cast<const float*>(reinterpret_cast<const char*>(h->bwd_partial) + (i ? h->bond_sums_bytes[0] : 0));
+                r.nsplit = i ? int((h->mgrad_f[0] + kBondRows - 1) / kBondRows) : h->bond_ranges;
+                r.rows_pad = r.a.R;
+                r.out_lo = H.dh.out_lo;
+                most = std::max(most, h->mgrad_f[i] * H.dh.plan.C);
+            }
+            hipLaunchKernelGGL(step_split_reduce_parts_two_kernel, dim3(uint32_t(std::min<int64_t>((most + 255) / 256, 8192)), uint32_t(n)),
+                               dim3(256), 0, st, two);
         }
         for (int i = 0; i < 2; ++i) {
             if (!wanted[i]) continue;
@@ -3347,46 +3557,18 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
             if (!H.pair) {
                 GemmSums f;
                 rc = launch_product_of(h, H.dh, at(2 + i), op, nullptr, part, part_bytes, st, &f);
-                if (rc == TN_OK) rc = reduce_sums(f, H.out_a, h->mgrad_f[i], H.dh.plan.C, static_cast<float*>(grads[H.out_a.slot]), add, st);
+                if (rc == TN_OK)
+                    rc = launch_grad_reduce(sums_out(f, H.out_a, h->mgrad_f[i], H.dh.plan.C, static_cast<float*>(grads[H.out_a.slot]), add), st);
                 if (rc != TN_OK) return rc;
                 continue;
             }
-            if (h->mgrad_bond) {
-                // the sums of its ranges or row panels, in place and in two parts
-                StepArgs r{};
-                r.Out = at(6);
-                r.crow = H.dh.crow;
-                r.ccol = H.dh.ccol;
-                r.total_rows = r.R = uint32_t(h->mgrad_f[i]);
-                r.C = r.Cp = int32_t(H.dh.plan.C);
-                const int64_t total = h->mgrad_f[i] * H.dh.plan.C;
-                const char* sums = reinterpret_cast<const char*>(h->bwd_partial) + (i ? h->bond_sums_bytes[0] : 0);
-                hipLaunchKernelGGL(step_split_reduce_parts_kernel, dim3(uint32_t(std::min<int64_t>((total + 255) / 256, 8192))), dim3(256), 0, st, r,
-                                   reinterpret_cast<const float*>(sums), i ? int((h->mgrad_f[0] + kBondRows - 1) / kBondRows) : h->bond_ranges, r.R,
-                                   H.dh.out_lo);
-            } else {
-                rc = launch_product_of(h, H.dh, at(2 + i), op, at(6), part, part_bytes, st);
-            }
+            if (!h->mgrad_bond) rc = launch_product_of(h, H.dh, at(2 + i), op, at(6 + 2 * i), part, part_bytes, st);
+            if (rc == TN_OK && !h->mgrad_together) rc = core_gradients(h, i, i, grads, part, part_bytes, add, st);
             if (rc != TN_OK) return rc;
-            for (int side = 0; side < 2; ++side) {
-                float* grad = static_cast<float*>(grads[side == 0 ? H.out_a.slot : H.out_b.slot]);
-                if (!grad) continue;
-                const int64_t f1p = tn::detail::round64(H.F1);
-                if (side == 1) transpose_parts(6, 7, H.F1, H.F2, f1p);
-                DevStep s;
-                s.plan.R = side == 0 ? H.F1 : H.F2;
-                s.plan.C = H.S;
-                s.plan.K = side == 0 ? H.F2 : f1p;
-                s.a_lo = side == 0 ? H.F1 * H.F2 : H.F2 * f1p;
-                s.Kp = int(s.plan.K);
-                s.Cp = round_up(int(H.S), kGradSumsPad);
-                s.cmode = 1;
-                s.variant = VAR_GEMM;
-                GemmSums f;
-                rc = launch_product_of(h, s, side == 0 ? at(6) : at(7), side == 0 ? H.b : H.a, nullptr, part, part_bytes, st, &f);
-                if (rc == TN_OK) rc = reduce_sums(f, side == 0 ? H.out_a : H.out_b, s.plan.R, H.S, grad, add, st);
-                if (rc != TN_OK) return rc;
-            }
+        }
+        if (h->mgrad_together) {
+            rc = core_gradients(h, 0, 1, grads, part, part_bytes, add, st);
+            if (rc != TN_OK) return rc;
         }
     }
     return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;

@@ -274,3 +274,24 @@ def test_launches_of_the_factor_pair_tests(fake_hip):
             for tokens, call in zip((1, 300), got["gradient_launches"]):
                 # two tokens a workgroup at 300
                 assert [l.grid for l in call if l.kernel == "factor_grad_kernel"] == [((tokens + 1) // 2, 1)] * (0 if flags else sides), spec
+
+
+def test_launches_of_the_core_gradient_tests(fake_hip):
+    """Rings of that GPU test: one launch for the transposed copies of the activations, one for those of dW, and one for both halves' or
+    one for each; a train's halves, and the four products of its cores' gradients, in a launch each."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    from test_gpu_gradients import RING_CORES, narrow_bond, ring_of_cores
+    made = create_all(fake_hip, [job(ring_of_cores(*ring), 48, flags=tn.TN_FLAG_TRAINABLE, grad_tokens=(48,)) for ring in sorted(RING_CORES)])
+    for ring, got in zip(sorted(RING_CORES), made):
+        assert got["gradients"] == [0]
+        turns = [l.grid[1] for l in got["gradient_launches"][0] if l.kernel == "transpose_kernel"]
+        assert turns == ([2, 2, 4] if RING_CORES[ring] else [2, 2, 2, 2]), (ring, turns)
+    spec, one_pass = narrow_bond(0, 64)
+    got = create(fake_hip, spec, 1000, [], flags=tn.TN_FLAG_TRAINABLE, grad_tokens=(1000,), tokens=(1000,))
+    many = lambda calls: [l.grid[1] for l in calls[0] if l.kernel == "step_gemm_many_kernel"]      # noqa: E731
+    assert one_pass and many(got["launches"]) == [2] and many(got["gradient_launches"]) == [2, 4]
+    assert [l.grid[1] for l in got["gradient_launches"][0] if l.kernel.startswith("grad_reduce")] == [4]
+    # with the gradients of some cores only
+    got = create(fake_hip, spec, 1000, [], flags=tn.TN_FLAG_TRAINABLE, grad_tokens=(1000,), wanted=[1])
+    assert many(got["gradient_launches"]) == [2] and got["gradients"] == [0]

@@ -210,3 +210,26 @@ def test_gradients_of_factor_pairs(case):
         layer.close()
     errs = [O.rel_max_err(g, r) for g, r in zip(*got)]
     assert max(errs) <= 2.0 ** -9, errs
+
+
+# rings through dW: (rank, second in-mode) -> the cores' gradients of both halves in shared launches, or (their halves' too large) one half
+# after the other
+RING_CORES = {(16, 8): True, (32, 16): False}
+
+
+def ring_of_cores(rank, mode):
+    return wl.TNSpec(wl.FORMAT_TR, "bf16", (8, 8, 8, 8), (8, mode, 8, 8), (rank,) * 5)
+
+
+@pytest.mark.parametrize("rank,mode", sorted(RING_CORES))
+def test_core_gradients_of_rings(rank, mode):
+    """Gradients of a ring's cores, with the launches of its two halves shared and not: dW and the halves are kept to 2^-16, as in the
+    narrow bonds above."""
+    spec = ring_of_cores(rank, mode)
+    rng = np.random.default_rng(rank)
+    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(s[0] * s[2]), "bf16") for s in spec.tensor_shapes()]
+    layer = make_layer(spec, ts, 48, flags=tn.TN_FLAG_TRAINABLE)
+    assert 0 < layer.query(tn.TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS) <= 48
+    layer.close()
+    errs = _check(spec, ts, 48, 71 + rank)
+    assert max(errs) <= 2.0 ** -13, errs
