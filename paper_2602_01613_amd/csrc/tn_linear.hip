@@ -42,6 +42,7 @@ namespace {
 #include "kernels/gemm.hpp"
 #include "kernels/stream.hpp"
 #include "kernels/chained.hpp"
+#include "kernels/factorpair.hpp"
 #include "kernels/kronsum.hpp"
 #include "kernels/krondirect.hpp"
 #include "kernels/grad.hpp"
@@ -72,7 +73,8 @@ struct DevStep {
     bool kept = false;            // `packed` is a tensor of the layer (not made by the call that reads it)
     bool fuse_next = false;       // this step and the next run as one launch
     void* chain_bbf = nullptr;    // chain2: the next step's packed tensor in the chained layout
-    int chain_cfg = 0;            // chain2 instantiation: 0 <3,6,5>, 1 <2,8,2>, 2 <2,5,2>
+    int chain_cfg = 0;            // chain2 instantiation: 0 <3,6,5>, 1 <2,8,2>, 2 <2,5,2>; 3: none, only pair_cfg
+    int pair_cfg = -1;            // instantiation of the kernels with a workgroup to a token (factor_pair_configs), -1: none
     int chain_run_c1 = 0;         // chain2: output pieces run along c1 (else along c2)
     void* q4_codes = nullptr;     // 4-bit stream of the tensor for decode-size launches (codes, then block scales)
     void* q4_scales = nullptr;
@@ -2294,6 +2296,96 @@ void place_matrix(tn_linear_s* h, void* mem) {
         }
 }
 
+// ---- both factors on a side of a Tucker core, a workgroup to a token ----
+using factor_pair_t = void (*)(FactorPairArgs, FactorPairArgs);
+struct FactorPairConfig {
+    bool in;                               // the side of the modes comes in
+    int A, B, P, Q;                        // largest extents
+    int per_cu;                            // workgroups on a compute unit
+    factor_pair_t kern;
+    size_t smem;
+};
+
+template <int A32, int B32, int P32, int Q32>
+constexpr FactorPairConfig factor_in_config() {
+    return {true, 32 * A32, 32 * B32, 32 * P32, 32 * Q32, A32 < 5 ? 4 : 2, factor_in_kernel<A32, B32, P32, Q32>, factor_in_smem<A32, B32, P32, Q32>()};
+}
+template <int A32, int B32, int P32, int Q32>
+constexpr FactorPairConfig factor_out_config() {
+    return {false, 32 * A32, 32 * B32, 32 * P32, 32 * Q32, A32 < 5 ? 4 : 2, factor_out_kernel<A32, B32, P32, Q32>, factor_out_smem<A32, B32, P32, Q32>()};
+}
+
+// Modes of up to 64 x 96, 64 x 128 and 160 x 160; the one of the least LDS that holds a pair is taken.
+constexpr int kFactorPairConfigs = 12;
+const FactorPairConfig* factor_pair_configs() {
+    static const FactorPairConfig c[kFactorPairConfigs] = {
+        factor_in_config<2, 3, 2, 2>(),  factor_in_config<2, 4, 2, 2>(),  factor_in_config<2, 4, 2, 3>(),  factor_in_config<5, 5, 1, 1>(),
+        factor_in_config<5, 5, 2, 2>(),  factor_in_config<5, 5, 3, 3>(),  factor_out_config<2, 3, 2, 2>(), factor_out_config<2, 3, 2, 3>(),
+        factor_out_config<2, 4, 2, 3>(), factor_out_config<5, 5, 1, 1>(), factor_out_config<5, 5, 2, 2>(), factor_out_config<5, 5, 3, 3>()};
+    return c;
+}
+
+// Two steps that are such a pair: a token's plain matrix [R][K] in, [C1][R] between them, a plain matrix [C1][C2] out, extents of whole
+// tiles of the matrix cores.
+bool is_factor_pair(const tn::Step& s, const tn::Step& u) {
+    auto strides = [](const std::vector<int32_t>& t, int64_t stride) {
+        for (size_t i = 0; i < t.size(); ++i)
+            if (t[i] != int64_t(i) * stride) return false;
+        return true;
+    };
+    if (!s.a_plain || !u.a_plain || s.trace_extent != 1 || u.trace_extent != 1 || u.R != s.C || u.K != s.R) return false;
+    if (s.R % 16 || s.K % 16 || s.C % 16 || u.C % 16) return false;
+    if (s.a_tok_stride != s.R * s.K || s.c_tok_stride != s.R * s.C || u.a_tok_stride != s.c_tok_stride || u.c_tok_stride != u.R * u.C) return false;
+    return strides(s.crow, 1) && strides(s.ccol, s.R) && strides(u.crow, u.C) && strides(u.ccol, 1);
+}
+
+int factor_pair_config(const tn::Step& s, const tn::Step& u) {
+    if (!is_factor_pair(s, u)) return -1;
+    int best = -1;
+    for (int i = 0; i < kFactorPairConfigs; ++i) {
+        const FactorPairConfig& c = factor_pair_configs()[i];
+        if (!(c.in ? s.R <= c.A && s.K <= c.B && u.C <= c.P && s.C <= c.Q : s.C <= c.A && u.C <= c.B && s.K <= c.P && s.R <= c.Q)) continue;
+        if (best < 0 || c.smem < factor_pair_configs()[best].smem) best = i;
+    }
+    return best;
+}
+
+// Calls of more (token, 32 columns) items than step_chain2_fine_kernel takes, which spreads a token over several compute units: below,
+// that is what counts (ranks of 96 to 160 x 160, one token: 4.5 us there, 5.4 here).
+constexpr int64_t kChain2FineMaxItems = 64;      // (token, c1 tile) items up to which every c2 tile gets a wave of its own
+
+bool factor_pair_applies(const DevStep& s1, int64_t tokens) {
+    return s1.pair_cfg >= 0 && (s1.chain_cfg == 3 || tokens * ((s1.plan.C + 31) / 32) > kChain2FineMaxItems);
+}
+
+FactorPairArgs factor_pair_args(const DevStep& s1, const DevStep& s2, const void* in, void* out, int64_t tokens) {
+    FactorPairArgs a;
+    a.in = static_cast<const bf16_t*>(in);
+    a.out = static_cast<bf16_t*>(out);
+    a.first = static_cast<const bf16_t*>(s1.packed);
+    a.second = static_cast<const bf16_t*>(s2.packed);
+    a.nks_first = s1.Kp >> 4;
+    a.nks_second = s2.Kp >> 4;
+    a.size_first = s1.Cp * s1.Kp * 2;
+    a.size_second = s2.Cp * s2.Kp * 2;
+    const bool i = factor_pair_configs()[s1.pair_cfg].in;
+    const int32_t R = int32_t(s1.plan.R), K = int32_t(s1.plan.K), C1 = int32_t(s1.plan.C), C2 = int32_t(s2.plan.C);
+    a.A = i ? R : C1;
+    a.B = i ? K : C2;
+    a.P = i ? C2 : K;
+    a.Q = i ? C1 : R;
+    a.tokens = int32_t(tokens);
+    return a;
+}
+
+// One launch for a pair of one layer (p1 == nullptr) or of two layers with the same instantiation.
+int launch_factor_pair(const tn_linear_s* h, int cfg, const FactorPairArgs& p0, const FactorPairArgs* p1, hipStream_t st) {
+    const FactorPairConfig& c = factor_pair_configs()[cfg];
+    const int64_t wgs = std::min<int64_t>(p0.tokens, int64_t(h->num_cus) * c.per_cu / (p1 ? 2 : 1));
+    hipLaunchKernelGGL(c.kern, dim3(uint32_t(wgs), p1 ? 2 : 1), dim3(256), c.smem, st, p0, p1 ? *p1 : p0);
+    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
+}
+
 // Pairs of steps the transposing chain kernel can run (see step_chain2_kernel): both plain, the
 // first step's output stored transposed ([c1][r], which is what the second step reads as rows c1
 // with K = r), the output in aligned runs of 8 along c1 or along c2, and sizes within one of the
@@ -2322,6 +2414,17 @@ int plan_chain2(tn_linear_s* h, hipStream_t st) {
         a.chain_cfg = cfg;
         a.chain_run_c1 = run_c1;
     }
+    // pairs for the kernels with a workgroup to a token: those above, and what has more rows or a longer K than they take
+    if (((h->flags >> TN_FLAG_VARIANT_SHIFT) & 0xff) != 0) return TN_OK;
+    for (size_t i = 0; i + 1 < h->steps.size(); ++i) {
+        DevStep& a = h->steps[i];
+        const DevStep& b = h->steps[i + 1];
+        if (a.variant == VAR_SCALAR || b.variant == VAR_SCALAR || (!a.fuse_next && (b.fuse_next || (i > 0 && h->steps[i - 1].fuse_next)))) continue;
+        a.pair_cfg = factor_pair_config(a.plan, b.plan);
+        if (a.fuse_next || a.pair_cfg < 0) continue;
+        a.fuse_next = true;
+        a.chain_cfg = 3;
+    }
     return TN_OK;
 }
 
@@ -2348,10 +2451,9 @@ Chain2Args chain2_args(const DevStep& s1, const DevStep& s2, const void* A, void
 
 // Few tokens: every (token, c1 tile) item of a chained pair gets a wave of its own, operands requested up front.
 bool chain2_small_applies(const tn_linear_s* h, const DevStep& s1, int64_t tokens) {
-    return tokens * ((s1.plan.C + 31) / 32) <= int64_t(h->num_cus) * 4 && !(h->flags & TN_FLAG_NO_DECODE_FUSION);
+    return tokens * ((s1.plan.C + 31) / 32) <= int64_t(h->num_cus) * 4 && !(h->flags & TN_FLAG_NO_DECODE_FUSION) &&
+           !factor_pair_applies(s1, tokens);
 }
-
-constexpr int64_t kChain2FineMaxItems = 64;      // (token, c1 tile) items up to which every c2 tile gets a wave of its own
 
 // One launch for the pair of one layer (p1 == nullptr) or of two layers with the same instantiation.
 int launch_chain2_small(const DevStep& s1, const Chain2Args& p0, const Chain2Args* p1, hipStream_t st) {
@@ -2391,6 +2493,7 @@ int launch_chain2(const tn_linear_s* h, const DevStep& s1, const DevStep& s2, co
                 return TN_ERR_HIP;
         return TN_OK;
     }
+    if (factor_pair_applies(s1, tokens)) return launch_factor_pair(h, s1.pair_cfg, factor_pair_args(s1, s2, A, Out, tokens), nullptr, st);
     Chain2Args p = chain2_args(s1, s2, A, Out, tokens);
     if (chain2_small_applies(h, s1, tokens)) return launch_chain2_small(s1, p, nullptr, st);
     // a wave per token when there are tokens enough to fill the chip, else a wave per (token, c1 tile)
@@ -2415,7 +2518,7 @@ constexpr size_t kFusedDecodeRedBytes = 8 * 1024 * sizeof(float);
 constexpr int kFusedDecodeKPW = 5;           // pieces of 64 k of the wide step per wave: K <= 8 * 5 * 64 = 2560
 
 bool chain2_split_applies(const tn_linear_s* h, const DevStep& s1, const DevStep& s3, int64_t tokens) {
-    if (!s1.fuse_next || s1.chain_cfg == 0 || (h->flags & (TN_FLAG_NO_SPLIT_K | TN_FLAG_NO_DECODE_FUSION))) return false;
+    if (!s1.fuse_next || s1.chain_cfg == 0 || s1.chain_cfg == 3 || (h->flags & (TN_FLAG_NO_SPLIT_K | TN_FLAG_NO_DECODE_FUSION))) return false;
     if (s3.fuse_next || s3.variant == VAR_SCALAR || s3.amode != 0 || s3.plan.R != 1) return false;
     if (tokens * ((s1.plan.C + 31) / 32) > 8 || s3.Kp > 8 * kFusedDecodeKPW * 64) return false;
     if (tokens * s3.plan.a_tok_stride * 2 > kFusedDecodeMaxZBytes) return false;
@@ -2598,6 +2701,10 @@ int configure_kernels(int device) {
          hipFuncSetAttribute(reinterpret_cast<const void*>(bond_grad_kernel<3>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, int(BondGradShape<3>::SMEM)) != hipSuccess))
         rc = TN_ERR_HIP;
+    for (int i = 0; i < kFactorPairConfigs && rc == TN_OK; ++i)
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(factor_pair_configs()[i].kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                int(factor_pair_configs()[i].smem)) != hipSuccess)
+            rc = TN_ERR_HIP;
     for (int i = 0; i < kFactorGradConfigs && rc == TN_OK; ++i)
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(factor_grad_configs()[i].kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 int(factor_grad_configs()[i].smem)) != hipSuccess)
@@ -2813,18 +2920,12 @@ int64_t factor_grad_groups(const tn_linear_s* h, int64_t tokens) {
     return (tokens + each - 1) / each;
 }
 
-// The kernel's layouts: the token's matrix [A][B] and the core side's [Q][P], both row-major, and between them [Q][A] (in-factors)
-// or [A][Q] (out-factors), as the planner lays out a Tucker layer of two modes on that side. Anything else is left to the steps.
+// Pairs at either end of a Tucker layer. Anything else is left to the steps.
 void plan_factor_grad(tn_linear_s* h) {
     const size_t n = h->steps.size();
     if (h->plan.format != TN_FORMAT_TUCKER || h->elt != 2 || n < 3 || (h->flags & (TN_FLAG_SCALAR_KERNELS | TN_FLAG_NO_CHAIN2)) ||
         ((h->flags >> TN_FLAG_VARIANT_SHIFT) & 0xff) != 0)
         return;
-    auto strides = [](const std::vector<int32_t>& t, int64_t stride) {
-        for (size_t i = 0; i < t.size(); ++i)
-            if (t[i] != int64_t(i) * stride) return false;
-        return true;
-    };
     for (int side = 0; side < 2; ++side) {
         if (side == 1 && n < (h->factor_grad[0].on ? 5u : 3u)) break;
         const tn::Step& s = h->steps[side ? n - 2 : 0].plan;
@@ -2832,12 +2933,7 @@ void plan_factor_grad(tn_linear_s* h) {
         tn_linear_s::FactorGrad f;
         if (side == 0) f.A = s.R, f.B = s.K, f.Q = s.C, f.P = u.C;
         else f.A = s.C, f.B = u.C, f.Q = s.R, f.P = s.K;
-        if (!s.a_plain || !u.a_plain || s.trace_extent != 1 || u.trace_extent != 1 || u.R != s.C || u.K != s.R) continue;
-        if (f.A % 16 || f.B % 16 || f.P % 16 || f.Q % 16) continue;       // whole tiles of the matrix cores
-        if (side == 0 ? !(strides(s.crow, 1) && strides(s.ccol, f.A) && strides(u.crow, f.P) && strides(u.ccol, 1))
-                      : !(strides(s.crow, 1) && strides(s.ccol, f.Q) && strides(u.crow, f.B) && strides(u.ccol, 1)))
-            continue;
-        if (s.a_tok_stride != s.R * s.K || s.c_tok_stride != u.a_tok_stride || u.c_tok_stride != u.R * u.C) continue;
+        if (!is_factor_pair(s, u)) continue;
         for (f.cfg = 0; f.cfg < kFactorGradConfigs; ++f.cfg) {
             const FactorGradConfig& c = factor_grad_configs()[f.cfg];
             if (f.A <= c.A && f.B <= c.B && f.P <= c.P && f.Q <= c.Q) break;
@@ -4263,6 +4359,12 @@ int tn_linear_forward2(tn_linear_t ha, tn_linear_t hb, const void* x, void* ya, 
         if (fuse[0] && fuse[1] && fa[0].kern == fa[1].kern) {
             rc = launch_chain2_split(&fa[0], &fa[1], st);          // pair and wide step of both layers in one launch
             skip[0] = skip[1] = true;
+        } else if (!skip[0] && !skip[1] && !fuse[0] && !fuse[1] && l.steps == 2 && factor_pair_applies(ha->steps[f], tokens) &&
+                   factor_pair_applies(hb->steps[f], tokens) && ha->steps[f].pair_cfg == hb->steps[f].pair_cfg) {
+            FactorPairArgs pa[2];
+            for (int n = 0; n < 2; ++n)
+                pa[n] = factor_pair_args(hs[n]->steps[f], hs[n]->steps[f + 1], buffer(n, hs[n]->schedule[li].in), buffer(n, hs[n]->schedule[li].out), tokens);
+            rc = launch_factor_pair(ha, ha->steps[f].pair_cfg, pa[0], &pa[1], st);
         } else if (!skip[0] && !skip[1] && !fuse[0] && !fuse[1] && l.steps == 2 &&
                    chain2_small_applies(ha, ha->steps[f], tokens) && chain2_small_applies(hb, hb->steps[f], tokens)) {
             Chain2Args ca[2];

@@ -295,3 +295,25 @@ def test_launches_of_the_core_gradient_tests(fake_hip):
     # with the gradients of some cores only
     got = create(fake_hip, spec, 1000, [], flags=tn.TN_FLAG_TRAINABLE, grad_tokens=(1000,), wanted=[1])
     assert many(got["gradient_launches"]) == [2] and got["gradients"] == [0]
+
+
+def test_launches_of_the_factor_pair_layers(fake_hip):
+    """Layers of those tests' kind: which side takes a launch with a workgroup to a token, and which instantiation (A, B, P, Q / 32)."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    shapes = [((160, 160), (64, 80), (96, 96, 48, 48), [("in", 2, 3, 2, 2), ("out", 5, 5, 3, 3)]),
+              ((64, 80), (160, 160), (32, 32, 48, 48), [("in", 5, 5, 2, 2), ("out", 2, 3, 2, 2)]),
+              ((64, 128), (64, 128), (48, 48, 16, 16), [("in", 2, 4, 2, 2), ("out", 2, 4, 2, 3)]),
+              ((160, 176), (64, 72), (32, 32, 16, 16), []),                                     # too long, no whole tiles
+              ((160, 160), (64, 80), (112, 96, 48, 48), [("in", 2, 3, 2, 2)])]                  # a rank too large
+    made = create_all(fake_hip, [job(wl.TNSpec(wl.FORMAT_TUCKER, "bf16", om, im, rk), 1100, tokens=(1, 70, 1100)) for om, im, rk, _ in shapes])
+    for (om, im, rk, want), got in zip(shapes, made):
+        for tokens, call in zip((1, 70, 1100), got["launches"]):
+            used = [(l.kernel[7:-7], *l.args) for l in call if l.kernel in ("factor_in_kernel", "factor_out_kernel")]
+            # a token is left to the kernels that spread it, where they hold it (K of the first step up to 128)
+            assert used == ([w for w in want if w[:2] == ("in", 5)] if tokens == 1 else want), (om, im, rk, tokens, used)
+            for l in call:
+                if l.kernel.startswith("factor_"):
+                    assert l.grid == (min(tokens, 256 * (4 if l.args[0] < 5 else 2)), 1)
+    off = create(fake_hip, wl.TNSpec(wl.FORMAT_TUCKER, "bf16", *shapes[0][:3]), 1100, [], flags=tn.TN_FLAG_NO_CHAIN2, tokens=(1100,))
+    assert not [l for l in off["launches"][0] if l.kernel.startswith("factor_")]

@@ -1,0 +1,50 @@
+"""Both factors on a side of a Tucker core in one launch with a workgroup to a token: against the oracle, and against one launch per step."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import workloads as wl
+import paper_2602_01613_amd as tn
+from gpu_util import TOL, make_layer, run_layer, to_dev, to_host
+from test_gpu_gradients import FACTOR_PAIRS, factor_pair
+
+pytestmark = pytest.mark.gpu
+
+
+def pair_layer(case, instance=0):
+    spec, _ = factor_pair(case)
+    rng = np.random.default_rng(500 + 10 * case + instance)
+    return spec, [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(max(1, s[-1])), "bf16") for s in spec.tensor_shapes()]
+
+
+@pytest.mark.parametrize("flags", [0, tn.TN_FLAG_TRANSPOSE])
+@pytest.mark.parametrize("case", range(len(FACTOR_PAIRS)))
+def test_factor_pairs(case, flags):
+    """A token; more items than the kernel that spreads a token takes; more tokens than workgroups fit the chip. The steps round the same
+    values, so what differs from them is the order of fp32 sums and by it a rounding of 2^-9 of some values."""
+    spec, ts = pair_layer(case)
+    for tokens in (1, 70, 1100):
+        n = spec.M if flags else spec.N
+        x = wl.round_to_dtype(np.random.default_rng(case * 7 + tokens).standard_normal((tokens, n)), "bf16")
+        y = run_layer(spec, ts, x, flags=flags)
+        sep = run_layer(spec, ts, x, flags=flags | tn.TN_FLAG_NO_CHAIN2)
+        assert O.rel_max_err(y, sep) <= 1e-2, (case, tokens)
+        if not flags and tokens < 100:
+            ref = O.forward(spec.format, ts, x, n_out_modes=len(spec.out_modes))
+            assert O.rel_max_err(y, ref) <= TOL["bf16"], (case, tokens)
+
+
+@pytest.mark.parametrize("case", [0, 3])
+def test_factor_pairs_of_two_layers(case):
+    """Two layers in one call have the bits of each by itself."""
+    spec, ta = pair_layer(case)
+    _, tb = pair_layer(case, 1)
+    for tokens in (1, 40, 700):
+        a, b = make_layer(spec, ta, tokens), make_layer(spec, tb, tokens)
+        x = to_dev(wl.round_to_dtype(np.random.default_rng(tokens).standard_normal((tokens, spec.N)), "bf16"), "bf16")
+        ya, yb = tn.forward2(a, b, x)
+        torch.cuda.synchronize()
+        assert np.array_equal(to_host(ya), to_host(a(x))) and np.array_equal(to_host(yb), to_host(b(x)))
+        a.close()
+        b.close()
