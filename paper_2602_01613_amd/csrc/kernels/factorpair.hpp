@@ -11,15 +11,16 @@
 //
 // Bound by memory: 18 KB and 51 KB a token for 3.9 million multiply-adds (160 x 160, ranks of 96), 1 us of a compute unit's matrix
 // cores beside 3.5 of its share of the memory's rate. So a workgroup does a whole token between a load and a store of whole rows, and two
-// to four of them on a compute unit cover each other's:
-//   * the token goes to LDS through registers, requested while the one before is multiplied; four waves 2 x 2, the factors' operands
-//     read from L2 for every token ahead of the barrier they are used behind;
+// or three of them on a compute unit cover each other's:
+//   * the token goes to LDS through registers, requested while the one before is multiplied; four waves 2 x 2. A wave's share of the
+//     factors stays in registers where that takes kFactorHeld of them (64 x 80 to ranks of 48, 8192 tokens from memory: 25 us, read from L2
+//     for every token 31), else it is requested ahead of the barrier behind which it is used;
 //   * the intermediate, in the registers of an accumulator along what the second product contracts, goes to LDS in 8-byte pieces. LDS
 //     decides how many workgroups there are, so it takes the place of what has been read: in, of Y; out, of nothing yet, but Y then of
 //     it and of G, and leaves in rows of 16-byte pieces;
 //   * rows in LDS are 16 bytes longer than the data, an odd number of 16-byte units; extents are padded to multiples of 32 with zeros.
-// us at 8192 tokens, a wave to a token (step_chain2_kernel) / so: 64 x 80 to ranks of 48 40 / 23, ranks of 96 to 160 x 160 154 / 123; at
-// 500 tokens 5.4 / 3.6 and 19.5 / 9.9. 160 x 160 to ranks of 96, which that kernel has no registers for, 24.7 at 500 tokens as two launches / 9.2.
+// us at 8192 tokens, a wave to a token (step_chain2_kernel) / so: 64 x 80 to ranks of 48 40 / 25, ranks of 96 to 160 x 160 154 / 125; at
+// 500 tokens 5.4 / 4.8 and 19.5 / 12. 160 x 160 to ranks of 96, which that kernel has no registers for, at 500 tokens 24.7 as two launches / 13.
 // ---------------------------------------------------------------------------------------------
 struct FactorPairArgs {
     const bf16_t* in;
@@ -39,6 +40,7 @@ struct FactorTile {
 
 typedef uint32_t factor_u32x4 __attribute__((ext_vector_type(4)));
 constexpr uint32_t kFactorNowhere = 0x80000000u;
+constexpr int kFactorHeld = 90;             // registers that a workgroup's share of both factors may take to be held throughout
 
 __device__ __forceinline__ bf16x8 factor_fetch(const bf16_t* p, int size, uint32_t at) {
 #ifdef __HIP_DEVICE_COMPILE__
@@ -91,9 +93,27 @@ __global__ void __launch_bounds__(256, 2) factor_in_kernel(FactorPairArgs g0, Fa
 #pragma unroll
         for (int n = 0; n < Ty::N; ++n) ry[n] = factor_fetch(g.in + int64_t(t) * g.A * g.B, g.A * g.B * 2, yo + uint32_t(n * Ty::ROWS * g.B * 2));
     };
+    constexpr bool HOLD = (Q32 * B32 + P32 * A32) * 4 <= kFactorHeld;
+    bf16x8 u2[Q32][B32], u1[P32][A32];
+    auto request_first = [&]() {
+#pragma unroll
+        for (int j = 0; j < Q32; ++j)
+#pragma unroll
+            for (int ks = 0; ks < B32; ++ks) u2[j][ks] = factor_operand(g.first, g.size_first, g.nks_first, wc * Q32 + j, ks, lane);
+    };
+    auto request_second = [&]() {
+#pragma unroll
+        for (int i = 0; i < P32; ++i)
+#pragma unroll
+            for (int ks = 0; ks < A32; ++ks) u1[i][ks] = factor_operand(g.second, g.size_second, g.nks_second, wr * P32 + i, ks, lane);
+    };
     const floatx4 none = {0.f, 0.f, 0.f, 0.f};
     if (int(blockIdx.x) >= g.tokens) return;
     request(blockIdx.x);
+    if constexpr (HOLD) {
+        request_first();
+        request_second();
+    }
     for (int t = blockIdx.x; t < g.tokens; t += gridDim.x) {
         if (y_row < Ty::ROWS) {
 #pragma unroll
@@ -106,11 +126,7 @@ __global__ void __launch_bounds__(256, 2) factor_in_kernel(FactorPairArgs g0, Fa
 #pragma unroll
             for (int j = 0; j < Q32; ++j) acc[i][j] = none;
         {
-            bf16x8 u2[Q32][B32];
-#pragma unroll
-            for (int j = 0; j < Q32; ++j)
-#pragma unroll
-                for (int ks = 0; ks < B32; ++ks) u2[j][ks] = factor_operand(g.first, g.size_first, g.nks_first, wc * Q32 + j, ks, lane);
+            if constexpr (!HOLD) request_first();
             __syncthreads();
             if (t + int(gridDim.x) < g.tokens) request(t + gridDim.x);
             bf16x8 f[2][A32];
@@ -130,11 +146,7 @@ __global__ void __launch_bounds__(256, 2) factor_in_kernel(FactorPairArgs g0, Fa
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        bf16x8 u1[P32][A32];
-#pragma unroll
-        for (int i = 0; i < P32; ++i)
-#pragma unroll
-            for (int ks = 0; ks < A32; ++ks) u1[i][ks] = factor_operand(g.second, g.size_second, g.nks_second, wr * P32 + i, ks, lane);
+        if constexpr (!HOLD) request_second();
         __syncthreads();                                            // Y has been read: S, [q][a], takes its place
 #pragma unroll
         for (int i = 0; i < A32; ++i)
@@ -217,9 +229,27 @@ __global__ void __launch_bounds__(256, 2) factor_out_kernel(FactorPairArgs g0, F
         for (int n = 0; n < Tg::N; ++n) rg[n] = factor_fetch(g.in + int64_t(t) * g.Q * g.P, g.Q * g.P * 2, go + uint32_t(n * Tg::ROWS * g.P * 2));
     };
     const int y_row = tid / Ty::PIECES, y_col = (tid - y_row * Ty::PIECES) * 8;
+    constexpr bool HOLD = (A32 * P32 + B32 * Q32) * 4 <= kFactorHeld;
+    bf16x8 u1[A32][P32], u2[B32][Q32];
+    auto request_first = [&]() {
+#pragma unroll
+        for (int i = 0; i < A32; ++i)
+#pragma unroll
+            for (int ks = 0; ks < P32; ++ks) u1[i][ks] = factor_operand(g.first, g.size_first, g.nks_first, wr * A32 + i, ks, lane);
+    };
+    auto request_second = [&]() {
+#pragma unroll
+        for (int j = 0; j < B32; ++j)
+#pragma unroll
+            for (int ks = 0; ks < Q32; ++ks) u2[j][ks] = factor_operand(g.second, g.size_second, g.nks_second, wc * B32 + j, ks, lane);
+    };
     const floatx4 none = {0.f, 0.f, 0.f, 0.f};
     if (int(blockIdx.x) >= g.tokens) return;
     request(blockIdx.x);
+    if constexpr (HOLD) {
+        request_first();
+        request_second();
+    }
     for (int t = blockIdx.x; t < g.tokens; t += gridDim.x) {
         if (g_row < Tg::ROWS) {
 #pragma unroll
@@ -227,11 +257,8 @@ __global__ void __launch_bounds__(256, 2) factor_out_kernel(FactorPairArgs g0, F
                 if ((n + 1) * Tg::ROWS <= LQ || n * Tg::ROWS + g_row < LQ) *reinterpret_cast<bf16x8*>(sG + (n * Tg::ROWS + g_row) * PG + g_col) = rg[n];
         }
         {
-            bf16x8 u1[A32][P32], f[P32][Q32];
-#pragma unroll
-            for (int i = 0; i < A32; ++i)
-#pragma unroll
-                for (int ks = 0; ks < P32; ++ks) u1[i][ks] = factor_operand(g.first, g.size_first, g.nks_first, wr * A32 + i, ks, lane);
+            bf16x8 f[P32][Q32];
+            if constexpr (!HOLD) request_first();
             __syncthreads();
             if (t + int(gridDim.x) < g.tokens) request(t + gridDim.x);
             floatx4 acc[A32][Q32];
@@ -256,11 +283,7 @@ __global__ void __launch_bounds__(256, 2) factor_out_kernel(FactorPairArgs g0, F
                 for (int j = 0; j < Q32; ++j)
                     *reinterpret_cast<bf16x4_t*>(sT + ((wr * A32 + i) * 16 + l16) * PT + (wc * Q32 + j) * 16 + 4 * h) = round4(acc[i][j]);
         }
-        bf16x8 u2[B32][Q32];
-#pragma unroll
-        for (int j = 0; j < B32; ++j)
-#pragma unroll
-            for (int ks = 0; ks < Q32; ++ks) u2[j][ks] = factor_operand(g.second, g.size_second, g.nks_second, wc * B32 + j, ks, lane);
+        if constexpr (!HOLD) request_second();
         __syncthreads();
         floatx4 o[A32][B32];
 #pragma unroll

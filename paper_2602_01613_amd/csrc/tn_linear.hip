@@ -2308,11 +2308,11 @@ struct FactorPairConfig {
 
 template <int A32, int B32, int P32, int Q32>
 constexpr FactorPairConfig factor_in_config() {
-    return {true, 32 * A32, 32 * B32, 32 * P32, 32 * Q32, A32 < 5 ? 4 : 2, factor_in_kernel<A32, B32, P32, Q32>, factor_in_smem<A32, B32, P32, Q32>()};
+    return {true, 32 * A32, 32 * B32, 32 * P32, 32 * Q32, A32 < 5 ? 3 : 2, factor_in_kernel<A32, B32, P32, Q32>, factor_in_smem<A32, B32, P32, Q32>()};
 }
 template <int A32, int B32, int P32, int Q32>
 constexpr FactorPairConfig factor_out_config() {
-    return {false, 32 * A32, 32 * B32, 32 * P32, 32 * Q32, A32 < 5 ? 4 : 2, factor_out_kernel<A32, B32, P32, Q32>, factor_out_smem<A32, B32, P32, Q32>()};
+    return {false, 32 * A32, 32 * B32, 32 * P32, 32 * Q32, A32 < 5 ? 3 : 2, factor_out_kernel<A32, B32, P32, Q32>, factor_out_smem<A32, B32, P32, Q32>()};
 }
 
 // Modes of up to 64 x 96, 64 x 128 and 160 x 160; the one of the least LDS that holds a pair is taken.

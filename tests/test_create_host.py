@@ -314,6 +314,6 @@ def test_launches_of_the_factor_pair_layers(fake_hip):
             assert used == ([w for w in want if w[:2] == ("in", 5)] if tokens == 1 else want), (om, im, rk, tokens, used)
             for l in call:
                 if l.kernel.startswith("factor_"):
-                    assert l.grid == (min(tokens, 256 * (4 if l.args[0] < 5 else 2)), 1)
+                    assert l.grid == (min(tokens, 256 * (3 if l.args[0] < 5 else 2)), 1)
     off = create(fake_hip, wl.TNSpec(wl.FORMAT_TUCKER, "bf16", *shapes[0][:3]), 1100, [], flags=tn.TN_FLAG_NO_CHAIN2, tokens=(1100,))
     assert not [l for l in off["launches"][0] if l.kernel.startswith("factor_")]
