@@ -317,3 +317,13 @@ def test_launches_of_the_factor_pair_layers(fake_hip):
                     assert l.grid == (min(tokens, 256 * (3 if l.args[0] < 5 else 2)), 1)
     off = create(fake_hip, wl.TNSpec(wl.FORMAT_TUCKER, "bf16", *shapes[0][:3]), 1100, [], flags=tn.TN_FLAG_NO_CHAIN2, tokens=(1100,))
     assert not [l for l in off["launches"][0] if l.kernel.startswith("factor_")]
+
+
+def test_launches_of_the_skinny_tests(fake_hip):
+    """The dense layers of that GPU test take the kernel that it is about."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    from test_gpu_skinny import SKINNY
+    for m, n, tokens, quant in SKINNY:
+        got = create(fake_hip, wl.TNSpec(wl.FORMAT_DENSE, "bf16", (m,), (n,), ()), tokens, [], flags=tn.TN_FLAG_QUANT_MXFP4 if quant else 0, tokens=(tokens,))
+        assert [l.args for l in got["launches"][0] if l.kernel == "step_skinny_kernel"] == [(2 if tokens > 32 else 1, 0, int(quant))], (m, n, tokens)
