@@ -70,7 +70,6 @@ struct DevStep {
     int variant = VAR_SCALAR;
     int amode = 0, cmode = 0;
     int bn = 64, bm = 64;
-    bool kept = false;            // `packed` is a tensor of the layer (not made by the call that reads it)
     bool fuse_next = false;       // this step and the next run as one launch
     void* chain_bbf = nullptr;    // chain2: the next step's packed tensor in the chained layout
     int chain_cfg = 0;            // chain2 instantiation: 0 <3,6,5>, 1 <2,8,2>, 2 <2,5,2>; 3: none, only pair_cfg
@@ -306,7 +305,6 @@ void free_handle(tn_linear_s* h) {
 
 void choose_variant(const tn_linear_s* h, DevStep* s, int flags) {
     const tn::Step& p = s->plan;
-    s->kept = true;
     if (h->plan.dtype != TN_DTYPE_BF16 || (flags & TN_FLAG_SCALAR_KERNELS)) {
         s->variant = VAR_SCALAR;
         s->bm = 64;
@@ -500,31 +498,24 @@ int launch_pipe(const DevStep& s, const StepArgs& a, int64_t rows, hipStream_t s
 // at most. 64 x 64 is for outputs of up to 64 columns, the gradients towards a bond, which read A once and are
 // bound by the loads in flight. Larger tiles do more per us, smaller ones leave less of the last round of workgroups empty and
 // pad fewer rows.
-// c1, c2: t1 and t2 of calls of up to kGemmColdRows rows with a tensor of the layer of kGemmKeptColdBytes or more as the column operand.
-// Between two uses of it a program reads other layers' (a fine-tuning step of one Tucker layer alone moves 400 MB), so it comes
-// from memory, for which the tiles of 256 columns wait most. Fitted to 18 products of 100 to 1500 rows with 23 to 42 MB of
-// it, each time another copy: the choice is 2.9 % above the best on average, with t1 and t2 7.4 % (500 x 2304 x 9216: 192 x 128
-// tiles in four ranges 31 us, 64 x 256 in three 39; 1500 rows: 224 x 256 in four 73, 64 x 256 94, sums added).
 // As times, which is how the orders of contraction are compared, they are 6 % low on average with the column operand in the caches, as W is
 // (0.92 to 1.19 of the price; 70 to 8192 rows of six products of up to 84 MB), and 13 % with it in memory (0.91 to 1.53, most at few rows); of
 // the two products with 262 MB of it 10 % high (0.71 to 1.04).
 struct GemmTile {
     int tm, tn, stages;
-    float t1, o1, t2, o2, c1, c2;
+    float t1, o1, t2, o2;
 };
 constexpr int kGemmTiles = 14;
 constexpr GemmTile kGemmTile[kGemmTiles] = {
-    {8, 8, 2, 1.25f, 7.1f, 0.f, 0.f, 1.32f, 0.f}, {7, 8, 2, 1.14f, 6.4f, 0.f, 0.f, 1.18f, 0.f}, {6, 8, 2, 0.95f, 6.7f, 0.f, 0.f, 1.02f, 0.f},
-    {5, 8, 3, 0.79f, 6.3f, 0.f, 0.f, 0.87f, 0.f}, {4, 8, 3, 0.69f, 5.3f, 0.f, 0.f, 0.81f, 0.f}, {3, 8, 3, 0.59f, 4.4f, 0.f, 0.f, 0.68f, 0.f},
-    {2, 8, 3, 0.43f, 4.6f, 0.f, 0.f, 0.58f, 0.f}, {8, 4, 3, 0.71f, 4.8f, 0.f, 0.f, 0.77f, 0.f}, {6, 4, 3, 0.59f, 4.0f, 0.f, 0.f, 0.62f, 0.f},
-    {5, 4, 2, 0.67f, 3.4f, 0.96f, 4.6f, 0.78f, 1.07f}, {4, 4, 2, 0.61f, 3.2f, 0.84f, 3.7f, 0.76f, 0.97f}, {3, 4, 2, 0.54f, 3.2f, 0.71f, 2.9f, 0.70f, 0.83f},
-    {2, 4, 3, 0.27f, 3.4f, 0.60f, 2.4f, 0.41f, 0.69f}, {2, 2, 4, 0.18f, 3.0f, 0.34f, 3.2f, 0.24f, 0.40f}};
+    {8, 8, 2, 1.25f, 7.1f, 0.f, 0.f}, {7, 8, 2, 1.14f, 6.4f, 0.f, 0.f}, {6, 8, 2, 0.95f, 6.7f, 0.f, 0.f}, {5, 8, 3, 0.79f, 6.3f, 0.f, 0.f},
+    {4, 8, 3, 0.69f, 5.3f, 0.f, 0.f}, {3, 8, 3, 0.59f, 4.4f, 0.f, 0.f}, {2, 8, 3, 0.43f, 4.6f, 0.f, 0.f}, {8, 4, 3, 0.71f, 4.8f, 0.f, 0.f},
+    {6, 4, 3, 0.59f, 4.0f, 0.f, 0.f}, {5, 4, 2, 0.67f, 3.4f, 0.96f, 4.6f}, {4, 4, 2, 0.61f, 3.2f, 0.84f, 3.7f},
+    {3, 4, 2, 0.54f, 3.2f, 0.71f, 2.9f}, {2, 4, 3, 0.27f, 3.4f, 0.60f, 2.4f},
+    {2, 2, 4, 0.18f, 3.0f, 0.34f, 3.2f}};
 
 // A K tile takes at least a load's time divided by the tiles in flight; a column operand above kGemmColdBytes comes from
 // memory. Without this, 600 x 5120 x 8192 takes 64-row tiles (92 us instead of 65).
 constexpr float kGemmColdUs = 1.0f, kGemmColdBytes = 60e6f;
-constexpr float kGemmKeptColdBytes = 20e6f;
-constexpr int64_t kGemmColdRows = 2048;           // more rows pass it through the caches several times
 
 struct GemmChoice {
     int tile = -1, n_split = 1, ktiles_per_split = 1;
@@ -557,7 +548,6 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
     const bool trans = s.cmode != 1;
     const uint32_t cus = uint32_t(h->num_cus);
     const float b_bytes = 2.f * float(s.plan.C) * float(s.Kp);
-    const bool cold = s.kept && rows <= kGemmColdRows && b_bytes >= kGemmKeptColdBytes && b_bytes <= kGemmColdBytes;
     for (int t = only < 0 ? 0 : only; t < (only < 0 ? kGemmTiles : only + 1); ++t) {
         const GemmTile& g = kGemmTile[t];
         if (uint32_t(s.Cp) % uint32_t(32 * g.tn) || (trans && (g.tm & 1))) continue;
@@ -580,10 +570,9 @@ GemmChoice gemm_choice(const tn_linear_s* h, const DevStep& s, int64_t rows, int
             const uint32_t full = items / slots, rest = items - full * slots;
             const bool half = g.t2 > 0.f && rest > 0 && rest <= cus;            // a last round with one workgroup per CU
             const float least = b_bytes > kGemmColdBytes ? kGemmColdUs / float(g.stages - 1) : 0.f;
-            const float t1 = std::max(cold ? g.c1 : g.t1, least), t2 = std::max(cold ? g.c2 : g.t2, least);
-            const float per_tile = g.t2 > 0.f ? t2 : t1, per_round = g.t2 > 0.f ? g.o2 : g.o1;
+            const float per_tile = std::max(g.t2 > 0.f ? g.t2 : g.t1, least), per_round = g.t2 > 0.f ? g.o2 : g.o1;
             const float rounds = float(full + (rest > 0 && !half ? 1 : 0));
-            float us = rounds * per_round + (half ? g.o1 : 0.f) + float(per) * (rounds * per_tile + (half ? t1 : 0.f));
+            float us = rounds * per_round + (half ? g.o1 : 0.f) + float(per) * (rounds * per_tile + (half ? std::max(g.t1, least) : 0.f));
             if (b_bytes > kGemmCachedBytes) {
                 const float bands = 0.25f * float((uint32_t(rows) + 32 * g.tm - 1) / uint32_t(32 * g.tm));
                 const float shown = std::min(1.f, float(64 - g.tm * g.tn) / 24.f);       // the largest tiles hide the passes
