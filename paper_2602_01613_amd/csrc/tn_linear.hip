@@ -46,7 +46,6 @@ namespace {
 #include "kernels/kronsum.hpp"
 #include "kernels/krondirect.hpp"
 #include "kernels/grad.hpp"
-#include "kernels/factorgrad.hpp"
 
 // ---------------------------------------------------------------------------------------------
 // host side
@@ -203,15 +202,6 @@ struct tn_linear_s {
     float* bwd_partial = nullptr;
     int64_t bwd_partial_bytes = 0;
     void* grad_product_mem = nullptr;         // in bwd_ws: transposed operands of launch_grad_product
-    // the factors on a side of a Tucker core in one launch (factor_grad_kernel): [0] steps 0 and 1, [1] the last two
-    struct FactorGrad {
-        bool on = false;
-        int cfg = 0;
-        int64_t A = 0, B = 0, P = 0, Q = 0;
-        int64_t sums_off = 0;                 // of its sums in factor_sums, in elements
-    } factor_grad[2];
-    float* factor_sums = nullptr;             // in bwd_partial, after what the other kernels leave there
-    int64_t factor_sums_bytes = 0;
     // gradients of many tokens: dW = dY^T X, and from it those of the tensors on the cut of tn_matrix.hpp (a dense layer's
     // tensor is W)
     bool mgrad = false;
@@ -2638,27 +2628,6 @@ int prepare_q4_stream(tn_linear_s* h, hipStream_t st) {
 // device current (every GPU holds its own copy of the array at its own address).
 void* g_scratch_ptr[64] = {};
 
-using factor_grad_t = void (*)(FactorGradArgs);
-struct FactorGradConfig {
-    int A, B, P, Q;                        // largest extents
-    factor_grad_t kern;
-    size_t smem;
-};
-
-template <int A32, int B32, int P32, int Q32>
-constexpr FactorGradConfig factor_grad_config() {
-    return {32 * A32, 32 * B32, 32 * P32, 32 * Q32, factor_grad_kernel<A32, B32, P32, Q32>, factor_grad_smem<A32, B32, P32, Q32>()};
-}
-
-// Modes of up to 64 x 128 and of up to 160 x 160, ranks of up to 32, 64 and 96: the first one that holds a pair is taken.
-constexpr int kFactorGradConfigs = 6;
-const FactorGradConfig* factor_grad_configs() {
-    static const FactorGradConfig c[kFactorGradConfigs] = {factor_grad_config<2, 4, 1, 1>(), factor_grad_config<2, 4, 2, 2>(),
-                                                           factor_grad_config<2, 4, 2, 3>(), factor_grad_config<5, 5, 1, 1>(),
-                                                           factor_grad_config<5, 5, 2, 2>(), factor_grad_config<5, 5, 3, 3>()};
-    return c;
-}
-
 int configure_kernels(int device) {
     static bool done[64] = {};
     static std::mutex lock;                // handles may be created from several host threads
@@ -2693,10 +2662,6 @@ int configure_kernels(int device) {
     for (int i = 0; i < kFactorPairConfigs && rc == TN_OK; ++i)
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(factor_pair_configs()[i].kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 int(factor_pair_configs()[i].smem)) != hipSuccess)
-            rc = TN_ERR_HIP;
-    for (int i = 0; i < kFactorGradConfigs && rc == TN_OK; ++i)
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(factor_grad_configs()[i].kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                int(factor_grad_configs()[i].smem)) != hipSuccess)
             rc = TN_ERR_HIP;
     for (int i = 0; i < 4 && rc == TN_OK; ++i)
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(small_chain_kernel_of((i & 1) != 0, (i & 2) != 0)),
@@ -2903,69 +2868,6 @@ int launch_grad_product(const tn_linear_s* h, const DevStep& s, const void* dOut
     return launch_product_of(h, g, a, b, nullptr, nullptr, 0, st, &f);
 }
 
-// ---- the factors on a side of a Tucker core in one launch ----
-int64_t factor_grad_groups(const tn_linear_s* h, int64_t tokens) {
-    const int64_t each = (tokens + h->num_cus - 1) / h->num_cus;
-    return (tokens + each - 1) / each;
-}
-
-// Pairs at either end of a Tucker layer. Anything else is left to the steps.
-void plan_factor_grad(tn_linear_s* h) {
-    const size_t n = h->steps.size();
-    if (h->plan.format != TN_FORMAT_TUCKER || h->elt != 2 || n < 3 || (h->flags & (TN_FLAG_SCALAR_KERNELS | TN_FLAG_NO_CHAIN2)) ||
-        ((h->flags >> TN_FLAG_VARIANT_SHIFT) & 0xff) != 0)
-        return;
-    for (int side = 0; side < 2; ++side) {
-        if (side == 1 && n < (h->factor_grad[0].on ? 5u : 3u)) break;
-        const tn::Step& s = h->steps[side ? n - 2 : 0].plan;
-        const tn::Step& u = h->steps[side ? n - 1 : 1].plan;
-        tn_linear_s::FactorGrad f;
-        if (side == 0) f.A = s.R, f.B = s.K, f.Q = s.C, f.P = u.C;
-        else f.A = s.C, f.B = u.C, f.Q = s.R, f.P = s.K;
-        if (!is_factor_pair(s, u)) continue;
-        for (f.cfg = 0; f.cfg < kFactorGradConfigs; ++f.cfg) {
-            const FactorGradConfig& c = factor_grad_configs()[f.cfg];
-            if (f.A <= c.A && f.B <= c.B && f.P <= c.P && f.Q <= c.Q) break;
-        }
-        f.on = f.cfg < kFactorGradConfigs;
-        h->factor_grad[side] = f;
-    }
-}
-
-// Y: x or dY; G: the gradient of the core's input, or the core's output, whose gradient dG then receives.
-int launch_factor_grad(const tn_linear_s* h, int side, const void* Y, const void* G, void* dG, int64_t tokens, hipStream_t st) {
-    const tn_linear_s::FactorGrad& f = h->factor_grad[side];
-    const size_t n = h->steps.size();
-    auto packed = [](const DevStep& s) { return static_cast<const bf16_t*>(s.packed); };
-    const DevStep& u2t = side ? h->bwd[n - 1] : h->steps[0];
-    const DevStep& u1 = side ? h->steps[n - 2] : h->bwd[1];
-    const DevStep& u1t = side ? h->bwd[n - 2] : h->steps[1];
-    FactorGradArgs a;
-    a.Y = static_cast<const bf16_t*>(Y);
-    a.G = static_cast<const bf16_t*>(G);
-    a.dG = static_cast<bf16_t*>(dG);
-    a.u2t = packed(u2t);
-    a.u1 = packed(u1);
-    a.u1t = packed(u1t);
-    a.nks_u2t = u2t.Kp >> 4;
-    a.nks_u1 = u1.Kp >> 4;
-    a.nks_u1t = u1t.Kp >> 4;
-    a.size_u2t = u2t.Cp * u2t.Kp * 2;
-    a.size_u1 = u1.Cp * u1.Kp * 2;
-    a.size_u1t = u1t.Cp * u1t.Kp * 2;
-    const int64_t groups = factor_grad_groups(h, tokens);
-    a.sums1 = h->factor_sums + f.sums_off;
-    a.sums2 = a.sums1 + groups * f.A * f.P;
-    a.A = int32_t(f.A);
-    a.B = int32_t(f.B);
-    a.P = int32_t(f.P);
-    a.Q = int32_t(f.Q);
-    a.tokens = int32_t(tokens);
-    const FactorGradConfig& c = factor_grad_configs()[f.cfg];
-    hipLaunchKernelGGL(c.kern, dim3(uint32_t(groups)), dim3(256), c.smem, st, a);
-    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
-}
-
 int prepare_backward(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     const size_t n = h->steps.size();
     if (!h->plan.merges.empty()) return TN_ERR_UNSUPPORTED;
@@ -3084,18 +2986,7 @@ int prepare_backward(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st)
     for (const auto& s : h->steps)
         need = std::max(need, int64_t(grad_splits(h, s.plan, chunk * s.plan.R, kMaxGradPartialBytes)) * s.plan.C * s.plan.K * 4);
     h->bwd_partial_bytes = need;
-    // the sums of the factor pairs wait there for each other, while the other kernels' come and go
-    need = (need + 255) & ~int64_t(255);
-    const int64_t sums_at = need;
-    plan_factor_grad(h);
-    for (auto& f : h->factor_grad) {
-        if (!f.on) continue;
-        f.sums_off = (need - sums_at) / 4;
-        need += std::min<int64_t>(chunk, h->num_cus) * (f.A * f.P + f.B * f.Q) * 4;
-    }
     if (hipMalloc(reinterpret_cast<void**>(&h->bwd_partial), size_t(need)) != hipSuccess) return TN_ERR_ALLOC;
-    h->factor_sums = h->bwd_partial + sums_at / 4;
-    h->factor_sums_bytes = need - h->bwd_partial_bytes;
     h->trainable = true;
     return TN_OK;
 }
@@ -3145,40 +3036,6 @@ void launch_grad_reduce_many(const GradOutMany& m, int count, hipStream_t st) {
     const int64_t per = (y ? 64 : 256) * (pairs ? 2 : 1);
     hipLaunchKernelGGL(kerns[2 * y + (pairs ? 1 : 0)], dim3(uint32_t(std::min<int64_t>((most + per - 1) / per, 4096)), uint32_t(count)),
                        dim3(y == 2 ? 1024 : 256), 0, st, m);
-}
-
-// The sums that factor_grad_kernel left, of both sides in one launch.
-int launch_factor_grad_reduce(const tn_linear_s* h, void* const* grads, int64_t tokens, bool accumulate, hipStream_t st) {
-    GradOutMany m;
-    memset(&m, 0, sizeof(m));
-    int count = 0;
-    const size_t n = h->steps.size();
-    const int64_t groups = factor_grad_groups(h, tokens);
-    for (int side = 0; side < 2; ++side) {
-        const tn_linear_s::FactorGrad& f = h->factor_grad[side];
-        if (!f.on) continue;
-        for (int w = 0; w < 2; ++w) {
-            // sums1 [A][P]: the in-factor of step 1 (columns p, k = a), the out-factor of step n - 2 (columns a, k = p); sums2
-            // [B][Q]: of step 0 (columns q, k = b), of step n - 1 (columns b, k = q)
-            const tn::Step& p = h->steps[side ? n - 2 + size_t(w) : size_t(1 - w)].plan;
-            if (!grads[p.slot]) continue;
-            GradOutArgs& o = m.o[count++];
-            const int64_t rows = w ? f.B : f.A, cols = w ? f.Q : f.P;
-            o.partial = h->factor_sums + f.sums_off + (w ? groups * f.A * f.P : 0);
-            o.grad = static_cast<float*>(grads[p.slot]);
-            o.C = uint32_t(rows);
-            o.K = uint32_t(cols);
-            o.ld = cols;
-            o.split_stride = rows * cols;
-            o.n_split = int32_t(groups);
-            o.accumulate = accumulate ? 1 : 0;
-            fill_grad_dims(&o, side ? p.cdims : p.kdims, side ? p.kdims : p.cdims);
-            o.trace_extent = 1;
-        }
-    }
-    if (count == 0) return TN_OK;
-    launch_grad_reduce_many(m, count, st);
-    return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
 
 // dP of one step from dOut and the step's saved input, into the caller's tensor.
@@ -4403,28 +4260,17 @@ int tn_linear_param_gradients(tn_linear_t h, const void* x, const void* dy, void
     for (int64_t t0 = 0; t0 < tokens; t0 += h->bwd_chunk) {
         const int64_t nt = std::min(h->bwd_chunk, tokens - t0);
         const void* xc = static_cast<const char*>(x) + t0 * h->plan.N * h->elt;
-        // forward, one launch per step, every step's input kept; of a factor pair that takes one launch only what the core reads and
-        // writes
-        const bool lead = h->factor_grad[0].on, trail = h->factor_grad[1].on;
+        // forward, one launch per step, every step's input kept
         const void* cur = xc;
-        for (size_t s = 0; s + (trail ? 2 : 1) < n; ++s) {
-            const bool both = lead && s == 0 && h->steps[0].fuse_next;
-            int rc = both ? launch_chain2(h, h->steps[0], h->steps[1], cur, saved(2), nt, st)
-                          : launch_step(h, w, h->steps[s], cur, saved(s + 1), nt, st);
+        for (size_t s = 0; s + 1 < n; ++s) {
+            int rc = launch_step(h, w, h->steps[s], cur, saved(s + 1), nt, st);
             if (rc != TN_OK) return rc;
-            if (both) ++s;
             cur = saved(s + 1);
         }
         // backward
         const void* dcur = static_cast<const char*>(dy) + t0 * h->plan.M * h->elt;
         int toggle = 0;
-        if (trail) {
-            int rc = launch_factor_grad(h, 1, dcur, saved(n - 2), dbufs[toggle], nt, st);
-            if (rc != TN_OK) return rc;
-            dcur = dbufs[toggle];
-            toggle ^= 1;
-        }
-        for (size_t s = trail ? n - 2 : n; s-- > (lead ? 2u : 0u);) {
+        for (size_t s = n; s-- > 0;) {
             const DevStep& fs = h->steps[s];
             const void* in_s = s == 0 ? xc : saved(s);
             void* g = grads[fs.plan.slot];
@@ -4439,14 +4285,6 @@ int tn_linear_param_gradients(tn_linear_t h, const void* x, const void* dy, void
                 dcur = dbufs[toggle];
                 toggle ^= 1;
             }
-        }
-        if (lead) {
-            int rc = launch_factor_grad(h, 0, xc, dcur, nullptr, nt, st);
-            if (rc != TN_OK) return rc;
-        }
-        if (lead || trail) {
-            int rc = launch_factor_grad_reduce(h, grads, nt, t0 > 0, st);
-            if (rc != TN_OK) return rc;
         }
     }
     return TN_OK;
@@ -4556,7 +4394,7 @@ int tn_linear_query(tn_linear_t h, int32_t what, int64_t* value) {
         case TN_QUERY_QUANT_BYTES: *value = h->quant_bytes; return TN_OK;
         case TN_QUERY_QUANT_STREAM_BYTES: *value = h->q4_stream_bytes; return TN_OK;
         case TN_QUERY_BACKWARD_CHUNK_TOKENS: *value = h->trainable ? (h->mgrad ? h->mgrad_chunk : h->bwd_chunk) : 0; return TN_OK;
-        case TN_QUERY_BACKWARD_WORKSPACE_BYTES: *value = h->trainable ? h->bwd_ws_bytes + h->bwd_partial_bytes + h->factor_sums_bytes : 0; return TN_OK;
+        case TN_QUERY_BACKWARD_WORKSPACE_BYTES: *value = h->trainable ? h->bwd_ws_bytes + h->bwd_partial_bytes : 0; return TN_OK;
         default: break;
     }
     if (what >= TN_QUERY_MATRIX_TOKENS_BASE) {

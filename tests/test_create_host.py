@@ -262,20 +262,6 @@ def test_kernels_of_the_gradient_tests(fake_hip):
             assert sorted(l.grid[0] for l in call if l.kernel == "step_mfma_pipe_kernel" and l.args[4] == 3) == grids, (om, rk, tokens)
 
 
-def test_launches_of_the_factor_pair_tests(fake_hip):
-    """Those layers take one launch for the factors of as many sides as the GPU test says, and none with the fused launches off."""
-    import paper_2602_01613_amd as tn
-    from test_gpu_gradients import FACTOR_PAIRS, factor_pair
-    pairs = [factor_pair(case) for case in range(len(FACTOR_PAIRS))]
-    for flags in (0, tn.TN_FLAG_NO_CHAIN2):
-        made = create_all(fake_hip, [job(spec, 300, flags=tn.TN_FLAG_TRAINABLE | flags, grad_tokens=(1, 300)) for spec, _ in pairs])
-        for (spec, sides), got in zip(pairs, made):
-            assert got["gradients"] == [0, 0]
-            for tokens, call in zip((1, 300), got["gradient_launches"]):
-                # two tokens a workgroup at 300
-                assert [l.grid for l in call if l.kernel == "factor_grad_kernel"] == [((tokens + 1) // 2, 1)] * (0 if flags else sides), spec
-
-
 def test_launches_of_the_core_gradient_tests(fake_hip):
     """Rings of that GPU test: one launch for the transposed copies of the activations, one for those of dW, and one for both halves' or
     one for each; a train's halves, and the four products of its cores' gradients, in a launch each."""
