@@ -174,44 +174,6 @@ def test_input_gradients_along_row_runs(case):
         assert max(errs) <= GRAD_TOL["bf16"], (tokens, errs)
 
 
-# Tucker layers whose factors of a side get their gradients from one launch (out-modes, in-modes, ranks), and those just outside
-FACTOR_PAIRS = [((160, 160), (64, 80), (96, 96, 16, 16), 2),        # the largest; in-factors padded to a k-step
-                ((16, 16), (16, 16), (16, 16, 16, 16), 2),          # the smallest
-                ((64, 128), (160, 144), (64, 96, 32, 16), 2),       # the edge of the narrow form; in-factors on the wide one
-                ((80, 64), (64, 128), (80, 48, 48, 16), 2),         # past it in the first mode
-                ((80, 64), (128, 64), (80, 48, 16, 48), 1),         # the outer in-mode first: x is gathered
-                ((64, 144), (48, 112), (32, 64, 32, 64), 0),        # so it is, and the inner out-factor comes first
-                ((32, 176), (64, 128), (32, 32, 32, 32), 1),        # a mode too long for it: the out-factors step by step
-                ((160, 160), (64, 72), (112, 32, 16, 16), 0),       # a rank too large; no whole tiles
-                ((4, 8, 16), (32, 48), (4, 8, 16, 32, 32), 1)]      # three out-modes
-
-
-def factor_pair(case):
-    om, im, rk, sides = FACTOR_PAIRS[case]
-    return wl.TNSpec(wl.FORMAT_TUCKER, "bf16", om, im, rk), sides
-
-
-@pytest.mark.parametrize("case", range(len(FACTOR_PAIRS)))
-def test_gradients_of_factor_pairs(case):
-    """The factors on a side of a Tucker core in one launch: a token and passes whose gradients are added against the oracle, and tokens that
-    leave some workgroups one less than others against the steps (fused launches off), which round the same values: what differs is the
-    order of fp32 sums, and by it one rounding of 2^-9 in some of the intermediates."""
-    spec, _ = factor_pair(case)
-    rng = np.random.default_rng(77 + case)
-    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(max(1, s[-1])), "bf16") for s in spec.tensor_shapes()]
-    for tokens, limit in ((1, 0), (20, 8 * 2 ** 20)):
-        errs = _check(spec, ts, tokens, 61 + tokens, workspace_limit_bytes=limit)
-        assert max(errs) <= GRAD_TOL["bf16"], (tokens, errs)
-    x, dy = (to_dev(wl.round_to_dtype(rng.standard_normal((300, n)), "bf16"), "bf16") for n in (spec.N, spec.M))
-    got = []
-    for flags in (0, tn.TN_FLAG_NO_CHAIN2):
-        layer = make_layer(spec, ts, 300, flags=tn.TN_FLAG_TRAINABLE | flags)
-        got.append([to_host(g) for g in layer.param_gradients(x, dy)])
-        layer.close()
-    errs = [O.rel_max_err(g, r) for g, r in zip(*got)]
-    assert max(errs) <= 2.0 ** -9, errs
-
-
 # rings through dW: (rank, second in-mode) -> the cores' gradients of both halves in shared launches, or (their halves' too large) one half
 # after the other
 RING_CORES = {(16, 8): True, (32, 16): False}
