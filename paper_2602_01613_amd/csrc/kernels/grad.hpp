@@ -499,47 +499,55 @@ struct GradOutArgs {
     int64_t trace_extent, trace_stride;
 };
 
-template <int Y>
-__global__ void __launch_bounds__(Y > 4 ? 64 * Y : 256) grad_reduce_kernel(GradOutArgs a) {
-    constexpr int GROUPS = Y >= 4 ? 1 : 4 / Y;                 // sets of 64 elements a workgroup takes at a time
-    __shared__ float red[Y > 1 ? GROUPS * Y * 64 : 1];
+// V: neighbouring elements of a row that a lane takes (K, ld and split_stride are multiples of it).
+template <int Y, int V>
+__device__ __forceinline__ void grad_reduce(const GradOutArgs& a) {
+    typedef float floats __attribute__((ext_vector_type(V)));
+    constexpr int GROUPS = Y >= 4 ? 1 : 4 / Y;                 // sets of 64 V elements a workgroup takes at a time
+    __shared__ floats red[Y > 1 ? GROUPS * Y * 64 : 1];
     const uint32_t total = a.C * a.K;                          // below 2^31 (checked by the host)
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, y = wave % Y, group = wave / Y;
-    for (uint32_t e0 = (blockIdx.x * GROUPS + group) * 64u; e0 - uint32_t(group) * 64u < total; e0 += gridDim.x * GROUPS * 64u) {
-        const uint32_t e = e0 + lane;
-        uint32_t c = e / a.K, k = e - c * a.K;
+    for (uint32_t e0 = (blockIdx.x * GROUPS + group) * 64u * V; e0 - uint32_t(group) * 64u * V < total; e0 += gridDim.x * GROUPS * 64u * V) {
+        const uint32_t e = e0 + lane * V;
+        uint32_t c = e / a.K;
+        const uint32_t k0 = e - c * a.K;
         c += a.c0;
-        float sum = 0.f;
+        floats sum = {};
         if (e < total) {
-            const float* p = a.partial + int64_t(c) * a.ld + k;
+            const float* p = a.partial + int64_t(c) * a.ld + k0;
 #pragma unroll 8
-            for (int s = y; s < a.n_split; s += Y) sum += p[int64_t(s) * a.split_stride];
+            for (int s = y; s < a.n_split; s += Y) sum += *reinterpret_cast<const floats*>(p + int64_t(s) * a.split_stride);
         }
         if (Y > 1) {
             red[(group * Y + y) * 64 + lane] = sum;
             __syncthreads();
             if (y == 0) {
-                sum = 0.f;
+                sum = floats{};
 #pragma unroll
                 for (int j = 0; j < Y; ++j) sum += red[(group * Y + j) * 64 + lane];
             }
             __syncthreads();
         }
         if (y != 0 || e >= total) continue;
-        int64_t off = 0;
-        for (int j = a.nk - 1; j >= 0; --j) {
-            const uint32_t q = k / a.kext[j];
-            off += int64_t(k - q * a.kext[j]) * a.kstr[j];
-            k = q;
-        }
+        int64_t c_off = 0;
         for (int j = a.nc - 1; j >= 0; --j) {
             const uint32_t q = c / a.cext[j];
-            off += int64_t(c - q * a.cext[j]) * a.cstr[j];
+            c_off += int64_t(c - q * a.cext[j]) * a.cstr[j];
             c = q;
         }
-        for (int64_t d = 0; d < a.trace_extent; ++d) {
-            float* p = a.grad + off + d * a.trace_stride;
-            *p = a.accumulate ? *p + sum : sum;
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            uint32_t k = k0 + v;
+            int64_t off = c_off;
+            for (int j = a.nk - 1; j >= 0; --j) {
+                const uint32_t q = k / a.kext[j];
+                off += int64_t(k - q * a.kext[j]) * a.kstr[j];
+                k = q;
+            }
+            for (int64_t d = 0; d < a.trace_extent; ++d) {
+                float* p = a.grad + off + d * a.trace_stride;
+                *p = a.accumulate ? *p + sum[v] : sum[v];
+            }
         }
     }
 }

@@ -7,13 +7,28 @@ import oracle as O
 import workloads as wl
 import paper_2602_01613_amd as tn
 from gpu_util import TOL, make_layer, run_layer, to_dev, to_host
-from test_gpu_gradients import FACTOR_PAIRS, factor_pair
 
 pytestmark = pytest.mark.gpu
 
+# out-modes, in-modes, ranks
+FACTOR_PAIRS = [((160, 160), (64, 80), (96, 96, 16, 16)),        # the largest; in-factors padded to a k-step
+                ((16, 16), (16, 16), (16, 16, 16, 16)),          # the smallest
+                ((64, 128), (160, 144), (64, 96, 32, 16)),       # the edge of the narrow form; in-factors on the wide one
+                ((80, 64), (64, 128), (80, 48, 48, 16)),         # past it in the first mode
+                ((80, 64), (128, 64), (80, 48, 16, 48)),         # the outer in-mode first: x is gathered
+                ((64, 144), (48, 112), (32, 64, 32, 64)),        # so it is, and the inner out-factor comes first
+                ((32, 176), (64, 128), (32, 32, 32, 32)),        # a mode too long
+                ((160, 160), (64, 72), (112, 32, 16, 16)),       # a rank too large; no whole tiles
+                ((4, 8, 16), (32, 48), (4, 8, 16, 32, 32))]      # three out-modes
+
+
+def factor_pair(case):
+    om, im, rk = FACTOR_PAIRS[case]
+    return wl.TNSpec(wl.FORMAT_TUCKER, "bf16", om, im, rk)
+
 
 def pair_layer(case, instance=0):
-    spec, _ = factor_pair(case)
+    spec = factor_pair(case)
     rng = np.random.default_rng(500 + 10 * case + instance)
     return spec, [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(max(1, s[-1])), "bf16") for s in spec.tensor_shapes()]
 
