@@ -3205,6 +3205,7 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
     };
     float us = 20.f;
     int64_t sums = 0;
+    std::vector<int64_t> second;              // of the second half's dH and its transpose, where they may have room of their own
     if (!dense) {
         room(2, M * N);
         if (!h->mgrad_bond) room(3, M * N);
@@ -3245,21 +3246,29 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
             sums = std::max(sums, std::max(G.F1, G.F2) * round_up(int(H.S), kGradSumsPad) * 4);
             us += 46.f + float(G.F1 * G.F2) * 12.f / 3.5e6f;
         }
-        // (a ring's dH may be as large as dW: one after the other then)
-        h->mgrad_together = h->mgrad_half[0].pair && h->mgrad_half[1].pair && (h->mgrad_bond || (dh + dht) * 4 <= kMatrixTogetherBytes);
         room(6, dh);
         room(7, dht);
-        for (int i = 6; i < 8; ++i) {
-            if (h->mgrad_together) room(i + 2, i == 6 ? dh : dht);
-            else h->mgrad_off[i + 2] = h->mgrad_off[i];
-        }
+        // (a ring's dH may be as large as dW: one after the other then)
+        if (h->mgrad_half[0].pair && h->mgrad_half[1].pair && (h->mgrad_bond || (dh + dht) * 4 <= kMatrixTogetherBytes)) second = {dh, dht};
     }
     // tokens per pass: X and dY transposed, tokens padded to 64
     const int64_t limit = desc->workspace_limit_bytes > 0 ? desc->workspace_limit_bytes : kDefaultWorkspaceBytes;
     const int64_t x_row = (N + tn::kMatrixColPad - 1) / tn::kMatrixColPad * tn::kMatrixColPad * 2, y_row = M * 2;
-    int64_t chunk = grad_tokens_pad(desc->max_tokens);
-    chunk = std::min<int64_t>(chunk, (limit - fixed - 512) / (x_row + y_row) / 64 * 64);
+    auto tokens_in = [&](int64_t taken) {
+        return std::min<int64_t>(grad_tokens_pad(desc->max_tokens), (limit - taken - 512) / (x_row + y_row) / 64 * 64);
+    };
+    const int64_t chunk = tokens_in(fixed);
     if (limit < fixed || chunk < 64) return TN_OK;
+    // both halves' cores in shared launches (44 us of launches less) where the second half's room takes no tokens from a pass, each of
+    // which moves dW again (rank-64 train 5120 -> 8192: 168 MB)
+    const int64_t without = fixed;
+    for (size_t i = 0; i < second.size(); ++i) room(8 + int(i), second[i]);
+    h->mgrad_together = !second.empty() && tokens_in(fixed) == chunk;
+    if (!h->mgrad_together) {
+        fixed = without;
+        h->mgrad_off[8] = h->mgrad_off[6];
+        h->mgrad_off[9] = h->mgrad_off[7];
+    }
     int64_t from = 0;
     const float flops = 3.f * float(h->plan.flops);
     for (int64_t t = kGradMinTokens; t <= desc->max_tokens && !from; t += t < 64 ? 8 : t / 8) {
@@ -3468,13 +3477,13 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
                                           h->mgrad_f[1], h->mgrad_f[0], false);
             launch_transposes(parts, 2, st);
         }
-        if (h->mgrad_bond) {
-            // the sums of its ranges or row panels, in place and in two parts
+        // one pass over dW: the sums of its ranges or row panels, in place and in two parts
+        auto bond_sums = [&](int first, int last) {
             SplitReducePartsTwo two;
             memset(&two, 0, sizeof(two));
             int n = 0;
             int64_t most = 0;
-            for (int i = 0; i < 2; ++i) {
+            for (int i = first; i <= last; ++i) {
                 if (!wanted[i]) continue;
                 const auto& H = h->mgrad_half[i];
                 SplitReduceParts& r = two.p[n++];
@@ -3491,7 +3500,8 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
             }
             hipLaunchKernelGGL(step_split_reduce_parts_two_kernel, dim3(uint32_t(std::min<int64_t>((most + 255) / 256, 8192)), uint32_t(n)),
                                dim3(256), 0, st, two);
-        }
+        };
+        if (h->mgrad_bond && h->mgrad_together) bond_sums(0, 1);
         for (int i = 0; i < 2; ++i) {
             if (!wanted[i]) continue;
             const auto& H = h->mgrad_half[i];
@@ -3505,6 +3515,7 @@ int matrix_gradients(tn_linear_s* h, const void* x, const void* dy, void* const*
                 continue;
             }
             if (!h->mgrad_bond) rc = launch_product_of(h, H.dh, at(2 + i), op, at(6 + 2 * i), part, part_bytes, st);
+            else if (!h->mgrad_together) bond_sums(i, i);
             if (rc == TN_OK && !h->mgrad_together) rc = core_gradients(h, i, i, grads, part, part_bytes, add, st);
             if (rc != TN_OK) return rc;
         }

@@ -313,3 +313,26 @@ def test_launches_of_the_skinny_tests(fake_hip):
     for m, n, tokens, quant in SKINNY:
         got = create(fake_hip, wl.TNSpec(wl.FORMAT_DENSE, "bf16", (m,), (n,), ()), tokens, [], flags=tn.TN_FLAG_QUANT_MXFP4 if quant else 0, tokens=(tokens,))
         assert [l.args for l in got["launches"][0] if l.kernel == "step_skinny_kernel"] == [(2 if tokens > 32 else 1, 0, int(quant))], (m, n, tokens)
+
+
+def test_room_of_gradients_through_dw(fake_hip):
+    """A second place for a half's gradient, for shared launches, is taken only where it takes no tokens from a pass: the smallest limits
+    under which these layers took the order through dW still give it, with 64 tokens to a pass, and each further 64 tokens' X and dY make
+    a pass 64 tokens longer."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    from test_gpu_gradients import ring_of_cores, tight_layers
+    whats = [tn.TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS, tn.TN_QUERY_BACKWARD_CHUNK_TOKENS]
+    layers = [(wl.baseline_spec(1)[0], 189.5e6), (wl.stack_spec(wl.FORMAT_TT, 25600, 5120, 96), 564.8e6), (ring_of_cores(16, 8), 152.2e6), (ring_of_cores(8, 8), 78.8e6)]
+    more = (0, 1, 3, 10)
+    made = create_all(fake_hip, [job(spec, 1000, whats, int(limit) + k * 64 * 2 * (spec.M + spec.N), tn.TN_FLAG_TRAINABLE) for spec, limit in layers for k in more])
+    for n, got in enumerate(made):
+        assert got["rc"] == 0 and got[str(whats[0])] > 0 and got[str(whats[1])] == 64 * (1 + more[n % len(more)]), (n, got)
+    # the layers of the GPU test of this: a half's sums and its cores' products, then the other's
+    made = create_all(fake_hip, [job(spec, tokens, whats, limit, tn.TN_FLAG_TRAINABLE, grad_tokens=(tokens,)) for spec, tokens, limit in tight_layers()])
+    for (spec, tokens, _), got in zip(tight_layers(), made):
+        assert got["gradients"] == [0] and got[str(whats[1])] == (192 if tokens == 300 else 64)
+        calls = got["gradient_launches"][0]
+        passes = (tokens + got[str(whats[1])] - 1) // got[str(whats[1])]
+        assert [l.grid[1] for l in calls if l.kernel == "grad_reduce_many_kernel"] == [2, 2] * passes
+        assert [l.grid[1] for l in calls if l.kernel == "step_split_reduce_parts_two_kernel"] == ([1, 1] * passes if spec.format == wl.FORMAT_TT else [])

@@ -195,3 +195,22 @@ def test_core_gradients_of_rings(rank, mode):
     layer.close()
     errs = _check(spec, ts, 48, 71 + rank)
     assert max(errs) <= 2.0 ** -13, errs
+
+
+# (layer, tokens, workspace limit): no room for the second half's gradients beside the first's, so one half after the other
+def tight_layers():
+    return [(narrow_bond(1, 64)[0], 300, 6 << 20), (narrow_bond(2, 96)[0], 300, 7 << 20), (ring_of_cores(16, 8), 48, 146 << 20)]
+
+
+@pytest.mark.parametrize("n", range(3))
+def test_core_gradients_in_little_room(n):
+    """A limit that leaves the halves' gradients one place: both halves one after the other, in two passes over the tokens for the trains, as
+    exact as above."""
+    spec, tokens, limit = tight_layers()[n]
+    rng = np.random.default_rng(90 + n)
+    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(s[0] * s[2]), "bf16") for s in spec.tensor_shapes()]
+    layer = make_layer(spec, ts, tokens, limit, flags=tn.TN_FLAG_TRAINABLE)
+    assert 0 < layer.query(tn.TN_QUERY_GRADIENT_MATRIX_MIN_TOKENS) <= tokens
+    layer.close()
+    errs = _check(spec, ts, tokens, 91 + n, workspace_limit_bytes=limit)
+    assert max(errs) <= 2.0 ** -13, errs
