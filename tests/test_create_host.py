@@ -22,11 +22,16 @@ hip = ctypes.CDLL(os.environ['LD_PRELOAD'])
 hip.fake_hip_take_launches.restype = ctypes.c_char_p
 def launches():
     return [[l.split()[0]] + [int(v) for v in l.split()[1:]] for l in hip.fake_hip_take_launches().decode().splitlines()]
-def layer(fmt, dtype, out_modes, in_modes, ranks, max_tokens, limit, flags, whats, scratch_tokens, grad_tokens, tokens, wanted):
+block = None
+def layer(fmt, dtype, out_modes, in_modes, ranks, max_tokens, limit, flags, whats, scratch_tokens, grad_tokens, tokens, wanted, block_bytes):
+    global block
+    if block_bytes and block is None:
+        block = ctypes.create_string_buffer(block_bytes + 256)
     spec = wl.TNSpec(fmt, dtype, tuple(out_modes), tuple(in_modes), tuple(ranks))
     mem = ctypes.create_string_buffer(64)
     ptrs = [ctypes.addressof(mem)] * len(spec.tensor_shapes())
-    d, keep = _make_desc(fmt, tn.TN_DTYPE_BF16 if dtype == 'bf16' else tn.TN_DTYPE_F32, out_modes, in_modes, ranks, ptrs, max_tokens, limit, flags, None)
+    d, keep = _make_desc(fmt, tn.TN_DTYPE_BF16 if dtype == 'bf16' else tn.TN_DTYPE_F32, out_modes, in_modes, ranks, ptrs, max_tokens, limit, flags, None,
+                         (ctypes.addressof(block) + 255) // 256 * 256 if block_bytes else None, block_bytes)
     h = ctypes.c_void_p()
     rc = lib.tn_linear_create(ctypes.byref(h), ctypes.byref(d))
     res = {"rc": rc}
@@ -63,10 +68,10 @@ def fake_hip():
     return out
 
 
-def job(spec, max_tokens, whats=(), limit=0, flags=0, scratch_tokens=(), grad_tokens=(), tokens=(), wanted=None):
+def job(spec, max_tokens, whats=(), limit=0, flags=0, scratch_tokens=(), grad_tokens=(), tokens=(), wanted=None, block_bytes=0):
     """A layer to make, and what to do with it."""
     return [spec.format, spec.dtype, list(spec.out_modes), list(spec.in_modes), list(spec.ranks), max_tokens, limit, flags, list(whats),
-            list(scratch_tokens), list(grad_tokens), list(tokens), wanted]
+            list(scratch_tokens), list(grad_tokens), list(tokens), wanted, block_bytes]
 
 
 def create_all(fake_hip, jobs, refuse=None):
@@ -336,3 +341,18 @@ def test_room_of_gradients_through_dw(fake_hip):
         passes = (tokens + got[str(whats[1])] - 1) // got[str(whats[1])]
         assert [l.grid[1] for l in calls if l.kernel == "grad_reduce_many_kernel"] == [2, 2] * passes
         assert [l.grid[1] for l in calls if l.kernel == "step_split_reduce_parts_two_kernel"] == ([1, 1] * passes if spec.format == wl.FORMAT_TT else [])
+
+
+def test_launches_of_one_range_and_of_most_tokens(fake_hip):
+    """The calls of that GPU test: without ranges of K the on-chip kernel alone, at the most tokens it and the launch that adds its sums."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    from test_gpu_direct import DIRECT_LAYERS, MOST_TOKENS, ONE_RANGE
+    for calls, tokens, flags in ((ONE_RANGE, (1, 7), tn.TN_FLAG_NO_SPLIT_K), (MOST_TOKENS, (16,), 0)):
+        made = create_all(fake_hip, [job(wl.TNSpec(fmt, "bf16", om, im, rk), 16, flags=flags, tokens=tokens, block_bytes=(1 << 30) * in_block)
+                                     for (fmt, om, im, rk, _, _), in_block in ((DIRECT_LAYERS[n], b) for n, b in calls)])
+        for (n, _), got in zip(calls, made):
+            for call in got["launches"]:
+                assert call[0].kernel == "step_krondirect_kernel" and call[0].args == DIRECT_LAYERS[n][4:], (n, call)
+                assert len(call) == (1 if flags else 2), (n, call)
+    assert {DIRECT_LAYERS[n][4] for n, _ in ONE_RANGE} == {0, 1, 2, 4}

@@ -49,3 +49,26 @@ def test_slices_made_on_chip(n):
             assert torch.equal(layer(xd), y)
     own.close()
     shared.close()
+
+
+# layers of the above that one workgroup a token walks the whole bond of where K ranges are switched off, straight to the output: one of each
+# instantiation that is cheaper so than the slices in memory, and whether in a shared workspace; and those that 16 tokens, the most, take
+ONE_RANGE = [(0, False), (1, False), (2, False), (4, True), (5, False), (6, True), (9, False), (10, False)]
+MOST_TOKENS = [(0, True), (10, True), (11, True), (11, False)]
+
+
+@pytest.mark.parametrize("n,in_block,tokens,flags", [(n, b, t, tn.TN_FLAG_NO_SPLIT_K) for n, b in ONE_RANGE for t in (1, 7)] + [(n, b, 16, 0) for n, b in MOST_TOKENS])
+def test_one_range_and_most_tokens(n, in_block, tokens, flags):
+    fmt, om, im, rk, _, _ = DIRECT_LAYERS[n]
+    spec = wl.TNSpec(fmt, "bf16", om, im, rk)
+    ts = wl.make_tensors(spec, 4, instance=720 + n)
+    rows = np.unique(np.concatenate([np.random.default_rng(n).choice(spec.M, 46, replace=False), [0, spec.M - 1]]))
+    w = O.tr_dense_rows(ts, rows) if fmt == wl.FORMAT_TR else O.dense_weight(fmt, ts, len(om))[rows]
+    block = torch.full((1 << 30,), 0xFF, dtype=torch.uint8, device="cuda") if in_block else None
+    layer = tn.TNLinear(fmt, dtype_code("bf16"), om, im, rk, [to_dev(t, "bf16") for t in ts], 16, flags=flags, workspace=block)
+    x = wl.make_x(spec, tokens, 4, instance=720 + n)
+    xd = to_dev(x, "bf16")
+    y = layer(xd)
+    assert O.rel_max_err(to_host(y)[:, rows], O.apply_linear(w, x)) <= TOL["bf16"]
+    assert torch.equal(layer(xd), y)
+    layer.close()
