@@ -1721,14 +1721,17 @@ int64_t direct_sums(const tn_linear_s* h) {
 }
 
 // Blocks of the bond for the workgroups of a call, one to a compute unit, of the least time: the launches, a value of the bond
-// (0.2 us, 0.5 with the resident cores in LDS, and 12 ns per MFMA of a wave), a turn of the resident cores, and the partial sums written and read. Expected /
-// measured, us: rings of one token 5120 -> 8192 rank 96 57 / 50 to 56, rank 32 17 / 16; 5120 -> 25600 rank 96 108 / 104 to 111, rank 32 30 / 31;
-// 25600 -> 5120 rank 96 99 / 102 to 109; 5120 -> 1024 rank 96 32 / 26 to 29; of two tokens 5120 -> 8192 rank 96 101 / 86.
+// (0.2 us, 0.5 with the resident cores in LDS, and 12 ns per MFMA of a wave), a turn of the resident cores (in LDS, longer the more steps
+// they have, the first of them above all), and the partial sums written and read. Expected / measured, us: rings of one token 5120 -> 8192
+// rank 96 57 / 56, rank 32 17 / 16; 5120 -> 25600 rank 96 108 / 104 to 116, rank 32 30 / 31; 25600 -> 5120 rank 96 104 / 110 to 116;
+// 5120 -> 1024 rank 96 32 / 28; of two tokens 5120 -> 8192 rank 96 98 / 90; trains 25600 -> 5120 rank 96 at 1, 6, 12 and 16 tokens 17.5 / 17.4,
+// 26.7 / 26.4, 35.4 / 35.1, 39.6 / 39.7 (28.2 and 31.7 for the last two, were a turn the same everywhere), rank 64 at 12 26.3 / 25.9.
 DirectGeom direct_geometry(const tn_linear_s* h, int64_t tokens, int64_t partial_cap) {
     const KronDirectArgs& a = h->direct_args;
     const int* g = tn::kDirectConfig[h->direct_cfg];
     const int mfmas = h->direct_steps * (g[6] * g[7] + g[9] * g[10]) + g[2] * (g[0] * g[1] + g[3] * ((g[0] + 1) / 2));
     const float per_value = (g[12] ? 0.5f : 0.2f) + float(mfmas) * 0.0123f;
+    const float more = g[12] ? float(h->direct_steps - 1) : 0.f, first = 9.f + 1.7f * more, per_turn = 1.f + 0.375f * more;
     const int64_t slots = std::max<int64_t>(1, h->num_cus / tokens);
     DirectGeom best;
     best.us = std::numeric_limits<float>::max();
@@ -1744,7 +1747,7 @@ DirectGeom direct_geometry(const tn_linear_s* h, int64_t tokens, int64_t partial
             c.n_splits = (a.n_res + c.res_per - 1) / c.res_per * str_blocks;
             c.partial_bytes = c.n_splits > 1 ? int64_t(c.n_splits) * tokens * direct_sums(h) * 4 : 0;
             const int64_t rounds = (tokens * c.n_splits + h->num_cus - 1) / h->num_cus;
-            c.us = 9.f + float(rounds) * float(c.res_per) * (1.f + float(str_per) * per_value) + float(c.partial_bytes) / 2e6f;
+            c.us = first + float(rounds) * float(c.res_per) * (per_turn + float(str_per) * per_value) + float(c.partial_bytes) / 2e6f;
             if (c.partial_bytes <= partial_cap && c.us < best.us) best = c;
         }
     }
@@ -1760,7 +1763,10 @@ void price_direct(tn_linear_s* h) {
     for (int64_t t = 1; h->direct && t <= std::min(h->max_tokens, kDirectMaxTokens); ++t) {
         DirectGeom g = direct_geometry(h, t, h->partial ? h->partial_bytes : 0);
         const float slices = h->lazy_slices_kept ? 0.f : 8.f + float(h->lazy_slice_bytes) / 3.4e6f;
-        g.taken = g.us < kron_us(h, h->lazy_dims, kron_geometry(h, h->lazy_dims, t, h->partial ? h->partial_bytes : 0)) + slices;
+        const KronGeom k = kron_geometry(h, h->lazy_dims, t, h->partial ? h->partial_bytes : 0);
+        // one workgroup walks the bond, one token: its four waves share a value there (rank-96 ring 25600 -> 5120 on chip 19.9 ms, from memory
+        // 16.0, from 2 tokens on 20.0 and 31.7; rank-96 train 562 us and 167)
+        g.taken = g.us < kron_us(h, h->lazy_dims, k) * (k.share && k.n_splits == 1 ? 0.5f : 1.f) + slices;
         h->direct_geom[t] = g;
     }
 }

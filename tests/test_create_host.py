@@ -348,7 +348,7 @@ def test_launches_of_one_range_and_of_most_tokens(fake_hip):
     import paper_2602_01613_amd as tn
     import workloads as wl
     from test_gpu_direct import DIRECT_LAYERS, MOST_TOKENS, ONE_RANGE
-    for calls, tokens, flags in ((ONE_RANGE, (1, 7), tn.TN_FLAG_NO_SPLIT_K), (MOST_TOKENS, (16,), 0)):
+    for calls, tokens, flags in ((ONE_RANGE, (2, 7), tn.TN_FLAG_NO_SPLIT_K), (MOST_TOKENS, (16,), 0)):
         made = create_all(fake_hip, [job(wl.TNSpec(fmt, "bf16", om, im, rk), 16, flags=flags, tokens=tokens, block_bytes=(1 << 30) * in_block)
                                      for (fmt, om, im, rk, _, _), in_block in ((DIRECT_LAYERS[n], b) for n, b in calls)])
         for (n, _), got in zip(calls, made):
@@ -356,3 +356,21 @@ def test_launches_of_one_range_and_of_most_tokens(fake_hip):
                 assert call[0].kernel == "step_krondirect_kernel" and call[0].args == DIRECT_LAYERS[n][4:], (n, call)
                 assert len(call) == (1 if flags else 2), (n, call)
     assert {DIRECT_LAYERS[n][4] for n, _ in ONE_RANGE} == {0, 1, 2, 4}
+
+
+def test_slices_on_chip_of_resident_cores_in_lds(fake_hip):
+    """A train 25600 -> 5120 of rank 96, whose resident cores go to LDS, 45 KB a turn: from 12 tokens on a workgroup has so many turns that the
+    slices in memory are the faster way. Rank 64 has fewer and shorter ones."""
+    import workloads as wl
+    made = create_all(fake_hip, [job(wl.stack_spec(wl.FORMAT_TT, 25600, 5120, rank), 16, tokens=(1, 8, 12, 16)) for rank in (64, 96)])
+    assert [[call[0].kernel == "step_krondirect_kernel" for call in got["launches"]] for got in made] == [[True] * 4, [True, True, False, False]]
+
+
+def test_slices_on_chip_without_ranges(fake_hip):
+    """Rank-96 layers without ranges of K: at one token, which four waves share there, the slices stay in memory; a ring's are made on chip from two
+    tokens on, those of a train 25600 -> 5120, each with its turn of resident cores, never."""
+    import paper_2602_01613_amd as tn
+    import workloads as wl
+    layers = [(wl.FORMAT_TR, 5120, 8192), (wl.FORMAT_TR, 25600, 5120), (wl.FORMAT_TT, 25600, 5120)]
+    made = create_all(fake_hip, [job(wl.stack_spec(fmt, n, m, 96), 16, flags=tn.TN_FLAG_NO_SPLIT_K, tokens=(1, 2, 16)) for fmt, n, m in layers])
+    assert [[call[0].kernel == "step_krondirect_kernel" for call in got["launches"]] for got in made] == [[False, True, True]] * 2 + [[False] * 3]
