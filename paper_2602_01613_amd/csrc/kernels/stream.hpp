@@ -522,11 +522,12 @@ __global__ void __launch_bounds__(512) step_skinny_kernel(StepArgs a, float* par
             for (int ks = 0; ks < 4; ++ks) bf[Q4 ? 0 : u][ks] = *reinterpret_cast<const bf16x8*>(Bp + (int64_t(ch) * 4 + ks) * 512);
         }
     };
-    // the rows of A over the split's k range, zero past K: the first pieces of every thread are requested ahead of the stream, which is then
-    // in flight while they go to LDS (loads return in order, so behind it they waited for its first D pieces and left nothing in
-    // flight; a wave without columns requests like the others, so that what a piece waits for is known: nothing behind it). us, the
-    // stream first / so: dense 25600 -> 5120 in 4 bits at 8 rows 19.2 / 18.2, 33 rows 31.1 / 29.4; 8192 -> 5120 in 4 bits, 64 rows 22.3 / 20.5;
-    // 5120 -> 8192 in bf16, 64 rows 29.1 / 27.2. Up to 32 rows in bf16 it is the stream's first pieces that count (262 MB: 54.5 / 54.7).
+    // the rows of A over the split's k range, zero past K. Where the split is longer than the D pieces first in flight, the first pieces of
+    // every thread are requested ahead of the stream, which is then in flight while they go to LDS (loads return in order, so behind it
+    // they waited for its first D pieces and left nothing in flight; a wave without columns requests like the others, so that what a
+    // piece waits for is known: nothing behind it). us, the stream first / so: dense 25600 -> 5120 in 4 bits at 8 rows 19.2 / 18.2, 33 rows
+    // 31.1 / 29.4; 8192 -> 5120 in 4 bits, 64 rows 22.3 / 20.5; 5120 -> 8192 in bf16, 64 rows 29.1 / 27.2. Up to 32 rows in bf16 it is the
+    // stream's first pieces that count (262 MB: 54.5 / 54.7), and a split of no more than D pieces has all of its stream in flight either way.
     constexpr int EARLY = AMODE == 0 && (Q4 || TM > 1) ? 6 : 0;
     const int k0 = ch_begin * 64, pieces_per_row = (ch_end - ch_begin) * 8, pieces = rows * pieces_per_row;
     auto base_of = [&](int g) {
@@ -538,34 +539,40 @@ __global__ void __launch_bounds__(512) step_skinny_kernel(StepArgs a, float* par
     for (int i = 0; i < 8; ++i) none[i] = bf16_t(0.f);
     bf16x8 early[EARLY > 0 ? EARLY : 1];
     int row[EARLY > 0 ? EARLY : 1], piece[EARLY > 0 ? EARLY : 1];                 // one division for all of them: a step is 512 pieces
-    const int step_rows = 512 / pieces_per_row, step_pieces = 512 - step_rows * pieces_per_row;
     const bool flat = a.R == 1 || a.a_tok_stride == int64_t(a.R) * a.K;
+    const bool ahead = EARLY > 0 && ch_end - ch_begin > D;                        // workgroup-uniform
+    if (ahead) {
+        const int step_rows = 512 / pieces_per_row, step_pieces = 512 - step_rows * pieces_per_row;
 #pragma unroll
-    for (int j = 0; j < EARLY; ++j) {
-        if (j == 0) {
-            row[0] = tid / pieces_per_row;
-            piece[0] = tid - row[0] * pieces_per_row;
-        } else {
-            piece[j] = piece[j - 1] + step_pieces;
-            row[j] = row[j - 1] + step_rows;
-            if (piece[j] >= pieces_per_row) {
-                piece[j] -= pieces_per_row;
-                ++row[j];
+        for (int j = 0; j < EARLY; ++j) {
+            if (j == 0) {
+                row[0] = tid / pieces_per_row;
+                piece[0] = tid - row[0] * pieces_per_row;
+            } else {
+                piece[j] = piece[j - 1] + step_pieces;
+                row[j] = row[j - 1] + step_rows;
+                if (piece[j] >= pieces_per_row) {
+                    piece[j] -= pieces_per_row;
+                    ++row[j];
+                }
             }
+            const int g = min(row[j], rows - 1);
+            const int64_t base = flat ? int64_t(g) * (a.R == 1 ? a.a_tok_stride : int64_t(a.K)) : base_of(g);
+            early[j] = *reinterpret_cast<const bf16x8*>(A + base + min(k0 + 8 * piece[j], a.K - 8));
         }
-        const int g = min(row[j], rows - 1);
-        const int64_t base = flat ? int64_t(g) * (a.R == 1 ? a.a_tok_stride : int64_t(a.K)) : base_of(g);
-        early[j] = *reinterpret_cast<const bf16x8*>(A + base + min(k0 + 8 * piece[j], a.K - 8));
-    }
-    __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int u = 0; u < D; ++u) request(u, min(ch_begin + u, ch_end - 1));        // pieces past the split: its last one, unused
-    __builtin_amdgcn_sched_barrier(0);
+        for (int u = 0; u < D; ++u) request(u, ch_begin + u);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int j = 0; j < EARLY; ++j) {
-        if (row[j] < rows) *reinterpret_cast<bf16x8*>(xs + row[j] * x_ld + 8 * piece[j]) = k0 + 8 * piece[j] < a.K ? early[j] : none;
+        for (int j = 0; j < EARLY; ++j) {
+            if (row[j] < rows) *reinterpret_cast<bf16x8*>(xs + row[j] * x_ld + 8 * piece[j]) = k0 + 8 * piece[j] < a.K ? early[j] : none;
+        }
+    } else if (has_cols) {
+#pragma unroll
+        for (int u = 0; u < D; ++u) request(u, min(ch_begin + u, ch_end - 1));    // pieces past the split: its last one, unused
     }
-    for (int e = tid + 512 * EARLY; e < pieces; e += 512) {
+    for (int e = tid + (ahead ? 512 * EARLY : 0); e < pieces; e += 512) {
         const int g = e / pieces_per_row, k = k0 + 8 * (e - g * pieces_per_row);
         const int64_t base = base_of(g);
         bf16x8 v = none;
