@@ -2551,13 +2551,17 @@ Chain2SplitArgs chain2_split_args(const DevStep& s1, const DevStep& s2, const De
 // One launch for one layer (p1 == nullptr) or for two layers on the same instantiation (grid.y = 2).
 int launch_chain2_split(const Chain2SplitArgs* p0, const Chain2SplitArgs* p1, hipStream_t st) {
     using k_t = void (*)(Chain2Args, StepArgs, int, Chain2Args, StepArgs, int);
-    static const k_t kerns[8] = {
-        step_chain2_split_kernel<8, 0, kFusedDecodeKPW, 0>, step_chain2_split_kernel<8, 1, kFusedDecodeKPW, 0>,
-        step_chain2_split_kernel<5, 0, kFusedDecodeKPW, 0>, step_chain2_split_kernel<5, 1, kFusedDecodeKPW, 0>,
-        step_chain2_split_kernel<8, 0, kFusedDecodeKPW, 1>, step_chain2_split_kernel<8, 1, kFusedDecodeKPW, 1>,
-        step_chain2_split_kernel<5, 0, kFusedDecodeKPW, 1>, step_chain2_split_kernel<5, 1, kFusedDecodeKPW, 1>};
+    static const k_t kerns[16] = {                                  // a block to a workgroup, several
+        step_chain2_split_kernel<8, 0, kFusedDecodeKPW, 0, 0>, step_chain2_split_kernel<8, 0, kFusedDecodeKPW, 0, 1>,
+        step_chain2_split_kernel<8, 1, kFusedDecodeKPW, 0, 0>, step_chain2_split_kernel<8, 1, kFusedDecodeKPW, 0, 1>,
+        step_chain2_split_kernel<5, 0, kFusedDecodeKPW, 0, 0>, step_chain2_split_kernel<5, 0, kFusedDecodeKPW, 0, 1>,
+        step_chain2_split_kernel<5, 1, kFusedDecodeKPW, 0, 0>, step_chain2_split_kernel<5, 1, kFusedDecodeKPW, 0, 1>,
+        step_chain2_split_kernel<8, 0, kFusedDecodeKPW, 1, 0>, step_chain2_split_kernel<8, 0, kFusedDecodeKPW, 1, 1>,
+        step_chain2_split_kernel<8, 1, kFusedDecodeKPW, 1, 0>, step_chain2_split_kernel<8, 1, kFusedDecodeKPW, 1, 1>,
+        step_chain2_split_kernel<5, 0, kFusedDecodeKPW, 1, 0>, step_chain2_split_kernel<5, 0, kFusedDecodeKPW, 1, 1>,
+        step_chain2_split_kernel<5, 1, kFusedDecodeKPW, 1, 0>, step_chain2_split_kernel<5, 1, kFusedDecodeKPW, 1, 1>};
     if (!p0) {                             // configuration call (create time)
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < 16; ++i)
             if (hipFuncSetAttribute(reinterpret_cast<const void*>(kerns[i]), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     int(kFusedDecodeRedBytes + size_t(kFusedDecodeMaxZBytes))) != hipSuccess)
                 return TN_ERR_HIP;
@@ -2568,7 +2572,7 @@ int launch_chain2_split(const Chain2SplitArgs* p0, const Chain2SplitArgs* p1, hi
     const uint32_t most = std::max(p0->col_blocks, q.col_blocks), all = p0->col_blocks + (p1 ? p1->col_blocks : 0);
     const uint32_t per = (all + kFusedDecodeWorkgroups - 1) / kFusedDecodeWorkgroups, blocks = (most + per - 1) / per;
     const size_t smem = kFusedDecodeRedBytes + size_t(std::max(p0->z_bytes, q.z_bytes));
-    hipLaunchKernelGGL(kerns[p0->kern], dim3(blocks, p1 ? 2 : 1), dim3(512), smem, st, p0->c, p0->a, p0->z_bytes, q.c, q.a,
+    hipLaunchKernelGGL(kerns[2 * p0->kern + (per > 1 ? 1 : 0)], dim3(blocks, p1 ? 2 : 1), dim3(512), smem, st, p0->c, p0->a, p0->z_bytes, q.c, q.a,
                        q.z_bytes);
     return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
