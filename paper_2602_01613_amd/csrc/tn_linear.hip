@@ -73,6 +73,7 @@ struct DevStep {
     void* chain_bbf = nullptr;    // chain2: the next step's packed tensor in the chained layout
     int chain_cfg = 0;            // chain2 instantiation: 0 <3,6,5>, 1 <2,8,2>, 2 <2,5,2>; 3: none, only pair_cfg
     int pair_cfg = -1;            // instantiation of the kernels with a workgroup to a token (factor_pair_configs), -1: none
+    int64_t pair_gap[2] = {0, 0}; // calls of more tokens than the first and fewer than the second are left to step_chain2_kernel
     int chain_run_c1 = 0;         // chain2: output pieces run along c1 (else along c2)
     void* q4_codes = nullptr;     // 4-bit stream of the tensor for decode-size launches (codes, then block scales)
     void* q4_scales = nullptr;
@@ -2289,6 +2290,8 @@ struct FactorPairConfig {
     int per_cu;                            // workgroups on a compute unit
     factor_pair_t kern;
     size_t smem;
+    // multiply-adds of a token, padding included, for each workgroup that a compute unit holds
+    int64_t work() const { return int64_t(A) * Q * (in ? B + P : P + B) / per_cu; }
 };
 
 template <int A32, int B32, int P32, int Q32>
@@ -2300,7 +2303,7 @@ constexpr FactorPairConfig factor_out_config() {
     return {false, 32 * A32, 32 * B32, 32 * P32, 32 * Q32, A32 < 5 ? 3 : 2, factor_out_kernel<A32, B32, P32, Q32>, factor_out_smem<A32, B32, P32, Q32>()};
 }
 
-// Modes of up to 64 x 96, 64 x 128 and 160 x 160; the one of the least LDS that holds a pair is taken.
+// Modes of up to 64 x 96, 64 x 128 and 160 x 160.
 constexpr int kFactorPairConfigs = 12;
 const FactorPairConfig* factor_pair_configs() {
     static const FactorPairConfig c[kFactorPairConfigs] = {
@@ -2324,23 +2327,51 @@ bool is_factor_pair(const tn::Step& s, const tn::Step& u) {
     return strides(s.crow, 1) && strides(s.ccol, s.R) && strides(u.crow, u.C) && strides(u.ccol, 1);
 }
 
+// The form that holds a pair with the least work; of two alike, on the way out the one that stores whole rows where there is much to store. us of a
+// layer of one such pair at 8192 tokens, so / by the least LDS, which all forms of 160 x 160 share: out-factors 80 x 80 from ranks of 32 49 / 94,
+// 96 x 96 from ranks of 48 68 / 108, 64 x 64 from ranks of 16 28 / 34.
 int factor_pair_config(const tn::Step& s, const tn::Step& u) {
     if (!is_factor_pair(s, u)) return -1;
+    const bool out = s.R * s.K < s.C * u.C;
     int best = -1;
     for (int i = 0; i < kFactorPairConfigs; ++i) {
         const FactorPairConfig& c = factor_pair_configs()[i];
         if (!(c.in ? s.R <= c.A && s.K <= c.B && u.C <= c.P && s.C <= c.Q : s.C <= c.A && u.C <= c.B && s.K <= c.P && s.R <= c.Q)) continue;
-        if (best < 0 || c.smem < factor_pair_configs()[best].smem) best = i;
+        const FactorPairConfig* b = best < 0 ? nullptr : &factor_pair_configs()[best];
+        if (!b || c.work() < b->work() || (c.work() == b->work() && b->in && !c.in && out && 2 * s.C * u.C > int64_t(c.A) * c.B)) best = i;
     }
     return best;
 }
 
+// Where step_chain2_kernel holds a pair too, with a wave to a token and no padding of small extents, it is the faster one for many tokens where the
+// ranks are no more than 32 on the way in (K up to 96), or a mode is on the way out: from more than a round of two workgroups on a
+// compute unit, and for ever unless the modes fill half of the form. us of a layer of one such pair there / here at 512, 1000, 2000 and 8192
+// tokens: in-factors 64 x 80 to ranks of 32 10.0 / 10.2, 10.7 / 11.4, 14.9 / 14.9, 31 / 29; 80 x 80 to 16 8.2 / 8.5, 8.5 / 10.7, 15.3 / 16.9, 38 / 43;
+// 48 x 48 to 32 10.0 / 10.2, 10.6 / 11.3, 14.1 / 14.8, 25.7 / 26.5; out-factors 32 x 32 from 16 7.1 / 7.2, 7.6 / 8.2, 11.3 / 11.6, 20.5 / 23.5. Not so: in-factors
+// 64 x 80 to ranks of 48 14.2 / 13.9, 18.2 / 16.9, 22.9 / 20.2, 45 / 38, and a K of 97 to 128 or larger out-modes whatever the ranks. Out-factors of
+// one small mode or from one small rank that are three quarters padding on a form of 160 x 160 stay there (128 x 64 from 96 and 32 at 128 and
+// 8192 tokens 8.8 / 9.8, 85 / 108; 160 x 32 from 48 and 16 at 16 and 200 28.9 / 30.0, 29.2 / 30.1 in a layer of in-factors 32 x 160). Over 98 pairs
+// of modes 32 to 160 and ranks 16 to 96.
+void share_factor_pair(DevStep* a, const tn::Step& u) {
+    const tn::Step& s = a->plan;
+    const FactorPairConfig& c = factor_pair_configs()[a->pair_cfg];
+    const bool in = s.R * s.K >= s.C * u.C, small = in ? a->chain_cfg != 1 && std::max(s.C, u.C) <= 32 : a->chain_cfg == 2 && std::min(s.C, u.C) <= 32;
+    const bool padding = 4 * (s.R * s.K * s.C + s.R * s.C * u.C) < c.work() * c.per_cu;
+    if (!in && padding && (a->chain_cfg == 1 || (small && c.A > 64))) a->pair_cfg = -1;
+    else if (small) {
+        a->pair_gap[0] = 512;
+        a->pair_gap[1] = 2 * (in ? s.R * s.K : s.C * u.C) > int64_t(c.A) * c.B ? 2048 : std::numeric_limits<int64_t>::max();
+    }
+}
+
 // Calls of more (token, 32 columns) items than step_chain2_fine_kernel takes, which spreads a token over several compute units: below,
-// that is what counts (ranks of 96 to 160 x 160, one token: 4.5 us there, 5.4 here).
+// that is what counts. us of a layer of one pair there / here: out-factors 160 x 160 from ranks of 96 at 8 tokens (40 items) 8.6 / 10.0, at 16
+// 11.2 / 10.2; 128 x 128 from 96 at 16 (64 items) 8.9 / 10.1, at 32 12.1 / 11.1; in-factors 96 x 96 to 64 at 32 (64 items) 12.4 / 13.3, at 64 16.0 / 15.7.
 constexpr int64_t kChain2FineMaxItems = 64;      // (token, c1 tile) items up to which every c2 tile gets a wave of its own
 
 bool factor_pair_applies(const DevStep& s1, int64_t tokens) {
-    return s1.pair_cfg >= 0 && (s1.chain_cfg == 3 || tokens * ((s1.plan.C + 31) / 32) > kChain2FineMaxItems);
+    if (s1.pair_cfg < 0 || s1.chain_cfg == 3) return s1.pair_cfg >= 0;
+    return tokens * ((s1.plan.C + 31) / 32) > kChain2FineMaxItems && (tokens <= s1.pair_gap[0] || tokens >= s1.pair_gap[1]);
 }
 
 FactorPairArgs factor_pair_args(const DevStep& s1, const DevStep& s2, const void* in, void* out, int64_t tokens) {
@@ -2406,7 +2437,11 @@ int plan_chain2(tn_linear_s* h, hipStream_t st) {
         const DevStep& b = h->steps[i + 1];
         if (a.variant == VAR_SCALAR || b.variant == VAR_SCALAR || (!a.fuse_next && (b.fuse_next || (i > 0 && h->steps[i - 1].fuse_next)))) continue;
         a.pair_cfg = factor_pair_config(a.plan, b.plan);
-        if (a.fuse_next || a.pair_cfg < 0) continue;
+        if (a.pair_cfg < 0) continue;
+        if (a.fuse_next) {
+            share_factor_pair(&a, b.plan);
+            continue;
+        }
         a.fuse_next = true;
         a.chain_cfg = 3;
     }

@@ -374,3 +374,16 @@ def test_slices_on_chip_without_ranges(fake_hip):
     layers = [(wl.FORMAT_TR, 5120, 8192), (wl.FORMAT_TR, 25600, 5120), (wl.FORMAT_TT, 25600, 5120)]
     made = create_all(fake_hip, [job(wl.stack_spec(fmt, n, m, 96), 16, flags=tn.TN_FLAG_NO_SPLIT_K, tokens=(1, 2, 16)) for fmt, n, m in layers])
     assert [[call[0].kernel == "step_krondirect_kernel" for call in got["launches"]] for got in made] == [[False, True, True]] * 2 + [[False] * 3]
+
+
+def test_forms_of_the_factor_pair_tests(fake_hip):
+    """The layers of that GPU test: of the forms that hold a pair the one with the least work, and the calls that stay with a wave to a token."""
+    import workloads as wl
+    from test_gpu_factor_pairs import FORM_PAIRS
+    made = create_all(fake_hip, [job(wl.TNSpec(wl.FORMAT_TUCKER, "bf16", om, im, rk), 2100, tokens=(70, 600, 2100)) for om, im, rk, _ in FORM_PAIRS])
+    seen = set()
+    for (om, im, rk, want), got in zip(FORM_PAIRS, made):
+        used = [[(l.kernel[7:-7], *l.args) for l in call if l.kernel in ("factor_in_kernel", "factor_out_kernel")] for call in got["launches"]]
+        assert used == want, (om, im, rk, used)
+        seen |= {f for call in used for f in call}
+    assert len(seen) == 12

@@ -63,3 +63,35 @@ def test_factor_pairs_of_two_layers(case):
         assert np.array_equal(to_host(ya), to_host(a(x))) and np.array_equal(to_host(yb), to_host(b(x)))
         a.close()
         b.close()
+
+
+# out-modes, in-modes, ranks; the forms (side, A, B, P, Q / 32) that 70, 600 and 2100 tokens take: each is held to them by test_create_host.py, and all
+# twelve are among them
+FORM_PAIRS = [((80, 64), (64, 64), (48, 32, 48, 64), [[("in", 2, 4, 2, 3)]] * 3),
+              ((64, 64), (80, 64), (32, 32, 48, 16), [[("out", 2, 3, 2, 3), ("out", 2, 3, 2, 2)]] * 3),
+              ((80, 80), (64, 80), (32, 32, 48, 48), [[("in", 2, 3, 2, 2), ("out", 5, 5, 1, 1)]] * 3),
+              ((160, 160), (64, 128), (96, 96, 48, 16), [[("in", 2, 4, 2, 2), ("out", 5, 5, 3, 3)]] * 3),
+              ((64, 128), (160, 160), (48, 48, 16, 96), [[("out", 2, 4, 2, 3)]] * 3),
+              ((16, 16), (160, 160), (16, 16, 96, 96), [[("in", 5, 5, 3, 3)]] * 3),
+              ((112, 96), (128, 128), (48, 48, 32, 16), [[("in", 5, 5, 1, 1)]] * 3),
+              ((112, 112), (48, 112), (48, 48, 16, 32), [[("out", 5, 5, 2, 2)]] * 3),
+              ((64, 80), (112, 112), (32, 32, 64, 64), [[("in", 5, 5, 2, 2), ("out", 2, 3, 2, 2)]] * 3),
+              # between 512 and 2048 tokens, or from 512 on, the small ones are a wave's; out-factors from one wide rank always
+              ((160, 160), (64, 80), (32, 32, 32, 32), [[("in", 2, 3, 2, 2), ("out", 5, 5, 1, 1)], [("out", 5, 5, 1, 1)], [("in", 2, 3, 2, 2), ("out", 5, 5, 1, 1)]]),
+              ((32, 32), (80, 80), (16, 16, 16, 16), [[("in", 5, 5, 1, 1), ("in", 2, 3, 2, 2)], [], []]),
+              ((128, 64), (16, 16), (96, 32, 16, 16), [[], [], []])]
+
+
+@pytest.mark.parametrize("case", range(len(FORM_PAIRS)))
+def test_forms_of_factor_pairs(case):
+    """As test_factor_pairs, for each form of the two kernels and at the edges of the counts that they take."""
+    om, im, rk, _ = FORM_PAIRS[case]
+    spec = wl.TNSpec(wl.FORMAT_TUCKER, "bf16", om, im, rk)
+    rng = np.random.default_rng(560 + case)
+    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(max(1, s[-1])), "bf16") for s in spec.tensor_shapes()]
+    for tokens in (70, 600, 2100):
+        x = wl.round_to_dtype(np.random.default_rng(case * 7 + tokens).standard_normal((tokens, spec.N)), "bf16")
+        y = run_layer(spec, ts, x, max_tokens=2100)
+        assert O.rel_max_err(y, run_layer(spec, ts, x, flags=tn.TN_FLAG_NO_CHAIN2, max_tokens=2100)) <= 1e-2, (case, tokens)
+        if tokens < 100:
+            assert O.rel_max_err(y, O.forward(spec.format, ts, x, n_out_modes=len(om))) <= TOL["bf16"], (case, tokens)
