@@ -690,9 +690,9 @@ __global__ void __launch_bounds__(64) step_chain2_fine_kernel(Chain2Args c0, Cha
 // A workgroup walks column blocks blockIdx.x, + gridDim.x, ... with the next block's pieces requested as the present one's are
 // multiplied: its registers leave room for one workgroup on a CU, and with a block each, the two layers' 2 x 288 blocks of the Tucker
 // pair 5120 -> 25600 of rank 96 were 2.25 rounds of workgroups that each started with the pair's result and an empty pipeline. us per
-// call over cold copies, a block each / so: that pair at one token 27.9 / 24.6, one layer 20.0 / 18.2, the pair in 4 bits 18.0 / 15.7.
-// WALK: some workgroup has more than one block; without, in line (a branch between the products of the pieces cost the last block 0.2 us of
-// 5 to 8). KPW: pieces of 64 k per wave. Q4: the wide step's tensor is read in its 4-bit form (see q4_stream_pack_kernel), one
+// call, a block each / so: that pair at one token 23.9 / 20.3; over cold copies one layer 20.0 / 18.2, the pair in 4 bits 18.0 / 15.7.
+// WALK: some workgroup has more than one block; without, in line (the branch between the products of two pieces costs a call of a block each
+// 0.2 us of 5 to 8). KPW: pieces of 64 k per wave. Q4: the wide step's tensor is read in its 4-bit form (see q4_stream_pack_kernel), one
 // 16-byte load of codes and one scale byte per lane and piece instead of four fragment loads.
 template <int K1S, int RUN_C1, int KPW, int Q4, int WALK>
 __global__ void __launch_bounds__(512) step_chain2_split_kernel(Chain2Args c0, StepArgs a0, int z_bytes0, Chain2Args c1,
@@ -750,7 +750,8 @@ __global__ void __launch_bounds__(512) step_chain2_split_kernel(Chain2Args c0, S
     //         they are multiplied. Lane l supplies token l%32, k = 16*ks + 8*(l/32) .. +7 from the LDS buffer
     const bool tv = lrow < int(a.total_rows);
     const bf16_t* zrow = z + int64_t(tv ? lrow : 0) * a.a_tok_stride + (Q4 ? 32 : 8) * lhalf;
-    auto block = [&](auto walk, int now) {
+    for (;;) {
+        const int next = cb + int(gridDim.x);
         floatx16 acc;
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] = 0.f;
@@ -773,7 +774,7 @@ __global__ void __launch_bounds__(512) step_chain2_split_kernel(Chain2Args c0, S
                     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[ks], x, acc, 0, 0, 0);
                 }
             }
-            if constexpr (decltype(walk)::value) request(u, now + int(gridDim.x));
+            if (WALK && next < n_cb) request(u, next);
         }
 #pragma unroll
         for (int v = 0; v < 16; ++v) red[(wave * 16 + v) * 64 + lane] = acc[v];
@@ -785,17 +786,13 @@ __global__ void __launch_bounds__(512) step_chain2_split_kernel(Chain2Args c0, S
 #pragma unroll
             for (int w = 0; w < NW; ++w) sum += red[w * 1024 + e];
             const uint32_t g = uint32_t(l & 31);
-            const int col = now * 32 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
+            const int col = cb * 32 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
             if (g >= a.total_rows || col >= a.C) continue;
             Out[int64_t(g) * a.c_tok_stride + a.crow[0] + a.ccol[col]] = bf16_t(sum);
         }
-    };
-    if constexpr (WALK) {
-        for (; cb + int(gridDim.x) < n_cb; cb += int(gridDim.x)) {
-            block(std::true_type(), cb);
-            __syncthreads();                                               // the sums have been read
-        }
+        if (!WALK || next >= n_cb) break;
+        cb = next;
+        __syncthreads();                                                   // the sums have been read
     }
-    block(std::false_type(), cb);
 }
 
