@@ -54,7 +54,14 @@ struct SourceArgs {
     int64_t rstr[tn::kMaxGatherDims], kstr[tn::kMaxGatherDims];
 };
 
-__global__ void __launch_bounds__(256) operand_source_kernel(SourceArgs p) {
+// Up to kSourceMany of them in one launch, blockIdx.y says which: a layer has four to a dozen, a few KB to a few MB each.
+constexpr int kSourceMany = 8;
+struct SourceMany {
+    SourceArgs s[kSourceMany];
+};
+
+__global__ void __launch_bounds__(256) operand_source_kernel(SourceMany m) {
+    const SourceArgs& p = m.s[blockIdx.y];
     const int64_t total = p.Rp * p.Kp;
     for (int64_t i = int64_t(blockIdx.x) * 256 + threadIdx.x; i < total; i += int64_t(gridDim.x) * 256) {
         const int64_t r = i / p.Kp, k = i - r * p.Kp;

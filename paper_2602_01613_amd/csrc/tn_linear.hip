@@ -179,6 +179,7 @@ struct tn_linear_s {
     size_t mat_kept_count = 0;                // of mat_kept: those of the forward order, which come first
     int64_t mat_kept_bytes = 0;
     std::vector<void*> mat_kept;              // operands made from the caller's tensors, and the tables
+    std::vector<SourceArgs> create_sources;   // operands that are still to be written (create time)
     std::vector<std::vector<int32_t>> create_tables;     // host copies of tables on their way to the GPU, until create's last wait
     // the plan of that order, made once and used by the two prepare functions; cleared when create ends
     struct MatrixPlans {
@@ -1821,8 +1822,8 @@ bool matrix_plan_of(tn_linear_s* h, const tn_linear_desc* desc) {
     return p.ok;
 }
 
-// An operand kept for the products: allocated, written on `st`, freed with the handle.
-int keep_operand(tn_linear_s* h, const tn_linear_desc* desc, const tn::SourceOp& o, int64_t Kp, bool packed, void** out, hipStream_t st,
+// An operand kept for the products: allocated, freed with the handle, written by the next write_operands.
+int keep_operand(tn_linear_s* h, const tn_linear_desc* desc, const tn::SourceOp& o, int64_t Kp, bool packed, void** out,
                  std::vector<void*>* owner = nullptr) {
     SourceArgs a;
     memset(&a, 0, sizeof(a));
@@ -1850,8 +1851,25 @@ int keep_operand(tn_linear_s* h, const tn_linear_desc* desc, const tn::SourceOp&
     h->packed_bytes += n * int64_t(sizeof(bf16_t));
     a.src = static_cast<const bf16_t*>(desc->tensors[o.slot]);
     a.dst = static_cast<bf16_t*>(dst);
-    hipLaunchKernelGGL(operand_source_kernel, dim3(uint32_t(std::min<int64_t>((n + 255) / 256, 65536))), dim3(256), 0, st, a);
+    h->create_sources.push_back(a);
     *out = dst;
+    return TN_OK;
+}
+
+// The operands asked for since the last time, on `st`.
+int write_operands(tn_linear_s* h, hipStream_t st) {
+    for (size_t i = 0; i < h->create_sources.size(); i += kSourceMany) {
+        const size_t n = std::min<size_t>(kSourceMany, h->create_sources.size() - i);
+        SourceMany m;
+        memset(&m, 0, sizeof(m));
+        int64_t most = 0;
+        for (size_t j = 0; j < n; ++j) {
+            m.s[j] = h->create_sources[i + j];
+            most = std::max(most, m.s[j].Rp * m.s[j].Kp);
+        }
+        hipLaunchKernelGGL(operand_source_kernel, dim3(uint32_t(std::min<int64_t>((most + 255) / 256, 65536)), uint32_t(n)), dim3(256), 0, st, m);
+    }
+    h->create_sources.clear();
     return hipGetLastError() == hipSuccess ? TN_OK : TN_ERR_HIP;
 }
 
@@ -1920,9 +1938,9 @@ int prepare_lazy(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
             p.s.crow = h->lazy_tables + at[4 + 2 * w];
             p.s.ccol = h->lazy_tables + at[5 + 2 * w];
             void* a = nullptr;
-            int rc = keep_operand(h, desc, sp.half[w].a, sp.half[w].Kp, false, &a, st, &h->lazy_sources);
+            int rc = keep_operand(h, desc, sp.half[w].a, sp.half[w].Kp, false, &a, &h->lazy_sources);
             p.a = a;
-            if (rc == TN_OK) rc = keep_operand(h, desc, sp.half[w].b, sp.half[w].Kp, true, &p.s.packed, st, &h->lazy_sources);
+            if (rc == TN_OK) rc = keep_operand(h, desc, sp.half[w].b, sp.half[w].Kp, true, &p.s.packed, &h->lazy_sources);
             if (rc != TN_OK) return rc;
         }
         d.x_vec8 = sp.x_vec8;
@@ -2059,7 +2077,7 @@ int prepare_direct(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
     for (int w = 0; w < 2; ++w)
         for (int side = 0; side < 2; ++side) {
             void* p = nullptr;
-            const int rc = keep_operand(h, desc, d.src[w][side], 32 * d.steps, true, &p, st, &h->lazy_sources);
+            const int rc = keep_operand(h, desc, d.src[w][side], 32 * d.steps, true, &p, &h->lazy_sources);
             if (rc != TN_OK) return rc;
             a.src[w][side] = p;
             a.tiles[w][side] = int32_t(d.tiles[w][side]);
@@ -2236,14 +2254,14 @@ int prepare_matrix(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t st) {
         int rc;
         void* p = nullptr;
         if (!h->mat_build[i]) {
-            rc = keep_operand(h, desc, H.keep, m.Krp, i == 1, &p, st);
+            rc = keep_operand(h, desc, H.keep, m.Krp, i == 1, &p);
             if (i == 0) h->mat_w.a = p;
             else h->mat_w.s.packed = p;
         } else {
             set_tables(&h->mat_half[i].s, 2 * i);
-            rc = keep_operand(h, desc, H.build.a, H.build.Kp, false, &p, st);
+            rc = keep_operand(h, desc, H.build.a, H.build.Kp, false, &p);
             h->mat_half[i].a = p;
-            if (rc == TN_OK) rc = keep_operand(h, desc, H.build.b, H.build.Kp, true, &h->mat_half[i].s.packed, st);
+            if (rc == TN_OK) rc = keep_operand(h, desc, H.build.b, H.build.Kp, true, &h->mat_half[i].s.packed);
         }
         if (rc != TN_OK) return rc;
     }
@@ -3359,14 +3377,14 @@ int prepare_matrix_grad(tn_linear_s* h, const tn_linear_desc* desc, hipStream_t 
         const tn::MatrixGradHalf& G = g.half[i];
         int rc;
         if (!H.pair) {
-            rc = keep_operand(h, desc, G.op_keep, G.op_keep.K, true, &H.op.s.packed, st);
+            rc = keep_operand(h, desc, G.op_keep, G.op_keep.K, true, &H.op.s.packed);
         } else {
             void* a = nullptr;
-            rc = keep_operand(h, desc, G.op.a, G.op.Kp, false, &a, st);
+            rc = keep_operand(h, desc, G.op.a, G.op.Kp, false, &a);
             H.op.a = a;
-            if (rc == TN_OK) rc = keep_operand(h, desc, G.op.b, G.op.Kp, true, &H.op.s.packed, st);
-            if (rc == TN_OK) rc = keep_operand(h, desc, G.a, tn::detail::round64(G.F1), true, &H.a, st);
-            if (rc == TN_OK) rc = keep_operand(h, desc, G.b, G.F2, true, &H.b, st);
+            if (rc == TN_OK) rc = keep_operand(h, desc, G.op.b, G.op.Kp, true, &H.op.s.packed);
+            if (rc == TN_OK) rc = keep_operand(h, desc, G.a, tn::detail::round64(G.F1), true, &H.a);
+            if (rc == TN_OK) rc = keep_operand(h, desc, G.b, G.F2, true, &H.b);
         }
         if (rc != TN_OK) return rc;
     }
@@ -3856,11 +3874,14 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
         const int64_t before = h->packed_bytes;
         rc = prepare_lazy(h, desc, st);
         if (rc == TN_OK) rc = prepare_direct(h, desc, st);
+        if (rc == TN_OK) rc = write_operands(h, st);
         h->lazy_kept_bytes = h->packed_bytes - before;
     }
     if (rc == TN_OK) {
         const int64_t before = h->packed_bytes;
         rc = prepare_matrix(h, desc, st);
+        if (rc == TN_OK) rc = write_operands(h, st);
+        h->create_sources.clear();
         h->mat_kept_count = h->mat_kept.size();
         h->mat_kept_bytes = h->packed_bytes - before;
         if (rc == TN_OK && h->matrix && !desc->workspace && hipMalloc(&h->mat_mem, size_t(h->mat_bytes)) != hipSuccess) {
@@ -3871,6 +3892,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
     }
     if (rc == TN_OK && (desc->flags & TN_FLAG_TRAINABLE)) {
         rc = prepare_matrix_grad(h, desc, st);
+        if (rc == TN_OK) rc = write_operands(h, st);
         if (rc == TN_OK) rc = prepare_backward(h, desc, st);
     }
     if (rc != TN_OK) {
@@ -4063,6 +4085,7 @@ int tn_linear_create(tn_linear_t* out, const tn_linear_desc* desc_in) {
     for (void* v : h->create_temps) (void)hipFree(v);
     h->create_temps.clear();
     h->create_tables = {};
+    h->create_sources = {};
     h->matrix_plans = {};
     *out = h;
     return TN_OK;

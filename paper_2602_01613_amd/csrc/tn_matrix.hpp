@@ -787,15 +787,30 @@ inline bool make_direct_plan(const Plan& net, const int (&tensors)[2][2], Direct
         // o = (rows' m, columns' m), k or a = (columns' n, rows' n)
         const int64_t O = row.M * col.M, K = row.N * col.N, k_steps = w == 0 ? g[1] : (g[0] + 1) / 2;
         std::vector<int32_t>&y = w == 0 ? out->yrow : out->ycol, &x = w == 0 ? out->xcol : out->xrow;
-        for (int64_t o = 0; o < O; ++o) y.push_back(int32_t(o / col.M * x_stride(net.y_idx, row.m) + o % col.M * x_stride(net.y_idx, col.m)));
-        for (int64_t k = 0; k < K; ++k) x.push_back(int32_t(k / row.N * x_stride(net.x_idx, col.n) + k % row.N * x_stride(net.x_idx, row.n)));
-        const int64_t tr = row.M * row.N / 16, tc = col.M * col.N / 16;
-        for (int64_t r = 0; r < tr; ++r)
-            for (int64_t c = 0; c < tc; ++c)
-                for (int64_t l = 0; l < 64; ++l) {
-                    const int64_t fr = 16 * r + 4 * (l / 16), fc = 16 * c + l % 16;
-                    const int64_t o = fr / row.N * col.M + fc % col.M, k = fc / col.M * row.N + fr % row.N;
-                    out->unit[w].push_back(uint16_t(direct_position(w, o, k, k_steps) / 8));
+        std::vector<uint32_t> at_o, at_k;               // a position is o's share and k's
+        const int64_t y_row = x_stride(net.y_idx, row.m), y_col = x_stride(net.y_idx, col.m), x_row = x_stride(net.x_idx, row.n), x_col = x_stride(net.x_idx, col.n);
+        for (int64_t o = 0; o < O; ++o) {
+            y.push_back(int32_t(o / col.M * y_row + o % col.M * y_col));
+            at_o.push_back(uint32_t(direct_position(w, o, 0, k_steps) / 8));
+        }
+        for (int64_t k = 0; k < K; ++k) {
+            x.push_back(int32_t(k / row.N * x_col + k % row.N * x_row));
+            at_k.push_back(uint32_t(direct_position(w, 0, k, k_steps) / 8));      // (four k from a multiple of 4 on are 8 bytes)
+        }
+        const uint32_t rows = uint32_t(row.M * row.N), cols = uint32_t(col.M * col.N);
+        std::vector<uint32_t> col_o, col_k;
+        for (uint32_t n = 0; n < uint32_t(col.N); ++n)
+            for (uint32_t m = 0; m < uint32_t(col.M); ++m) {
+                col_o.push_back(m);
+                col_k.push_back(n * uint32_t(row.N));
+            }
+        out->unit[w].resize(size_t(rows / 16) * (cols / 16) * 64);
+        uint16_t* unit = out->unit[w].data();
+        for (uint32_t r = 0; r < rows; r += 16)
+            for (uint32_t c = 0; c < cols; c += 16)
+                for (uint32_t fr = r; fr < r + 16; fr += 4) {
+                    const uint32_t *o = &at_o[fr / uint32_t(row.N) * uint32_t(col.M)], *k = &at_k[fr % uint32_t(row.N)];
+                    for (uint32_t fc = c; fc < c + 16; ++fc) *unit++ = uint16_t(o[col_o[fc]] + k[col_k[fc]]);
                 }
         (w == 0 ? out->O1 : out->C1) = O;
         (w == 0 ? out->K0 : out->A) = K;

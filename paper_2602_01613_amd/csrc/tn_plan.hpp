@@ -375,9 +375,11 @@ inline std::vector<int32_t> offset_table(const std::vector<int>& ids, const std:
     std::vector<int32_t> tab(static_cast<size_t>(total), 0);
     std::vector<int64_t> digit(ids.size(), 0);
     int64_t off = 0;
-    for (int64_t f = 0; f < total; ++f) {
-        tab[size_t(f)] = int32_t(off);
-        for (int j = int(ids.size()) - 1; j >= 0; --j) {
+    const int last = int(ids.size()) - 1;
+    const int64_t run = last < 0 ? 1 : ext[ids[last]], step = last < 0 ? 0 : st[last];
+    for (int64_t f = 0; f < total; f += run) {
+        for (int64_t d = 0; d < run; ++d) tab[size_t(f + d)] = int32_t(off + d * step);
+        for (int j = last - 1; j >= 0; --j) {
             off += st[j];
             if (++digit[j] < ext[ids[j]]) break;
             off -= st[j] * ext[ids[j]];
@@ -708,8 +710,9 @@ inline bool kron_shape(const Plan& p, KronDims* d) {
     if (s0.C > (int64_t(1) << 30) || s1.K > (int64_t(1) << 30)) return false;
     for (int64_t r = 0; r < A; ++r)
         if (s0.crow[size_t(r)] != r * P) return false;
-    for (int64_t c = 0; c < s0.C; ++c)
-        if (s0.ccol[size_t(c)] != (c / P) * (A * P) + c % P) return false;
+    for (int64_t o = 0; o < O1; ++o)                    // (a division per entry would be most of a ring's create time)
+        for (int64_t q = 0; q < P; ++q)
+            if (s0.ccol[size_t(o * P + q)] != o * (A * P) + q) return false;
     bool x_vec8 = true;             // 8 consecutive k of one a are one aligned 16-byte piece of x
     if (!s0.a_plain) {
         for (int64_t r = 0; r < A; ++r)

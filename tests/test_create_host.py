@@ -45,8 +45,8 @@ def layer(fmt, dtype, out_modes, in_modes, ranks, max_tokens, limit, flags, what
     res["scratch"] = [lib.tn_linear_forward_scratch(h, at, at + 256, t, None) for t in scratch_tokens] if rc == 0 else []
     grads = (ctypes.c_void_p * len(ptrs))(*[at + 512 if wanted is None or i in wanted else None for i in range(len(ptrs))])
     res["launches"], res["gradient_launches"] = [], []
+    res["create_launches"] = launches()
     if rc == 0:
-        launches()
         for t in tokens:
             assert lib.tn_linear_forward(h, at, at + 256, t, None) == 0
             res["launches"].append(launches())
@@ -387,3 +387,12 @@ def test_forms_of_the_factor_pair_tests(fake_hip):
         assert used == want, (om, im, rk, used)
         seen |= {f for call in used for f in call}
     assert len(seen) == 12
+
+
+def test_operands_of_a_layer_are_written_together(fake_hip):
+    """Layers in a shared block have the operands of the slices, in memory and on chip: eight, one launch."""
+    import workloads as wl
+    made = create_all(fake_hip, [job(wl.stack_spec(fmt, 5120, 8192, rank), 16, block_bytes=1 << 28) for fmt, rank in ((wl.FORMAT_TT, 32), (wl.FORMAT_TR, 96))])
+    for got in made:
+        written = [l for l in got["create_launches"] if "operand_source_kernel" in l[0]]
+        assert len(written) == 1, written
