@@ -565,7 +565,7 @@ struct GradOutMany {
 };
 
 template <int Y, int V>
-__global__ void __launch_bounds__(Y > 4 ? 64 * Y : 256) grad_reduce_many_kernel(GradOutMany m) {
+__global__ void __launch_bounds__(256) grad_reduce_many_kernel(GradOutMany m) {
     if (Y == 4 && m.o[blockIdx.y].n_split < 4) grad_reduce<1, V>(m.o[blockIdx.y]);      // no splits to share out
     else grad_reduce<Y, V>(m.o[blockIdx.y]);
 }

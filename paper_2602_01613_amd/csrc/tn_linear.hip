@@ -2551,7 +2551,6 @@ int launch_chain2(const tn_linear_s* h, const DevStep& s1, const DevStep& s2, co
 // split-K kernel with one split and 8 waves, its rows are the tokens themselves (R = 1), its K fits the kernel's
 // register budget and every (token, column tile) item of the pair gets a wave of its own.
 constexpr int64_t kFusedDecodeMaxZBytes = 32 * 1024;
-constexpr uint32_t kFusedDecodeWorkgroups = 256;
 constexpr size_t kFusedDecodeRedBytes = 8 * 1024 * sizeof(float);
 constexpr int kFusedDecodeKPW = 5;           // pieces of 64 k of the wide step per wave: K <= 8 * 5 * 64 = 2560
 
@@ -2602,7 +2601,7 @@ Chain2SplitArgs chain2_split_args(const DevStep& s1, const DevStep& s2, const De
 }
 
 // One launch for one layer (p1 == nullptr) or for two layers on the same instantiation (grid.y = 2).
-int launch_chain2_split(const Chain2SplitArgs* p0, const Chain2SplitArgs* p1, hipStream_t st) {
+int launch_chain2_split(const tn_linear_s* h, const Chain2SplitArgs* p0, const Chain2SplitArgs* p1, hipStream_t st) {
     using k_t = void (*)(Chain2Args, StepArgs, int, Chain2Args, StepArgs, int);
     static const k_t kerns[16] = {                                  // a block to a workgroup, several
         step_chain2_split_kernel<8, 0, kFusedDecodeKPW, 0, 0>, step_chain2_split_kernel<8, 0, kFusedDecodeKPW, 0, 1>,
@@ -2623,7 +2622,7 @@ int launch_chain2_split(const Chain2SplitArgs* p0, const Chain2SplitArgs* p1, hi
     const Chain2SplitArgs& q = p1 ? *p1 : *p0;
     // one workgroup to a compute unit (registers), each with the same number of blocks where the layers are alike
     const uint32_t most = std::max(p0->col_blocks, q.col_blocks), all = p0->col_blocks + (p1 ? p1->col_blocks : 0);
-    const uint32_t per = (all + kFusedDecodeWorkgroups - 1) / kFusedDecodeWorkgroups, blocks = (most + per - 1) / per;
+    const uint32_t cus = uint32_t(h->num_cus), per = (all + cus - 1) / cus, blocks = (most + per - 1) / per;
     const size_t smem = kFusedDecodeRedBytes + size_t(std::max(p0->z_bytes, q.z_bytes));
     hipLaunchKernelGGL(kerns[2 * p0->kern + (per > 1 ? 1 : 0)], dim3(blocks, p1 ? 2 : 1), dim3(512), smem, st, p0->c, p0->a, p0->z_bytes, q.c, q.a,
                        q.z_bytes);
@@ -2703,7 +2702,7 @@ int configure_kernels(int device) {
     if (rc == TN_OK) rc = launch_pipe<4, 1, 2, 4, 1, 2>(none, a, 0, nullptr);
     if (rc == TN_OK) rc = configure_gemm();
     if (rc == TN_OK) rc = launch_chain2(no_handle, none, none, nullptr, nullptr, 0, nullptr);
-    if (rc == TN_OK) rc = launch_chain2_split(nullptr, nullptr, nullptr);
+    if (rc == TN_OK) rc = launch_chain2_split(nullptr, nullptr, nullptr, nullptr);
     for (int i = 0; i < kSkinnyKernels && rc == TN_OK; ++i)
         if (hipFuncSetAttribute(reinterpret_cast<const void*>(skinny_kernels()[i]), hipFuncAttributeMaxDynamicSharedMemorySize,
                                 int(kSplitLdsRowBytes)) != hipSuccess)
@@ -3093,12 +3092,11 @@ void launch_grad_reduce_many(const GradOutMany& m, int count, hipStream_t st) {
         pairs = pairs && o.K % 2 == 0 && o.ld % 2 == 0 && o.split_stride % 2 == 0;
     }
     using reduce_t = void (*)(GradOutMany);
-    static const reduce_t kerns[6] = {grad_reduce_many_kernel<1, 1>, grad_reduce_many_kernel<1, 2>, grad_reduce_many_kernel<4, 1>,
-                                      grad_reduce_many_kernel<4, 2>, grad_reduce_many_kernel<16, 1>, grad_reduce_many_kernel<16, 2>};
-    const int y = n_split >= 64 ? 2 : (n_split >= 16 ? 1 : 0);
+    static const reduce_t kerns[4] = {grad_reduce_many_kernel<1, 1>, grad_reduce_many_kernel<1, 2>, grad_reduce_many_kernel<4, 1>,
+                                      grad_reduce_many_kernel<4, 2>};
+    const int y = n_split >= 16 ? 1 : 0;                     // (up to 32: the matrix-product kernel's ranges of K)
     const int64_t per = (y ? 64 : 256) * (pairs ? 2 : 1);
-    hipLaunchKernelGGL(kerns[2 * y + (pairs ? 1 : 0)], dim3(uint32_t(std::min<int64_t>((most + per - 1) / per, 4096)), uint32_t(count)),
-                       dim3(y == 2 ? 1024 : 256), 0, st, m);
+    hipLaunchKernelGGL(kerns[2 * y + (pairs ? 1 : 0)], dim3(uint32_t(std::min<int64_t>((most + per - 1) / per, 4096)), uint32_t(count)), dim3(256), 0, st, m);
 }
 
 // dP of one step from dOut and the step's saved input, into the caller's tensor.
@@ -4193,7 +4191,7 @@ int forward_in(tn_linear_s* h, const Workspace& w, bool allow_lazy, const void* 
                 const tn::LaunchIO& l2 = h->schedule[li + 1];
                 void* Out2 = l2.out == tn::kBufY ? static_cast<void*>(yb + t0 * h->plan.M * h->elt) : w.ws[l2.out];
                 const Chain2SplitArgs fa = chain2_split_args(s, h->steps[size_t(l.first) + 1], h->steps[size_t(l.first) + 2], A, Out2, nt);
-                rc = launch_chain2_split(&fa, nullptr, st);
+                rc = launch_chain2_split(h, &fa, nullptr, st);
                 ++li;
             } else {
                 rc = l.steps == 2 ? launch_chain2(h, s, h->steps[size_t(l.first) + 1], A, Out, nt, st)
@@ -4282,7 +4280,7 @@ int tn_linear_forward2(tn_linear_t ha, tn_linear_t hb, const void* x, void* ya, 
                                           buffer(n, hs[n]->schedule[li].in), buffer(n, hs[n]->schedule[li + 1].out), tokens);
         }
         if (fuse[0] && fuse[1] && fa[0].kern == fa[1].kern) {
-            rc = launch_chain2_split(&fa[0], &fa[1], st);          // pair and wide step of both layers in one launch
+            rc = launch_chain2_split(ha, &fa[0], &fa[1], st);          // pair and wide step of both layers in one launch
             skip[0] = skip[1] = true;
         } else if (!skip[0] && !skip[1] && !fuse[0] && !fuse[1] && l.steps == 2 && factor_pair_applies(ha->steps[f], tokens) &&
                    factor_pair_applies(hb->steps[f], tokens) && ha->steps[f].pair_cfg == hb->steps[f].pair_cfg) {
@@ -4304,7 +4302,7 @@ int tn_linear_forward2(tn_linear_t ha, tn_linear_t hb, const void* x, void* ya, 
                     continue;
                 }
                 if (fuse[n]) {                     // e.g. only this layer qualifies, or only one streams its 4-bit form
-                    rc = launch_chain2_split(&fa[n], nullptr, st);
+                    rc = launch_chain2_split(hs[n], &fa[n], nullptr, st);
                     skip[n] = true;
                     continue;
                 }

@@ -389,6 +389,15 @@ def test_forms_of_the_factor_pair_tests(fake_hip):
     assert len(seen) == 12
 
 
+def test_reductions_of_the_odd_bond_tests(fake_hip):
+    import paper_2602_01613_amd as tn
+    from test_gpu_gradients import ODD_BONDS, ring_of_bond
+    rings = sorted(ODD_BONDS)
+    made = create_all(fake_hip, [job(ring_of_bond(*ring), 48, flags=tn.TN_FLAG_TRAINABLE, grad_tokens=(48,)) for ring in rings])
+    for ring, got in zip(rings, made):
+        assert [(l.args, l.grid[1]) for l in got["gradient_launches"][0] if l.kernel == "grad_reduce_many_kernel"] == [(ODD_BONDS[ring], 4)], ring
+
+
 def test_operands_of_a_layer_are_written_together(fake_hip):
     """Layers in a shared block have the operands of the slices, in memory and on chip: eight, one launch."""
     import workloads as wl

@@ -214,3 +214,21 @@ def test_core_gradients_in_little_room(n):
     layer.close()
     errs = _check(spec, ts, tokens, 91 + n, workspace_limit_bytes=limit)
     assert max(errs) <= 2.0 ** -13, errs
+
+
+# rings (second modes, inner bond), and the reduction (rows of threads to an element, elements a lane) of their cores' gradients: even bonds two a lane
+ODD_BONDS = {(8, 8, 62): (1, 2), (8, 8, 63): (1, 1), (16, 10, 31): (4, 1)}
+
+
+def ring_of_bond(m, n, inner):
+    return wl.TNSpec(wl.FORMAT_TR, "bf16", (8, m, 8, 8), (8, n, 8, 8), (16, inner, 16, inner, 16))
+
+
+@pytest.mark.parametrize("ring", sorted(ODD_BONDS))
+def test_core_gradients_of_odd_bonds(ring):
+    """Rows of an odd number of elements: added one to a lane."""
+    spec = ring_of_bond(*ring)
+    rng = np.random.default_rng(sum(ring))
+    ts = [wl.round_to_dtype(rng.standard_normal(s) / np.sqrt(s[0] * s[2]), "bf16") for s in spec.tensor_shapes()]
+    errs = _check(spec, ts, 48, 73 + sum(ring))
+    assert max(errs) <= 2.0 ** -13, errs
