@@ -113,7 +113,8 @@ extern "C" {
 #define TN_FLAG_NO_DECODE_FUSION (1 << 24) /* none of the forms kept for calls of a few tokens: a chained factor pair and the
                                        wide step after it as one launch (the in-factor products and the core of a Tucker
                                        layer), chained pairs on the kernels that request their operands up front, the
-                                       Kronecker-sum kernel with the four waves of a workgroup sharing one token */
+                                       Kronecker-sum kernel with the four waves of a workgroup sharing one token, and
+                                       its form that makes the slices of a lazily merged plan on chip */
 #define TN_FLAG_NO_Q4_STREAM (1 << 27)   /* a TN_FLAG_QUANT_MXFP4 layer never reads the 4-bit form in its kernels: every call
                                        multiplies with the bf16 copies of the dequantised tensors */
 #define TN_FLAG_NO_SKINNY (1 << 28)      /* never run a launch of 5 to 64 rows on the kernel that keeps the rows in LDS and
@@ -150,7 +151,8 @@ extern "C" {
                                            such calls run that one launch on its tensors, rebuilt in the workspace
                                            from the caller's compact ones (microseconds): per call when the
                                            workspace is a caller's block shared with other layers, once at create
-                                           when it is the handle's own; 1 since the kernel has a one-token form */
+                                           when it is the handle's own (a few tokens: made on chip instead, where that is
+                                       priced lower); 1 since the kernel has a one-token form */
 #define TN_QUERY_LAZY_FLOPS_PER_TOKEN 13 /* handle only: FLOPs per token of that plan (0 if none) */
 #define TN_QUERY_BACKWARD_CHUNK_TOKENS 14 /* handle only: tokens per pass of tn_linear_param_gradients (0: not trainable) */
 #define TN_QUERY_BACKWARD_WORKSPACE_BYTES 15 /* handle only: device memory held for those passes */

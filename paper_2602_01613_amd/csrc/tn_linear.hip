@@ -102,7 +102,9 @@ struct DirectGeom {
     float us = 0.f;
     bool taken = false;       // the price is below that of the slices in memory
 };
-constexpr int64_t kDirectMaxTokens = 16;      // the price grows with the token: rings of rank 32 pay up to here, of rank 96 up to 3 tokens
+// Prices are kept for calls of up to this many tokens. Below it they decide: of a decoder's projections, rings of rank 96 are taken at one token in a
+// workspace of their own and up to 2 to 4 in a shared one, of rank 32 up to 2 to 8 and 8 to 16; trains of rank 32 all the way.
+constexpr int64_t kDirectMaxTokens = 16;
 
 struct tn_linear_s {
     tn::Plan plan;
